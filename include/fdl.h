@@ -101,10 +101,9 @@ FDL_API fdl_status fdl_forward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * GPU, held from the moment the library is loaded there until the process ends).  The call allocates and frees
  * nothing; the first call on a GPU looks up the array's device address (a host-side query, no stream work).
  *
- * Limit: problems whose forward scratch exceeds the array are rejected with FDL_ERR_WORKSPACE before any device
- * call.  The forward scratch is 8 bytes per (row, column tile) of partial row statistics - none on the bf16 path
- * with K % 128 == 0, N % 256 == 0, N <= 8192, M >= 128, which normalises without partials - plus 512 K bytes when
- * that path sees a ragged M.  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
+ * Limit: problems that need more than the array holds are rejected with FDL_ERR_WORKSPACE before any device call.  What
+ * counts is the forward scratch plus 8 bytes per (row, column tile of 64 or 128) - nothing for the latter on the bf16
+ * path with K % 128 == 0, N % 256 == 0, N <= 8192, M >= 128.  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
  * one GPU (different streams, different host threads) race: order them on one stream or with events.
  */
 #define FDL_STATIC_SCRATCH_BYTES (16 * 1024 * 1024)
@@ -145,8 +144,7 @@ FDL_API fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * Forward pass for inference (the paper's experiments are mostly forward kernels: section "Optimizing individual
  * operations", task table of the robust kernel benchmark): Y as fdl_forward computes it, and nothing saved for a
  * backward pass.  The pre-activation passes through Y itself and is normalised in place, so the workspace holds no
- * M x N tensor: row statistics, partial statistics where the contraction emits them, and for batches of 16384 rows
- * and more on the tuned bf16 kernels a transposed copy of W (2 N K bytes):
+ * M x N tensor: row statistics, and for batches of 16384 rows and more on the tuned bf16 kernels a transposed copy of W (2 N K bytes):
  * fdl_forward_inference_workspace_bytes bytes (0 for an invalid dtype or shape), 256-byte aligned.
  * in : X [M,K], W [N,K] (dt);  b, gamma, beta [N] fp32;  eps >= 0.     out: Y [M,N] (dt).
  */

@@ -32,56 +32,11 @@ template <> __device__ __forceinline__ bf16_t to_storage<bf16_t, float>(float v)
 template <> __device__ __forceinline__ bf16_t to_storage<bf16_t, double>(double v) { return (bf16_t)(float)v; }
 
 // ---------------------------------------------------------------------------------------------
-// Standard normal CDF Phi and density phi, the two pieces of GELU_erf and its derivative:
+// The normal distribution's CDF Phi and density phi are the two pieces of GELU_erf and its derivative:
 //   GELU(z) = z Phi(z),   GELU'(z) = Phi(z) + z phi(z).
-// double: library erfc/exp (erfc form keeps relative accuracy for z << 0).
-// float : used with bf16 storage only.  Phi(z) = 1/2 + zc P(zc^2/16) with zc = clamp(z, -4, 4) and P a degree-8
-//         minimax polynomial: no division, no exponential, |error| <= 2.7e-5 (the tail beyond |z| = 4 included),
-//         two orders below what bf16 storage resolves.  GELU multiplies Phi by max(z, -4) instead of z so that
-//         the polynomial's residual at the left clamp (2.5e-5) is not scaled by an arbitrarily large |z|: the
-//         absolute error of GELU is <= 1.1e-4 for z < 0 and its relative error <= 2.6e-5 for z > 0.
-//         phi needs one hardware exp2.  Within one forward/backward pair every kernel evaluates GELU the same
-//         way - through these functions, or all of them through the table below (GaussTable) - so the row
-//         statistics of the forward pass, the values normalised later and the backward pass agree exactly.
-template <class C> struct Gauss;
-
-template <> struct Gauss<double> {
-  static __device__ __forceinline__ void eval(double z, double& Phi, double& phi) {
-    Phi = 0.5 * erfc(-z * 0.70710678118654752440);
-    phi = exp(-0.5 * z * z) * 0.39894228040143267794;
-  }
-  static __device__ __forceinline__ double cdf(double z) { return 0.5 * erfc(-z * 0.70710678118654752440); }
-  static __device__ __forceinline__ double gelu_of(double z, double Phi) { return z * Phi; }
-};
-
-template <> struct Gauss<float> {
-  static __device__ __forceinline__ float cdf(float z) {
-    const float zc = __builtin_amdgcn_fmed3f(z, -4.0f, 4.0f);
-    // P is fitted in (zc/4)^2; its coefficients are scaled by exact powers of two so that Horner runs on zc^2
-    const float u = zc * zc;
-    float p = 3.463215330e-01f * 0x1p-32f;
-    p = __builtin_fmaf(p, u, -1.879980461e+00f * 0x1p-28f);
-    p = __builtin_fmaf(p, u, 4.556957157e+00f * 0x1p-24f);
-    p = __builtin_fmaf(p, u, -6.600788584e+00f * 0x1p-20f);
-    p = __builtin_fmaf(p, u, 6.482041631e+00f * 0x1p-16f);
-    p = __builtin_fmaf(p, u, -4.644545581e+00f * 0x1p-12f);
-    p = __builtin_fmaf(p, u, 2.528634197e+00f * 0x1p-8f);
-    p = __builtin_fmaf(p, u, -1.062569532e+00f * 0x1p-4f);
-    p = __builtin_fmaf(p, u, 3.989227098e-01f);
-    return __builtin_fmaf(zc, p, 0.5f);
-  }
-  // max(z, -4) written as the median of (z, -4, largest finite float): one instruction, where a plain maximum
-  // first canonicalises its input (the two agree for every finite z)
-  static __device__ __forceinline__ float gelu_of(float z, float Phi) {
-    return __builtin_amdgcn_fmed3f(z, -4.0f, 3.402823466e+38f) * Phi;
-  }
-  static __device__ __forceinline__ void eval(float z, float& Phi, float& phi) {
-    Phi = cdf(z);
-    phi = __builtin_amdgcn_exp2f(-0.72134752044448170368f * z * z) * 0.39894228040143267794f;   // exp(-z^2/2)/sqrt(2 pi)
-  }
-};
-
-template <class C> __device__ __forceinline__ C gelu(C z) { return Gauss<C>::gelu_of(z, Gauss<C>::cdf(z)); }
+// fp32 storage evaluates them with the library's fp64 erfc and exp, bf16 storage reads them from the table below; every
+// row kernel does it through ActTable, so that the forward statistics, the values normalised and the backward pass agree
+// exactly (for a constant row, rstd = eps^-1/2 multiplies any difference between them into Ahat).
 
 // ---------------------------------------------------------------------------------------------
 // Compile-time evaluation of the normal distribution in double precision (for the table below: its entries are
@@ -123,13 +78,12 @@ constexpr double erf_pos(double x) {
 //   H = Phi(|z|) - 1/2      and (kPair) Q = |z| phi(|z|),
 // both odd in z, as fp32 roundings of an fp64 evaluation.  Smaller magnitudes use the first entry (H, Q < 2.5e-5)
 // and larger ones the last (H = 1/2, Q = 0 to fp32).  A lookup is: clamp the magnitude bits, one LDS read, copy
-// the sign of z onto the entries - five integer instructions instead of the eleven of the polynomial, and
-// GELU(z) = z (1/2 + sign(z) H) carries no approximation error beyond fp32 rounding.  The entries are compile-time
+// the sign of z onto the entries - five integer instructions, and GELU(z) = z (1/2 + sign(z) H) carries no approximation error beyond fp32 rounding.  The entries are compile-time
 // constants in device memory; every workgroup copies them into its LDS (coalesced, a few KB from the L2).
 constexpr uint32_t kGaussLo = 0x3880u;          // bf16 bits of 2^-14
 constexpr uint32_t kGaussHi = 0x417fu;          // bf16 bits of the largest bf16 number below 16
 constexpr int kGaussEntries = (int)(kGaussHi - kGaussLo) + 1;
-struct GaussTableData { float h[kGaussEntries]; float pair[2 * kGaussEntries]; };
+struct GaussTableData { alignas(16) float h[kGaussEntries]; alignas(16) float pair[2 * kGaussEntries]; };
 constexpr GaussTableData make_gauss_table() {
   GaussTableData t = {};
   for (int i = 0; i < kGaussEntries; i++) {
@@ -153,8 +107,11 @@ template <bool kPair> struct GaussTable {
 
   // tbl: LDS; every thread of the workgroup calls this (followed by a barrier at the caller)
   static __device__ __forceinline__ void build(float* tbl, int tid, int nthreads) {
-    const float* src = kPair ? g_gauss_table.pair : g_gauss_table.h;
-    for (int i = tid; i < (kPair ? 2 : 1) * kEntries; i += nthreads) tbl[i] = src[i];
+    const f32x4* src = reinterpret_cast<const f32x4*>(kPair ? g_gauss_table.pair : g_gauss_table.h);
+    constexpr int kVectors = kBytes / 16;
+    static_assert(kBytes % 16 == 0, "whole vectors");
+#pragma unroll 8
+    for (int i = tid; i < kVectors; i += nthreads) reinterpret_cast<f32x4*>(tbl)[i] = src[i];
   }
   // LDS address of the entry for the bf16 number whose bits (sign included or not) are in the low 16 bits of
   // `bits`: clamped magnitude bits times the entry size plus origin(table address), in three instructions
@@ -171,6 +128,45 @@ template <bool kPair> struct GaussTable {
   static __device__ __forceinline__ float with_sign_of(float h, float z) {
     return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, h) & 0x7fffffffu) |
                                          (__builtin_bit_cast(uint32_t, z) & 0x80000000u));
+  }
+};
+
+// What the row kernels ask: T = float evaluates in fp64, T = bf16 holds the table in the workgroup's LDS (kPair: with
+// z phi(z), for the backward pass).  NT: threads of the workgroup; 0 makes an empty object (no activation).
+template <class T, bool kPair, int NT> struct ActTable;
+template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
+  __device__ __forceinline__ void build() {}
+  static __device__ __forceinline__ double gelu(double z) { return z * (0.5 * erfc(-z * 0.70710678118654752440)); }
+  static __device__ __forceinline__ void eval(double z, double& Phi, double& zphi) {
+    Phi = 0.5 * erfc(-z * 0.70710678118654752440);
+    zphi = z * (exp(-0.5 * z * z) * 0.39894228040143267794);
+  }
+};
+template <bool kPair> struct ActTable<bf16_t, kPair, 0> {
+  __device__ __forceinline__ void build() {}
+  static __device__ __forceinline__ float gelu(float z) { return z; }
+};
+template <bool kPair, int NT> struct ActTable<bf16_t, kPair, NT> {
+  typedef GaussTable<kPair> GT;
+  typedef __attribute__((address_space(3))) float lds_float;
+  typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
+  uint32_t org;
+  // every thread of the workgroup calls this; ends with a barrier
+  __device__ __forceinline__ void build() {
+    __shared__ __attribute__((aligned(16))) float tbl[(kPair ? 2 : 1) * GT::kEntries];
+    GT::build(tbl, threadIdx.x, NT);
+    org = GT::origin((uint32_t)(uintptr_t)(const lds_float*)tbl);
+    __syncthreads();
+  }
+  // z: a bf16 number
+  __device__ __forceinline__ float gelu(float z) const {
+    const float h = *(const lds_float*)(uintptr_t)GT::address_of(__builtin_bit_cast(uint32_t, z) >> 16, org);
+    return z * (0.5f + GT::with_sign_of(h, z));
+  }
+  __device__ __forceinline__ void eval(float z, float& Phi, float& zphi) const {
+    const f32x2 e = *(const lds_f32x2*)(uintptr_t)GT::address_of(__builtin_bit_cast(uint32_t, z) >> 16, org);
+    Phi = 0.5f + GT::with_sign_of(e[0], z);
+    zphi = GT::with_sign_of(e[1], z);
   }
 };
 

@@ -106,12 +106,8 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
 
   // ---- forward
   q.f1_fast = q.pad || (dt == kBF16 && fast_f1_supported(M, K, N));
-  q.f2_rows = q.f1_fast && f2_rows_supported(dt, N);
   q.f1_wb = pick_wb(Mp, N);
-  q.stat_tile_w = q.f1_fast ? fast_f1_stat_tile_w() : 16 * q.f1_wb;
-  q.stat_tiles = (int)((N + q.stat_tile_w - 1) / q.stat_tile_w);
   size_t off = 0;
-  q.off_part = off; off += align256(q.f2_rows ? 0 : (size_t)q.stat_tiles * Mp * 8);   // no partials where F2 takes the statistics
   q.off_xtail = off; off += align256(q.pad ? fast_padded_tail_bytes(K) : (q.f1_fast ? fast_f1_tail_bytes(M, K) : 0));
   q.off_wpad_f = off; off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_bpad_f = off; off += align256(q.pad ? (size_t)Np * 4 : 0);
@@ -121,16 +117,20 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.f1_wt = q.f1_fast && !q.pad && M >= kTransposeFromRows;
   q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
   q.fwd_bytes = off;
+  // The static entry point's limit is part of its contract (see the header): 8 bytes per (row, column tile) wherever rows
+  // are not normalised by the wavefront-per-row kernel on the tuned path, whether a plan needs them or not.
+  const int64_t limit_tile = q.f1_fast ? 128 : 16 * q.f1_wb;
+  const bool limit_free = q.f1_fast && N % 8 == 0 && N <= 8192;
+  q.static_need = (limit_free ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8));
 
   // ---- backward
-  q.b1_fused = b1_fused_supported(dt, N);
+  q.b1_fused = b1_fused_supported(dt, N, q.ldz);
   if (q.b1_fused) {
     const int64_t want = b1_fused_groups(dt, Mp, N);
     q.b1_groups = (int)(Mp < want ? Mp : want);
     q.b1_rows_per_group = 0;
   } else {
-    int64_t rpg = (Mp + 1023) / 1024;
-    if (rpg < 16) rpg = 16;
+    const int64_t rpg = b1b_rows_per_group(dt, Mp, N);
     q.b1_rows_per_group = (int)rpg;
     q.b1_groups = (int)((Mp + rpg - 1) / rpg);
   }
@@ -153,7 +153,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   // kernel over the last rows, no padded pitch); the vector path of the row kernel needs N % 8 = 0, which the tiles imply
   // (the row kernel pays for it with about 8 % of its time where a row fills 1024 threads, dX gains about 9 %: not
   //  worth it when such rows meet a short K)
-  q.dz_blocked = dt == kBF16 && q.b1_fused && !q.pad && q.b3_fast && q.b4_fast && q.b4_fast_rows == M && M % 32 == 0 &&
+  q.dz_blocked = dt == kBF16 && q.b1_fused && N <= 8192 && !q.pad && q.b3_fast && q.b4_fast && q.b4_fast_rows == M && M % 32 == 0 &&
                  N % 32 == 0 && (K >= 1024 || N <= 4096);
   // fp32 partial sums of dW: the parts of a split reduction, one more for the rows the fast kernel leaves to the
   // generic one; in padded mode the fast kernel always writes partials
@@ -267,31 +267,28 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
                                    const float* beta, float eps, void* Y, void* Zsave, float* mean, float* rstd,
                                    char* ws, hipStream_t s) {
   const int64_t M = p.M, K = p.K, N = p.N;
-  void* part = ws + p.off_part;
   {
     PhaseTimer t(FDL_PHASE_F1, s);
     if (p.pad) {
       void* Wp = ws + p.off_wpad_f;
       float* bp = reinterpret_cast<float*>(ws + p.off_bpad_f);
       launch_fast_pad_weights(K, N, W, b, Wp, bp, s);
-      launch_fast_f1_padded(M, K, N, X, Wp, bp, Zsave, p.f2_rows ? nullptr : part, ws + p.off_xtail, s);
+      launch_fast_f1_padded(M, K, N, X, Wp, bp, Zsave, ws + p.off_xtail, s);
     } else if (p.f1_fast) {
       void* Wt = p.f1_wt ? ws + p.off_wt : nullptr;
       if (p.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
-      launch_fast_f1(M, K, N, X, W, Wt, b, Zsave, p.f2_rows ? nullptr : part, ws + p.off_xtail, s);
+      launch_fast_xwt(0, M, K, N, X, false, W, Wt, b, nullptr, Zsave, false, ws + p.off_xtail, s);
     } else {
       GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
-      launch_generic_f1(p.dt, g, b, Zsave, part, s);
+      launch_generic_xwt(p.dt, 0, g, b, nullptr, Zsave, s);
     }
   }
   {
-    PhaseTimer t(FDL_PHASE_FS, s);
-    if (!p.f2_rows) launch_stats_finalize(part, p.stat_tiles, p.stat_tile_w, M, N, eps, mean, rstd, s);
+    PhaseTimer t(FDL_PHASE_FS, s);   // (the statistics are F2's own: nothing is launched here)
   }
   {
     PhaseTimer t(FDL_PHASE_F2, s);
-    if (p.f2_rows) launch_f2_rows(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
-    else launch_f2(p.dt, M, N, Zsave, mean, rstd, gamma, beta, Y, s);
+    launch_f2(p.dt, M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
   }
   return launch_status();
 }
@@ -340,17 +337,17 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   Plan p;
   const fdl_status st = check_forward_args(dt, M, K, N, X, W, b, gamma, beta, eps, Y, Zsave, mean, rstd, &p);
   if (st != FDL_OK) return st;
-  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
+  if (p.static_need + p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
     p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the transposed weights: the kernel reads W as it is
   }
-  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;   // the problem needs more than the array holds
+  if (p.static_need + p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;   // the problem needs more than the array holds
   if (!forward_args_aligned(X, W, b, gamma, beta, Y, Zsave, mean, rstd)) return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;
   clear_stale_error();
   char* ws = static_scratch_address();
   if (ws == nullptr) return launch_status();
-  // every scratch location a forward pass reads has been written earlier in the same pass (partial statistics
-  // per row and column tile, the padded copy of X's last rows), so nothing has to be cleared between calls
+  // every scratch location a forward pass reads has been written earlier in the same pass (padded or transposed
+  // weights, the padded copy of X's last rows), so nothing has to be cleared between calls
   return forward_launches(p, X, W, b, gamma, beta, eps, Y, Zsave, mean, rstd, ws, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -387,13 +384,12 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
   {
     PhaseTimer t(FDL_PHASE_B1, s);
     if (p.b1_fused) {
-      launch_b1_fused((int)dt, M, N, p.ldz, p.b1_groups, p.f2_rows != 0, p.dz_blocked != 0, dY, Zsave, gamma, mean, rstd, dZ,
-                      colpart, s);
+      launch_b1_fused((int)dt, M, N, p.ldz, p.b1_groups, p.dz_blocked != 0, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
     } else {
       launch_b1a((int)dt, M, N, dY, Zsave, gamma, mean, rstd, c12, s);
       launch_b1b((int)dt, M, N, p.ldz, p.b1_rows_per_group, p.b1_groups, dY, Zsave, gamma, mean, rstd, c12, dZ, colpart, s);
     }
-    if (p.pad) launch_zero_cols_bf16(dZ, M, N, p.ldz, s);   // the surplus columns enter the dX and dW contractions
+    if (p.pad && !p.b1_fused) launch_zero_cols_bf16(dZ, M, N, p.ldz, s);   // the surplus columns enter the dX and dW contractions
   }
   // Where the contractions below leave split reductions behind (bf16 tuned path), their sums and the column sums
   // share one launch at the end of the pass; otherwise the column sums are finished here.

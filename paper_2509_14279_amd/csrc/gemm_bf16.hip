@@ -3,8 +3,7 @@
 //     D[i][j] = sum_r P(i,r) * Q(j,r)      stored as C[j][i]   (C row-major, leading dimension I)
 //
 // P feeds the MFMA "A" side, Q the "B" side, so a lane ends up with 4 consecutive i (output columns) of one
-// output row j in adjacent accumulator registers, and a row reduction over i (the LayerNorm statistics, where
-// the forward pass takes them here) is a sum inside the lane plus one cross-half exchange.
+// output row j in adjacent accumulator registers.
 //
 //   F1  Z[m][n]  = sum_k X[m][k] W[n][k] + b[n]   P = W (i = n, r-contiguous)   Q = X  (j = m, r-contiguous)
 //       or, for large batches,                    P = W^T (a transposed copy: r = k major)
@@ -62,11 +61,11 @@ template <int BK> struct Geo {
   static constexpr int kWaveBytes = kOperandBytes / 4;    // each wave fills a quarter of an operand tile
 };
 
-// EPI_STORE: C = acc.  EPI_BIAS: C = acc + bias.  EPI_F1: EPI_BIAS plus GELU and partial row statistics.
+// EPI_STORE: C = acc.  EPI_BIAS: C = acc + bias.
 // EPI_PARTIAL: fp32 partial sums of a split reduction.  EPI_RELU: C = max(acc + bias, 0).
 // EPI_MASK: C = aux where acc + bias > 0, else 0 (aux [J][I]: the upstream gradient of a ReLU).
 // EPI_GATE: two P operands (gate and up weights), C = SiLU(Q P^T) * (Q P2^T): see the kernel's p_origin.
-enum { EPI_STORE = 0, EPI_F1 = 1, EPI_BIAS = 2, EPI_PARTIAL = 3, EPI_RELU = 4, EPI_MASK = 5, EPI_GATE = 6 };
+enum { EPI_STORE = 0, EPI_BIAS = 2, EPI_PARTIAL = 3, EPI_RELU = 4, EPI_MASK = 5, EPI_GATE = 6 };
 
 struct FastParams {
   const bf16_t* P; const bf16_t* Q;
@@ -76,9 +75,8 @@ struct FastParams {
   int64_t ldp, ldq;
   bf16_t* C;             // [J][I]
   float* Cpart;          // [split][J][I] fp32 (split > 1)
-  const float* bias;     // [I]   (EPI_F1, EPI_BIAS, EPI_RELU, EPI_MASK)
+  const float* bias;     // [I]   (EPI_BIAS, EPI_RELU, EPI_MASK)
   const bf16_t* aux;     // [J][I] (EPI_MASK)
-  f32x2* part;           // [I/128][J]  (EPI_F1)
   int I, J;              // J: valid output rows (RAG: any number >= 1; otherwise a multiple of 256)
   int tiles_i, tiles_j;
   int nkt;               // reduction slices per workgroup
@@ -245,7 +243,7 @@ __device__ __forceinline__ TileCoord tile_coord(int L, int tiles_i, int tiles_j)
 // CRAG (with RAG): the number of output columns I is a multiple of 8 but not of the tile.  The host hands over a P
 // operand that is readable up to the end of the last column tile (a zero-padded copy of the weights, or a matrix
 // whose surplus columns are the start of its next row) and a bias padded likewise; the surplus columns are computed
-// and not stored, and are left out of the row statistics where the epilogue takes them.
+// and not stored.
 // A reduction length that is not a whole number of pipeline rounds is the host's business as well: it rounds the
 // length up and makes one operand zero over the surplus (the other only has to be readable and finite there).
 // The body of the kernel: the persistent tile loop of workgroup `bid` of `nblk` on reduction part `part`.  It is a
@@ -350,7 +348,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   // values are fetched at the top of the tile by two direct loads into its output staging area, which is idle
   // until the epilogue: like every direct load they are older than the slice loads issued after them, so the main
   // loop's own waits cover them, and no register or compiler-inserted wait is involved.
-  constexpr bool kBias = EPI == EPI_BIAS || EPI == EPI_F1 || EPI == EPI_RELU || EPI == EPI_MASK;
+  constexpr bool kBias = EPI == EPI_BIAS || EPI == EPI_RELU || EPI == EPI_MASK;
 
   for (;;) {
     // slice 0 of this tile has landed in stage 0 (initial fill, or prefetched during the previous tile and
@@ -524,7 +522,6 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     asm volatile("" : "+v"(le));
     const int e_half = le >> 5, e_l32 = le & 31;
     const int i0 = tc.i0, j0 = tc.j0;
-    const int jw = j0 + wj * 128 + e_l32;          // + b*32
     lds_char* wtile = lds + kLdsStages + wave * 8192;
     uint32_t woff[4][4];                         // LDS byte offset of the lane's 8-byte unit (a, g) in row lane%32
 #pragma unroll
@@ -633,7 +630,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
           }
         __builtin_amdgcn_sched_barrier(0);
       }
-    } else if (EPI != EPI_F1) {
+    } else {
       // rounded to bf16 and stored (forward: the bias is in the accumulators since their start; the row statistics
       // are taken by the normalisation kernel)
 #pragma unroll
@@ -650,52 +647,6 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
           }
         flush_rows(b);
         __builtin_amdgcn_sched_barrier(0);   // one block row at a time: keeps the accumulator copies in few registers
-      }
-    } else {
-      // Z (bias included) rounded to bf16 and stored; A = GELU(stored Z); per output row j, mean and sum of squared
-      // deviations of A over this wave's 128 columns: 64 values in the lane, 64 in lane ^ 32.
-      const int stat_tile = (i0 + wi * 128) >> 7;
-      // CRAG: columns of this wave's 128 that exist (a multiple of 4, wave-uniform); the others are masked out
-      int nvalid = 128;
-      if (CRAG) { nvalid = p.I - (i0 + wi * 128); nvalid = nvalid < 0 ? 0 : (nvalid > 128 ? 128 : nvalid); }
-      const float inv_valid = 1.0f / (float)(nvalid > 0 ? nvalid : 1);
-#pragma unroll
-      for (int b = 0; b < 4; b++) {
-        const int64_t j = jw + b * 32;
-        float sum = 0.0f;
-#pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-          for (int g = 0; g < 4; g++) {
-            bf16x4 zs;
-            const bool live = !CRAG || a * 32 + g * 8 + e_half * 4 < nvalid;
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              zs[e] = (bf16_t)acc[a][b][g * 4 + e];
-              const float act = live ? gelu<float>((float)zs[e]) : 0.0f;
-              acc[a][b][g * 4 + e] = act;
-              sum += act;
-            }
-            *(lds_bf16x4*)(wtile + woff[a][g]) = zs;
-          }
-        sum += __shfl_xor(sum, 32, kWave);
-        const float mean = sum * inv_valid;
-        float m2 = 0.0f;
-#pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-          for (int r = 0; r < 16; r++) {
-            const bool live = !CRAG || a * 32 + (r >> 2) * 8 + e_half * 4 < nvalid;
-            const float d = live ? acc[a][b][r] - mean : 0.0f;
-            m2 = __builtin_fmaf(d, d, m2);
-          }
-        m2 += __shfl_xor(m2, 32, kWave);
-        if (e_half == 0 && (!RAG || j < p.J) && (!CRAG || nvalid > 0)) {
-          f32x2 o; o[0] = mean; o[1] = m2;
-          p.part[(int64_t)stat_tile * p.J + j] = o;
-        }
-        flush_rows(b);
-        __builtin_amdgcn_sched_barrier(0);
       }
     }
 
@@ -857,7 +808,6 @@ int64_t fast_b4_rows(int64_t M) { const int64_t u = (int64_t)kB4BK * stages_of(k
 bool fast_b4_supported(int64_t M, int64_t K, int64_t N) {
   return fast_b4_rows(M) >= 128 && dims_ok(K, N, fast_b4_rows(M), kB4BK);
 }
-int fast_f1_stat_tile_w() { return 128; }
 size_t fast_f1_tail_bytes(int64_t M, int64_t K) { return M % kTile ? (size_t)kTile * K * 2 : 0; }
 
 // ---- padded mode: N and K multiples of 8 (16-byte rows) but not both multiples of the tile ----------------------
@@ -911,69 +861,32 @@ void launch_fast_transpose_gate(int64_t H, int64_t D, const void* Wg, const void
   hipLaunchKernelGGL(transpose64_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wu, H, D, (bf16_t*)Wcat, 2 * H, 128, 64);
 }
 
-// part != nullptr: also emit the per-(row, 128-column tile) partial statistics of GELU(Zsave).
-// xtail: fast_f1_tail_bytes(M, K) bytes of scratch for the padded copy of X's last rows (M not a multiple of 256)
-// Wt: null, or W^T [K][N] (launch_fast_transpose): the weights then enter as the r-major operand.  A tile slice of an
-// r-major operand is 32 runs of 512 contiguous bytes, of an r-contiguous one 256 runs of 128 or 64 bytes, and the
-// contraction runs faster for every operand it can read the first way (measured on 65536 x 2048 x 8192: 1.77 -> 1.65
-// ms; with the reduction long enough to hide the tile boundaries the three combinations reach 1.16 - 1.27, 1.31 - 1.35
-// and 1.43 - 1.44 PFLOP/s), which pays for transposing the weights once the batch is large (the caller decides).
-void launch_fast_f1(int64_t M, int64_t K, int64_t N, const void* X, const void* W, const void* Wt, const float* bias,
-                    void* Zsave, void* part, void* xtail, hipStream_t s) {
-  FastParams p = {};
-  p.P = (const bf16_t*)W; p.Q = (const bf16_t*)X; p.ldp = K; p.ldq = K;
-  p.C = (bf16_t*)Zsave; p.bias = bias; p.part = (f32x2*)part;
-  p.I = (int)N; p.J = (int)M; p.tiles_i = (int)(N / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
-  p.nkt = (int)(K / kF1BK); p.split = 1;
-  const bool rag = M % kTile != 0;
-  if (rag) {
-    p.Qtail = (const bf16_t*)xtail;
-    hipLaunchKernelGGL(copy_tail_rows_kernel, dim3(64), dim3(256), 0, s, (const bf16_t*)X, M, K,
-                       (int64_t)(p.tiles_j - 1) * kTile, (bf16_t*)xtail, kTile);
-  }
-  if (Wt != nullptr) {
-    p.P = (const bf16_t*)Wt; p.ldp = N; p.nkt = (int)(K / kB3BK);
-    constexpr int NS = stages_of(kB3BK);
-    if (rag) {
-      if (part != nullptr) launch<true, false, EPI_F1, kB3BK, NS, true>(p, s);
-      else launch<true, false, EPI_BIAS, kB3BK, NS, true>(p, s);
-    } else {
-      if (part != nullptr) launch<true, false, EPI_F1, kB3BK, NS>(p, s);
-      else launch<true, false, EPI_BIAS, kB3BK, NS>(p, s);
-    }
-    return;
-  }
-  if (rag) {
-    if (part != nullptr) launch<false, false, EPI_F1, kF1BK, stages_of(kF1BK), true>(p, s);
-    else launch<false, false, EPI_BIAS, kF1BK, stages_of(kF1BK), true>(p, s);
-  } else {
-    if (part != nullptr) launch<false, false, EPI_F1, kF1BK, stages_of(kF1BK)>(p, s);
-    else launch<false, false, EPI_BIAS, kF1BK, stages_of(kF1BK)>(p, s);
-  }
-}
-
 // Padded mode: Wp [Np][Kp], biasp [Np] from launch_fast_pad_weights; xtail: fast_padded_tail_bytes(K) bytes
 void launch_fast_f1_padded(int64_t M, int64_t K, int64_t N, const void* X, const void* Wp, const float* biasp, void* Zsave,
-                           void* part, void* xtail, hipStream_t s) {
+                           void* xtail, hipStream_t s) {
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
   FastParams p = {};
   p.P = (const bf16_t*)Wp; p.Q = (const bf16_t*)X; p.ldp = Kp; p.ldq = K;
-  p.C = (bf16_t*)Zsave; p.bias = biasp; p.part = (f32x2*)part;
+  p.C = (bf16_t*)Zsave; p.bias = biasp;
   p.I = (int)N; p.J = (int)M; p.tiles_i = (int)(Np / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
   p.nkt = (int)(Kp / kF1BK); p.split = 1;
   // the last row tile always comes from the copy: its rows are read up to Kp columns, and X's last row has no successor
   p.Qtail = (const bf16_t*)xtail;
   hipLaunchKernelGGL(copy_tail_rows_kernel, dim3(64), dim3(256), 0, s, (const bf16_t*)X, M, K,
                      (int64_t)(p.tiles_j - 1) * kTile, (bf16_t*)xtail, kTile + 1);
-  if (part != nullptr) launch<false, false, EPI_F1, kF1BK, stages_of(kF1BK), true, true>(p, s);
-  else launch<false, false, EPI_BIAS, kF1BK, stages_of(kF1BK), true, true>(p, s);
+  launch<false, false, EPI_BIAS, kF1BK, stages_of(kF1BK), true, true>(p, s);
 }
 
-// out[m][n] = f(sum_k X[m][k] W[n][k] + bias[n]) for the sibling operators; same shape rules as launch_fast_f1.
+// out[m][n] = f(sum_k X[m][k] W[n][k] + bias[n]): the forward product (fast_f1_supported shapes).
 //   kind 0: plain product (bias may be null: then none is added)      kind 1: max(. , 0)
 //   kind 2: aux[m][n] where the sum is positive, else 0
 // xtail: fast_f1_tail_bytes(M, K) bytes of scratch when M is not a multiple of 256, unless X itself has readable rows
-// up to the next multiple of 256 (x_padded).  Wt: null, or W^T [K][N] from launch_fast_transpose.
+// up to the next multiple of 256 (x_padded).
+// Wt: null, or W^T [K][N] (launch_fast_transpose): the weights then enter as the r-major operand.  A tile slice of an
+// r-major operand is 32 runs of 512 contiguous bytes, of an r-contiguous one 256 runs of 128 or 64 bytes, and the
+// contraction runs faster for every operand it can read the first way (measured on 65536 x 2048 x 8192: 1.77 -> 1.65
+// ms; with the reduction long enough to hide the tile boundaries the three combinations reach 1.16 - 1.27, 1.31 - 1.35
+// and 1.43 - 1.44 PFLOP/s), which pays for transposing the weights once the batch is large (the caller decides).
 // out_blocked (kind 2 only; M, N multiples of 32): out is written in 32 x 32 blocks, as the dX and dW kernels read it best.
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
                      const void* Wt, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
@@ -991,7 +904,7 @@ void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, b
     hipLaunchKernelGGL(copy_tail_rows_kernel, dim3(64), dim3(256), 0, s, (const bf16_t*)X, M, K,
                        (int64_t)(p.tiles_j - 1) * kTile, (bf16_t*)xtail, kTile);
   }
-  if (Wt != nullptr) {   // the weights as the r-major operand (see launch_fast_f1)
+  if (Wt != nullptr) {   // the weights as the r-major operand
     p.P = (const bf16_t*)Wt; p.ldp = N; p.nkt = (int)(K / kB3BK);
     constexpr int NST = stages_of(kB3BK);
 #define FDL_XWT_T(EPI)                                                            \
@@ -1040,7 +953,7 @@ void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void
     hipLaunchKernelGGL(copy_tail_rows_kernel, dim3(64), dim3(256), 0, s, (const bf16_t*)X, M, D,
                        (int64_t)(p.tiles_j - 1) * kTile, (bf16_t*)xtail, kTile);
   }
-  if (Wcat != nullptr) {   // Wcat from launch_fast_transpose_gate: the weights as one r-major operand (see launch_fast_f1)
+  if (Wcat != nullptr) {   // Wcat from launch_fast_transpose_gate: the weights as one r-major operand (see launch_fast_xwt)
     p.P = (const bf16_t*)Wcat; p.P2 = nullptr; p.ldp = 2 * H; p.nkt = (int)(D / kB3BK);
     constexpr int NST = stages_of(kB3BK);
     if (rag) launch<true, false, EPI_GATE, kB3BK, NST, true>(p, s);

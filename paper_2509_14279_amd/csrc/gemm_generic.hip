@@ -25,13 +25,13 @@
 namespace fdl {
 namespace {
 
-// EPI_STORE: C = acc (+ bias[j] when given).  EPI_F1: bias, GELU and partial row statistics.  EPI_STORE_F32: fp32 C.
+// EPI_STORE: C = acc (+ bias[j] when given).  EPI_STORE_F32: fp32 C.
 // EPI_RELU: C = max(acc + bias[j], 0).  EPI_MASK: C = aux[i][j] where acc + bias[j] > 0, else 0.
-enum { EPI_STORE = 0, EPI_F1 = 1, EPI_STORE_F32 = 2, EPI_RELU = 3, EPI_MASK = 4 };
+enum { EPI_STORE = 0, EPI_STORE_F32 = 2, EPI_RELU = 3, EPI_MASK = 4 };
 
 struct GemmParams {
   const void* A; const void* B; void* C;
-  const float* bias; f32x2* part;
+  const float* bias;
   const void* aux;       // [I][J] in the storage type (EPI_MASK)
   int64_t I, J, R, lda, ldb;
   int a_vec, b_vec;
@@ -44,8 +44,6 @@ template <class AccT> struct Mma;
 // accumulators held in AGPRs, and in this kernel it ran 20 % slower.)
 template <> struct Mma<double> {
   typedef f64x4 acc_t;
-  static constexpr int kRowsPerLane = 4;      // distinct output rows among a lane's four accumulator elements
-  static constexpr int kRowLanes = 16;        // lanes that share a row
   static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)b, c, 0, 0, 0);
   }
@@ -75,8 +73,6 @@ template <> struct Mma<float> {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, pa), __builtin_bit_cast(s16x4, pb), c, 0, 0, 0);
   }
   // accumulator register r of lane l holds output row 4(l/16) + r, column l%16
-  static constexpr int kRowsPerLane = 4;
-  static constexpr int kRowLanes = 16;
   static __device__ __forceinline__ int row(int lane, int r) { return (lane >> 4) * 4 + r; }
   static __device__ __forceinline__ int col(int lane, int) { return lane & 15; }
 };
@@ -298,7 +294,7 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmParams p) {
           if (i < p.I && j < p.J) Cf[i * p.J + j] = (float)acc[a][b][r];
         }
       }
-  } else if (EPI == EPI_STORE || EPI == EPI_RELU || EPI == EPI_MASK) {
+  } else {
     AccT bias[WB][4];
 #pragma unroll
     for (int b = 0; b < WB; b++)
@@ -322,54 +318,6 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmParams p) {
             else if (EPI == EPI_RELU) C[i * p.J + j] = to_storage<T, AccT>(z > (AccT)0 ? z : (AccT)0);
             else C[i * p.J + j] = to_storage<T, AccT>(z);
           }
-        }
-      }
-  } else {
-    // Z = acc + bias, stored rounded; A = GELU(stored Z); two-pass mean / sum of squared deviations over
-    // this wave's 16*WB columns of the row, reduced across the lanes that share the row (written for any
-    // assignment of a lane's accumulator elements to rows: kRowsPerLane of them, kRowLanes lanes per row).
-    constexpr int RPL = M::kRowsPerLane;
-    constexpr int NE = (4 / RPL) * WB;           // elements of one row held by a lane
-    const int64_t tile = jw / (16 * WB);
-    int64_t nvalid = p.J - jw;
-    if (nvalid > 16 * WB) nvalid = 16 * WB;
-#pragma unroll
-    for (int a = 0; a < WB; a++)
-#pragma unroll
-      for (int slot = 0; slot < RPL; slot++) {
-        const int64_t i = iw + a * 16 + M::row(lane, slot);
-        AccT act[NE];
-        bool ok[NE];
-        AccT sum = 0;
-        int n = 0;
-#pragma unroll
-        for (int b = 0; b < WB; b++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            if (RPL == 4 && r != slot) continue;
-            const int64_t j = jw + b * 16 + M::col(lane, r);
-            ok[n] = j < p.J;
-            const AccT bias = ok[n] ? (AccT)p.bias[j] : (AccT)0;
-            const T zs = to_storage<T, AccT>(acc[a][b][r] + bias);
-            if (ok[n] && i < p.I) C[i * p.J + j] = zs;
-            act[n] = ok[n] ? gelu<AccT>((AccT)to_f32<T>(zs)) : (AccT)0;
-            sum += act[n];
-            n++;
-          }
-#pragma unroll
-        for (int m = 1; m < M::kRowLanes; m <<= 1) sum += __shfl_xor(sum, m, kWave);
-        const AccT mean = nvalid > 0 ? sum / (AccT)nvalid : (AccT)0;
-        AccT m2 = 0;
-#pragma unroll
-        for (int e = 0; e < NE; e++) {
-          const AccT d = act[e] - mean;
-          m2 += ok[e] ? d * d : (AccT)0;
-        }
-#pragma unroll
-        for (int m = 1; m < M::kRowLanes; m <<= 1) m2 += __shfl_xor(m2, m, kWave);
-        if ((lane & (M::kRowLanes - 1)) == 0 && i < p.I && nvalid > 0) {
-          f32x2 o; o[0] = (float)mean; o[1] = (float)m2;
-          p.part[tile * p.I + i] = o;
         }
       }
   }
@@ -396,10 +344,6 @@ void set_vec(GemmParams* p, const GemmDesc& g, bool a_rc, bool b_rc, size_t elem
 template <class T, int EPI> void dispatch(const GemmDesc& g, GemmParams p, hipStream_t s) {
   set_vec(&p, g, g.a_rc, g.b_rc, sizeof(T));
   const bool big = g.wb == 4;
-  if (EPI == EPI_F1) {           // F1 always has both operands reduction-contiguous
-    if (big) launch_one<T, true, true, 4, EPI>(p, s); else launch_one<T, true, true, 2, EPI>(p, s);
-    return;
-  }
   if (g.a_rc && !g.b_rc) {
     if (big) launch_one<T, true, false, 4, EPI>(p, s); else launch_one<T, true, false, 2, EPI>(p, s);
   } else if (!g.a_rc && !g.b_rc) {
@@ -413,18 +357,12 @@ template <class T, int EPI> void dispatch(const GemmDesc& g, GemmParams p, hipSt
 
 GemmParams base_params(const GemmDesc& g) {
   GemmParams p;
-  p.A = g.A; p.B = g.B; p.C = nullptr; p.bias = nullptr; p.part = nullptr; p.aux = nullptr;
+  p.A = g.A; p.B = g.B; p.C = nullptr; p.bias = nullptr; p.aux = nullptr;
   p.I = g.I; p.J = g.J; p.R = g.R; p.lda = g.lda; p.ldb = g.ldb; p.a_vec = 0; p.b_vec = 0; p.wide = 0;
   return p;
 }
 
 }  // namespace
-
-void launch_generic_f1(int dt, const GemmDesc& g, const float* bias, void* Zsave, void* part, hipStream_t s) {
-  GemmParams p = base_params(g);
-  p.C = Zsave; p.bias = bias; p.part = static_cast<f32x2*>(part);
-  if (dt == kF32) dispatch<float, EPI_F1>(g, p, s); else dispatch<bf16_t, EPI_F1>(g, p, s);
-}
 
 // only the operand orientation of the dW contraction (both operands indexed by the reduction row) is needed
 void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s) {

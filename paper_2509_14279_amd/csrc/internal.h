@@ -1,11 +1,8 @@
 // Host-side declarations shared by the translation units of libfdl: the launch plan (which
 // kernels run, how the workspace is carved up) and one launcher per phase of the block.
 //
-// Phases:  F1  Z = X W^T + b, Zsave, per-(row, column tile) partial statistics of GELU(Zsave)
-//          FS  merge partial statistics -> mean, rstd
-//          F2  Y = (GELU(Zsave) - mean) rstd gamma + beta
-//              (bf16 fast path with rows that fit a wavefront's registers: F1 stores Zsave only, F2 takes the
-//               statistics itself and FS is empty)
+// Phases:  F1  Zsave = X W^T + b
+//          F2  mean, rstd of GELU(Zsave), Y = (GELU(Zsave) - mean) rstd gamma + beta   (one kernel)
 //          B1  dZ and the column partials of dbeta, dgamma, db  (B1a: row sums c1, c2 first)
 //          B2  column partials -> dbeta, dgamma, db
 //          B3  dX = dZ W            B4  dW = dZ^T X
@@ -25,15 +22,12 @@ struct Plan {
   int64_t M, K, N;
   // forward
   int f1_fast;            // 1: bf16 fast MFMA kernel, 0: generic kernel
-  int f2_rows;            // 1: F1 stores Zsave only; one kernel takes the row statistics and normalises (no FS)
   int f1_wb;              // generic kernel: 16x16 blocks per wave tile side (wave tile = 16*wb)
-  int stat_tile_w;        // width of one partial-statistics column tile
-  int stat_tiles;         // number of such tiles per row
-  size_t off_part;        // float2 [stat_tiles][M]
   int f1_wt;              // 1: the fast kernel reads the weights from a transposed copy (large batches)
   size_t off_wt;          // bf16 [K][N], the last region of the forward workspace
   size_t fwd_bytes;       // (without the transposed weights: fwd_bytes - align256(N K 2), see fwd_bytes_plain)
   size_t fwd_bytes_plain; // forward workspace of the same plan with f1_wt = 0
+  size_t static_need;     // what fdl_forward_static compares with its array (the header's rule)
   // backward
   int b1_fused;           // 1: one pass with the row held in registers; 0: B1a + B1b
   int b1_groups;          // number of row groups that produce column partials
@@ -88,8 +82,6 @@ struct GemmDesc {
   bool a_rc, b_rc;
   int wb;
 };
-// F1: C = Zsave [I][J] (storage type), bias [J], partial statistics part[tile][I] (float2).
-void launch_generic_f1(int dt, const GemmDesc& g, const float* bias, void* Zsave, void* part, hipStream_t s);
 // forward-product orientation with an optional bias and a ReLU or ReLU-mask epilogue (sibling operators)
 void launch_generic_xwt(int dt, int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s);
 // plain store: C [I][J] in the storage type
@@ -98,29 +90,24 @@ void launch_generic_store(int dt, const GemmDesc& g, void* C, hipStream_t s);
 void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s);
 
 // ---- row-wise / column-wise phases ------------------------------------------------------------
-void launch_stats_finalize(const void* part, int tiles, int tile_w, int64_t M, int64_t N, float eps,
-                           float* mean, float* rstd, hipStream_t s);
-void launch_f2(int dt, int64_t M, int64_t N, const void* Zsave, const float* mean, const float* rstd,
-               const float* gamma, const float* beta, void* Y, hipStream_t s);
-// statistics and normalisation in one kernel (a wavefront per row); replaces FS + F2 when F1 emits no partials
-bool f2_rows_supported(int dt, int64_t N);
-void launch_f2_rows(int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
-                    float* mean, float* rstd, hipStream_t s);
+// row statistics of GELU(Zsave) and the normalised output (Zsave and Y may be the same buffer)
+void launch_f2(int dt, int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
+               float* mean, float* rstd, hipStream_t s);
 void launch_b1a(int dt, int64_t M, int64_t N, const void* dY, const void* Zsave, const float* gamma,
                 const float* mean, const float* rstd, void* c12, hipStream_t s);
 // ldz: pitch of dZ in elements (N, or N rounded up to the tile in the padded mode of the fast contractions)
 void launch_b1b(int dt, int64_t M, int64_t N, int64_t ldz, int rows_per_group, int groups, const void* dY, const void* Zsave,
                 const float* gamma, const float* mean, const float* rstd, const void* c12, void* dZ,
                 void* colpart, hipStream_t s);
-// fused single pass (row held in registers); returns false if this N is not supported by it
-bool b1_fused_supported(int dt, int64_t N);
+// fused single pass (row held in registers; ldz: pitch of dZ, whose surplus columns it zeroes); returns false if the row
+// is too long for it
+bool b1_fused_supported(int dt, int64_t N, int64_t ldz);
 int b1_fused_groups(int dt, int64_t M, int64_t N);   // number of row groups it should be launched with (before capping at M)
-// table: evaluate GELU from the LDS table, as the forward pass did (bf16, plan.f2_rows); else as the other kernels do
+int b1b_rows_per_group(int dt, int64_t M, int64_t N);
 void launch_zero_cols_bf16(void* dZ, int64_t M, int64_t N, int64_t ldz, hipStream_t s);
 // blocked: dZ is written as [M / 32][N / 32] blocks of 32 x 32 elements (bf16, M and N multiples of 32, ldz = N)
-void launch_b1_fused(int dt, int64_t M, int64_t N, int64_t ldz, int groups, bool table, bool blocked, const void* dY,
-                     const void* Zsave, const float* gamma, const float* mean, const float* rstd, void* dZ, void* colpart,
-                     hipStream_t s);
+void launch_b1_fused(int dt, int64_t M, int64_t N, int64_t ldz, int groups, bool blocked, const void* dY, const void* Zsave,
+                     const float* gamma, const float* mean, const float* rstd, void* dZ, void* colpart, hipStream_t s);
 void launch_b2(int dt, int64_t N, int groups, const void* colpart, float* dbeta, float* dgamma, float* db,
                hipStream_t s);
 // bf16: the column sums (as launch_b2) and up to two sums of fp32 split-reduction partials
@@ -154,12 +141,9 @@ bool fast_b3_supported(int64_t M, int64_t K, int64_t N);
 // B4 reduces over M: the fast kernel takes the first fast_b4_rows(M) rows; the rest (< 128) is left to the caller
 bool fast_b4_supported(int64_t M, int64_t K, int64_t N);
 int64_t fast_b4_rows(int64_t M);
-int fast_f1_stat_tile_w();
 size_t fast_f1_tail_bytes(int64_t M, int64_t K);
 // Wt: null, or the transposed weights [K][N] from launch_fast_transpose (N, K multiples of 64)
 void launch_fast_transpose(int64_t N, int64_t K, const void* W, void* Wt, hipStream_t s);
-void launch_fast_f1(int64_t M, int64_t K, int64_t N, const void* X, const void* W, const void* Wt, const float* bias,
-                    void* Zsave, void* part, void* xtail, hipStream_t s);
 // padded mode (N, K multiples of 8 but not both of 256): see gemm_bf16.hip
 bool fast_padded_supported(int64_t M, int64_t K, int64_t N);
 int64_t fast_pad_dim(int64_t n);
@@ -167,11 +151,11 @@ size_t fast_padded_tail_bytes(int64_t K);
 int64_t fast_padded_b4_rows(int64_t M, int64_t K);
 void launch_fast_pad_weights(int64_t K, int64_t N, const void* W, const float* bias, void* Wp, float* biasp, hipStream_t s);
 void launch_fast_f1_padded(int64_t M, int64_t K, int64_t N, const void* X, const void* Wp, const float* biasp, void* Zsave,
-                           void* part, void* xtail, hipStream_t s);
+                           void* xtail, hipStream_t s);
 void launch_fast_b3_padded(int64_t M, int64_t K, int64_t N, const void* dZ, const void* Wp, void* dX, hipStream_t s);
 void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, const void* dZ, const void* X, void* dwpart,
                            hipStream_t s);
-// sibling operators on the forward product's kernel (see gemm_bf16.hip); shapes as fast_f1_supported;
+// the forward product, also of the sibling operators (see gemm_bf16.hip); shapes as fast_f1_supported;
 // Wt: null, or the transposed weights from launch_fast_transpose
 constexpr int64_t kTransposeFromRows = 16384;   // batch size from which transposing the weights first pays
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,

@@ -1,5 +1,4 @@
-// Streaming (HBM-bound) phases of the fused dense-layer block: LayerNorm statistics merge and
-// normalisation (forward), the LayerNorm/GELU gradient row pass with its column partial sums
+// Streaming (HBM-bound) phases of the fused dense-layer block: row statistics and normalisation (forward), the LayerNorm/GELU gradient row pass with its column partial sums
 // (backward), and the column reduction that finishes dbeta, dgamma, db.
 //
 // Row reductions follow the idiom of the paper's row-normalisation kernels (appendix "Highlighted CUDA
@@ -16,99 +15,28 @@ namespace fdl {
 namespace {
 
 // ------------------------------------------------------------------------------------------------
-// FS: merge per-(row, column tile) partial (mean, sum of squared deviations) pairs with the pairwise
-// update of Chan et al., in fp64.  part is [tiles][M].  Sixteen lanes share a row: lane l merges tiles l, l + 16, ...
-// in order, then the sixteen (count, mean, M2) triples are merged pairwise across the lanes - the update is
-// associative, and with one thread per row a matrix of a few thousand rows kept a dozen workgroups busy with a
-// serial chain of fp64 divisions per tile.
-struct Moments { double n, mu, m2; };
-__device__ __forceinline__ Moments merge_moments(const Moments& a, const Moments& b) {
-  Moments r;
-  r.n = a.n + b.n;
-  const double d = b.mu - a.mu, w = r.n > 0.0 ? b.n / r.n : 0.0;
-  r.mu = a.mu + d * w;
-  r.m2 = a.m2 + b.m2 + d * d * a.n * w;
-  return r;
-}
-__global__ __launch_bounds__(256) void stats_finalize_kernel(const f32x2* __restrict__ part, int tiles, int tile_w,
-                                                             int64_t M, int64_t N, float eps,
-                                                             float* __restrict__ mean, float* __restrict__ rstd) {
-  constexpr int kLanes = 16;
-  const int l = threadIdx.x & (kLanes - 1);
-  const int64_t m = (int64_t)blockIdx.x * (256 / kLanes) + (threadIdx.x / kLanes);
-  const int64_t mc = m < M ? m : M - 1;      // lanes past the last row redo it (no early exit before the shuffles)
-  Moments acc = {0.0, 0.0, 0.0};
-  for (int t = l; t < tiles; t += kLanes) {
-    int64_t nb = N - (int64_t)t * tile_w;
-    if (nb <= 0) break;
-    if (nb > tile_w) nb = tile_w;
-    const f32x2 p = part[(int64_t)t * M + mc];
-    const Moments x = {(double)nb, (double)p[0], (double)p[1]};
-    acc = merge_moments(acc, x);
-  }
-#pragma unroll
-  for (int k = 1; k < kLanes; k <<= 1) {
-    Moments o;
-    o.n = __shfl_xor(acc.n, k, kWave); o.mu = __shfl_xor(acc.mu, k, kWave); o.m2 = __shfl_xor(acc.m2, k, kWave);
-    // both lanes of a pair merge the same two triples in the same order (lower lane's first)
-    acc = (l & k) ? merge_moments(o, acc) : merge_moments(acc, o);
-  }
-  if (l == 0 && m < M) {
-    mean[m] = (float)acc.mu;
-    rstd[m] = (float)(1.0 / sqrt(acc.m2 / (double)N + (double)eps));
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// F2: Y = (GELU(Zsave) - mean) * rstd * gamma + beta.  A workgroup owns a strip of 256*V columns and a
-// block of rows; gamma and beta for the thread's V columns stay in registers across the rows.
-template <class T, int V>
-// (Z and Y may be the same buffer - the forward-only entry point normalises in place; each element is read by the
-// thread that writes it, before it writes it - so the two are not declared restrict.)
-__global__ __launch_bounds__(256) void f2_kernel(int64_t M, int64_t N, int rows_per_wg, int strips,
-                                                 const T* Z, const float* __restrict__ mean,
-                                                 const float* __restrict__ rstd, const float* __restrict__ gamma,
-                                                 const float* __restrict__ beta, T* Y) {
-  typedef typename ComputeOf<T>::type C;
-  const int strip = blockIdx.x % strips;
-  const int64_t rb = blockIdx.x / strips;
-  const int64_t col = ((int64_t)strip * 256 + threadIdx.x) * V;
-  if (col >= N) return;
-  C gm[V], bt[V];
-#pragma unroll
-  for (int v = 0; v < V; v++) { gm[v] = (C)gamma[col + v]; bt[v] = (C)beta[col + v]; }
-  const int64_t r0 = rb * rows_per_wg;
-  int64_t r1 = r0 + rows_per_wg;
-  if (r1 > M) r1 = M;
-#pragma unroll 4
-  for (int64_t r = r0; r < r1; r++) {
-    C z[V], y[V];
-    VecIO<T, V>::load(Z + r * N + col, z);
-    const C mu = (C)mean[r], rs = (C)rstd[r];
-#pragma unroll
-    for (int v = 0; v < V; v++) y[v] = (gelu<C>(z[v]) - mu) * rs * gm[v] + bt[v];
-    VecIO<T, V>::store(Y + r * N + col, y);
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// F2 with its own statistics (bf16 storage, N % 8 == 0, N <= 512 CH): a wavefront owns a row and keeps it in
+// F2 with its own statistics, narrow rows (bf16 storage, N <= 512 CH): a wavefront owns a row and keeps it in
 // registers over three sweeps (GELU and sum; deviations and their squares; scale, shift, store), so Zsave is read
 // once, no partial statistics pass through memory and no barrier separates the sweeps.  Lane l holds the 8-element
 // vectors c*64 + l, c < CH, of its row (every load and store of a wavefront covers 1 KB of one row); the next
 // row's vectors are fetched while the current row is processed.  gamma and beta sit in LDS, permuted so that a
 // lane's four 16-byte reads per vector are lane-contiguous.  Workgroups of NT/64 wavefronts walk the rows with
 // stride (8 wavefronts; 4 for the widest masked variant, whose extra per-vector state needs the larger register
-// budget of one wavefront per SIMD).
-// FULL: N == 512 CH, every lane holds every vector.  Otherwise the vectors past the end of the row are fetched
-// from a clamped address, masked to zero (GELU(0) = 0 adds nothing to the sum), left out of the squared
-// deviations and never stored; the code stays free of divergent branches either way.
+// budget of one wavefront per SIMD).  WPR = 2: two neighbouring wavefronts share a row of up to 16384 and exchange their
+// sums through LDS (as a workgroup of 1024 threads per row the same normalisation of 4096 x 16384 took 66 - 89 us: its two
+// reductions stop every wavefront of the compute unit).
+// FIT_FULL: N == 512 CH, every lane holds every vector.  FIT_VECTORS (N % 8 == 0): the vectors past the end of the row
+// are fetched from a clamped address, masked to zero (GELU(0) = 0 adds nothing to the sum), left out of the squared
+// deviations and never stored; the code stays free of divergent branches either way.  FIT_ANY: rows start at any element
+// and end inside a vector - the same 16-byte loads and stores from element-aligned addresses (the hardware splits what
+// straddles a line), the row's last, partial vector element by element by the one lane that holds it.
 // ACT selects what is normalised: ACT_GELU the GELU of the input (the block's second forward phase; Z and Y may then
 // be the same buffer - a lane reads its part of a row before it writes it - so they are not declared restrict),
 // ACT_NONE the input itself (stand-alone LayerNorm forward), ACT_RMS the input without mean subtraction and without
 // beta (RMSNorm forward: y = x (mean(x^2) + eps)^-1/2 w; mean and rstd are not written).
 enum { ACT_GELU = 0, ACT_NONE = 1, ACT_RMS = 2 };
-template <int CH, bool FULL, int NT, int ACT>
+enum { FIT_FULL = 0, FIT_VECTORS = 1, FIT_ANY = 2 };
+template <int CH, int FIT, int NT, int ACT, int WPR>
 __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float eps, const bf16_t* Z,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
                                                       bf16_t* Y, float* __restrict__ mean,
@@ -116,19 +44,33 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   // products are formed once and reused (fusing GELU's final multiplication into each later use would keep
   // both of its factors alive for every element of the row); the fused operations wanted are written out
 #pragma clang fp contract(off)
-  extern __shared__ f32x4 gb[];   // [CH][4][64]: gamma[0:4], gamma[4:8], beta[0:4], beta[4:8] of vector c*64 + lane
+  constexpr bool FULL = FIT == FIT_FULL, ANY = FIT == FIT_ANY;
+  typedef __bf16 bf16x8_u __attribute__((ext_vector_type(8), aligned(2)));
+  typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
+  extern __shared__ f32x4 gb[];   // [CH * WPR][4][64]: gamma[0:4], gamma[4:8], beta[0:4], beta[4:8] of each vector
+  __shared__ float pair[2][NT / 64];
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
   typedef GaussTable<false> GT;
   typedef __attribute__((address_space(3))) float lds_float;
-  float* htab = reinterpret_cast<float*>(gb + CH * 4 * 64);           // Phi - 1/2 for every bf16 magnitude
+  float* htab = reinterpret_cast<float*>(gb + CH * WPR * 4 * 64);     // Phi - 1/2 for every bf16 magnitude
   const uint32_t horg = GT::origin((uint32_t)(uintptr_t)(const lds_float*)htab);
   if (ACT == ACT_GELU) GT::build(htab, threadIdx.x, NT);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: row addresses stay scalar
-  const int nvec = (int)(N >> 3);
-  for (int idx = threadIdx.x; idx < CH * 64; idx += NT) {
-    const int64_t src = (int64_t)(idx < nvec ? idx : nvec - 1) * 8;
+  const int nvec = (int)(N >> 3);              // whole vectors of a row
+  const int rest = ANY ? (int)(N & 7) : 0;     // elements of its partial one
+  for (int idx = threadIdx.x; idx < CH * WPR * 64; idx += NT) {
     const int c = idx >> 6, l = idx & 63;
+    if (ANY && idx >= nvec) {
+      const int have = idx == nvec ? rest : 0;
+      float* dst = reinterpret_cast<float*>(gb);
+      for (int e = 0; e < 8; e++) {
+        dst[((c * 4 + (e >> 2)) * 64 + l) * 4 + (e & 3)] = e < have ? gamma[(int64_t)idx * 8 + e] : 0.0f;
+        if (ACT != ACT_RMS) dst[((c * 4 + 2 + (e >> 2)) * 64 + l) * 4 + (e & 3)] = e < have ? beta[(int64_t)idx * 8 + e] : 0.0f;
+      }
+      continue;
+    }
+    const int64_t src = (int64_t)(idx < nvec ? idx : nvec - 1) * 8;
     gb[(c * 4 + 0) * 64 + l] = *reinterpret_cast<const f32x4*>(gamma + src);
     gb[(c * 4 + 1) * 64 + l] = *reinterpret_cast<const f32x4*>(gamma + src + 4);
     if (ACT != ACT_RMS) {
@@ -137,16 +79,31 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
     }
   }
   __syncthreads();
-  const int64_t nw = (int64_t)gridDim.x * (NT / 64);
+  const int64_t nw = (int64_t)gridDim.x * (NT / 64 / WPR);
   const float inv_n = 1.0f / (float)N;
-  // per-lane element offset of vector c inside a row, and whether the row has that vector
-  int voff[CH];
+  const int sub = WPR == 1 ? 0 : wave % WPR;   // which part of every vector group this wavefront of the row holds
+  // sum over the wavefronts of a row (pass k of a row: slot k; see the loop on why one barrier each is enough)
+  auto row_sum = [&](float x, int k) -> float {
+    x = wave_sum(x);
+    if constexpr (WPR > 1) {
+      if (lane == 0) pair[k][wave] = x;
+      __syncthreads();
+      x = pair[k][wave - sub];
+#pragma unroll
+      for (int w = 1; w < WPR; w++) x += pair[k][wave - sub + w];
+    }
+    return x;
+  };
+  // per-lane element offset of vector c inside a row, and whether the row has that vector (FIT_ANY: how many of its
+  // elements)
+  int voff[CH], have[CH];
   uint32_t keep[CH];
 #pragma unroll
   for (int c = 0; c < CH; c++) {
-    const int vi = c * 64 + lane;
-    voff[c] = (FULL || vi < nvec ? vi : nvec - 1) * 8;
+    const int vi = (c * WPR + sub) * 64 + lane;
+    voff[c] = (FULL || vi < nvec ? vi : (ANY ? 0 : nvec - 1)) * 8;
     keep[c] = (FULL || vi < nvec) ? 0xffffffffu : 0u;
+    have[c] = vi < nvec ? 8 : (vi == nvec ? rest : 0);
   }
 
   u32x4 raw[CH];
@@ -154,20 +111,36 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   auto fetch1 = [&](int c, const bf16_t* zr) {
     if (FULL) {
       // scalar base per vector + one shared per-lane offset (the immediate offset field reaches only 4 KB)
-      const bf16_t* zc = zr + c * 512;
+      const bf16_t* zc = zr + (c * WPR + sub) * 512;
       asm("" : "+s"(zc));
       raw[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(zc + lane * 8));
+    } else if (ANY) {
+      if (have[c] == 8) {
+        raw[c] = *reinterpret_cast<const u32x4_u*>(zr + voff[c]);
+      } else {
+        raw[c] = u32x4{0u, 0u, 0u, 0u};
+        if (have[c] != 0) {
+          bf16x8 t;
+#pragma unroll
+          for (int v = 0; v < 8; v++) t[v] = v < have[c] ? zr[nvec * 8 + v] : (bf16_t)0.0f;
+          raw[c] = __builtin_bit_cast(u32x4, t);
+        }
+      }
     } else {
       raw[c] = *reinterpret_cast<const u32x4*>(zr + voff[c]);
     }
   };
-  int64_t row = (int64_t)blockIdx.x * (NT / 64) + wave;
+  int64_t row = (int64_t)blockIdx.x * (NT / 64 / WPR) + wave / WPR;
   {
     const bf16_t* zr = Z + (row < M ? row : M - 1) * N;
 #pragma unroll
     for (int c = 0; c < CH; c++) fetch1(c, zr);
   }
-  for (; row < M; row += nw) {
+  // Where wavefronts share rows, those of a workgroup stay together (barriers): the last trip may find some of them past
+  // the last row, which they then redo without storing.  A sum's slot is written again only after the barrier of the
+  // other sum, which every wavefront reaches after it has read the slot.
+  for (int64_t lead = (int64_t)blockIdx.x * (NT / 64 / WPR); WPR == 1 ? row < M : lead < M; row += nw, lead += nw) {
+    const bool live = WPR == 1 || row < M;
     float a[CH][8];
     float sum = 0.0f;
     const bf16_t* znext = Z + (row + nw < M ? row + nw : M - 1) * N;
@@ -175,7 +148,7 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
     for (int c = 0; c < CH; c++) {
 #pragma unroll
       for (int h = 0; h < 4; h++) {
-        const uint32_t w = FULL ? raw[c][h] : (raw[c][h] & keep[c]);
+        const uint32_t w = (FULL || ANY) ? raw[c][h] : (raw[c][h] & keep[c]);
         const float z0 = __builtin_bit_cast(float, w << 16);                        // bf16 -> fp32 is a 16-bit shift
         const float z1 = __builtin_bit_cast(float, w & 0xffff0000u);
         if (ACT == ACT_GELU) {
@@ -205,25 +178,27 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
     }
     float rs;
     if (ACT == ACT_RMS) {
-      rs = 1.0f / __builtin_sqrtf(wave_sum(sum) * inv_n + eps);     // masked vectors hold zeros: they add nothing
+      rs = 1.0f / __builtin_sqrtf(row_sum(sum, 0) * inv_n + eps);   // masked vectors hold zeros: they add nothing
     } else {
-      const float mu = wave_sum(sum) * inv_n;
+      const float mu = row_sum(sum, 0) * inv_n;
       float m2 = 0.0f;
 #pragma unroll
       for (int c = 0; c < CH; c++)
 #pragma unroll
         for (int v = 0; v < 8; v++) {
           const float d = a[c][v] - mu;
-          a[c][v] = FULL ? d : (keep[c] ? d : 0.0f);
+          a[c][v] = FULL ? d : ((ANY ? v < have[c] : keep[c] != 0u) ? d : 0.0f);
           m2 = __builtin_fmaf(a[c][v], a[c][v], m2);
         }
-      rs = 1.0f / __builtin_sqrtf(wave_sum(m2) * inv_n + eps);
-      if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
+      rs = 1.0f / __builtin_sqrtf(row_sum(m2, 1) * inv_n + eps);
+      if (lane == 0 && sub == 0 && live) { mean[row] = mu; rstd[row] = rs; }
     }
+    if (!live) continue;
     bf16_t* yr = Y + row * N;
 #pragma unroll
     for (int c = 0; c < CH; c++) {
-      const f32x4 g0 = gb[(c * 4 + 0) * 64 + lane], g1 = gb[(c * 4 + 1) * 64 + lane];
+      const int cg = c * WPR + sub;
+      const f32x4 g0 = gb[(cg * 4 + 0) * 64 + lane], g1 = gb[(cg * 4 + 1) * 64 + lane];
       bf16x8 o;
       if (ACT == ACT_RMS) {
 #pragma unroll
@@ -232,7 +207,7 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
           o[v + 4] = (bf16_t)(a[c][v + 4] * rs * g1[v]);
         }
       } else {
-        const f32x4 b0 = gb[(c * 4 + 2) * 64 + lane], b1 = gb[(c * 4 + 3) * 64 + lane];
+        const f32x4 b0 = gb[(cg * 4 + 2) * 64 + lane], b1 = gb[(cg * 4 + 3) * 64 + lane];
 #pragma unroll
         for (int v = 0; v < 4; v++) {
           o[v] = (bf16_t)__builtin_fmaf(a[c][v] * rs, g0[v], b0[v]);
@@ -240,11 +215,16 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
         }
       }
       if (FULL) {
-        bf16_t* yc = yr + c * 512;
+        bf16_t* yc = yr + (c * WPR + sub) * 512;
         asm("" : "+s"(yc));
         __builtin_nontemporal_store(o, reinterpret_cast<bf16x8*>(yc + lane * 8));
       } else if (keep[c]) {
-        *reinterpret_cast<bf16x8*>(yr + voff[c]) = o;
+        if (ANY) *reinterpret_cast<bf16x8_u*>(yr + voff[c]) = o;
+        else *reinterpret_cast<bf16x8*>(yr + voff[c]) = o;
+      } else if (ANY && have[c] != 0) {
+#pragma unroll
+        for (int v = 0; v < 8; v++)
+          if (v < have[c]) yr[nvec * 8 + v] = o[v];
       }
       __builtin_amdgcn_sched_barrier(0);   // keep the LDS reads of later vectors from being hoisted (registers)
     }
@@ -274,26 +254,113 @@ template <class C, int NW> __device__ __forceinline__ void wg_sum2(C& a, C& b, C
   }
 }
 
-// B1a (two-kernel path): c1_i = mean_j g_ij, c2_i = mean_j g_ij Ahat_ij with g = dY gamma.
-template <class T, int V>
+// nv of V consecutive column sums of a thread to memory, 16 bytes at a time from an element-aligned address (one 4-byte
+// store per column and wavefront touches sixteen lines for 256 bytes: a workgroup's 3 N sums took longer than a row)
+template <class C, int V> __device__ __forceinline__ void store_columns(C* p, const C (&a)[V], int nv) {
+  constexpr int W = 16 / (int)sizeof(C);
+  typedef C vec_t __attribute__((ext_vector_type(W), aligned(sizeof(C))));
+  if (nv == V) {
+#pragma unroll
+    for (int h = 0; h < V / W; h++) {
+      vec_t t;
+#pragma unroll
+      for (int e = 0; e < W; e++) t[e] = a[h * W + e];
+      *reinterpret_cast<vec_t*>(p + h * W) = t;
+    }
+  } else {
+#pragma unroll
+    for (int v = 0; v < V; v++)
+      if (v < nv) p[v] = a[v];
+  }
+}
+
+// A row's vectors of 16 bytes.  ANY: rows start at any element and end inside a vector - the same 16-byte accesses from
+// element-aligned addresses (the hardware splits what straddles a line), the last, partial vector element by element.
+template <class T, bool ANY> struct RawVec;
+template <> struct RawVec<float, false> { typedef f32x4 type; };
+template <> struct RawVec<bf16_t, false> { typedef bf16x8 type; };
+template <> struct RawVec<float, true> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct RawVec<bf16_t, true> { typedef __bf16 type __attribute__((ext_vector_type(8), aligned(2))); };
+
+template <class T, bool ANY>
+__device__ __forceinline__ typename RawVec<T, ANY>::type raw_load(const T* p, int nv) {
+  typedef typename RawVec<T, ANY>::type raw_t;
+  constexpr int V = 16 / (int)sizeof(T);
+  if (!ANY || nv == V) return __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(p));
+  raw_t r;
+#pragma unroll
+  for (int v = 0; v < V; v++) r[v] = v < nv ? p[v] : (T)0.0f;
+  return r;
+}
+// the same without the streaming hint (the two-kernel path reads its rows twice)
+template <class T, bool ANY>
+__device__ __forceinline__ typename RawVec<T, ANY>::type row_load(const T* p, int nv) {
+  typedef typename RawVec<T, ANY>::type raw_t;
+  constexpr int V = 16 / (int)sizeof(T);
+  if (!ANY || nv == V) return *reinterpret_cast<const raw_t*>(p);
+  raw_t r;
+#pragma unroll
+  for (int v = 0; v < V; v++) r[v] = v < nv ? p[v] : (T)0.0f;
+  return r;
+}
+template <class T, bool ANY> __device__ __forceinline__ void row_store(T* p, typename RawVec<T, ANY>::type o, int nv) {
+  typedef typename RawVec<T, ANY>::type raw_t;
+  constexpr int V = 16 / (int)sizeof(T);
+  if (!ANY || nv == V) {
+    *reinterpret_cast<raw_t*>(p) = o;
+  } else {
+#pragma unroll
+    for (int v = 0; v < V; v++)
+      if (v < nv) p[v] = o[v];
+  }
+}
+// nv elements of the row, then zeros up to the end of the pitch (left: elements from here to there): the surplus columns
+// of a padded dZ enter the contractions that read it
+template <class T, bool ANY>
+__device__ __forceinline__ void raw_store(T* p, typename RawVec<T, ANY>::type o, int nv, int64_t left) {
+  typedef typename RawVec<T, ANY>::type raw_t;
+  constexpr int V = 16 / (int)sizeof(T);
+  if (!ANY || left >= V) {
+    __builtin_nontemporal_store(o, reinterpret_cast<raw_t*>(p));
+  } else {
+#pragma unroll
+    for (int v = 0; v < V; v++)
+      if (v < left) p[v] = o[v];
+  }
+}
+
+// B1a (two-kernel path, rows too long for one workgroup's registers): c1_i = mean_j g_ij, c2_i = mean_j g_ij Ahat_ij with
+// g = dY gamma.
+template <class T, bool ANY>
 __global__ __launch_bounds__(256) void b1a_kernel(int64_t M, int64_t N, const T* __restrict__ dY,
                                                   const T* __restrict__ Z, const float* __restrict__ gamma,
                                                   const float* __restrict__ mean, const float* __restrict__ rstd,
                                                   typename ComputeOf<T>::type* __restrict__ c12) {
   typedef typename ComputeOf<T>::type C;
+  constexpr int V = 16 / (int)sizeof(T);
   __shared__ C red[2][4][2];
+  ActTable<T, false, 256> tab;
+  tab.build();
   int par = 0;
   for (int64_t row = blockIdx.x; row < M; row += gridDim.x, par ^= 1) {
     const C mu = (C)mean[row], rs = (C)rstd[row];
     C s1 = 0, s2 = 0;
     for (int64_t col = (int64_t)threadIdx.x * V; col < N; col += 256 * V) {
-      C dy[V], z[V];
-      VecIO<T, V>::load(dY + row * N + col, dy);
-      VecIO<T, V>::load(Z + row * N + col, z);
+      const int nv = !ANY || N - col > V ? V : (int)(N - col);
+      const auto dy = row_load<T, ANY>(dY + row * N + col, nv);
+      const auto z = row_load<T, ANY>(Z + row * N + col, nv);
+      float gm[V];
+      if (nv == V) {
+#pragma unroll
+        for (int v = 0; v < V; v++) gm[v] = gamma[col + v];
+      } else {
+#pragma unroll
+        for (int v = 0; v < V; v++) gm[v] = v < nv ? gamma[col + v] : 0.0f;
+      }
 #pragma unroll
       for (int v = 0; v < V; v++) {
-        const C g = dy[v] * (C)gamma[col + v];
-        const C ah = (gelu<C>(z[v]) - mu) * rs;
+        const C g = (C)to_f32<T>(dy[v]) * (C)gm[v];
+        const C ah = (tab.gelu((C)to_f32<T>(z[v])) - mu) * rs;
         s1 += g;
         s2 += g * ah;
       }
@@ -303,8 +370,18 @@ __global__ __launch_bounds__(256) void b1a_kernel(int64_t M, int64_t N, const T*
   }
 }
 
+__device__ __forceinline__ float read_lane(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+__device__ __forceinline__ double read_lane(double v, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // B1b (two-kernel path): dZ and column partials, given c1 and c2.
-template <class T, int V>
+template <class T, bool ANY>
 __global__ __launch_bounds__(256) void b1b_kernel(int64_t M, int64_t N, int64_t ldz, int rows_per_group, int strips,
                                                   const T* __restrict__ dY, const T* __restrict__ Z,
                                                   const float* __restrict__ gamma, const float* __restrict__ mean,
@@ -312,222 +389,214 @@ __global__ __launch_bounds__(256) void b1b_kernel(int64_t M, int64_t N, int64_t 
                                                   const typename ComputeOf<T>::type* __restrict__ c12,
                                                   T* __restrict__ dZ, typename ComputeOf<T>::type* __restrict__ colpart) {
   typedef typename ComputeOf<T>::type C;
+  typedef typename RawVec<T, ANY>::type raw_t;
+  constexpr int V = 16 / (int)sizeof(T);
   const int strip = blockIdx.x % strips;
   const int64_t grp = blockIdx.x / strips;
   const int64_t col = ((int64_t)strip * 256 + threadIdx.x) * V;
-  if (col >= N) return;
+  ActTable<T, true, 256> tab;
+  tab.build();
+  // (threads past the end of the row stay: their lanes hold scalars of the group's rows)
+  const int nv = col >= N ? 0 : (!ANY || N - col > V ? V : (int)(N - col));
   C gm[V], accb[V], accg[V], accz[V];
 #pragma unroll
-  for (int v = 0; v < V; v++) { gm[v] = (C)gamma[col + v]; accb[v] = 0; accg[v] = 0; accz[v] = 0; }
+  for (int v = 0; v < V; v++) { gm[v] = v < nv ? (C)gamma[col + v] : (C)0; accb[v] = 0; accg[v] = 0; accz[v] = 0; }
   const int64_t r0 = grp * rows_per_group;
   int64_t r1 = r0 + rows_per_group;
   if (r1 > M) r1 = M;
-#pragma unroll 2
-  for (int64_t r = r0; r < r1; r++) {
-    C dy[V], z[V], dz[V];
-    VecIO<T, V>::load(dY + r * N + col, dy);
-    VecIO<T, V>::load(Z + r * N + col, z);
-    const C mu = (C)mean[r], rs = (C)rstd[r], c1 = c12[r], c2 = c12[M + r];
+  // lane l holds the four scalars of row r0 + 64 k + l (read row by row they would be scalar loads, which every wait for
+  // the table's LDS reads waits for)
+  const int lane = threadIdx.x & 63;
+  float lmu = 0.0f, lrs = 0.0f;
+  C lc1 = 0, lc2 = 0;
+  // two rows of loads in flight
+  raw_t rdy[2], rz[2];
+#pragma unroll
+  for (int v = 0; v < V; v++) { rdy[0][v] = rdy[1][v] = (T)0.0f; rz[0][v] = rz[1][v] = (T)0.0f; }
+  auto fetch = [&](int k, int64_t r) {
+    if (r < r1 && nv > 0) {
+      rdy[k] = row_load<T, ANY>(dY + r * N + col, nv);
+      rz[k] = row_load<T, ANY>(Z + r * N + col, nv);
+    }
+  };
+  auto process = [&](int k, int64_t r) {
+    const int at = (int)(r - r0) & 63;
+    if (at == 0) {
+      const int64_t q = r + lane < M ? r + lane : M - 1;
+      lmu = mean[q]; lrs = rstd[q]; lc1 = c12[q]; lc2 = c12[M + q];
+    }
+    const C mu = (C)read_lane(lmu, at), rs = (C)read_lane(lrs, at), c1 = read_lane(lc1, at), c2 = read_lane(lc2, at);
+    raw_t o;
 #pragma unroll
     for (int v = 0; v < V; v++) {
-      C Phi, phi;
-      Gauss<C>::eval(z[v], Phi, phi);
-      const C ah = (Gauss<C>::gelu_of(z[v], Phi) - mu) * rs;
-      const C g = dy[v] * gm[v];
-      dz[v] = rs * (g - c1 - ah * c2) * (Phi + z[v] * phi);
-      accb[v] += dy[v];
-      accg[v] += dy[v] * ah;
-      accz[v] += dz[v];
+      const C z = (C)to_f32<T>(rz[k][v]), dy = (C)to_f32<T>(rdy[k][v]);
+      C Phi, zphi;
+      tab.eval(z, Phi, zphi);
+      const C ah = (z * Phi - mu) * rs;
+      C dz = rs * (dy * gm[v] - c1 - ah * c2) * (Phi + zphi);
+      if (ANY) dz = v < nv ? dz : (C)0;
+      accb[v] += dy;
+      accg[v] += dy * ah;
+      accz[v] += dz;
+      o[v] = to_storage<T, C>(dz);
     }
-    VecIO<T, V>::store(dZ + r * ldz + col, dz);
+    fetch(k, r + 2);
+    if (nv > 0) row_store<T, ANY>(dZ + r * ldz + col, o, nv);
+  };
+  fetch(0, r0);
+  fetch(1, r0 + 1);
+  for (int64_t r = r0; r < r1; r += 2) {
+    process(0, r);
+    if (r + 1 < r1) process(1, r + 1);
   }
-#pragma unroll
-  for (int v = 0; v < V; v++) {
-    colpart[(grp * 3 + 0) * N + col + v] = accb[v];
-    colpart[(grp * 3 + 1) * N + col + v] = accg[v];
-    colpart[(grp * 3 + 2) * N + col + v] = accz[v];
-  }
+  if (nv == 0) return;
+  store_columns<C, V>(colpart + (grp * 3 + 0) * N + col, accb, nv);
+  store_columns<C, V>(colpart + (grp * 3 + 1) * N + col, accg, nv);
+  store_columns<C, V>(colpart + (grp * 3 + 2) * N + col, accz, nv);
 }
 
 // ------------------------------------------------------------------------------------------------
-// B1 fused: one pass, the row held in registers (S strips of NT*V columns, NT threads).  A workgroup walks rows
-// blockIdx.x, blockIdx.x + gridDim.x, ... ; two rows of loads are in flight while a row is processed; one barrier
-// per row (the LDS exchange slot alternates between consecutive rows).
-template <class T, int V> struct RawVec;
-template <> struct RawVec<float, 4> { typedef f32x4 type; };
-template <> struct RawVec<float, 1> { typedef float type; };
-template <> struct RawVec<bf16_t, 8> { typedef bf16x8 type; };
-template <> struct RawVec<bf16_t, 1> { typedef bf16_t type; };
-
-// Row data is used once per pass and is far larger than the caches: loads and stores of the big row-major
-// tensors carry the non-temporal hint.
-template <class T, int V> __device__ __forceinline__ typename RawVec<T, V>::type raw_load(const T* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const typename RawVec<T, V>::type*>(p));
-}
-template <class T, int V, class C> __device__ __forceinline__ C raw_get(const typename RawVec<T, V>::type& r, int v) {
-  if constexpr (V == 1) return (C)to_f32<T>(r); else return (C)to_f32<T>(r[v]);
-}
-template <class T, int V> __device__ __forceinline__ typename RawVec<T, V>::type raw_zero() {
-  typename RawVec<T, V>::type r;
-  if constexpr (V == 1) r = (T)0.0f; else { for (int v = 0; v < V; v++) r[v] = (T)0.0f; }
-  return r;
-}
-
-// TAB (bf16 only): Phi and z phi(z) come from the LDS table (exact for bf16 arguments) instead of the polynomial
-// and the hardware exponential.  The backward pass must evaluate GELU exactly as the forward pass that produced
-// mean and rstd did - for a constant row, rstd = eps^-1/2 multiplies any difference between the two into Ahat -
-// so the launcher selects TAB if and only if the forward pass normalised with the table.
-// BLK (16-byte vectors, one strip): dZ is written as [M / 32][N / 32] blocks of 32 x 32 elements, each block row-major
+// B1 fused: one pass, the row held in registers (NT threads of one 16-byte vector each).  A workgroup walks rows
+// blockIdx.x, blockIdx.x + gridDim.x, ... ; D rows of loads are in flight while a row is processed; one barrier
+// per row (the LDS exchange slot alternates between consecutive rows).  Row data is used once per pass and is far larger
+// than the caches: loads and stores of the big row-major tensors carry the non-temporal hint.
+// ANY: rows start at any element and end inside a vector - the same 16-byte accesses from element-aligned addresses, the
+// last, partial vector of a row element by element (one element per lane and access, as before, took 46 us for fp32
+// 3001 x 1537 and 15 us for bf16).
+// bf16: Phi and z phi(z) come from the LDS table, as in the forward pass's normalisation (see ActTable).
+// BLK: dZ is written as [M / 32][N / 32] blocks of 32 x 32 elements, each block row-major
 // (what the tuned dX and dW kernels read best, see gemm_bf16.hip).  A row's 16 bytes per lane are then 64-byte pieces,
 // each half of a 128-byte line whose other half belongs to the next row: the group walks rows in neighbouring pairs,
 // parks both rows' vectors in a per-wave LDS area and stores whole lines (lanes 8j .. 8j+3 the even row's piece j,
 // lanes 8j+4 .. 8j+7 the odd row's).  Half-line stores straight from the registers cost the phase a third of its
 // bandwidth (0.55 -> 0.73 ms on 65536 x 8192), halves merged in the L2 still a tenth.
-template <class T, int V, int S, int NT, bool TAB, bool BLK = false>
+template <class T, int NT, bool ANY, bool BLK = false>
 __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int64_t ldz, const T* __restrict__ dY,
                                                        const T* __restrict__ Z, const float* __restrict__ gamma,
                                                        const float* __restrict__ mean, const float* __restrict__ rstd,
                                                        T* __restrict__ dZ,
                                                        typename ComputeOf<T>::type* __restrict__ colpart) {
   typedef typename ComputeOf<T>::type C;
-  typedef typename RawVec<T, V>::type raw_t;
-  typedef GaussTable<true> GT;
-  typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
-  static_assert(!BLK || (V * sizeof(T) == 16 && S == 1), "blocked output: 16-byte vectors, one strip");
-  constexpr bool blocked = BLK;
+  typedef typename RawVec<T, ANY>::type raw_t;
+  constexpr int V = 16 / (int)sizeof(T), D = 2;
+  static_assert(!BLK || (sizeof(T) == 2 && !ANY), "blocked output: bf16, whole vectors");
   __shared__ C red[2][NT / 64][2];
-  __shared__ __attribute__((aligned(8))) float gtab[TAB ? 2 * GT::kEntries : 2];
   __shared__ __attribute__((aligned(16))) raw_t park[BLK ? NT / 64 : 1][2][BLK ? 64 : 1];   // [wave][row of the pair][lane]
-  uint32_t gorg = 0;
-  if (TAB) {
-    GT::build(gtab, threadIdx.x, NT);
-    gorg = GT::origin((uint32_t)(uintptr_t)(const lds_f32x2*)gtab);
-    __syncthreads();
-  }
-  int64_t col[S];
-  bool ok[S];
-  C gm[S][V], accb[S][V], accg[S][V], accz[S][V];
+  ActTable<T, true, NT> tab;
+  tab.build();
+  const int64_t col = (int64_t)threadIdx.x * V;
+  const int nv = col >= N ? 0 : (N - col > V ? V : (int)(N - col));
+  const int64_t left = ldz - col;              // columns of dZ this thread and those behind it write
+  C gm[V], accb[V], accg[V], accz[V];
 #pragma unroll
-  for (int s = 0; s < S; s++) {
-    col[s] = ((int64_t)s * NT + threadIdx.x) * V;
-    ok[s] = col[s] < N;
+  for (int v = 0; v < V; v++) { gm[v] = 0; accb[v] = 0; accg[v] = 0; accz[v] = 0; }
+  if (nv == V) {
 #pragma unroll
-    for (int v = 0; v < V; v++) {
-      gm[s][v] = ok[s] ? (C)gamma[col[s] + v] : (C)0;
-      accb[s][v] = 0; accg[s][v] = 0; accz[s][v] = 0;
-    }
+    for (int v = 0; v < V; v++) gm[v] = (C)gamma[col + v];
+  } else {
+#pragma unroll
+    for (int v = 0; v < V; v++)
+      if (v < nv) gm[v] = (C)gamma[col + v];
   }
-  // Two rows are kept in flight: buffers 0 and 1 hold the raw rows r and r + G (G = gridDim.x; r and r + 1 where dZ
-  // is blocked); as soon as a buffer has been unpacked its refill with the row 2G further on is issued, ahead of that
-  // row's barrier and second phase.
-  raw_t bdy[2][S], bz[2][S];
+  // D rows are kept in flight, one per buffer; as soon as a buffer has been unpacked its refill with the row D G further
+  // on is issued (G = gridDim.x), ahead of that row's barrier and second phase.  mean and rstd travel with the row, as
+  // vector loads (zero is a register the compiler cannot see through): a scalar load at the head of the row's work would
+  // be waited for there.
+  raw_t bdy[D], bz[D];
+  float bmu[D], brs[D];
+  int zero = 0;
+  asm volatile("" : "+v"(zero));
   const int64_t G = gridDim.x;
   auto fetch = [&](int buf, int64_t r) {
     if (r < M) {
-#pragma unroll
-      for (int s = 0; s < S; s++) {
-        if (ok[s]) { bdy[buf][s] = raw_load<T, V>(dY + r * N + col[s]); bz[buf][s] = raw_load<T, V>(Z + r * N + col[s]); }
+      bmu[buf] = mean[r + zero];
+      brs[buf] = rstd[r + zero];
+      if (nv > 0) {
+        bdy[buf] = raw_load<T, ANY>(dY + r * N + col, nv);
+        bz[buf] = raw_load<T, ANY>(Z + r * N + col, nv);
       }
     }
   };
 #pragma unroll
-  for (int buf = 0; buf < 2; buf++)
+  for (int buf = 0; buf < D; buf++)
 #pragma unroll
-    for (int s = 0; s < S; s++) { bdy[buf][s] = raw_zero<T, V>(); bz[buf][s] = raw_zero<T, V>(); }
+    for (int v = 0; v < V; v++) { bdy[buf][v] = (T)0.0f; bz[buf][v] = (T)0.0f; }
   // Row-major dZ: the group walks rows b, b + G, b + 2G, ... .  Blocked dZ: rows 2b, 2b + 1, then 2G further on - the
   // two rows in flight are neighbours, so the two 64-byte halves of every line of dZ leave the same compute unit
   // within one row time and merge in its L2 (M is even where dZ is blocked).
-  const int64_t first = blocked ? 2 * (int64_t)blockIdx.x : (int64_t)blockIdx.x;
-  const int64_t second = blocked ? 1 : G;
-  fetch(0, first);
-  fetch(1, first + second);
+  const int64_t first = BLK ? 2 * (int64_t)blockIdx.x : (int64_t)blockIdx.x;
+  auto ahead = [&](int buf) -> int64_t { return BLK ? (buf >> 1) * 2 * G + (buf & 1) : buf * G; };
+#pragma unroll
+  for (int buf = 0; buf < D; buf++) fetch(buf, first + ahead(buf));
 
   const C inv_n = (C)1 / (C)N;
   auto process = [&](int buf, int64_t row) {
-    const C mu = (C)mean[row], rs = (C)rstd[row];
-    const C nmr = -mu * rs;
-    C ah[S][V], gp[S][V], g[S][V];
+    const C rs = (C)brs[buf], nmr = -(C)bmu[buf] * rs;
+    C ah[V], gp[V], g[V];
     C s1 = 0, s2 = 0;
 #pragma unroll
-    for (int s = 0; s < S; s++)
-#pragma unroll
-      for (int v = 0; v < V; v++) {
-        const C z = raw_get<T, V, C>(bz[buf][s], v);
-        const C dy = raw_get<T, V, C>(bdy[buf][s], v);
-        if constexpr (TAB) {
-          const uint32_t zbits = __builtin_bit_cast(uint32_t, (float)z) >> 16;      // the bf16 bits of z
-          const f32x2 e = *(const lds_f32x2*)(uintptr_t)GT::address_of(zbits, gorg);
-          const float Phi = 0.5f + GT::with_sign_of(e[0], (float)z);
-          ah[s][v] = ((float)z * Phi) * rs + nmr;
-          gp[s][v] = (Phi + GT::with_sign_of(e[1], (float)z)) * rs;
-        } else {
-          C Phi, phi;
-          Gauss<C>::eval(z, Phi, phi);
-          ah[s][v] = Gauss<C>::gelu_of(z, Phi) * rs + nmr;   // (A - mean) rstd, one fused multiply-add
-          gp[s][v] = (Phi + z * phi) * rs;
-        }
-        g[s][v] = dy * gm[s][v];
-        s1 += g[s][v];
-        s2 += g[s][v] * ah[s][v];
-        accb[s][v] += dy;
-        accg[s][v] += dy * ah[s][v];
-      }
-    fetch(buf, row + 2 * G);
-    wg_sum2<C, NT / 64>(s1, s2, red[buf]);
+    for (int v = 0; v < V; v++) {
+      const C z = (C)to_f32<T>(bz[buf][v]);
+      const C dy = (C)to_f32<T>(bdy[buf][v]);
+      C Phi, zphi;
+      tab.eval(z, Phi, zphi);
+      ah[v] = (z * Phi) * rs + nmr;                        // (A - mean) rstd, one fused multiply-add
+      gp[v] = (Phi + zphi) * rs;
+      g[v] = dy * gm[v];                                   // (columns past the end: dY and gamma are zero)
+      s1 += g[v];
+      s2 += g[v] * ah[v];
+      accb[v] += dy;
+      accg[v] += dy * ah[v];
+    }
+    fetch(buf, row + D * G);
+    wg_sum2<C, NT / 64>(s1, s2, red[buf & 1]);
     const C c1 = s1 * inv_n, c2 = s2 * inv_n;
+    raw_t o;
 #pragma unroll
-    for (int s = 0; s < S; s++) {
-      C dz[V];
+    for (int v = 0; v < V; v++) {
+      C dz = (g[v] - c1 - ah[v] * c2) * gp[v];
+      if (ANY) dz = v < nv ? dz : (C)0;
+      accz[v] += dz;
+      o[v] = to_storage<T, C>(dz);
+    }
+    if constexpr (BLK) {
+      // (every lane takes part in the stores, also one whose own columns lie past the end of the row: the pieces it
+      //  stores belong to other lanes' columns)
+      const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+      if (nv > 0) park[wv][buf & 1][ln] = o;
+      if (buf & 1) {
+        // this wave's 16 pieces per row (piece = 4 lanes = 32 columns = one block): two stores of 8 whole lines
+        const int64_t even = row - 1;
 #pragma unroll
-      for (int v = 0; v < V; v++) {
-        dz[v] = (g[s][v] - c1 - ah[s][v] * c2) * gp[s][v];
-        accz[s][v] += dz[v];
-      }
-      typename RawVec<T, V>::type o;
-      if constexpr (V == 1) o = to_storage<T, C>(dz[0]); else { for (int v = 0; v < V; v++) o[v] = to_storage<T, C>(dz[v]); }
-      if constexpr (BLK) {
-        // (every lane takes part in the stores, also one whose own columns lie past the end of the row: the pieces it
-        //  stores belong to other lanes' columns)
-        const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-        if (ok[s]) park[wv][buf][ln] = o;
-        if (buf == 1) {
-          // this wave's 16 pieces per row (piece = 4 lanes = 32 columns = one block): two stores of 8 whole lines
-          const int64_t even = row - 1;
-#pragma unroll
-          for (int half = 0; half < 2; half++) {
-            const int j = half * 8 + (ln >> 3), i = ln & 7;
-            const int64_t nb = (int64_t)wv * 16 + j;                       // block column of piece j
-            if (nb * 32 < N) {                                             // N is a multiple of 32: a piece is whole or absent
-              const raw_t v = park[wv][i >> 2][4 * j + (i & 3)];
-              const int64_t at = (((even >> 5) * (N >> 5) + nb) << 10) + ((even & 31) << 5) + i * 8;
-              __builtin_nontemporal_store(v, reinterpret_cast<raw_t*>(dZ + at));
-            }
+        for (int half = 0; half < 2; half++) {
+          const int j = half * 8 + (ln >> 3), i = ln & 7;
+          const int64_t nb = (int64_t)wv * 16 + j;                       // block column of piece j
+          if (nb * 32 < N) {                                             // N is a multiple of 32: a piece is whole or absent
+            const raw_t v = park[wv][i >> 2][4 * j + (i & 3)];
+            const int64_t at = (((even >> 5) * (N >> 5) + nb) << 10) + ((even & 31) << 5) + i * 8;
+            __builtin_nontemporal_store(v, reinterpret_cast<raw_t*>(dZ + at));
           }
         }
-      } else if (ok[s]) {
-        __builtin_nontemporal_store(o, reinterpret_cast<typename RawVec<T, V>::type*>(dZ + row * ldz + col[s]));
       }
+    } else if (ANY ? left > 0 : nv > 0) {
+      raw_store<T, ANY>(dZ + row * ldz + col, o, nv, left);
     }
   };
-  for (int64_t row = first; row < M; row += 2 * G) {
-    process(0, row);
-    if (row + second < M) process(1, row + second);
+  for (int64_t row = first; row < M; row += D * G) {
+#pragma unroll
+    for (int buf = 0; buf < D; buf++)
+      if (row + ahead(buf) < M) process(buf, row + ahead(buf));     // uniform over the workgroup
   }
-#pragma unroll
-  for (int s = 0; s < S; s++)
-    if (ok[s]) {
-#pragma unroll
-      for (int v = 0; v < V; v++) {
-        colpart[((int64_t)blockIdx.x * 3 + 0) * N + col[s] + v] = accb[s][v];
-        colpart[((int64_t)blockIdx.x * 3 + 1) * N + col[s] + v] = accg[s][v];
-        colpart[((int64_t)blockIdx.x * 3 + 2) * N + col[s] + v] = accz[s][v];
-      }
-    }
+  if (nv > 0) {
+    store_columns<C, V>(colpart + ((int64_t)blockIdx.x * 3 + 0) * N + col, accb, nv);
+    store_columns<C, V>(colpart + ((int64_t)blockIdx.x * 3 + 1) * N + col, accg, nv);
+    store_columns<C, V>(colpart + ((int64_t)blockIdx.x * 3 + 2) * N + col, accz, nv);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
 // B2: colpart [groups][3][N] -> dbeta, dgamma, db.  64 consecutive columns per workgroup (coalesced), the groups
-// dealt over the 16 wavefronts, four independent partial sums per thread so that several loads are in flight
+// dealt over the 16 wavefronts, eight loads in flight per thread
 // (the phase is pure latency: a few tens of MB), fp64 sums in a fixed order.
 // (nwhich = gridDim.y kinds of partial per group, colpart [groups][nwhich][N]; kind w goes to out_w)
 template <class C>
@@ -536,19 +605,21 @@ __device__ __forceinline__ void b2_columns(int64_t N, int groups, int nwhich, co
   constexpr int kSlices = 16;
   const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
   const int64_t col = (int64_t)cblock * 64 + lane;
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
   if (col < N) {
     const C* src = colpart + (int64_t)which * N + col;
     const int64_t gstride = (int64_t)nwhich * N;
     int g = slice;
-    for (; g + 3 * kSlices < groups; g += 4 * kSlices) {
-      const C v0 = src[(int64_t)g * gstride], v1 = src[(int64_t)(g + kSlices) * gstride];
-      const C v2 = src[(int64_t)(g + 2 * kSlices) * gstride], v3 = src[(int64_t)(g + 3 * kSlices) * gstride];
-      a0 += (double)v0; a1 += (double)v1; a2 += (double)v2; a3 += (double)v3;
+    for (; g + 7 * kSlices < groups; g += 8 * kSlices) {
+      C v[8];
+#pragma unroll
+      for (int e = 0; e < 8; e++) v[e] = src[(int64_t)(g + e * kSlices) * gstride];
+#pragma unroll
+      for (int e = 0; e < 8; e++) a[e & 3] += (double)v[e];
     }
-    for (; g < groups; g += kSlices) a0 += (double)src[(int64_t)g * gstride];
+    for (; g < groups; g += kSlices) a[0] += (double)src[(int64_t)g * gstride];
   }
-  red[slice][lane] = (a0 + a1) + (a2 + a3);
+  red[slice][lane] = (a[0] + a[1]) + (a[2] + a[3]);
   __syncthreads();
   if (slice == 0 && col < N) {
     double t = 0.0;
@@ -601,15 +672,142 @@ __global__ __launch_bounds__(1024) void finish_kernel(TailSums j) {
 
 
 // ------------------------------------------------------------------------------------------------
-// Stand-alone row normalisation for any shape and both storage types: one workgroup per row at a time, the row read
-// from memory (and then from the caches) once per pass - sum, squared deviations, output - as in the paper's
-// two-step LayerNorm and strided RMSNorm kernels.  MODE: ACT_NONE LayerNorm (writes mean, rstd), ACT_RMS RMSNorm.
-template <class T, int V, int MODE>
-__global__ __launch_bounds__(256) void norm_wg_kernel(int64_t M, int64_t N, float eps, const T* __restrict__ A,
-                                                      const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                      T* __restrict__ Y, float* __restrict__ mean, float* __restrict__ rstd) {
+// Normalisation with its own statistics, fp32 storage: a workgroup of NT threads owns a row and holds it in registers
+// over the three sweeps (activation and sum; deviations and their squares; scale, shift, store), S vectors of four per
+// thread, so that a row is read once.  ACT as above; Z and Y may be the same buffer (a thread reads its part of a row
+// before it writes it).
+// Bound: HBM (with GELU: the fp64 erfc).  What keeps loads in flight: the next row's vectors are fetched as soon as this
+// one's are unpacked, ahead of its two reductions, and several workgroups share a compute unit.  The row streams past the
+// caches: LayerNorm of 8192 x 4096 took 74 us with three trips through memory and caches per row, 64 us in this form with
+// plain loads and stores, 52 us (5.2 TB/s) with the non-temporal hint on both.
+// Rows start at any element: the vectors are read and written with the widest instructions from element-aligned
+// addresses (the hardware splits what straddles a line), the last, partial one of a row element by element.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int NT, int S, int ACT>
+__global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float eps, const float* Z,
+                                                    const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                    float* Y, float* __restrict__ mean, float* __restrict__ rstd) {
+  typedef ActTable<float, false, NT> Act;
+  constexpr int V = 4, NW = NT / 64;
+  constexpr bool kKeep = NT < 1024;      // gamma and beta stay in registers (1024 threads have 128 each: read per row)
+  __shared__ double red[2][NW];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int col[S], nv[S];
+  float gm[S][V], bt[S][V];
+  auto affine = [&](int s) {
+    if (nv[s] == V) {
+      const f32x4 g4 = *reinterpret_cast<const f32x4*>(gamma + col[s]);
+      const f32x4 b4 = *reinterpret_cast<const f32x4*>((ACT == ACT_RMS ? gamma : beta) + col[s]);
+#pragma unroll
+      for (int v = 0; v < V; v++) { gm[s][v] = g4[v]; bt[s][v] = ACT == ACT_RMS ? 0.0f : b4[v]; }
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        gm[s][v] = v < nv[s] ? gamma[col[s] + v] : 0.0f;
+        bt[s][v] = (ACT != ACT_RMS && v < nv[s]) ? beta[col[s] + v] : 0.0f;
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < S; s++) {
+    col[s] = (s * NT + (int)threadIdx.x) * V;
+    const int64_t left = N - col[s];
+    nv[s] = left < 0 ? 0 : (left > V ? V : (int)left);
+    if (kKeep) affine(s);
+  }
+  f32x4_u raw[S];
+  auto fetch = [&](int64_t row) {
+    const float* z = Z + (row < M ? row : M - 1) * N;  // past the last row: a harmless re-read of it
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+      if (nv[s] == V) {
+        raw[s] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_u*>(z + col[s]));
+      } else {
+#pragma unroll
+        for (int v = 0; v < V; v++) raw[s][v] = v < nv[s] ? z[col[s] + v] : 0.0f;
+      }
+    }
+  };
+  // sum over the workgroup; consecutive calls use the two slots in turn, so one barrier each is enough: a slot is
+  // written again only after the barrier of the call in between
+  int slot = 0;
+  auto wg_sum = [&](double x) -> double {
+    x = wave_sum(x);
+    if constexpr (NW == 1) {
+      return x;
+    } else {
+      if (lane == 0) red[slot][wave] = x;
+      __syncthreads();
+      double t = red[slot][0];
+#pragma unroll
+      for (int w = 1; w < NW; w++) t += red[slot][w];
+      slot ^= 1;
+      return t;
+    }
+  };
+  const double inv_n = 1.0 / (double)N;
+  fetch(blockIdx.x);
+  for (int64_t row = blockIdx.x; row < M; row += gridDim.x) {
+    double a[S][V], sum = 0;
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+#pragma unroll
+      for (int v = 0; v < V; v++) a[s][v] = 0;
+      if (nv[s] == 0) continue;                        // (a whole wavefront past the end of the row skips the activation)
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        const double z = (double)raw[s][v];
+        a[s][v] = ACT == ACT_GELU ? Act::gelu(z) : z;  // zeros past the end of the row: GELU(0) = 0
+        sum += ACT == ACT_RMS ? z * z : a[s][v];
+      }
+    }
+    fetch(row + gridDim.x);
+    double rs;
+    if (ACT == ACT_RMS) {
+      rs = 1.0 / sqrt(wg_sum(sum) * inv_n + (double)eps);
+    } else {
+      const double mu = wg_sum(sum) * inv_n;
+      double m2 = 0;
+#pragma unroll
+      for (int s = 0; s < S; s++)
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+          a[s][v] = v < nv[s] ? a[s][v] - mu : 0.0;
+          m2 += a[s][v] * a[s][v];
+        }
+      rs = 1.0 / sqrt(wg_sum(m2) * inv_n + (double)eps);
+      if (threadIdx.x == 0) { mean[row] = (float)mu; rstd[row] = (float)rs; }
+    }
+    float* y = Y + row * N;
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+      if (!kKeep) affine(s);
+      f32x4_u o;
+#pragma unroll
+      for (int v = 0; v < V; v++) o[v] = (float)(a[s][v] * rs * (double)gm[s][v] + (double)bt[s][v]);
+      if (nv[s] == V) {
+        __builtin_nontemporal_store(o, reinterpret_cast<f32x4_u*>(y + col[s]));
+      } else {
+#pragma unroll
+        for (int v = 0; v < V; v++)
+          if (v < nv[s]) y[col[s] + v] = o[v];
+      }
+    }
+  }
+}
+
+// The same for rows too long for the registers of a workgroup: the row is read from memory (and then from the caches)
+// once per sweep, as in the paper's two-step LayerNorm and strided RMSNorm kernels.
+template <class T, int V, int ACT>
+__global__ __launch_bounds__(256) void row_stream_kernel(int64_t M, int64_t N, float eps, const T* A,
+                                                         const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                         T* Y, float* __restrict__ mean, float* __restrict__ rstd) {
   typedef typename ComputeOf<T>::type C;
   __shared__ C red[2][4][2];
+  ActTable<T, false, ACT == ACT_GELU ? 256 : 0> tab;
+  tab.build();
+  auto act = [&](C x) -> C { return ACT == ACT_GELU ? tab.gelu(x) : x; };
   for (int64_t row = blockIdx.x; row < M; row += gridDim.x) {
     const T* a = A + row * N;
     C s1 = 0, s2 = 0;
@@ -617,11 +815,11 @@ __global__ __launch_bounds__(256) void norm_wg_kernel(int64_t M, int64_t N, floa
       C x[V];
       VecIO<T, V>::load(a + col, x);
 #pragma unroll
-      for (int v = 0; v < V; v++) { s1 += x[v]; s2 += x[v] * x[v]; }
+      for (int v = 0; v < V; v++) { const C f = act(x[v]); s1 += f; if (ACT == ACT_RMS) s2 += f * f; }
     }
     wg_sum2<C, 4>(s1, s2, red[0]);
     C mu = 0, rs;
-    if (MODE == ACT_RMS) {
+    if (ACT == ACT_RMS) {
       rs = (C)1 / sqrt(s2 / (C)N + (C)eps);
     } else {
       mu = s1 / (C)N;
@@ -630,7 +828,7 @@ __global__ __launch_bounds__(256) void norm_wg_kernel(int64_t M, int64_t N, floa
         C x[V];
         VecIO<T, V>::load(a + col, x);
 #pragma unroll
-        for (int v = 0; v < V; v++) { const C d = x[v] - mu; d2 += d * d; }
+        for (int v = 0; v < V; v++) { const C d = act(x[v]) - mu; d2 += d * d; }
       }
       wg_sum2<C, 4>(d2, dummy, red[1]);
       rs = (C)1 / sqrt(d2 / (C)N + (C)eps);
@@ -641,8 +839,8 @@ __global__ __launch_bounds__(256) void norm_wg_kernel(int64_t M, int64_t N, floa
       VecIO<T, V>::load(a + col, x);
 #pragma unroll
       for (int v = 0; v < V; v++) {
-        if (MODE == ACT_RMS) y[v] = x[v] * rs * (C)gamma[col + v];
-        else y[v] = (x[v] - mu) * rs * (C)gamma[col + v] + (C)beta[col + v];
+        if (ACT == ACT_RMS) y[v] = x[v] * rs * (C)gamma[col + v];
+        else y[v] = (act(x[v]) - mu) * rs * (C)gamma[col + v] + (C)beta[col + v];
       }
       VecIO<T, V>::store(Y + row * N + col, y);
     }
@@ -686,8 +884,8 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(int64_t M, int64_t 
       for (int v = 0; v < V; v++) acc[v] += x[v];
     }
   }
-#pragma unroll
-  for (int v = 0; v < V; v++) colpart[(int64_t)grp * N + col + v] = acc[v];
+  if constexpr (V > 1) store_columns<C, V>(colpart + (int64_t)grp * N + col, acc, V);
+  else colpart[(int64_t)grp * N + col] = acc[0];
 }
 
 // H = SiLU(G) * U, element by element (the gated feed-forward block's activation); H may be G or U.
@@ -707,187 +905,154 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(int64_t n, const T* G, co
   }
 }
 
-// vector width usable for rows of length N starting at `base` (every row start must be aligned)
-template <class T> int vec_width(const void* a, const void* b, const void* c, int64_t N) {
-  constexpr int V = 16 / (int)sizeof(T);
-  const uintptr_t m = (uintptr_t)a | (uintptr_t)b | (uintptr_t)c;
-  return (N % V == 0 && m % 16 == 0) ? V : 1;
-}
-
-template <class T> void f2_impl(int64_t M, int64_t N, const void* Z, const float* mean, const float* rstd,
-                                const float* gamma, const float* beta, void* Y, hipStream_t s) {
-  constexpr int VMAX = 16 / (int)sizeof(T);
-  const int V = vec_width<T>(Z, Y, nullptr, N);
-  const int strips = (int)((N + 256 * (int64_t)V - 1) / (256 * (int64_t)V));
-  // 16 rows per workgroup keep gamma and beta in registers across rows; fewer where the matrix is so small that the
-  // chip would otherwise see only a handful of workgroups
-  int64_t rows_per_wg = M * strips / 2048;
-  rows_per_wg = rows_per_wg < 1 ? 1 : (rows_per_wg > 16 ? 16 : rows_per_wg);
-  const int64_t blocks = (int64_t)strips * ((M + rows_per_wg - 1) / rows_per_wg);
-  if (V == VMAX)
-    hipLaunchKernelGGL((f2_kernel<T, VMAX>), dim3((unsigned)blocks), dim3(256), 0, s, M, N, (int)rows_per_wg, strips,
-                       (const T*)Z, mean, rstd, gamma, beta, (T*)Y);
-  else
-    hipLaunchKernelGGL((f2_kernel<T, 1>), dim3((unsigned)blocks), dim3(256), 0, s, M, N, (int)rows_per_wg, strips,
-                       (const T*)Z, mean, rstd, gamma, beta, (T*)Y);
-}
-
 template <class T> void b1a_impl(int64_t M, int64_t N, const void* dY, const void* Z, const float* gamma,
                                  const float* mean, const float* rstd, void* c12, hipStream_t s) {
   typedef typename ComputeOf<T>::type C;
-  constexpr int VMAX = 16 / (int)sizeof(T);
-  const int V = vec_width<T>(dY, Z, nullptr, N);
   const unsigned blocks = (unsigned)(M < 4096 ? M : 4096);
-  if (V == VMAX)
-    hipLaunchKernelGGL((b1a_kernel<T, VMAX>), dim3(blocks), dim3(256), 0, s, M, N, (const T*)dY, (const T*)Z, gamma,
-                       mean, rstd, (C*)c12);
-  else
-    hipLaunchKernelGGL((b1a_kernel<T, 1>), dim3(blocks), dim3(256), 0, s, M, N, (const T*)dY, (const T*)Z, gamma, mean,
-                       rstd, (C*)c12);
+  auto kern = N % (16 / (int)sizeof(T)) == 0 ? b1a_kernel<T, false> : b1a_kernel<T, true>;
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, M, N, (const T*)dY, (const T*)Z, gamma, mean, rstd, (C*)c12);
 }
 
 template <class T> void b1b_impl(int64_t M, int64_t N, int64_t ldz, int rows_per_group, int groups, const void* dY, const void* Z,
                                  const float* gamma, const float* mean, const float* rstd, const void* c12, void* dZ,
                                  void* colpart, hipStream_t s) {
   typedef typename ComputeOf<T>::type C;
-  constexpr int VMAX = 16 / (int)sizeof(T);
-  const int V = (ldz % VMAX == 0) ? vec_width<T>(dY, Z, dZ, N) : 1;
+  constexpr int V = 16 / (int)sizeof(T);
   const int strips = (int)((N + 256 * (int64_t)V - 1) / (256 * (int64_t)V));
   const int64_t blocks = (int64_t)strips * groups;
-  if (V == VMAX)
-    hipLaunchKernelGGL((b1b_kernel<T, VMAX>), dim3((unsigned)blocks), dim3(256), 0, s, M, N, ldz, rows_per_group, strips,
-                       (const T*)dY, (const T*)Z, gamma, mean, rstd, (const C*)c12, (T*)dZ, (C*)colpart);
-  else
-    hipLaunchKernelGGL((b1b_kernel<T, 1>), dim3((unsigned)blocks), dim3(256), 0, s, M, N, ldz, rows_per_group, strips,
-                       (const T*)dY, (const T*)Z, gamma, mean, rstd, (const C*)c12, (T*)dZ, (C*)colpart);
+  auto kern = N % V == 0 && ldz % V == 0 ? b1b_kernel<T, false> : b1b_kernel<T, true>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, M, N, ldz, rows_per_group, strips, (const T*)dY,
+                     (const T*)Z, gamma, mean, rstd, (const C*)c12, (T*)dZ, (C*)colpart);
 }
 
-// Launch shapes of the fused kernel (threads NT, strips S): full-width vectors use one strip and 256, 512
-// or 1024 threads; the scalar (unaligned rows) variant also has a two-strip, 1024-thread shape.
-struct FusedShape { int nt, s; };
-inline bool fused_shape(int64_t N, int V, bool vec, FusedShape* out) {
-  const int64_t per_thread = (N + V - 1) / V;   // vectors per row
-  const int nts[3] = {256, 512, 1024};
-  for (int i = 0; i < 3; i++)
-    if (per_thread <= nts[i]) { out->nt = nts[i]; out->s = 1; return true; }
-  if (!vec && per_thread <= 2048) { out->nt = 1024; out->s = 2; return true; }
-  return false;
+// Threads of a workgroup of the fused kernel: one 16-byte vector each, the row's pitch in dZ included (the surplus columns
+// of a padded dZ are zeroed by the threads behind the row's end).  0: the row does not fit.
+inline int fused_threads(int dt, int64_t N, int64_t ldz) {
+  const int V = dt == kF32 ? 4 : 8;
+  const int64_t per_row = ((ldz > N ? ldz : N) + V - 1) / V;
+  if (per_row <= 256) return 256;
+  if (per_row <= 512) return 512;
+  return per_row <= 1024 ? 1024 : 0;
 }
 
-template <class T, bool TAB> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int groups, bool blocked, const void* dY, const void* Z,
-                                                const float* gamma, const float* mean, const float* rstd, void* dZ,
-                                                void* colpart, hipStream_t s) {
+template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int groups, bool blocked, const void* dY, const void* Z,
+                                      const float* gamma, const float* mean, const float* rstd, void* dZ,
+                                      void* colpart, hipStream_t s) {
   typedef typename ComputeOf<T>::type C;
-  constexpr int VMAX = 16 / (int)sizeof(T);
-  const int V = vec_width<T>(dY, Z, dZ, N);
-  FusedShape fs;
-  if (!fused_shape(N, V, V == VMAX, &fs)) return;   // callers check b1_fused_supported first
-#define FDL_B1F(VV, SS, NTT)                                                                                       \
-  hipLaunchKernelGGL((b1_fused_kernel<T, VV, SS, NTT, TAB>), dim3((unsigned)groups), dim3(NTT), 0, s, M, N, ldz,      \
-                     (const T*)dY, (const T*)Z, gamma, mean, rstd, (T*)dZ, (C*)colpart)
-#define FDL_B1F_BLK(NTT)                                                                                           \
-  hipLaunchKernelGGL((b1_fused_kernel<T, VMAX, 1, NTT, TAB, true>), dim3((unsigned)groups), dim3(NTT), 0, s, M, N,  \
-                     ldz, (const T*)dY, (const T*)Z, gamma, mean, rstd, (T*)dZ, (C*)colpart)
-  if (V == VMAX && blocked) {
-    if constexpr (sizeof(T) == 2) {
-      if (fs.nt == 256) FDL_B1F_BLK(256); else if (fs.nt == 512) FDL_B1F_BLK(512); else FDL_B1F_BLK(1024);
-    }
-  } else if (V == VMAX) {
-    if (fs.nt == 256) FDL_B1F(VMAX, 1, 256); else if (fs.nt == 512) FDL_B1F(VMAX, 1, 512); else FDL_B1F(VMAX, 1, 1024);
-  } else {
-    if (fs.s == 2) FDL_B1F(1, 2, 1024);
-    else if (fs.nt == 256) FDL_B1F(1, 1, 256); else if (fs.nt == 512) FDL_B1F(1, 1, 512); else FDL_B1F(1, 1, 1024);
+  constexpr int V = 16 / (int)sizeof(T);
+  const int nt = fused_threads(sizeof(T) == 4 ? kF32 : kBF16, N, ldz);   // callers check b1_fused_supported first
+  // a row of whole vectors, or one that starts or ends inside a vector or is followed by columns to be zeroed
+  const bool any = N % V != 0 || ldz != N;
+  const dim3 grid((unsigned)groups);
+#define FDL_B1_ARGS s, M, N, ldz, (const T*)dY, (const T*)Z, gamma, mean, rstd, (T*)dZ, (C*)colpart
+#define FDL_B1F(NT, ANY, BLK) hipLaunchKernelGGL((b1_fused_kernel<T, NT, ANY, BLK>), grid, dim3(NT), 0, FDL_B1_ARGS)
+#define FDL_B1F_NT(ANY, BLK)                                                                                              \
+  do { if (nt == 256) FDL_B1F(256, ANY, BLK); else if (nt == 512) FDL_B1F(512, ANY, BLK); else FDL_B1F(1024, ANY, BLK); } while (0)
+  if constexpr (sizeof(T) == 2) {
+    if (blocked) { FDL_B1F_NT(false, true); return; }
   }
-#undef FDL_B1F_BLK
+  if (any) FDL_B1F_NT(true, false);
+  else FDL_B1F_NT(false, false);
+#undef FDL_B1F_NT
 #undef FDL_B1F
+#undef FDL_B1_ARGS
 }
 
 }  // namespace
 
-void launch_stats_finalize(const void* part, int tiles, int tile_w, int64_t M, int64_t N, float eps, float* mean,
-                           float* rstd, hipStream_t s) {
-  const unsigned blocks = (unsigned)((M + 15) / 16);   // sixteen lanes per row
-  hipLaunchKernelGGL(stats_finalize_kernel, dim3(blocks), dim3(256), 0, s, (const f32x2*)part, tiles, tile_w, M, N, eps,
-                     mean, rstd);
-}
-
-void launch_f2(int dt, int64_t M, int64_t N, const void* Zsave, const float* mean, const float* rstd,
-               const float* gamma, const float* beta, void* Y, hipStream_t s) {
-  if (dt == kF32) f2_impl<float>(M, N, Zsave, mean, rstd, gamma, beta, Y, s);
-  else f2_impl<bf16_t>(M, N, Zsave, mean, rstd, gamma, beta, Y, s);
-}
-
 // one instantiation: gamma/beta (4 KB per 512 columns) plus the Phi table can exceed the default 64 KB of dynamic LDS
-template <int CH, bool FULL, int NT, int ACT>
+template <int CH, int FIT, int NT, int ACT, int WPR = 1>
 void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float eps, const bf16_t* Z, const float* gamma,
                         const float* beta, bf16_t* Y, float* mean, float* rstd) {
-  constexpr size_t kLds = (size_t)CH * 4096 + GaussTable<false>::kBytes;
+  constexpr size_t kLds = (size_t)CH * WPR * 4096 + GaussTable<false>::kBytes;
   static OnceFlags configured;
-  auto kern = f2_rows_kernel<CH, FULL, NT, ACT>;
+  auto kern = f2_rows_kernel<CH, FIT, NT, ACT, WPR>;
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLds, &configured)) return;
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(NT), kLds, s, M, N, eps, Z, gamma, beta, Y, mean, rstd);
 }
 
-bool f2_rows_supported(int dt, int64_t N) { return dt == kBF16 && N % 8 == 0 && N <= 8192; }
-
 template <int ACT>
 void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
                      float* mean, float* rstd, hipStream_t s) {
-  int ch = 2;
-  while (ch * 512 < N) ch *= 2;
-  const bool full = N == (int64_t)ch * 512;
-  const int nt = (!full && ch == 16) ? 256 : 512;
+  int ch = 2, wpr = 1;
+  while (ch < 16 && ch * 512 < N) ch *= 2;
+  if (ch * 512 < N) wpr = 2;
+  const int fit = N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
+  const int nt = (fit != FIT_FULL && ch == 16) ? 256 : 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
-  const int64_t per_wg = nt / 64;
+  const int64_t per_wg = nt / 64 / wpr;
   int64_t wgs = (M + per_wg - 1) / per_wg;
   DeviceInfo di;
   if (!device_info(&di)) return;
   const int64_t cap = (int64_t)di.cus * (16 / ch);
   if (wgs > cap) wgs = cap;
-#define FDL_F2R(CHH, FULL, NTT)                                                                                    \
-  launch_f2_rows_one<CHH, FULL, NTT, ACT>(wgs, s, M, N,                                                                 \
-                     eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
-  if (full) {
-    if (ch == 2) FDL_F2R(2, true, 512); else if (ch == 4) FDL_F2R(4, true, 512);
-    else if (ch == 8) FDL_F2R(8, true, 512); else FDL_F2R(16, true, 512);
-  } else {
-    if (ch == 2) FDL_F2R(2, false, 512); else if (ch == 4) FDL_F2R(4, false, 512);
-    else if (ch == 8) FDL_F2R(8, false, 512); else FDL_F2R(16, false, 256);
-  }
+#define FDL_F2R(CHH, FIT, NTT)                                                                                        \
+  launch_f2_rows_one<CHH, FIT, NTT, ACT>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
+#define FDL_F2R_FIT(FIT, NTW)                                                                                         \
+  do {                                                                                                                \
+    if (wpr == 2)                                                                                                     \
+      launch_f2_rows_one<16, FIT, NTW, ACT, 2>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd); \
+    else if (ch == 2) FDL_F2R(2, FIT, 512); else if (ch == 4) FDL_F2R(4, FIT, 512);                                        \
+    else if (ch == 8) FDL_F2R(8, FIT, 512); else FDL_F2R(16, FIT, NTW);                                               \
+  } while (0)
+  if (fit == FIT_FULL) FDL_F2R_FIT(FIT_FULL, 512);
+  else if (fit == FIT_VECTORS) FDL_F2R_FIT(FIT_VECTORS, 256);
+  else FDL_F2R_FIT(FIT_ANY, 256);
+#undef FDL_F2R_FIT
 #undef FDL_F2R
 }
 
-void launch_f2_rows(int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
-                    float* mean, float* rstd, hipStream_t s) {
-  launch_rows_act<ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
+// Which kernel normalises rows of N elements: up to 16384, bf16 rows go one to a wavefront (a pair of them beyond 8192),
+// fp32 rows one to a workgroup that is as small as the row allows; longer ones are streamed.
+template <class T, int ACT>
+void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta, void* Y,
+                     float* mean, float* rstd, hipStream_t s) {
+  constexpr int V = 16 / (int)sizeof(T);
+  if constexpr (sizeof(T) == 4) {
+    DeviceInfo di;
+    if (!device_info(&di)) return;
+    const int64_t vectors = (N + V - 1) / V;
+#define FDL_ROW(NT, S)                                                                                              \
+  do {                                                                                                              \
+    const int64_t cap = (int64_t)di.cus * (2048 / NT);                                                              \
+    hipLaunchKernelGGL((row_wg_kernel<NT, S, ACT>), dim3((unsigned)(M < cap ? M : cap)), dim3(NT), 0, s, M, N, eps, \
+                       (const T*)A, gamma, beta, (T*)Y, mean, rstd);                                                \
+    return;                                                                                                         \
+  } while (0)
+    if (vectors <= 64) FDL_ROW(64, 1);
+    if (vectors <= 256) FDL_ROW(256, 1);
+    if (vectors <= 512) FDL_ROW(256, 2);
+    if (vectors <= 1024) FDL_ROW(256, 4);
+    if (vectors <= 2048) FDL_ROW(512, 4);
+    if (vectors <= 4096) FDL_ROW(1024, 4);
+#undef FDL_ROW
+  } else if (N <= 16384) {
+    launch_rows_act<ACT>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
+    return;
+  }
+  const bool vec = N % V == 0 && ((uintptr_t)A | (uintptr_t)Y) % 16 == 0;
+  const unsigned blocks = (unsigned)(M < 8192 ? M : 8192);
+  if (vec) hipLaunchKernelGGL((row_stream_kernel<T, V, ACT>), dim3(blocks), dim3(256), 0, s, M, N, eps, (const T*)A, gamma, beta, (T*)Y, mean, rstd);
+  else hipLaunchKernelGGL((row_stream_kernel<T, 1, ACT>), dim3(blocks), dim3(256), 0, s, M, N, eps, (const T*)A, gamma, beta, (T*)Y, mean, rstd);
 }
 
-
-bool rows_act_supported(int dt, int64_t N) { return f2_rows_supported(dt, N); }
-
-template <class T, int MODE>
-static void norm_wg_impl(int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta, void* Y,
-                         float* mean, float* rstd, hipStream_t s) {
-  constexpr int VMAX = 16 / (int)sizeof(T);
-  const bool vec = N % VMAX == 0 && ((uintptr_t)A | (uintptr_t)Y) % 16 == 0;
-  const unsigned blocks = (unsigned)(M < 8192 ? M : 8192);
-  if (vec) hipLaunchKernelGGL((norm_wg_kernel<T, VMAX, MODE>), dim3(blocks), dim3(256), 0, s, M, N, eps, (const T*)A, gamma, beta, (T*)Y, mean, rstd);
-  else hipLaunchKernelGGL((norm_wg_kernel<T, 1, MODE>), dim3(blocks), dim3(256), 0, s, M, N, eps, (const T*)A, gamma, beta, (T*)Y, mean, rstd);
+void launch_f2(int dt, int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
+               float* mean, float* rstd, hipStream_t s) {
+  if (dt == kF32) launch_row_norm<float, ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
+  else launch_row_norm<bf16_t, ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
 }
 
 // Y = LayerNorm(A) gamma + beta over the last dimension; mean, rstd [M] out
 void launch_layernorm(int dt, int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta,
                       void* Y, float* mean, float* rstd, hipStream_t s) {
-  if (rows_act_supported(dt, N)) launch_rows_act<ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
-  else if (dt == kF32) norm_wg_impl<float, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
-  else norm_wg_impl<bf16_t, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
+  if (dt == kF32) launch_row_norm<float, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
+  else launch_row_norm<bf16_t, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
 }
 
 // Y = A (mean(A^2) + eps)^-1/2 weight over the last dimension
 void launch_rmsnorm(int dt, int64_t M, int64_t N, float eps, const void* A, const float* weight, void* Y, hipStream_t s) {
-  if (rows_act_supported(dt, N)) launch_rows_act<ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, s);
-  else if (dt == kF32) norm_wg_impl<float, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, s);
-  else norm_wg_impl<bf16_t, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, s);
+  if (dt == kF32) launch_row_norm<float, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, s);
+  else launch_row_norm<bf16_t, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, s);
 }
 
 // groups of the first stage of a column sum over M rows
@@ -960,39 +1125,35 @@ void launch_zero_cols_bf16(void* dZ, int64_t M, int64_t N, int64_t ldz, hipStrea
   hipLaunchKernelGGL(zero_cols_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (unsigned short*)dZ, M, N, ldz);
 }
 
-// Whether rows can be read with full-width vectors depends on N only here (base pointers are required to be
-// 16-byte aligned by the entry points).
-bool b1_fused_supported(int dt, int64_t N) {
-  const int vmax = dt == kF32 ? 4 : 8;
-  const int V = (N % vmax == 0) ? vmax : 1;
-  FusedShape fs;
-  return fused_shape(N, V, V == vmax, &fs);
-}
+bool b1_fused_supported(int dt, int64_t N, int64_t ldz) { return fused_threads(dt, N, ldz) != 0; }
 
-// Row groups (= workgroups) of the fused kernel.  Each group leaves 3 N partial column sums behind, so fewer groups
-// mean less traffic for the phase and for the column reduction after it, while the rows in flight (two per group)
-// must keep the memory system busy.  Measured: 256 groups are best once a row takes at least 512 lanes (with 1024
-// threads a workgroup fills a CU's register file, all groups are resident at once and the rows in flight form one
-// contiguous window); narrower rows need 512 groups, unless the matrix is so short that a group would walk fewer
-// than 8 rows.
+// Row groups (= workgroups) of the fused kernel.  Each group leaves 3 N partial column sums behind and pays for its start
+// (the table, the first rows), so fewer groups mean less traffic for the phase and for the column reduction after it;
+// more of them hide the chain of each row's reductions behind one another.  Measured with the column reduction, us, for
+// 256 / 512 / 1024 groups: bf16 3001 x 1537: 26.2 / 23.3 / 28.1; 32768 x 1024: 103 / 72.8 / 65.4; 16384 x 4096: 85.3 / 82.0
+// / 88.9; 65536 x 8192: 578 / 569 / 578; 1000 x 5000: 22.3 / 28.5; fp32, whose fp64 arithmetic fills the vector units
+// with one workgroup of 512 threads per compute unit: 3001 x 1537 46.5 / 50.6, 8192 x 4096 191 / 200.
 int b1_fused_groups(int dt, int64_t M, int64_t N) {
-  const int vmax = dt == kF32 ? 4 : 8;
-  const int V = (N % vmax == 0) ? vmax : 1;
-  FusedShape fs;
-  if (!fused_shape(N, V, V == vmax, &fs)) return 512;
-  const int64_t lanes = (N + V - 1) / V;
-  int64_t groups = lanes >= 512 ? 256 : 512;
-  if (M / 8 < groups) groups = M / 8 < 256 ? 256 : M / 8;
-  return (int)groups;
+  const int nt = fused_threads(dt, N, N);
+  if (dt == kF32 && nt > 256) return 256;
+  if (nt <= 256 && M >= 16 * 1024) return 1024;
+  return M >= (nt < 1024 ? 5 : 16) * 512 ? 512 : 256;
 }
 
-void launch_b1_fused(int dt, int64_t M, int64_t N, int64_t ldz, int groups, bool table, bool blocked, const void* dY,
-                     const void* Zsave, const float* gamma, const float* mean, const float* rstd, void* dZ, void* colpart,
-                     hipStream_t s) {
-  const bool blk = blocked && dt == kBF16;
-  if (dt == kF32) b1_fused_impl<float, false>(M, N, ldz, groups, false, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
-  else if (table) b1_fused_impl<bf16_t, true>(M, N, ldz, groups, blk, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
-  else b1_fused_impl<bf16_t, false>(M, N, ldz, groups, blk, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
+// Rows per group of the two-kernel path: about 1024 workgroups, but at least 16 rows each (partial column sums as above;
+// bf16 4096 x 16384 with the column reduction: 16 rows 157 us, 32 146, 64 155; 1273 x 14080: 8 rows 44.9, 16 42.0, 32 48.2)
+int b1b_rows_per_group(int dt, int64_t M, int64_t N) {
+  const int64_t width = 256 * (dt == kF32 ? 4 : 8), strips = (N + width - 1) / width;
+  int64_t rpg = M * strips / 1024;
+  if (rpg < 16) rpg = 16;
+  if (rpg < (M + 1023) / 1024) rpg = (M + 1023) / 1024;     // at most 1024 groups' worth of partial sums
+  return (int)rpg;
+}
+
+void launch_b1_fused(int dt, int64_t M, int64_t N, int64_t ldz, int groups, bool blocked, const void* dY, const void* Zsave,
+                     const float* gamma, const float* mean, const float* rstd, void* dZ, void* colpart, hipStream_t s) {
+  if (dt == kF32) b1_fused_impl<float>(M, N, ldz, groups, false, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
+  else b1_fused_impl<bf16_t>(M, N, ldz, groups, blocked, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
 }
 
 void launch_b2(int dt, int64_t N, int groups, const void* colpart, float* dbeta, float* dgamma, float* db,

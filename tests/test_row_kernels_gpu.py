@@ -1,0 +1,53 @@
+"""The row kernels at the edges of their row lengths: one wavefront, a pair of wavefronts or a workgroup per row, streamed
+rows; rows that end inside a 16-byte vector; matrices of one row and of more rows than one pass holds.  Same bars as the
+other parity tests (tests/harness.py), against the fp64 oracles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fdl_oracle as O
+from oracle import siblings_oracle as S
+from paper_2509_14279_amd import api, inputs as I
+import harness as H
+
+pytestmark = pytest.mark.gpu
+
+BF16_WIDTHS = [7, 511, 1025, 4095, 8191, 8193, 8208, 16383, 16384, 16391]
+F32_WIDTHS = [3, 257, 1023, 1026, 4097, 8192, 16383, 16388]
+WIDTHS = [("bf16", n) for n in BF16_WIDTHS] + [("f32", n) for n in F32_WIDTHS]
+
+
+@pytest.mark.parametrize("dtype,N", WIDTHS)
+@pytest.mark.parametrize("M", [1, 1037])
+def test_stand_alone_norms(dtype, N, M):
+    print(f"[rows] {dtype} {M}x{N}", flush=True)
+    t = I.generate_norm(dtype, M, N, seed=8000 + N + M)
+    n = {k: v.numpy().astype(np.float64) for k, v in t.items()}
+    dt = I.storage_torch_dtype(dtype)
+    A = t["A"].to("cuda", dt)
+    out = {"Y": H.Guarded((M, N), dt), "mean": H.Guarded((M,), torch.float32), "rstd": H.Guarded((M,), torch.float32),
+           "R": H.Guarded((M, N), dt)}
+    gamma, beta = t["gamma"].to("cuda"), t["beta"].to("cuda")
+    api.fdl_layernorm_forward(dtype, A, gamma, beta, 1e-5, out["Y"].view, out["mean"].view, out["rstd"].view)
+    api.fdl_rmsnorm_forward(dtype, A, gamma, 1e-5, out["R"].view)
+    torch.cuda.synchronize()
+    for k, g in out.items():
+        assert g.intact(), f"kernel wrote outside the {k} buffer"
+    ref = S.layernorm_forward(n["A"], n["gamma"], n["beta"], 1e-5)
+    H.check(dtype, "Y", H.to_f64(out["Y"].view), ref["Y"])
+    H.check(dtype, "mean", H.to_f64(out["mean"].view), ref["mean"])
+    H.check(dtype, "R", H.to_f64(out["R"].view), S.rmsnorm_forward(n["A"], n["gamma"], 1e-5)["Y"])
+
+
+@pytest.mark.parametrize("dtype,M,N", [("bf16", 37, 8193), ("bf16", 530, 16384), ("bf16", 65, 11570), ("bf16", 70, 16392),
+                                       ("bf16", 2600, 1030), ("bf16", 300, 4093), ("f32", 70, 4100), ("f32", 33, 8190),
+                                       ("f32", 2600, 515), ("f32", 40, 16390)])
+def test_forward_and_backward_of_the_block(dtype, M, N):
+    cfg = I.custom(dtype, M, 16, N, seed=8100 + M + N)
+    print(f"[rows] {cfg.name}", flush=True)
+    t = I.generate(cfg)
+    got = H.run_fdl(cfg, t)
+    n = {k: v.numpy().astype(np.float64) for k, v in t.items()}
+    ref = O.forward_backward(n["X"], n["W"], n["b"], n["gamma"], n["beta"], n["dY"], cfg.eps)
+    for k in H.OUTPUTS + ("mean",):
+        H.check(dtype, k, H.to_f64(got[k]), ref[k])
