@@ -21,9 +21,7 @@ namespace {
 // vectors c*64 + l, c < CH, of its row (every load and store of a wavefront covers 1 KB of one row); the next
 // row's vectors are fetched while the current row is processed.  gamma and beta sit in LDS, permuted so that a
 // lane's four 16-byte reads per vector are lane-contiguous.  Workgroups of NT/64 wavefronts walk the rows with
-// stride (8 wavefronts; 4 for the widest masked variant, whose extra per-vector state needs the larger register
-// budget of one wavefront per SIMD).  WPR = 2: two neighbouring wavefronts share a row of up to 16384 and exchange their
-// sums through LDS (as a workgroup of 1024 threads per row the same normalisation of 4096 x 16384 took 66 - 89 us: its two
+// stride.  WPR > 1: neighbouring wavefronts share a row and exchange their sums through LDS (as a workgroup of 1024 threads per row the same normalisation of 4096 x 16384 took 66 - 89 us: its two
 // reductions stop every wavefront of the compute unit).
 // FIT_FULL: N == 512 CH, every lane holds every vector.  FIT_VECTORS (N % 8 == 0): the vectors past the end of the row
 // are fetched from a clamped address, masked to zero (GELU(0) = 0 adds nothing to the sum), left out of the squared
@@ -974,35 +972,42 @@ void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float 
 template <int ACT>
 void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
                      float* mean, float* rstd, hipStream_t s) {
+  // Rows of 8192 and 16384 take 16 vectors per lane.  The others, whose masks cost registers (one wavefront per SIMD with
+  // 16 vectors), take at most 8 and more wavefronts per row: 10000 x 5000 70.7 -> 50.1 us, 8192 x 10496 101.6 -> 71.6,
+  // 3001 x 12345 64.9 -> 48.6.
   int ch = 2, wpr = 1;
-  while (ch < 16 && ch * 512 < N) ch *= 2;
-  if (ch * 512 < N) wpr = 2;
+  while (ch < 8 && ch * 512 < N) ch *= 2;
+  while (ch * wpr * 512 < N) wpr *= 2;
+  if (N == 8192 || N == 16384) { ch = 16; wpr /= 2; }
   const int fit = N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
-  const int nt = (fit != FIT_FULL && ch == 16) ? 256 : 512;
+  const int nt = 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
   const int64_t per_wg = nt / 64 / wpr;
   int64_t wgs = (M + per_wg - 1) / per_wg;
   DeviceInfo di;
   if (!device_info(&di)) return;
-  const int64_t cap = (int64_t)di.cus * (16 / ch);
+  const int64_t cap = (int64_t)di.cus * (16 / ch > wpr ? 16 / ch / wpr : 1);
   if (wgs > cap) wgs = cap;
-#define FDL_F2R(CHH, FIT, NTT)                                                                                        \
-  launch_f2_rows_one<CHH, FIT, NTT, ACT>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
-#define FDL_F2R_FIT(FIT, NTW)                                                                                         \
+#define FDL_F2R(CHH, FIT, WPR)                                                                                        \
+  launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
+#define FDL_F2R_FIT(FIT)                                                                                              \
   do {                                                                                                                \
-    if (wpr == 2)                                                                                                     \
-      launch_f2_rows_one<16, FIT, NTW, ACT, 2>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd); \
-    else if (ch == 2) FDL_F2R(2, FIT, 512); else if (ch == 4) FDL_F2R(4, FIT, 512);                                        \
-    else if (ch == 8) FDL_F2R(8, FIT, 512); else FDL_F2R(16, FIT, NTW);                                               \
+    if (ch == 2) FDL_F2R(2, FIT, 1); else if (ch == 4) FDL_F2R(4, FIT, 1); else if (wpr == 1) FDL_F2R(8, FIT, 1);     \
+    else if (wpr == 2) FDL_F2R(8, FIT, 2); else FDL_F2R(8, FIT, 4);                                                   \
   } while (0)
-  if (fit == FIT_FULL) FDL_F2R_FIT(FIT_FULL, 512);
-  else if (fit == FIT_VECTORS) FDL_F2R_FIT(FIT_VECTORS, 256);
-  else FDL_F2R_FIT(FIT_ANY, 256);
+  if (fit == FIT_FULL) {
+    if (ch == 2) FDL_F2R(2, FIT_FULL, 1); else if (ch == 4) FDL_F2R(4, FIT_FULL, 1); else if (ch == 8) FDL_F2R(8, FIT_FULL, 1);
+    else if (wpr == 1) FDL_F2R(16, FIT_FULL, 1); else FDL_F2R(16, FIT_FULL, 2);
+  } else if (fit == FIT_VECTORS) {
+    FDL_F2R_FIT(FIT_VECTORS);
+  } else {
+    FDL_F2R_FIT(FIT_ANY);
+  }
 #undef FDL_F2R_FIT
 #undef FDL_F2R
 }
 
-// Which kernel normalises rows of N elements: up to 16384, bf16 rows go one to a wavefront (a pair of them beyond 8192),
+// Which kernel normalises rows of N elements: up to 16384, bf16 rows go one to a wavefront or to two or four of them,
 // fp32 rows one to a workgroup that is as small as the row allows; longer ones are streamed.
 template <class T, int ACT>
 void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta, void* Y,
