@@ -105,23 +105,27 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   auto pick_wb = [dt](int64_t I, int64_t J) { return pick_generic_wb(dt, I, J); };
 
   // ---- forward
+  q.f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
   q.f1_fast = q.pad || (dt == kBF16 && fast_f1_supported(M, K, N));
   q.f1_wb = pick_wb(Mp, N);
   size_t off = 0;
-  q.off_xtail = off; off += align256(q.pad ? fast_padded_tail_bytes(K) : (q.f1_fast ? fast_f1_tail_bytes(M, K) : 0));
-  q.off_wpad_f = off; off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
-  q.off_bpad_f = off; off += align256(q.pad ? (size_t)Np * 4 : 0);
+  const bool tiled = q.f1_fast && !q.f1_skinny;
+  q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_tail_bytes(K) : fast_f1_tail_bytes(M, K)));
+  q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
+  q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
   // Large batches on the tuned kernel (tile-aligned N and K): the weights are transposed first, 4 N K bytes of traffic
   // against about 6 % of the contraction's time; that pays from roughly 10^4 rows, with a margin for the extra launch.
   q.fwd_bytes_plain = off;
-  q.f1_wt = q.f1_fast && !q.pad && M >= kTransposeFromRows;
+  q.f1_wt = tiled && !q.pad && M >= kTransposeFromRows;
   q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
   q.fwd_bytes = off;
-  // The static entry point's limit is part of its contract (see the header): 8 bytes per (row, column tile) wherever rows
-  // are not normalised by the wavefront-per-row kernel on the tuned path, whether a plan needs them or not.
+  // The static entry point's limit is part of its contract (see the header) and does not move with the plan: the tiled
+  // kernels' copies, and 8 bytes per (row, column tile) unless rows of whole vectors up to 8192 meet the tiled kernel.
   const int64_t limit_tile = q.f1_fast ? 128 : 16 * q.f1_wb;
   const bool limit_free = q.f1_fast && N % 8 == 0 && N <= 8192;
-  q.static_need = (limit_free ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8));
+  q.static_need = (limit_free ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8)) +
+                  align256(q.pad ? fast_padded_tail_bytes(K) : (q.f1_fast ? fast_f1_tail_bytes(M, K) : 0)) +
+                  align256(q.pad ? (size_t)Np * Kp * 2 : 0) + align256(q.pad ? (size_t)Np * 4 : 0);
 
   // ---- backward
   q.b1_fused = b1_fused_supported(dt, N, q.ldz);
@@ -269,7 +273,9 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
   const int64_t M = p.M, K = p.K, N = p.N;
   {
     PhaseTimer t(FDL_PHASE_F1, s);
-    if (p.pad) {
+    if (p.f1_skinny) {
+      launch_skinny_xwt(0, M, K, N, X, W, b, nullptr, Zsave, s);
+    } else if (p.pad) {
       void* Wp = ws + p.off_wpad_f;
       float* bp = reinterpret_cast<float*>(ws + p.off_bpad_f);
       launch_fast_pad_weights(K, N, W, b, Wp, bp, s);
@@ -337,10 +343,11 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   Plan p;
   const fdl_status st = check_forward_args(dt, M, K, N, X, W, b, gamma, beta, eps, Y, Zsave, mean, rstd, &p);
   if (st != FDL_OK) return st;
-  if (p.static_need + p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
+  if (p.static_need > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;   // more than the array is stated to hold
+  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
     p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the transposed weights: the kernel reads W as it is
   }
-  if (p.static_need + p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;   // the problem needs more than the array holds
+  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;
   if (!forward_args_aligned(X, W, b, gamma, beta, Y, Zsave, mean, rstd)) return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;
   clear_stale_error();
@@ -521,6 +528,7 @@ namespace {
 // storage type with rows padded to whole tiles (the fast dX kernel reads whole tiles), the first-stage column
 // partials of db, the fp32 partial sums of a split dW reduction, and the padded copy of X's last rows.
 struct ReluPlan {
+  int f1_skinny;           // few rows: the forward product (and its recomputation) on the kernel made for them
   int f1_fast, b3_fast, b4_fast, b4_split, f1_wb, b3_wb, b4_wb;
   int f1_wt;               // the forward product (and its recomputation) reads the weights from a transposed copy
   int g_blocked;           // the masked gradient G lives in 32 x 32 blocks (tuned kernels write and read all of it)
@@ -534,7 +542,8 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   const int64_t Mp = M > 0 ? M : 1;
   auto pick_wb = [dt](int64_t I, int64_t J) { return pick_generic_wb(dt, I, J); };
   // the tuned kernels where the shape fits their tiles and pipeline rounds as it is; the generic kernel otherwise
-  q->f1_fast = dt == kBF16 && fast_f1_supported(M, K, N);
+  q->f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
+  q->f1_fast = dt == kBF16 && !q->f1_skinny && fast_f1_supported(M, K, N);
   q->b3_fast = dt == kBF16 && fast_b3_supported(M, K, N);
   q->b4_fast = dt == kBF16 && fast_b4_supported(M, K, N);
   q->b4_fast_rows = q->b4_fast ? fast_b4_rows(M) : 0;
@@ -579,7 +588,9 @@ extern "C" fdl_status fdl_linear_relu_forward(fdl_dtype dt, int64_t M, int64_t K
   clear_stale_error();
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* ws = static_cast<char*>(workspace);
-  if (q.f1_fast) {
+  if (q.f1_skinny) {
+    launch_skinny_xwt(1, M, K, N, X, W, b, nullptr, Y, s);
+  } else if (q.f1_fast) {
     void* Wt = q.f1_wt ? ws + q.off_wt : nullptr;
     if (q.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
     launch_fast_xwt(1, M, K, N, X, false, W, Wt, b, nullptr, Y, false, ws + q.off_xtail, s);
@@ -689,6 +700,7 @@ namespace {
 // down projection's fast kernel may read a partial last row tile; U only where the two products are separate kernels),
 // then the padded copy of X's last rows.
 struct FfnPlan {
+  int gate_skinny, down_skinny;   // few rows: the kernel made for them
   int gate_fused;          // 1: one kernel forms both products and the gated activation (no M x H round trip)
   int up_fast, down_fast, up_wb, down_wb;
   int down_wt;             // the down projection reads its weights from a transposed copy
@@ -703,15 +715,17 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   const size_t ts = dt == kF32 ? 4 : 2;
   const int64_t Mp = M > 0 ? M : 1;
   auto pick_wb = [dt](int64_t I, int64_t J) { return pick_generic_wb(dt, I, J); };
-  q->gate_fused = dt == kBF16 && fast_gate_supported(M, D, H);
-  q->up_fast = dt == kBF16 && fast_f1_supported(M, D, H);      // [M,D] x [H,D]^T
-  q->down_fast = dt == kBF16 && fast_f1_supported(M, H, D);    // [M,H] x [D,H]^T
+  q->gate_skinny = dt == kBF16 && skinny_supported(Mp, D, 2 * H);
+  q->down_skinny = dt == kBF16 && skinny_supported(Mp, H, D);
+  q->gate_fused = dt == kBF16 && !q->gate_skinny && fast_gate_supported(M, D, H);
+  q->up_fast = dt == kBF16 && !q->gate_skinny && fast_f1_supported(M, D, H);      // [M,D] x [H,D]^T
+  q->down_fast = dt == kBF16 && !q->down_skinny && fast_f1_supported(M, H, D);    // [M,H] x [D,H]^T
   q->up_wb = pick_wb(Mp, H);
   q->down_wb = pick_wb(Mp, D);
   size_t off = 0;
   const size_t mh = align256((size_t)((Mp + 255) / 256 * 256) * H * ts);
   q->off_g = off; off += mh;
-  q->off_u = off; off += q->gate_fused ? 0 : mh;    // the fused kernel never materialises the up product
+  q->off_u = off; off += q->gate_fused || q->gate_skinny ? 0 : mh;    // the fused kernels never materialise the up product
   q->off_xtail = off; off += align256((q->up_fast || q->gate_fused) ? fast_f1_tail_bytes(M, D) : 0);
   q->down_wt = q->down_fast && M >= kTransposeFromRows;
   q->off_wt = off; off += align256(q->down_wt ? (size_t)D * H * 2 : 0);
@@ -745,7 +759,9 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
   char* ws = static_cast<char*>(workspace);
   void* G = ws + q.off_g;
   void* U = ws + q.off_u;
-  if (q.gate_fused) {
+  if (q.gate_skinny) {
+    launch_skinny_gate(M, D, H, X, Wg, Wu, G, s);
+  } else if (q.gate_fused) {
     void* Wcat = q.gate_wt ? ws + q.off_wcat : nullptr;
     if (q.gate_wt) launch_fast_transpose_gate(H, D, Wg, Wu, Wcat, s);
     launch_fast_gate(M, D, H, X, Wg, Wu, Wcat, G, q.g_blocked != 0, ws + q.off_xtail, s);
@@ -758,8 +774,10 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     g.B = Wu;
     launch_generic_xwt((int)dt, 0, g, nullptr, nullptr, U, s);
   }
-  if (!q.gate_fused) launch_silu_mul((int)dt, M * H, G, U, G, s);
-  if (q.down_fast) {
+  if (!q.gate_fused && !q.gate_skinny) launch_silu_mul((int)dt, M * H, G, U, G, s);
+  if (q.down_skinny) {
+    launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, s);
+  } else if (q.down_fast) {
     void* Wt = q.down_wt ? ws + q.off_wt : nullptr;
     if (q.down_wt) launch_fast_transpose(D, H, Wd, Wt, s);
     launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wt, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0);

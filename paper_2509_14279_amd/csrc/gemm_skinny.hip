@@ -1,0 +1,238 @@
+// bf16 products with few rows: out[m][n] = f(sum_k X[m][k] W[n][k]) for batches below (or not far above) one tile of the
+// large contraction kernel - serving a handful of requests, a decoding step of the feed-forward block.
+//
+// Bound: the weights, which are read once and used for M rows only (2 M flop per byte: at M = 16 a 250th of what would
+// keep the matrix pipes busy).  So the kernel is built to keep loads in flight, and nothing else:
+//   * a workgroup owns 16 NB output columns and 16 MB rows, and its wavefronts split the reduction among themselves: a
+//     4096-wide layer has 256 workgroups of 8 wavefronts, all of them streaming different parts of W;
+//   * a lane's MFMA fragment (v_mfma_f32_16x16x32_bf16: row lane % 16, eight reduction indices) is 16 contiguous bytes of
+//     a row of X or W, so both operands go straight from global memory into the registers the matrix pipe reads: no LDS
+//     tile, no barrier, and U steps of loads in flight per wavefront;
+//   * the wavefronts' sums meet in LDS once, at the end, in a fixed order (pairwise), in fp32.
+// Measured (weights not in the L2), M x K x N, us: 16 x 4096 x 4096 10 (3.4 TB/s), 32 rows 14, 64 rows 20, 128 rows 27;
+// 16 x 11008 x 4096 24 (3.8 TB/s); gated 16 x 4096 x 11008 46 (3.9 TB/s).  The 64 x 64 tiles of the generic kernel took 93 us
+// for 32 x 4096 x 4096 (64 workgroups, each alone with 256 slices) and 158 for each product of the 16-row block.  Loads of W
+// past the caches cost 10 - 20 %; 16 steps in flight gain nothing over 8.
+#include "common.hip.h"
+#include "internal.h"
+
+namespace fdl {
+namespace {
+
+enum { SK_STORE = 0, SK_RELU = 1, SK_MASK = 2, SK_GATE = 3 };
+
+struct SkinnyParams {
+  const bf16_t* X; const bf16_t* W; const bf16_t* W2;   // W2: SK_GATE, the up weights
+  const float* bias;      // may be null (SK_STORE, SK_RELU, SK_MASK)
+  const bf16_t* aux;      // SK_MASK: [M][N]
+  bf16_t* out;            // [M][N]
+  int64_t K;
+  int M, N;
+  int mblocks;            // row blocks of 16 MB
+};
+
+template <bool AL> __device__ __forceinline__ bf16x8 load8(const bf16_t* p) {
+  if constexpr (AL) {
+    return *reinterpret_cast<const bf16x8*>(p);
+  } else {
+    typedef __bf16 bf16x8_u __attribute__((ext_vector_type(8), aligned(2)));
+    return *reinterpret_cast<const bf16x8_u*>(p);
+  }
+}
+
+// AL: K is a multiple of 8 (every row starts on 16 bytes); otherwise the same loads from element-aligned addresses.
+template <int MB, int NB, int EPI, int WAVES, int U, bool AL>
+__global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p) {
+  constexpr int NMAT = EPI == SK_GATE ? 2 : 1;
+  constexpr int NF = NMAT * NB;                      // W fragments per step
+  __shared__ f32x4 red[WAVES > 1 ? WAVES / 2 : 1][NF * MB][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  // Row blocks of the same columns are neighbours on one die (workgroup ids are dealt round-robin over 8 dies), so that
+  // the weights they share are in its L2 when the second block reads them.
+  const int bid = (int)blockIdx.x;
+  const int slot = bid >> 3;
+  const int strip = (slot / p.mblocks) * 8 + (bid & 7);
+  const int n0 = strip * 16 * NB, m0 = (slot % p.mblocks) * 16 * MB;
+  if (n0 >= p.N) return;                             // (the grid is rounded up to whole groups of 8)
+
+  // rows past the end of either matrix read the last row; what they contribute is not stored
+  const bf16_t* wp[NF];
+  const bf16_t* xp[MB];
+#pragma unroll
+  for (int f = 0; f < NF; f++) {
+    int n = n0 + (f % NB) * 16 + l16;
+    n = n < p.N ? n : p.N - 1;
+    wp[f] = (f < NB ? p.W : p.W2) + (int64_t)n * p.K + g * 8;
+  }
+#pragma unroll
+  for (int b = 0; b < MB; b++) {
+    int m = m0 + b * 16 + l16;
+    m = m < p.M ? m : p.M - 1;
+    xp[b] = p.X + (int64_t)m * p.K + g * 8;
+  }
+  f32x4 acc[NF][MB];
+#pragma unroll
+  for (int f = 0; f < NF; f++)
+#pragma unroll
+    for (int b = 0; b < MB; b++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[f][b][r] = 0.0f;
+
+  const int full = (int)(p.K >> 5);                  // whole steps of 32
+  // groups of U steps are dealt over the wavefronts in turn: together they walk 64 U WAVES contiguous bytes of each row
+  for (int s = wave * U; s < full; s += WAVES * U) {
+    bf16x8 w[U][NF], x[U][MB];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int64_t k = (int64_t)(s + u < full ? s + u : full - 1) * 32;   // past the end: the last step again, unused
+#pragma unroll
+      for (int f = 0; f < NF; f++) w[u][f] = load8<AL>(wp[f] + k);
+#pragma unroll
+      for (int b = 0; b < MB; b++) x[u][b] = load8<AL>(xp[b] + k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (s + u < full) {                            // wave-uniform
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+          for (int b = 0; b < MB; b++) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][f], x[u][b], acc[f][b], 0, 0, 0);
+      }
+  }
+  if ((p.K & 31) != 0 && wave == WAVES - 1) {        // the last, partial step: element by element, zeros past the end
+    const int64_t k = (int64_t)full * 32;
+    bf16x8 w[NF], x[MB];
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const bool in = k + g * 8 + e < p.K;
+#pragma unroll
+      for (int f = 0; f < NF; f++) w[f][e] = in ? wp[f][k + e] : (bf16_t)0.0f;
+#pragma unroll
+      for (int b = 0; b < MB; b++) x[b][e] = in ? xp[b][k + e] : (bf16_t)0.0f;
+    }
+#pragma unroll
+    for (int f = 0; f < NF; f++)
+#pragma unroll
+      for (int b = 0; b < MB; b++) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[f], x[b], acc[f][b], 0, 0, 0);
+  }
+
+  // pairwise over the wavefronts: the upper half hands its sums to the lower half until one is left
+#pragma unroll
+  for (int half = WAVES / 2; half >= 1; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int f = 0; f < NF; f++)
+#pragma unroll
+        for (int b = 0; b < MB; b++) red[wave - half][f * MB + b][lane] = acc[f][b];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int f = 0; f < NF; f++)
+#pragma unroll
+        for (int b = 0; b < MB; b++) {
+          const f32x4 t = red[wave][f * MB + b][lane];
+#pragma unroll
+          for (int r = 0; r < 4; r++) acc[f][b][r] += t[r];
+        }
+    }
+    if (half > 1) __syncthreads();                   // the slots are written again
+  }
+  if (wave != 0) return;
+
+  // a lane holds columns n0 + 16 f + 4 g .. + 3 of row m0 + 16 b + l16
+  const bool vec = (p.N & 3) == 0;                   // then a group of four columns exists whole or not at all
+#pragma unroll
+  for (int f = 0; f < NB; f++) {
+    const int n = n0 + f * 16 + g * 4;
+    if (n >= p.N) continue;
+    float bias[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) bias[r] = (EPI != SK_GATE && p.bias != nullptr && n + r < p.N) ? p.bias[n + r] : 0.0f;
+#pragma unroll
+    for (int b = 0; b < MB; b++) {
+      const int m = m0 + b * 16 + l16;
+      if (m >= p.M) continue;
+      const int64_t at = (int64_t)m * p.N + n;
+      bf16x4 o;
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        float v = acc[f][b][r];
+        if (EPI == SK_GATE) {
+          const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * v));
+          v = v * sg * acc[NF - NB + f][b][r];
+        } else {
+          v += bias[r];
+          if (EPI == SK_RELU) v = v > 0.0f ? v : 0.0f;
+        }
+        if (EPI == SK_MASK) o[r] = (v > 0.0f && n + r < p.N) ? p.aux[at + r] : (bf16_t)0.0f;
+        else o[r] = (bf16_t)v;
+      }
+      if (vec) {
+        *reinterpret_cast<bf16x4*>(p.out + at) = o;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+          if (n + r < p.N) p.out[at + r] = o[r];
+      }
+    }
+  }
+}
+
+template <int MB, int NB, int EPI, int WAVES, int U> void launch_skinny(SkinnyParams p, hipStream_t s) {
+  p.mblocks = (p.M + 16 * MB - 1) / (16 * MB);
+  const int strips = (p.N + 16 * NB - 1) / (16 * NB);
+  const unsigned grid = (unsigned)((strips + 7) / 8 * 8) * (unsigned)p.mblocks;
+  if (p.K % 8 == 0) hipLaunchKernelGGL((gemm_skinny_kernel<MB, NB, EPI, WAVES, U, true>), dim3(grid), dim3(64 * WAVES), 0, s, p);
+  else hipLaunchKernelGGL((gemm_skinny_kernel<MB, NB, EPI, WAVES, U, false>), dim3(grid), dim3(64 * WAVES), 0, s, p);
+}
+
+// Tile and depth by the number of rows: the fewer there are, the more loads of W a wavefront can hold; from 33 rows on
+// two column blocks share each load of X, and from 65 four row blocks each load of W where that still gives every compute
+// unit a workgroup.
+template <int EPI> void dispatch_skinny(const SkinnyParams& p, hipStream_t s) {
+  if (p.M <= 16) { launch_skinny<1, 1, EPI, 8, 8>(p, s); return; }
+  if (p.M <= 32) { launch_skinny<2, 1, EPI, 8, 4>(p, s); return; }
+  if constexpr (EPI == SK_GATE) {
+    launch_skinny<4, 1, EPI, 8, 4>(p, s);
+  } else {
+    const int64_t wide = (int64_t)((p.N + 31) / 32) * ((p.M + 63) / 64);
+    if (wide >= 256) launch_skinny<4, 2, EPI, 8, 4>(p, s);
+    else launch_skinny<2, 2, EPI, 8, 4>(p, s);
+  }
+}
+
+}  // namespace
+
+// Where this kernel is the faster one.  It rereads X for every 16 or 32 columns, so its time grows with the output, while
+// the tiled kernel needs the whole reduction's slices however few tiles there are.  us, this kernel / the tiled one, for
+// K x N and M rows: 4096 x 4096: 128 rows 29 / 81, 256 48 / 78, 384 68 / 82, 512 78 / 77; 1024 x 1024: 512 11 / 24, 1024 16 /
+// 25, 1536 24 / 25; 4096 x 1024: 1024 48 / 77, 1536 72 / 77.  Rows that start at any element (K % 8) cost it twice the
+// loads; against the generic kernel, 771 x 1537: 256 rows 17 / 24, 384 24.5 / 24.2, 768 36 / 29.  Below 128 rows the tiled
+// kernel does not run at all, and the generic one is slower at every size (4096 x 4096, 64 rows: 20 / 88).
+bool skinny_supported(int64_t M, int64_t K, int64_t N) {
+  return M < 128 || M * N <= (K % 8 == 0 ? 3 << 19 : 1 << 19);
+}
+
+// out[m][n] = f(sum_k X[m][k] W[n][k] + bias[n]): kind 0 plain (bias may be null), 1 max(., 0), 2 aux[m][n] where positive
+void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias,
+                       const void* aux, void* out, hipStream_t s) {
+  SkinnyParams p = {};
+  p.X = (const bf16_t*)X; p.W = (const bf16_t*)W; p.bias = bias; p.aux = (const bf16_t*)aux; p.out = (bf16_t*)out;
+  p.K = K; p.M = (int)M; p.N = (int)N;
+  if (kind == 1) dispatch_skinny<SK_RELU>(p, s);
+  else if (kind == 2) dispatch_skinny<SK_MASK>(p, s);
+  else dispatch_skinny<SK_STORE>(p, s);
+}
+
+// out[m][h] = SiLU(sum_d X[m][d] Wg[h][d]) * (sum_d X[m][d] Wu[h][d])
+void launch_skinny_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s) {
+  SkinnyParams p = {};
+  p.X = (const bf16_t*)X; p.W = (const bf16_t*)Wg; p.W2 = (const bf16_t*)Wu; p.out = (bf16_t*)out;
+  p.K = D; p.M = (int)M; p.N = (int)H;
+  dispatch_skinny<SK_GATE>(p, s);
+}
+
+}  // namespace fdl

@@ -21,6 +21,7 @@ struct Plan {
   int dt;
   int64_t M, K, N;
   // forward
+  int f1_skinny;          // 1: bf16 kernel for few rows (before the two below)
   int f1_fast;            // 1: bf16 fast MFMA kernel, 0: generic kernel
   int f1_wb;              // generic kernel: 16x16 blocks per wave tile side (wave tile = 16*wb)
   int f1_wt;              // 1: the fast kernel reads the weights from a transposed copy (large batches)
@@ -133,6 +134,12 @@ int colsum_groups(int64_t M);
 // blocked: G is stored in 32 x 32 blocks (bf16; M, N multiples of 32)
 void launch_colsum(int dt, int64_t M, int64_t N, const void* G, bool blocked, void* colpart, float* out, hipStream_t s);
 void launch_silu_mul(int dt, int64_t n, const void* G, const void* U, void* H, hipStream_t s);
+
+// ---- bf16 products with few rows (gemm_skinny.hip): any K and N -----------------------------------
+bool skinny_supported(int64_t M, int64_t K, int64_t N);
+void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias,
+                       const void* aux, void* out, hipStream_t s);
+void launch_skinny_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s);
 
 // ---- bf16 fast path -----------------------------------------------------------------------------
 // F1 and B3 accept any M >= 128 (the last row tile may be partial); N, K as the tiles and the pipeline require.
