@@ -96,21 +96,19 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
 
   // ---- which contraction kernels run
   // bf16: the tuned kernel where N and K are multiples of the tile and the pipeline round (as they are), or - padded
-  // mode - merely multiples of 8: the kernels then run on N and K rounded up to the tile, on a zero-padded copy of
-  // the weights, and leave the surplus unstored.  Everything else takes the generic kernel.
+  // mode - on N and K rounded up to the tile, on zero-padded copies of the weights (and of X where its rows start at any
+  // element), leaving the surplus unstored.  Everything else takes the generic kernel.
   q.pad = dt == kBF16 && fast_padded_supported(M, K, N);
   const int64_t Np = q.pad ? fast_pad_dim(N) : N, Kp = q.pad ? fast_pad_dim(K) : K;
-  q.ldz = Np;
   const int64_t Mp = M > 0 ? M : 1;
-  auto pick_wb = [dt](int64_t I, int64_t J) { return pick_generic_wb(dt, I, J); };
 
   // ---- forward
   q.f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
   q.f1_fast = q.pad || (dt == kBF16 && fast_f1_supported(M, K, N));
-  q.f1_wb = pick_wb(Mp, N);
+  q.f1_wb = pick_generic_wb(dt, Mp, N);
   size_t off = 0;
   const bool tiled = q.f1_fast && !q.f1_skinny;
-  q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_tail_bytes(K) : fast_f1_tail_bytes(M, K)));
+  q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K) : fast_f1_tail_bytes(M, K)));
   q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
   // Large batches on the tuned kernel (tile-aligned N and K): the weights are transposed first, 4 N K bytes of traffic
@@ -120,15 +118,22 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
   q.fwd_bytes = off;
   // The static entry point's limit is part of its contract (see the header) and does not move with the plan: the tiled
-  // kernels' copies, and 8 bytes per (row, column tile) unless rows of whole vectors up to 8192 meet the tiled kernel.
-  const int64_t limit_tile = q.f1_fast ? 128 : 16 * q.f1_wb;
-  const bool limit_free = q.f1_fast && N % 8 == 0 && N <= 8192;
-  q.static_need = (limit_free ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8)) +
-                  align256(q.pad ? fast_padded_tail_bytes(K) : (q.f1_fast ? fast_f1_tail_bytes(M, K) : 0)) +
-                  align256(q.pad ? (size_t)Np * Kp * 2 : 0) + align256(q.pad ? (size_t)Np * 4 : 0);
+  // kernels' copies for whole 16-byte rows, and 8 bytes per (row, column tile) unless rows of whole vectors up to 8192 meet
+  // the tiled kernel.
+  const bool copies = q.pad && N % 8 == 0 && K % 8 == 0 && K >= 128;
+  const bool limit_fast = copies || (!q.pad && q.f1_fast);
+  const int64_t limit_tile = limit_fast ? 128 : 16 * q.f1_wb;
+  q.static_need = (limit_fast && N % 8 == 0 && N <= 8192 ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8)) +
+                  align256(copies ? fast_padded_tail_bytes(K) : (limit_fast ? fast_f1_tail_bytes(M, K) : 0)) +
+                  align256(copies ? (size_t)Np * Kp * 2 : 0) + align256(copies ? (size_t)Np * 4 : 0);
 
   // ---- backward
-  q.b1_fused = b1_fused_supported(dt, N, q.ldz);
+  // dZ in 32 x 32 blocks where only the fused row kernel writes it and only the tuned kernels read it; the vector path of
+  // the row kernel needs N % 8 = 0, which the tiles imply
+  // (the row kernel pays for it with about 8 % of its time where a row fills 1024 threads, dX gains about 9 %: not
+  //  worth it when such rows meet a short K)
+  q.b1_fused = b1_fused_supported(dt, N, Np);
+  const bool may_block = q.b1_fused && (K >= 1024 || N <= 4096);
   if (q.b1_fused) {
     const int64_t want = b1_fused_groups(dt, Mp, N);
     q.b1_groups = (int)(Mp < want ? Mp : want);
@@ -138,9 +143,30 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
     q.b1_rows_per_group = (int)rpg;
     q.b1_groups = (int)((Mp + rpg - 1) / rpg);
   }
+  off = 0;
+  q.off_c12 = off; off += align256(q.b1_fused ? 0 : (size_t)2 * Mp * cs);
+  q.off_colpart = off; off += align256((size_t)q.b1_groups * 3 * N * cs);
+  make_grad_plan(dt, M, K, N, may_block, &off, &q.g);
+  q.bwd_bytes = off;
+  q.bytes = q.fwd_bytes > q.bwd_bytes ? q.fwd_bytes : q.bwd_bytes;
+  *p = q;
+  return true;
+}
+
+// The two contractions that end a backward pass, dX [M,K] = dZ W and dW [N,K] = dZ^T X, with the workspace regions they
+// need behind *off.  may_block: the kernel that writes dZ can write it in 32 x 32 blocks.
+void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, size_t* off, GradPlan* p) {
+  GradPlan q = {};
+  const size_t ts = dt == kF32 ? 4 : 2;
+  const int64_t Mp = M > 0 ? M : 1;
+  q.dt = dt; q.M = M; q.K = K; q.N = N;
+  q.pad = dt == kBF16 && fast_padded_supported(M, K, N);
+  q.stage_x = q.pad && fast_padded_stages_x(K);
+  const int64_t Np = q.pad ? fast_pad_dim(N) : N, Kp = q.pad ? fast_pad_dim(K) : K;
+  q.ldz = Np;
   q.b3_fast = q.pad || (dt == kBF16 && fast_b3_supported(M, K, N));
-  q.b3_wb = pick_wb(Mp, K);
-  q.b4_wb = pick_wb(N, K);
+  q.b3_wb = pick_generic_wb(dt, Mp, K);
+  q.b4_wb = pick_generic_wb(dt, N, K);
   if (q.pad) {
     q.b4_fast_rows = fast_padded_b4_rows(M, K);
     q.b4_fast = q.b4_fast_rows >= 128;
@@ -149,33 +175,20 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
     q.b4_fast = dt == kBF16 && fast_b4_supported(M, K, N);
     q.b4_fast_rows = q.b4_fast ? fast_b4_rows(M) : 0;
   }
-  q.b4_split = q.b4_fast ? fast_b4_split(q.b4_fast_rows, K, N) : 1;
-  q.pair_sa = q.pair_sb = 1;
-  q.pair = !q.pad && q.b3_fast && q.b4_fast && q.b4_fast_rows == M && fast_pair_plan(M, K, N, &q.pair_sa, &q.pair_sb);
-  if (q.pair) q.b4_split = q.pair_sb;
-  // dZ in 32 x 32 blocks where only the fused row kernel writes it and only the tuned kernels read it (no generic
-  // kernel over the last rows, no padded pitch); the vector path of the row kernel needs N % 8 = 0, which the tiles imply
-  // (the row kernel pays for it with about 8 % of its time where a row fills 1024 threads, dX gains about 9 %: not
-  //  worth it when such rows meet a short K)
-  q.dz_blocked = dt == kBF16 && q.b1_fused && N <= 8192 && !q.pad && q.b3_fast && q.b4_fast && q.b4_fast_rows == M && M % 32 == 0 &&
-                 N % 32 == 0 && (K >= 1024 || N <= 4096);
-  // fp32 partial sums of dW: the parts of a split reduction, one more for the rows the fast kernel leaves to the
-  // generic one; in padded mode the fast kernel always writes partials
-  int b4_parts = q.b4_split + (q.b4_fast && q.b4_fast_rows < M ? 1 : 0);
-  if (q.pad && q.b4_fast && b4_parts < 2) b4_parts = 2;   // (a single part is still a partial: reduced into dW)
-  off = 0;
-  // dZ: the fast dX kernel reads whole 256-row tiles, so the buffer is rounded up (the surplus rows are never
-  // written and never reach an output)
-  q.off_dz = off; off += align256((size_t)((Mp + 255) / 256 * 256) * Np * ts);
-  q.off_c12 = off; off += align256(q.b1_fused ? 0 : (size_t)2 * Mp * cs);
-  q.off_colpart = off; off += align256((size_t)q.b1_groups * 3 * N * cs);
-  q.off_dwpart = off; off += align256(b4_parts > 1 ? (size_t)b4_parts * N * K * 4 : 0);
-  q.off_wpad_b = off; off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
-  q.off_dxpart = off; off += align256(q.pair && q.pair_sa > 1 ? (size_t)q.pair_sa * M * K * 4 : 0);
-  q.bwd_bytes = off;
-  q.bytes = q.fwd_bytes > q.bwd_bytes ? q.fwd_bytes : q.bwd_bytes;
+  q.extra = q.b4_fast && q.b4_fast_rows < M ? 1 : 0;    // rows of dW's reduction left to the generic kernel: one more partial
+  q.split_a = 1;
+  q.split_b = q.b4_fast ? fast_b4_split(q.b4_fast_rows, K, N) : 1;
+  q.pair = q.b3_fast && q.b4_fast && fast_pair_plan(M, K, N, q.b4_fast_rows, &q.split_a, &q.split_b);
+  q.blocked = may_block && dt == kBF16 && !q.pad && q.b3_fast && q.b4_fast && q.b4_fast_rows == M && M % 32 == 0 && N % 32 == 0;
+  // dZ: the fast dX kernel reads whole 256-row tiles, so the buffer is rounded up (the surplus rows never reach an output)
+  q.off_dz = *off; *off += align256((size_t)((Mp + 255) / 256 * 256) * Np * ts);
+  // fp32 partial sums: the parts of a split reduction, one more for the rows the fast kernel leaves to the generic one
+  q.parts_b = q.split_b + q.extra;
+  q.off_dxpart = *off; *off += align256(q.split_a > 1 ? (size_t)q.split_a * partial_stride(M * K) * 4 : 0);
+  q.off_dwpart = *off; *off += align256(q.parts_b > 1 ? (size_t)q.parts_b * partial_stride(N * K) * 4 : 0);
+  q.off_wpad = *off; *off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
+  q.off_xpad = *off; *off += align256(q.stage_x ? fast_padded_x_bytes(M, K) : 0);
   *p = q;
-  return true;
 }
 
 }  // namespace fdl
@@ -274,12 +287,14 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
   {
     PhaseTimer t(FDL_PHASE_F1, s);
     if (p.f1_skinny) {
-      launch_skinny_xwt(0, M, K, N, X, W, b, nullptr, Zsave, s);
+      launch_skinny_xwt(0, M, K, N, X, W, b, nullptr, Zsave, N, s);
     } else if (p.pad) {
       void* Wp = ws + p.off_wpad_f;
       float* bp = reinterpret_cast<float*>(ws + p.off_bpad_f);
-      launch_fast_pad_weights(K, N, W, b, Wp, bp, s);
-      launch_fast_f1_padded(M, K, N, X, Wp, bp, Zsave, ws + p.off_xtail, s);
+      StageJobs j = {};
+      stage_padded(&j, M, K, N, X, W, b, ws + p.off_xtail, Wp, bp);
+      launch_stage(j, s);
+      launch_fast_xwt_padded(0, M, K, N, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, s);
     } else if (p.f1_fast) {
       void* Wt = p.f1_wt ? ws + p.off_wt : nullptr;
       if (p.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
@@ -347,7 +362,9 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
     p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the transposed weights: the kernel reads W as it is
   }
-  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;
+  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) {
+    p.pad = 0; p.f1_fast = 0; p.fwd_bytes = 0;        // no room for the padded copies either: the generic kernel needs none
+  }
   if (!forward_args_aligned(X, W, b, gamma, beta, Y, Zsave, mean, rstd)) return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;
   clear_stale_error();
@@ -356,6 +373,72 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   // every scratch location a forward pass reads has been written earlier in the same pass (padded or transposed
   // weights, the padded copy of X's last rows), so nothing has to be cleared between calls
   return forward_launches(p, X, W, b, gamma, beta, eps, Y, Zsave, mean, rstd, ws, static_cast<hipStream_t>(hip_stream));
+}
+
+// ---- dX and dW (see make_grad_plan) ---------------------------------------------------------------------------------
+// whether the contractions leave fp32 partial sums behind for launch_finish
+static bool grad_leaves_sums(const GradPlan& p) { return p.split_a > 1 || p.parts_b > 1; }
+
+// padded mode: the copies the contractions read, and zeros in the rows behind dZ's last where dW's reduction covers them
+static void stage_grad(const GradPlan& p, StageJobs* j, const void* X, const void* W, char* ws) {
+  stage_padded(j, p.M, p.K, p.N, p.stage_x ? X : nullptr, W, nullptr, ws + p.off_xpad, ws + p.off_wpad, nullptr);
+  if (p.b4_fast_rows > p.M)
+    stage_matrix(j, nullptr, 0, 0, 0, ws + p.off_dz + (size_t)p.M * p.ldz * 2, p.b4_fast_rows - p.M, p.ldz);
+}
+
+static void sum_later(TailSums* tj, int k, const void* part, int parts, int64_t n, void* out) {
+  tj->part[k] = static_cast<const float*>(part); tj->parts[k] = parts; tj->n[k] = n; tj->out[k] = out;
+}
+
+// dX = dZ W; where both contractions share a launch (p.pair), dW too
+static void launch_grad_dx(const GradPlan& p, const void* dZ, const void* W, const void* X, void* dX, void* dW, char* ws,
+                           TailSums* tj, hipStream_t s) {
+  const int64_t M = p.M, K = p.K, N = p.N;
+  const int64_t Kp = p.pad ? fast_pad_dim(K) : K;
+  if (p.pair) {
+    PairArgs a = {};
+    a.M = M; a.K = K; a.N = N; a.rows = p.b4_fast_rows; a.sa = p.split_a; a.sb = p.split_b; a.extra = p.extra;
+    a.dZ = dZ; a.ldz = p.ldz; a.dz_blocked = p.blocked != 0;
+    a.W = p.pad ? ws + p.off_wpad : W; a.ldw = Kp;
+    a.X = p.stage_x ? ws + p.off_xpad : X; a.ldx = p.stage_x ? Kp : K;
+    a.dX = dX; a.dxpart = ws + p.off_dxpart; a.dW = dW; a.dwpart = ws + p.off_dwpart;
+    launch_fast_pair(a, s);
+    if (p.split_a > 1) sum_later(tj, 0, ws + p.off_dxpart, p.split_a, M * K, dX);
+  } else if (p.pad) {
+    launch_fast_b3_padded(M, K, N, dZ, ws + p.off_wpad, dX, s);
+  } else if (p.b3_fast) {
+    launch_fast_b3(M, K, N, dZ, p.blocked != 0, W, dX, s);
+  } else {
+    GemmDesc g = {dZ, W, M, K, N, p.ldz, K, true, false, p.b3_wb};
+    launch_generic_store(p.dt, g, dX, s);
+  }
+}
+
+// dW = dZ^T X.  The fast kernel reduces over the first b4_fast_rows rows (a whole number of pipeline rounds); the few rows
+// after them go through the generic kernel into one more fp32 partial sum.
+static void launch_grad_dw(const GradPlan& p, const void* dZ, const void* X, void* dW, char* ws, TailSums* tj, hipStream_t s) {
+  const int64_t K = p.K, N = p.N, Mf = p.b4_fast_rows;
+  float* dwpart = reinterpret_cast<float*>(ws + p.off_dwpart);
+  if (!p.b4_fast) {
+    GemmDesc g = {dZ, X, N, K, p.M, p.ldz, K, false, false, p.b4_wb};
+    launch_generic_store(p.dt, g, dW, s);
+    return;
+  }
+  if (p.pair) {
+    // (with dX)
+  } else if (p.pad) {
+    launch_fast_b4_padded(Mf, K, N, p.split_b, p.extra, dZ, p.stage_x ? ws + p.off_xpad : X, p.stage_x ? fast_pad_dim(K) : K, dW,
+                          dwpart, s);
+  } else {
+    launch_fast_b4(Mf, K, N, p.split_b, p.extra, dZ, p.blocked != 0, X, dW, dwpart, s);
+  }
+  if (p.extra) {
+    const char* dZt = static_cast<const char*>(dZ) + (size_t)Mf * p.ldz * 2;
+    const char* Xt = static_cast<const char*>(X) + (size_t)Mf * K * 2;
+    GemmDesc g = {dZt, Xt, N, K, p.M - Mf, p.ldz, K, false, false, p.b4_wb};
+    launch_generic_store_f32(g, dwpart + (size_t)p.split_b * partial_stride(N * K), s);
+  }
+  if (p.parts_b > 1) sum_later(tj, 1, dwpart, p.parts_b, N * K, dW);
 }
 
 extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N, const void* dY, const void* X,
@@ -384,92 +467,42 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
     return launch_status();
   }
   char* ws = static_cast<char*>(workspace);
-  void* dZ = ws + p.off_dz;
+  void* dZ = ws + p.g.off_dz;
   void* c12 = ws + p.off_c12;
   void* colpart = ws + p.off_colpart;
 
   {
     PhaseTimer t(FDL_PHASE_B1, s);
     if (p.b1_fused) {
-      launch_b1_fused((int)dt, M, N, p.ldz, p.b1_groups, p.dz_blocked != 0, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
+      launch_b1_fused((int)dt, M, N, p.g.ldz, p.b1_groups, p.g.blocked != 0, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
     } else {
       launch_b1a((int)dt, M, N, dY, Zsave, gamma, mean, rstd, c12, s);
-      launch_b1b((int)dt, M, N, p.ldz, p.b1_rows_per_group, p.b1_groups, dY, Zsave, gamma, mean, rstd, c12, dZ, colpart, s);
+      launch_b1b((int)dt, M, N, p.g.ldz, p.b1_rows_per_group, p.b1_groups, dY, Zsave, gamma, mean, rstd, c12, dZ, colpart, s);
+      if (p.g.pad) launch_zero_cols_bf16(dZ, M, N, p.g.ldz, s);   // the surplus columns enter the contractions
     }
-    if (p.pad && !p.b1_fused) launch_zero_cols_bf16(dZ, M, N, p.ldz, s);   // the surplus columns enter the dX and dW contractions
   }
   // Where the contractions below leave split reductions behind (bf16 tuned path), their sums and the column sums
   // share one launch at the end of the pass; otherwise the column sums are finished here.
-  const bool pair_sums = p.pair && (p.pair_sa > 1 || p.pair_sb > 1);
-  const bool b4_sums = !p.pair && p.b4_fast && (p.pad || p.b4_split > 1 || p.b4_fast_rows < M);
-  const bool tail = dt == FDL_BF16 && (pair_sums || b4_sums);
+  const bool tail = grad_leaves_sums(p.g);
   TailSums tj = {};
-  tj.colpart = static_cast<const float*>(colpart); tj.groups = p.b1_groups; tj.N = N;
-  tj.dbeta = dbeta; tj.dgamma = dgamma; tj.db = db;
-  auto sum_later = [&](int k, const void* part, int parts, int64_t n, void* out) {
-    tj.part[k] = static_cast<const float*>(part); tj.parts[k] = parts; tj.n[k] = n; tj.out[k] = out;
-  };
+  tj.colpart = static_cast<const float*>(colpart); tj.groups = p.b1_groups; tj.N = N; tj.kinds = 3;
+  tj.col_out[0] = dbeta; tj.col_out[1] = dgamma; tj.col_out[2] = db;
   {
     PhaseTimer t(FDL_PHASE_B2, s);
     if (!tail) launch_b2((int)dt, N, p.b1_groups, colpart, dbeta, dgamma, db, s);
   }
-  {
-    // B3: dX[M,K] = dZ[M,N] W[N,K]
-    PhaseTimer t(FDL_PHASE_B3, s);
-    if (p.pair) {
-      // one launch for both contractions (B4 below only sums the partial sums of dW, where its reduction is split)
-      launch_fast_pair(M, K, N, p.pair_sa, p.pair_sb, dZ, p.dz_blocked != 0, W, X, dX, ws + p.off_dxpart, dW,
-                       ws + p.off_dwpart, s);
-      if (p.pair_sa > 1) sum_later(0, ws + p.off_dxpart, p.pair_sa, M * K, dX);
-    } else if (p.pad) {
-      void* Wp = ws + p.off_wpad_b;
-      launch_fast_pad_weights(K, N, W, nullptr, Wp, nullptr, s);
-      launch_fast_b3_padded(M, K, N, dZ, Wp, dX, s);
-    } else if (p.b3_fast) {
-      launch_fast_b3(M, K, N, dZ, p.dz_blocked != 0, W, dX, s);
-    } else {
-      GemmDesc g = {dZ, W, M, K, N, p.ldz, K, true, false, p.b3_wb};
-      launch_generic_store((int)dt, g, dX, s);
-    }
+  if (p.g.pad) {
+    StageJobs j = {};
+    stage_grad(p.g, &j, X, W, ws);
+    launch_stage(j, s);
   }
   {
-    // B4: dW[N,K] = dZ^T[N,M] X[M,K]
+    PhaseTimer t(FDL_PHASE_B3, s);
+    launch_grad_dx(p.g, dZ, W, X, dX, dW, ws, &tj, s);
+  }
+  {
     PhaseTimer t(FDL_PHASE_B4, s);
-    if (p.pair) {
-      if (p.pair_sb > 1) sum_later(1, ws + p.off_dwpart, p.pair_sb, N * K, dW);
-    } else if (p.pad && p.b4_fast) {
-      // padded mode: the fast kernel writes fp32 partials of the first b4_fast_rows rows; the generic kernel adds one
-      // for the remaining rows (there is always at least one when K is not a multiple of the tile)
-      const int64_t Mf = p.b4_fast_rows;
-      float* dwpart = reinterpret_cast<float*>(ws + p.off_dwpart);
-      launch_fast_b4_padded(Mf, K, N, p.b4_split, dZ, X, dwpart, s);
-      int parts = p.b4_split;
-      if (Mf < M) {
-        const char* dZt = static_cast<const char*>(dZ) + (size_t)Mf * p.ldz * 2;
-        const char* Xt = static_cast<const char*>(X) + (size_t)Mf * K * 2;
-        GemmDesc g = {dZt, Xt, N, K, M - Mf, p.ldz, K, false, false, p.b4_wb};
-        launch_generic_store_f32(g, dwpart + (size_t)parts * N * K, s);
-        parts++;
-      }
-      sum_later(1, dwpart, parts, N * K, dW);
-    } else if (p.b4_fast) {
-      // the fast kernel reduces over the first b4_fast_rows rows (a whole number of pipeline rounds); the few rows
-      // after them go through the generic kernel into one more fp32 partial sum
-      const int64_t Mf = p.b4_fast_rows;
-      const int extra = Mf < M ? 1 : 0;
-      float* dwpart = reinterpret_cast<float*>(ws + p.off_dwpart);
-      launch_fast_b4(Mf, K, N, p.b4_split, extra, dZ, p.dz_blocked != 0, X, dW, dwpart, s);
-      if (extra) {
-        const char* dZt = static_cast<const char*>(dZ) + (size_t)Mf * N * 2;
-        const char* Xt = static_cast<const char*>(X) + (size_t)Mf * K * 2;
-        GemmDesc g = {dZt, Xt, N, K, M - Mf, N, K, false, false, p.b4_wb};
-        launch_generic_store_f32(g, dwpart + (size_t)p.b4_split * N * K, s);
-      }
-      if (p.b4_split + extra > 1) sum_later(1, dwpart, p.b4_split + extra, N * K, dW);
-    } else {
-      GemmDesc g = {dZ, X, N, K, M, p.ldz, K, false, false, p.b4_wb};
-      launch_generic_store((int)dt, g, dW, s);
-    }
+    launch_grad_dw(p.g, dZ, X, dW, ws, &tj, s);
     if (tail) launch_finish(tj, s);
   }
   return launch_status();
@@ -524,40 +557,41 @@ extern "C" fdl_status fdl_forward_inference(fdl_dtype dt, int64_t M, int64_t K, 
 
 // ---- Linear + ReLU -------------------------------------------------------------------------------------------------
 namespace {
-// Workspace of the Linear+ReLU pair (one layout for both passes): the masked upstream gradient G [M][N] in the
-// storage type with rows padded to whole tiles (the fast dX kernel reads whole tiles), the first-stage column
-// partials of db, the fp32 partial sums of a split dW reduction, and the padded copy of X's last rows.
+// Workspace of the Linear+ReLU pair (one layout for both passes): the first-stage column partials of db, the copies the
+// forward product needs (padded weights and bias, X or its last rows, or transposed weights), and what the two gradient
+// contractions need, the masked upstream gradient G among it (the dZ of GradPlan).
 struct ReluPlan {
   int f1_skinny;           // few rows: the forward product (and its recomputation) on the kernel made for them
-  int f1_fast, b3_fast, b4_fast, b4_split, f1_wb, b3_wb, b4_wb;
+  int f1_fast, f1_wb;
+  int pad;                 // padded mode of the fast contractions
   int f1_wt;               // the forward product (and its recomputation) reads the weights from a transposed copy
-  int g_blocked;           // the masked gradient G lives in 32 x 32 blocks (tuned kernels write and read all of it)
-  int64_t b4_fast_rows;
-  size_t off_g, off_colpart, off_dwpart, off_xtail, off_wt, bytes;
+  GradPlan g;
+  size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, bytes;
 };
 bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   if (dt != kF32 && dt != kBF16) return false;
   if (!shape_ok(M, K, N)) return false;
-  const size_t ts = dt == kF32 ? 4 : 2, cs = dt == kF32 ? 8 : 4;
+  const size_t cs = dt == kF32 ? 8 : 4;
   const int64_t Mp = M > 0 ? M : 1;
-  auto pick_wb = [dt](int64_t I, int64_t J) { return pick_generic_wb(dt, I, J); };
-  // the tuned kernels where the shape fits their tiles and pipeline rounds as it is; the generic kernel otherwise
+  // the tuned kernels where the shape fits their tiles and pipeline rounds, as it is or padded; else the generic kernel
+  q->pad = dt == kBF16 && fast_padded_supported(M, K, N);
   q->f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
-  q->f1_fast = dt == kBF16 && !q->f1_skinny && fast_f1_supported(M, K, N);
-  q->b3_fast = dt == kBF16 && fast_b3_supported(M, K, N);
-  q->b4_fast = dt == kBF16 && fast_b4_supported(M, K, N);
-  q->b4_fast_rows = q->b4_fast ? fast_b4_rows(M) : 0;
-  q->b4_split = q->b4_fast ? fast_b4_split(q->b4_fast_rows, K, N) : 1;
-  q->f1_wb = pick_wb(Mp, N); q->b3_wb = pick_wb(Mp, K); q->b4_wb = pick_wb(N, K);
-  const int b4_parts = q->b4_split + (q->b4_fast && q->b4_fast_rows < M ? 1 : 0);
+  q->f1_fast = dt == kBF16 && fast_f1_supported(M, K, N);
+  q->f1_wb = pick_generic_wb(dt, Mp, N);
+  const bool tiled = !q->f1_skinny;
   size_t off = 0;
-  q->off_g = off; off += align256((size_t)((Mp + 255) / 256 * 256) * N * ts);
   q->off_colpart = off; off += align256((size_t)colsum_groups(Mp) * N * cs);
-  q->off_dwpart = off; off += align256(b4_parts > 1 ? (size_t)b4_parts * N * K * 4 : 0);
-  q->off_xtail = off; off += align256(q->f1_fast ? fast_f1_tail_bytes(M, K) : 0);
-  q->f1_wt = q->f1_fast && M >= kTransposeFromRows;
+  // (the masking epilogue of the tuned forward product can write blocks)
+  make_grad_plan(dt, M, K, N, /*may_block=*/tiled && q->f1_fast, &off, &q->g);
+  // the padded copies of W and (where all of it is copied) X serve the forward product and the gradient contractions
+  q->off_wpad = q->g.off_wpad;
+  q->off_xtail = q->g.off_xpad;
+  if (tiled && !q->g.stage_x) {
+    q->off_xtail = off; off += align256(q->pad ? fast_padded_tail_bytes(K) : (q->f1_fast ? fast_f1_tail_bytes(M, K) : 0));
+  }
+  q->off_bpad = off; off += align256(tiled && q->pad ? (size_t)fast_pad_dim(N) * 4 : 0);
+  q->f1_wt = tiled && q->f1_fast && M >= kTransposeFromRows;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
-  q->g_blocked = q->f1_fast && q->b3_fast && q->b4_fast && q->b4_fast_rows == M && M % 32 == 0 && N % 32 == 0;
   q->bytes = off;
   return true;
 }
@@ -565,6 +599,25 @@ fdl_status check_ws(const void* workspace, size_t have, size_t need) {
   if (workspace == nullptr || have < need) return FDL_ERR_WORKSPACE;
   if (!aligned(workspace, 256)) return FDL_ERR_ALIGN;
   return FDL_OK;
+}
+
+// out = f(X W^T + b): kind 1 the forward output, 2 the masked upstream gradient (out: the G buffer of the plan).  In padded
+// mode the operands' copies must have been staged (off_xtail, off_wpad, off_bpad).
+void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int64_t N, const void* X, const void* W,
+                  const float* b, const void* aux, void* out, char* ws, hipStream_t s) {
+  if (q.f1_skinny) {
+    launch_skinny_xwt(kind, M, K, N, X, W, b, aux, out, kind == 2 ? q.g.ldz : N, s);
+  } else if (q.pad) {
+    launch_fast_xwt_padded(kind, M, K, N, X, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<const float*>(ws + q.off_bpad),
+                           aux, out, s);
+  } else if (q.f1_fast) {
+    void* Wt = q.f1_wt ? ws + q.off_wt : nullptr;
+    if (q.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
+    launch_fast_xwt(kind, M, K, N, X, false, W, Wt, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s);
+  } else {
+    GemmDesc g = {X, W, M, N, K, K, K, true, true, q.f1_wb};
+    launch_generic_xwt(dt, kind, g, b, aux, out, s);
+  }
 }
 }  // namespace
 
@@ -588,16 +641,12 @@ extern "C" fdl_status fdl_linear_relu_forward(fdl_dtype dt, int64_t M, int64_t K
   clear_stale_error();
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* ws = static_cast<char*>(workspace);
-  if (q.f1_skinny) {
-    launch_skinny_xwt(1, M, K, N, X, W, b, nullptr, Y, s);
-  } else if (q.f1_fast) {
-    void* Wt = q.f1_wt ? ws + q.off_wt : nullptr;
-    if (q.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
-    launch_fast_xwt(1, M, K, N, X, false, W, Wt, b, nullptr, Y, false, ws + q.off_xtail, s);
-  } else {
-    GemmDesc g = {X, W, M, N, K, K, K, true, true, q.f1_wb};
-    launch_generic_xwt((int)dt, 1, g, b, nullptr, Y, s);
+  if (q.pad && !q.f1_skinny) {
+    StageJobs j = {};
+    stage_padded(&j, M, K, N, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
+    launch_stage(j, s);
   }
+  relu_product(q, 1, (int)dt, M, K, N, X, W, b, nullptr, Y, ws, s);
   return launch_status();
 }
 
@@ -615,7 +664,6 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
     return FDL_ERR_ALIGN;
   clear_stale_error();
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  const ReluPlan& p = q;
   if (M == 0) {
     const int64_t nk = N * K;
     if (dt == FDL_F32) hipLaunchKernelGGL(zero_f32_kernel, dim3(256), dim3(256), 0, s, (float*)dW, nk);
@@ -624,40 +672,33 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
     return launch_status();
   }
   char* ws = static_cast<char*>(workspace);
-  void* G = ws + q.off_g;
+  void* G = ws + q.g.off_dz;
   void* colpart = ws + q.off_colpart;
-  // G = dY where X W^T + b > 0: the pre-activation is recomputed and never stored
-  if (p.f1_fast) {
-    void* Wt = p.f1_wt ? ws + q.off_wt : nullptr;
-    if (p.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
-    launch_fast_xwt(2, M, K, N, X, false, W, Wt, b, dY, G, p.g_blocked != 0, ws + q.off_xtail, s);
-  } else {
-    GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
-    launch_generic_xwt((int)dt, 2, g, b, dY, G, s);
-  }
-  launch_colsum((int)dt, M, N, G, p.g_blocked != 0, colpart, db, s);
-  if (p.b3_fast) {
-    launch_fast_b3(M, K, N, G, p.g_blocked != 0, W, dX, s);
-  } else {
-    GemmDesc g = {G, W, M, K, N, N, K, true, false, p.b3_wb};
-    launch_generic_store((int)dt, g, dX, s);
-  }
-  if (p.b4_fast) {
-    const int64_t Mf = p.b4_fast_rows;
-    const int extra = Mf < M ? 1 : 0;
-    float* dwpart = reinterpret_cast<float*>(ws + q.off_dwpart);
-    launch_fast_b4(Mf, K, N, p.b4_split, extra, G, p.g_blocked != 0, X, dW, dwpart, s);
-    if (extra) {
-      const char* Gt = static_cast<const char*>(G) + (size_t)Mf * N * 2;
-      const char* Xt = static_cast<const char*>(X) + (size_t)Mf * K * 2;
-      GemmDesc g = {Gt, Xt, N, K, M - Mf, N, K, false, false, p.b4_wb};
-      launch_generic_store_f32(g, dwpart + (size_t)p.b4_split * N * K, s);
+  if (q.pad) {
+    // the copies serve the recomputation and both gradient contractions; X goes with the recomputation's where that is tiled
+    StageJobs j = {};
+    if (q.f1_skinny) {
+      stage_padded(&j, M, K, N, q.g.stage_x ? X : nullptr, W, nullptr, ws + q.g.off_xpad, ws + q.g.off_wpad, nullptr);
+      // (that kernel writes columns up to N only: the surplus of G is cleared first, with the rows behind its last)
+      stage_matrix(&j, nullptr, 0, 0, 0, G, q.g.b4_fast_rows > M ? q.g.b4_fast_rows : M, q.g.ldz);
+    } else {
+      stage_padded(&j, M, K, N, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
+      if (q.g.b4_fast_rows > M)
+        stage_matrix(&j, nullptr, 0, 0, 0, static_cast<char*>(G) + (size_t)M * q.g.ldz * 2, q.g.b4_fast_rows - M, q.g.ldz);
     }
-    if (p.b4_split + extra > 1) launch_fast_b4_reduce(K, N, p.b4_split + extra, dwpart, dW, s);
-  } else {
-    GemmDesc g = {G, X, N, K, M, N, K, false, false, p.b4_wb};
-    launch_generic_store((int)dt, g, dW, s);
+    launch_stage(j, s);
   }
+  // G = dY where X W^T + b > 0: the pre-activation is recomputed and never stored
+  relu_product(q, 2, (int)dt, M, K, N, X, W, b, dY, G, ws, s);
+  launch_colsum_partial((int)dt, M, N, q.g.ldz, G, q.g.blocked != 0, colpart, s);
+  // the column sums end with the contractions' split sums where those leave any, else here
+  const bool tail = grad_leaves_sums(q.g);
+  TailSums tj = {};
+  tj.colpart = static_cast<const float*>(colpart); tj.groups = colsum_groups(M); tj.N = N; tj.kinds = 1; tj.col_out[0] = db;
+  if (!tail) launch_colsum_finish((int)dt, M, N, colpart, db, s);
+  launch_grad_dx(q.g, G, W, X, dX, dW, ws, &tj, s);
+  launch_grad_dw(q.g, G, X, dW, ws, &tj, s);
+  if (tail) launch_finish(tj, s);
   return launch_status();
 }
 
@@ -702,11 +743,13 @@ namespace {
 struct FfnPlan {
   int gate_skinny, down_skinny;   // few rows: the kernel made for them
   int gate_fused;          // 1: one kernel forms both products and the gated activation (no M x H round trip)
+  int gate_pad, down_pad;  // the same kernels on zero-padded copies of the weights (widths off their tiles)
   int up_fast, down_fast, up_wb, down_wb;
+  int64_t ldg;             // pitch of G
   int down_wt;             // the down projection reads its weights from a transposed copy
   int gate_wt;             // the fused gate/up kernel reads both weight matrices from one interleaved transposed copy
   int g_blocked;           // the gated activation passes from the fused kernel to the down projection in 32 x 32 blocks
-  size_t off_g, off_u, off_xtail, off_wt, off_wcat, bytes;
+  size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, bytes;
 };
 bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   if (dt != kF32 && dt != kBF16) return false;
@@ -717,16 +760,28 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   auto pick_wb = [dt](int64_t I, int64_t J) { return pick_generic_wb(dt, I, J); };
   q->gate_skinny = dt == kBF16 && skinny_supported(Mp, D, 2 * H);
   q->down_skinny = dt == kBF16 && skinny_supported(Mp, H, D);
+  // off the tiles: padded copies, where the padding is not most of the work nor the launches most of the time
+  const int64_t Hp = fast_gate_pad_h(H), Dq = fast_gate_pad_d(D), Dp = fast_pad_dim(D);
+  const bool can_pad = dt == kBF16 && M >= 128 && M * D * H >= kStageFromWork && Hp * Dp <= 6 * H * D && (Hp / 128) * ((M + 255) / 256) <= (1 << 30);
   q->gate_fused = dt == kBF16 && !q->gate_skinny && fast_gate_supported(M, D, H);
-  q->up_fast = dt == kBF16 && !q->gate_skinny && fast_f1_supported(M, D, H);      // [M,D] x [H,D]^T
-  q->down_fast = dt == kBF16 && !q->down_skinny && fast_f1_supported(M, H, D);    // [M,H] x [D,H]^T
+  q->gate_pad = !q->gate_skinny && !q->gate_fused && can_pad;
+  q->ldg = q->gate_pad ? Hp : H;
+  // [M,D] x [H,D]^T for the separate gate and up products, [M,H] x [D,H]^T
+  q->up_fast = dt == kBF16 && !q->gate_skinny && !q->gate_pad && fast_f1_supported(M, D, H);
+  q->down_fast = dt == kBF16 && !q->gate_pad && !q->down_skinny && fast_f1_supported(M, H, D);
+  q->down_pad = !q->down_fast && can_pad && (q->gate_pad || (!q->down_skinny && H % 128 == 0));
+  if (q->down_pad) q->down_skinny = 0;
   q->up_wb = pick_wb(Mp, H);
   q->down_wb = pick_wb(Mp, D);
   size_t off = 0;
-  const size_t mh = align256((size_t)((Mp + 255) / 256 * 256) * H * ts);
+  const size_t mh = align256((size_t)((Mp + 255) / 256 * 256) * q->ldg * ts);
   q->off_g = off; off += mh;
-  q->off_u = off; off += q->gate_fused || q->gate_skinny ? 0 : mh;    // the fused kernels never materialise the up product
-  q->off_xtail = off; off += align256((q->up_fast || q->gate_fused) ? fast_f1_tail_bytes(M, D) : 0);
+  q->off_u = off; off += q->gate_fused || q->gate_skinny || q->gate_pad ? 0 : mh;    // the fused kernels never materialise the up product
+  const size_t xpad = fast_padded_stages_x(D) ? (size_t)fast_padded_rows(Mp) * Dq * 2 : fast_padded_tail_bytes(D);
+  q->off_xtail = off; off += align256(q->gate_pad ? xpad : ((q->up_fast || q->gate_fused) ? fast_f1_tail_bytes(M, D) : 0));
+  q->off_wgp = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
+  q->off_wup = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
+  q->off_wdp = off; off += align256(q->down_pad ? (size_t)Dp * Hp * 2 : 0);
   q->down_wt = q->down_fast && M >= kTransposeFromRows;
   q->off_wt = off; off += align256(q->down_wt ? (size_t)D * H * 2 : 0);
   q->gate_wt = q->gate_fused && M >= kTransposeFromRows && H % 64 == 0 && D % 64 == 0;
@@ -759,8 +814,21 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
   char* ws = static_cast<char*>(workspace);
   void* G = ws + q.off_g;
   void* U = ws + q.off_u;
+  if (q.gate_pad || q.down_pad) {
+    const int64_t Hp = fast_gate_pad_h(H), Dq = fast_gate_pad_d(D);
+    StageJobs j = {};
+    if (q.gate_pad) {
+      stage_gate_x(&j, X, M, D, ws + q.off_xtail);
+      stage_matrix(&j, Wg, H, D, D, ws + q.off_wgp, Hp, Dq);
+      stage_matrix(&j, Wu, H, D, D, ws + q.off_wup, Hp, Dq);
+    }
+    if (q.down_pad) stage_matrix(&j, Wd, D, H, H, ws + q.off_wdp, fast_pad_dim(D), Hp);
+    launch_stage(j, s);
+  }
   if (q.gate_skinny) {
     launch_skinny_gate(M, D, H, X, Wg, Wu, G, s);
+  } else if (q.gate_pad) {
+    launch_fast_gate_padded(M, D, H, X, ws + q.off_xtail, ws + q.off_wgp, ws + q.off_wup, G, s);
   } else if (q.gate_fused) {
     void* Wcat = q.gate_wt ? ws + q.off_wcat : nullptr;
     if (q.gate_wt) launch_fast_transpose_gate(H, D, Wg, Wu, Wcat, s);
@@ -774,9 +842,11 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     g.B = Wu;
     launch_generic_xwt((int)dt, 0, g, nullptr, nullptr, U, s);
   }
-  if (!q.gate_fused && !q.gate_skinny) launch_silu_mul((int)dt, M * H, G, U, G, s);
-  if (q.down_skinny) {
-    launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, s);
+  if (!q.gate_fused && !q.gate_skinny && !q.gate_pad) launch_silu_mul((int)dt, M * H, G, U, G, s);
+  if (q.down_pad) {
+    launch_fast_down_padded(M, D, q.ldg, G, ws + q.off_wdp, Y, s);
+  } else if (q.down_skinny) {
+    launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, s);
   } else if (q.down_fast) {
     void* Wt = q.down_wt ? ws + q.off_wt : nullptr;
     if (q.down_wt) launch_fast_transpose(D, H, Wd, Wt, s);

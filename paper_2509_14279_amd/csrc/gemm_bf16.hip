@@ -73,10 +73,12 @@ struct FastParams {
   const bf16_t* Qtail;   // RAG: the Q rows of the last (partial) row tile as a padded 256-row copy, or null if Q
                          //      itself has readable rows up to the end of that tile
   int64_t ldp, ldq;
-  bf16_t* C;             // [J][I]
-  float* Cpart;          // [split][J][I] fp32 (split > 1)
+  bf16_t* C;             // [J][ldc]
+  float* Cpart;          // [split][J][I] fp32, pstride elements from part to part (EPI_PARTIAL)
   const float* bias;     // [I]   (EPI_BIAS, EPI_RELU, EPI_MASK)
   const bf16_t* aux;     // [J][I] (EPI_MASK)
+  int64_t ldc;           // row pitch of C (at least I)
+  int64_t pstride;
   int I, J;              // J: valid output rows (RAG: any number >= 1; otherwise a multiple of 256)
   int tiles_i, tiles_j;
   int nkt;               // reduction slices per workgroup
@@ -240,10 +242,11 @@ __device__ __forceinline__ TileCoord tile_coord(int L, int tiles_i, int tiles_j)
 // RAG: the number of output rows J is not a multiple of the tile (ragged batch dimension of F1 and B3, ragged N of
 // B4).  The last row tile then reads its Q rows from a padded copy (or from a Q buffer that is itself padded), computes
 // the surplus rows on whatever that padding holds - rows of a product are independent - and does not store them.
-// CRAG (with RAG): the number of output columns I is a multiple of 8 but not of the tile.  The host hands over a P
-// operand that is readable up to the end of the last column tile (a zero-padded copy of the weights, or a matrix
-// whose surplus columns are the start of its next row) and a bias padded likewise; the surplus columns are computed
-// and not stored.
+// CRAG (with RAG): the number of output columns I is any number, and so is the pitch of the output's rows (stores go to
+// element-aligned addresses).  The host hands over a P operand that is readable up to the end of the last column tile (a
+// zero-padded copy of the weights, or a matrix whose surplus columns are the start of its next row) and a bias padded
+// likewise; the surplus columns are computed and not stored - EPI_MASK excepted, whose output, a buffer of the library
+// with whole tiles of columns, gets zeros there.
 // A reduction length that is not a whole number of pipeline rounds is the host's business as well: it rounds the
 // length up and makes one operand zero over the surplus (the other only has to be readable and finite there).
 // The body of the kernel: the persistent tile loop of workgroup `bid` of `nblk` on reduction part `part`.  It is a
@@ -534,15 +537,16 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     uint32_t roff[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) roff[c] = (uint32_t)((c * 4 + e_rq) * 256 + ((e_m ^ (c * 4 + e_rq)) << 4));
-    const uint32_t svoff = (uint32_t)(e_rq * p.I + e_m * 8) * 2u;   // byte offset of the lane inside 4 output rows
+    const uint32_t svoff = (uint32_t)(e_rq * (int)p.ldc + e_m * 8) * 2u;   // byte offset of the lane inside 4 output rows
+    typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
     // Block row b of the wave tile (32 output rows) leaves as soon as it is complete.
     auto flush_rows = [&](int b) {
       // wave-uniform base of row it*4 of the block row; the lane adds (lane/16) rows and 16 (lane%16) bytes
-      char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 32) * p.I + i0 + wi * 128);
+      char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 32) * p.ldc + i0 + wi * 128);
 #pragma unroll
       for (int it = 0; it < 8; it++) {
         const u32x4 v = *(const lds_u32x4*)(wtile + roff[it & 3] + (it >> 2) * 4096);
-        u32x4* dst = reinterpret_cast<u32x4*>(cbase + (int64_t)(it * 4) * p.I * 2 + svoff);
+        u32x4* dst = reinterpret_cast<u32x4*>(cbase + (int64_t)(it * 4) * p.ldc * 2 + svoff);
         if (EPI == EPI_MASK && p.cblocked) {
           // row R0 + lane/16 (R0 a multiple of 4, so the four rows share a block row), columns col .. col + 7:
           // four rows x 64 bytes of each of the four blocks = 256 contiguous bytes per block
@@ -551,12 +555,32 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
           dst = reinterpret_cast<u32x4*>(p.C + (((R0 >> 5) * (p.I >> 5) + (col >> 5)) << 10) + (((R0 & 31) + e_rq) << 5) + (col & 31));
         }
         if (RAG && j0 + wj * 128 + b * 32 + it * 4 + e_rq >= p.J) continue;   // a row past the end
-        if (CRAG && i0 + wi * 128 + e_m * 8 >= p.I) continue;                  // 8 columns past the end
+        const int cleft = CRAG ? p.I - (i0 + wi * 128 + e_m * 8) : 8;          // columns from this lane's first to the end
+        if (CRAG && EPI != EPI_MASK) {
+          if (cleft >= 8) {
+            if (kBias) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_u*>(dst));
+            else *reinterpret_cast<u32x4_u*>(dst) = v;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+              if (e < cleft) reinterpret_cast<unsigned short*>(dst)[e] = (unsigned short)(v[e >> 1] >> ((e & 1) * 16));
+          }
+          continue;
+        }
         if (EPI == EPI_MASK) {
           // v: 8 pre-activations as bf16.  The upstream gradient passes where the pre-activation is positive (bits
           // 0x0001 .. 0x7fff: sign clear, magnitude non-zero) and is zero elsewhere.
-          const char* abase = reinterpret_cast<const char*>(p.aux + (int64_t)(j0 + wj * 128 + b * 32) * p.I + i0 + wi * 128);
-          const u32x4 d = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(abase + (int64_t)(it * 4) * p.I * 2 + svoff));
+          const bf16_t* ap = p.aux + (int64_t)(j0 + wj * 128 + b * 32 + it * 4 + e_rq) * p.I + i0 + wi * 128 + e_m * 8;
+          u32x4 d = {0u, 0u, 0u, 0u};
+          if (!CRAG) {
+            d = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ap));
+          } else if (cleft >= 8) {
+            d = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(ap));
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+              if (e < cleft) d[e >> 1] |= (uint32_t)reinterpret_cast<const unsigned short*>(ap)[e] << ((e & 1) * 16);
+          }
           u32x4 g;
 #pragma unroll
           for (int e = 0; e < 4; e++) {
@@ -593,7 +617,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
             }
             *(lds_bf16x4*)(wtile + woff[a][g]) = v;
           }
-        char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 32) * p.I + h0);
+        char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 32) * p.ldc + h0);
 #pragma unroll
         for (int it = 0; it < 4; it++) {
           const int row = it * 8 + g_rq;
@@ -606,13 +630,14 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
             *reinterpret_cast<u32x4*>(p.C + (((R >> 5) * (p.I >> 5) + (col >> 5)) << 10) + ((R & 31) << 5) + (col & 31)) = v;
             continue;
           }
-          *reinterpret_cast<u32x4*>(cbase + ((int64_t)row * p.I + g_m * 8) * 2) = v;
+          *reinterpret_cast<u32x4*>(cbase + ((int64_t)row * p.ldc + g_m * 8) * 2) = v;
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     } else if (EPI == EPI_PARTIAL) {
       // fp32 partial sums of this reduction part, straight from the registers (wave-uniform base + lane offset)
-      float* out = p.Cpart + (int64_t)part * p.J * p.I;
+      float* out = p.Cpart + (int64_t)part * p.pstride;
+      typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
       const uint32_t pvoff = (uint32_t)(e_l32 * p.I + e_half * 4) * 4u;
 #pragma unroll
       for (int b = 0; b < 4; b++) {
@@ -625,8 +650,17 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
 #pragma unroll
             for (int e = 0; e < 4; e++) v[e] = acc[a][b][g * 4 + e];
             if (RAG && j0 + wj * 128 + b * 32 + e_l32 >= p.J) continue;                          // a row past the end
-            if (CRAG && i0 + wi * 128 + a * 32 + g * 8 + e_half * 4 >= p.I) continue;            // 4 columns past the end
-            *reinterpret_cast<f32x4*>(obase + (a * 32 + g * 8) * 4 + pvoff) = v;
+            float* dst = reinterpret_cast<float*>(obase + (a * 32 + g * 8) * 4 + pvoff);
+            const int cleft = CRAG ? p.I - (i0 + wi * 128 + a * 32 + g * 8 + e_half * 4) : 4;    // columns to the end
+            if (CRAG && cleft < 4) {
+#pragma unroll
+              for (int e = 0; e < 4; e++)
+                if (e < cleft) dst[e] = v[e];
+            } else if (CRAG) {
+              *reinterpret_cast<f32x4_u*>(dst) = v;
+            } else {
+              *reinterpret_cast<f32x4*>(dst) = v;
+            }
           }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -667,32 +701,17 @@ void gemm_bf16_kernel(FastParams p) {
 // product on the rest (nb workgroups per part of its reduction); a split reduction writes fp32 partial sums.  For
 // outputs so small that neither contraction has a tile for every compute unit - a dX with few column tiles, a small
 // dW - the two together still fill the chip, where two launches in a row would each leave part of it idle.
-template <int BK, int NS, int EPIA, int EPIB>
+template <int BK, int NS, int EPIA, int EPIB, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_bf16_pair_kernel(FastParams pa, FastParams pb, int na, int nb) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int id = (int)blockIdx.x, a_all = na * pa.split;
   if (id < a_all) {
-    gemm_tile_loop<true, false, EPIA, BK, NS, false>(pa, smem, id % na, na, id / na);
+    gemm_tile_loop<true, false, EPIA, BK, NS, RAG, RAG>(pa, smem, id % na, na, id / na);
   } else {
     const int t = id - a_all;
-    gemm_tile_loop<true, true, EPIB, BK, NS, false>(pb, smem, t % nb, nb, t / nb);
+    gemm_tile_loop<true, true, EPIB, BK, NS, RAG, RAG>(pb, smem, t % nb, nb, t / nb);
   }
-}
-
-// Sum split-reduction partials [split][n] fp32 -> bf16.
-__global__ __launch_bounds__(256) void reduce_split_kernel(const float* __restrict__ part, int split, int64_t n,
-                                                           bf16_t* __restrict__ out) {
-  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i >= n) return;
-  f32x4 s = *reinterpret_cast<const f32x4*>(part + i);
-  for (int k = 1; k < split; k++) {
-    const f32x4 t = *reinterpret_cast<const f32x4*>(part + (int64_t)k * n + i);
-    s[0] += t[0]; s[1] += t[1]; s[2] += t[2]; s[3] += t[3];
-  }
-  bf16x4 o;
-  o[0] = (bf16_t)s[0]; o[1] = (bf16_t)s[1]; o[2] = (bf16_t)s[2]; o[3] = (bf16_t)s[3];
-  *reinterpret_cast<bf16x4*>(out + i) = o;
 }
 
 // dst [cols][rows] = src [rows][cols]^T in 64 x 64 tiles through LDS (rows, cols multiples of 64): both sides move
@@ -724,35 +743,42 @@ __global__ __launch_bounds__(256) void transpose64_kernel(const bf16_t* __restri
   *reinterpret_cast<u32x4*>(dp + 8) = o1;
 }
 
-// Padded copy of the rows [row0, rows) of a row-major matrix: rows_out rows of the same pitch, zeros past the end.
-// (256 rows for a ragged row count; one more where the kernel also reads past the end of every row - a reduction
-// length rounded up - so that the last row's surplus stays inside the copy.)
-__global__ __launch_bounds__(256) void copy_tail_rows_kernel(const bf16_t* __restrict__ src, int64_t rows, int64_t ld,
-                                                             int64_t row0, bf16_t* __restrict__ dst, int rows_out) {
-  const int64_t n8 = (int64_t)rows_out * ld / 8;   // ld is a multiple of 8 on this path
-  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n8; v += (int64_t)gridDim.x * 256) {
-    const int64_t r = (v * 8) / ld;
-    u32x4 x = {0u, 0u, 0u, 0u};
-    if (row0 + r < rows) x = *reinterpret_cast<const u32x4*>(src + row0 * ld + v * 8);
-    *reinterpret_cast<u32x4*>(dst + v * 8) = x;
+// Zero-padded copies, several in one launch (they are small dependent launches otherwise, a few microseconds each):
+// job k: dst [rows_out][cols_out] = src [rows][cols] with zeros around it (src null: all zeros), cols_out a multiple of 8,
+// src rows `ld` elements apart at any element; then the fp32 vector vdst [vn_out] = vsrc [vn] and zeros.
+__global__ __launch_bounds__(256) void stage_kernel(StageJobs j) {
+  typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
+  int id = (int)blockIdx.x;
+  for (int k = 0; k < j.count; k++) {
+    const StageJob& q = j.job[k];
+    if (id >= q.blocks) { id -= q.blocks; continue; }
+    const int64_t vpr = q.cols_out / 8;                      // vectors per row
+    const int per = vpr < 256 ? (int)(256 / vpr) : 1;        // rows a workgroup copies at a time
+    const int tr = vpr < 256 ? (int)threadIdx.x / (int)vpr : 0;
+    const int64_t tc = vpr < 256 ? (int)threadIdx.x % (int)vpr : threadIdx.x;
+    if (tr >= per) return;
+    const unsigned short* src = static_cast<const unsigned short*>(q.src);
+    unsigned short* dst = static_cast<unsigned short*>(q.dst);
+    for (int64_t r = (int64_t)id * per + tr; r < q.rows_out; r += (int64_t)q.blocks * per)
+      for (int64_t v = tc; v < vpr; v += 256) {
+        const int64_t c = v * 8;
+        u32x4 x = {0u, 0u, 0u, 0u};
+        if (src != nullptr && r < q.rows) {
+          const unsigned short* s = src + r * q.ld + c;
+          if (c + 8 <= q.cols) {
+            x = *reinterpret_cast<const u32x4_u*>(s);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+              if (c + e < q.cols) x[e >> 1] |= (uint32_t)s[e] << ((e & 1) * 16);
+          }
+        }
+        *reinterpret_cast<u32x4*>(dst + r * q.cols_out + c) = x;
+      }
+    return;
   }
-}
-
-// Zero-padded copy of a row-major matrix: dst [rows_out][cols_out] = src [rows][cols] (cols, cols_out multiples of 8).
-__global__ __launch_bounds__(256) void pad_matrix_kernel(const bf16_t* __restrict__ src, int64_t rows, int64_t cols,
-                                                         bf16_t* __restrict__ dst, int64_t rows_out, int64_t cols_out) {
-  const int64_t vpr = cols_out / 8, n8 = rows_out * vpr;
-  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n8; v += (int64_t)gridDim.x * 256) {
-    const int64_t r = v / vpr, c = (v - r * vpr) * 8;
-    u32x4 x = {0u, 0u, 0u, 0u};
-    if (r < rows && c < cols) x = *reinterpret_cast<const u32x4*>(src + r * cols + c);
-    *reinterpret_cast<u32x4*>(dst + r * cols_out + c) = x;
-  }
-}
-__global__ __launch_bounds__(256) void pad_vector_kernel(const float* __restrict__ src, int64_t n, float* __restrict__ dst,
-                                                         int64_t n_out) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_out; i += (int64_t)gridDim.x * 256)
-    dst[i] = i < n ? src[i] : 0.0f;
+  const int64_t i = (int64_t)id * 256 + threadIdx.x;
+  if (i < j.vn_out) j.vdst[i] = i < j.vn ? j.vsrc[i] : 0.0f;
 }
 
 template <bool P_RM, bool Q_RM, int EPI, int BK, int NS, bool RAG = false, bool CRAG = false>
@@ -764,6 +790,8 @@ void launch(FastParams p, hipStream_t s) {
   if (!device_info(&di)) return;
   // persistent: at most one workgroup per CU (the LDS footprint allows no more); a multiple of the die count
   // whenever the tile count is, so that every die gets the same number
+  if (p.ldc == 0) p.ldc = p.I;
+  if (p.pstride == 0) p.pstride = (int64_t)p.I * p.J;
   const int ntiles = p.tiles_i * p.tiles_j;
   int wgs = di.cus / p.split;
   if (wgs < di.xcds) wgs = di.xcds;
@@ -810,40 +838,71 @@ bool fast_b4_supported(int64_t M, int64_t K, int64_t N) {
 }
 size_t fast_f1_tail_bytes(int64_t M, int64_t K) { return M % kTile ? (size_t)kTile * K * 2 : 0; }
 
-// ---- padded mode: N and K multiples of 8 (16-byte rows) but not both multiples of the tile ----------------------
+// ---- padded mode: N and K not both multiples of the tile ---------------------------------------------------------
 // The contractions then run on the same kernels with N and K rounded up to the tile: the weights are copied into a
-// zero-padded [Np][Kp] matrix (small: it is the only operand that is copied whole), the bias into a padded vector,
+// zero-padded [Np][Kp] matrix (small: it is the only operand that is always copied whole), the bias into a padded vector,
 // dZ is laid out with pitch Np and zero surplus columns, and the kernels leave the surplus output columns and rows
-// unstored.  Where X is read past the end of its rows (K rounded up: forward) the surplus is the start of X's next
-// row times the weights' zero padding; only X's last row has no next row, so the forward pass takes its last row tile
-// from a copy with one spare row.
+// unstored.  X enters in one of two ways:
+//   K a multiple of 8 (16-byte rows) and at least 128: as it is.  Where it is read past the end of its rows the surplus is
+//     the start of X's next row times the weights' zero padding; only X's last row has no next row, so the forward pass
+//     takes its last row tile from a copy with one spare row, and the dW product leaves the last rows to the generic kernel.
+//   any other K: through a copy with pitch Kp, zeros around it and whole row tiles (M K elements read and written once,
+//     against three contractions at six to eight times the generic kernel's rate); the rows behind dZ's last are cleared up
+//     to a pipeline round, so that dW needs no remainder.
 int64_t fast_pad_dim(int64_t n) { return (n + kTile - 1) / kTile * kTile; }
 bool fast_padded_supported(int64_t M, int64_t K, int64_t N) {
-  // K >= 128: a row read up to the rounded-up K then ends inside the next row (Kp <= 2 K), which is what keeps those
-  // reads inside X (every row the kernels read that way has a successor) and inside the copy of X's last rows
-  if (M < kMinRaggedRows || N < 8 || K < 128 || N % 8 || K % 8) return false;
+  // K >= 128 for the first way: a row read up to the rounded-up K then ends inside the next row (Kp <= 2 K)
+  if (M < kMinRaggedRows || N < 8) return false;
   if (N % kTile == 0 && K % kTile == 0) return false;     // nothing to pad: the plain fast path applies
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K), tj = (M + kTile - 1) / kTile;
-  return Np <= (1 << 24) && Kp <= (1 << 24) && M <= (1 << 24) && (Np / kTile) * tj <= (1 << 30) && (Kp / kTile) * tj <= (1 << 30) &&
-         (Np / kTile) * (Kp / kTile) <= (1 << 30);
+  if (Np > (1 << 24) || Kp > (1 << 24) || M > (1 << 24) || (Np / kTile) * tj > (1 << 30) || (Kp / kTile) * tj > (1 << 30) ||
+      (Np / kTile) * (Kp / kTile) > (1 << 30))
+    return false;
+  if (N % 8 == 0 && K % 8 == 0 && K >= 128) return true;
+  // odd rows: not where the padding is most of the work, nor where the copies' launches are
+  return Np * Kp <= 6 * N * K && M * N * K >= kStageFromWork;
 }
+bool fast_padded_stages_x(int64_t K) { return K % 8 != 0 || K < 128; }
 size_t fast_padded_tail_bytes(int64_t K) { return (size_t)(kTile + 1) * K * 2; }
-// rows of the dW reduction the fast kernel covers in padded mode: where X is read past the end of its rows (K rounded
-// up) the last row it touches must have a successor
+int64_t fast_padded_rows(int64_t M) { return (M + kTile - 1) / kTile * kTile; }
+// rows of the dW reduction the fast kernel covers in padded mode (X as it is: where it is read past the end of its rows
+// the last row it touches must have a successor)
 int64_t fast_padded_b4_rows(int64_t M, int64_t K) {
   const int64_t u = (int64_t)kB4BK * stages_of(kB4BK);
+  if (fast_padded_stages_x(K)) return (M + u - 1) / u * u;
   return (K % kTile ? M - 1 : M) / u * u;
 }
 
-// Wp [Np][Kp] and biasp [Np] (biasp and bias may be null) from W [N][K] and bias [N]
-void launch_fast_pad_weights(int64_t K, int64_t N, const void* W, const float* bias, void* Wp, float* biasp, hipStream_t s) {
+void stage_matrix(StageJobs* j, const void* src, int64_t rows, int64_t cols, int64_t ld, void* dst, int64_t rows_out, int64_t cols_out) {
+  if (rows_out <= 0) return;
+  StageJob& q = j->job[j->count++];
+  q.src = src; q.dst = dst; q.rows = rows; q.cols = cols; q.ld = ld; q.rows_out = rows_out; q.cols_out = cols_out;
+  const int64_t wanted = (rows_out * (cols_out / 8) + 1023) / 1024;      // four vectors per thread
+  q.blocks = (int)(wanted < 1 ? 1 : (wanted > 2048 ? 2048 : wanted));
+}
+void stage_vector(StageJobs* j, const float* src, int64_t n, float* dst, int64_t n_out) {
+  j->vsrc = src; j->vdst = dst; j->vn = n; j->vn_out = n_out;
+}
+void launch_stage(const StageJobs& j, hipStream_t s) {
+  int64_t blocks = (j.vn_out + 255) / 256;
+  for (int k = 0; k < j.count; k++) blocks += j.job[k].blocks;
+  if (blocks > 0) hipLaunchKernelGGL(stage_kernel, dim3((unsigned)blocks), dim3(256), 0, s, j);
+}
+// the last row tile of X with one spare row, from rows that are read past their end
+static void stage_x_tail(StageJobs* j, const void* X, int64_t M, int64_t K, void* xtail, int64_t spare) {
+  const int64_t row0 = (M + kTile - 1) / kTile * kTile - kTile;
+  stage_matrix(j, static_cast<const bf16_t*>(X) + row0 * K, M - row0, K, K, xtail, kTile + spare, K);
+}
+// W [N][K] -> Wp [Np][Kp], bias (may be null) -> biasp [Np], and X: its last row tile -> xw (K as it is) or all of it
+void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias, void* xw,
+                  void* Wp, float* biasp) {
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
-  const int64_t n8 = Np * Kp / 8;
-  int64_t blocks = (n8 + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(pad_matrix_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t*)W, N, K, (bf16_t*)Wp, Np, Kp);
-  if (biasp != nullptr)
-    hipLaunchKernelGGL(pad_vector_kernel, dim3((unsigned)((Np + 255) / 256)), dim3(256), 0, s, bias, N, biasp, Np);
+  if (X != nullptr) {
+    if (fast_padded_stages_x(K)) stage_matrix(j, X, M, K, K, xw, fast_padded_rows(M), Kp);
+    else stage_x_tail(j, X, M, K, xw, 1);
+  }
+  stage_matrix(j, W, N, K, K, Wp, Np, Kp);
+  if (biasp != nullptr) stage_vector(j, bias, N, biasp, Np);
 }
 
 // Wt [K][N] = W^T (N, K multiples of 64).
@@ -861,20 +920,24 @@ void launch_fast_transpose_gate(int64_t H, int64_t D, const void* Wg, const void
   hipLaunchKernelGGL(transpose64_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wu, H, D, (bf16_t*)Wcat, 2 * H, 128, 64);
 }
 
-// Padded mode: Wp [Np][Kp], biasp [Np] from launch_fast_pad_weights; xtail: fast_padded_tail_bytes(K) bytes
-void launch_fast_f1_padded(int64_t M, int64_t K, int64_t N, const void* X, const void* Wp, const float* biasp, void* Zsave,
-                           void* xtail, hipStream_t s) {
+// Padded mode: the operands of stage_padded.  kind as launch_fast_xwt; kind 2 writes out [..][Np], the others [M][N].
+void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* xw, const void* Wp,
+                            const float* biasp, const void* aux, void* out, hipStream_t s) {
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
+  const bool staged = fast_padded_stages_x(K);
   FastParams p = {};
-  p.P = (const bf16_t*)Wp; p.Q = (const bf16_t*)X; p.ldp = Kp; p.ldq = K;
-  p.C = (bf16_t*)Zsave; p.bias = biasp;
+  p.P = (const bf16_t*)Wp; p.ldp = Kp;
+  p.Q = (const bf16_t*)(staged ? xw : X); p.ldq = staged ? Kp : K;
+  // X as it is: the last row tile always comes from the copy (its rows are read past their end)
+  p.Qtail = staged ? nullptr : (const bf16_t*)xw;
+  p.C = (bf16_t*)out; p.bias = biasp; p.aux = (const bf16_t*)aux; p.ldc = kind == 2 ? Np : N;
   p.I = (int)N; p.J = (int)M; p.tiles_i = (int)(Np / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
-  p.nkt = (int)(Kp / kF1BK); p.split = 1;
-  // the last row tile always comes from the copy: its rows are read up to Kp columns, and X's last row has no successor
-  p.Qtail = (const bf16_t*)xtail;
-  hipLaunchKernelGGL(copy_tail_rows_kernel, dim3(64), dim3(256), 0, s, (const bf16_t*)X, M, K,
-                     (int64_t)(p.tiles_j - 1) * kTile, (bf16_t*)xtail, kTile + 1);
-  launch<false, false, EPI_BIAS, kF1BK, stages_of(kF1BK), true, true>(p, s);
+  constexpr int NS = stages_of(kF1BK), round = NS * kF1BK;
+  p.nkt = (int)((K + round - 1) / round * NS); p.split = 1;
+  if (kind == 1) launch<false, false, EPI_RELU, kF1BK, NS, true, true>(p, s);
+  else if (kind == 2) launch<false, false, EPI_MASK, kF1BK, NS, true, true>(p, s);
+  else if (biasp != nullptr) launch<false, false, EPI_BIAS, kF1BK, NS, true, true>(p, s);
+  else launch<false, false, EPI_STORE, kF1BK, NS, true, true>(p, s);
 }
 
 // out[m][n] = f(sum_k X[m][k] W[n][k] + bias[n]): the forward product (fast_f1_supported shapes).
@@ -901,8 +964,9 @@ void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, b
   const bool rag = M % kTile != 0;
   if (rag && !x_padded) {
     p.Qtail = (const bf16_t*)xtail;
-    hipLaunchKernelGGL(copy_tail_rows_kernel, dim3(64), dim3(256), 0, s, (const bf16_t*)X, M, K,
-                       (int64_t)(p.tiles_j - 1) * kTile, (bf16_t*)xtail, kTile);
+    StageJobs j = {};
+    stage_x_tail(&j, X, M, K, xtail, 0);
+    launch_stage(j, s);
   }
   if (Wt != nullptr) {   // the weights as the r-major operand
     p.P = (const bf16_t*)Wt; p.ldp = N; p.nkt = (int)(K / kB3BK);
@@ -950,8 +1014,9 @@ void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void
   const bool rag = M % kTile != 0;
   if (rag) {
     p.Qtail = (const bf16_t*)xtail;
-    hipLaunchKernelGGL(copy_tail_rows_kernel, dim3(64), dim3(256), 0, s, (const bf16_t*)X, M, D,
-                       (int64_t)(p.tiles_j - 1) * kTile, (bf16_t*)xtail, kTile);
+    StageJobs j = {};
+    stage_x_tail(&j, X, M, D, xtail, 0);
+    launch_stage(j, s);
   }
   if (Wcat != nullptr) {   // Wcat from launch_fast_transpose_gate: the weights as one r-major operand (see launch_fast_xwt)
     p.P = (const bf16_t*)Wcat; p.P2 = nullptr; p.ldp = 2 * H; p.nkt = (int)(D / kB3BK);
@@ -963,6 +1028,37 @@ void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void
   constexpr int NS = stages_of(kF1BK);
   if (rag) launch<false, false, EPI_GATE, kF1BK, NS, true>(p, s);
   else launch<false, false, EPI_GATE, kF1BK, NS, false>(p, s);
+}
+
+// Padded: Wgp, Wup [Hp][Dp] zero-padded copies (Hp a multiple of 128, Dp of the pipeline round); X as it is (xw: the copy of
+// its last row tile) or as a copy xw with pitch Dp (fast_padded_stages_x); Hout [..][Hp] with zero surplus columns.
+int64_t fast_gate_pad_h(int64_t H) { return (H + 127) / 128 * 128; }
+int64_t fast_gate_pad_d(int64_t D) { const int64_t u = (int64_t)stages_of(kF1BK) * kF1BK; return (D + u - 1) / u * u; }
+void launch_fast_gate_padded(int64_t M, int64_t D, int64_t H, const void* X, const void* xw, const void* Wgp, const void* Wup,
+                             void* Hout, hipStream_t s) {
+  const int64_t Hp = fast_gate_pad_h(H), Dp = fast_gate_pad_d(D);
+  const bool staged = fast_padded_stages_x(D);
+  FastParams p = {};
+  p.P = (const bf16_t*)Wgp; p.P2 = (const bf16_t*)Wup; p.ldp = Dp;
+  p.Q = (const bf16_t*)(staged ? xw : X); p.ldq = staged ? Dp : D;
+  p.Qtail = staged ? nullptr : (const bf16_t*)xw;
+  p.C = (bf16_t*)Hout;
+  p.I = (int)Hp; p.J = (int)M; p.tiles_i = (int)(Hp / 128); p.tiles_j = (int)((M + kTile - 1) / kTile);
+  p.nkt = (int)(Dp / kF1BK); p.split = 1;
+  launch<false, false, EPI_GATE, kF1BK, stages_of(kF1BK), true>(p, s);
+}
+// out [M][D] = G [..][Hp] Wdp^T with Wdp [D rounded up to the tile][Hp]; G has readable rows up to the next row tile
+void launch_fast_down_padded(int64_t M, int64_t D, int64_t Hp, const void* G, const void* Wdp, void* out, hipStream_t s) {
+  FastParams p = {};
+  p.P = (const bf16_t*)Wdp; p.Q = (const bf16_t*)G; p.ldp = Hp; p.ldq = Hp;
+  p.C = (bf16_t*)out;
+  p.I = (int)D; p.J = (int)M; p.tiles_i = (int)(fast_pad_dim(D) / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
+  p.nkt = (int)(Hp / kF1BK); p.split = 1;
+  launch<false, false, EPI_STORE, kF1BK, stages_of(kF1BK), true, true>(p, s);
+}
+void stage_gate_x(StageJobs* j, const void* X, int64_t M, int64_t D, void* xw) {
+  if (fast_padded_stages_x(D)) stage_matrix(j, X, M, D, D, xw, fast_padded_rows(M), fast_gate_pad_d(D));
+  else stage_x_tail(j, X, M, D, xw, 1);
 }
 
 void launch_fast_b3(int64_t M, int64_t K, int64_t N, const void* dZ, bool dz_blocked, const void* W, void* dX,
@@ -1014,8 +1110,7 @@ int fast_b4_split(int64_t M, int64_t K, int64_t N) {
 
 // dW from the first M rows (a whole number of pipeline rounds, see fast_b4_rows).  With split > 1 or extra > 0 the
 // kernel writes fp32 partial sums dwpart[0 .. split); the caller may add `extra` more partials behind them (the
-// rows the fast kernel does not cover) and then sums them (launch_fast_b4_reduce, or the backward pass's finishing
-// launch); otherwise dW is final on return.
+// rows the fast kernel does not cover) and then sums them (the backward pass's finishing launch); otherwise dW is final on return.
 void launch_fast_b4(int64_t M, int64_t K, int64_t N, int split, int extra, const void* dZ, bool dz_blocked, const void* X,
                     void* dW, void* dwpart, hipStream_t s) {
   FastParams p = {};
@@ -1028,46 +1123,40 @@ void launch_fast_b4(int64_t M, int64_t K, int64_t N, int split, int extra, const
   else launch<true, true, EPI_STORE, kB4BK, stages_of(kB4BK)>(p, s);
 }
 
-// Padded mode: dZ has pitch Np (zero surplus columns); X is read up to Kp columns per row, so M must be at most
-// fast_padded_b4_rows.  Always writes fp32 partial sums dwpart[0 .. split) (pitch K, surplus rows and columns unstored);
-// the caller adds what it must and calls launch_fast_b4_reduce.
-void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, const void* dZ, const void* X, void* dwpart,
-                           hipStream_t s) {
+// Padded mode: dZ has pitch Np (zero surplus columns), X pitch ldx (K or, as a copy, Kp); M at most fast_padded_b4_rows.
+// With split > 1 or extra > 0 fp32 partial sums as launch_fast_b4, otherwise dW [N][K] is final on return.
+void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, int extra, const void* dZ, const void* X, int64_t ldx,
+                           void* dW, void* dwpart, hipStream_t s) {
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
   FastParams p = {};
-  p.P = (const bf16_t*)X; p.Q = (const bf16_t*)dZ; p.ldp = K; p.ldq = Np;
-  p.C = nullptr; p.Cpart = (float*)dwpart;
+  p.P = (const bf16_t*)X; p.Q = (const bf16_t*)dZ; p.ldp = ldx; p.ldq = Np;
+  p.C = (bf16_t*)dW; p.Cpart = (float*)dwpart; p.pstride = partial_stride(N * K);
   p.I = (int)K; p.J = (int)N; p.tiles_i = (int)(Kp / kTile); p.tiles_j = (int)(Np / kTile);
   p.nkt = (int)(M / kB4BK / split); p.split = split;
-  launch<true, true, EPI_PARTIAL, kB4BK, stages_of(kB4BK), true, true>(p, s);
+  if (split > 1 || extra > 0) launch<true, true, EPI_PARTIAL, kB4BK, stages_of(kB4BK), true, true>(p, s);
+  else launch<true, true, EPI_STORE, kB4BK, stages_of(kB4BK), true, true>(p, s);
 }
 
-void launch_fast_b4_reduce(int64_t K, int64_t N, int parts, const void* dwpart, void* dW, hipStream_t s) {
-  const int64_t n = N * K;
-  hipLaunchKernelGGL(reduce_split_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s,
-                     (const float*)dwpart, parts, n, (bf16_t*)dW);
-}
-
-// dX and dW in one launch (see gemm_bf16_pair_kernel): for shapes where every dimension is a whole number of tiles and
-// the two outputs together have at most one tile per compute unit of the plan's part (kPlanCUs: the split is part of
-// the workspace plan and must not depend on the device).  The reductions (over N for dX, over M for dW) are split into
-// sa and sb parts - whole pipeline rounds of at least 512 - so that the workgroups fill the chip and the longer of the
-// two kinds of workgroup is as short as possible.  Returns false if the shape does not qualify.
-bool fast_pair_plan(int64_t M, int64_t K, int64_t N, int* sa_out, int* sb_out) {
-  if (static_cast<int>(kB3BK) != static_cast<int>(kB4BK)) return false;
-  if (M % kTile || !dims_ok(K, M, N, kB3BK) || !dims_ok(K, N, M, kB4BK)) return false;
-  const int64_t ta = (K / kTile) * (M / kTile), tb = (K / kTile) * (N / kTile);
+// dX and dW in one launch (see gemm_bf16_pair_kernel): for shapes where the two outputs together have at most one tile per
+// compute unit of the plan's part (kPlanCUs: the split is part of the workspace plan and must not depend on the device).
+// The reductions - over N (padded: Np) for dX, over `rows` rows for dW - are split into sa and sb parts, whole pipeline
+// rounds of at least 512, so that the workgroups fill the chip and the longer of the two kinds of workgroup is as short as
+// possible.  M, N, K: any with padded operands, else K and N multiples of the tile.  Returns false if it does not qualify.
+bool fast_pair_plan(int64_t M, int64_t K, int64_t N, int64_t rows, int* sa_out, int* sb_out) {
+  static_assert(kB3BK == kB4BK, "one pipeline shape for both");
+  const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K), tj = (M + kTile - 1) / kTile;
+  const int64_t ta = (Kp / kTile) * tj, tb = (Kp / kTile) * (Np / kTile);
   if (ta + tb > kPlanCUs) return false;
   const int64_t unit = (int64_t)kB3BK * stages_of(kB3BK);
   int best_sa = 0, best_sb = 0;
   int64_t best_len = 0, best_wgs = 0;
-  for (int sa = 1; sa <= 16; sa *= 2) {
-    if (N % (sa * unit) || (sa > 1 && N / sa < 512)) break;
-    for (int sb = 1; sb <= 16; sb *= 2) {
-      if (M % (sb * unit) || (sb > 1 && M / sb < 512)) break;
+  for (int sa = 1; sa <= 16; sa++) {
+    if (Np % (sa * unit) || (sa > 1 && Np / sa < 512)) continue;
+    for (int sb = 1; sb <= 16; sb++) {
+      if (rows % (sb * unit) || (sb > 1 && rows / sb < 512)) continue;
       const int64_t wgs = ta * sa + tb * sb;
       if (wgs > kPlanCUs) break;
-      const int64_t len = N / sa > M / sb ? N / sa : M / sb;     // reduction length of the longest workgroup
+      const int64_t len = Np / sa > rows / sb ? Np / sa : rows / sb;     // reduction length of the longest workgroup
       if (best_sa == 0 || len < best_len || (len == best_len && wgs < best_wgs)) {
         best_sa = sa; best_sb = sb; best_len = len; best_wgs = wgs;
       }
@@ -1078,36 +1167,46 @@ bool fast_pair_plan(int64_t M, int64_t K, int64_t N, int* sa_out, int* sb_out) {
   return true;
 }
 
-// dxpart: sa [M][K] fp32 partial sums (sa > 1), dwpart: sb [N][K] (sb > 1); an unsplit product goes to dX / dW directly.
-// The caller sums the partials (launch_fast_b4_reduce works for either).
-void launch_fast_pair(int64_t M, int64_t K, int64_t N, int sa, int sb, const void* dZ, bool dz_blocked, const void* W,
-                      const void* X, void* dX, void* dxpart, void* dW, void* dwpart, hipStream_t s) {
+// dxpart: sa fp32 partial sums [M][K] (sa > 1), dwpart: sb [N][K] (sb > 1, or more of the caller's behind them: extra > 0),
+// partial_stride elements apart; an unsplit product goes to dX / dW directly.  Wp: W, or its padded copy (ldw); X with
+// pitch ldx; dZ with pitch ldz.
+void launch_fast_pair(const PairArgs& a, hipStream_t s) {
+  const int64_t Np = fast_pad_dim(a.N), Kp = fast_pad_dim(a.K);
   FastParams pa = {}, pb = {};
-  pa.qblocked = pb.qblocked = dz_blocked ? 1 : 0;
-  pa.P = (const bf16_t*)W; pa.Q = (const bf16_t*)dZ; pa.ldp = K; pa.ldq = N; pa.C = (bf16_t*)dX; pa.Cpart = (float*)dxpart;
-  pa.I = (int)K; pa.J = (int)M; pa.tiles_i = (int)(K / kTile); pa.tiles_j = (int)(M / kTile);
-  pa.nkt = (int)(N / kB3BK / sa); pa.split = sa;
-  pb.P = (const bf16_t*)X; pb.Q = (const bf16_t*)dZ; pb.ldp = K; pb.ldq = N; pb.C = (bf16_t*)dW; pb.Cpart = (float*)dwpart;
-  pb.I = (int)K; pb.J = (int)N; pb.tiles_i = (int)(K / kTile); pb.tiles_j = (int)(N / kTile);
-  pb.nkt = (int)(M / kB4BK / sb); pb.split = sb;
+  pa.qblocked = pb.qblocked = a.dz_blocked ? 1 : 0;
+  pa.P = (const bf16_t*)a.W; pa.Q = (const bf16_t*)a.dZ; pa.ldp = a.ldw; pa.ldq = a.ldz; pa.C = (bf16_t*)a.dX; pa.Cpart = (float*)a.dxpart;
+  pa.I = (int)a.K; pa.J = (int)a.M; pa.ldc = a.K; pa.pstride = partial_stride(a.M * a.K);
+  pa.tiles_i = (int)(Kp / kTile); pa.tiles_j = (int)((a.M + kTile - 1) / kTile);
+  pa.nkt = (int)(Np / kB3BK / a.sa); pa.split = a.sa;
+  pb.P = (const bf16_t*)a.X; pb.Q = (const bf16_t*)a.dZ; pb.ldp = a.ldx; pb.ldq = a.ldz; pb.C = (bf16_t*)a.dW; pb.Cpart = (float*)a.dwpart;
+  pb.I = (int)a.K; pb.J = (int)a.N; pb.ldc = a.K; pb.pstride = partial_stride(a.N * a.K);
+  pb.tiles_i = (int)(Kp / kTile); pb.tiles_j = (int)(Np / kTile);
+  pb.nkt = (int)(a.rows / kB4BK / a.sb); pb.split = a.sb;
   DeviceInfo di;
   if (!device_info(&di)) return;
   const int na = pa.tiles_i * pa.tiles_j, nb = pb.tiles_i * pb.tiles_j;     // one tile per workgroup
   const bool die_aware = di.xcds > 1 && na % di.xcds == 0 && nb % di.xcds == 0;
   pa.xcds = die_aware ? di.xcds : 1; pb.xcds = pa.xcds;
-  const dim3 grid((unsigned)(na * sa + nb * sb));
+  const dim3 grid((unsigned)(na * a.sa + nb * a.sb));
   constexpr int NS = stages_of(kB3BK);
-#define FDL_PAIR(EA, EB)                                                                                   \
+  const bool rag = a.M % kTile || a.N % kTile || a.K % kTile, parta = a.sa > 1, partb = a.sb > 1 || a.extra > 0;
+#define FDL_PAIR(EA, EB, RAG)                                                                              \
   do {                                                                                                     \
     static OnceFlags configured;                                                                           \
-    auto kern = gemm_bf16_pair_kernel<kB3BK, NS, EA, EB>;                                                  \
+    auto kern = gemm_bf16_pair_kernel<kB3BK, NS, EA, EB, RAG>;                                             \
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kLdsBytes, &configured)) return;          \
     hipLaunchKernelGGL(kern, grid, dim3(256), kLdsBytes, s, pa, pb, na, nb);                               \
   } while (0)
-  if (sa > 1 && sb > 1) FDL_PAIR(EPI_PARTIAL, EPI_PARTIAL);
-  else if (sa > 1) FDL_PAIR(EPI_PARTIAL, EPI_STORE);
-  else if (sb > 1) FDL_PAIR(EPI_STORE, EPI_PARTIAL);
-  else FDL_PAIR(EPI_STORE, EPI_STORE);
+#define FDL_PAIR_RAG(RAG)                                                  \
+  do {                                                                     \
+    if (parta && partb) FDL_PAIR(EPI_PARTIAL, EPI_PARTIAL, RAG);           \
+    else if (parta) FDL_PAIR(EPI_PARTIAL, EPI_STORE, RAG);                 \
+    else if (partb) FDL_PAIR(EPI_STORE, EPI_PARTIAL, RAG);                 \
+    else FDL_PAIR(EPI_STORE, EPI_STORE, RAG);                              \
+  } while (0)
+  if (rag) FDL_PAIR_RAG(true);
+  else FDL_PAIR_RAG(false);
+#undef FDL_PAIR_RAG
 #undef FDL_PAIR
 }
 

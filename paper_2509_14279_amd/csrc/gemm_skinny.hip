@@ -25,7 +25,8 @@ struct SkinnyParams {
   const bf16_t* X; const bf16_t* W; const bf16_t* W2;   // W2: SK_GATE, the up weights
   const float* bias;      // may be null (SK_STORE, SK_RELU, SK_MASK)
   const bf16_t* aux;      // SK_MASK: [M][N]
-  bf16_t* out;            // [M][N]
+  bf16_t* out;            // [M][ldo]
+  int64_t ldo;
   int64_t K;
   int M, N;
   int mblocks;            // row blocks of 16 MB
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
   if (wave != 0) return;
 
   // a lane holds columns n0 + 16 f + 4 g .. + 3 of row m0 + 16 b + l16
-  const bool vec = (p.N & 3) == 0;                   // then a group of four columns exists whole or not at all
+  const bool vec = (p.N & 3) == 0 && (p.ldo & 3) == 0;   // then a group of four columns exists whole or not at all
 #pragma unroll
   for (int f = 0; f < NB; f++) {
     const int n = n0 + f * 16 + g * 4;
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
     for (int b = 0; b < MB; b++) {
       const int m = m0 + b * 16 + l16;
       if (m >= p.M) continue;
-      const int64_t at = (int64_t)m * p.N + n;
+      const int64_t at = (int64_t)m * p.N + n, to = (int64_t)m * p.ldo + n;
       bf16x4 o;
 #pragma unroll
       for (int r = 0; r < 4; r++) {
@@ -171,11 +172,11 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
         else o[r] = (bf16_t)v;
       }
       if (vec) {
-        *reinterpret_cast<bf16x4*>(p.out + at) = o;
+        *reinterpret_cast<bf16x4*>(p.out + to) = o;
       } else {
 #pragma unroll
         for (int r = 0; r < 4; r++)
-          if (n + r < p.N) p.out[at + r] = o[r];
+          if (n + r < p.N) p.out[to + r] = o[r];
       }
     }
   }
@@ -218,8 +219,9 @@ bool skinny_supported(int64_t M, int64_t K, int64_t N) {
 
 // out[m][n] = f(sum_k X[m][k] W[n][k] + bias[n]): kind 0 plain (bias may be null), 1 max(., 0), 2 aux[m][n] where positive
 void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias,
-                       const void* aux, void* out, hipStream_t s) {
+                       const void* aux, void* out, int64_t ldo, hipStream_t s) {
   SkinnyParams p = {};
+  p.ldo = ldo;
   p.X = (const bf16_t*)X; p.W = (const bf16_t*)W; p.bias = bias; p.aux = (const bf16_t*)aux; p.out = (bf16_t*)out;
   p.K = K; p.M = (int)M; p.N = (int)N;
   if (kind == 1) dispatch_skinny<SK_RELU>(p, s);
@@ -231,7 +233,7 @@ void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X,
 void launch_skinny_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s) {
   SkinnyParams p = {};
   p.X = (const bf16_t*)X; p.W = (const bf16_t*)Wg; p.W2 = (const bf16_t*)Wu; p.out = (bf16_t*)out;
-  p.K = D; p.M = (int)M; p.N = (int)H;
+  p.K = D; p.M = (int)M; p.N = (int)H; p.ldo = H;
   dispatch_skinny<SK_GATE>(p, s);
 }
 

@@ -17,6 +17,27 @@ namespace fdl {
 
 enum DType { kF32 = 0, kBF16 = 1 };
 
+// The two contractions that end a backward pass: dX [M,K] = dZ W, dW [N,K] = dZ^T X.
+struct GradPlan {
+  int dt;
+  int64_t M, K, N;
+  int b3_fast, b4_fast;   // dX, dW on the tuned kernels
+  int b3_wb, b4_wb;
+  int pad;                // 1: padded mode of the fast contractions (N, K not both multiples of 256)
+  int stage_x;            // 1 (padded mode): X goes through a copy with pitch Kp
+  int64_t ldz;            // pitch of the dZ buffer in elements (N, or N rounded up to 256 in padded mode)
+  int blocked;            // 1: dZ lives in 32 x 32 blocks (its writer -> tuned dX and dW kernels only)
+  int64_t b4_fast_rows;   // rows of dW's reduction the fast kernel covers
+  int extra;              // 1: the generic kernel adds a partial sum for the rows after them
+  int pair;               // 1: both contractions share one launch
+  int split_a, split_b;   // parts of the reductions over N (dX) and over M (dW)
+  int parts_b;            // partial sums of dW: split_b + extra
+  size_t off_dz;          // T [M rounded up to 256][ldz]
+  size_t off_dxpart;      // float [split_a][M][K]   (split_a > 1)
+  size_t off_dwpart;      // float [parts_b][N][K]   (parts_b > 1)
+  size_t off_wpad, off_xpad;   // zero-padded copies of W and (stage_x) X
+};
+
 struct Plan {
   int dt;
   int64_t M, K, N;
@@ -33,27 +54,17 @@ struct Plan {
   int b1_fused;           // 1: one pass with the row held in registers; 0: B1a + B1b
   int b1_groups;          // number of row groups that produce column partials
   int b1_rows_per_group;  // B1b only
-  int b3_fast, b4_fast;
-  int b3_wb, b4_wb;
-  int b4_split;           // split of the reduction over M in B4 (fast kernel)
-  int64_t b4_fast_rows;   // rows of the reduction the fast kernel covers (the rest goes through the generic kernel)
-  int pair;               // 1: dX and dW share one launch, their reductions split into pair_sa and pair_sb parts
-  int pair_sa, pair_sb;
-  int dz_blocked;         // 1: dZ lives in 32 x 32 blocks (fused row kernel -> tuned dX and dW kernels only)
-  size_t off_dxpart;      // float [pair_sa][M][K] (pair_sa > 1)
-  int pad;                // 1: padded mode of the fast contractions (N, K multiples of 8, not both of 256)
-  int64_t ldz;            // pitch of the dZ buffer in elements (N, or N rounded up to 256 in padded mode)
+  GradPlan g;             // dX and dW
+  int pad;                // forward: padded mode of the fast contraction (N, K not both multiples of 256)
   size_t off_wpad_f, off_bpad_f;   // forward: zero-padded copies of W [Np][Kp] and b [Np]
-  size_t off_wpad_b;               // backward: zero-padded copy of W
-  size_t off_xtail;       // forward: padded copy of X's last rows (ragged M on the fast path)
-  size_t off_dz;          // T [M][N]
+  size_t off_xtail;       // forward: padded copy of X's last rows (ragged M on the fast path), or of X
   size_t off_c12;         // C [2][M]
   size_t off_colpart;     // C [groups][3][N]
-  size_t off_dwpart;      // float [split][N][K]
   size_t bwd_bytes;
   size_t bytes;           // max(fwd, bwd)
 };
 
+void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, size_t* off, GradPlan* p);
 // Returns false when the shape or dtype is not supported.
 bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p);
 
@@ -87,7 +98,7 @@ struct GemmDesc {
 void launch_generic_xwt(int dt, int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s);
 // plain store: C [I][J] in the storage type
 void launch_generic_store(int dt, const GemmDesc& g, void* C, hipStream_t s);
-// plain store of the fp32 accumulators: C [I][J] float (bf16 storage; a partial sum for launch_fast_b4_reduce)
+// plain store of the fp32 accumulators: C [I][J] float (bf16 storage; a partial sum for launch_finish)
 void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s);
 
 // ---- row-wise / column-wise phases ------------------------------------------------------------
@@ -112,17 +123,19 @@ void launch_b1_fused(int dt, int64_t M, int64_t N, int64_t ldz, int groups, bool
 void launch_b2(int dt, int64_t N, int groups, const void* colpart, float* dbeta, float* dgamma, float* db,
                hipStream_t s);
 // bf16: the column sums (as launch_b2) and up to two sums of fp32 split-reduction partials
-// (out[k][i] = bf16(sum over q < parts[k] of part[k][q * n[k] + i]); parts[k] = 0: none) in one launch
+// (out[k][i] = bf16(sum over q < parts[k] of part[k][q * partial_stride(n[k]) + i]); parts[k] = 0: none) in one launch
 struct TailSums {
   const float* part[2];
   int parts[2];
   int64_t n[2];
   void* out[2];
-  int blocks[2];          // filled in by launch_finish
-  const float* colpart;   // [groups][3][N]
+  int blocks[2];          // filled in by launch_finish, as stride
+  int64_t stride[2];
+  const float* colpart;
   int groups;
   int64_t N;
-  float *dbeta, *dgamma, *db;
+  int kinds;              // kinds of column sum: colpart [groups][kinds][N] -> col_out
+  float* col_out[3];
 };
 void launch_finish(TailSums j, hipStream_t s);
 
@@ -131,14 +144,15 @@ void launch_layernorm(int dt, int64_t M, int64_t N, float eps, const void* A, co
                       void* Y, float* mean, float* rstd, hipStream_t s);
 void launch_rmsnorm(int dt, int64_t M, int64_t N, float eps, const void* A, const float* weight, void* Y, hipStream_t s);
 int colsum_groups(int64_t M);
-// blocked: G is stored in 32 x 32 blocks (bf16; M, N multiples of 32)
-void launch_colsum(int dt, int64_t M, int64_t N, const void* G, bool blocked, void* colpart, float* out, hipStream_t s);
+// ldg: pitch of G; blocked: G is stored in 32 x 32 blocks (bf16; M, N multiples of 32)
+void launch_colsum_partial(int dt, int64_t M, int64_t N, int64_t ldg, const void* G, bool blocked, void* colpart, hipStream_t s);
+void launch_colsum_finish(int dt, int64_t M, int64_t N, const void* colpart, float* out, hipStream_t s);
 void launch_silu_mul(int dt, int64_t n, const void* G, const void* U, void* H, hipStream_t s);
 
 // ---- bf16 products with few rows (gemm_skinny.hip): any K and N -----------------------------------
 bool skinny_supported(int64_t M, int64_t K, int64_t N);
 void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias,
-                       const void* aux, void* out, hipStream_t s);
+                       const void* aux, void* out, int64_t ldo, hipStream_t s);
 void launch_skinny_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s);
 
 // ---- bf16 fast path -----------------------------------------------------------------------------
@@ -151,17 +165,38 @@ int64_t fast_b4_rows(int64_t M);
 size_t fast_f1_tail_bytes(int64_t M, int64_t K);
 // Wt: null, or the transposed weights [K][N] from launch_fast_transpose (N, K multiples of 64)
 void launch_fast_transpose(int64_t N, int64_t K, const void* W, void* Wt, hipStream_t s);
-// padded mode (N, K multiples of 8 but not both of 256): see gemm_bf16.hip
+// zero-padded copies of up to four matrices and one vector in one launch (see stage_kernel)
+struct StageJob { const void* src; void* dst; int64_t rows, cols, ld, rows_out, cols_out; int blocks; };
+struct StageJobs { StageJob job[4]; int count; const float* vsrc; float* vdst; int64_t vn, vn_out; };
+void stage_matrix(StageJobs* j, const void* src, int64_t rows, int64_t cols, int64_t ld, void* dst, int64_t rows_out, int64_t cols_out);
+void stage_vector(StageJobs* j, const float* src, int64_t n, float* dst, int64_t n_out);
+void launch_stage(const StageJobs& j, hipStream_t s);
+// padded mode (N, K not both multiples of 256): see gemm_bf16.hip
+constexpr int64_t kStageFromWork = (int64_t)1 << 28;   // M N K from which odd rows are worth copying
 bool fast_padded_supported(int64_t M, int64_t K, int64_t N);
+bool fast_padded_stages_x(int64_t K);          // X goes through a copy with pitch Kp (else only its last row tile is copied)
 int64_t fast_pad_dim(int64_t n);
+int64_t fast_padded_rows(int64_t M);           // rows of that copy, and of dZ
 size_t fast_padded_tail_bytes(int64_t K);
+inline size_t fast_padded_x_bytes(int64_t M, int64_t K) {
+  return fast_padded_stages_x(K) ? (size_t)fast_padded_rows(M) * fast_pad_dim(K) * 2 : fast_padded_tail_bytes(K);
+}
 int64_t fast_padded_b4_rows(int64_t M, int64_t K);
-void launch_fast_pad_weights(int64_t K, int64_t N, const void* W, const float* bias, void* Wp, float* biasp, hipStream_t s);
-void launch_fast_f1_padded(int64_t M, int64_t K, int64_t N, const void* X, const void* Wp, const float* biasp, void* Zsave,
-                           void* xtail, hipStream_t s);
+void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias, void* xw,
+                  void* Wp, float* biasp);
+void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* xw, const void* Wp,
+                            const float* biasp, const void* aux, void* out, hipStream_t s);
+int64_t fast_gate_pad_h(int64_t H);
+int64_t fast_gate_pad_d(int64_t D);
+void stage_gate_x(StageJobs* j, const void* X, int64_t M, int64_t D, void* xw);
+void launch_fast_gate_padded(int64_t M, int64_t D, int64_t H, const void* X, const void* xw, const void* Wgp, const void* Wup,
+                             void* Hout, hipStream_t s);
+void launch_fast_down_padded(int64_t M, int64_t D, int64_t Hp, const void* G, const void* Wdp, void* out, hipStream_t s);
+// fp32 partial sums of n elements lie this far apart (16-byte parts)
+inline int64_t partial_stride(int64_t n) { return (n + 3) & ~(int64_t)3; }
 void launch_fast_b3_padded(int64_t M, int64_t K, int64_t N, const void* dZ, const void* Wp, void* dX, hipStream_t s);
-void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, const void* dZ, const void* X, void* dwpart,
-                           hipStream_t s);
+void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, int extra, const void* dZ, const void* X, int64_t ldx,
+                           void* dW, void* dwpart, hipStream_t s);
 // the forward product, also of the sibling operators (see gemm_bf16.hip); shapes as fast_f1_supported;
 // Wt: null, or the transposed weights from launch_fast_transpose
 constexpr int64_t kTransposeFromRows = 16384;   // batch size from which transposing the weights first pays
@@ -181,10 +216,16 @@ void launch_fast_b3(int64_t M, int64_t K, int64_t N, const void* dZ, bool dz_blo
 int fast_b4_split(int64_t M, int64_t K, int64_t N);
 void launch_fast_b4(int64_t M, int64_t K, int64_t N, int split, int extra, const void* dZ, bool dz_blocked, const void* X,
                     void* dW, void* dwpart, hipStream_t s);
-void launch_fast_b4_reduce(int64_t K, int64_t N, int parts, const void* dwpart, void* dW, hipStream_t s);
 // dX and dW in one launch where together they have at most a tile per compute unit; sa, sb: parts of the two reductions
-bool fast_pair_plan(int64_t M, int64_t K, int64_t N, int* sa, int* sb);
-void launch_fast_pair(int64_t M, int64_t K, int64_t N, int sa, int sb, const void* dZ, bool dz_blocked, const void* W,
-                      const void* X, void* dX, void* dxpart, void* dW, void* dwpart, hipStream_t s);
+bool fast_pair_plan(int64_t M, int64_t K, int64_t N, int64_t rows, int* sa, int* sb);
+struct PairArgs {
+  int64_t M, K, N, rows;       // rows: of the dW reduction
+  int sa, sb, extra;
+  const void* dZ; int64_t ldz; bool dz_blocked;
+  const void* W; int64_t ldw;
+  const void* X; int64_t ldx;
+  void* dX; void* dxpart; void* dW; void* dwpart;
+};
+void launch_fast_pair(const PairArgs& a, hipStream_t s);
 
 }  // namespace fdl

@@ -639,7 +639,7 @@ __global__ __launch_bounds__(1024) void b2_kernel(int64_t N, int groups, const C
 
 // The tail of a bf16 backward pass in one launch, for shapes where the contractions leave split reductions behind:
 // workgroups [0, a.blocks) and [a.blocks, a.blocks + b.blocks) add the fp32 partial products of up to two outputs
-// (4096 elements per workgroup, partials summed in index order, one rounding to bf16), the remaining 3 ceil(N / 64)
+// (4096 elements per workgroup, partials summed in index order, one rounding to bf16), the remaining kinds ceil(N / 64)
 // workgroups finish the column sums exactly as b2_kernel does.  Small dependent launches cost a few microseconds each
 // whatever they do, which is what this saves for mid-sized layers.
 __global__ __launch_bounds__(1024) void finish_kernel(TailSums j) {
@@ -652,20 +652,25 @@ __global__ __launch_bounds__(1024) void finish_kernel(TailSums j) {
       const float* part = j.part[k];
       f32x4 acc = *reinterpret_cast<const f32x4*>(part + i);
       for (int q = 1; q < j.parts[k]; q++) {
-        const f32x4 t = *reinterpret_cast<const f32x4*>(part + (int64_t)q * j.n[k] + i);
+        const f32x4 t = *reinterpret_cast<const f32x4*>(part + (int64_t)q * j.stride[k] + i);
         acc[0] += t[0]; acc[1] += t[1]; acc[2] += t[2]; acc[3] += t[3];
       }
       bf16x4 o;
       o[0] = (bf16_t)acc[0]; o[1] = (bf16_t)acc[1]; o[2] = (bf16_t)acc[2]; o[3] = (bf16_t)acc[3];
-      *reinterpret_cast<bf16x4*>(static_cast<bf16_t*>(j.out[k]) + i) = o;
+      bf16_t* out = static_cast<bf16_t*>(j.out[k]) + i;
+      if (i + 4 <= j.n[k]) {
+        *reinterpret_cast<bf16x4*>(out) = o;
+      } else {
+        for (int e = 0; i + e < j.n[k]; e++) out[e] = o[e];
+      }
       return;
     }
     id -= j.blocks[k];
   }
   const int cblocks = (int)((j.N + 63) / 64);
   const int which = id / cblocks;
-  b2_columns<float>(j.N, j.groups, 3, j.colpart, id % cblocks, which,
-                    which == 0 ? j.dbeta : (which == 1 ? j.dgamma : j.db), red);
+  b2_columns<float>(j.N, j.groups, j.kinds, j.colpart, id % cblocks, which,
+                    which == 0 ? j.col_out[0] : (which == 1 ? j.col_out[1] : j.col_out[2]), red);
 }
 
 
@@ -851,7 +856,7 @@ __global__ __launch_bounds__(256) void row_stream_kernel(int64_t M, int64_t N, f
 // BLK: the matrix is stored in 32 x 32 blocks (see gemm_bf16.hip); a lane's 16 bytes are then a quarter of a 64-byte
 // piece, and the group walks rows in neighbouring pairs, whose pieces share a line (M even).
 template <class T, int V, bool BLK = false>
-__global__ __launch_bounds__(256) void colsum_partial_kernel(int64_t M, int64_t N, int strips, int groups,
+__global__ __launch_bounds__(256) void colsum_partial_kernel(int64_t M, int64_t N, int64_t ldg, int strips, int groups,
                                                              const T* __restrict__ G,
                                                              typename ComputeOf<T>::type* __restrict__ colpart) {
   typedef typename ComputeOf<T>::type C;
@@ -877,12 +882,12 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(int64_t M, int64_t 
 #pragma unroll 4
     for (int64_t r = grp; r < M; r += groups) {
       C x[V];
-      VecIO<T, V>::load(G + r * N + col, x);
+      VecIO<T, V>::load(G + r * ldg + col, x);
 #pragma unroll
       for (int v = 0; v < V; v++) acc[v] += x[v];
     }
   }
-  if constexpr (V > 1) store_columns<C, V>(colpart + (int64_t)grp * N + col, acc, V);
+  if constexpr (V > 1) store_columns<C, V>(colpart + (int64_t)grp * N + col, acc, N - col > V ? V : (int)(N - col));
   else colpart[(int64_t)grp * N + col] = acc[0];
 }
 
@@ -1063,24 +1068,27 @@ void launch_rmsnorm(int dt, int64_t M, int64_t N, float eps, const void* A, cons
 // groups of the first stage of a column sum over M rows
 int colsum_groups(int64_t M) { return (int)(M < 256 ? (M > 0 ? M : 1) : 256); }
 
-// out[j] = sum_i G[i][j]; colpart: colsum_groups(M) * N values of the arithmetic type
-void launch_colsum(int dt, int64_t M, int64_t N, const void* G, bool blocked, void* colpart, float* out, hipStream_t s) {
+// sums over the rows of G [M][N], pitch ldg: colsum_groups(M) partial sums per column, then the sums themselves
+void launch_colsum_partial(int dt, int64_t M, int64_t N, int64_t ldg, const void* G, bool blocked, void* colpart, hipStream_t s) {
   const int groups = colsum_groups(M);
   const int vmax = dt == kF32 ? 4 : 8;
-  const bool vec = N % vmax == 0 && (uintptr_t)G % 16 == 0;
+  const bool vec = ldg % vmax == 0;            // (a vector that passes N stays inside the pitch)
   const int V = vec ? vmax : 1;
   const int strips = (int)((N + 256 * (int64_t)V - 1) / (256 * (int64_t)V));
   const dim3 grid((unsigned)(strips * groups));
   if (dt == kF32) {
-    if (vec) hipLaunchKernelGGL((colsum_partial_kernel<float, 4>), grid, dim3(256), 0, s, M, N, strips, groups, (const float*)G, (double*)colpart);
-    else hipLaunchKernelGGL((colsum_partial_kernel<float, 1>), grid, dim3(256), 0, s, M, N, strips, groups, (const float*)G, (double*)colpart);
-    hipLaunchKernelGGL((b2_kernel<double>), dim3((unsigned)((N + 63) / 64), 1), dim3(1024), 0, s, N, groups, (const double*)colpart, out, out, out);
+    auto kern = vec ? colsum_partial_kernel<float, 4> : colsum_partial_kernel<float, 1>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, M, N, ldg, strips, groups, (const float*)G, (double*)colpart);
   } else {
-    if (vec && blocked) hipLaunchKernelGGL((colsum_partial_kernel<bf16_t, 8, true>), grid, dim3(256), 0, s, M, N, strips, groups, (const bf16_t*)G, (float*)colpart);
-    else if (vec) hipLaunchKernelGGL((colsum_partial_kernel<bf16_t, 8>), grid, dim3(256), 0, s, M, N, strips, groups, (const bf16_t*)G, (float*)colpart);
-    else hipLaunchKernelGGL((colsum_partial_kernel<bf16_t, 1>), grid, dim3(256), 0, s, M, N, strips, groups, (const bf16_t*)G, (float*)colpart);
-    hipLaunchKernelGGL((b2_kernel<float>), dim3((unsigned)((N + 63) / 64), 1), dim3(1024), 0, s, N, groups, (const float*)colpart, out, out, out);
+    auto kern = vec && blocked ? colsum_partial_kernel<bf16_t, 8, true> : (vec ? colsum_partial_kernel<bf16_t, 8> : colsum_partial_kernel<bf16_t, 1>);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, M, N, ldg, strips, groups, (const bf16_t*)G, (float*)colpart);
   }
+}
+void launch_colsum_finish(int dt, int64_t M, int64_t N, const void* colpart, float* out, hipStream_t s) {
+  const int groups = colsum_groups(M);
+  const dim3 grid((unsigned)((N + 63) / 64), 1);
+  if (dt == kF32) hipLaunchKernelGGL((b2_kernel<double>), grid, dim3(1024), 0, s, N, groups, (const double*)colpart, out, out, out);
+  else hipLaunchKernelGGL((b2_kernel<float>), grid, dim3(1024), 0, s, N, groups, (const float*)colpart, out, out, out);
 }
 
 // H = SiLU(G) * U over n elements (H may alias G or U)
@@ -1168,14 +1176,14 @@ void launch_b2(int dt, int64_t N, int groups, const void* colpart, float* dbeta,
   else hipLaunchKernelGGL((b2_kernel<float>), grid, dim3(1024), 0, s, N, groups, (const float*)colpart, dbeta, dgamma, db);
 }
 
-// n[k] must be multiples of 4 (they are products of tile-aligned or 8-aligned dimensions on the bf16 tuned path).
 void launch_finish(TailSums j, hipStream_t s) {
   unsigned blocks = 0;
   for (int k = 0; k < 2; k++) {
-    j.blocks[k] = j.parts[k] > 0 ? (int)((j.n[k] / 4 + 1023) / 1024) : 0;
+    j.blocks[k] = j.parts[k] > 0 ? (int)(((j.n[k] + 3) / 4 + 1023) / 1024) : 0;
+    j.stride[k] = partial_stride(j.n[k]);
     blocks += (unsigned)j.blocks[k];
   }
-  blocks += 3u * (unsigned)((j.N + 63) / 64);
+  blocks += (unsigned)j.kinds * (unsigned)((j.N + 63) / 64);
   hipLaunchKernelGGL(finish_kernel, dim3(blocks), dim3(1024), 0, s, j);
 }
 

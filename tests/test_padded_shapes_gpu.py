@@ -1,0 +1,96 @@
+"""The tuned bf16 contractions on widths that are no multiple of their tile: rows that start at any element (X goes through a
+padded copy), rows of 16-byte pieces (X as it is), reductions below 128, widths that end inside a vector, batches that end
+inside a tile or a pipeline round; dX and dW in one launch and in two; every epilogue.  The workspace starts as NaNs, so that
+nothing is read that was not written.  Bars as in the other parity tests, against the fp64 oracles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fdl_oracle as O
+from oracle import siblings_oracle as S
+from paper_2509_14279_amd import api, inputs as I
+import harness as H
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(129, 1451, 1451), (700, 100, 4096), (3001, 771, 120), (1000, 515, 2049), (640, 1000, 4101), (2500, 1000, 300),
+          (385, 1285, 770), (257, 4099, 264), (20000, 130, 126)]
+
+
+def nan_workspace(nbytes):
+    ws = H.Guarded((max(256, nbytes),), torch.uint8)
+    ws.view.fill_(0xff)
+    return ws
+
+
+def f64(t):
+    return {k: v.numpy().astype(np.float64) for k, v in t.items()}
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+def test_block(M, K, N):
+    cfg = I.custom("bf16", M, K, N, seed=9300 + M + K + N)
+    print(f"[padded] {cfg.name}", flush=True)
+    t = I.generate(cfg)
+    bf = torch.bfloat16
+    X, W, dY = (t[k].to("cuda", bf) for k in ("X", "W", "dY"))
+    b, gamma, beta = (t[k].to("cuda") for k in ("b", "gamma", "beta"))
+    out = {k: H.Guarded(sh, dt) for k, sh, dt in (
+        ("Y", (M, N), bf), ("Z", (M, N), bf), ("mean", (M,), torch.float32), ("rstd", (M,), torch.float32),
+        ("dX", (M, K), bf), ("dW", (N, K), bf), ("db", (N,), torch.float32), ("dgamma", (N,), torch.float32),
+        ("dbeta", (N,), torch.float32))}
+    ws = nan_workspace(api.fdl_workspace_bytes("bf16", M, K, N))
+    v = {k: g.view for k, g in out.items()}
+    api.fdl_forward("bf16", X, W, b, gamma, beta, cfg.eps, v["Y"], v["Z"], v["mean"], v["rstd"], ws.view)
+    ws.view.fill_(0xff)
+    api.fdl_backward("bf16", dY, X, W, gamma, v["Z"], v["mean"], v["rstd"], v["dX"], v["dW"], v["db"], v["dgamma"],
+                     v["dbeta"], ws.view)
+    torch.cuda.synchronize()
+    for k, g in list(out.items()) + [("workspace", ws)]:
+        assert g.intact(), f"kernel wrote outside the {k} buffer"
+    n = f64(t)
+    ref = O.forward_backward(n["X"], n["W"], n["b"], n["gamma"], n["beta"], n["dY"], cfg.eps)
+    for k in H.OUTPUTS + ("Z", "mean"):
+        H.check("bf16", k, H.to_f64(v[k]), ref[k])
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+def test_linear_relu(M, K, N):
+    cfg = I.custom("bf16", M, K, N, seed=9400 + M + K + N)
+    print(f"[padded] relu {cfg.name}", flush=True)
+    t = I.generate(cfg)
+    bf = torch.bfloat16
+    X, W, dY = (t[k].to("cuda", bf) for k in ("X", "W", "dY"))
+    b = t["b"].to("cuda")
+    out = {"Y": H.Guarded((M, N), bf), "dX": H.Guarded((M, K), bf), "dW": H.Guarded((N, K), bf), "db": H.Guarded((N,), torch.float32)}
+    ws = nan_workspace(api.fdl_linear_relu_workspace_bytes("bf16", M, K, N))
+    api.fdl_linear_relu_forward("bf16", X, W, b, out["Y"].view, ws.view)
+    ws.view.fill_(0xff)
+    api.fdl_linear_relu_backward("bf16", dY, X, W, b, out["dX"].view, out["dW"].view, out["db"].view, ws.view)
+    torch.cuda.synchronize()
+    for k, g in list(out.items()) + [("workspace", ws)]:
+        assert g.intact(), f"kernel wrote outside the {k} buffer"
+    n = f64(t)
+    H.check("bf16", "Y", H.to_f64(out["Y"].view), S.linear_relu_forward(n["X"], n["W"], n["b"])["Y"])
+    # a mask within 2^-20 of the sum of its terms (fp32 sums of at most 4099 products) may go either way
+    ref = S.linear_relu_backward(n["dY"], n["X"], n["W"], n["b"])
+    unsure = np.abs(n["dY"]) * (np.abs(ref["Z"]) <= 2.0 ** -20 * (np.abs(n["X"]) @ np.abs(n["W"]).T + np.abs(n["b"])))
+    add = {"dX": unsure @ np.abs(n["W"]), "dW": unsure.T @ np.abs(n["X"]), "db": unsure.sum(axis=0)}
+    for k in ("dX", "dW", "db"):
+        got = H.to_f64(out[k].view)
+        assert np.all(np.abs(got - ref[k]) <= 2e-2 * np.abs(ref[k]).max() + add[k]), k
+
+
+@pytest.mark.parametrize("M,D,Hd", [(130, 1451, 1500), (1000, 640, 1000), (777, 1000, 1003), (4096, 264, 257), (512, 512, 1100),
+                                    (600, 700, 1280)])
+def test_feed_forward_block(M, D, Hd):
+    print(f"[padded] ffn {M}x{D}x{Hd}", flush=True)
+    t = I.generate_ffn("bf16", M, D, Hd, seed=9500 + M + D + Hd)
+    d = {k: v.to("cuda", torch.bfloat16) for k, v in t.items()}
+    Y = H.Guarded((M, D), torch.bfloat16)
+    ws = nan_workspace(api.fdl_llama_ffn_workspace_bytes("bf16", M, D, Hd))
+    api.fdl_llama_ffn_forward("bf16", d["X"], d["Wg"], d["Wu"], d["Wd"], Y.view, ws.view)
+    torch.cuda.synchronize()
+    assert Y.intact() and ws.intact()
+    n = f64(t)
+    H.check("bf16", "Y", H.to_f64(Y.view), S.llama_ffn_forward(n["X"], n["Wg"], n["Wu"], n["Wd"])["Y"])
