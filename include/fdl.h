@@ -102,7 +102,7 @@ FDL_API fdl_status fdl_forward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * nothing; the first call on a GPU looks up the array's device address (a host-side query, no stream work).
  *
  * Limit: problems that need more than the array holds are rejected with FDL_ERR_WORKSPACE before any device call.  What
- * counts is the forward scratch plus 8 bytes per (row, column tile of 64 or 128) - nothing for the latter on the bf16
+ * counts is the forward scratch plus 8 bytes per (row, column tile of 32 to 128) - nothing for the latter on the bf16
  * path with K % 128 == 0, N % 256 == 0, N <= 8192, M >= 128.  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
  * one GPU (different streams, different host threads) race: order them on one stream or with events.
  */

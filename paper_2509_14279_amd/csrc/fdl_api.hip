@@ -32,13 +32,10 @@ bool shape_ok(int64_t M, int64_t K, int64_t N) {
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // Block tile of the generic kernel (as 16 x 16 blocks per wave tile side): 128 x 128 where that still gives every
-// compute unit a tile, else 64 x 64.  fp32 storage always takes the small tile: its fp64 accumulators leave room for
-// one workgroup per compute unit only at the large one, and with four the latencies of its register-staged loads are
-// covered (measured: twice as fast on the forward contraction of the ragged fp32 configuration).
-int pick_generic_wb(int dt, int64_t I, int64_t J) {
-  if (dt == kF32) return 2;
-  return (((I + 127) / 128) * ((J + 127) / 128) >= 256) ? 4 : 2;
-}
+// compute unit a tile, else 64 x 64.
+int pick_generic_wb(int64_t I, int64_t J) { return (((I + 127) / 128) * ((J + 127) / 128) >= 256) ? 4 : 2; }
+// fp32 storage: all tiles as they are, where there is no scratch for the sums of split ones
+F64Split f64_unsplit(int64_t I, int64_t J) { return F64Split{((I + 63) / 64) * ((J + 63) / 64), 0, 1}; }
 
 thread_local bool t_failure_noted = false;
 
@@ -105,7 +102,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   // ---- forward
   q.f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
   q.f1_fast = q.pad || (dt == kBF16 && fast_f1_supported(M, K, N));
-  q.f1_wb = pick_generic_wb(dt, Mp, N);
+  q.f1_wb = pick_generic_wb(Mp, N);
   size_t off = 0;
   const bool tiled = q.f1_fast && !q.f1_skinny;
   q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K) : fast_f1_tail_bytes(M, K)));
@@ -113,6 +110,10 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
   // Large batches on the tuned kernel (tile-aligned N and K): the weights are transposed first, 4 N K bytes of traffic
   // against about 6 % of the contraction's time; that pays from roughly 10^4 rows, with a margin for the extra launch.
+  if (dt == kF32) {
+    q.f1_s64 = f64_plan(Mp, N, K);
+    q.off_part64 = off; off += align256(f64_part_bytes(q.f1_s64));
+  }
   q.fwd_bytes_plain = off;
   q.f1_wt = tiled && !q.pad && M >= kTransposeFromRows;
   q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
@@ -122,7 +123,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   // the tiled kernel.
   const bool copies = q.pad && N % 8 == 0 && K % 8 == 0 && K >= 128;
   const bool limit_fast = copies || (!q.pad && q.f1_fast);
-  const int64_t limit_tile = limit_fast ? 128 : 16 * q.f1_wb;
+  const int64_t limit_tile = limit_fast ? 128 : (dt == kF32 ? 32 : 16 * q.f1_wb);
   q.static_need = (limit_fast && N % 8 == 0 && N <= 8192 ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8)) +
                   align256(copies ? fast_padded_tail_bytes(K) : (limit_fast ? fast_f1_tail_bytes(M, K) : 0)) +
                   align256(copies ? (size_t)Np * Kp * 2 : 0) + align256(copies ? (size_t)Np * 4 : 0);
@@ -148,7 +149,9 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.off_colpart = off; off += align256((size_t)q.b1_groups * 3 * N * cs);
   make_grad_plan(dt, M, K, N, may_block, &off, &q.g);
   q.bwd_bytes = off;
-  q.bytes = q.fwd_bytes > q.bwd_bytes ? q.fwd_bytes : q.bwd_bytes;
+  // (one buffer for both passes and for fdl_forward_inference, which keeps mean and rstd in it)
+  const size_t fwd_all = q.fwd_bytes + 2 * align256((size_t)Mp * 4) + 256;
+  q.bytes = fwd_all > q.bwd_bytes ? fwd_all : q.bwd_bytes;
   *p = q;
   return true;
 }
@@ -165,8 +168,8 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, siz
   const int64_t Np = q.pad ? fast_pad_dim(N) : N, Kp = q.pad ? fast_pad_dim(K) : K;
   q.ldz = Np;
   q.b3_fast = q.pad || (dt == kBF16 && fast_b3_supported(M, K, N));
-  q.b3_wb = pick_generic_wb(dt, Mp, K);
-  q.b4_wb = pick_generic_wb(dt, N, K);
+  q.b3_wb = pick_generic_wb(Mp, K);
+  q.b4_wb = pick_generic_wb(N, K);
   if (q.pad) {
     q.b4_fast_rows = fast_padded_b4_rows(M, K);
     q.b4_fast = q.b4_fast_rows >= 128;
@@ -188,6 +191,12 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, siz
   q.off_dwpart = *off; *off += align256(q.parts_b > 1 ? (size_t)q.parts_b * partial_stride(N * K) * 4 : 0);
   q.off_wpad = *off; *off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_xpad = *off; *off += align256(q.stage_x ? fast_padded_x_bytes(M, K) : 0);
+  if (dt == kF32) {
+    q.s64_a = f64_plan(Mp, K, N);
+    q.s64_b = f64_plan(N, K, Mp);
+    const size_t a = f64_part_bytes(q.s64_a), b = f64_part_bytes(q.s64_b);
+    q.off_part64 = *off; *off += align256(a > b ? a : b);
+  }
   *p = q;
 }
 
@@ -301,7 +310,8 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
       launch_fast_xwt(0, M, K, N, X, false, W, Wt, b, nullptr, Zsave, false, ws + p.off_xtail, s);
     } else {
       GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
-      launch_generic_xwt(p.dt, 0, g, b, nullptr, Zsave, s);
+      if (p.dt == kF32) launch_f64(0, g, p.f1_s64, b, nullptr, Zsave, ws + p.off_part64, s);
+      else launch_generic_xwt(0, g, b, nullptr, Zsave, s);
     }
   }
   {
@@ -363,7 +373,8 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
     p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the transposed weights: the kernel reads W as it is
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) {
-    p.pad = 0; p.f1_fast = 0; p.fwd_bytes = 0;        // no room for the padded copies either: the generic kernel needs none
+    p.pad = 0; p.f1_fast = 0; p.fwd_bytes = 0;        // no room for the padded copies either: the generic kernel needs none,
+    p.f1_s64 = f64_unsplit(M, N);                     // nor the fp64 kernel, with all tiles whole
   }
   if (!forward_args_aligned(X, W, b, gamma, beta, Y, Zsave, mean, rstd)) return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;
@@ -410,7 +421,8 @@ static void launch_grad_dx(const GradPlan& p, const void* dZ, const void* W, con
     launch_fast_b3(M, K, N, dZ, p.blocked != 0, W, dX, s);
   } else {
     GemmDesc g = {dZ, W, M, K, N, p.ldz, K, true, false, p.b3_wb};
-    launch_generic_store(p.dt, g, dX, s);
+    if (p.dt == kF32) launch_f64(0, g, p.s64_a, nullptr, nullptr, dX, ws + p.off_part64, s);
+    else launch_generic_store(g, dX, s);
   }
 }
 
@@ -421,7 +433,8 @@ static void launch_grad_dw(const GradPlan& p, const void* dZ, const void* X, voi
   float* dwpart = reinterpret_cast<float*>(ws + p.off_dwpart);
   if (!p.b4_fast) {
     GemmDesc g = {dZ, X, N, K, p.M, p.ldz, K, false, false, p.b4_wb};
-    launch_generic_store(p.dt, g, dW, s);
+    if (p.dt == kF32) launch_f64(0, g, p.s64_b, nullptr, nullptr, dW, ws + p.off_part64, s);
+    else launch_generic_store(g, dW, s);
     return;
   }
   if (p.pair) {
@@ -566,7 +579,8 @@ struct ReluPlan {
   int pad;                 // padded mode of the fast contractions
   int f1_wt;               // the forward product (and its recomputation) reads the weights from a transposed copy
   GradPlan g;
-  size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, bytes;
+  F64Split f1_s64;         // fp32 storage
+  size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, off_part64, bytes;
 };
 bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   if (dt != kF32 && dt != kBF16) return false;
@@ -577,7 +591,7 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   q->pad = dt == kBF16 && fast_padded_supported(M, K, N);
   q->f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
   q->f1_fast = dt == kBF16 && fast_f1_supported(M, K, N);
-  q->f1_wb = pick_generic_wb(dt, Mp, N);
+  q->f1_wb = pick_generic_wb(Mp, N);
   const bool tiled = !q->f1_skinny;
   size_t off = 0;
   q->off_colpart = off; off += align256((size_t)colsum_groups(Mp) * N * cs);
@@ -592,6 +606,10 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   q->off_bpad = off; off += align256(tiled && q->pad ? (size_t)fast_pad_dim(N) * 4 : 0);
   q->f1_wt = tiled && q->f1_fast && M >= kTransposeFromRows;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
+  if (dt == kF32) {
+    q->f1_s64 = f64_plan(Mp, N, K);
+    q->off_part64 = off; off += align256(f64_part_bytes(q->f1_s64));
+  }
   q->bytes = off;
   return true;
 }
@@ -616,7 +634,8 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
     launch_fast_xwt(kind, M, K, N, X, false, W, Wt, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s);
   } else {
     GemmDesc g = {X, W, M, N, K, K, K, true, true, q.f1_wb};
-    launch_generic_xwt(dt, kind, g, b, aux, out, s);
+    if (dt == kF32) launch_f64(kind, g, q.f1_s64, b, aux, out, ws + q.off_part64, s);
+    else launch_generic_xwt(kind, g, b, aux, out, s);
   }
 }
 }  // namespace
@@ -749,7 +768,8 @@ struct FfnPlan {
   int down_wt;             // the down projection reads its weights from a transposed copy
   int gate_wt;             // the fused gate/up kernel reads both weight matrices from one interleaved transposed copy
   int g_blocked;           // the gated activation passes from the fused kernel to the down projection in 32 x 32 blocks
-  size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, bytes;
+  F64Split up_s64, down_s64;   // fp32 storage
+  size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, off_part64, bytes;
 };
 bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   if (dt != kF32 && dt != kBF16) return false;
@@ -757,7 +777,6 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   if (M * H > kMaxElems || M * D > kMaxElems || H * D > kMaxElems) return false;
   const size_t ts = dt == kF32 ? 4 : 2;
   const int64_t Mp = M > 0 ? M : 1;
-  auto pick_wb = [dt](int64_t I, int64_t J) { return pick_generic_wb(dt, I, J); };
   q->gate_skinny = dt == kBF16 && skinny_supported(Mp, D, 2 * H);
   q->down_skinny = dt == kBF16 && skinny_supported(Mp, H, D);
   // off the tiles: padded copies, where the padding is not most of the work nor the launches most of the time
@@ -771,8 +790,8 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   q->down_fast = dt == kBF16 && !q->gate_pad && !q->down_skinny && fast_f1_supported(M, H, D);
   q->down_pad = !q->down_fast && can_pad && (q->gate_pad || (!q->down_skinny && H % 128 == 0));
   if (q->down_pad) q->down_skinny = 0;
-  q->up_wb = pick_wb(Mp, H);
-  q->down_wb = pick_wb(Mp, D);
+  q->up_wb = pick_generic_wb(Mp, H);
+  q->down_wb = pick_generic_wb(Mp, D);
   size_t off = 0;
   const size_t mh = align256((size_t)((Mp + 255) / 256 * 256) * q->ldg * ts);
   q->off_g = off; off += mh;
@@ -787,6 +806,12 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   q->gate_wt = q->gate_fused && M >= kTransposeFromRows && H % 64 == 0 && D % 64 == 0;
   q->off_wcat = off; off += align256(q->gate_wt ? (size_t)2 * D * H * 2 : 0);
   q->g_blocked = q->gate_fused && q->down_wt && H % 32 == 0;
+  if (dt == kF32) {
+    q->up_s64 = f64_plan(Mp, H, D);
+    q->down_s64 = f64_plan(Mp, D, H);
+    const size_t a = f64_part_bytes(q->up_s64), b = f64_part_bytes(q->down_s64);
+    q->off_part64 = off; off += align256(a > b ? a : b);
+  }
   q->bytes = off;
   return true;
 }
@@ -838,9 +863,11 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     launch_fast_xwt(0, M, D, H, X, false, Wu, nullptr, nullptr, nullptr, U, false, ws + q.off_xtail, s);
   } else {
     GemmDesc g = {X, Wg, M, H, D, D, D, true, true, q.up_wb};
-    launch_generic_xwt((int)dt, 0, g, nullptr, nullptr, G, s);
+    if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, G, ws + q.off_part64, s);
+    else launch_generic_xwt(0, g, nullptr, nullptr, G, s);
     g.B = Wu;
-    launch_generic_xwt((int)dt, 0, g, nullptr, nullptr, U, s);
+    if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, U, ws + q.off_part64, s);
+    else launch_generic_xwt(0, g, nullptr, nullptr, U, s);
   }
   if (!q.gate_fused && !q.gate_skinny && !q.gate_pad) launch_silu_mul((int)dt, M * H, G, U, G, s);
   if (q.down_pad) {
@@ -853,7 +880,8 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wt, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0);
   } else {
     GemmDesc g = {G, Wd, M, D, H, H, H, true, true, q.down_wb};
-    launch_generic_xwt((int)dt, 0, g, nullptr, nullptr, Y, s);
+    if (dt == FDL_F32) launch_f64(0, g, q.down_s64, nullptr, nullptr, Y, ws + q.off_part64, s);
+    else launch_generic_xwt(0, g, nullptr, nullptr, Y, s);
   }
   return launch_status();
 }

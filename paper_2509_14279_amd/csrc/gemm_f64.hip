@@ -1,0 +1,294 @@
+// fp32-storage contractions with fp64 arithmetic, any shape and alignment:
+//
+//     C[i][j] = f( sum_r A(i,r) * B(j,r) + bias[j] )          I x J outputs, reduction length R
+//
+// the three products of the block and of Linear+ReLU and the feed-forward block's, in every operand orientation.
+//
+// Bound: the fp64 matrix rate (77 TFLOP/s measured), which v_mfma_f64_16x16x4_f64 shares with the vector ALU: whatever the
+// loop does besides MFMAs comes on top.  Hence
+//   * an element is widened once, on its way into LDS (which holds doubles), not by each wavefront that reads it;
+//   * the loop carries no bounds: rows past the end of an operand are read from its last row (their results are not
+//     stored), slices that could reach past a row or the matrix - the last one - are done apart, element by element;
+//   * a slice costs a thread two 16-byte loads from pointers that advance by a constant, eight conversions, four LDS
+//     writes, and its wavefront 16 MFMAs.
+// Workgroup: 256 threads = 4 waves (2 x 2), block tile 64 x 64, wave tile 32 x 32, slices of 16, loads two slices ahead,
+// LDS double-buffered with one barrier per slice; four workgroups per compute unit cover each other's latencies.
+//
+// A compute unit's time is the number of tiles it is dealt.  Whole rounds of 256 tiles are done as they are; the tiles of an
+// incomplete last round (all tiles of a small output) are split over the reduction in the same launch, leave fp64 sums, and
+// a second kernel adds them in order (f64_plan).
+// Measured, us (floor at 77 TFLOP/s): 8192 x 1024 x 1024 251 - 260 (223) for each orientation; 64-wide tiles whose operands
+// were widened at every read, with bounds in the loop, took 314 - 325 for 4096 x 1024 x 2048 (now 256 - 281).
+#include "common.hip.h"
+#include "internal.h"
+
+namespace fdl {
+namespace {
+
+enum { F64_STORE = 0, F64_RELU = 1, F64_MASK = 2 };
+
+struct F64Params {
+  const float* A; const float* B; float* C;
+  const float* bias;       // [J] or null
+  const float* aux;        // [I][J] (F64_MASK)
+  double* part;            // [split][split tiles][64][64]
+  int64_t lda, ldb, I, J, R;
+  int64_t rlen;            // reduction length of a part (a multiple of 16)
+  int tiles_j;
+  int whole;               // tiles done as a whole: the first of them; the others are split
+  int parted;              // tiles split
+};
+
+typedef __attribute__((ext_vector_type(2))) double f64x2;
+typedef float f32x4_e __attribute__((ext_vector_type(4), aligned(4)));
+
+// One operand's 64 x 16 slice.  RC (reduction-contiguous in memory): LDS [64][18] doubles, a thread holds four reduction
+// indices of one row; else (row index = reduction index): LDS [16][68] doubles, four consecutive i of one reduction index.
+// The pads keep a fragment's 16-byte (8-byte) reads within two lanes per bank.
+template <bool RC> struct Side {
+  static constexpr int kDoubles = RC ? 64 * 18 : 16 * 68;
+  const float* at;         // this thread's chunk of the slice fetched next
+  int64_t step;            // elements from slice to slice
+  int put;                 // its place in LDS, in doubles
+  int get[2];              // the lane's fragments (blocks 0, 1)
+
+  __device__ __forceinline__ void init(const float* base, int64_t ld, int64_t i0, int64_t I, int64_t r0, int tid, int w) {
+    const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    if (RC) {
+      int64_t row = i0 + (tid >> 2);
+      row = row < I ? row : I - 1;
+      at = base + row * ld + r0 + (tid & 3) * 4;
+      step = 16;
+      put = (tid >> 2) * 18 + (tid & 3) * 4;
+      get[0] = (w * 32 + l16) * 18 + g * 4;
+      get[1] = get[0] + 16 * 18;
+    } else {
+      int64_t col = i0 + (tid & 15) * 4;
+      col = col < I ? col : (I - 1) & ~(int64_t)3;
+      at = base + (r0 + (tid >> 4)) * ld + col;
+      step = 16 * ld;
+      put = (tid >> 4) * 68 + (tid & 15) * 4;
+      get[0] = g * 4 * 68 + w * 32 + l16;
+      get[1] = get[0] + 16;
+    }
+  }
+  __device__ __forceinline__ f32x4_e fetch() const { return *reinterpret_cast<const f32x4_e*>(at); }
+  // the chunk of the slice at r0, element by element: zeros past the end of either dimension
+  static __device__ __forceinline__ f32x4_e fetch_guarded(const float* base, int64_t ld, int64_t i0, int64_t I, int64_t r0,
+                                                          int64_t R, int tid) {
+    f32x4_e v;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int64_t i = RC ? i0 + (tid >> 2) : i0 + (tid & 15) * 4 + e;
+      const int64_t r = RC ? r0 + (tid & 3) * 4 + e : r0 + (tid >> 4);
+      v[e] = i < I && r < R ? base[RC ? i * ld + r : r * ld + i] : 0.0f;
+    }
+    return v;
+  }
+  __device__ __forceinline__ void stash(double* lds, f32x4_e v) const {
+    f64x2 lo, hi;
+    lo[0] = (double)v[0]; lo[1] = (double)v[1]; hi[0] = (double)v[2]; hi[1] = (double)v[3];
+    *reinterpret_cast<f64x2*>(lds + put) = lo;
+    *reinterpret_cast<f64x2*>(lds + put + 2) = hi;
+  }
+  __device__ __forceinline__ void frag(const double* lds, int a, double (&f)[4]) const {
+    if (RC) {
+      const f64x2 lo = *reinterpret_cast<const f64x2*>(lds + get[a]), hi = *reinterpret_cast<const f64x2*>(lds + get[a] + 2);
+      f[0] = lo[0]; f[1] = lo[1]; f[2] = hi[0]; f[3] = hi[1];
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; s++) f[s] = lds[get[a] + s * 68];
+    }
+  }
+};
+
+template <int EPI> __device__ __forceinline__ void finish_element(const F64Params& p, int64_t i, int64_t j, double z) {
+  if (EPI == F64_MASK) p.C[i * p.J + j] = z > 0.0 ? p.aux[i * p.J + j] : 0.0f;
+  else p.C[i * p.J + j] = (float)(EPI == F64_RELU ? (z > 0.0 ? z : 0.0) : z);
+}
+
+template <bool A_RC, bool B_RC, int EPI>
+__global__ __launch_bounds__(256) void gemm_f64_kernel(F64Params p) {
+  typedef Side<A_RC> SA;
+  typedef Side<B_RC> SB;
+  __shared__ __attribute__((aligned(16))) double lds[2][SA::kDoubles + SB::kDoubles];
+  // neighbouring tiles - they share operand panels - on one die (ids are dealt round-robin over 8)
+  const int id = (int)blockIdx.x, per = (p.whole + 7) / 8;
+  const bool parted = id >= per * 8;
+  const int unit = id - per * 8;                    // (part, tile) of the split tiles
+  const int pt = parted ? unit / p.parted : 0;
+  const int tile = parted ? p.whole + unit % p.parted : (id & 7) * per + (id >> 3);
+  if (!parted && tile >= p.whole) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wi = wave >> 1, wj = wave & 1;
+  const int64_t i0 = (int64_t)(tile / p.tiles_j) * 64, j0 = (int64_t)(tile % p.tiles_j) * 64;
+  const int64_t r_begin = parted ? pt * p.rlen : 0;
+  const int64_t r_end = parted && r_begin + p.rlen < p.R ? r_begin + p.rlen : p.R;
+  // Slices the loop may read with whole vectors: inside the reduction and, where a row is a reduction index and a vector
+  // may pass its end into the next row, not with the matrix's last row (a vector passes by at most three elements).
+  const bool plain = (A_RC || p.lda >= 4) && (B_RC || p.ldb >= 4);
+  const int64_t r_safe = (A_RC && B_RC) || r_end < p.R ? r_end : p.R - 1;
+  const int full = plain && r_safe > r_begin ? (int)((r_safe - r_begin) / 16) : 0;
+
+  f64x4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; a++)
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[a][b][r] = 0.0;
+  SA sa; SB sb;
+  sa.init(p.A, p.lda, i0, p.I, r_begin, tid, wi);
+  sb.init(p.B, p.ldb, j0, p.J, r_begin, tid, wj);
+  // the accumulators stay in AGPRs from slice to slice (left to itself the compiler moves all of them to VGPRs and back
+  // once per trip through the loop, on the unit that does the products)
+  auto pin = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+      for (int b = 0; b < 2; b++) asm volatile("" : "+a"(acc[a][b]));
+  };
+  pin();
+  auto multiply = [&](const double* la, const double* lb) __attribute__((always_inline)) {
+    double fa[2][4], fb[2][4];
+#pragma unroll
+    for (int a = 0; a < 2; a++) { sa.frag(la, a, fa[a]); sb.frag(lb, a, fb[a]); }
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int b = 0; b < 2; b++) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a][s], fb[b][s], acc[a][b], 0, 0, 0);
+    pin();
+  };
+
+  if (full > 0) {
+    f32x4_e ra[2], rb[2];
+    // (past the last slice the pointers stay: it is fetched again, unused)
+    int ahead = 0;
+    auto advance = [&]() __attribute__((always_inline)) {
+      const bool more = ++ahead < full;
+      sa.at += more ? sa.step : 0;
+      sb.at += more ? sb.step : 0;
+    };
+    ra[0] = sa.fetch(); rb[0] = sb.fetch(); advance();
+    ra[1] = sa.fetch(); rb[1] = sb.fetch(); advance();
+    sa.stash(lds[0], ra[0]); sb.stash(lds[0] + SA::kDoubles, rb[0]);
+    __syncthreads();
+    auto slice = [&](int k) __attribute__((always_inline)) {      // k: the LDS buffer, a constant once inlined
+      ra[k] = sa.fetch(); rb[k] = sb.fetch(); advance();
+      multiply(lds[k], lds[k] + SA::kDoubles);
+      sa.stash(lds[k ^ 1], ra[k ^ 1]); sb.stash(lds[k ^ 1] + SA::kDoubles, rb[k ^ 1]);
+      __syncthreads();
+    };
+    int s = 0;
+    for (; s + 2 <= full; s += 2) { slice(0); slice(1); }
+    if (s < full) slice(0);
+  }
+  for (int64_t r = r_begin + (int64_t)full * 16; r < r_end; r += 16) {
+    const f32x4_e va = SA::fetch_guarded(p.A, p.lda, i0, p.I, r, r_end, tid);
+    const f32x4_e vb = SB::fetch_guarded(p.B, p.ldb, j0, p.J, r, r_end, tid);
+    __syncthreads();
+    sa.stash(lds[0], va); sb.stash(lds[0] + SA::kDoubles, vb);
+    __syncthreads();
+    multiply(lds[0], lds[0] + SA::kDoubles);
+  }
+
+  // accumulator register r of lane l: output row 4 r + l / 16, column l % 16
+  if (parted) {
+    double* out = p.part + ((int64_t)pt * p.parted + (tile - p.whole)) * 4096;
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+          out[(wi * 32 + a * 16 + r * 4 + (lane >> 4)) * 64 + wj * 32 + b * 16 + (lane & 15)] = acc[a][b][r];
+    return;
+  }
+#pragma unroll
+  for (int b = 0; b < 2; b++) {
+    const int64_t j = j0 + wj * 32 + b * 16 + (lane & 15);
+    if (j >= p.J) continue;
+    const double bias = p.bias != nullptr ? (double)p.bias[j] : 0.0;
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int64_t i = i0 + wi * 32 + a * 16 + r * 4 + (lane >> 4);
+        if (i >= p.I) continue;
+        finish_element<EPI>(p, i, j, acc[a][b][r] + bias);
+      }
+  }
+}
+
+// the split tiles' outputs: the parts' sums in order, then as above; four workgroups per tile, four columns per thread
+template <int EPI>
+__global__ __launch_bounds__(256) void f64_reduce_kernel(F64Params p, int split) {
+  const int t = (int)blockIdx.x >> 2, tile = p.whole + t;
+  const int at = ((int)blockIdx.x & 3) * 1024 + (int)threadIdx.x * 4;
+  const int64_t i = (int64_t)(tile / p.tiles_j) * 64 + at / 64, j = (int64_t)(tile % p.tiles_j) * 64 + at % 64;
+  if (i >= p.I || j >= p.J) return;
+  f64x4 z = *reinterpret_cast<const f64x4*>(p.part + (int64_t)t * 4096 + at);
+  for (int k = 1; k < split; k++) {
+    const f64x4 x = *reinterpret_cast<const f64x4*>(p.part + ((int64_t)k * p.parted + t) * 4096 + at);
+#pragma unroll
+    for (int e = 0; e < 4; e++) z[e] += x[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; e++)
+    if (j + e < p.J) finish_element<EPI>(p, i, j + e, z[e] + (p.bias != nullptr ? (double)p.bias[j + e] : 0.0));
+}
+
+template <int EPI> void dispatch_f64(const GemmDesc& g, const F64Params& p, int split, hipStream_t s) {
+  const dim3 grid((unsigned)((p.whole + 7) / 8 * 8 + p.parted * split));
+  auto kern = g.a_rc ? (g.b_rc ? gemm_f64_kernel<true, true, EPI> : gemm_f64_kernel<true, false, EPI>)
+                     : (g.b_rc ? gemm_f64_kernel<false, true, EPI> : gemm_f64_kernel<false, false, EPI>);
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
+  if (p.parted > 0) hipLaunchKernelGGL(f64_reduce_kernel<EPI>, dim3((unsigned)p.parted * 4), dim3(256), 0, s, p, split);
+}
+
+}  // namespace
+
+// Which tiles are split, and into how many parts.  A compute unit works through what it is dealt at about 0.52 us per slice
+// of 16, a workgroup alone on it at 0.68, one with little company at 0.58 (0.75 for the stragglers of an incomplete last
+// round behind four full ones); the second kernel costs about 4 us, the sums' traffic 6 ns per part of a tile.  Either the tiles of the last round are split,
+// or all of them.  Measured, us, without / with the split: 3001 x 771 x 1537 by reduction over 771 (1175 tiles) 143 / 133,
+// over 1537 (611) 166 / 140, over 3001 (325, all in 3 parts) 199 / 148; 256^3 (16 tiles, 8 parts) 14.5 / 11; 512^3 24.5 / 16;
+// 128 x 4096 x 1024 (32 tiles) 159 / 30.  The plan must not depend on the device: 256 compute units.
+F64Split f64_plan(int64_t I, int64_t J, int64_t R) {
+  const int64_t tiles = ((I + 63) / 64) * ((J + 63) / 64), slices = (R + 15) / 16;
+  const int64_t full = tiles / 256, rest = tiles % 256;
+  F64Split best = {tiles, 0, 1};
+  double best_cost = (double)slices * ((full == 1 && rest == 0 ? 0.68 : full * 0.52) + (rest == 0 ? 0.0 : (full >= 4 ? 0.75 : (full == 0 ? 0.68 : 0.55))));
+  for (int split = 2; split <= 16 && split <= slices; split++)
+    for (int all = 0; all < 2; all++) {
+      const int64_t rounds = all ? 0 : full, parted = tiles - rounds * 256, units = parted * split;
+      if (units == 0 || units > 8192 || (all && full == 0)) continue;
+      const int64_t more = (units + 255) / 256, len = (slices + split - 1) / split;
+      double cost = (double)(rounds * slices + more * len) * (rounds + more == 1 ? 0.68 : (rounds == 1 ? 0.58 : 0.52));
+      if (rounds > 0 && cost < slices * 0.68) cost = slices * 0.68;
+      cost += 4.0 + units * 0.006 + split * 0.15;
+      if (cost < (best.split == 1 ? 0.97 : 1.0) * best_cost) { best.whole = rounds * 256; best.parted = parted; best.split = split; best_cost = cost; }
+    }
+  return best;
+}
+size_t f64_part_bytes(const F64Split& q) { return q.split > 1 ? (size_t)q.parted * q.split * 4096 * 8 : 0; }
+
+// kind 0 plain (bias may be null), 1 max(., 0), 2 aux where the sum is positive else 0; part: f64_part_bytes(q) of scratch,
+// q from f64_plan(I, J, R) or {tiles, 0, 1}
+void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
+                hipStream_t s) {
+  F64Params p = {};
+  p.A = (const float*)g.A; p.B = (const float*)g.B; p.C = (float*)C; p.bias = bias; p.aux = (const float*)aux;
+  p.part = (double*)part;
+  p.lda = g.lda; p.ldb = g.ldb; p.I = g.I; p.J = g.J; p.R = g.R;
+  p.tiles_j = (int)((g.J + 63) / 64);
+  p.whole = (int)q.whole; p.parted = (int)q.parted;
+  const int64_t slices = (g.R + 15) / 16;
+  p.rlen = (slices + q.split - 1) / q.split * 16;
+  if (kind == 1) dispatch_f64<F64_RELU>(g, p, q.split, s);
+  else if (kind == 2) dispatch_f64<F64_MASK>(g, p, q.split, s);
+  else dispatch_f64<F64_STORE>(g, p, q.split, s);
+}
+
+}  // namespace fdl

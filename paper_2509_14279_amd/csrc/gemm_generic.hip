@@ -1,4 +1,4 @@
-// Generic MFMA GEMM for the fused dense-layer block: any shape, any alignment, both storage types.
+// Generic MFMA GEMM for the fused dense-layer block: any shape, any alignment, bf16 storage.
 //
 //     C[i][j] = sum_r A(i,r) * B(j,r)          I x J outputs, reduction length R
 //
@@ -10,12 +10,10 @@
 // "Highlighted CUDA Kernels: Code", done here on the matrix cores instead of one thread or warp per
 // output element).
 //
-// Storage fp32  -> operands widened to fp64 in registers, v_mfma_f64_16x16x4_f64, fp64 accumulators.
-// Storage bf16  -> operands widened to fp32 at the global load (one LDS layout for both storage types), packed back
-//                  to bf16 at the fragment (exact), v_mfma_f32_16x16x16_bf16, fp32 accumulators.
-// A lane's fragment is the four reduction indices 4*(lane/16)+s, s = 0..3, of a 16-deep slice for A and B alike
-// (row/col = lane%16): four steps of the fp64 instruction, which takes one value per lane and step, or the
-// operand of one bf16 instruction; an r-contiguous operand is read from LDS with one 16-byte read per fragment.
+// Operands are widened to fp32 at the global load and packed back to bf16 at the fragment (exact):
+// v_mfma_f32_16x16x16_bf16, fp32 accumulators.  A lane's fragment is the four reduction indices 4*(lane/16)+s, s = 0..3, of
+// a 16-deep slice for A and B alike (row/col = lane%16), the operand of one instruction; an r-contiguous operand is read
+// from LDS with one 16-byte read per fragment.
 //
 // Workgroup: 256 threads = 4 waves as 2x2; wave tile (16*WB)^2; block tile (32*WB)^2; 16-deep reduction
 // slices, double-buffered in LDS with the global loads of the next two slices in flight during the MFMAs.
@@ -39,29 +37,8 @@ struct GemmParams {
 };
 
 template <class AccT> struct Mma;
-// fp64: v_mfma_f64_16x16x4_f64.  (Four v_mfma_f64_4x4x4_4b with the B fragment rotated by blocks of four lanes
-// compute the same product; over the chip that form sustains 70 TFLOP/s against 77 for this one, measured with the
-// accumulators held in AGPRs, and in this kernel it ran 20 % slower.)
-template <> struct Mma<double> {
-  typedef f64x4 acc_t;
-  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)b, c, 0, 0, 0);
-  }
-  // the lane's four reduction steps of a 16-deep slice
-  static __device__ __forceinline__ acc_t mma4(const float (&a)[4], const float (&b)[4], acc_t c) {
-#pragma unroll
-    for (int s = 0; s < 4; s++) c = mma(a[s], b[s], c);
-    return c;
-  }
-  // accumulator register r of lane l holds output row 4r + l/16, column l%16
-  static __device__ __forceinline__ int row(int lane, int r) { return r * 4 + (lane >> 4); }
-  static __device__ __forceinline__ int col(int lane, int) { return lane & 15; }
-};
 template <> struct Mma<float> {
   typedef f32x4 acc_t;
-  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
   // The values are bf16 numbers widened to fp32 on their way through LDS, so packing the lane's four reduction
   // steps back into bf16 is exact and one v_mfma_f32_16x16x16_bf16 (k = 4 (lane/16) + e, the same assignment of
   // reduction indices to lanes) does the work of four fp32 steps at sixteen times the rate.
@@ -78,10 +55,6 @@ template <> struct Mma<float> {
 };
 
 template <class T> __device__ __forceinline__ void load4(const T* p, float (&v)[4]);
-template <> __device__ __forceinline__ void load4<float>(const float* p, float (&v)[4]) {
-  const f32x4 t = *reinterpret_cast<const f32x4*>(p);
-  v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3];
-}
 template <> __device__ __forceinline__ void load4<bf16_t>(const bf16_t* p, float (&v)[4]) {
   const bf16x4 t = *reinterpret_cast<const bf16x4*>(p);
   v[0] = (float)t[0]; v[1] = (float)t[1]; v[2] = (float)t[2]; v[3] = (float)t[3];
@@ -90,11 +63,6 @@ template <> __device__ __forceinline__ void load4<bf16_t>(const bf16_t* p, float
 // the same from an address that is only element-aligned (rows of a ragged matrix start anywhere): the compiler picks
 // the widest load the target allows for the stated alignment
 template <class T> __device__ __forceinline__ void load4u(const T* p, float (&v)[4]);
-template <> __device__ __forceinline__ void load4u<float>(const float* p, float (&v)[4]) {
-  typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
-  const f32x4_u t = *reinterpret_cast<const f32x4_u*>(p);
-  v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3];
-}
 template <> __device__ __forceinline__ void load4u<bf16_t>(const bf16_t* p, float (&v)[4]) {
   typedef __bf16 bf16x4_u __attribute__((ext_vector_type(4), aligned(2)));
   const bf16x4_u t = *reinterpret_cast<const bf16x4_u*>(p);
@@ -375,24 +343,20 @@ void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s) {
 
 // C[i][j] = f(sum_r A(i,r) B(j,r) + bias[j]), both operands reduction-contiguous (the forward product's orientation):
 // kind 0 plain (bias may be null), 1 max(., 0), 2 aux[i][j] where the sum is positive else 0
-void launch_generic_xwt(int dt, int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s) {
+void launch_generic_xwt(int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s) {
   GemmParams p = base_params(g);
   p.C = C; p.bias = bias; p.aux = aux;
-  set_vec(&p, g, true, true, dt == kF32 ? 4 : 2);
+  set_vec(&p, g, true, true, 2);
   const bool big = g.wb == 4;
 #define FDL_GX(T, EPI) do { if (big) launch_one<T, true, true, 4, EPI>(p, s); else launch_one<T, true, true, 2, EPI>(p, s); } while (0)
-  if (dt == kF32) {
-    if (kind == 1) FDL_GX(float, EPI_RELU); else if (kind == 2) FDL_GX(float, EPI_MASK); else FDL_GX(float, EPI_STORE);
-  } else {
-    if (kind == 1) FDL_GX(bf16_t, EPI_RELU); else if (kind == 2) FDL_GX(bf16_t, EPI_MASK); else FDL_GX(bf16_t, EPI_STORE);
-  }
+  if (kind == 1) FDL_GX(bf16_t, EPI_RELU); else if (kind == 2) FDL_GX(bf16_t, EPI_MASK); else FDL_GX(bf16_t, EPI_STORE);
 #undef FDL_GX
 }
 
-void launch_generic_store(int dt, const GemmDesc& g, void* C, hipStream_t s) {
+void launch_generic_store(const GemmDesc& g, void* C, hipStream_t s) {
   GemmParams p = base_params(g);
   p.C = C;
-  if (dt == kF32) dispatch<float, EPI_STORE>(g, p, s); else dispatch<bf16_t, EPI_STORE>(g, p, s);
+  dispatch<bf16_t, EPI_STORE>(g, p, s);
 }
 
 }  // namespace fdl

@@ -17,6 +17,9 @@ namespace fdl {
 
 enum DType { kF32 = 0, kBF16 = 1 };
 
+// How a product in fp64 is dealt out (gemm_f64.hip): tiles done as a whole, tiles split into `split` parts
+struct F64Split { int64_t whole, parted; int split; };
+
 // The two contractions that end a backward pass: dX [M,K] = dZ W, dW [N,K] = dZ^T X.
 struct GradPlan {
   int dt;
@@ -36,6 +39,8 @@ struct GradPlan {
   size_t off_dxpart;      // float [split_a][M][K]   (split_a > 1)
   size_t off_dwpart;      // float [parts_b][N][K]   (parts_b > 1)
   size_t off_wpad, off_xpad;   // zero-padded copies of W and (stage_x) X
+  F64Split s64_a, s64_b;  // fp32 storage: dX, dW
+  size_t off_part64;      // their split tiles' sums, one after the other
 };
 
 struct Plan {
@@ -47,6 +52,8 @@ struct Plan {
   int f1_wb;              // generic kernel: 16x16 blocks per wave tile side (wave tile = 16*wb)
   int f1_wt;              // 1: the fast kernel reads the weights from a transposed copy (large batches)
   size_t off_wt;          // bf16 [K][N], the last region of the forward workspace
+  F64Split f1_s64;        // fp32 storage
+  size_t off_part64;
   size_t fwd_bytes;       // (without the transposed weights: fwd_bytes - align256(N K 2), see fwd_bytes_plain)
   size_t fwd_bytes_plain; // forward workspace of the same plan with f1_wt = 0
   size_t static_need;     // what fdl_forward_static compares with its array (the header's rule)
@@ -84,7 +91,7 @@ constexpr int kMaxDevices = 64;
 struct OnceFlags { std::atomic<unsigned char> done[kMaxDevices]; };
 bool ensure_dynamic_lds(const void* kernel, int bytes, OnceFlags* flags);
 
-// ---- generic MFMA GEMM: C[i][j] = sum_r A(i,r) B(j,r), any shape, any alignment -----------------
+// ---- generic bf16 MFMA GEMM: C[i][j] = sum_r A(i,r) B(j,r), any shape, any alignment ------------
 // a_rc / b_rc: the operand is contiguous along the reduction index r (element (i,r) at A[i*ld + r]);
 // otherwise it is contiguous along i (element (i,r) at A[r*ld + i]).
 struct GemmDesc {
@@ -95,11 +102,17 @@ struct GemmDesc {
   int wb;
 };
 // forward-product orientation with an optional bias and a ReLU or ReLU-mask epilogue (sibling operators)
-void launch_generic_xwt(int dt, int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s);
-// plain store: C [I][J] in the storage type
-void launch_generic_store(int dt, const GemmDesc& g, void* C, hipStream_t s);
+void launch_generic_xwt(int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s);
+// plain store: C [I][J]
+void launch_generic_store(const GemmDesc& g, void* C, hipStream_t s);
 // plain store of the fp32 accumulators: C [I][J] float (bf16 storage; a partial sum for launch_finish)
 void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s);
+
+// ---- fp32-storage contractions in fp64 (gemm_f64.hip): GemmDesc as above, any shape ---------------
+F64Split f64_plan(int64_t I, int64_t J, int64_t R);
+size_t f64_part_bytes(const F64Split& q);
+void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
+                hipStream_t s);
 
 // ---- row-wise / column-wise phases ------------------------------------------------------------
 // row statistics of GELU(Zsave) and the normalised output (Zsave and Y may be the same buffer)
