@@ -194,8 +194,8 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, siz
   if (dt == kF32) {
     q.s64_a = f64_plan(Mp, K, N);
     q.s64_b = f64_plan(N, K, Mp);
-    const size_t a = f64_part_bytes(q.s64_a), b = f64_part_bytes(q.s64_b);
-    q.off_part64 = *off; *off += align256(a > b ? a : b);
+    q.off_part64_a = *off; *off += align256(f64_part_bytes(q.s64_a));
+    q.off_part64_b = *off; *off += align256(f64_part_bytes(q.s64_b));
   }
   *p = q;
 }
@@ -401,7 +401,17 @@ static void sum_later(TailSums* tj, int k, const void* part, int parts, int64_t 
   tj->part[k] = static_cast<const float*>(part); tj->parts[k] = parts; tj->n[k] = n; tj->out[k] = out;
 }
 
-// dX = dZ W; where both contractions share a launch (p.pair), dW too
+// fp32 storage: the operands of the launch that both contractions share
+static F64Grads grad_f64(const GradPlan& p, const void* dZ, const void* W, const void* X, void* dX, void* dW, char* ws) {
+  F64Grads a = {};
+  a.dx = {dZ, W, p.M, p.K, p.N, p.ldz, p.K, true, false, 2};
+  a.dw = {dZ, X, p.N, p.K, p.M, p.ldz, p.K, false, false, 2};
+  a.qx = p.s64_a; a.qw = p.s64_b;
+  a.dX = dX; a.partx = ws + p.off_part64_a; a.dW = dW; a.partw = ws + p.off_part64_b;
+  return a;
+}
+
+// bf16 storage: dX = dZ W; where both contractions share a launch (p.pair), dW too
 static void launch_grad_dx(const GradPlan& p, const void* dZ, const void* W, const void* X, void* dX, void* dW, char* ws,
                            TailSums* tj, hipStream_t s) {
   const int64_t M = p.M, K = p.K, N = p.N;
@@ -421,8 +431,7 @@ static void launch_grad_dx(const GradPlan& p, const void* dZ, const void* W, con
     launch_fast_b3(M, K, N, dZ, p.blocked != 0, W, dX, s);
   } else {
     GemmDesc g = {dZ, W, M, K, N, p.ldz, K, true, false, p.b3_wb};
-    if (p.dt == kF32) launch_f64(0, g, p.s64_a, nullptr, nullptr, dX, ws + p.off_part64, s);
-    else launch_generic_store(g, dX, s);
+    launch_generic_store(g, dX, s);
   }
 }
 
@@ -433,8 +442,7 @@ static void launch_grad_dw(const GradPlan& p, const void* dZ, const void* X, voi
   float* dwpart = reinterpret_cast<float*>(ws + p.off_dwpart);
   if (!p.b4_fast) {
     GemmDesc g = {dZ, X, N, K, p.M, p.ldz, K, false, false, p.b4_wb};
-    if (p.dt == kF32) launch_f64(0, g, p.s64_b, nullptr, nullptr, dW, ws + p.off_part64, s);
-    else launch_generic_store(g, dW, s);
+    launch_generic_store(g, dW, s);
     return;
   }
   if (p.pair) {
@@ -500,9 +508,16 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
   TailSums tj = {};
   tj.colpart = static_cast<const float*>(colpart); tj.groups = p.b1_groups; tj.N = N; tj.kinds = 3;
   tj.col_out[0] = dbeta; tj.col_out[1] = dgamma; tj.col_out[2] = db;
+  if (dt == FDL_F32) {
+    const F64Grads a = grad_f64(p.g, dZ, W, X, dX, dW, ws);
+    { PhaseTimer t(FDL_PHASE_B2, s); }      // (the column sums are finished with the contractions')
+    { PhaseTimer t(FDL_PHASE_B3, s); launch_f64_grads(a, s); }
+    { PhaseTimer t(FDL_PHASE_B4, s); launch_f64_grads_finish(a, tj, s); }
+    return launch_status();
+  }
   {
     PhaseTimer t(FDL_PHASE_B2, s);
-    if (!tail) launch_b2((int)dt, N, p.b1_groups, colpart, dbeta, dgamma, db, s);
+    if (!tail) launch_b2(N, p.b1_groups, colpart, dbeta, dgamma, db, s);
   }
   if (p.g.pad) {
     StageJobs j = {};
@@ -714,7 +729,13 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
   const bool tail = grad_leaves_sums(q.g);
   TailSums tj = {};
   tj.colpart = static_cast<const float*>(colpart); tj.groups = colsum_groups(M); tj.N = N; tj.kinds = 1; tj.col_out[0] = db;
-  if (!tail) launch_colsum_finish((int)dt, M, N, colpart, db, s);
+  if (dt == FDL_F32) {
+    const F64Grads a = grad_f64(q.g, G, W, X, dX, dW, ws);
+    launch_f64_grads(a, s);
+    launch_f64_grads_finish(a, tj, s);
+    return launch_status();
+  }
+  if (!tail) launch_colsum_finish(M, N, colpart, db, s);
   launch_grad_dx(q.g, G, W, X, dX, dW, ws, &tj, s);
   launch_grad_dw(q.g, G, X, dW, ws, &tj, s);
   if (tail) launch_finish(tj, s);

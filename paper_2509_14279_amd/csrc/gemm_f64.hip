@@ -107,13 +107,17 @@ template <int EPI> __device__ __forceinline__ void finish_element(const F64Param
   else p.C[i * p.J + j] = (float)(EPI == F64_RELU ? (z > 0.0 ? z : 0.0) : z);
 }
 
+constexpr int kF64LdsDoubles = 2 * 2 * Side<true>::kDoubles;      // two slices of both operands, the larger layout
+inline int f64_units(const F64Params& p, int split) { return (p.whole + 7) / 8 * 8 + p.parted * split; }
+
+// unit `id` of a product (f64_units of them)
 template <bool A_RC, bool B_RC, int EPI>
-__global__ __launch_bounds__(256) void gemm_f64_kernel(F64Params p) {
+__device__ __forceinline__ void f64_unit(const F64Params& p, const int id, double* smem) {
   typedef Side<A_RC> SA;
   typedef Side<B_RC> SB;
-  __shared__ __attribute__((aligned(16))) double lds[2][SA::kDoubles + SB::kDoubles];
+  double* lds[2] = {smem, smem + SA::kDoubles + SB::kDoubles};
   // neighbouring tiles - they share operand panels - on one die (ids are dealt round-robin over 8)
-  const int id = (int)blockIdx.x, per = (p.whole + 7) / 8;
+  const int per = (p.whole + 7) / 8;
   const bool parted = id >= per * 8;
   const int unit = id - per * 8;                    // (part, tile) of the split tiles
   const int pt = parted ? unit / p.parted : 0;
@@ -221,11 +225,24 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(F64Params p) {
   }
 }
 
-// the split tiles' outputs: the parts' sums in order, then as above; four workgroups per tile, four columns per thread
-template <int EPI>
-__global__ __launch_bounds__(256) void f64_reduce_kernel(F64Params p, int split) {
-  const int t = (int)blockIdx.x >> 2, tile = p.whole + t;
-  const int at = ((int)blockIdx.x & 3) * 1024 + (int)threadIdx.x * 4;
+template <bool A_RC, bool B_RC, int EPI>
+__global__ __launch_bounds__(256) void gemm_f64_kernel(F64Params p) {
+  __shared__ __attribute__((aligned(16))) double lds[kF64LdsDoubles];
+  f64_unit<A_RC, B_RC, EPI>(p, (int)blockIdx.x, lds);
+}
+
+// dX = dZ W and dW = dZ^T X side by side in one launch (launch_f64_grads says where).  dW comes
+// first (its reduction, over the batch, is usually the longer one).
+__global__ __launch_bounds__(256) void gemm_f64_pair_kernel(F64Params dx, F64Params dw, int dw_units) {
+  __shared__ __attribute__((aligned(16))) double lds[kF64LdsDoubles];
+  const int id = (int)blockIdx.x;
+  if (id < dw_units) f64_unit<false, false, F64_STORE>(dw, id, lds);
+  else f64_unit<true, false, F64_STORE>(dx, id - dw_units, lds);
+}
+
+// the split tiles' outputs: the parts' sums in order, then as above; 1024 elements of a tile from `at`, four per thread
+template <int EPI> __device__ __forceinline__ void f64_reduce_tile(const F64Params& p, int split, int t, int at) {
+  const int tile = p.whole + t;
   const int64_t i = (int64_t)(tile / p.tiles_j) * 64 + at / 64, j = (int64_t)(tile % p.tiles_j) * 64 + at % 64;
   if (i >= p.I || j >= p.J) return;
   f64x4 z = *reinterpret_cast<const f64x4*>(p.part + (int64_t)t * 4096 + at);
@@ -239,11 +256,39 @@ __global__ __launch_bounds__(256) void f64_reduce_kernel(F64Params p, int split)
     if (j + e < p.J) finish_element<EPI>(p, i, j + e, z[e] + (p.bias != nullptr ? (double)p.bias[j + e] : 0.0));
 }
 
-template <int EPI> void dispatch_f64(const GemmDesc& g, const F64Params& p, int split, hipStream_t s) {
-  const dim3 grid((unsigned)((p.whole + 7) / 8 * 8 + p.parted * split));
+// four workgroups per tile
+template <int EPI>
+__global__ __launch_bounds__(256) void f64_reduce_kernel(F64Params p, int split) {
+  f64_reduce_tile<EPI>(p, split, (int)blockIdx.x >> 2, ((int)blockIdx.x & 3) * 1024 + (int)threadIdx.x * 4);
+}
+
+// The end of a backward pass in one launch: the split tiles of dX and dW, a workgroup per tile, then the column sums
+// (j.kinds ceil(N / 64) workgroups, as b2_kernel).
+__global__ __launch_bounds__(1024) void f64_finish_kernel(F64Params dx, int split_x, F64Params dw, int split_w, TailSums j) {
+  __shared__ double red[16][64];
+  int id = (int)blockIdx.x;
+  if (id < dw.parted) { f64_reduce_tile<F64_STORE>(dw, split_w, id, (int)threadIdx.x * 4); return; }
+  id -= dw.parted;
+  if (id < dx.parted) { f64_reduce_tile<F64_STORE>(dx, split_x, id, (int)threadIdx.x * 4); return; }
+  id -= dx.parted;
+  const int cblocks = (int)((j.N + 63) / 64), which = id / cblocks;
+  b2_columns<double>(j.N, j.groups, j.kinds, reinterpret_cast<const double*>(j.colpart), id % cblocks, which,
+                     which == 0 ? j.col_out[0] : (which == 1 ? j.col_out[1] : j.col_out[2]), red);
+}
+
+// Units that are resident at once (four workgroups on each of 256 compute units): the two gradient products share a launch
+// up to here - small layers, which are bound by the launches (256^3: step 45 -> 31 us).  Beyond, each product's own rounds
+// are the better schedule (758 x 2048 x 2304: step 398 us with two launches, 427 with one).
+constexpr int kF64Resident = 1024;
+
+template <int EPI> void dispatch_f64_main(const GemmDesc& g, const F64Params& p, int split, hipStream_t s) {
+  const dim3 grid((unsigned)f64_units(p, split));
   auto kern = g.a_rc ? (g.b_rc ? gemm_f64_kernel<true, true, EPI> : gemm_f64_kernel<true, false, EPI>)
                      : (g.b_rc ? gemm_f64_kernel<false, true, EPI> : gemm_f64_kernel<false, false, EPI>);
   hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
+}
+template <int EPI> void dispatch_f64(const GemmDesc& g, const F64Params& p, int split, hipStream_t s) {
+  dispatch_f64_main<EPI>(g, p, split, s);
   if (p.parted > 0) hipLaunchKernelGGL(f64_reduce_kernel<EPI>, dim3((unsigned)p.parted * 4), dim3(256), 0, s, p, split);
 }
 
@@ -276,8 +321,7 @@ size_t f64_part_bytes(const F64Split& q) { return q.split > 1 ? (size_t)q.parted
 
 // kind 0 plain (bias may be null), 1 max(., 0), 2 aux where the sum is positive else 0; part: f64_part_bytes(q) of scratch,
 // q from f64_plan(I, J, R) or {tiles, 0, 1}
-void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
-                hipStream_t s) {
+static F64Params f64_params(const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part) {
   F64Params p = {};
   p.A = (const float*)g.A; p.B = (const float*)g.B; p.C = (float*)C; p.bias = bias; p.aux = (const float*)aux;
   p.part = (double*)part;
@@ -286,9 +330,31 @@ void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bia
   p.whole = (int)q.whole; p.parted = (int)q.parted;
   const int64_t slices = (g.R + 15) / 16;
   p.rlen = (slices + q.split - 1) / q.split * 16;
+  return p;
+}
+void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
+                hipStream_t s) {
+  const F64Params p = f64_params(g, q, bias, aux, C, part);
   if (kind == 1) dispatch_f64<F64_RELU>(g, p, q.split, s);
   else if (kind == 2) dispatch_f64<F64_MASK>(g, p, q.split, s);
   else dispatch_f64<F64_STORE>(g, p, q.split, s);
+}
+
+// dX (rows of dZ times W) and dW (columns of dZ times X); launch_f64_grads_finish ends both, and the column sums
+void launch_f64_grads(const F64Grads& a, hipStream_t s) {
+  const F64Params dx = f64_params(a.dx, a.qx, nullptr, nullptr, a.dX, a.partx), dw = f64_params(a.dw, a.qw, nullptr, nullptr, a.dW, a.partw);
+  const int nw = f64_units(dw, a.qw.split), nx = f64_units(dx, a.qx.split);
+  if (nw + nx > kF64Resident) {
+    dispatch_f64_main<F64_STORE>(a.dx, dx, a.qx.split, s);
+    dispatch_f64_main<F64_STORE>(a.dw, dw, a.qw.split, s);
+    return;
+  }
+  hipLaunchKernelGGL(gemm_f64_pair_kernel, dim3((unsigned)(nw + nx)), dim3(256), 0, s, dx, dw, nw);
+}
+void launch_f64_grads_finish(const F64Grads& a, const TailSums& j, hipStream_t s) {
+  const F64Params dx = f64_params(a.dx, a.qx, nullptr, nullptr, a.dX, a.partx), dw = f64_params(a.dw, a.qw, nullptr, nullptr, a.dW, a.partw);
+  const unsigned blocks = (unsigned)(dx.parted + dw.parted) + (unsigned)j.kinds * (unsigned)((j.N + 63) / 64);
+  hipLaunchKernelGGL(f64_finish_kernel, dim3(blocks), dim3(1024), 0, s, dx, a.qx.split, dw, a.qw.split, j);
 }
 
 }  // namespace fdl

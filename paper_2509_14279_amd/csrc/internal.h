@@ -40,7 +40,7 @@ struct GradPlan {
   size_t off_dwpart;      // float [parts_b][N][K]   (parts_b > 1)
   size_t off_wpad, off_xpad;   // zero-padded copies of W and (stage_x) X
   F64Split s64_a, s64_b;  // fp32 storage: dX, dW
-  size_t off_part64;      // their split tiles' sums, one after the other
+  size_t off_part64_a, off_part64_b;   // their split tiles' sums
 };
 
 struct Plan {
@@ -133,8 +133,8 @@ void launch_zero_cols_bf16(void* dZ, int64_t M, int64_t N, int64_t ldz, hipStrea
 // blocked: dZ is written as [M / 32][N / 32] blocks of 32 x 32 elements (bf16, M and N multiples of 32, ldz = N)
 void launch_b1_fused(int dt, int64_t M, int64_t N, int64_t ldz, int groups, bool blocked, const void* dY, const void* Zsave,
                      const float* gamma, const float* mean, const float* rstd, void* dZ, void* colpart, hipStream_t s);
-void launch_b2(int dt, int64_t N, int groups, const void* colpart, float* dbeta, float* dgamma, float* db,
-               hipStream_t s);
+// bf16 storage
+void launch_b2(int64_t N, int groups, const void* colpart, float* dbeta, float* dgamma, float* db, hipStream_t s);
 // bf16: the column sums (as launch_b2) and up to two sums of fp32 split-reduction partials
 // (out[k][i] = bf16(sum over q < parts[k] of part[k][q * partial_stride(n[k]) + i]); parts[k] = 0: none) in one launch
 struct TailSums {
@@ -151,6 +151,11 @@ struct TailSums {
   float* col_out[3];
 };
 void launch_finish(TailSums j, hipStream_t s);
+// fp32 storage: both gradient contractions in one launch; then their split tiles' sums and the column sums (j.colpart holds
+// doubles, j's split products unused) in another
+struct F64Grads { GemmDesc dx, dw; F64Split qx, qw; void *dX, *partx, *dW, *partw; };
+void launch_f64_grads(const F64Grads& a, hipStream_t s);
+void launch_f64_grads_finish(const F64Grads& a, const TailSums& j, hipStream_t s);
 
 // ---- sibling operators' row-wise / element-wise kernels ------------------------------------------
 void launch_layernorm(int dt, int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta,
@@ -159,7 +164,7 @@ void launch_rmsnorm(int dt, int64_t M, int64_t N, float eps, const void* A, cons
 int colsum_groups(int64_t M);
 // ldg: pitch of G; blocked: G is stored in 32 x 32 blocks (bf16; M, N multiples of 32)
 void launch_colsum_partial(int dt, int64_t M, int64_t N, int64_t ldg, const void* G, bool blocked, void* colpart, hipStream_t s);
-void launch_colsum_finish(int dt, int64_t M, int64_t N, const void* colpart, float* out, hipStream_t s);
+void launch_colsum_finish(int64_t M, int64_t N, const void* colpart, float* out, hipStream_t s);
 void launch_silu_mul(int dt, int64_t n, const void* G, const void* U, void* H, hipStream_t s);
 
 // ---- bf16 products with few rows (gemm_skinny.hip): any K and N -----------------------------------

@@ -593,48 +593,15 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
 }
 
 // ------------------------------------------------------------------------------------------------
-// B2: colpart [groups][3][N] -> dbeta, dgamma, db.  64 consecutive columns per workgroup (coalesced), the groups
-// dealt over the 16 wavefronts, eight loads in flight per thread
-// (the phase is pure latency: a few tens of MB), fp64 sums in a fixed order.
-// (nwhich = gridDim.y kinds of partial per group, colpart [groups][nwhich][N]; kind w goes to out_w)
-template <class C>
-__device__ __forceinline__ void b2_columns(int64_t N, int groups, int nwhich, const C* __restrict__ colpart, int cblock,
-                                           int which, float* __restrict__ out, double (*red)[64]) {
-  constexpr int kSlices = 16;
-  const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
-  const int64_t col = (int64_t)cblock * 64 + lane;
-  double a[4] = {0.0, 0.0, 0.0, 0.0};
-  if (col < N) {
-    const C* src = colpart + (int64_t)which * N + col;
-    const int64_t gstride = (int64_t)nwhich * N;
-    int g = slice;
-    for (; g + 7 * kSlices < groups; g += 8 * kSlices) {
-      C v[8];
-#pragma unroll
-      for (int e = 0; e < 8; e++) v[e] = src[(int64_t)(g + e * kSlices) * gstride];
-#pragma unroll
-      for (int e = 0; e < 8; e++) a[e & 3] += (double)v[e];
-    }
-    for (; g < groups; g += kSlices) a[0] += (double)src[(int64_t)g * gstride];
-  }
-  red[slice][lane] = (a[0] + a[1]) + (a[2] + a[3]);
-  __syncthreads();
-  if (slice == 0 && col < N) {
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < kSlices; w++) t += red[w][lane];
-    out[col] = (float)t;
-  }
-}
-
-template <class C>
-__global__ __launch_bounds__(1024) void b2_kernel(int64_t N, int groups, const C* __restrict__ colpart,
+// B2: colpart [groups][3][N] -> dbeta, dgamma, db (b2_columns) in a launch of its own (bf16 storage; the fp32 path ends
+// with f64_finish_kernel).
+__global__ __launch_bounds__(1024) void b2_kernel(int64_t N, int groups, const float* __restrict__ colpart,
                                                   float* __restrict__ dbeta, float* __restrict__ dgamma,
                                                   float* __restrict__ db) {
   __shared__ double red[16][64];
   const int which = blockIdx.y;
-  b2_columns<C>(N, groups, (int)gridDim.y, colpart, (int)blockIdx.x, which,
-                which == 0 ? dbeta : (which == 1 ? dgamma : db), red);
+  b2_columns<float>(N, groups, (int)gridDim.y, colpart, (int)blockIdx.x, which,
+                    which == 0 ? dbeta : (which == 1 ? dgamma : db), red);
 }
 
 // The tail of a bf16 backward pass in one launch, for shapes where the contractions leave split reductions behind:
@@ -1084,11 +1051,9 @@ void launch_colsum_partial(int dt, int64_t M, int64_t N, int64_t ldg, const void
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, M, N, ldg, strips, groups, (const bf16_t*)G, (float*)colpart);
   }
 }
-void launch_colsum_finish(int dt, int64_t M, int64_t N, const void* colpart, float* out, hipStream_t s) {
-  const int groups = colsum_groups(M);
-  const dim3 grid((unsigned)((N + 63) / 64), 1);
-  if (dt == kF32) hipLaunchKernelGGL((b2_kernel<double>), grid, dim3(1024), 0, s, N, groups, (const double*)colpart, out, out, out);
-  else hipLaunchKernelGGL((b2_kernel<float>), grid, dim3(1024), 0, s, N, groups, (const float*)colpart, out, out, out);
+void launch_colsum_finish(int64_t M, int64_t N, const void* colpart, float* out, hipStream_t s) {
+  hipLaunchKernelGGL(b2_kernel, dim3((unsigned)((N + 63) / 64), 1), dim3(1024), 0, s, N, colsum_groups(M), (const float*)colpart,
+                     out, out, out);
 }
 
 // H = SiLU(G) * U over n elements (H may alias G or U)
@@ -1169,11 +1134,9 @@ void launch_b1_fused(int dt, int64_t M, int64_t N, int64_t ldz, int groups, bool
   else b1_fused_impl<bf16_t>(M, N, ldz, groups, blocked, dY, Zsave, gamma, mean, rstd, dZ, colpart, s);
 }
 
-void launch_b2(int dt, int64_t N, int groups, const void* colpart, float* dbeta, float* dgamma, float* db,
-               hipStream_t s) {
-  const dim3 grid((unsigned)((N + 63) / 64), 3);
-  if (dt == kF32) hipLaunchKernelGGL((b2_kernel<double>), grid, dim3(1024), 0, s, N, groups, (const double*)colpart, dbeta, dgamma, db);
-  else hipLaunchKernelGGL((b2_kernel<float>), grid, dim3(1024), 0, s, N, groups, (const float*)colpart, dbeta, dgamma, db);
+void launch_b2(int64_t N, int groups, const void* colpart, float* dbeta, float* dgamma, float* db, hipStream_t s) {
+  hipLaunchKernelGGL(b2_kernel, dim3((unsigned)((N + 63) / 64), 3), dim3(1024), 0, s, N, groups, (const float*)colpart, dbeta,
+                     dgamma, db);
 }
 
 void launch_finish(TailSums j, hipStream_t s) {
