@@ -110,12 +110,11 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
   // Large batches on the tuned kernel (tile-aligned N and K): the weights are transposed first, 4 N K bytes of traffic
   // against about 6 % of the contraction's time; that pays from roughly 10^4 rows, with a margin for the extra launch.
-  if (dt == kF32) {
-    q.f1_s64 = f64_plan(Mp, N, K);
-    q.off_part64 = off; off += align256(f64_part_bytes(q.f1_s64));
-  }
+  if (dt == kF32) q.f1_s64 = f64_plan(Mp, N, K);
+  q.f1_split = tiled ? fast_xwt_split(M, K, N) : 1;
+  q.off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q.f1_s64) : fast_xwt_part_bytes(M, N, q.f1_split));
   q.fwd_bytes_plain = off;
-  q.f1_wt = tiled && !q.pad && M >= kTransposeFromRows;
+  q.f1_wt = tiled && !q.pad && M >= kTransposeFromRows && q.f1_split == 1;
   q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
   q.fwd_bytes = off;
   // The static entry point's limit is part of its contract (see the header) and does not move with the plan: the tiled
@@ -303,14 +302,15 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
       StageJobs j = {};
       stage_padded(&j, M, K, N, X, W, b, ws + p.off_xtail, Wp, bp);
       launch_stage(j, s);
-      launch_fast_xwt_padded(0, M, K, N, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, s);
+      launch_fast_xwt_padded(0, M, K, N, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, p.f1_split, ws + p.off_part, s);
     } else if (p.f1_fast) {
       void* Wt = p.f1_wt ? ws + p.off_wt : nullptr;
       if (p.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
-      launch_fast_xwt(0, M, K, N, X, false, W, Wt, b, nullptr, Zsave, false, ws + p.off_xtail, s);
+      launch_fast_xwt(0, M, K, N, X, false, W, Wt, b, nullptr, Zsave, false, ws + p.off_xtail, s, false, p.f1_split,
+                      ws + p.off_part);
     } else {
       GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
-      if (p.dt == kF32) launch_f64(0, g, p.f1_s64, b, nullptr, Zsave, ws + p.off_part64, s);
+      if (p.dt == kF32) launch_f64(0, g, p.f1_s64, b, nullptr, Zsave, ws + p.off_part, s);
       else launch_generic_xwt(0, g, b, nullptr, Zsave, s);
     }
   }
@@ -371,6 +371,9 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   if (p.static_need > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;   // more than the array is stated to hold
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
     p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the transposed weights: the kernel reads W as it is
+  }
+  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_split > 1) {
+    p.f1_split = 1; p.fwd_bytes = p.off_part;         // (the sums of a split reduction are the last region here)
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) {
     p.pad = 0; p.f1_fast = 0; p.fwd_bytes = 0;        // no room for the padded copies either: the generic kernel needs none,
@@ -595,7 +598,8 @@ struct ReluPlan {
   int f1_wt;               // the forward product (and its recomputation) reads the weights from a transposed copy
   GradPlan g;
   F64Split f1_s64;         // fp32 storage
-  size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, off_part64, bytes;
+  int f1_split;            // bf16, tiled: parts of the forward product's reduction
+  size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, off_part, bytes;
 };
 bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   if (dt != kF32 && dt != kBF16) return false;
@@ -611,7 +615,7 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   size_t off = 0;
   q->off_colpart = off; off += align256((size_t)colsum_groups(Mp) * N * cs);
   // (the masking epilogue of the tuned forward product can write blocks)
-  make_grad_plan(dt, M, K, N, /*may_block=*/tiled && q->f1_fast, &off, &q->g);
+  make_grad_plan(dt, M, K, N, /*may_block=*/tiled && q->f1_fast && fast_xwt_split(M, K, N) == 1, &off, &q->g);
   // the padded copies of W and (where all of it is copied) X serve the forward product and the gradient contractions
   q->off_wpad = q->g.off_wpad;
   q->off_xtail = q->g.off_xpad;
@@ -619,12 +623,11 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
     q->off_xtail = off; off += align256(q->pad ? fast_padded_tail_bytes(K) : (q->f1_fast ? fast_f1_tail_bytes(M, K) : 0));
   }
   q->off_bpad = off; off += align256(tiled && q->pad ? (size_t)fast_pad_dim(N) * 4 : 0);
-  q->f1_wt = tiled && q->f1_fast && M >= kTransposeFromRows;
+  q->f1_split = tiled && (q->pad || q->f1_fast) ? fast_xwt_split(M, K, N) : 1;
+  q->f1_wt = tiled && q->f1_fast && M >= kTransposeFromRows && q->f1_split == 1;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
-  if (dt == kF32) {
-    q->f1_s64 = f64_plan(Mp, N, K);
-    q->off_part64 = off; off += align256(f64_part_bytes(q->f1_s64));
-  }
+  if (dt == kF32) q->f1_s64 = f64_plan(Mp, N, K);
+  q->off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q->f1_s64) : fast_xwt_part_bytes(M, N, q->f1_split));
   q->bytes = off;
   return true;
 }
@@ -642,14 +645,15 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
     launch_skinny_xwt(kind, M, K, N, X, W, b, aux, out, kind == 2 ? q.g.ldz : N, s);
   } else if (q.pad) {
     launch_fast_xwt_padded(kind, M, K, N, X, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<const float*>(ws + q.off_bpad),
-                           aux, out, s);
+                           aux, out, q.f1_split, ws + q.off_part, s);
   } else if (q.f1_fast) {
     void* Wt = q.f1_wt ? ws + q.off_wt : nullptr;
     if (q.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
-    launch_fast_xwt(kind, M, K, N, X, false, W, Wt, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s);
+    launch_fast_xwt(kind, M, K, N, X, false, W, Wt, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s, false,
+                    q.f1_split, ws + q.off_part);
   } else {
     GemmDesc g = {X, W, M, N, K, K, K, true, true, q.f1_wb};
-    if (dt == kF32) launch_f64(kind, g, q.f1_s64, b, aux, out, ws + q.off_part64, s);
+    if (dt == kF32) launch_f64(kind, g, q.f1_s64, b, aux, out, ws + q.off_part, s);
     else launch_generic_xwt(kind, g, b, aux, out, s);
   }
 }
@@ -790,7 +794,8 @@ struct FfnPlan {
   int gate_wt;             // the fused gate/up kernel reads both weight matrices from one interleaved transposed copy
   int g_blocked;           // the gated activation passes from the fused kernel to the down projection in 32 x 32 blocks
   F64Split up_s64, down_s64;   // fp32 storage
-  size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, off_part64, bytes;
+  int down_split;              // bf16, tiled: parts of the down projection's reduction
+  size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, off_part, bytes;
 };
 bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   if (dt != kF32 && dt != kBF16) return false;
@@ -798,7 +803,7 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   if (M * H > kMaxElems || M * D > kMaxElems || H * D > kMaxElems) return false;
   const size_t ts = dt == kF32 ? 4 : 2;
   const int64_t Mp = M > 0 ? M : 1;
-  q->gate_skinny = dt == kBF16 && skinny_supported(Mp, D, 2 * H);
+  q->gate_skinny = dt == kBF16 && skinny_gate_supported(Mp, D, H);
   q->down_skinny = dt == kBF16 && skinny_supported(Mp, H, D);
   // off the tiles: padded copies, where the padding is not most of the work nor the launches most of the time
   const int64_t Hp = fast_gate_pad_h(H), Dq = fast_gate_pad_d(D), Dp = fast_pad_dim(D);
@@ -822,7 +827,8 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   q->off_wgp = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wup = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wdp = off; off += align256(q->down_pad ? (size_t)Dp * Hp * 2 : 0);
-  q->down_wt = q->down_fast && M >= kTransposeFromRows;
+  q->down_split = q->down_pad || q->down_fast ? fast_xwt_split(M, q->down_pad ? Hp : H, D) : 1;
+  q->down_wt = q->down_fast && M >= kTransposeFromRows && q->down_split == 1;
   q->off_wt = off; off += align256(q->down_wt ? (size_t)D * H * 2 : 0);
   q->gate_wt = q->gate_fused && M >= kTransposeFromRows && H % 64 == 0 && D % 64 == 0;
   q->off_wcat = off; off += align256(q->gate_wt ? (size_t)2 * D * H * 2 : 0);
@@ -830,9 +836,10 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   if (dt == kF32) {
     q->up_s64 = f64_plan(Mp, H, D);
     q->down_s64 = f64_plan(Mp, D, H);
-    const size_t a = f64_part_bytes(q->up_s64), b = f64_part_bytes(q->down_s64);
-    q->off_part64 = off; off += align256(a > b ? a : b);
   }
+  const size_t up64 = dt == kF32 ? f64_part_bytes(q->up_s64) : 0;
+  const size_t down = dt == kF32 ? f64_part_bytes(q->down_s64) : fast_xwt_part_bytes(M, D, q->down_split);
+  q->off_part = off; off += align256(up64 > down ? up64 : down);
   q->bytes = off;
   return true;
 }
@@ -884,24 +891,25 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     launch_fast_xwt(0, M, D, H, X, false, Wu, nullptr, nullptr, nullptr, U, false, ws + q.off_xtail, s);
   } else {
     GemmDesc g = {X, Wg, M, H, D, D, D, true, true, q.up_wb};
-    if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, G, ws + q.off_part64, s);
+    if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, G, ws + q.off_part, s);
     else launch_generic_xwt(0, g, nullptr, nullptr, G, s);
     g.B = Wu;
-    if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, U, ws + q.off_part64, s);
+    if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, U, ws + q.off_part, s);
     else launch_generic_xwt(0, g, nullptr, nullptr, U, s);
   }
   if (!q.gate_fused && !q.gate_skinny && !q.gate_pad) launch_silu_mul((int)dt, M * H, G, U, G, s);
   if (q.down_pad) {
-    launch_fast_down_padded(M, D, q.ldg, G, ws + q.off_wdp, Y, s);
+    launch_fast_down_padded(M, D, q.ldg, G, ws + q.off_wdp, Y, q.down_split, ws + q.off_part, s);
   } else if (q.down_skinny) {
     launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, s);
   } else if (q.down_fast) {
     void* Wt = q.down_wt ? ws + q.off_wt : nullptr;
     if (q.down_wt) launch_fast_transpose(D, H, Wd, Wt, s);
-    launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wt, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0);
+    launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wt, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0,
+                    q.down_split, ws + q.off_part);
   } else {
     GemmDesc g = {G, Wd, M, D, H, H, H, true, true, q.down_wb};
-    if (dt == FDL_F32) launch_f64(0, g, q.down_s64, nullptr, nullptr, Y, ws + q.off_part64, s);
+    if (dt == FDL_F32) launch_f64(0, g, q.down_s64, nullptr, nullptr, Y, ws + q.off_part, s);
     else launch_generic_xwt(0, g, nullptr, nullptr, Y, s);
   }
   return launch_status();

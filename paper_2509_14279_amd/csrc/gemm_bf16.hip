@@ -920,9 +920,13 @@ void launch_fast_transpose_gate(int64_t H, int64_t D, const void* Wg, const void
   hipLaunchKernelGGL(transpose64_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wu, H, D, (bf16_t*)Wcat, 2 * H, 128, 64);
 }
 
+static void launch_xwt_split(FastParams p, bool rag, bool crag, int kind, int split, void* part, int64_t M, int64_t N,
+                             const float* bias, const void* aux, void* out, int64_t ldo, hipStream_t s);
+
 // Padded mode: the operands of stage_padded.  kind as launch_fast_xwt; kind 2 writes out [..][Np], the others [M][N].
+// split, part: see fast_xwt_split.
 void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* xw, const void* Wp,
-                            const float* biasp, const void* aux, void* out, hipStream_t s) {
+                            const float* biasp, const void* aux, void* out, int split, void* part, hipStream_t s) {
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
   const bool staged = fast_padded_stages_x(K);
   FastParams p = {};
@@ -934,6 +938,7 @@ void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const voi
   p.I = (int)N; p.J = (int)M; p.tiles_i = (int)(Np / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
   constexpr int NS = stages_of(kF1BK), round = NS * kF1BK;
   p.nkt = (int)((K + round - 1) / round * NS); p.split = 1;
+  if (split > 1) { launch_xwt_split(p, true, true, kind, split, part, M, N, biasp, aux, out, p.ldc, s); return; }
   if (kind == 1) launch<false, false, EPI_RELU, kF1BK, NS, true, true>(p, s);
   else if (kind == 2) launch<false, false, EPI_MASK, kF1BK, NS, true, true>(p, s);
   else if (biasp != nullptr) launch<false, false, EPI_BIAS, kF1BK, NS, true, true>(p, s);
@@ -953,7 +958,7 @@ void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const voi
 // out_blocked (kind 2 only; M, N multiples of 32): out is written in 32 x 32 blocks, as the dX and dW kernels read it best.
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
                      const void* Wt, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
-                     hipStream_t s, bool x_blocked) {
+                     hipStream_t s, bool x_blocked, int split, void* part) {
   FastParams p = {};
   p.cblocked = (out_blocked && kind == 2) ? 1 : 0;
   p.qblocked = (x_blocked && Wt != nullptr) ? 1 : 0;   // only the transposed-weight kernels read a blocked X
@@ -983,6 +988,7 @@ void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, b
 #undef FDL_XWT_T
     return;
   }
+  if (split > 1) { launch_xwt_split(p, rag, false, kind, split, part, M, N, bias, aux, out, N, s); return; }
   constexpr int NS = stages_of(kF1BK);
 #define FDL_XWT(EPI)                                                              \
   do {                                                                            \
@@ -994,6 +1000,96 @@ void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, b
   else if (bias != nullptr) FDL_XWT(EPI_BIAS);
   else FDL_XWT(EPI_STORE);
 #undef FDL_XWT
+}
+
+// ---- the forward product with a split reduction ------------------------------------------------------------------
+// A batch of a few hundred rows has few output tiles (512 x 4096: 32 on 256 compute units), and each takes its whole
+// reduction, about 1.1 us per slice of 64 however few there are.  The parts of a split leave fp32 sums, which a second
+// kernel adds in order and finishes.
+// Prices, us: a tile's start and end 6, a slice 1.1; a part's with its 256 KB of sums 13, the second kernel 5 and its reading
+// at 6 TB/s.  Measured, us, whole / split, K x N and rows: 4096 x 4096: 512 77 / 42, 1024 78 / 58, 2048 82 / 87 (not split);
+// 4096 x 1024: 2048 77 / 43, 4096 79 / 62; 2048 x 2048: 1024 42 / 32; 4096 x 512: 4096 77 / 42, 8192 78 / 61.
+double fast_xwt_cost(int64_t M, int64_t K, int64_t N, int* split_out) {
+  const int64_t tiles = fast_pad_dim(N) / kTile * ((M + kTile - 1) / kTile);
+  constexpr int NS = stages_of(kF1BK), round = NS * kF1BK;
+  const int64_t rounds_k = (K + round - 1) / round;       // pipeline rounds of the reduction
+  int best = 1;
+  double best_cost = (double)((tiles + kPlanCUs - 1) / kPlanCUs) * ((double)rounds_k * NS * 1.1 + 6.0);
+  for (int split = 2; split <= 16 && tiles * split <= kPlanCUs; split++) {
+    if (rounds_k % split) continue;
+    const double cost = (double)(rounds_k / split) * NS * 1.1 + 18.0 + (double)split * (double)M * (double)N * 4.0 / 6e6;
+    if (cost < 0.9 * best_cost) { best = split; best_cost = cost; }
+  }
+  if (split_out != nullptr) *split_out = best;
+  return best_cost;
+}
+int fast_xwt_split(int64_t M, int64_t K, int64_t N) {
+  int split = 1;
+  fast_xwt_cost(M, K, N, &split);
+  return split;
+}
+size_t fast_xwt_part_bytes(int64_t M, int64_t N, int split) { return split > 1 ? (size_t)split * partial_stride(M * N) * 4 : 0; }
+
+namespace {
+// out[m][n] = f(the parts' sums + bias[n]), kinds as launch_fast_xwt; out has pitch ldo (kind 2: zeros from N to ldo)
+template <int KIND>
+__global__ __launch_bounds__(256) void xwt_reduce_kernel(const float* __restrict__ part, int split, int64_t stride, int64_t M,
+                                                         int64_t N, const float* __restrict__ bias,
+                                                         const bf16_t* __restrict__ aux, bf16_t* __restrict__ out, int64_t ldo) {
+  typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+  typedef __bf16 bf16x4_u __attribute__((ext_vector_type(4), aligned(2)));
+  const int64_t width = KIND == 2 ? ldo : N, vpr = (width + 3) / 4;
+  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < M * vpr; v += (int64_t)gridDim.x * 256) {
+    const int64_t m = v / vpr, n = (v - m * vpr) * 4;
+    const int left = N - n > 4 ? 4 : (N - n < 0 ? 0 : (int)(N - n));
+    float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    const float* src = part + m * N + n;
+    if (left == 4) {
+      for (int k = 0; k < split; k++) {
+        const f32x4_u t = *reinterpret_cast<const f32x4_u*>(src + (int64_t)k * stride);
+#pragma unroll
+        for (int e = 0; e < 4; e++) z[e] += t[e];
+      }
+    } else {
+      for (int k = 0; k < split; k++)
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          if (e < left) z[e] += src[(int64_t)k * stride + e];
+    }
+    bf16x4_u o;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float x = z[e] + (bias != nullptr && e < left ? bias[n + e] : 0.0f);
+      if (KIND == 2) o[e] = e < left && x > 0.0f ? aux[m * N + n + e] : (bf16_t)0.0f;
+      else o[e] = (bf16_t)(KIND == 1 ? (x > 0.0f ? x : 0.0f) : x);
+    }
+    bf16_t* dst = out + m * ldo + n;
+    if (n + 4 <= width) {
+      *reinterpret_cast<bf16x4_u*>(dst) = o;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+        if (n + e < width) dst[e] = o[e];
+    }
+  }
+}
+}  // namespace
+
+// split > 1: part holds fast_xwt_part_bytes; p: the product's operands, tiles and sizes (a forward product of the functions
+// above, before its epilogue is chosen); crag: any N
+static void launch_xwt_split(FastParams p, bool rag, bool crag, int kind, int split, void* part, int64_t M, int64_t N,
+                             const float* bias, const void* aux, void* out, int64_t ldo, hipStream_t s) {
+  p.bias = nullptr; p.aux = nullptr;
+  p.Cpart = (float*)part; p.pstride = partial_stride(M * N); p.split = split; p.nkt /= split;
+  constexpr int NS = stages_of(kF1BK);
+  if (crag) launch<false, false, EPI_PARTIAL, kF1BK, NS, true, true>(p, s);
+  else if (rag) launch<false, false, EPI_PARTIAL, kF1BK, NS, true>(p, s);
+  else launch<false, false, EPI_PARTIAL, kF1BK, NS>(p, s);
+  const int64_t vectors = M * ((ldo + 3) / 4);
+  const unsigned blocks = (unsigned)((vectors + 255) / 256 < 4096 ? (vectors + 255) / 256 : 4096);
+  auto kern = kind == 1 ? xwt_reduce_kernel<1> : (kind == 2 ? xwt_reduce_kernel<2> : xwt_reduce_kernel<0>);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, (const float*)part, split, p.pstride, M, N, bias, (const bf16_t*)aux,
+                     (bf16_t*)out, ldo);
 }
 
 // Gated pair of products for the feed-forward block: Hout[m][h] = SiLU(sum_d X[m][d] Wg[h][d]) * (sum_d X[m][d] Wu[h][d]).
@@ -1048,12 +1144,14 @@ void launch_fast_gate_padded(int64_t M, int64_t D, int64_t H, const void* X, con
   launch<false, false, EPI_GATE, kF1BK, stages_of(kF1BK), true>(p, s);
 }
 // out [M][D] = G [..][Hp] Wdp^T with Wdp [D rounded up to the tile][Hp]; G has readable rows up to the next row tile
-void launch_fast_down_padded(int64_t M, int64_t D, int64_t Hp, const void* G, const void* Wdp, void* out, hipStream_t s) {
+void launch_fast_down_padded(int64_t M, int64_t D, int64_t Hp, const void* G, const void* Wdp, void* out, int split, void* part,
+                             hipStream_t s) {
   FastParams p = {};
   p.P = (const bf16_t*)Wdp; p.Q = (const bf16_t*)G; p.ldp = Hp; p.ldq = Hp;
   p.C = (bf16_t*)out;
   p.I = (int)D; p.J = (int)M; p.tiles_i = (int)(fast_pad_dim(D) / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
   p.nkt = (int)(Hp / kF1BK); p.split = 1;
+  if (split > 1) { launch_xwt_split(p, true, true, 0, split, part, M, D, nullptr, nullptr, out, D, s); return; }
   launch<false, false, EPI_STORE, kF1BK, stages_of(kF1BK), true, true>(p, s);
 }
 void stage_gate_x(StageJobs* j, const void* X, int64_t M, int64_t D, void* xw) {

@@ -207,14 +207,29 @@ template <int EPI> void dispatch_skinny(const SkinnyParams& p, hipStream_t s) {
 
 }  // namespace
 
-// Where this kernel is the faster one.  It rereads X for every 16 or 32 columns, so its time grows with the output, while
-// the tiled kernel needs the whole reduction's slices however few tiles there are.  us, this kernel / the tiled one, for
-// K x N and M rows: 4096 x 4096: 128 rows 29 / 81, 256 48 / 78, 384 68 / 82, 512 78 / 77; 1024 x 1024: 512 11 / 24, 1024 16 /
-// 25, 1536 24 / 25; 4096 x 1024: 1024 48 / 77, 1536 72 / 77.  Rows that start at any element (K % 8) cost it twice the
-// loads; against the generic kernel, 771 x 1537: 256 rows 17 / 24, 384 24.5 / 24.2, 768 36 / 29.  Below 128 rows the tiled
-// kernel does not run at all, and the generic one is slower at every size (4096 x 4096, 64 rows: 20 / 88).
+// Where this kernel is the faster one.  It rereads X for every 16 or 32 columns, so its time grows with the output: about
+// 10.5 us per 10^9 products for whole 16-byte rows (row blocks of 64), three times that for rows that start at any element.
+// The tiled kernel's time is its own estimate, and the padded copies' where they are needed.  Measured, us, this kernel / the
+// tiled one, K x N and rows: 4096 x 4096: 128 29 / 31, 256 48 / 35; 1024 x 1024: 512 11 / 24, 1536 24 / 25; 2048 x 2048: 512
+// 27 / 28, 768 38 / 31; 4096 x 1024: 384 33 / 34, 1536 72 / 41.  Where only the generic kernel is left (odd widths and little
+// work), up to 1.5 M outputs, or 0.5 M for odd rows (771 x 1537: 256 rows 17 / 24, 384 24.5 / 24.2).  Below 128 rows the
+// tiled kernel does not run, and the generic one is slower at every size (4096 x 4096, 64 rows: 20 / 88).
+static double skinny_cost(int64_t M, int64_t K, int64_t N) {
+  return 4.0 + (K % 8 == 0 ? 10.5e-9 : 34e-9) * (double)((M + 63) / 64 * 64) * (double)K * (double)N;
+}
 bool skinny_supported(int64_t M, int64_t K, int64_t N) {
-  return M < 128 || M * N <= (K % 8 == 0 ? 3 << 19 : 1 << 19);
+  if (M < 128) return true;
+  const bool pad = fast_padded_supported(M, K, N);
+  if (!pad && !fast_f1_supported(M, K, N)) return M * N <= (K % 8 == 0 ? 3 << 19 : 1 << 19);
+  return skinny_cost(M, K, N) < fast_xwt_cost(M, K, N, nullptr) + (pad ? 12.0 : 0.0);
+}
+// the gate and up products together: the tiled kernel has a tile of 128 columns and no split
+bool skinny_gate_supported(int64_t M, int64_t D, int64_t H) {
+  if (M < 128) return true;
+  const bool fits = fast_gate_supported(M, D, H);
+  if (!fits && M * D * H < kStageFromWork) return M * 2 * H <= (D % 8 == 0 ? 3 << 19 : 1 << 19);
+  const int64_t tiles = ((H + 127) / 128) * ((M + 255) / 256);
+  return skinny_cost(M, D, 2 * H) < (double)((tiles + 255) / 256) * ((double)D / 64 * 1.1 + 8.0) + (fits ? 0.0 : 12.0);
 }
 
 // out[m][n] = f(sum_k X[m][k] W[n][k] + bias[n]): kind 0 plain (bias may be null), 1 max(., 0), 2 aux[m][n] where positive

@@ -53,7 +53,8 @@ struct Plan {
   int f1_wt;              // 1: the fast kernel reads the weights from a transposed copy (large batches)
   size_t off_wt;          // bf16 [K][N], the last region of the forward workspace
   F64Split f1_s64;        // fp32 storage
-  size_t off_part64;
+  int f1_split;           // bf16, tiled: parts of the reduction where there are few tiles
+  size_t off_part;        // their sums
   size_t fwd_bytes;       // (without the transposed weights: fwd_bytes - align256(N K 2), see fwd_bytes_plain)
   size_t fwd_bytes_plain; // forward workspace of the same plan with f1_wt = 0
   size_t static_need;     // what fdl_forward_static compares with its array (the header's rule)
@@ -169,6 +170,7 @@ void launch_silu_mul(int dt, int64_t n, const void* G, const void* U, void* H, h
 
 // ---- bf16 products with few rows (gemm_skinny.hip): any K and N -----------------------------------
 bool skinny_supported(int64_t M, int64_t K, int64_t N);
+bool skinny_gate_supported(int64_t M, int64_t D, int64_t H);
 void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias,
                        const void* aux, void* out, int64_t ldo, hipStream_t s);
 void launch_skinny_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s);
@@ -203,13 +205,18 @@ int64_t fast_padded_b4_rows(int64_t M, int64_t K);
 void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias, void* xw,
                   void* Wp, float* biasp);
 void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* xw, const void* Wp,
-                            const float* biasp, const void* aux, void* out, hipStream_t s);
+                            const float* biasp, const void* aux, void* out, int split, void* part, hipStream_t s);
+// parts of the forward product's reduction where it has few tiles, and their fp32 sums
+int fast_xwt_split(int64_t M, int64_t K, int64_t N);
+double fast_xwt_cost(int64_t M, int64_t K, int64_t N, int* split);    // estimated time, us
+size_t fast_xwt_part_bytes(int64_t M, int64_t N, int split);
 int64_t fast_gate_pad_h(int64_t H);
 int64_t fast_gate_pad_d(int64_t D);
 void stage_gate_x(StageJobs* j, const void* X, int64_t M, int64_t D, void* xw);
 void launch_fast_gate_padded(int64_t M, int64_t D, int64_t H, const void* X, const void* xw, const void* Wgp, const void* Wup,
                              void* Hout, hipStream_t s);
-void launch_fast_down_padded(int64_t M, int64_t D, int64_t Hp, const void* G, const void* Wdp, void* out, hipStream_t s);
+void launch_fast_down_padded(int64_t M, int64_t D, int64_t Hp, const void* G, const void* Wdp, void* out, int split, void* part,
+                             hipStream_t s);
 // fp32 partial sums of n elements lie this far apart (16-byte parts)
 inline int64_t partial_stride(int64_t n) { return (n + 3) & ~(int64_t)3; }
 void launch_fast_b3_padded(int64_t M, int64_t K, int64_t N, const void* dZ, const void* Wp, void* dX, hipStream_t s);
@@ -220,7 +227,8 @@ void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, int extra
 constexpr int64_t kTransposeFromRows = 16384;   // batch size from which transposing the weights first pays
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
                      const void* Wt, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
-                     hipStream_t s, bool x_blocked = false);   // x_blocked: X in 32 x 32 blocks (needs Wt, x_padded)
+                     hipStream_t s, bool x_blocked = false,    // x_blocked: X in 32 x 32 blocks (needs Wt, x_padded)
+                     int split = 1, void* part = nullptr);     // see fast_xwt_split (without Wt)
 // gate and up products of the feed-forward block with the gated activation in the epilogue (see gemm_bf16.hip)
 bool fast_gate_supported(int64_t M, int64_t D, int64_t H);
 // Wcat: null, or the interleaved transposed weights [D][2H] from launch_fast_transpose_gate
