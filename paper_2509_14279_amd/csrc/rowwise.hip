@@ -935,9 +935,11 @@ template <int CH, int FIT, int NT, int ACT, int WPR = 1>
 void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float eps, const bf16_t* Z, const float* gamma,
                         const float* beta, bf16_t* Y, float* mean, float* rstd) {
   constexpr size_t kLds = (size_t)CH * WPR * 4096 + GaussTable<false>::kBytes;
-  static OnceFlags configured;
   auto kern = f2_rows_kernel<CH, FIT, NT, ACT, WPR>;
-  if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLds, &configured)) return;
+  if constexpr (kLds > 64 * 1024) {
+    static OnceFlags configured;
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLds, &configured)) return;
+  }
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(NT), kLds, s, M, N, eps, Z, gamma, beta, Y, mean, rstd);
 }
 
@@ -986,12 +988,10 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
                      float* mean, float* rstd, hipStream_t s) {
   constexpr int V = 16 / (int)sizeof(T);
   if constexpr (sizeof(T) == 4) {
-    DeviceInfo di;
-    if (!device_info(&di)) return;
     const int64_t vectors = (N + V - 1) / V;
 #define FDL_ROW(NT, S)                                                                                              \
   do {                                                                                                              \
-    const int64_t cap = (int64_t)di.cus * (2048 / NT);                                                              \
+    const int64_t cap = (int64_t)256 * (2048 / NT);   /* a full part's wavefronts; any number is correct */         \
     hipLaunchKernelGGL((row_wg_kernel<NT, S, ACT>), dim3((unsigned)(M < cap ? M : cap)), dim3(NT), 0, s, M, N, eps, \
                        (const T*)A, gamma, beta, (T*)Y, mean, rstd);                                                \
     return;                                                                                                         \
