@@ -96,6 +96,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   // mode - on N and K rounded up to the tile, on zero-padded copies of the weights (and of X where its rows start at any
   // element), leaving the surplus unstored.  Everything else takes the generic kernel.
   q.pad = dt == kBF16 && fast_padded_supported(M, K, N);
+  q.stage_x = q.pad && fast_padded_stages_x(K);
   const int64_t Np = q.pad ? fast_pad_dim(N) : N, Kp = q.pad ? fast_pad_dim(K) : K;
   const int64_t Mp = M > 0 ? M : 1;
 
@@ -105,7 +106,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.f1_wb = pick_generic_wb(Mp, N);
   size_t off = 0;
   const bool tiled = q.f1_fast && !q.f1_skinny;
-  q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K) : fast_f1_tail_bytes(M, K)));
+  q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K, q.stage_x != 0) : fast_f1_tail_bytes(M, K)));
   q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
   // Large batches on the tuned kernel (tile-aligned N and K): the weights are transposed first, 4 N K bytes of traffic
@@ -183,13 +184,13 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, siz
   q.pair = q.b3_fast && q.b4_fast && fast_pair_plan(M, K, N, q.b4_fast_rows, &q.split_a, &q.split_b);
   q.blocked = may_block && dt == kBF16 && !q.pad && q.b3_fast && q.b4_fast && q.b4_fast_rows == M && M % 32 == 0 && N % 32 == 0;
   // dZ: the fast dX kernel reads whole 256-row tiles, so the buffer is rounded up (the surplus rows never reach an output)
-  q.off_dz = *off; *off += align256((size_t)((Mp + 255) / 256 * 256) * Np * ts);
+  q.off_dz = *off; *off += align256((size_t)fast_padded_rows(Mp) * Np * ts);
   // fp32 partial sums: the parts of a split reduction, one more for the rows the fast kernel leaves to the generic one
   q.parts_b = q.split_b + q.extra;
   q.off_dxpart = *off; *off += align256(q.split_a > 1 ? (size_t)q.split_a * partial_stride(M * K) * 4 : 0);
   q.off_dwpart = *off; *off += align256(q.parts_b > 1 ? (size_t)q.parts_b * partial_stride(N * K) * 4 : 0);
   q.off_wpad = *off; *off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
-  q.off_xpad = *off; *off += align256(q.stage_x ? fast_padded_x_bytes(M, K) : 0);
+  q.off_xpad = *off; *off += align256(q.stage_x ? fast_padded_x_bytes(M, K, true) : 0);
   if (dt == kF32) {
     q.s64_a = f64_plan(Mp, K, N);
     q.s64_b = f64_plan(N, K, Mp);
@@ -300,9 +301,9 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
       void* Wp = ws + p.off_wpad_f;
       float* bp = reinterpret_cast<float*>(ws + p.off_bpad_f);
       StageJobs j = {};
-      stage_padded(&j, M, K, N, X, W, b, ws + p.off_xtail, Wp, bp);
+      stage_padded(&j, M, K, N, p.stage_x != 0, X, W, b, ws + p.off_xtail, Wp, bp);
       launch_stage(j, s);
-      launch_fast_xwt_padded(0, M, K, N, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, p.f1_split, ws + p.off_part, s);
+      launch_fast_xwt_padded(0, M, K, N, p.stage_x != 0, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, p.f1_split, ws + p.off_part, s);
     } else if (p.f1_fast) {
       void* Wt = p.f1_wt ? ws + p.off_wt : nullptr;
       if (p.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
@@ -375,6 +376,13 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_split > 1) {
     p.f1_split = 1; p.fwd_bytes = p.off_part;         // (the sums of a split reduction are the last region here)
   }
+  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.pad && p.stage_x && !p.f1_skinny && fast_padded_can_skip_copy(K)) {
+    // X as it is: only its last row tile is copied
+    p.stage_x = 0;
+    p.off_wpad_f = p.off_xtail + align256(fast_padded_x_bytes(M, K, false));
+    p.off_bpad_f = p.off_wpad_f + align256((size_t)fast_pad_dim(N) * fast_pad_dim(K) * 2);
+    p.fwd_bytes = p.off_bpad_f + align256((size_t)fast_pad_dim(N) * 4);
+  }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) {
     p.pad = 0; p.f1_fast = 0; p.fwd_bytes = 0;        // no room for the padded copies either: the generic kernel needs none,
     p.f1_s64 = f64_unsplit(M, N);                     // nor the fp64 kernel, with all tiles whole
@@ -395,7 +403,7 @@ static bool grad_leaves_sums(const GradPlan& p) { return p.split_a > 1 || p.part
 
 // padded mode: the copies the contractions read, and zeros in the rows behind dZ's last where dW's reduction covers them
 static void stage_grad(const GradPlan& p, StageJobs* j, const void* X, const void* W, char* ws) {
-  stage_padded(j, p.M, p.K, p.N, p.stage_x ? X : nullptr, W, nullptr, ws + p.off_xpad, ws + p.off_wpad, nullptr);
+  stage_padded(j, p.M, p.K, p.N, true, p.stage_x ? X : nullptr, W, nullptr, ws + p.off_xpad, ws + p.off_wpad, nullptr);
   if (p.b4_fast_rows > p.M)
     stage_matrix(j, nullptr, 0, 0, 0, ws + p.off_dz + (size_t)p.M * p.ldz * 2, p.b4_fast_rows - p.M, p.ldz);
 }
@@ -644,7 +652,7 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
   if (q.f1_skinny) {
     launch_skinny_xwt(kind, M, K, N, X, W, b, aux, out, kind == 2 ? q.g.ldz : N, s);
   } else if (q.pad) {
-    launch_fast_xwt_padded(kind, M, K, N, X, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<const float*>(ws + q.off_bpad),
+    launch_fast_xwt_padded(kind, M, K, N, q.g.stage_x != 0, X, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<const float*>(ws + q.off_bpad),
                            aux, out, q.f1_split, ws + q.off_part, s);
   } else if (q.f1_fast) {
     void* Wt = q.f1_wt ? ws + q.off_wt : nullptr;
@@ -681,7 +689,7 @@ extern "C" fdl_status fdl_linear_relu_forward(fdl_dtype dt, int64_t M, int64_t K
   char* ws = static_cast<char*>(workspace);
   if (q.pad && !q.f1_skinny) {
     StageJobs j = {};
-    stage_padded(&j, M, K, N, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
+    stage_padded(&j, M, K, N, q.g.stage_x != 0, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
     launch_stage(j, s);
   }
   relu_product(q, 1, (int)dt, M, K, N, X, W, b, nullptr, Y, ws, s);
@@ -716,11 +724,11 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
     // the copies serve the recomputation and both gradient contractions; X goes with the recomputation's where that is tiled
     StageJobs j = {};
     if (q.f1_skinny) {
-      stage_padded(&j, M, K, N, q.g.stage_x ? X : nullptr, W, nullptr, ws + q.g.off_xpad, ws + q.g.off_wpad, nullptr);
+      stage_padded(&j, M, K, N, true, q.g.stage_x ? X : nullptr, W, nullptr, ws + q.g.off_xpad, ws + q.g.off_wpad, nullptr);
       // (that kernel writes columns up to N only: the surplus of G is cleared first, with the rows behind its last)
       stage_matrix(&j, nullptr, 0, 0, 0, G, q.g.b4_fast_rows > M ? q.g.b4_fast_rows : M, q.g.ldz);
     } else {
-      stage_padded(&j, M, K, N, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
+      stage_padded(&j, M, K, N, q.g.stage_x != 0, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
       if (q.g.b4_fast_rows > M)
         stage_matrix(&j, nullptr, 0, 0, 0, static_cast<char*>(G) + (size_t)M * q.g.ldz * 2, q.g.b4_fast_rows - M, q.g.ldz);
     }

@@ -843,15 +843,15 @@ size_t fast_f1_tail_bytes(int64_t M, int64_t K) { return M % kTile ? (size_t)kTi
 // zero-padded [Np][Kp] matrix (small: it is the only operand that is always copied whole), the bias into a padded vector,
 // dZ is laid out with pitch Np and zero surplus columns, and the kernels leave the surplus output columns and rows
 // unstored.  X enters in one of two ways:
-//   K a multiple of 8 (16-byte rows) and at least 128: as it is.  Where it is read past the end of its rows the surplus is
-//     the start of X's next row times the weights' zero padding; only X's last row has no next row, so the forward pass
-//     takes its last row tile from a copy with one spare row, and the dW product leaves the last rows to the generic kernel.
-//   any other K: through a copy with pitch Kp, zeros around it and whole row tiles (M K elements read and written once,
-//     against three contractions at six to eight times the generic kernel's rate); the rows behind dZ's last are cleared up
-//     to a pipeline round, so that dW needs no remainder.
+//   through a copy with pitch Kp, zeros around it and whole row tiles (M K elements read and written once, against three
+//     contractions at six to eight times the generic kernel's rate); the rows behind dZ's last are cleared up to a pipeline
+//     round, so that dW needs no remainder.  Everywhere but where
+//   K is a multiple of the forward pass's pipeline round (128), or the static entry point has no room for the copy and K is
+//     a multiple of 8 and at least 128: as it is.  Its last row tile comes from a copy with one spare row, because rows may
+//     be read past their end (the surplus meets the weights' zeros: an infinity there makes the row before it NaN, which is
+//     why the copy is preferred), and the dW product leaves the last rows to the generic kernel.
 int64_t fast_pad_dim(int64_t n) { return (n + kTile - 1) / kTile * kTile; }
 bool fast_padded_supported(int64_t M, int64_t K, int64_t N) {
-  // K >= 128 for the first way: a row read up to the rounded-up K then ends inside the next row (Kp <= 2 K)
   if (M < kMinRaggedRows || N < 8) return false;
   if (N % kTile == 0 && K % kTile == 0) return false;     // nothing to pad: the plain fast path applies
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K), tj = (M + kTile - 1) / kTile;
@@ -862,14 +862,19 @@ bool fast_padded_supported(int64_t M, int64_t K, int64_t N) {
   // odd rows: not where the padding is most of the work, nor where the copies' launches are
   return Np * Kp <= 6 * N * K && M * N * K >= kStageFromWork;
 }
-bool fast_padded_stages_x(int64_t K) { return K % 8 != 0 || K < 128; }
+bool fast_padded_stages_x(int64_t K) { return K % (stages_of(kF1BK) * kF1BK) != 0; }
+// X as it is although rows are read past their end: K >= 128, so that such a read ends inside the next row (Kp <= 2 K)
+bool fast_padded_can_skip_copy(int64_t K) { return K % 8 == 0 && K >= 128; }
 size_t fast_padded_tail_bytes(int64_t K) { return (size_t)(kTile + 1) * K * 2; }
-int64_t fast_padded_rows(int64_t M) { return (M + kTile - 1) / kTile * kTile; }
+// Rows of X's copy and of dZ, and of dW's reduction over them: whole row tiles, and from 4096 rows a multiple of 512 - the
+// reduction is split into equal parts of whole pipeline rounds, and 10000 rows make 79 of those, a prime number (Linear+ReLU
+// 10000 x 1000 x 3000: 380 us, 334 with 80 rounds).
+int64_t fast_padded_rows(int64_t M) { const int64_t u = M >= 4096 ? 512 : kTile; return (M + u - 1) / u * u; }
 // rows of the dW reduction the fast kernel covers in padded mode (X as it is: where it is read past the end of its rows
 // the last row it touches must have a successor)
 int64_t fast_padded_b4_rows(int64_t M, int64_t K) {
   const int64_t u = (int64_t)kB4BK * stages_of(kB4BK);
-  if (fast_padded_stages_x(K)) return (M + u - 1) / u * u;
+  if (fast_padded_stages_x(K)) return M >= 4096 ? fast_padded_rows(M) : (M + u - 1) / u * u;
   return (K % kTile ? M - 1 : M) / u * u;
 }
 
@@ -893,12 +898,12 @@ static void stage_x_tail(StageJobs* j, const void* X, int64_t M, int64_t K, void
   const int64_t row0 = (M + kTile - 1) / kTile * kTile - kTile;
   stage_matrix(j, static_cast<const bf16_t*>(X) + row0 * K, M - row0, K, K, xtail, kTile + spare, K);
 }
-// W [N][K] -> Wp [Np][Kp], bias (may be null) -> biasp [Np], and X: its last row tile -> xw (K as it is) or all of it
-void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias, void* xw,
-                  void* Wp, float* biasp) {
+// W [N][K] -> Wp [Np][Kp], bias (may be null) -> biasp [Np], and X -> xw: all of it (staged) or its last row tile
+void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, bool staged, const void* X, const void* W, const float* bias,
+                  void* xw, void* Wp, float* biasp) {
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
   if (X != nullptr) {
-    if (fast_padded_stages_x(K)) stage_matrix(j, X, M, K, K, xw, fast_padded_rows(M), Kp);
+    if (staged) stage_matrix(j, X, M, K, K, xw, fast_padded_rows(M), Kp);
     else stage_x_tail(j, X, M, K, xw, 1);
   }
   stage_matrix(j, W, N, K, K, Wp, Np, Kp);
@@ -925,10 +930,9 @@ static void launch_xwt_split(FastParams p, bool rag, bool crag, int kind, int sp
 
 // Padded mode: the operands of stage_padded.  kind as launch_fast_xwt; kind 2 writes out [..][Np], the others [M][N].
 // split, part: see fast_xwt_split.
-void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* xw, const void* Wp,
+void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, bool staged, const void* X, const void* xw, const void* Wp,
                             const float* biasp, const void* aux, void* out, int split, void* part, hipStream_t s) {
   const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
-  const bool staged = fast_padded_stages_x(K);
   FastParams p = {};
   p.P = (const bf16_t*)Wp; p.ldp = Kp;
   p.Q = (const bf16_t*)(staged ? xw : X); p.ldq = staged ? Kp : K;

@@ -64,6 +64,7 @@ struct Plan {
   int b1_rows_per_group;  // B1b only
   GradPlan g;             // dX and dW
   int pad;                // forward: padded mode of the fast contraction (N, K not both multiples of 256)
+  int stage_x;            // forward, padded mode: X goes through a copy with pitch Kp
   size_t off_wpad_f, off_bpad_f;   // forward: zero-padded copies of W [Np][Kp] and b [Np]
   size_t off_xtail;       // forward: padded copy of X's last rows (ragged M on the fast path), or of X
   size_t off_c12;         // C [2][M]
@@ -195,16 +196,17 @@ void launch_stage(const StageJobs& j, hipStream_t s);
 constexpr int64_t kStageFromWork = (int64_t)1 << 28;   // M N K from which odd rows are worth copying
 bool fast_padded_supported(int64_t M, int64_t K, int64_t N);
 bool fast_padded_stages_x(int64_t K);          // X goes through a copy with pitch Kp (else only its last row tile is copied)
+bool fast_padded_can_skip_copy(int64_t K);
 int64_t fast_pad_dim(int64_t n);
 int64_t fast_padded_rows(int64_t M);           // rows of that copy, and of dZ
 size_t fast_padded_tail_bytes(int64_t K);
-inline size_t fast_padded_x_bytes(int64_t M, int64_t K) {
-  return fast_padded_stages_x(K) ? (size_t)fast_padded_rows(M) * fast_pad_dim(K) * 2 : fast_padded_tail_bytes(K);
+inline size_t fast_padded_x_bytes(int64_t M, int64_t K, bool staged) {
+  return staged ? (size_t)fast_padded_rows(M) * fast_pad_dim(K) * 2 : fast_padded_tail_bytes(K);
 }
 int64_t fast_padded_b4_rows(int64_t M, int64_t K);
-void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias, void* xw,
-                  void* Wp, float* biasp);
-void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* xw, const void* Wp,
+void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, bool staged, const void* X, const void* W, const float* bias,
+                  void* xw, void* Wp, float* biasp);
+void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, bool staged, const void* X, const void* xw, const void* Wp,
                             const float* biasp, const void* aux, void* out, int split, void* part, hipStream_t s);
 // parts of the forward product's reduction where it has few tiles, and their fp32 sums
 int fast_xwt_split(int64_t M, int64_t K, int64_t N);

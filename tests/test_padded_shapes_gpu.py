@@ -94,3 +94,34 @@ def test_feed_forward_block(M, D, Hd):
     assert Y.intact() and ws.intact()
     n = f64(t)
     H.check("bf16", "Y", H.to_f64(Y.view), S.llama_ffn_forward(n["X"], n["Wg"], n["Wu"], n["Wd"])["Y"])
+
+
+@pytest.mark.parametrize("M,K,N", [(300, 200, 264), (640, 1000, 1000), (400, 771, 1100), (256, 384, 520)])
+def test_an_infinity_stays_in_its_row(M, K, N):
+    # rows of a product are independent: an infinite and a NaN element of X change their own rows of the outputs only
+    cfg = I.custom("bf16", M, K, N, seed=9800 + M + K + N)
+    t = I.generate(cfg)
+    bf = torch.bfloat16
+    W = t["W"].to("cuda", bf)
+    b, gamma, beta = (t[k].to("cuda") for k in ("b", "gamma", "beta"))
+    bad = (7, M // 2, M - 1)
+
+    def run(X):
+        Y = torch.empty(M, N, device="cuda", dtype=bf)
+        Z = torch.empty_like(Y); R = torch.empty_like(Y); F = torch.empty(M, K, device="cuda", dtype=bf)
+        mean = torch.empty(M, device="cuda"); rstd = torch.empty(M, device="cuda")
+        ws = torch.empty(max(api.fdl_workspace_bytes("bf16", M, K, N), api.fdl_linear_relu_workspace_bytes("bf16", M, K, N),
+                             api.fdl_llama_ffn_workspace_bytes("bf16", M, K, N)), device="cuda", dtype=torch.uint8)
+        api.fdl_forward("bf16", X, W, b, gamma, beta, cfg.eps, Y, Z, mean, rstd, ws)
+        api.fdl_linear_relu_forward("bf16", X, W, b, R, ws)
+        api.fdl_llama_ffn_forward("bf16", X, W, W, W.t().contiguous(), F, ws)
+        torch.cuda.synchronize()
+        return Y, Z, R, F
+
+    X = t["X"].to("cuda", bf)
+    clean = run(X)
+    X = X.clone()
+    X[bad[0], 0] = float("inf"); X[bad[1], 1] = float("nan"); X[bad[2], 0] = float("-inf")
+    good = [r for r in range(M) if r not in bad]
+    for a, c in zip(run(X), clean):
+        assert torch.equal(a[good].view(torch.int16), c[good].view(torch.int16))
