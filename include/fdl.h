@@ -101,9 +101,12 @@ FDL_API fdl_status fdl_forward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * GPU, held from the moment the library is loaded there until the process ends).  The call allocates and frees
  * nothing; the first call on a GPU looks up the array's device address (a host-side query, no stream work).
  *
- * Limit: problems that need more than the array holds are rejected with FDL_ERR_WORKSPACE before any device call.  What
- * counts is the forward scratch plus 8 bytes per (row, column tile of 32 to 128) - nothing for the latter on the bf16
- * path with K % 128 == 0, N % 256 == 0, N <= 8192, M >= 128.  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
+ * Limit: rejected with FDL_ERR_WORKSPACE before any device call are the problems that count for more than the array
+ * holds.  What counts, independent of the kernels a problem takes today: 8 bytes per (row, column tile of 32 to 128) -
+ * nothing for them on the bf16 path with K % 128 == 0, N % 256 == 0, N <= 8192, M >= 128 - plus, where bf16 N and K are
+ * multiples of 8 off the tile, the zero-padded weights and last rows of X.  Scratch beyond that is optional: where the
+ * array has no room for it the call runs without (weights not transposed, a reduction not split, X not copied, the
+ * kernel that needs none).  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
  * one GPU (different streams, different host threads) race: order them on one stream or with events.
  */
 #define FDL_STATIC_SCRATCH_BYTES (16 * 1024 * 1024)
@@ -143,8 +146,10 @@ FDL_API fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
 /*
  * Forward pass for inference (the paper's experiments are mostly forward kernels: section "Optimizing individual
  * operations", task table of the robust kernel benchmark): Y as fdl_forward computes it, and nothing saved for a
- * backward pass.  The pre-activation passes through Y itself and is normalised in place, so the workspace holds no
- * M x N tensor: row statistics, and for batches of 16384 rows and more on the tuned bf16 kernels a transposed copy of W (2 N K bytes):
+ * backward pass.  The pre-activation passes through Y itself and is normalised in place.  The workspace holds row
+ * statistics and what the contraction needs: on the tuned bf16 kernels a transposed copy of W for batches of 16384 rows
+ * and more (2 N K bytes), zero-padded copies of W and X where N or K is off the tile, and partial sums (at most 64 MB) where
+ * few output tiles make it split its reduction; for fp32 storage the partial sums of the last, incomplete round of tiles:
  * fdl_forward_inference_workspace_bytes bytes (0 for an invalid dtype or shape), 256-byte aligned.
  * in : X [M,K], W [N,K] (dt);  b, gamma, beta [N] fp32;  eps >= 0.     out: Y [M,N] (dt).
  */
@@ -199,7 +204,8 @@ FDL_API fdl_status fdl_rmsnorm_forward(fdl_dtype dt, int64_t M, int64_t N,
  * "Highlighted CUDA Kernels: Analysis", LlamaFFW: three matrix products and a fused SiLU-multiply, no biases):
  *   Y = ( SiLU(X Wg^T) * (X Wu^T) ) Wd^T,     SiLU(z) = z / (1 + exp(-z)).
  * in : X [M,D], Wg, Wu [H,D], Wd [D,H] (dt).     out: Y [M,D] (dt).
- * Workspace: fdl_llama_ffn_workspace_bytes bytes (the two M x H intermediates; 0 for an invalid dtype or shape).
+ * Workspace: fdl_llama_ffn_workspace_bytes bytes (the two M x H intermediates, and copies of operands
+ * where the tuned kernels want them transposed or padded; 0 for an invalid dtype or shape).
  */
 FDL_API size_t fdl_llama_ffn_workspace_bytes(fdl_dtype dt, int64_t M, int64_t D, int64_t H);
 FDL_API fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, int64_t H,
@@ -211,7 +217,7 @@ FDL_API fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, int
  * followed by many timed runs, appendix "Kernel Evaluation Environment"; this hook lets a harness time
  * each phase of a call with HIP events on the call's own stream).
  *
- * Phases: forward = F1 (GEMM + fused epilogue), FS (statistics merge), F2 (normalise);
+ * Phases: forward = F1 (GEMM + fused epilogue), FS (nothing: the statistics are F2's), F2 (statistics + normalise);
  *         backward = B1 (row pass), B2 (column reduce), B3 (dX GEMM), B4 (dW GEMM).
  * `events` is a HOST array of 2*FDL_PHASE_COUNT hipEvent_t handles created by the caller (or NULL to switch
  * the instrumentation off, the default).  While set, fdl_forward / fdl_backward record events[2*p] just
