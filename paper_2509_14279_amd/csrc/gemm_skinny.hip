@@ -213,12 +213,16 @@ template <int EPI> void dispatch_skinny(const SkinnyParams& p, hipStream_t s) {
 // tiled one, K x N and rows: 4096 x 4096: 128 29 / 31, 256 48 / 35; 1024 x 1024: 512 11 / 24, 1536 24 / 25; 2048 x 2048: 512
 // 27 / 28, 768 38 / 31; 4096 x 1024: 384 33 / 34, 1536 72 / 41.  Where only the generic kernel is left (odd widths and little
 // work), up to 1.5 M outputs, or 0.5 M for odd rows (771 x 1537: 256 rows 17 / 24, 384 24.5 / 24.2).  Below 128 rows the
-// tiled kernel does not run, and the generic one is slower at every size (4096 x 4096, 64 rows: 20 / 88).
+// tiled kernel does not run, and the generic one is slower at every size (4096 x 4096, 64 rows: 20 / 88).  Its price holds
+// while X stays in the caches: whole inference calls with 64 columns, this kernel / the tiled one: 4096 x 1024 24 / 37,
+// 4096 x 4096 65 / 91, 16384 x 1024 about 58 / 44; odd rows against the generic one: 2048 x 771 x 33 22 / 31, 4096 rows 35 / 32.
+static int64_t skinny_rows(int64_t K) { return K % 8 == 0 ? 4096 : 2048; }
 static double skinny_cost(int64_t M, int64_t K, int64_t N) {
   return 4.0 + (K % 8 == 0 ? 10.5e-9 : 34e-9) * (double)((M + 63) / 64 * 64) * (double)K * (double)N;
 }
 bool skinny_supported(int64_t M, int64_t K, int64_t N) {
   if (M < 128) return true;
+  if (M > skinny_rows(K)) return false;
   const bool pad = fast_padded_supported(M, K, N);
   if (!pad && !fast_f1_supported(M, K, N)) return M * N <= (K % 8 == 0 ? 3 << 19 : 1 << 19);
   return skinny_cost(M, K, N) < fast_xwt_cost(M, K, N, nullptr) + (pad ? 12.0 : 0.0);
@@ -226,6 +230,7 @@ bool skinny_supported(int64_t M, int64_t K, int64_t N) {
 // the gate and up products together: the tiled kernel has a tile of 128 columns and no split
 bool skinny_gate_supported(int64_t M, int64_t D, int64_t H) {
   if (M < 128) return true;
+  if (M > skinny_rows(D)) return false;
   const bool fits = fast_gate_supported(M, D, H);
   if (!fits && M * D * H < kStageFromWork) return M * 2 * H <= (D % 8 == 0 ? 3 << 19 : 1 << 19);
   const int64_t tiles = ((H + 127) / 128) * ((M + 255) / 256);

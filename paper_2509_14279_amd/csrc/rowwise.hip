@@ -21,8 +21,10 @@ namespace {
 // vectors c*64 + l, c < CH, of its row (every load and store of a wavefront covers 1 KB of one row); the next
 // row's vectors are fetched while the current row is processed.  gamma and beta sit in LDS, permuted so that a
 // lane's four 16-byte reads per vector are lane-contiguous.  Workgroups of NT/64 wavefronts walk the rows with
-// stride.  WPR > 1: neighbouring wavefronts share a row and exchange their sums through LDS (as a workgroup of 1024 threads per row the same normalisation of 4096 x 16384 took 66 - 89 us: its two
-// reductions stop every wavefront of the compute unit).
+// stride.  WPR > 1: neighbouring wavefronts share a row and exchange their sums through LDS (as a workgroup of 1024
+// threads per row the same normalisation of 4096 x 16384 took 66 - 89 us: its two reductions stop every wavefront of the
+// compute unit).  WPR = 8, rows above 16384: gamma and beta do not fit in LDS and are read from the caches at each row
+// (LayerNorm of 4096 x 32768: 105 us, 176 with the row reread from the caches for each sweep; x 30003: 163, 293).
 // FIT_FULL: N == 512 CH, every lane holds every vector.  FIT_VECTORS (N % 8 == 0): the vectors past the end of the row
 // are fetched from a clamped address, masked to zero (GELU(0) = 0 adds nothing to the sum), left out of the squared
 // deviations and never stored; the code stays free of divergent branches either way.  FIT_ANY: rows start at any element
@@ -34,6 +36,8 @@ namespace {
 // beta (RMSNorm forward: y = x (mean(x^2) + eps)^-1/2 w; mean and rstd are not written).
 enum { ACT_GELU = 0, ACT_NONE = 1, ACT_RMS = 2 };
 enum { FIT_FULL = 0, FIT_VECTORS = 1, FIT_ANY = 2 };
+// gamma and beta of 512 vectors' columns take 4 KB per 64 vectors
+constexpr bool affine_in_lds(int groups) { return groups <= 32; }
 template <int CH, int FIT, int NT, int ACT, int WPR>
 __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float eps, const bf16_t* Z,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
@@ -50,14 +54,15 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
   typedef GaussTable<false> GT;
   typedef __attribute__((address_space(3))) float lds_float;
-  float* htab = reinterpret_cast<float*>(gb + CH * WPR * 4 * 64);     // Phi - 1/2 for every bf16 magnitude
+  constexpr bool kAffineLds = affine_in_lds(CH * WPR);
+  float* htab = reinterpret_cast<float*>(gb + (kAffineLds ? CH * WPR * 4 * 64 : 0));     // Phi - 1/2 for every bf16 magnitude
   const uint32_t horg = GT::origin((uint32_t)(uintptr_t)(const lds_float*)htab);
   if (ACT == ACT_GELU) GT::build(htab, threadIdx.x, NT);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: row addresses stay scalar
   const int nvec = (int)(N >> 3);              // whole vectors of a row
   const int rest = ANY ? (int)(N & 7) : 0;     // elements of its partial one
-  for (int idx = threadIdx.x; idx < CH * WPR * 64; idx += NT) {
+  for (int idx = threadIdx.x; idx < (kAffineLds ? CH * WPR * 64 : 0); idx += NT) {
     const int c = idx >> 6, l = idx & 63;
     if (ANY && idx >= nvec) {
       const int have = idx == nvec ? rest : 0;
@@ -196,7 +201,26 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
 #pragma unroll
     for (int c = 0; c < CH; c++) {
       const int cg = c * WPR + sub;
-      const f32x4 g0 = gb[(cg * 4 + 0) * 64 + lane], g1 = gb[(cg * 4 + 1) * 64 + lane];
+      f32x4 g0, g1, b0 = {}, b1 = {};
+      if constexpr (kAffineLds) {
+        g0 = gb[(cg * 4 + 0) * 64 + lane], g1 = gb[(cg * 4 + 1) * 64 + lane];
+        if (ACT != ACT_RMS) b0 = gb[(cg * 4 + 2) * 64 + lane], b1 = gb[(cg * 4 + 3) * 64 + lane];
+      } else if (!ANY || have[c] == 8) {
+        // (voff of a vector past the end is that of one inside)
+        const int at = FULL ? (cg * 64 + lane) * 8 : voff[c];
+        g0 = *reinterpret_cast<const f32x4*>(gamma + at), g1 = *reinterpret_cast<const f32x4*>(gamma + at + 4);
+        if (ACT != ACT_RMS) b0 = *reinterpret_cast<const f32x4*>(beta + at), b1 = *reinterpret_cast<const f32x4*>(beta + at + 4);
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+          g0[v] = v < have[c] ? gamma[nvec * 8 + v] : 0.0f;
+          g1[v] = v + 4 < have[c] ? gamma[nvec * 8 + v + 4] : 0.0f;
+          if (ACT != ACT_RMS) {
+            b0[v] = v < have[c] ? beta[nvec * 8 + v] : 0.0f;
+            b1[v] = v + 4 < have[c] ? beta[nvec * 8 + v + 4] : 0.0f;
+          }
+        }
+      }
       bf16x8 o;
       if (ACT == ACT_RMS) {
 #pragma unroll
@@ -205,7 +229,6 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
           o[v + 4] = (bf16_t)(a[c][v + 4] * rs * g1[v]);
         }
       } else {
-        const f32x4 b0 = gb[(cg * 4 + 2) * 64 + lane], b1 = gb[(cg * 4 + 3) * 64 + lane];
 #pragma unroll
         for (int v = 0; v < 4; v++) {
           o[v] = (bf16_t)__builtin_fmaf(a[c][v] * rs, g0[v], b0[v]);
@@ -934,7 +957,7 @@ template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int gro
 template <int CH, int FIT, int NT, int ACT, int WPR = 1>
 void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float eps, const bf16_t* Z, const float* gamma,
                         const float* beta, bf16_t* Y, float* mean, float* rstd) {
-  constexpr size_t kLds = (size_t)CH * WPR * 4096 + GaussTable<false>::kBytes;
+  constexpr size_t kLds = (affine_in_lds(CH * WPR) ? (size_t)CH * WPR * 4096 : 0) + GaussTable<false>::kBytes;
   auto kern = f2_rows_kernel<CH, FIT, NT, ACT, WPR>;
   if constexpr (kLds > 64 * 1024) {
     static OnceFlags configured;
@@ -960,17 +983,18 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   int64_t wgs = (M + per_wg - 1) / per_wg;
   DeviceInfo di;
   if (!device_info(&di)) return;
-  const int64_t cap = (int64_t)di.cus * (16 / ch > wpr ? 16 / ch / wpr : 1);
+  const int64_t cap = (int64_t)di.cus * (wpr == 8 ? 2 : (16 / ch > wpr ? 16 / ch / wpr : 1));
   if (wgs > cap) wgs = cap;
 #define FDL_F2R(CHH, FIT, WPR)                                                                                        \
   launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
 #define FDL_F2R_FIT(FIT)                                                                                              \
   do {                                                                                                                \
     if (ch == 2) FDL_F2R(2, FIT, 1); else if (ch == 4) FDL_F2R(4, FIT, 1); else if (wpr == 1) FDL_F2R(8, FIT, 1);     \
-    else if (wpr == 2) FDL_F2R(8, FIT, 2); else FDL_F2R(8, FIT, 4);                                                   \
+    else if (wpr == 2) FDL_F2R(8, FIT, 2); else if (wpr == 4) FDL_F2R(8, FIT, 4); else FDL_F2R(8, FIT, 8);            \
   } while (0)
   if (fit == FIT_FULL) {
-    if (ch == 2) FDL_F2R(2, FIT_FULL, 1); else if (ch == 4) FDL_F2R(4, FIT_FULL, 1); else if (ch == 8) FDL_F2R(8, FIT_FULL, 1);
+    if (ch == 2) FDL_F2R(2, FIT_FULL, 1); else if (ch == 4) FDL_F2R(4, FIT_FULL, 1);
+    else if (ch == 8 && wpr == 1) FDL_F2R(8, FIT_FULL, 1); else if (ch == 8) FDL_F2R(8, FIT_FULL, 8);
     else if (wpr == 1) FDL_F2R(16, FIT_FULL, 1); else FDL_F2R(16, FIT_FULL, 2);
   } else if (fit == FIT_VECTORS) {
     FDL_F2R_FIT(FIT_VECTORS);
@@ -981,7 +1005,7 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
 #undef FDL_F2R
 }
 
-// Which kernel normalises rows of N elements: up to 16384, bf16 rows go one to a wavefront or to two or four of them,
+// Which kernel normalises rows of N elements: up to 32768, bf16 rows go one to a wavefront or to two, four or eight of them,
 // fp32 rows one to a workgroup that is as small as the row allows; longer ones are streamed.
 template <class T, int ACT>
 void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta, void* Y,
@@ -1003,7 +1027,7 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
     if (vectors <= 2048) FDL_ROW(512, 4);
     if (vectors <= 4096) FDL_ROW(1024, 4);
 #undef FDL_ROW
-  } else if (N <= 16384) {
+  } else if (N <= 32768) {
     launch_rows_act<ACT>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
     return;
   }

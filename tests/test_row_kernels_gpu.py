@@ -12,7 +12,7 @@ import harness as H
 
 pytestmark = pytest.mark.gpu
 
-BF16_WIDTHS = [7, 511, 1025, 4095, 8191, 8193, 8208, 16383, 16384, 16391]
+BF16_WIDTHS = [7, 511, 1025, 4095, 8191, 8193, 8208, 16383, 16384, 16391, 32760, 32768, 32771]
 F32_WIDTHS = [3, 257, 1023, 1026, 4097, 8192, 16383, 16388]
 WIDTHS = [("bf16", n) for n in BF16_WIDTHS] + [("f32", n) for n in F32_WIDTHS]
 
@@ -41,7 +41,8 @@ def test_stand_alone_norms(dtype, N, M):
 
 @pytest.mark.parametrize("dtype,M,N", [("bf16", 37, 8193), ("bf16", 530, 16384), ("bf16", 65, 11570), ("bf16", 70, 16392),
                                        ("bf16", 2600, 1030), ("bf16", 300, 4093), ("f32", 70, 4100), ("f32", 33, 8190),
-                                       ("f32", 2600, 515), ("f32", 40, 16390)])
+                                       ("f32", 2600, 515), ("f32", 40, 16390), ("bf16", 530, 32768),
+                                       ("bf16", 33, 30003), ("bf16", 20, 32776)])
 def test_forward_and_backward_of_the_block(dtype, M, N):
     cfg = I.custom(dtype, M, 16, N, seed=8100 + M + N)
     print(f"[rows] {cfg.name}", flush=True)
