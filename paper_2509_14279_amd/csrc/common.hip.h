@@ -171,6 +171,13 @@ template <bool kPair, int NT> struct ActTable<bf16_t, kPair, NT> {
 };
 
 // ---------------------------------------------------------------------------------------------
+// Sums over the wavefronts that share a row pass through LDS: each wavefront writes its part into a slot, meets one barrier
+// and reads the others' parts.  With one barrier per sum two consecutive sums must not share a slot: a wavefront may write the
+// next sum's slot while another still reads this one's, and only the barrier after that shows that it is done.  So the two
+// slots take turns from sum to sum, across rows: sum k of trip t of a walk with so many sums per row.
+constexpr int row_sum_slot(int sums_per_row, int trip, int k) { return (sums_per_row * trip + k) & 1; }
+
+// ---------------------------------------------------------------------------------------------
 // Vector access helpers: V consecutive storage elements <-> V values of the arithmetic type.
 template <class T, int V> struct VecIO;
 

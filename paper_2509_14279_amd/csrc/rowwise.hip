@@ -85,15 +85,17 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   const int64_t nw = (int64_t)gridDim.x * (NT / 64 / WPR);
   const float inv_n = 1.0f / (float)N;
   const int sub = WPR == 1 ? 0 : wave % WPR;   // which part of every vector group this wavefront of the row holds
-  // sum over the wavefronts of a row (pass k of a row: slot k; see the loop on why one barrier each is enough)
+  // sum k of this trip's row over the wavefronts that share it (row_sum_slot: why one barrier each is enough)
+  int trip = 0;
   auto row_sum = [&](float x, int k) -> float {
     x = wave_sum(x);
     if constexpr (WPR > 1) {
-      if (lane == 0) pair[k][wave] = x;
+      const int slot = row_sum_slot(ACT == ACT_RMS ? 1 : 2, trip, k);
+      if (lane == 0) pair[slot][wave] = x;
       __syncthreads();
-      x = pair[k][wave - sub];
+      x = pair[slot][wave - sub];
 #pragma unroll
-      for (int w = 1; w < WPR; w++) x += pair[k][wave - sub + w];
+      for (int w = 1; w < WPR; w++) x += pair[slot][wave - sub + w];
     }
     return x;
   };
@@ -140,9 +142,8 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
     for (int c = 0; c < CH; c++) fetch1(c, zr);
   }
   // Where wavefronts share rows, those of a workgroup stay together (barriers): the last trip may find some of them past
-  // the last row, which they then redo without storing.  A sum's slot is written again only after the barrier of the
-  // other sum, which every wavefront reaches after it has read the slot.
-  for (int64_t lead = (int64_t)blockIdx.x * (NT / 64 / WPR); WPR == 1 ? row < M : lead < M; row += nw, lead += nw) {
+  // the last row, which they then redo without storing.
+  for (int64_t lead = (int64_t)blockIdx.x * (NT / 64 / WPR); WPR == 1 ? row < M : lead < M; row += nw, lead += nw, trip++) {
     const bool live = WPR == 1 || row < M;
     float a[CH][8];
     float sum = 0.0f;

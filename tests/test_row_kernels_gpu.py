@@ -52,3 +52,24 @@ def test_forward_and_backward_of_the_block(dtype, M, N):
     ref = O.forward_backward(n["X"], n["W"], n["b"], n["gamma"], n["beta"], n["dY"], cfg.eps)
     for k in H.OUTPUTS + ("mean",):
         H.check(dtype, k, H.to_f64(got[k]), ref[k])
+
+
+@pytest.mark.parametrize("N", [4104, 5003, 8200, 12345, 16384, 16392, 20001, 32768])
+def test_rows_do_not_depend_on_the_rows_beside_them(N):
+    # rows shared by two, four and eight wavefronts: a workgroup that walks several rows must give each the bits it has when
+    # every workgroup holds one row (at most 256 rows: one trip)
+    M = 5000
+    t = I.generate_norm("bf16", 256, N, seed=8200 + N)
+    A = t["A"].to("cuda", torch.bfloat16)
+    A = torch.cat([A.roll(k, 0) * (1.0 + k / 8) for k in range(20)])[:M].contiguous()
+    gamma, beta = t["gamma"].to("cuda"), t["beta"].to("cuda")
+
+    def run(A):
+        m = A.shape[0]
+        out = [torch.empty_like(A), torch.empty_like(A), torch.empty(m, device="cuda"), torch.empty(m, device="cuda")]
+        api.fdl_rmsnorm_forward("bf16", A, gamma, 1e-5, out[0])
+        api.fdl_layernorm_forward("bf16", A, gamma, beta, 1e-5, *out[1:])
+        return out
+
+    for whole, parts in zip(run(A), zip(*[run(A[i:i + 256].contiguous()) for i in range(0, M, 256)])):
+        assert torch.equal(whole.view(torch.uint8), torch.cat(parts).view(torch.uint8))
