@@ -239,6 +239,36 @@ template <> __device__ __forceinline__ float wave_sum<float>(float v) {
   v += dpp_f<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3: row 3 now holds the total
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
+// fp64, the same way in two halves
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ double dpp_d(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xF, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <> __device__ __forceinline__ double wave_sum<double>(double v) {
+  v += dpp_d<0xB1, 0xF>(v);
+  v += dpp_d<0x4E, 0xF>(v);
+  v += dpp_d<0x141, 0xF>(v);
+  v += dpp_d<0x140, 0xF>(v);
+  v += dpp_d<0x142, 0xA>(v);
+  v += dpp_d<0x143, 0xC>(v);
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// v^-1/2 to the last bit of fp32 or nearly so: the hardware's estimate (about 2^-23) and one Newton step in fp64 (1e-13);
+// outside the estimate's range - variances that vanish, infinities - the library's square root.  v is wave-uniform.
+__device__ __forceinline__ float inv_sqrt(double v) {
+  const float x = (float)v;
+  if (x > 1e-30f && x < 1e30f) {
+    const double r = (double)__builtin_amdgcn_rsqf(x);
+    return (float)(r * (1.5 - 0.5 * v * r * r));
+  }
+  return (float)(1.0 / sqrt(v));
+}
 
 // ---------------------------------------------------------------------------------------------
 // Column sums from per-group partial sums, colpart [groups][nwhich][N]: 64 consecutive columns per workgroup of 1024

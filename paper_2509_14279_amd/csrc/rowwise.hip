@@ -11,8 +11,20 @@
 #include "common.hip.h"
 #include "internal.h"
 
+#include <type_traits>
+
 namespace fdl {
 namespace {
+
+__device__ __forceinline__ float read_lane(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+__device__ __forceinline__ double read_lane(double v, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 
 // ------------------------------------------------------------------------------------------------
 // F2 with its own statistics, narrow rows (bf16 storage, N <= 512 CH): a wavefront owns a row and keeps it in
@@ -47,10 +59,17 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   // both of its factors alive for every element of the row); the fused operations wanted are written out
 #pragma clang fp contract(off)
   constexpr bool FULL = FIT == FIT_FULL, ANY = FIT == FIT_ANY;
+  // The block's statistics (ACT_GELU; saved, and multiplied into everything the backward pass forms): fp32 inside a vector -
+  // up to 1024 columns, where a row has little other work, inside a row of 16 lanes - and fp64 from there on, as is rstd.
+  // (fp32 throughout, inference 65536 x 128 x 512: 61.1 us, so 61.9, fp64 from the vector on 64.2; 4096 x 128 x 16384: 108.8,
+  // now 110.9; no difference at 4096 and 8192 columns.)  The stand-alone norms keep fp32 (LayerNorm 65536 x 512 22.5 us, 24.3).
+  constexpr bool kWide = ACT == ACT_GELU, kShort = CH * WPR <= 2;
+  typedef typename std::conditional<kWide && !kShort, double, float>::type sum_t;     // of a lane
+  typedef typename std::conditional<kWide, double, float>::type stat_t;               // of a row
   typedef __bf16 bf16x8_u __attribute__((ext_vector_type(8), aligned(2)));
   typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
   extern __shared__ f32x4 gb[];   // [CH * WPR][4][64]: gamma[0:4], gamma[4:8], beta[0:4], beta[4:8] of each vector
-  __shared__ float pair[2][NT / 64];
+  __shared__ stat_t pair[2][NT / 64];
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
   typedef GaussTable<false> GT;
   typedef __attribute__((address_space(3))) float lds_float;
@@ -83,12 +102,18 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   }
   __syncthreads();
   const int64_t nw = (int64_t)gridDim.x * (NT / 64 / WPR);
-  const float inv_n = 1.0f / (float)N;
+  const stat_t inv_n = (stat_t)1 / (stat_t)N;
   const int sub = WPR == 1 ? 0 : wave % WPR;   // which part of every vector group this wavefront of the row holds
   // sum k of this trip's row over the wavefronts that share it (row_sum_slot: why one barrier each is enough)
   int trip = 0;
-  auto row_sum = [&](float x, int k) -> float {
-    x = wave_sum(x);
+  auto row_sum = [&](sum_t part, int k) -> stat_t {
+    stat_t x;
+    if constexpr (kWide && kShort) {
+      part = row16_sum(part);
+      x = ((double)read_lane(part, 0) + (double)read_lane(part, 16)) + ((double)read_lane(part, 32) + (double)read_lane(part, 48));
+    } else {
+      x = wave_sum(part);
+    }
     if constexpr (WPR > 1) {
       const int slot = row_sum_slot(ACT == ACT_RMS ? 1 : 2, trip, k);
       if (lane == 0) pair[slot][wave] = x;
@@ -146,10 +171,11 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   for (int64_t lead = (int64_t)blockIdx.x * (NT / 64 / WPR); WPR == 1 ? row < M : lead < M; row += nw, lead += nw, trip++) {
     const bool live = WPR == 1 || row < M;
     float a[CH][8];
-    float sum = 0.0f;
+    sum_t sum = 0;
     const bf16_t* znext = Z + (row + nw < M ? row + nw : M - 1) * N;
 #pragma unroll
     for (int c = 0; c < CH; c++) {
+      float sum8 = kWide ? 0.0f : (float)sum;          // (fp32 throughout: one chain over the lane's vectors)
 #pragma unroll
       for (int h = 0; h < 4; h++) {
         const uint32_t w = (FULL || ANY) ? raw[c][h] : (raw[c][h] & keep[c]);
@@ -165,13 +191,14 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
           a[c][2 * h + 1] = z1;
         }
         if (ACT == ACT_RMS) {
-          sum = __builtin_fmaf(z0, z0, sum);
-          sum = __builtin_fmaf(z1, z1, sum);
+          sum8 = __builtin_fmaf(z0, z0, sum8);
+          sum8 = __builtin_fmaf(z1, z1, sum8);
         } else {
-          sum += a[c][2 * h];
-          sum += a[c][2 * h + 1];
+          sum8 += a[c][2 * h];
+          sum8 += a[c][2 * h + 1];
         }
       }
+      sum = kWide ? sum + (sum_t)sum8 : (sum_t)sum8;
       // One vector at a time (interleaving all of a row's evaluations would keep their temporaries alive), and as
       // soon as a vector is unpacked its registers take the same vector of the wavefront's next row: the loads
       // trickle out through the whole first sweep and have the rest of the row's work to arrive, while a row of
@@ -184,17 +211,22 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
     if (ACT == ACT_RMS) {
       rs = 1.0f / __builtin_sqrtf(row_sum(sum, 0) * inv_n + eps);   // masked vectors hold zeros: they add nothing
     } else {
-      const float mu = row_sum(sum, 0) * inv_n;
-      float m2 = 0.0f;
+      const float mu = (float)(row_sum(sum, 0) * inv_n);
+      sum_t m2 = 0;
 #pragma unroll
-      for (int c = 0; c < CH; c++)
+      for (int c = 0; c < CH; c++) {
+        float sq8 = kWide ? 0.0f : (float)m2;
 #pragma unroll
         for (int v = 0; v < 8; v++) {
           const float d = a[c][v] - mu;
           a[c][v] = FULL ? d : ((ANY ? v < have[c] : keep[c] != 0u) ? d : 0.0f);
-          m2 = __builtin_fmaf(a[c][v], a[c][v], m2);
+          sq8 = __builtin_fmaf(a[c][v], a[c][v], sq8);
         }
-      rs = 1.0f / __builtin_sqrtf(row_sum(m2, 1) * inv_n + eps);
+        m2 = kWide ? m2 + (sum_t)sq8 : (sum_t)sq8;
+      }
+      const stat_t var = row_sum(m2, 1) * inv_n + (stat_t)eps;
+      if constexpr (kWide) rs = inv_sqrt(var);
+      else rs = 1.0f / __builtin_sqrtf(var);
       if (lane == 0 && sub == 0 && live) { mean[row] = mu; rstd[row] = rs; }
     }
     if (!live) continue;
@@ -390,16 +422,6 @@ __global__ __launch_bounds__(256) void b1a_kernel(int64_t M, int64_t N, const T*
     wg_sum2<C, 4>(s1, s2, red[par]);
     if (threadIdx.x == 0) { c12[row] = s1 / (C)N; c12[M + row] = s2 / (C)N; }
   }
-}
-
-__device__ __forceinline__ float read_lane(float v, int l) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
-}
-__device__ __forceinline__ double read_lane(double v, int l) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
 // B1b (two-kernel path): dZ and column partials, given c1 and c2.

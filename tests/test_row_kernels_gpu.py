@@ -73,3 +73,21 @@ def test_rows_do_not_depend_on_the_rows_beside_them(N):
 
     for whole, parts in zip(run(A), zip(*[run(A[i:i + 256].contiguous()) for i in range(0, M, 256)])):
         assert torch.equal(whole.view(torch.uint8), torch.cat(parts).view(torch.uint8))
+
+
+@pytest.mark.parametrize("M,K,N", [(300, 100, 1000), (300, 77, 4095), (300, 64, 8200), (200, 64, 12345), (200, 64, 16384),
+                                   (100, 64, 30001)])
+def test_statistics_of_nearly_constant_rows(M, K, N):
+    # Z is 8 with a spread of one bf16 step (1/16) and less: GELU(z) = z to fp32, sums of such values are exact, and squared
+    # deviations of few distinct sizes make every rounding of a long chain go the same way.  The saved mean is the rounded
+    # exact one (2^-24); 1/rstd^2 carries at most the chain of a vector's eight squares (8 roundings) and rstd its own
+    # rounding: 5 x 2^-24.
+    cfg = I.custom("bf16", M, K, N, seed=8300 + M + N)
+    t = I.generate(cfg, with_dY=False)
+    t["W"] = (t["W"] * 0.02).to(torch.bfloat16).float()
+    t["b"] = t["b"] + 8.0
+    got = H.run_fdl(cfg, t, backward=False)
+    A = O.gelu(H.to_f64(got["Z"]))
+    mean, rstd = A.mean(axis=1), (A.var(axis=1) + cfg.eps) ** -0.5
+    assert np.abs(H.to_f64(got["mean"]) / mean - 1).max() <= 2.0 ** -24 * 1.001
+    assert np.abs(H.to_f64(got["rstd"]) / rstd - 1).max() <= 5 * 2.0 ** -24
