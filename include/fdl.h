@@ -149,7 +149,8 @@ FDL_API fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * backward pass.  The pre-activation passes through Y itself and is normalised in place.  The workspace holds row
  * statistics and what the contraction needs: on the tuned bf16 kernels a transposed copy of W for batches of 16384 rows
  * and more (2 N K bytes), zero-padded copies of W and X where N or K is off the tile, and partial sums (at most 64 MB) where
- * few output tiles make it split its reduction; for fp32 storage the partial sums of the last, incomplete round of tiles:
+ * few output tiles make it split its reduction; for fp32 storage the partial sums of the last, incomplete round of tiles;
+ * for rows above 32768 (bf16) or 16384 (fp32) elements 16 bytes per row and 4096 or 2048 columns:
  * fdl_forward_inference_workspace_bytes bytes (0 for an invalid dtype or shape), 256-byte aligned.
  * in : X [M,K], W [N,K] (dt);  b, gamma, beta [N] fp32;  eps >= 0.     out: Y [M,N] (dt).
  */

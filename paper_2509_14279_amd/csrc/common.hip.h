@@ -132,7 +132,7 @@ template <bool kPair> struct GaussTable {
 };
 
 // What the row kernels ask: T = float evaluates in fp64, T = bf16 holds the table in the workgroup's LDS (kPair: with
-// z phi(z), for the backward pass).  NT: threads of the workgroup; 0 makes an empty object (no activation).
+// z phi(z), for the backward pass).  NT: threads of the workgroup.
 template <class T, bool kPair, int NT> struct ActTable;
 template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
   __device__ __forceinline__ void build() {}
@@ -141,10 +141,6 @@ template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
     Phi = 0.5 * erfc(-z * 0.70710678118654752440);
     zphi = z * (exp(-0.5 * z * z) * 0.39894228040143267794);
   }
-};
-template <bool kPair> struct ActTable<bf16_t, kPair, 0> {
-  __device__ __forceinline__ void build() {}
-  static __device__ __forceinline__ float gelu(float z) { return z; }
 };
 template <bool kPair, int NT> struct ActTable<bf16_t, kPair, NT> {
   typedef GaussTable<kPair> GT;
@@ -246,11 +242,15 @@ template <int CTRL, int ROW_MASK> __device__ __forceinline__ double dpp_d(double
   const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xF, false);
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-template <> __device__ __forceinline__ double wave_sum<double>(double v) {
+__device__ __forceinline__ double row16_sum(double v) {
   v += dpp_d<0xB1, 0xF>(v);
   v += dpp_d<0x4E, 0xF>(v);
   v += dpp_d<0x141, 0xF>(v);
   v += dpp_d<0x140, 0xF>(v);
+  return v;
+}
+template <> __device__ __forceinline__ double wave_sum<double>(double v) {
+  v = row16_sum(v);
   v += dpp_d<0x142, 0xA>(v);
   v += dpp_d<0x143, 0xC>(v);
   const uint64_t b = __builtin_bit_cast(uint64_t, v);

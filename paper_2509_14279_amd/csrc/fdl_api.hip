@@ -106,6 +106,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.f1_wb = pick_generic_wb(Mp, N);
   size_t off = 0;
   const bool tiled = q.f1_fast && !q.f1_skinny;
+  q.off_rows = off; off += align256(f2_part_bytes(dt, Mp, N));
   q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K, q.stage_x != 0) : fast_f1_tail_bytes(M, K)));
   q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
@@ -320,7 +321,7 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
   }
   {
     PhaseTimer t(FDL_PHASE_F2, s);
-    launch_f2(p.dt, M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
+    launch_f2(p.dt, M, N, eps, Zsave, gamma, beta, Y, mean, rstd, ws + p.off_rows, s);
   }
   return launch_status();
 }
@@ -384,7 +385,7 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
     p.fwd_bytes = p.off_bpad_f + align256((size_t)fast_pad_dim(N) * 4);
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) {
-    p.pad = 0; p.f1_fast = 0; p.fwd_bytes = 0;        // no room for the padded copies either: the generic kernel needs none,
+    p.pad = 0; p.f1_fast = 0; p.fwd_bytes = p.off_xtail;   // no room for the padded copies either: the generic kernel needs none,
     p.f1_s64 = f64_unsplit(M, N);                     // nor the fp64 kernel, with all tiles whole
   }
   if (!forward_args_aligned(X, W, b, gamma, beta, Y, Zsave, mean, rstd)) return FDL_ERR_ALIGN;

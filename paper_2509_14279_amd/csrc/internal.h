@@ -52,6 +52,7 @@ struct Plan {
   int f1_wb;              // generic kernel: 16x16 blocks per wave tile side (wave tile = 16*wb)
   int f1_wt;              // 1: the fast kernel reads the weights from a transposed copy (large batches)
   size_t off_wt;          // bf16 [K][N], the last region of the forward workspace
+  size_t off_rows;        // F2's scratch for rows beyond its registers, the first
   F64Split f1_s64;        // fp32 storage
   int f1_split;           // bf16, tiled: parts of the reduction where there are few tiles
   size_t off_part;        // their sums
@@ -117,9 +118,10 @@ void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bia
                 hipStream_t s);
 
 // ---- row-wise / column-wise phases ------------------------------------------------------------
-// row statistics of GELU(Zsave) and the normalised output (Zsave and Y may be the same buffer)
+// row statistics of GELU(Zsave) and the normalised output (Zsave and Y may be the same buffer); part: f2_part_bytes of scratch
+size_t f2_part_bytes(int dt, int64_t M, int64_t N);
 void launch_f2(int dt, int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
-               float* mean, float* rstd, hipStream_t s);
+               float* mean, float* rstd, void* part, hipStream_t s);
 void launch_b1a(int dt, int64_t M, int64_t N, const void* dY, const void* Zsave, const float* gamma,
                 const float* mean, const float* rstd, void* c12, hipStream_t s);
 // ldz: pitch of dZ in elements (N, or N rounded up to the tile in the padded mode of the fast contractions)

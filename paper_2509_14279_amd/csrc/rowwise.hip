@@ -813,17 +813,198 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
   }
 }
 
-// The same for rows too long for the registers of a workgroup: the row is read from memory (and then from the caches)
+// F2 for rows too long for the registers of a workgroup: two launches over segments of kLongVectors vectors per thread.  The
+// first leaves every segment's mean and sum of squared deviations (fp64) in `part` [M][segments], the second merges a row's
+// and normalises its segment.  So GELU is evaluated twice per element and the row read twice, and a few long rows fill the
+// chip: a workgroup takes rows_per_wg rows of one segment (gamma and beta stay in its registers), as many as leave about 2048
+// workgroups.
+// Bound: HBM for bf16, the fp64 erfc for fp32 storage.  One workgroup per row that streams it three times took, whole
+// inference calls, us, that / now: fp32 17 x 42
+// x 24886 141 / 20, 256 x 34 x 44889 343 / 128; bf16 32 x 256 x 78860 236 / 43, 4096 x 256 x 65536 686 / 609; with the sums taken
+// in the contraction's epilogue as well as an earlier form did, which read each row once, 43, 153, 86 and 612.
+constexpr int kLongVectors = 2;
+template <class T> constexpr int64_t long_segment() { return 256 * (16 / (int)sizeof(T)) * kLongVectors; }
+
+// One thread's vectors of a segment: columns, how many elements each has, and the raw values of two rows in flight
+template <class T, bool ANY> struct LongLane {
+  static constexpr int V = 16 / (int)sizeof(T);
+  int64_t col[kLongVectors];
+  int nv[kLongVectors];
+  typename RawVec<T, ANY>::type raw[2][kLongVectors];
+  __device__ __forceinline__ void init(int64_t N, int64_t c0) {
+#pragma unroll
+    for (int s = 0; s < kLongVectors; s++) {
+      col[s] = c0 + (s * 256 + (int)threadIdx.x) * V;
+      const int64_t left = N - col[s];
+      nv[s] = left <= 0 ? 0 : (left > V ? V : (int)left);
+#pragma unroll
+      for (int v = 0; v < V; v++) raw[0][s][v] = raw[1][s][v] = (T)0.0f;
+    }
+  }
+  __device__ __forceinline__ void fetch(int buf, const T* Z, int64_t N, int64_t row, int64_t end) {
+    if (row >= end) return;
+#pragma unroll
+    for (int s = 0; s < kLongVectors; s++)
+      if (nv[s] > 0) raw[buf][s] = row_load<T, ANY>(Z + row * N + col[s], nv[s]);
+  }
+};
+
+// A wavefront's sums are of the differences to its first element: both in one pass, and nothing cancels where the elements
+// are nearly equal.  The four wavefronts' means and sums of squares are then merged.
+template <class T, bool ANY>
+__global__ __launch_bounds__(256) void long_moments_kernel(int64_t M, int64_t N, int segments, int rows_per_wg, const T* Z,
+                                                           double2* __restrict__ part) {
+  typedef typename ComputeOf<T>::type C;
+  constexpr int V = LongLane<T, ANY>::V;
+  __shared__ double red[2][2][4][2];
+  ActTable<T, false, 256> tab;
+  tab.build();
+  const int seg = blockIdx.x % segments, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r0 = (int64_t)(blockIdx.x / segments) * rows_per_wg, r1 = r0 + rows_per_wg < M ? r0 + rows_per_wg : M;
+  LongLane<T, ANY> l;
+  l.init(N, seg * long_segment<T>());
+  double count[4], n = 0.0;                    // elements of each wavefront, and of the segment
+#pragma unroll
+  for (int w = 0; w < 4; w++) {
+    int64_t c = 0;
+#pragma unroll
+    for (int s = 0; s < kLongVectors; s++) {
+      const int64_t left = N - (seg * long_segment<T>() + (s * 256 + w * 64) * V);
+      c += left <= 0 ? 0 : (left > 64 * V ? 64 * V : left);
+    }
+    count[w] = (double)c;
+    n += count[w];
+  }
+  const double inv_n = 1.0 / n, n_wave = count[wave], inv_wave = n_wave > 0.0 ? 1.0 / n_wave : 0.0;
+  l.fetch(0, Z, N, r0, r1);
+  l.fetch(1, Z, N, r0 + 1, r1);
+  // two rows at a time: their reductions overlap and share a barrier
+  for (int64_t row = r0; row < r1; row += 2) {
+    const int slot = row_sum_slot(1, (int)((row - r0) >> 1), 0);
+    double sum[2], sq[2];
+    C base[2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      sum[k] = 0.0; sq[k] = 0.0; base[k] = 0;
+      if (k > 0 && row + k >= r1) continue;                      // (uniform)
+      C a[kLongVectors][V];
+#pragma unroll
+      for (int s = 0; s < kLongVectors; s++)
+#pragma unroll
+        for (int v = 0; v < V; v++) a[s][v] = tab.gelu((C)to_f32<T>(l.raw[k][s][v]));
+      l.fetch(k, Z, N, row + k + 2, r1);
+      base[k] = read_lane(a[0][0], 0);
+#pragma unroll
+      for (int s = 0; s < kLongVectors; s++) {
+        if (l.nv[s] == 0) continue;
+        C ps = 0, pq = 0;
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+          const C d = !ANY || v < l.nv[s] ? a[s][v] - base[k] : (C)0;
+          ps += d;
+          pq = __builtin_elementwise_fma(d, d, pq);
+        }
+        sum[k] += (double)ps;
+        sq[k] += (double)pq;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; k++) { sum[k] = wave_sum(sum[k]); sq[k] = wave_sum(sq[k]); }
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        red[slot][k][wave][0] = (double)base[k] + sum[k] * inv_wave;
+        red[slot][k][wave][1] = sq[k] - sum[k] * sum[k] * inv_wave;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && row + threadIdx.x < r1) {
+      const double (*q)[2] = red[slot][threadIdx.x];
+      double mean = 0.0, m2 = 0.0;
+#pragma unroll
+      for (int w = 0; w < 4; w++) mean += count[w] * q[w][0];
+      mean *= inv_n;
+#pragma unroll
+      for (int w = 0; w < 4; w++) { const double d = q[w][0] - mean; m2 += q[w][1] + count[w] * d * d; }
+      part[(row + threadIdx.x) * segments + seg] = double2{mean, m2};
+    }
+  }
+}
+
+template <class T, bool ANY>
+__global__ __launch_bounds__(256) void long_apply_kernel(int64_t M, int64_t N, int segments, int rows_per_wg, float eps,
+                                                         const T* Z, const double2* __restrict__ part,
+                                                         const float* __restrict__ gamma, const float* __restrict__ beta, T* Y,
+                                                         float* __restrict__ mean_out, float* __restrict__ rstd_out) {
+  typedef typename ComputeOf<T>::type C;
+  constexpr int V = LongLane<T, ANY>::V;
+  __shared__ C stats[2][16][2];                // mean and rstd of sixteen rows, twice
+  ActTable<T, false, 256> tab;
+  tab.build();
+  const int seg = blockIdx.x % segments;
+  const int64_t r0 = (int64_t)(blockIdx.x / segments) * rows_per_wg, r1 = r0 + rows_per_wg < M ? r0 + rows_per_wg : M;
+  LongLane<T, ANY> l;
+  l.init(N, seg * long_segment<T>());
+  float gm[kLongVectors][V], bt[kLongVectors][V];
+#pragma unroll
+  for (int s = 0; s < kLongVectors; s++)
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      gm[s][v] = v < l.nv[s] ? gamma[l.col[s] + v] : 0.0f;
+      bt[s][v] = v < l.nv[s] ? beta[l.col[s] + v] : 0.0f;
+    }
+  const double full = (double)long_segment<T>(), last = (double)(N - (segments - 1) * long_segment<T>());
+  auto process = [&](int buf, int64_t row) {
+    const int at = (int)(row - r0) & 15, half = (int)((row - r0) >> 4) & 1;
+    const C mu = stats[half][at][0], rs = stats[half][at][1];
+    typename RawVec<T, ANY>::type o[kLongVectors];
+#pragma unroll
+    for (int s = 0; s < kLongVectors; s++)
+#pragma unroll
+      for (int v = 0; v < V; v++)
+        o[s][v] = to_storage<T, C>((tab.gelu((C)to_f32<T>(l.raw[buf][s][v])) - mu) * rs * (C)gm[s][v] + (C)bt[s][v]);
+    l.fetch(buf, Z, N, row + 2, r1);
+#pragma unroll
+    for (int s = 0; s < kLongVectors; s++)
+      if (l.nv[s] > 0) raw_store<T, ANY>(Y + row * N + l.col[s], o[s], l.nv[s], l.nv[s]);
+  };
+  l.fetch(0, Z, N, r0, r1);
+  l.fetch(1, Z, N, r0 + 1, r1);
+  for (int64_t row = r0; row < r1; row += 2) {
+    if (((row - r0) & 15) == 0) {
+      // the next sixteen rows' segments merged, sixteen lanes per row (the half written was read before the last barrier)
+      const int t0 = threadIdx.x & 15;
+      const int64_t q = row + (threadIdx.x >> 4);
+      const double2* p = part + (q < M ? q : M - 1) * segments;
+      double mean = 0.0, m2 = 0.0;
+      for (int t = t0; t < segments; t += 16) mean += (t == segments - 1 ? last : full) * p[t].x;
+      mean = row16_sum(mean) / (double)N;
+      for (int t = t0; t < segments; t += 16) {
+        const double d = p[t].x - mean;
+        m2 += p[t].y + (t == segments - 1 ? last : full) * d * d;
+      }
+      const double rstd = 1.0 / sqrt(row16_sum(m2) / (double)N + (double)eps);
+      if (t0 == 0) {
+        C* out = stats[(int)((row - r0) >> 4) & 1][threadIdx.x >> 4];
+        out[0] = (C)mean; out[1] = (C)rstd;
+        if (seg == 0 && q < r1) { mean_out[q] = (float)mean; rstd_out[q] = (float)rstd; }
+      }
+      __syncthreads();
+    }
+    process(0, row);
+    if (row + 1 < r1) process(1, row + 1);
+  }
+}
+
+// The stand-alone norms, which have no scratch, for rows that long: the row is read from memory (and then from the caches)
 // once per sweep, as in the paper's two-step LayerNorm and strided RMSNorm kernels.
 template <class T, int V, int ACT>
-__global__ __launch_bounds__(256) void row_stream_kernel(int64_t M, int64_t N, float eps, const T* A,
+__global__ __launch_bounds__(256) void row_stream_kernel(int64_t M, int64_t N, float eps, const T* __restrict__ A,
                                                          const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                         T* Y, float* __restrict__ mean, float* __restrict__ rstd) {
+                                                         T* __restrict__ Y, float* __restrict__ mean,
+                                                         float* __restrict__ rstd) {
   typedef typename ComputeOf<T>::type C;
   __shared__ C red[2][4][2];
-  ActTable<T, false, ACT == ACT_GELU ? 256 : 0> tab;
-  tab.build();
-  auto act = [&](C x) -> C { return ACT == ACT_GELU ? tab.gelu(x) : x; };
   for (int64_t row = blockIdx.x; row < M; row += gridDim.x) {
     const T* a = A + row * N;
     C s1 = 0, s2 = 0;
@@ -831,7 +1012,7 @@ __global__ __launch_bounds__(256) void row_stream_kernel(int64_t M, int64_t N, f
       C x[V];
       VecIO<T, V>::load(a + col, x);
 #pragma unroll
-      for (int v = 0; v < V; v++) { const C f = act(x[v]); s1 += f; if (ACT == ACT_RMS) s2 += f * f; }
+      for (int v = 0; v < V; v++) { s1 += x[v]; s2 += x[v] * x[v]; }
     }
     wg_sum2<C, 4>(s1, s2, red[0]);
     C mu = 0, rs;
@@ -844,7 +1025,7 @@ __global__ __launch_bounds__(256) void row_stream_kernel(int64_t M, int64_t N, f
         C x[V];
         VecIO<T, V>::load(a + col, x);
 #pragma unroll
-        for (int v = 0; v < V; v++) { const C d = act(x[v]) - mu; d2 += d * d; }
+        for (int v = 0; v < V; v++) { const C d = x[v] - mu; d2 += d * d; }
       }
       wg_sum2<C, 4>(d2, dummy, red[1]);
       rs = (C)1 / sqrt(d2 / (C)N + (C)eps);
@@ -856,7 +1037,7 @@ __global__ __launch_bounds__(256) void row_stream_kernel(int64_t M, int64_t N, f
 #pragma unroll
       for (int v = 0; v < V; v++) {
         if (ACT == ACT_RMS) y[v] = x[v] * rs * (C)gamma[col + v];
-        else y[v] = (act(x[v]) - mu) * rs * (C)gamma[col + v] + (C)beta[col + v];
+        else y[v] = (x[v] - mu) * rs * (C)gamma[col + v] + (C)beta[col + v];
       }
       VecIO<T, V>::store(Y + row * N + col, y);
     }
@@ -1028,11 +1209,18 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
 #undef FDL_F2R
 }
 
-// Which kernel normalises rows of N elements: up to 32768, bf16 rows go one to a wavefront or to two, four or eight of them,
-// fp32 rows one to a workgroup that is as small as the row allows; longer ones are streamed.
+// Which kernel normalises rows of N elements: bf16 rows up to 32768 go one to a wavefront or to two, four or eight of them,
+// fp32 rows up to 16384 one to a workgroup that is as small as the row allows.  Longer ones are streamed by the stand-alone
+// norms and dealt out in segments by the block (part: f2_part_bytes).
+constexpr int64_t kRowsLimitBf16 = 32768, kRowsLimitF32 = 16384;
+size_t f2_part_bytes(int dt, int64_t M, int64_t N) {
+  if (N <= (dt == kF32 ? kRowsLimitF32 : kRowsLimitBf16)) return 0;
+  const int64_t seg = dt == kF32 ? long_segment<float>() : long_segment<bf16_t>();
+  return (size_t)M * (size_t)((N + seg - 1) / seg) * sizeof(double2);
+}
 template <class T, int ACT>
 void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta, void* Y,
-                     float* mean, float* rstd, hipStream_t s) {
+                     float* mean, float* rstd, void* part, hipStream_t s) {
   constexpr int V = 16 / (int)sizeof(T);
   if constexpr (sizeof(T) == 4) {
     const int64_t vectors = (N + V - 1) / V;
@@ -1048,10 +1236,23 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
     if (vectors <= 512) FDL_ROW(256, 2);
     if (vectors <= 1024) FDL_ROW(256, 4);
     if (vectors <= 2048) FDL_ROW(512, 4);
-    if (vectors <= 4096) FDL_ROW(1024, 4);
+    if (N <= kRowsLimitF32) FDL_ROW(1024, 4);
 #undef FDL_ROW
-  } else if (N <= 32768) {
+  } else if (N <= kRowsLimitBf16) {
     launch_rows_act<ACT>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
+    return;
+  }
+  if constexpr (ACT == ACT_GELU) {
+    const int64_t segments = (N + long_segment<T>() - 1) / long_segment<T>();
+    int64_t rows = M * segments / 2048;
+    if (rows < 1) rows = 1;
+    const dim3 grid((unsigned)(segments * ((M + rows - 1) / rows)));
+    double2* moments = static_cast<double2*>(part);
+    auto first = N % V == 0 ? long_moments_kernel<T, false> : long_moments_kernel<T, true>;
+    auto second = N % V == 0 ? long_apply_kernel<T, false> : long_apply_kernel<T, true>;
+    hipLaunchKernelGGL(first, grid, dim3(256), 0, s, M, N, (int)segments, (int)rows, (const T*)A, moments);
+    hipLaunchKernelGGL(second, grid, dim3(256), 0, s, M, N, (int)segments, (int)rows, eps, (const T*)A, moments, gamma, beta,
+                       (T*)Y, mean, rstd);
     return;
   }
   const bool vec = N % V == 0 && ((uintptr_t)A | (uintptr_t)Y) % 16 == 0;
@@ -1061,22 +1262,22 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
 }
 
 void launch_f2(int dt, int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
-               float* mean, float* rstd, hipStream_t s) {
-  if (dt == kF32) launch_row_norm<float, ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
-  else launch_row_norm<bf16_t, ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, s);
+               float* mean, float* rstd, void* part, hipStream_t s) {
+  if (dt == kF32) launch_row_norm<float, ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, part, s);
+  else launch_row_norm<bf16_t, ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, part, s);
 }
 
 // Y = LayerNorm(A) gamma + beta over the last dimension; mean, rstd [M] out
 void launch_layernorm(int dt, int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta,
                       void* Y, float* mean, float* rstd, hipStream_t s) {
-  if (dt == kF32) launch_row_norm<float, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
-  else launch_row_norm<bf16_t, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);
+  if (dt == kF32) launch_row_norm<float, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, nullptr, s);
+  else launch_row_norm<bf16_t, ACT_NONE>(M, N, eps, A, gamma, beta, Y, mean, rstd, nullptr, s);
 }
 
 // Y = A (mean(A^2) + eps)^-1/2 weight over the last dimension
 void launch_rmsnorm(int dt, int64_t M, int64_t N, float eps, const void* A, const float* weight, void* Y, hipStream_t s) {
-  if (dt == kF32) launch_row_norm<float, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, s);
-  else launch_row_norm<bf16_t, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, s);
+  if (dt == kF32) launch_row_norm<float, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, nullptr, s);
+  else launch_row_norm<bf16_t, ACT_RMS>(M, N, eps, A, weight, weight, Y, nullptr, nullptr, nullptr, s);
 }
 
 // groups of the first stage of a column sum over M rows

@@ -42,7 +42,11 @@ def test_stand_alone_norms(dtype, N, M):
 @pytest.mark.parametrize("dtype,M,N", [("bf16", 37, 8193), ("bf16", 530, 16384), ("bf16", 65, 11570), ("bf16", 70, 16392),
                                        ("bf16", 2600, 1030), ("bf16", 300, 4093), ("f32", 70, 4100), ("f32", 33, 8190),
                                        ("f32", 2600, 515), ("f32", 40, 16390), ("bf16", 530, 32768),
-                                       ("bf16", 33, 30003), ("bf16", 20, 32776)])
+                                       ("bf16", 33, 30003), ("bf16", 20, 32776),
+                                       # segments of 4096 (bf16) and 2048 (fp32) columns: a last one of one element, of part
+                                       # of a wavefront, whole; rows that share a workgroup in odd and even numbers; one row
+                                       ("bf16", 1, 36865), ("bf16", 700, 32769), ("bf16", 2300, 40960), ("bf16", 33, 37000),
+                                       ("f32", 1, 18433), ("f32", 600, 16385), ("f32", 1300, 18432), ("f32", 37, 20001)])
 def test_forward_and_backward_of_the_block(dtype, M, N):
     cfg = I.custom(dtype, M, 16, N, seed=8100 + M + N)
     print(f"[rows] {cfg.name}", flush=True)
@@ -76,7 +80,7 @@ def test_rows_do_not_depend_on_the_rows_beside_them(N):
 
 
 @pytest.mark.parametrize("M,K,N", [(300, 100, 1000), (300, 77, 4095), (300, 64, 8200), (200, 64, 12345), (200, 64, 16384),
-                                   (100, 64, 30001)])
+                                   (100, 64, 30001), (100, 64, 32769), (40, 32, 65536)])
 def test_statistics_of_nearly_constant_rows(M, K, N):
     # Z is 8 with a spread of one bf16 step (1/16) and less: GELU(z) = z to fp32, sums of such values are exact, and squared
     # deviations of few distinct sizes make every rounding of a long chain go the same way.  The saved mean is the rounded
