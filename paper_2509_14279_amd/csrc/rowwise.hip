@@ -820,7 +820,7 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
 // workgroups.
 // Bound: HBM for bf16, the fp64 erfc for fp32 storage.  One workgroup per row that streams it three times took, whole
 // inference calls, us, that / now: fp32 17 x 42
-// x 24886 141 / 20, 256 x 34 x 44889 343 / 128; bf16 32 x 256 x 78860 236 / 43, 4096 x 256 x 65536 686 / 609; with the sums taken
+// x 24886 141 / 19, 256 x 34 x 44889 343 / 122; bf16 32 x 256 x 78860 236 / 34, 4096 x 256 x 65536 686 / 606; with the sums taken
 // in the contraction's epilogue as well as an earlier form did, which read each row once, 43, 153, 86 and 612.
 constexpr int kLongVectors = 2;
 template <class T> constexpr int64_t long_segment() { return 256 * (16 / (int)sizeof(T)) * kLongVectors; }
@@ -947,12 +947,22 @@ __global__ __launch_bounds__(256) void long_apply_kernel(int64_t M, int64_t N, i
   l.init(N, seg * long_segment<T>());
   float gm[kLongVectors][V], bt[kLongVectors][V];
 #pragma unroll
-  for (int s = 0; s < kLongVectors; s++)
+  for (int s = 0; s < kLongVectors; s++) {
+    if (l.nv[s] == V) {
 #pragma unroll
-    for (int v = 0; v < V; v++) {
-      gm[s][v] = v < l.nv[s] ? gamma[l.col[s] + v] : 0.0f;
-      bt[s][v] = v < l.nv[s] ? beta[l.col[s] + v] : 0.0f;
+      for (int v = 0; v < V; v += 4) {
+        const f32x4 g4 = *reinterpret_cast<const f32x4*>(gamma + l.col[s] + v), b4 = *reinterpret_cast<const f32x4*>(beta + l.col[s] + v);
+#pragma unroll
+        for (int e = 0; e < 4; e++) { gm[s][v + e] = g4[e]; bt[s][v + e] = b4[e]; }
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        gm[s][v] = v < l.nv[s] ? gamma[l.col[s] + v] : 0.0f;
+        bt[s][v] = v < l.nv[s] ? beta[l.col[s] + v] : 0.0f;
+      }
     }
+  }
   const double full = (double)long_segment<T>(), last = (double)(N - (segments - 1) * long_segment<T>());
   auto process = [&](int buf, int64_t row) {
     const int at = (int)(row - r0) & 15, half = (int)((row - r0) >> 4) & 1;
