@@ -31,9 +31,6 @@ bool shape_ok(int64_t M, int64_t K, int64_t N) {
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
-// Block tile of the generic kernel (as 16 x 16 blocks per wave tile side): 128 x 128 where that still gives every
-// compute unit a tile, else 64 x 64.
-int pick_generic_wb(int64_t I, int64_t J) { return (((I + 127) / 128) * ((J + 127) / 128) >= 256) ? 4 : 2; }
 // fp32 storage: all tiles as they are, where there is no scratch for the sums of split ones
 F64Split f64_unsplit(int64_t I, int64_t J) { return F64Split{((I + 63) / 64) * ((J + 63) / 64), 0, 1}; }
 
@@ -92,20 +89,22 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.dt = dt; q.M = M; q.K = K; q.N = N;
 
   // ---- which contraction kernels run
-  // bf16: the tuned kernel where N and K are multiples of the tile and the pipeline round (as they are), or - padded
-  // mode - on N and K rounded up to the tile, on zero-padded copies of the weights (and of X where its rows start at any
-  // element), leaving the surplus unstored.  Everything else takes the generic kernel.
-  q.pad = dt == kBF16 && fast_padded_supported(M, K, N);
-  q.stage_x = q.pad && fast_padded_stages_x(K);
-  const int64_t Np = q.pad ? fast_pad_dim(N) : N, Kp = q.pad ? fast_pad_dim(K) : K;
+  // bf16, forward: the kernel with the lowest estimated time.  The tiled one runs where N and K are multiples of the tile and
+  // the pipeline round (as they are), or - padded mode - on N and K rounded up to the tile, on zero-padded copies of the weights
+  // (and of X where its rows start at any element), leaving the surplus unstored.
+  const bool can_pad = dt == kBF16 && fast_padded_supported(M, K, N), can_tile = dt == kBF16 && fast_f1_supported(M, K, N);
+  const int64_t Np = can_pad ? fast_pad_dim(N) : N, Kp = can_pad ? fast_pad_dim(K) : K;
   const int64_t Mp = M > 0 ? M : 1;
 
   // ---- forward
-  q.f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
-  q.f1_fast = q.pad || (dt == kBF16 && fast_f1_supported(M, K, N));
-  q.f1_wb = pick_generic_wb(Mp, N);
+  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N) : Xwt::kGeneric;
+  const bool tiled = f1 == Xwt::kTiled || f1 == Xwt::kPadded;
+  q.f1_skinny = f1 == Xwt::kSkinny;
+  q.pad = f1 == Xwt::kPadded;
+  q.stage_x = q.pad && fast_padded_stages_x(K);
+  q.f1_fast = tiled;
+  q.f1_wb = generic_wb(Mp, N);
   size_t off = 0;
-  const bool tiled = q.f1_fast && !q.f1_skinny;
   q.off_rows = off; off += align256(f2_part_bytes(dt, Mp, N));
   q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K, q.stage_x != 0) : fast_f1_tail_bytes(M, K)));
   q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
@@ -122,8 +121,8 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   // The static entry point's limit is part of its contract (see the header) and does not move with the plan: the tiled
   // kernels' copies for whole 16-byte rows, and 8 bytes per (row, column tile) unless rows of whole vectors up to 8192 meet
   // the tiled kernel.
-  const bool copies = q.pad && N % 8 == 0 && K % 8 == 0 && K >= 128;
-  const bool limit_fast = copies || (!q.pad && q.f1_fast);
+  const bool copies = can_pad && N % 8 == 0 && K % 8 == 0 && K >= 128;
+  const bool limit_fast = copies || (!can_pad && can_tile);
   const int64_t limit_tile = limit_fast ? 128 : (dt == kF32 ? 32 : 16 * q.f1_wb);
   q.static_need = (limit_fast && N % 8 == 0 && N <= 8192 ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8)) +
                   align256(copies ? fast_padded_tail_bytes(K) : (limit_fast ? fast_f1_tail_bytes(M, K) : 0)) +
@@ -169,8 +168,8 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, siz
   const int64_t Np = q.pad ? fast_pad_dim(N) : N, Kp = q.pad ? fast_pad_dim(K) : K;
   q.ldz = Np;
   q.b3_fast = q.pad || (dt == kBF16 && fast_b3_supported(M, K, N));
-  q.b3_wb = pick_generic_wb(Mp, K);
-  q.b4_wb = pick_generic_wb(N, K);
+  q.b3_wb = generic_wb(Mp, K);
+  q.b4_wb = generic_wb(N, K);
   if (q.pad) {
     q.b4_fast_rows = fast_padded_b4_rows(M, K);
     q.b4_fast = q.b4_fast_rows >= 128;
@@ -313,7 +312,7 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
     } else {
       GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
       if (p.dt == kF32) launch_f64(0, g, p.f1_s64, b, nullptr, Zsave, ws + p.off_part, s);
-      else launch_generic_xwt(0, g, b, nullptr, Zsave, s);
+      else launch_generic_xwt(0, g, b, nullptr, Zsave, N, s);
     }
   }
   {
@@ -602,8 +601,8 @@ namespace {
 // contractions need, the masked upstream gradient G among it (the dZ of GradPlan).
 struct ReluPlan {
   int f1_skinny;           // few rows: the forward product (and its recomputation) on the kernel made for them
-  int f1_fast, f1_wb;
-  int pad;                 // padded mode of the fast contractions
+  int f1_fast, f1_wb;      // the tuned kernel, on the operands as they are
+  int pad;                 // or in padded mode (then the gradient contractions run in it too)
   int f1_wt;               // the forward product (and its recomputation) reads the weights from a transposed copy
   GradPlan g;
   F64Split f1_s64;         // fp32 storage
@@ -615,25 +614,25 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   if (!shape_ok(M, K, N)) return false;
   const size_t cs = dt == kF32 ? 8 : 4;
   const int64_t Mp = M > 0 ? M : 1;
-  // the tuned kernels where the shape fits their tiles and pipeline rounds, as it is or padded; else the generic kernel
-  q->pad = dt == kBF16 && fast_padded_supported(M, K, N);
-  q->f1_skinny = dt == kBF16 && skinny_supported(Mp, K, N);
-  q->f1_fast = dt == kBF16 && fast_f1_supported(M, K, N);
-  q->f1_wb = pick_generic_wb(Mp, N);
-  const bool tiled = !q->f1_skinny;
+  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N) : Xwt::kGeneric;
+  const bool tiled = f1 == Xwt::kTiled || f1 == Xwt::kPadded;
+  q->pad = f1 == Xwt::kPadded;
+  q->f1_skinny = f1 == Xwt::kSkinny;
+  q->f1_fast = f1 == Xwt::kTiled;
+  q->f1_wb = generic_wb(Mp, N);
   size_t off = 0;
   q->off_colpart = off; off += align256((size_t)colsum_groups(Mp) * N * cs);
   // (the masking epilogue of the tuned forward product can write blocks)
-  make_grad_plan(dt, M, K, N, /*may_block=*/tiled && q->f1_fast && fast_xwt_split(M, K, N) == 1, &off, &q->g);
+  make_grad_plan(dt, M, K, N, /*may_block=*/q->f1_fast && fast_xwt_split(M, K, N) == 1, &off, &q->g);
   // the padded copies of W and (where all of it is copied) X serve the forward product and the gradient contractions
   q->off_wpad = q->g.off_wpad;
   q->off_xtail = q->g.off_xpad;
   if (tiled && !q->g.stage_x) {
     q->off_xtail = off; off += align256(q->pad ? fast_padded_tail_bytes(K) : (q->f1_fast ? fast_f1_tail_bytes(M, K) : 0));
   }
-  q->off_bpad = off; off += align256(tiled && q->pad ? (size_t)fast_pad_dim(N) * 4 : 0);
-  q->f1_split = tiled && (q->pad || q->f1_fast) ? fast_xwt_split(M, K, N) : 1;
-  q->f1_wt = tiled && q->f1_fast && M >= kTransposeFromRows && q->f1_split == 1;
+  q->off_bpad = off; off += align256(q->pad ? (size_t)fast_pad_dim(N) * 4 : 0);
+  q->f1_split = tiled ? fast_xwt_split(M, K, N) : 1;
+  q->f1_wt = q->f1_fast && M >= kTransposeFromRows && q->f1_split == 1;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
   if (dt == kF32) q->f1_s64 = f64_plan(Mp, N, K);
   q->off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q->f1_s64) : fast_xwt_part_bytes(M, N, q->f1_split));
@@ -663,7 +662,7 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
   } else {
     GemmDesc g = {X, W, M, N, K, K, K, true, true, q.f1_wb};
     if (dt == kF32) launch_f64(kind, g, q.f1_s64, b, aux, out, ws + q.off_part, s);
-    else launch_generic_xwt(kind, g, b, aux, out, s);
+    else launch_generic_xwt(kind, g, b, aux, out, kind == 2 ? q.g.ldz : N, s);
   }
 }
 }  // namespace
@@ -688,7 +687,7 @@ extern "C" fdl_status fdl_linear_relu_forward(fdl_dtype dt, int64_t M, int64_t K
   clear_stale_error();
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* ws = static_cast<char*>(workspace);
-  if (q.pad && !q.f1_skinny) {
+  if (q.pad) {
     StageJobs j = {};
     stage_padded(&j, M, K, N, q.g.stage_x != 0, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
     launch_stage(j, s);
@@ -721,12 +720,12 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
   char* ws = static_cast<char*>(workspace);
   void* G = ws + q.g.off_dz;
   void* colpart = ws + q.off_colpart;
-  if (q.pad) {
-    // the copies serve the recomputation and both gradient contractions; X goes with the recomputation's where that is tiled
+  if (q.g.pad) {
+    // the copies serve the recomputation, where that is tiled, and both gradient contractions
     StageJobs j = {};
-    if (q.f1_skinny) {
+    if (!q.pad) {
       stage_padded(&j, M, K, N, true, q.g.stage_x ? X : nullptr, W, nullptr, ws + q.g.off_xpad, ws + q.g.off_wpad, nullptr);
-      // (that kernel writes columns up to N only: the surplus of G is cleared first, with the rows behind its last)
+      // (the other kernels write columns up to N only: the surplus of G is cleared first, with the rows behind its last)
       stage_matrix(&j, nullptr, 0, 0, 0, G, q.g.b4_fast_rows > M ? q.g.b4_fast_rows : M, q.g.ldz);
     } else {
       stage_padded(&j, M, K, N, q.g.stage_x != 0, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
@@ -797,7 +796,7 @@ struct FfnPlan {
   int gate_skinny, down_skinny;   // few rows: the kernel made for them
   int gate_fused;          // 1: one kernel forms both products and the gated activation (no M x H round trip)
   int gate_pad, down_pad;  // the same kernels on zero-padded copies of the weights (widths off their tiles)
-  int up_fast, down_fast, up_wb, down_wb;
+  int down_fast, up_wb, down_wb;
   int64_t ldg;             // pitch of G
   int down_wt;             // the down projection reads its weights from a transposed copy
   int gate_wt;             // the fused gate/up kernel reads both weight matrices from one interleaved transposed copy
@@ -812,27 +811,25 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   if (M * H > kMaxElems || M * D > kMaxElems || H * D > kMaxElems) return false;
   const size_t ts = dt == kF32 ? 4 : 2;
   const int64_t Mp = M > 0 ? M : 1;
-  q->gate_skinny = dt == kBF16 && skinny_gate_supported(Mp, D, H);
-  q->down_skinny = dt == kBF16 && skinny_supported(Mp, H, D);
   // off the tiles: padded copies, where the padding is not most of the work nor the launches most of the time
   const int64_t Hp = fast_gate_pad_h(H), Dq = fast_gate_pad_d(D), Dp = fast_pad_dim(D);
   const bool can_pad = dt == kBF16 && M >= 128 && M * D * H >= kStageFromWork && Hp * Dp <= 6 * H * D && (Hp / 128) * ((M + 255) / 256) <= (1 << 30);
-  q->gate_fused = dt == kBF16 && !q->gate_skinny && fast_gate_supported(M, D, H);
-  q->gate_pad = !q->gate_skinny && !q->gate_fused && can_pad;
+  const GatePlan g = dt == kBF16 ? pick_gate(Mp, D, H, can_pad) : GatePlan{Gate::kSeparate, Xwt::kGeneric};
+  q->gate_skinny = g.gate == Gate::kSkinny;
+  q->gate_fused = g.gate == Gate::kTiled;
+  q->gate_pad = g.gate == Gate::kPadded;
   q->ldg = q->gate_pad ? Hp : H;
-  // [M,D] x [H,D]^T for the separate gate and up products, [M,H] x [D,H]^T
-  q->up_fast = dt == kBF16 && !q->gate_skinny && !q->gate_pad && fast_f1_supported(M, D, H);
-  q->down_fast = dt == kBF16 && !q->gate_pad && !q->down_skinny && fast_f1_supported(M, H, D);
-  q->down_pad = !q->down_fast && can_pad && (q->gate_pad || (!q->down_skinny && H % 128 == 0));
-  if (q->down_pad) q->down_skinny = 0;
-  q->up_wb = pick_generic_wb(Mp, H);
-  q->down_wb = pick_generic_wb(Mp, D);
+  q->down_skinny = g.down == Xwt::kSkinny;
+  q->down_fast = g.down == Xwt::kTiled;
+  q->down_pad = g.down == Xwt::kPadded;
+  q->up_wb = generic_wb(Mp, H);
+  q->down_wb = generic_wb(Mp, D);
   size_t off = 0;
   const size_t mh = align256((size_t)((Mp + 255) / 256 * 256) * q->ldg * ts);
   q->off_g = off; off += mh;
   q->off_u = off; off += q->gate_fused || q->gate_skinny || q->gate_pad ? 0 : mh;    // the fused kernels never materialise the up product
   const size_t xpad = fast_padded_stages_x(D) ? (size_t)fast_padded_rows(Mp) * Dq * 2 : fast_padded_tail_bytes(D);
-  q->off_xtail = off; off += align256(q->gate_pad ? xpad : ((q->up_fast || q->gate_fused) ? fast_f1_tail_bytes(M, D) : 0));
+  q->off_xtail = off; off += align256(q->gate_pad ? xpad : (q->gate_fused ? fast_f1_tail_bytes(M, D) : 0));
   q->off_wgp = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wup = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wdp = off; off += align256(q->down_pad ? (size_t)Dp * Hp * 2 : 0);
@@ -895,16 +892,13 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     void* Wcat = q.gate_wt ? ws + q.off_wcat : nullptr;
     if (q.gate_wt) launch_fast_transpose_gate(H, D, Wg, Wu, Wcat, s);
     launch_fast_gate(M, D, H, X, Wg, Wu, Wcat, G, q.g_blocked != 0, ws + q.off_xtail, s);
-  } else if (q.up_fast) {
-    launch_fast_xwt(0, M, D, H, X, false, Wg, nullptr, nullptr, nullptr, G, false, ws + q.off_xtail, s);
-    launch_fast_xwt(0, M, D, H, X, false, Wu, nullptr, nullptr, nullptr, U, false, ws + q.off_xtail, s);
   } else {
     GemmDesc g = {X, Wg, M, H, D, D, D, true, true, q.up_wb};
     if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, G, ws + q.off_part, s);
-    else launch_generic_xwt(0, g, nullptr, nullptr, G, s);
+    else launch_generic_xwt(0, g, nullptr, nullptr, G, H, s);
     g.B = Wu;
     if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, U, ws + q.off_part, s);
-    else launch_generic_xwt(0, g, nullptr, nullptr, U, s);
+    else launch_generic_xwt(0, g, nullptr, nullptr, U, H, s);
   }
   if (!q.gate_fused && !q.gate_skinny && !q.gate_pad) launch_silu_mul((int)dt, M * H, G, U, G, s);
   if (q.down_pad) {
@@ -919,7 +913,7 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
   } else {
     GemmDesc g = {G, Wd, M, D, H, H, H, true, true, q.down_wb};
     if (dt == FDL_F32) launch_f64(0, g, q.down_s64, nullptr, nullptr, Y, ws + q.off_part, s);
-    else launch_generic_xwt(0, g, nullptr, nullptr, Y, s);
+    else launch_generic_xwt(0, g, nullptr, nullptr, Y, D, s);
   }
   return launch_status();
 }

@@ -32,6 +32,7 @@ struct GemmParams {
   const float* bias;
   const void* aux;       // [I][J] in the storage type (EPI_MASK)
   int64_t I, J, R, lda, ldb;
+  int64_t ldc;           // pitch of C (J, or more)
   int a_vec, b_vec;
   int wide;              // both contiguous extents hold at least one chunk of four: ragged rows take vector loads too
 };
@@ -282,9 +283,9 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmParams p) {
           const int64_t j = jw + b * 16 + M::col(lane, r);
           if (i < p.I && j < p.J) {
             const AccT z = acc[a][b][r] + bias[b][r];
-            if (EPI == EPI_MASK) C[i * p.J + j] = z > (AccT)0 ? aux[i * p.J + j] : (T)0.0f;
-            else if (EPI == EPI_RELU) C[i * p.J + j] = to_storage<T, AccT>(z > (AccT)0 ? z : (AccT)0);
-            else C[i * p.J + j] = to_storage<T, AccT>(z);
+            if (EPI == EPI_MASK) C[i * p.ldc + j] = z > (AccT)0 ? aux[i * p.J + j] : (T)0.0f;
+            else if (EPI == EPI_RELU) C[i * p.ldc + j] = to_storage<T, AccT>(z > (AccT)0 ? z : (AccT)0);
+            else C[i * p.ldc + j] = to_storage<T, AccT>(z);
           }
         }
       }
@@ -326,11 +327,31 @@ template <class T, int EPI> void dispatch(const GemmDesc& g, GemmParams p, hipSt
 GemmParams base_params(const GemmDesc& g) {
   GemmParams p;
   p.A = g.A; p.B = g.B; p.C = nullptr; p.bias = nullptr; p.aux = nullptr;
-  p.I = g.I; p.J = g.J; p.R = g.R; p.lda = g.lda; p.ldb = g.ldb; p.a_vec = 0; p.b_vec = 0; p.wide = 0;
+  p.I = g.I; p.J = g.J; p.R = g.R; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.J; p.a_vec = 0; p.b_vec = 0; p.wide = 0;
   return p;
 }
 
 }  // namespace
+
+// Block tile (as 16 x 16 blocks per wave tile side): 128 x 128 where that still gives every compute unit a tile, else 64 x 64.
+int generic_wb(int64_t I, int64_t J) { return (((I + 127) / 128) * ((J + 127) / 128) >= 256) ? 4 : 2; }
+
+// Estimated time of the forward product, us: slices of 16 at a price that grows with the workgroups a compute unit holds at
+// once (up to eight small tiles, two large ones, then one round after the other), more where rows start at any element, and
+// the output at 2 TB/s.  Within 0.84 - 1.24 of the measured time for 90 % of 2172 shapes (1 - 5000 rows, K to 8192, N to 262144).
+double generic_xwt_cost(int64_t M, int64_t K, int64_t N) {
+  const bool whole = K % 4 == 0;
+  const int64_t slices = (K + 15) / 16;
+  double slice;
+  if (generic_wb(M, N) == 4) {
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
+    slice = (whole ? 0.84 : 1.0) * (double)((tiles + 511) / 512);
+  } else {
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64), held = (tiles + 255) / 256;
+    slice = whole ? 0.21 + 0.11 * (double)held : 0.22 + 0.15 * (double)held;
+  }
+  return 4.5 + (double)slices * slice + (double)M * (double)N / 1e6;
+}
 
 // only the operand orientation of the dW contraction (both operands indexed by the reduction row) is needed
 void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s) {
@@ -342,10 +363,10 @@ void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s) {
 }
 
 // C[i][j] = f(sum_r A(i,r) B(j,r) + bias[j]), both operands reduction-contiguous (the forward product's orientation):
-// kind 0 plain (bias may be null), 1 max(., 0), 2 aux[i][j] where the sum is positive else 0
-void launch_generic_xwt(int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s) {
+// kind 0 plain (bias may be null), 1 max(., 0), 2 aux[i][j] where the sum is positive else 0; C has pitch ldc
+void launch_generic_xwt(int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, int64_t ldc, hipStream_t s) {
   GemmParams p = base_params(g);
-  p.C = C; p.bias = bias; p.aux = aux;
+  p.C = C; p.bias = bias; p.aux = aux; p.ldc = ldc;
   set_vec(&p, g, true, true, 2);
   const bool big = g.wb == 4;
 #define FDL_GX(T, EPI) do { if (big) launch_one<T, true, true, 4, EPI>(p, s); else launch_one<T, true, true, 2, EPI>(p, s); } while (0)

@@ -193,48 +193,94 @@ template <int MB, int NB, int EPI, int WAVES, int U> void launch_skinny(SkinnyPa
 // Tile and depth by the number of rows: the fewer there are, the more loads of W a wavefront can hold; from 33 rows on
 // two column blocks share each load of X, and from 65 four row blocks each load of W where that still gives every compute
 // unit a workgroup.
+struct SkinnyTile { int mb, nb; };
+SkinnyTile skinny_tile(int64_t M, int64_t N) {
+  if (M <= 16) return {1, 1};
+  if (M <= 32) return {2, 1};
+  return {((N + 31) / 32) * ((M + 63) / 64) >= 256 ? 4 : 2, 2};
+}
 template <int EPI> void dispatch_skinny(const SkinnyParams& p, hipStream_t s) {
-  if (p.M <= 16) { launch_skinny<1, 1, EPI, 8, 8>(p, s); return; }
-  if (p.M <= 32) { launch_skinny<2, 1, EPI, 8, 4>(p, s); return; }
+  const SkinnyTile t = skinny_tile(p.M, p.N);
+  if (t.mb == 1) { launch_skinny<1, 1, EPI, 8, 8>(p, s); return; }
+  if (t.nb == 1) { launch_skinny<2, 1, EPI, 8, 4>(p, s); return; }
   if constexpr (EPI == SK_GATE) {
     launch_skinny<4, 1, EPI, 8, 4>(p, s);
   } else {
-    const int64_t wide = (int64_t)((p.N + 31) / 32) * ((p.M + 63) / 64);
-    if (wide >= 256) launch_skinny<4, 2, EPI, 8, 4>(p, s);
+    if (t.mb == 4) launch_skinny<4, 2, EPI, 8, 4>(p, s);
     else launch_skinny<2, 2, EPI, 8, 4>(p, s);
   }
 }
 
 }  // namespace
 
-// Where this kernel is the faster one.  It rereads X for every 16 or 32 columns, so its time grows with the output: about
-// 10.5 us per 10^9 products for whole 16-byte rows (row blocks of 64), three times that for rows that start at any element.
-// The tiled kernel's time is its own estimate, and the padded copies' where they are needed.  Measured, us, this kernel / the
-// tiled one, K x N and rows: 4096 x 4096: 128 29 / 31, 256 48 / 35; 1024 x 1024: 512 11 / 24, 1536 24 / 25; 2048 x 2048: 512
-// 27 / 28, 768 38 / 31; 4096 x 1024: 384 33 / 34, 1536 72 / 41.  Where only the generic kernel is left (odd widths and little
-// work), up to 1.5 M outputs, or 0.5 M for odd rows (771 x 1537: 256 rows 17 / 24, 384 24.5 / 24.2).  Below 128 rows the
-// tiled kernel does not run, and the generic one is slower at every size (4096 x 4096, 64 rows: 20 / 88).  Its price holds
-// while X stays in the caches: whole inference calls with 64 columns, this kernel / the tiled one: 4096 x 1024 24 / 37,
-// 4096 x 4096 65 / 91, 16384 x 1024 about 58 / 44; odd rows against the generic one: 2048 x 771 x 33 22 / 31, 4096 rows 35 / 32.
+// Which kernel forms a forward product: the one with the lowest estimated time, the others charged 10 % (this one with rows
+// that start at any element 25 %) against the generic kernel, whose estimate is the steadier one.  This kernel rereads X for
+// every 16 or 32 columns, so its time grows with its workgroups: per 256 of them a start and a price per element of K, which
+// depends on the tile and on where rows start; above 4096 rows (2048 that start at any element) X no longer stays in the
+// caches and the estimate no longer holds.  The tiled kernel's time is its own estimate, and the padded copies' where they are
+// needed.  On 2247 shapes (1 - 5000 rows, K to 8192, N to 262144) the kernel picked takes 1.01 times the fastest one's time on
+// average, 1.06 at the 95th percentile.  Measured, us, this kernel / generic: 4096 x 4096: 16 rows 10 / 87, 64 rows 20 / 88;
+// 64 x 65536, 127 rows 36 / 16; 4097 x 65536: 31 rows 567 / 261, 127 rows 1169 / 293; this kernel / tiled: 4096 x 4096: 128 rows
+// 29 / 31, 256 rows 48 / 35; 4096 x 1024: 384 rows 33 / 34, 1536 rows 72 / 41.
 static int64_t skinny_rows(int64_t K) { return K % 8 == 0 ? 4096 : 2048; }
 static double skinny_cost(int64_t M, int64_t K, int64_t N) {
-  return 4.0 + (K % 8 == 0 ? 10.5e-9 : 34e-9) * (double)((M + 63) / 64 * 64) * (double)K * (double)N;
+  // start, per 256 workgroups, the same and 1000 elements of K, 1000 elements of K
+  static const double price[4][2][4] = {
+      {{2.6, 0.55, 1.2, 0.9}, {2.7, 0.70, 5.2, 2.0}},      // 1 x 1 blocks: rows of whole 16 bytes, any rows
+      {{2.8, 0.43, 1.9, 1.6}, {3.0, 0.49, 8.4, 1.5}},      // 2 x 1
+      {{3.5, 0.63, 1.0, 3.0}, {3.5, 0.43, 2.8, 9.7}},      // 2 x 2
+      {{2.7, 1.8, 4.6, 1.2}, {3.1, 1.9, 14.0, 1.5}}};      // 4 x 2
+  const SkinnyTile t = skinny_tile(M, N);
+  const double* p = price[t.mb == 1 ? 0 : (t.nb == 1 ? 1 : (t.mb == 2 ? 2 : 3))][K % 8 == 0 ? 0 : 1];
+  const double wgs = (double)((N + 16 * t.nb - 1) / (16 * t.nb)) * (double)((M + 16 * t.mb - 1) / (16 * t.mb)) / 256.0;
+  const double k = (double)K / 1000.0;
+  return p[0] + (double)M / 2000.0 + wgs * (p[1] + p[2] * k) + p[3] * k;
 }
-bool skinny_supported(int64_t M, int64_t K, int64_t N) {
-  if (M < 128) return true;
-  if (M > skinny_rows(K)) return false;
-  const bool pad = fast_padded_supported(M, K, N);
-  if (!pad && !fast_f1_supported(M, K, N)) return M * N <= (K % 8 == 0 ? 3 << 19 : 1 << 19);
-  return skinny_cost(M, K, N) < fast_xwt_cost(M, K, N, nullptr) + (pad ? 12.0 : 0.0);
+Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_pad, double* cost_out) {
+  Xwt best = Xwt::kGeneric;
+  double cost = generic_xwt_cost(M, K, N);
+  auto offer = [&](Xwt kernel, double c) { if (c < cost) { best = kernel; cost = c; } };
+  if (M <= skinny_rows(K)) offer(Xwt::kSkinny, skinny_cost(M, K, N) * (K % 8 == 0 ? 1.1 : 1.25));
+  if (fast_f1_supported(M, K, N)) {
+    offer(Xwt::kTiled, 1.1 * (fast_xwt_cost(M, K, N, nullptr) + 2.0));
+  } else if (may_pad && fast_padded_supported(M, K, N)) {
+    const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
+    const double copies = (double)(Np * Kp) * 2.0 + (fast_padded_stages_x(K) ? (double)(M * Kp) * 2.0 : 0.0);
+    offer(Xwt::kPadded, 1.1 * (10.0 + fast_xwt_cost(M, K, N, nullptr) + copies / 3e6));
+  }
+  if (cost_out != nullptr) *cost_out = cost;
+  return best;
 }
-// the gate and up products together: the tiled kernel has a tile of 128 columns and no split
-bool skinny_gate_supported(int64_t M, int64_t D, int64_t H) {
-  if (M < 128) return true;
-  if (M > skinny_rows(D)) return false;
-  const bool fits = fast_gate_supported(M, D, H);
-  if (!fits && M * D * H < kStageFromWork) return M * 2 * H <= (D % 8 == 0 ? 3 << 19 : 1 << 19);
+
+// How the feed-forward block's gate and up products run, with what follows from it for the down product: the lowest estimated
+// time of both.  The tiled gate kernel has a tile of 128 columns and no split; in padded mode it hands the activation on with a
+// padded pitch, which the down product then takes in padded mode too.  This kernel's gate variant: about 10.5 us per 10^9
+// products (row blocks of 64; the narrower ones count as 26 - 50 rows), three times that for rows that start at any element.
+// Measured, us, whole blocks: gate on this kernel / as two generic products: 16 x 4096 x 11008 74 / 478, 16 x 4097 x 11008 147 /
+// 280, 66 x 4097 x 65536 2963 / 2120.
+GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad) {
+  GatePlan best = {Gate::kSeparate, Xwt::kGeneric};
+  double down = 0.0;
+  best.down = pick_xwt(M, H, D, can_pad && H % 128 == 0, &down);
+  const double mh = (double)M * (double)H;
+  double cost = 2.0 * generic_xwt_cost(M, D, H) + 5.0 + mh * 6.0 / 4e6 + down;
+  auto offer = [&](Gate gate, double c) { if (c < cost) { best.gate = gate; cost = c; } };
+  const bool whole = D % 8 == 0;
+  const double rows = M <= 16 ? (whole ? 40.0 : 26.0) : (M <= 32 ? (whole ? 50.0 : 46.0) : (double)((M + 63) / 64 * 64));
+  if (M <= skinny_rows(D))
+    offer(Gate::kSkinny, 1.1 * (4.0 + (whole ? 10.5e-9 : 34e-9) * rows * (double)D * 2.0 * (double)H) + down);
   const int64_t tiles = ((H + 127) / 128) * ((M + 255) / 256);
-  return skinny_cost(M, D, 2 * H) < (double)((tiles + 255) / 256) * ((double)D / 64 * 1.1 + 8.0) + (fits ? 0.0 : 12.0);
+  const double tiled = (double)((tiles + 255) / 256) * ((double)D / 64 * 1.1 + 8.0);
+  if (fast_gate_supported(M, D, H)) {
+    offer(Gate::kTiled, 1.1 * tiled + down);
+  } else if (can_pad) {
+    const int64_t Hp = fast_gate_pad_h(H), Dq = fast_gate_pad_d(D);
+    const double copies = (double)(Hp * Dq) * 4.0 + (double)(Hp * fast_pad_dim(D)) * 2.0 +
+                          (fast_padded_stages_x(D) ? (double)(M * Dq) * 2.0 : 0.0);
+    const double padded = 1.1 * (10.0 + copies / 3e6 + tiled + fast_xwt_cost(M, Hp, D, nullptr));
+    if (padded < cost) { best.gate = Gate::kPadded; best.down = Xwt::kPadded; }
+  }
+  return best;
 }
 
 // out[m][n] = f(sum_k X[m][k] W[n][k] + bias[n]): kind 0 plain (bias may be null), 1 max(., 0), 2 aux[m][n] where positive

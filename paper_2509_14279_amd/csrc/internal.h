@@ -104,8 +104,10 @@ struct GemmDesc {
   bool a_rc, b_rc;
   int wb;
 };
+int generic_wb(int64_t I, int64_t J);        // GemmDesc::wb
 // forward-product orientation with an optional bias and a ReLU or ReLU-mask epilogue (sibling operators)
-void launch_generic_xwt(int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, hipStream_t s);
+void launch_generic_xwt(int kind, const GemmDesc& g, const float* bias, const void* aux, void* C, int64_t ldc, hipStream_t s);
+double generic_xwt_cost(int64_t M, int64_t K, int64_t N);
 // plain store: C [I][J]
 void launch_generic_store(const GemmDesc& g, void* C, hipStream_t s);
 // plain store of the fp32 accumulators: C [I][J] float (bf16 storage; a partial sum for launch_finish)
@@ -172,8 +174,13 @@ void launch_colsum_finish(int64_t M, int64_t N, const void* colpart, float* out,
 void launch_silu_mul(int dt, int64_t n, const void* G, const void* U, void* H, hipStream_t s);
 
 // ---- bf16 products with few rows (gemm_skinny.hip): any K and N -----------------------------------
-bool skinny_supported(int64_t M, int64_t K, int64_t N);
-bool skinny_gate_supported(int64_t M, int64_t D, int64_t H);
+// Which kernel forms the forward product [M,K] x [N,K]^T (see gemm_skinny.hip)
+enum class Xwt { kGeneric, kSkinny, kTiled, kPadded };
+Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_pad = true, double* cost = nullptr);
+// and the gate and up products of the feed-forward block, [M,D] x [H,D]^T twice, then its down product
+enum class Gate { kSeparate, kSkinny, kTiled, kPadded };
+struct GatePlan { Gate gate; Xwt down; };
+GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad);
 void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias,
                        const void* aux, void* out, int64_t ldo, hipStream_t s);
 void launch_skinny_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s);
