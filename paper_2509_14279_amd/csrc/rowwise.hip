@@ -1190,14 +1190,19 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   while (ch < 8 && ch * 512 < N) ch *= 2;
   while (ch * wpr * 512 < N) wpr *= 2;
   if (N == 8192 || N == 16384) { ch = 16; wpr /= 2; }
+  DeviceInfo di;
+  if (!device_info(&di)) return;
+  // A row that starts at any element, one of few: a wavefront's own work on it is the call's time, so it takes two vectors per
+  // lane where the wavefronts are there for it.  LayerNorm, us: 16 x 2071 8.8 -> 4.6, 512 x 3001 9.0 -> 4.7, 16 x 5003 8.8 -> 4.5;
+  // 2048 x 4097 and beyond are faster the other way.
+  const int spread = ch * wpr / 2;
+  if (N % 8 != 0 && spread >= 2 && spread <= 8 && M * spread <= (int64_t)di.cus * 32) { ch = 2; wpr = spread; }
   const int fit = N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
   const int nt = 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
   const int64_t per_wg = nt / 64 / wpr;
   int64_t wgs = (M + per_wg - 1) / per_wg;
-  DeviceInfo di;
-  if (!device_info(&di)) return;
-  const int64_t cap = (int64_t)di.cus * (wpr == 8 ? 2 : (16 / ch > wpr ? 16 / ch / wpr : 1));
+  const int64_t cap = (int64_t)di.cus * (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (16 / ch > wpr ? 16 / ch / wpr : 1));
   if (wgs > cap) wgs = cap;
 #define FDL_F2R(CHH, FIT, WPR)                                                                                        \
   launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
@@ -1212,6 +1217,12 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
     else if (wpr == 1) FDL_F2R(16, FIT_FULL, 1); else FDL_F2R(16, FIT_FULL, 2);
   } else if (fit == FIT_VECTORS) {
     FDL_F2R_FIT(FIT_VECTORS);
+  } else if (ch == 2 && wpr == 2) {
+    FDL_F2R(2, FIT_ANY, 2);
+  } else if (ch == 2 && wpr == 4) {
+    FDL_F2R(2, FIT_ANY, 4);
+  } else if (ch == 2 && wpr == 8) {
+    FDL_F2R(2, FIT_ANY, 8);
   } else {
     FDL_F2R_FIT(FIT_ANY);
   }
@@ -1241,12 +1252,18 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
                        (const T*)A, gamma, beta, (T*)Y, mean, rstd);                                                \
     return;                                                                                                         \
   } while (0)
-    if (vectors <= 64) FDL_ROW(64, 1);
-    if (vectors <= 256) FDL_ROW(256, 1);
-    if (vectors <= 512) FDL_ROW(256, 2);
-    if (vectors <= 1024) FDL_ROW(256, 4);
-    if (vectors <= 2048) FDL_ROW(512, 4);
-    if (N <= kRowsLimitF32) FDL_ROW(1024, 4);
+    // (stand-alone norms: three small trips through the caches beat workgroups that do not all fit, where there are more rows
+    // than compute units and few for each.  LayerNorm, us, this way / in registers: 824 x 4424 9.0 / 14.5, 363 x 8424 9.2 / 11.7,
+    // 2048 x 2680 11.1 / 12.7; 824 x 2048 6.3 / 4.9, 824 x 12000 23.9 / 22.4, 4096 x 4424 38.4 / 36.7, 128 x 5120 5.4 / 4.5)
+    const bool streamed = ACT != ACT_GELU && N > 2048 && N <= 10240 && M > 256 && M <= 2048;
+    if (!streamed) {
+      if (vectors <= 64) FDL_ROW(64, 1);
+      if (vectors <= 256) FDL_ROW(256, 1);
+      if (vectors <= 512) FDL_ROW(256, 2);
+      if (vectors <= 1024) FDL_ROW(256, 4);
+      if (vectors <= 2048) FDL_ROW(512, 4);
+      if (N <= kRowsLimitF32) FDL_ROW(1024, 4);
+    }
 #undef FDL_ROW
   } else if (N <= kRowsLimitBf16) {
     launch_rows_act<ACT>(M, N, eps, A, gamma, beta, Y, mean, rstd, s);

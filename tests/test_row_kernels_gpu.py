@@ -12,7 +12,7 @@ import harness as H
 
 pytestmark = pytest.mark.gpu
 
-BF16_WIDTHS = [7, 511, 1025, 4095, 8191, 8193, 8208, 16383, 16384, 16391, 32760, 32768, 32771]
+BF16_WIDTHS = [7, 511, 1025, 1727, 2049, 4095, 4097, 8191, 8193, 8208, 16383, 16384, 16391, 32760, 32768, 32771]
 F32_WIDTHS = [3, 257, 1023, 1026, 4097, 8192, 16383, 16388]
 WIDTHS = [("bf16", n) for n in BF16_WIDTHS] + [("f32", n) for n in F32_WIDTHS]
 
@@ -58,11 +58,12 @@ def test_forward_and_backward_of_the_block(dtype, M, N):
         H.check(dtype, k, H.to_f64(got[k]), ref[k])
 
 
-@pytest.mark.parametrize("N", [4104, 5003, 8200, 12345, 16384, 16392, 20001, 32768])
-def test_rows_do_not_depend_on_the_rows_beside_them(N):
+# (the last four: rows that start at any element, spread over more wavefronts while they are few)
+@pytest.mark.parametrize("N,M", [(4104, 5000), (8200, 5000), (12345, 5000), (16384, 5000), (16392, 5000), (20001, 5000),
+                                 (32768, 5000), (1500, 4000), (3001, 2000), (5003, 1000), (8191, 1000)])
+def test_rows_do_not_depend_on_the_rows_beside_them(N, M):
     # rows shared by two, four and eight wavefronts: a workgroup that walks several rows must give each the bits it has when
     # every workgroup holds one row (at most 256 rows: one trip)
-    M = 5000
     t = I.generate_norm("bf16", 256, N, seed=8200 + N)
     A = t["A"].to("cuda", torch.bfloat16)
     A = torch.cat([A.roll(k, 0) * (1.0 + k / 8) for k in range(20)])[:M].contiguous()
