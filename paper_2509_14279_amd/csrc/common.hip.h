@@ -260,7 +260,7 @@ template <> __device__ __forceinline__ double wave_sum<double>(double v) {
 }
 
 // v^-1/2 to the last bit of fp32 or nearly so: the hardware's estimate (about 2^-23) and one Newton step in fp64 (1e-13);
-// outside the estimate's range - variances that vanish, infinities - the library's square root.  v is wave-uniform.
+// outside the estimate's range - variances that vanish, infinities - the library's square root.
 __device__ __forceinline__ float inv_sqrt(double v) {
   const float x = (float)v;
   if (x > 1e-30f && x < 1e30f) {

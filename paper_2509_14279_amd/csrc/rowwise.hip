@@ -311,7 +311,7 @@ template <class C, int NW> __device__ __forceinline__ void wg_sum2(C& a, C& b, C
 // nv of V consecutive column sums of a thread to memory, 16 bytes at a time from an element-aligned address (one 4-byte
 // store per column and wavefront touches sixteen lines for 256 bytes: a workgroup's 3 N sums took longer than a row)
 template <class C, int V> __device__ __forceinline__ void store_columns(C* p, const C (&a)[V], int nv) {
-  constexpr int W = 16 / (int)sizeof(C);
+  constexpr int W = 16 / (int)sizeof(C) < V ? 16 / (int)sizeof(C) : V;
   typedef C vec_t __attribute__((ext_vector_type(W), aligned(sizeof(C))));
   if (nv == V) {
 #pragma unroll
@@ -330,16 +330,16 @@ template <class C, int V> __device__ __forceinline__ void store_columns(C* p, co
 
 // A row's vectors of 16 bytes.  ANY: rows start at any element and end inside a vector - the same 16-byte accesses from
 // element-aligned addresses (the hardware splits what straddles a line), the last, partial vector element by element.
-template <class T, bool ANY> struct RawVec;
+template <class T, bool ANY, int V = 16 / (int)sizeof(T)> struct RawVec;
 template <> struct RawVec<float, false> { typedef f32x4 type; };
 template <> struct RawVec<bf16_t, false> { typedef bf16x8 type; };
 template <> struct RawVec<float, true> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
 template <> struct RawVec<bf16_t, true> { typedef __bf16 type __attribute__((ext_vector_type(8), aligned(2))); };
+template <class T> struct RawVec<T, true, 1> { typedef T type __attribute__((ext_vector_type(1))); };
 
-template <class T, bool ANY>
-__device__ __forceinline__ typename RawVec<T, ANY>::type raw_load(const T* p, int nv) {
-  typedef typename RawVec<T, ANY>::type raw_t;
-  constexpr int V = 16 / (int)sizeof(T);
+template <class T, bool ANY, int V = 16 / (int)sizeof(T)>
+__device__ __forceinline__ typename RawVec<T, ANY, V>::type raw_load(const T* p, int nv) {
+  typedef typename RawVec<T, ANY, V>::type raw_t;
   if (!ANY || nv == V) return __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(p));
   raw_t r;
 #pragma unroll
@@ -370,10 +370,9 @@ template <class T, bool ANY> __device__ __forceinline__ void row_store(T* p, typ
 }
 // nv elements of the row, then zeros up to the end of the pitch (left: elements from here to there): the surplus columns
 // of a padded dZ enter the contractions that read it
-template <class T, bool ANY>
-__device__ __forceinline__ void raw_store(T* p, typename RawVec<T, ANY>::type o, int nv, int64_t left) {
-  typedef typename RawVec<T, ANY>::type raw_t;
-  constexpr int V = 16 / (int)sizeof(T);
+template <class T, bool ANY, int V = 16 / (int)sizeof(T)>
+__device__ __forceinline__ void raw_store(T* p, typename RawVec<T, ANY, V>::type o, int nv, int64_t left) {
+  typedef typename RawVec<T, ANY, V>::type raw_t;
   if (!ANY || left >= V) {
     __builtin_nontemporal_store(o, reinterpret_cast<raw_t*>(p));
   } else {
@@ -514,15 +513,16 @@ __global__ __launch_bounds__(256) void b1b_kernel(int64_t M, int64_t N, int64_t 
 // parks both rows' vectors in a per-wave LDS area and stores whole lines (lanes 8j .. 8j+3 the even row's piece j,
 // lanes 8j+4 .. 8j+7 the odd row's).  Half-line stores straight from the registers cost the phase a third of its
 // bandwidth (0.55 -> 0.73 ms on 65536 x 8192), halves merged in the L2 still a tenth.
-template <class T, int NT, bool ANY, bool BLK = false>
+// V: elements per thread; 1 for narrow rows that start at any element (see b1_fused_impl).
+template <class T, int NT, bool ANY, bool BLK = false, int V = 16 / (int)sizeof(T)>
 __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int64_t ldz, const T* __restrict__ dY,
                                                        const T* __restrict__ Z, const float* __restrict__ gamma,
                                                        const float* __restrict__ mean, const float* __restrict__ rstd,
                                                        T* __restrict__ dZ,
                                                        typename ComputeOf<T>::type* __restrict__ colpart) {
   typedef typename ComputeOf<T>::type C;
-  typedef typename RawVec<T, ANY>::type raw_t;
-  constexpr int V = 16 / (int)sizeof(T), D = 2;
+  typedef typename RawVec<T, ANY, V>::type raw_t;
+  constexpr int D = 2;
   static_assert(!BLK || (sizeof(T) == 2 && !ANY), "blocked output: bf16, whole vectors");
   __shared__ C red[2][NT / 64][2];
   __shared__ __attribute__((aligned(16))) raw_t park[BLK ? NT / 64 : 1][2][BLK ? 64 : 1];   // [wave][row of the pair][lane]
@@ -556,8 +556,8 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
       bmu[buf] = mean[r + zero];
       brs[buf] = rstd[r + zero];
       if (nv > 0) {
-        bdy[buf] = raw_load<T, ANY>(dY + r * N + col, nv);
-        bz[buf] = raw_load<T, ANY>(Z + r * N + col, nv);
+        bdy[buf] = raw_load<T, ANY, V>(dY + r * N + col, nv);
+        bz[buf] = raw_load<T, ANY, V>(Z + r * N + col, nv);
       }
     }
   };
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
         }
       }
     } else if (ANY ? left > 0 : nv > 0) {
-      raw_store<T, ANY>(dZ + row * ldz + col, o, nv, left);
+      raw_store<T, ANY, V>(dZ + row * ldz + col, o, nv, left);
     }
   };
   for (int64_t row = first; row < M; row += D * G) {
@@ -809,6 +809,65 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
         for (int v = 0; v < V; v++)
           if (v < nv[s]) y[col[s] + v] = o[v];
       }
+    }
+  }
+}
+
+// F2 for narrow rows (up to 16 K elements): sixteen lanes share a row, lane l holding its elements l, l + 16, ..., so that a
+// wavefront has four rows at once, whatever their alignment.  Bound: the latency of a row's chain of loads and sums (a wavefront
+// per row, or a workgroup of fp32 storage, has a few lanes' work in it): inference, us, 60000 x 24 x 15 fp32 69 -> 19, bf16
+// 20000 x 16 x 15 22.5 -> 7.5, 60000 x 99 x 127 67 -> 34.
+template <class T, int K>
+__global__ __launch_bounds__(256) void f2_narrow_kernel(int64_t M, int64_t N, float eps, const T* Z, const float* __restrict__ gamma,
+                                                        const float* __restrict__ beta, T* Y, float* __restrict__ mean,
+                                                        float* __restrict__ rstd) {
+  typedef typename ComputeOf<T>::type C;
+  ActTable<T, false, 256> tab;
+  tab.build();
+  const int l = threadIdx.x & 15;
+  float gm[K], bt[K];
+  int at[K];
+#pragma unroll
+  for (int k = 0; k < K; k++) {
+    at[k] = l + 16 * k < N ? l + 16 * k : (int)N - 1;              // past the end: the last element again, unused
+    gm[k] = gamma[at[k]];
+    bt[k] = beta[at[k]];
+  }
+  const double inv_n = 1.0 / (double)N;
+  const int64_t step = (int64_t)gridDim.x * 16;
+  T raw[K];
+  auto fetch = [&](int64_t row) {
+    const T* z = Z + (row < M ? row : M - 1) * N;
+#pragma unroll
+    for (int k = 0; k < K; k++) raw[k] = z[at[k]];
+  };
+  // (the lanes of a wavefront stay together: row16_sum; a row past the last is done like it and not stored)
+  int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  fetch(row);
+  for (int64_t lead = (int64_t)blockIdx.x * 16; lead < M; lead += step, row += step) {
+    C a[K], sum = 0, sq = 0;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      a[k] = l + 16 * k < N ? tab.gelu((C)to_f32<T>(raw[k])) : (C)0;
+      sum += a[k];
+    }
+    fetch(row + step);
+    const double mu = (double)row16_sum(sum) * inv_n;
+    const C m = (C)mu;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      a[k] = l + 16 * k < N ? a[k] - m : (C)0;
+      sq += a[k] * a[k];
+    }
+    const double var = (double)row16_sum(sq) * inv_n + (double)eps;
+    C rs;
+    if constexpr (sizeof(T) == 4) rs = 1.0 / sqrt(var);
+    else rs = inv_sqrt(var);
+    if (row < M) {
+      if (l == 0) { mean[row] = (float)mu; rstd[row] = (float)rs; }
+#pragma unroll
+      for (int k = 0; k < K; k++)
+        if (l + 16 * k < N) Y[row * N + l + 16 * k] = to_storage<T, C>(a[k] * rs * (C)gm[k] + (C)bt[k]);
     }
   }
 }
@@ -1158,6 +1217,12 @@ template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int gro
   if constexpr (sizeof(T) == 2) {
     if (blocked) { FDL_B1F_NT(false, true); return; }
   }
+  if (any && ldz <= 256) {
+    // narrow: an element per thread.  (A thread with eight holds the whole of a row of seven, one load after the other:
+    // 13288 x 7 bf16 42 us, so 17)
+    hipLaunchKernelGGL((b1_fused_kernel<T, 256, true, false, 1>), grid, dim3(256), 0, FDL_B1_ARGS);
+    return;
+  }
   if (any) FDL_B1F_NT(true, false);
   else FDL_B1F_NT(false, false);
 #undef FDL_B1F_NT
@@ -1243,6 +1308,16 @@ template <class T, int ACT>
 void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float* gamma, const float* beta, void* Y,
                      float* mean, float* rstd, void* part, hipStream_t s) {
   constexpr int V = 16 / (int)sizeof(T);
+  if constexpr (ACT == ACT_GELU) {
+    if (N <= (sizeof(T) == 4 ? 64 : 128)) {
+      const int64_t wgs = (M + 15) / 16;
+      const dim3 grid((unsigned)(wgs < 2048 ? wgs : 2048));
+#define FDL_NARROW(K) hipLaunchKernelGGL((f2_narrow_kernel<T, K>), grid, dim3(256), 0, s, M, N, eps, (const T*)A, gamma, beta, (T*)Y, mean, rstd)
+      if (N <= 16) FDL_NARROW(1); else if (N <= 32) FDL_NARROW(2); else if (N <= 64) FDL_NARROW(4); else FDL_NARROW(8);
+#undef FDL_NARROW
+      return;
+    }
+  }
   if constexpr (sizeof(T) == 4) {
     const int64_t vectors = (N + V - 1) / V;
 #define FDL_ROW(NT, S)                                                                                              \

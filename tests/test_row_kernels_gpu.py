@@ -46,6 +46,11 @@ def test_stand_alone_norms(dtype, N, M):
                                        # segments of 4096 (bf16) and 2048 (fp32) columns: a last one of one element, of part
                                        # of a wavefront, whole; rows that share a workgroup in odd and even numbers; one row
                                        ("bf16", 1, 36865), ("bf16", 700, 32769), ("bf16", 2300, 40960), ("bf16", 33, 37000),
+                                       # narrow rows: sixteen lanes each (to 128 and 64 columns), an element per thread in
+                                       # the backward pass (to 256, where they are ragged or padded)
+                                       ("bf16", 2600, 15), ("bf16", 33000, 17), ("bf16", 1037, 33), ("bf16", 37, 127),
+                                       ("bf16", 300, 128), ("bf16", 70, 129), ("bf16", 515, 255), ("f32", 2600, 17),
+                                       ("f32", 33000, 7), ("f32", 500, 64), ("f32", 70, 65), ("f32", 41, 255),
                                        ("f32", 1, 18433), ("f32", 600, 16385), ("f32", 1300, 18432), ("f32", 37, 20001)])
 def test_forward_and_backward_of_the_block(dtype, M, N):
     cfg = I.custom(dtype, M, 16, N, seed=8100 + M + N)
