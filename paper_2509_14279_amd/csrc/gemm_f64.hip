@@ -81,7 +81,15 @@ template <bool RC> struct Side {
     for (int e = 0; e < 4; e++) {
       const int64_t i = RC ? i0 + (tid >> 2) : i0 + (tid & 15) * 4 + e;
       const int64_t r = RC ? r0 + (tid & 3) * 4 + e : r0 + (tid >> 4);
-      v[e] = i < I && r < R ? base[RC ? i * ld + r : r * ld + i] : 0.0f;
+      // (unconditional, from the nearest element inside: a load under a condition waits for the one before it)
+      const int64_t ic = i < I ? i : I - 1, rc = r < R ? r : R - 1;
+      v[e] = base[RC ? ic * ld + rc : rc * ld + ic];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int64_t i = RC ? i0 + (tid >> 2) : i0 + (tid & 15) * 4 + e;
+      const int64_t r = RC ? r0 + (tid & 3) * 4 + e : r0 + (tid >> 4);
+      v[e] = i < I && r < R ? v[e] : 0.0f;
     }
     return v;
   }
