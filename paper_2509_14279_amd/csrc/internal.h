@@ -176,7 +176,7 @@ void launch_silu_mul(int dt, int64_t n, const void* G, const void* U, void* H, h
 // ---- bf16 products with few rows (gemm_skinny.hip): any K and N -----------------------------------
 // Which kernel forms the forward product [M,K] x [N,K]^T (see gemm_skinny.hip)
 enum class Xwt { kGeneric, kSkinny, kTiled, kPadded };
-Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_pad = true, double* cost = nullptr);
+Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_pad = true, bool x_padded = false, double* cost = nullptr);
 // and the gate and up products of the feed-forward block, [M,D] x [H,D]^T twice, then its down product
 enum class Gate { kSeparate, kSkinny, kTiled, kPadded };
 struct GatePlan { Gate gate; Xwt down; };
