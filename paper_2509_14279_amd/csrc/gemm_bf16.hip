@@ -882,7 +882,7 @@ void stage_matrix(StageJobs* j, const void* src, int64_t rows, int64_t cols, int
   if (rows_out <= 0) return;
   StageJob& q = j->job[j->count++];
   q.src = src; q.dst = dst; q.rows = rows; q.cols = cols; q.ld = ld; q.rows_out = rows_out; q.cols_out = cols_out;
-  const int64_t wanted = (rows_out * (cols_out / 8) + 1023) / 1024;      // four vectors per thread
+  const int64_t wanted = (rows_out * (cols_out / 8) + 255) / 256;        // a vector per thread, up to 2048 workgroups
   q.blocks = (int)(wanted < 1 ? 1 : (wanted > 2048 ? 2048 : wanted));
 }
 void stage_vector(StageJobs* j, const float* src, int64_t n, float* dst, int64_t n_out) {
