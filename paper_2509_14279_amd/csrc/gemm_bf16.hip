@@ -500,8 +500,10 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         typedef __attribute__((address_space(3))) float lds_float;
         const float xb = *(const lds_float*)(lds + kLdsStages + wave * 8192 + (a * 32 + l32) * 4);
         const float x = half == 0 ? xb : 0.0f;
-        const bf16_t hi = (bf16_t)x;
-        const float r1 = x - (float)hi;
+        // (an infinity has one piece; the largest finite numbers, which bf16 would round to one, take their leading bits)
+        const bool huge = __builtin_fabsf(x) >= 0x1.fep127f && __builtin_fabsf(x) < __builtin_inff();
+        const bf16_t hi = huge ? (bf16_t)__builtin_copysignf(0x1.fep127f, x) : (bf16_t)x;
+        const float r1 = __builtin_isinf(x) ? 0.0f : x - (float)hi;
         const bf16_t mid = (bf16_t)r1;
         const bf16_t lo = (bf16_t)(r1 - (float)mid);
 #pragma unroll
@@ -569,7 +571,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         }
         if (EPI == EPI_MASK) {
           // v: 8 pre-activations as bf16.  The upstream gradient passes where the pre-activation is positive (bits
-          // 0x0001 .. 0x7fff: sign clear, magnitude non-zero) and is zero elsewhere.
+          // 0x0001 .. 0x7f80: sign clear, magnitude non-zero, up to infinity) and is zero elsewhere, NaN included.
           const bf16_t* ap = p.aux + (int64_t)(j0 + wj * 128 + b * 32 + it * 4 + e_rq) * p.I + i0 + wi * 128 + e_m * 8;
           u32x4 d = {0u, 0u, 0u, 0u};
           if (!CRAG) {
@@ -584,8 +586,8 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
           u32x4 g;
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            const uint32_t lo = ((v[e] & 0xffffu) - 1u) < 0x7fffu ? 0x0000ffffu : 0u;
-            const uint32_t hi = ((v[e] >> 16) - 1u) < 0x7fffu ? 0xffff0000u : 0u;
+            const uint32_t lo = ((v[e] & 0xffffu) - 1u) < 0x7f80u ? 0x0000ffffu : 0u;
+            const uint32_t hi = ((v[e] >> 16) - 1u) < 0x7f80u ? 0xffff0000u : 0u;
             g[e] = d[e] & (lo | hi);
           }
           *dst = g;
