@@ -245,8 +245,8 @@ __device__ __forceinline__ TileCoord tile_coord(int L, int tiles_i, int tiles_j)
 // CRAG (with RAG): the number of output columns I is any number, and so is the pitch of the output's rows (stores go to
 // element-aligned addresses).  The host hands over a P operand that is readable up to the end of the last column tile (a
 // zero-padded copy of the weights, or a matrix whose surplus columns are the start of its next row) and a bias padded
-// likewise; the surplus columns are computed and not stored - EPI_MASK excepted, whose output, a buffer of the library
-// with whole tiles of columns, gets zeros there.
+// likewise; the surplus columns are computed and not stored - EPI_MASK and EPI_GATE excepted, whose output, a buffer of the
+// library with whole tiles of columns, gets zeros there.
 // A reduction length that is not a whole number of pipeline rounds is the host's business as well: it rounds the
 // length up and makes one operand zero over the surplus (the other only has to be readable and finite there).
 // The body of the kernel: the persistent tile loop of workgroup `bid` of `nblk` on reduction part `part`.  It is a
@@ -623,8 +623,14 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
 #pragma unroll
         for (int it = 0; it < 4; it++) {
           const int row = it * 8 + g_rq;
-          const u32x4 v = *(const lds_u32x4*)(wtile + row * 256 + ((g_m ^ (row & 15)) << 4));
+          u32x4 v = *(const lds_u32x4*)(wtile + row * 256 + ((g_m ^ (row & 15)) << 4));
           if (RAG && j0 + wj * 128 + b * 32 + row >= p.J) continue;   // a row past the end
+          if (CRAG && h0 + g_m * 8 + 8 > p.I) {
+            // the surplus columns of a padded width are zeros (their sums are too, but not where X holds an infinity)
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+              if (h0 + g_m * 8 + e >= p.I) v[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
+          }
           if (p.cblocked) {
             // blocked output (the down projection reads it best that way): row R of the matrix, columns col .. col + 7
             const int64_t R = j0 + wj * 128 + b * 32 + row;
@@ -1144,10 +1150,10 @@ void launch_fast_gate_padded(int64_t M, int64_t D, int64_t H, const void* X, con
   p.P = (const bf16_t*)Wgp; p.P2 = (const bf16_t*)Wup; p.ldp = Dp;
   p.Q = (const bf16_t*)(staged ? xw : X); p.ldq = staged ? Dp : D;
   p.Qtail = staged ? nullptr : (const bf16_t*)xw;
-  p.C = (bf16_t*)Hout;
-  p.I = (int)Hp; p.J = (int)M; p.tiles_i = (int)(Hp / 128); p.tiles_j = (int)((M + kTile - 1) / kTile);
+  p.C = (bf16_t*)Hout; p.ldc = Hp;
+  p.I = (int)H; p.J = (int)M; p.tiles_i = (int)(Hp / 128); p.tiles_j = (int)((M + kTile - 1) / kTile);
   p.nkt = (int)(Dp / kF1BK); p.split = 1;
-  launch<false, false, EPI_GATE, kF1BK, stages_of(kF1BK), true>(p, s);
+  launch<false, false, EPI_GATE, kF1BK, stages_of(kF1BK), true, true>(p, s);
 }
 // out [M][D] = G [..][Hp] Wdp^T with Wdp [D rounded up to the tile][Hp]; G has readable rows up to the next row tile
 void launch_fast_down_padded(int64_t M, int64_t D, int64_t Hp, const void* G, const void* Wdp, void* out, int split, void* part,

@@ -72,3 +72,22 @@ def test_a_nan_pre_activation_passes_no_gradient(M, K, N):
     for r in rows:
         assert torch.all(dX[r] == 0)
     assert torch.isfinite(dX.float()).all() and torch.isfinite(db).all()
+
+
+# gate and up products on padded copies (H % 128 != 0; D as it is, D through a copy of X), fused, on few rows, separate
+@pytest.mark.parametrize("M,D,H", [(4500, 384, 1100), (4097, 771, 1003), (4608, 256, 640), (16, 256, 264), (150, 100, 130)])
+def test_an_infinite_row_of_the_feed_forward_block(M, D, H):
+    print(f"[special] ffn {M}x{D}x{H}", flush=True)
+    t = I.generate_ffn("bf16", M, D, H, seed=9950 + M)
+    # all weights positive: an infinite element of X makes every sum of its row +infinity, gate, activation and output alike
+    d = {k: (v.abs() + 2.0 ** -10 if k != "X" else v).to("cuda", torch.bfloat16) for k, v in t.items()}
+    Y = torch.empty(M, D, device="cuda", dtype=torch.bfloat16)
+    ws = torch.empty(max(256, api.fdl_llama_ffn_workspace_bytes("bf16", M, D, H)), dtype=torch.uint8, device="cuda")
+    rows = [5, M - 1]
+    for r in rows:
+        d["X"][r, 1] = float("inf")
+    api.fdl_llama_ffn_forward("bf16", d["X"], d["Wg"], d["Wu"], d["Wd"], Y, ws)
+    torch.cuda.synchronize()
+    assert torch.all(Y[rows] == float("inf"))
+    rest = [r for r in range(M) if r not in rows]
+    assert torch.isfinite(Y[rest].float()).all()
