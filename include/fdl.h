@@ -24,8 +24,8 @@
  * The library allocates nothing and never synchronises: every call only
  * enqueues kernels on `hip_stream` (a hipStream_t passed as void*; NULL is the
  * default stream) and returns.  Scratch memory comes from the caller through
- * `workspace` (device memory, 256-byte aligned, at least
- * fdl_workspace_bytes(...) bytes, contents undefined before and after a call).
+ * `workspace` (device memory, 256-byte aligned, fdl_workspace_bytes(...) bytes,
+ * contents undefined before and after a call).
  * Outputs are overwritten, never accumulated into.  Input and output buffers
  * must not overlap.  Calls that share a workspace must be ordered on a stream.
  *
@@ -54,7 +54,7 @@ typedef enum {
   FDL_ERR_SHAPE = 2,      /* M, K or N < 1, or a product overflows the supported range */
   FDL_ERR_DTYPE = 3,      /* dt is not a member of fdl_dtype                      */
   FDL_ERR_EPS = 4,        /* eps is negative, NaN or infinite                     */
-  FDL_ERR_WORKSPACE = 5,  /* workspace is NULL or smaller than fdl_workspace_bytes */
+  FDL_ERR_WORKSPACE = 5,  /* workspace is NULL or too small (see fdl_workspace_bytes) */
   FDL_ERR_ALIGN = 6,      /* a base pointer is not 16-byte aligned (workspace: 256) */
   FDL_ERR_LAUNCH = 7      /* HIP reported an error when launching                 */
 } fdl_status;
@@ -71,6 +71,14 @@ FDL_API const char* fdl_status_string(fdl_status s);
  * Bytes of device scratch that fdl_forward and fdl_backward need for this
  * problem (the larger of the two, so one buffer serves both).  Returns 0 for
  * an invalid dtype or shape.  Host-only: touches no device.
+ * Part of it may be room for the partial sums of split reductions (at most
+ * 64 MB for the forward product and for each fp32 gradient), which some shapes
+ * want and larger batches do not: the size can fall as M grows.  A buffer that
+ * lacks only this part, say one sized for a larger batch, is accepted, and the
+ * call runs without splitting (slower, results equal to within the order of
+ * the sums); the forward passes of the block also run without the copies of
+ * operands that some shapes want.  A smaller one is rejected with
+ * FDL_ERR_WORKSPACE.  The same holds for the sizes of the other entry points.
  */
 FDL_API size_t fdl_workspace_bytes(fdl_dtype dt, int64_t M, int64_t K, int64_t N);
 
@@ -149,7 +157,7 @@ FDL_API fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * backward pass.  The pre-activation passes through Y itself and is normalised in place.  The workspace holds row
  * statistics and what the contraction needs: on the tuned bf16 kernels a transposed copy of W for batches of 16384 rows
  * and more (2 N K bytes), zero-padded copies of W and X where N or K is off the tile, and partial sums (at most 64 MB) where
- * few output tiles make it split its reduction; for fp32 storage the partial sums of the last, incomplete round of tiles;
+ * few output tiles make it split its reduction; for fp32 storage the partial sums of split tiles (at most 64 MB);
  * for rows above 32768 (bf16) or 16384 (fp32) elements 16 bytes per row and 4096 or 2048 columns:
  * fdl_forward_inference_workspace_bytes bytes (0 for an invalid dtype or shape), 256-byte aligned.
  * in : X [M,K], W [N,K] (dt);  b, gamma, beta [N] fp32;  eps >= 0.     out: Y [M,N] (dt).

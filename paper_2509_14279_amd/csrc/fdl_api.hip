@@ -80,11 +80,11 @@ bool ensure_dynamic_lds(const void* kernel, int bytes, OnceFlags* flags) {
   return true;
 }
 
-bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
+bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
   if (dt != kF32 && dt != kBF16) return false;
   if (!shape_ok(M, K, N)) return false;
-  const size_t ts = dt == kF32 ? 4 : 2;   // storage element
   const size_t cs = dt == kF32 ? 8 : 4;   // arithmetic element
+  const bool split = room == Room::kAll;
   Plan q = {};
   q.dt = dt; q.M = M; q.K = K; q.N = N;
 
@@ -97,7 +97,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   const int64_t Mp = M > 0 ? M : 1;
 
   // ---- forward
-  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N) : Xwt::kGeneric;
+  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N, room != Room::kNoCopies) : Xwt::kGeneric;
   const bool tiled = f1 == Xwt::kTiled || f1 == Xwt::kPadded;
   q.f1_skinny = f1 == Xwt::kSkinny;
   q.pad = f1 == Xwt::kPadded;
@@ -111,8 +111,8 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
   // Large batches on the tuned kernel (tile-aligned N and K): the weights are transposed first, 4 N K bytes of traffic
   // against about 6 % of the contraction's time; that pays from roughly 10^4 rows, with a margin for the extra launch.
-  if (dt == kF32) q.f1_s64 = f64_plan(Mp, N, K);
-  q.f1_split = tiled ? fast_xwt_split(M, K, N) : 1;
+  if (dt == kF32) q.f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
+  q.f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
   q.off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q.f1_s64) : fast_xwt_part_bytes(M, N, q.f1_split));
   q.fwd_bytes_plain = off;
   q.f1_wt = tiled && !q.pad && M >= kTransposeFromRows && q.f1_split == 1;
@@ -147,7 +147,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
   off = 0;
   q.off_c12 = off; off += align256(q.b1_fused ? 0 : (size_t)2 * Mp * cs);
   q.off_colpart = off; off += align256((size_t)q.b1_groups * 3 * N * cs);
-  make_grad_plan(dt, M, K, N, may_block, &off, &q.g);
+  make_grad_plan(dt, M, K, N, split, may_block, &off, &q.g);
   q.bwd_bytes = off;
   // (one buffer for both passes and for fdl_forward_inference, which keeps mean and rstd in it)
   const size_t fwd_all = q.fwd_bytes + 2 * align256((size_t)Mp * 4) + 256;
@@ -158,7 +158,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p) {
 
 // The two contractions that end a backward pass, dX [M,K] = dZ W and dW [N,K] = dZ^T X, with the workspace regions they
 // need behind *off.  may_block: the kernel that writes dZ can write it in 32 x 32 blocks.
-void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, size_t* off, GradPlan* p) {
+void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool split, bool may_block, size_t* off, GradPlan* p) {
   GradPlan q = {};
   const size_t ts = dt == kF32 ? 4 : 2;
   const int64_t Mp = M > 0 ? M : 1;
@@ -178,10 +178,11 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, siz
     q.b4_fast = dt == kBF16 && fast_b4_supported(M, K, N);
     q.b4_fast_rows = q.b4_fast ? fast_b4_rows(M) : 0;
   }
+  if (!split && q.b4_fast_rows < M) { q.b4_fast = 0; q.b4_fast_rows = 0; }   // (two partial sums: all of dW on the generic kernel)
   q.extra = q.b4_fast && q.b4_fast_rows < M ? 1 : 0;    // rows of dW's reduction left to the generic kernel: one more partial
   q.split_a = 1;
-  q.split_b = q.b4_fast ? fast_b4_split(q.b4_fast_rows, K, N) : 1;
-  q.pair = q.b3_fast && q.b4_fast && fast_pair_plan(M, K, N, q.b4_fast_rows, &q.split_a, &q.split_b);
+  q.split_b = q.b4_fast && split ? fast_b4_split(q.b4_fast_rows, K, N) : 1;
+  q.pair = split && q.b3_fast && q.b4_fast && fast_pair_plan(M, K, N, q.b4_fast_rows, &q.split_a, &q.split_b);
   q.blocked = may_block && dt == kBF16 && !q.pad && q.b3_fast && q.b4_fast && q.b4_fast_rows == M && M % 32 == 0 && N % 32 == 0;
   // dZ: the fast dX kernel reads whole 256-row tiles, so the buffer is rounded up (the surplus rows never reach an output)
   q.off_dz = *off; *off += align256((size_t)fast_padded_rows(Mp) * Np * ts);
@@ -192,8 +193,8 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, siz
   q.off_wpad = *off; *off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_xpad = *off; *off += align256(q.stage_x ? fast_padded_x_bytes(M, K, true) : 0);
   if (dt == kF32) {
-    q.s64_a = f64_plan(Mp, K, N);
-    q.s64_b = f64_plan(N, K, Mp);
+    q.s64_a = split ? f64_plan(Mp, K, N) : f64_unsplit(Mp, K);
+    q.s64_b = split ? f64_plan(N, K, Mp) : f64_unsplit(N, K);
     q.off_part64_a = *off; *off += align256(f64_part_bytes(q.s64_a));
     q.off_part64_b = *off; *off += align256(f64_part_bytes(q.s64_b));
   }
@@ -220,17 +221,28 @@ extern "C" const char* fdl_status_string(fdl_status s) {
 
 extern "C" size_t fdl_workspace_bytes(fdl_dtype dt, int64_t M, int64_t K, int64_t N) {
   Plan p;
-  if (!make_plan((int)dt, M, K, N, &p)) return 0;
+  if (!make_plan((int)dt, M, K, N, Room::kAll, &p)) return 0;
   return p.bytes;
+}
+
+// A workspace that lacks only the room for split reductions serves the call all the same, without them, and the block's forward
+// pass does without the operands' copies: needs fall with M where few rows make a reduction split or a larger batch runs on a
+// kernel without copies, and a caller that allocated for its largest batch must not fail on a smaller one.
+// make(room, plan) fills a plan (false: unsupported shape) with its need in plan->bytes.
+template <class P, class Make> static fdl_status fit_plan(const void* workspace, size_t have, P* plan, Make make) {
+  if (!make(Room::kAll, plan)) return FDL_ERR_SHAPE;
+  if (workspace == nullptr) return FDL_ERR_WORKSPACE;
+  for (Room room : {Room::kNoSplit, Room::kNoCopies})
+    if (have < plan->bytes) (void)make(room, plan);
+  if (have < plan->bytes) return FDL_ERR_WORKSPACE;
+  if (!aligned(workspace, 256)) return FDL_ERR_ALIGN;
+  return FDL_OK;
 }
 
 static fdl_status check_common(fdl_dtype dt, int64_t M, int64_t K, int64_t N, const void* workspace,
                                size_t workspace_bytes, Plan* p) {
   if (dt != FDL_F32 && dt != FDL_BF16) return FDL_ERR_DTYPE;
-  if (!make_plan((int)dt, M, K, N, p)) return FDL_ERR_SHAPE;
-  if (workspace == nullptr || workspace_bytes < p->bytes) return FDL_ERR_WORKSPACE;
-  if (!aligned(workspace, 256)) return FDL_ERR_ALIGN;
-  return FDL_OK;
+  return fit_plan(workspace, workspace_bytes, p, [&](Room room, Plan* q) { return make_plan((int)dt, M, K, N, room, q); });
 }
 
 // ---- optional per-phase event instrumentation
@@ -279,7 +291,7 @@ static fdl_status check_forward_args(fdl_dtype dt, int64_t M, int64_t K, int64_t
   if (!X || !W || !b || !gamma || !beta || !Y || !Zsave || !mean || !rstd) return FDL_ERR_NULL;
   if (dt != FDL_F32 && dt != FDL_BF16) return FDL_ERR_DTYPE;
   if (!(eps >= 0.0f) || std::isinf(eps)) return FDL_ERR_EPS;
-  if (!make_plan((int)dt, M, K, N, p)) return FDL_ERR_SHAPE;
+  if (!make_plan((int)dt, M, K, N, Room::kAll, p)) return FDL_ERR_SHAPE;
   return FDL_OK;
 }
 static bool forward_args_aligned(const void* X, const void* W, const float* b, const float* gamma, const float* beta,
@@ -558,8 +570,8 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
 // epilogue emits them, and the padded copy of X's last rows.
 namespace {
 struct InferencePlan { Plan p; size_t off_mean, off_rstd, bytes; };
-bool make_inference_plan(int dt, int64_t M, int64_t K, int64_t N, InferencePlan* q) {
-  if (!make_plan(dt, M, K, N, &q->p)) return false;
+bool make_inference_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, InferencePlan* q) {
+  if (!make_plan(dt, M, K, N, room, &q->p)) return false;
   const int64_t Mp = M > 0 ? M : 1;
   size_t off = q->p.fwd_bytes;
   q->off_mean = off; off += align256((size_t)Mp * 4);
@@ -571,7 +583,7 @@ bool make_inference_plan(int dt, int64_t M, int64_t K, int64_t N, InferencePlan*
 
 extern "C" size_t fdl_forward_inference_workspace_bytes(fdl_dtype dt, int64_t M, int64_t K, int64_t N) {
   InferencePlan q;
-  if (!make_inference_plan((int)dt, M, K, N, &q)) return 0;
+  if (!make_inference_plan((int)dt, M, K, N, Room::kAll, &q)) return 0;
   return q.bytes;
 }
 
@@ -582,9 +594,9 @@ extern "C" fdl_status fdl_forward_inference(fdl_dtype dt, int64_t M, int64_t K, 
   if (dt != FDL_F32 && dt != FDL_BF16) return FDL_ERR_DTYPE;
   if (!(eps >= 0.0f) || std::isinf(eps)) return FDL_ERR_EPS;
   InferencePlan q;
-  if (!make_inference_plan((int)dt, M, K, N, &q)) return FDL_ERR_SHAPE;
-  if (workspace == nullptr || workspace_bytes < q.bytes) return FDL_ERR_WORKSPACE;
-  if (!aligned(workspace, 256)) return FDL_ERR_ALIGN;
+  const fdl_status st = fit_plan(workspace, workspace_bytes, &q,
+                                 [&](Room room, InferencePlan* p) { return make_inference_plan((int)dt, M, K, N, room, p); });
+  if (st != FDL_OK) return st;
   if (!aligned(X, 16) || !aligned(W, 16) || !aligned(Y, 16) || !aligned(b, 16) || !aligned(gamma, 16) || !aligned(beta, 16))
     return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;
@@ -609,7 +621,8 @@ struct ReluPlan {
   int f1_split;            // bf16, tiled: parts of the forward product's reduction
   size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, off_part, bytes;
 };
-bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
+bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan* q) {
+  const bool split = room == Room::kAll;
   if (dt != kF32 && dt != kBF16) return false;
   if (!shape_ok(M, K, N)) return false;
   const size_t cs = dt == kF32 ? 8 : 4;
@@ -623,7 +636,8 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
   size_t off = 0;
   q->off_colpart = off; off += align256((size_t)colsum_groups(Mp) * N * cs);
   // (the masking epilogue of the tuned forward product can write blocks)
-  make_grad_plan(dt, M, K, N, /*may_block=*/q->f1_fast && fast_xwt_split(M, K, N) == 1, &off, &q->g);
+  q->f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
+  make_grad_plan(dt, M, K, N, split, /*may_block=*/q->f1_fast && q->f1_split == 1, &off, &q->g);
   // the padded copies of W and (where all of it is copied) X serve the forward product and the gradient contractions
   q->off_wpad = q->g.off_wpad;
   q->off_xtail = q->g.off_xpad;
@@ -631,18 +645,12 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, ReluPlan* q) {
     q->off_xtail = off; off += align256(q->pad ? fast_padded_tail_bytes(K) : (q->f1_fast ? fast_f1_tail_bytes(M, K) : 0));
   }
   q->off_bpad = off; off += align256(q->pad ? (size_t)fast_pad_dim(N) * 4 : 0);
-  q->f1_split = tiled ? fast_xwt_split(M, K, N) : 1;
   q->f1_wt = q->f1_fast && M >= kTransposeFromRows && q->f1_split == 1;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
-  if (dt == kF32) q->f1_s64 = f64_plan(Mp, N, K);
+  if (dt == kF32) q->f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
   q->off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q->f1_s64) : fast_xwt_part_bytes(M, N, q->f1_split));
   q->bytes = off;
   return true;
-}
-fdl_status check_ws(const void* workspace, size_t have, size_t need) {
-  if (workspace == nullptr || have < need) return FDL_ERR_WORKSPACE;
-  if (!aligned(workspace, 256)) return FDL_ERR_ALIGN;
-  return FDL_OK;
 }
 
 // out = f(X W^T + b): kind 1 the forward output, 2 the masked upstream gradient (out: the G buffer of the plan).  In padded
@@ -669,7 +677,7 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
 
 extern "C" size_t fdl_linear_relu_workspace_bytes(fdl_dtype dt, int64_t M, int64_t K, int64_t N) {
   ReluPlan q;
-  if (!make_relu_plan((int)dt, M, K, N, &q)) return 0;
+  if (!make_relu_plan((int)dt, M, K, N, Room::kAll, &q)) return 0;
   return q.bytes;
 }
 
@@ -679,8 +687,8 @@ extern "C" fdl_status fdl_linear_relu_forward(fdl_dtype dt, int64_t M, int64_t K
   if (!X || !W || !b || !Y) return FDL_ERR_NULL;
   if (dt != FDL_F32 && dt != FDL_BF16) return FDL_ERR_DTYPE;
   ReluPlan q;
-  if (!make_relu_plan((int)dt, M, K, N, &q)) return FDL_ERR_SHAPE;
-  const fdl_status st = check_ws(workspace, workspace_bytes, q.bytes);
+  const fdl_status st = fit_plan(workspace, workspace_bytes, &q,
+                                 [&](Room room, ReluPlan* p) { return make_relu_plan((int)dt, M, K, N, room, p); });
   if (st != FDL_OK) return st;
   if (!aligned(X, 16) || !aligned(W, 16) || !aligned(Y, 16) || !aligned(b, 16)) return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;
@@ -702,8 +710,8 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
   if (!dY || !X || !W || !b || !dX || !dW || !db) return FDL_ERR_NULL;
   if (dt != FDL_F32 && dt != FDL_BF16) return FDL_ERR_DTYPE;
   ReluPlan q;
-  if (!make_relu_plan((int)dt, M, K, N, &q)) return FDL_ERR_SHAPE;
-  const fdl_status st = check_ws(workspace, workspace_bytes, q.bytes);
+  const fdl_status st = fit_plan(workspace, workspace_bytes, &q,
+                                 [&](Room room, ReluPlan* p) { return make_relu_plan((int)dt, M, K, N, room, p); });
   if (st != FDL_OK) return st;
   if (!aligned(dY, 16) || !aligned(X, 16) || !aligned(W, 16) || !aligned(b, 16) || !aligned(dX, 16) || !aligned(dW, 16) ||
       !aligned(db, 16))
@@ -805,7 +813,8 @@ struct FfnPlan {
   int down_split;              // bf16, tiled: parts of the down projection's reduction
   size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, off_part, bytes;
 };
-bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
+bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* q) {
+  const bool split = room == Room::kAll;
   if (dt != kF32 && dt != kBF16) return false;
   if (M < 0 || D < 1 || H < 1 || M > kMaxDim || D > kMaxDim || H > kMaxDim) return false;
   if (M * H > kMaxElems || M * D > kMaxElems || H * D > kMaxElems) return false;
@@ -833,15 +842,15 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
   q->off_wgp = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wup = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wdp = off; off += align256(q->down_pad ? (size_t)Dp * Hp * 2 : 0);
-  q->down_split = q->down_pad || q->down_fast ? fast_xwt_split(M, q->down_pad ? Hp : H, D) : 1;
+  q->down_split = split && (q->down_pad || q->down_fast) ? fast_xwt_split(M, q->down_pad ? Hp : H, D) : 1;
   q->down_wt = q->down_fast && M >= kTransposeFromRows && q->down_split == 1;
   q->off_wt = off; off += align256(q->down_wt ? (size_t)D * H * 2 : 0);
   q->gate_wt = q->gate_fused && M >= kTransposeFromRows && H % 64 == 0 && D % 64 == 0;
   q->off_wcat = off; off += align256(q->gate_wt ? (size_t)2 * D * H * 2 : 0);
   q->g_blocked = q->gate_fused && q->down_wt && H % 32 == 0;
   if (dt == kF32) {
-    q->up_s64 = f64_plan(Mp, H, D);
-    q->down_s64 = f64_plan(Mp, D, H);
+    q->up_s64 = split ? f64_plan(Mp, H, D) : f64_unsplit(Mp, H);
+    q->down_s64 = split ? f64_plan(Mp, D, H) : f64_unsplit(Mp, D);
   }
   const size_t up64 = dt == kF32 ? f64_part_bytes(q->up_s64) : 0;
   const size_t down = dt == kF32 ? f64_part_bytes(q->down_s64) : fast_xwt_part_bytes(M, D, q->down_split);
@@ -853,7 +862,7 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, FfnPlan* q) {
 
 extern "C" size_t fdl_llama_ffn_workspace_bytes(fdl_dtype dt, int64_t M, int64_t D, int64_t H) {
   FfnPlan q;
-  if (!make_ffn_plan((int)dt, M, D, H, &q)) return 0;
+  if (!make_ffn_plan((int)dt, M, D, H, Room::kAll, &q)) return 0;
   return q.bytes;
 }
 
@@ -863,8 +872,8 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
   if (!X || !Wg || !Wu || !Wd || !Y) return FDL_ERR_NULL;
   if (dt != FDL_F32 && dt != FDL_BF16) return FDL_ERR_DTYPE;
   FfnPlan q;
-  if (!make_ffn_plan((int)dt, M, D, H, &q)) return FDL_ERR_SHAPE;
-  const fdl_status st = check_ws(workspace, workspace_bytes, q.bytes);
+  const fdl_status st = fit_plan(workspace, workspace_bytes, &q,
+                                 [&](Room room, FfnPlan* p) { return make_ffn_plan((int)dt, M, D, H, room, p); });
   if (st != FDL_OK) return st;
   if (!aligned(X, 16) || !aligned(Wg, 16) || !aligned(Wu, 16) || !aligned(Wd, 16) || !aligned(Y, 16)) return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;

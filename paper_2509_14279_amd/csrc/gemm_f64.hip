@@ -15,7 +15,7 @@
 // LDS double-buffered with one barrier per slice; four workgroups per compute unit cover each other's latencies.
 //
 // A compute unit's time is the number of tiles it is dealt.  Whole rounds of 256 tiles are done as they are; the tiles of an
-// incomplete last round (all tiles of a small output) are split over the reduction in the same launch, leave fp64 sums, and
+// incomplete last round (or all tiles, where that is estimated to be faster) are split over the reduction in the same launch, leave fp64 sums, and
 // a second kernel adds them in order (f64_plan).
 // Measured, us (floor at 77 TFLOP/s): 8192 x 1024 x 1024 251 - 260 (223) for each orientation; 64-wide tiles whose operands
 // were widened at every read, with bounds in the loop, took 314 - 325 for 4096 x 1024 x 2048 (now 256 - 281).
@@ -308,6 +308,7 @@ template <int EPI> void dispatch_f64(const GemmDesc& g, const F64Params& p, int 
 // or all of them.  Measured, us, without / with the split: 3001 x 771 x 1537 by reduction over 771 (1175 tiles) 143 / 133,
 // over 1537 (611) 166 / 140, over 3001 (325, all in 3 parts) 199 / 148; 256^3 (16 tiles, 8 parts) 14.5 / 11; 512^3 24.5 / 16;
 // 128 x 4096 x 1024 (32 tiles) 159 / 30.  The plan must not depend on the device: 256 compute units.
+constexpr int64_t kF64MaxUnits = 2048;      // parts of 32 KB each: at most 64 MB
 F64Split f64_plan(int64_t I, int64_t J, int64_t R) {
   const int64_t tiles = ((I + 63) / 64) * ((J + 63) / 64), slices = (R + 15) / 16;
   const int64_t full = tiles / 256, rest = tiles % 256;
@@ -316,7 +317,7 @@ F64Split f64_plan(int64_t I, int64_t J, int64_t R) {
   for (int split = 2; split <= 16 && split <= slices; split++)
     for (int all = 0; all < 2; all++) {
       const int64_t rounds = all ? 0 : full, parted = tiles - rounds * 256, units = parted * split;
-      if (units == 0 || units > 8192 || (all && full == 0)) continue;
+      if (units == 0 || units > kF64MaxUnits || (all && full == 0)) continue;
       const int64_t more = (units + 255) / 256, len = (slices + split - 1) / split;
       double cost = (double)(rounds * slices + more * len) * (rounds + more == 1 ? 0.68 : (rounds == 1 ? 0.58 : 0.52));
       if (rounds > 0 && cost < slices * 0.68) cost = slices * 0.68;

@@ -236,15 +236,15 @@ static double skinny_cost(int64_t M, int64_t K, int64_t N) {
   const double k = (double)K / 1000.0;
   return p[0] + (double)M / 2000.0 + wgs * (p[1] + p[2] * k) + p[3] * k;
 }
-Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_pad, bool x_padded, double* cost_out) {
+Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy, bool may_pad, bool x_padded, double* cost_out) {
   Xwt best = Xwt::kGeneric;
   double cost = generic_xwt_cost(M, K, N);
   auto offer = [&](Xwt kernel, double c) { if (c < cost) { best = kernel; cost = c; } };
   if (M <= skinny_rows(K)) offer(Xwt::kSkinny, skinny_cost(M, K, N) * (K % 8 == 0 ? 1.1 : 1.25));
-  if (fast_f1_supported(M, K, N)) {
+  if (fast_f1_supported(M, K, N) && (may_copy || M % 256 == 0)) {
     // (a partial last row tile takes a copy of X's last rows, unless X has readable rows behind them)
     offer(Xwt::kTiled, 1.05 * (fast_xwt_cost(M, K, N, nullptr) + (M % 256 != 0 && !x_padded ? 4.0 : 1.0)));
-  } else if (may_pad && fast_padded_supported(M, K, N)) {
+  } else if (may_copy && may_pad && fast_padded_supported(M, K, N)) {
     const int64_t Np = fast_pad_dim(N), Kp = fast_pad_dim(K);
     const double copies = (double)(Np * Kp) * 2.0 + (fast_padded_stages_x(K) ? (double)(M * Kp) * 2.0 : 0.0);
     offer(Xwt::kPadded, 1.05 * (10.0 + fast_xwt_cost(M, K, N, nullptr) + copies / 3e6));
@@ -262,7 +262,7 @@ Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_pad, bool x_padded, doubl
 GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad) {
   GatePlan best = {Gate::kSeparate, Xwt::kGeneric};
   double down = 0.0;
-  best.down = pick_xwt(M, H, D, can_pad && H % 128 == 0, /*x_padded=*/true, &down);
+  best.down = pick_xwt(M, H, D, true, can_pad && H % 128 == 0, /*x_padded=*/true, &down);
   const double mh = (double)M * (double)H;
   double cost = 2.0 * generic_xwt_cost(M, D, H) + 5.0 + mh * 6.0 / 4e6 + down;
   auto offer = [&](Gate gate, double c) { if (c < cost) { best.gate = gate; cost = c; } };

@@ -74,9 +74,13 @@ struct Plan {
   size_t bytes;           // max(fwd, bwd)
 };
 
-void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool may_block, size_t* off, GradPlan* p);
+// split = false: no reduction split, that is without the partial sums that are the optional part of the workspace.
+void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool split, bool may_block, size_t* off, GradPlan* p);
+// What a plan may use the workspace for: everything; no partial sums of split reductions; nor, in the block's forward pass,
+// copies of the operands (the kernels that need none then form its product).
+enum class Room { kAll, kNoSplit, kNoCopies };
 // Returns false when the shape or dtype is not supported.
-bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Plan* p);
+bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p);
 
 // ---- per-device facts and per-call failure notes --------------------------------------------------
 // Compute units and accelerator dies (each die has its own L2) of the calling thread's current device, queried from
@@ -176,7 +180,8 @@ void launch_silu_mul(int dt, int64_t n, const void* G, const void* U, void* H, h
 // ---- bf16 products with few rows (gemm_skinny.hip): any K and N -----------------------------------
 // Which kernel forms the forward product [M,K] x [N,K]^T (see gemm_skinny.hip)
 enum class Xwt { kGeneric, kSkinny, kTiled, kPadded };
-Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_pad = true, bool x_padded = false, double* cost = nullptr);
+// may_copy: into padded or partly copied operands; may_pad: into padded ones; x_padded: X has readable rows behind a partial tile
+Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy = true, bool may_pad = true, bool x_padded = false, double* cost = nullptr);
 // and the gate and up products of the feed-forward block, [M,D] x [H,D]^T twice, then its down product
 enum class Gate { kSeparate, kSkinny, kTiled, kPadded };
 struct GatePlan { Gate gate; Xwt down; };

@@ -178,3 +178,39 @@ def test_sibling_entry_points_reject_bad_arguments_before_any_launch():
     assert api.fdl_llama_ffn_forward_raw("f32", 4, 4, 4, P, P, P, P, P, P, 8, None) == api.FDL_ERR_WORKSPACE
     assert api.fdl_llama_ffn_forward_raw("f32", 4, 4, 4, P, P, P, P + 4, P, P, big, None) == api.FDL_ERR_ALIGN
     assert api.fdl_llama_ffn_forward_raw(-1, 4, 4, 4, P, P, P, P, P, P, big, None) == api.FDL_ERR_DTYPE
+
+
+def test_a_workspace_sized_for_a_large_batch_serves_smaller_ones():
+    """Few rows make a reduction split, whose partial sums need room that a large batch does not: a buffer sized for the
+    large one is accepted all the same.  (A misaligned matrix is found after the workspace has been accepted, and before any
+    device call.)"""
+    bad = P + 4
+
+    def calls(dt, M, K, N, nb):
+        return (api.fdl_forward_inference_raw(dt, M, K, N, bad, P, P, P, P, 1e-5, P, P, nb, None),
+                api.fdl_linear_relu_forward_raw(dt, M, K, N, bad, P, P, P, P, nb, None),
+                api.fdl_linear_relu_backward_raw(dt, M, K, N, bad, P, P, P, P, P, P, P, nb, None),
+                api.fdl_llama_ffn_forward_raw(dt, M, K, N, bad, P, P, P, P, P, nb, None),
+                _fwd(dt, M, K, N, ws_bytes=nb, X=bad), _bwd(dt, M, K, N, ws_bytes=nb, X=bad))
+
+    sizes = (api.fdl_forward_inference_workspace_bytes, api.fdl_linear_relu_workspace_bytes, api.fdl_linear_relu_workspace_bytes,
+             api.fdl_llama_ffn_workspace_bytes, api.fdl_workspace_bytes, api.fdl_workspace_bytes)
+    falls = 0
+    for dt, most, shapes in (("f32", 4096, [(4096, 4096), (1024, 1024), (771, 1537)]),
+                             ("bf16", 8192, [(4096, 4096), (2048, 2048), (1024, 4096)])):
+        for K, N in shapes:
+            for M in (16, 128, 256, 512, 1024, 2048, 4096):
+                for size, k in zip(sizes, range(6)):
+                    falls += size(dt, M, K, N) > size(dt, most, K, N)
+                    assert calls(dt, M, K, N, size(dt, most, K, N))[k] == api.FDL_ERR_ALIGN, (dt, M, K, N, k)
+                    # what holds no more than the outputs' own scratch is refused as ever
+                    assert calls(dt, M, K, N, 255)[k] == api.FDL_ERR_WORKSPACE, (dt, M, K, N, k)
+    assert falls > 20        # the sizes asked for do fall with M
+
+
+def test_partial_sums_stay_below_their_stated_limit():
+    for dt, M, K, N in (("f32", 1984, 65536, 1024), ("f32", 128, 16384, 16384), ("f32", 700, 8192, 700), ("bf16", 512, 8192, 8192),
+                        ("bf16", 1024, 4096, 4096), ("bf16", 300, 16384, 4000)):
+        have = api.fdl_forward_inference_workspace_bytes(dt, M, K, N)
+        copies = 0 if dt == "f32" or N % 256 == 0 else 2 * ((N + 255) // 256 * 256) * K + 2 * 257 * K
+        assert have <= copies + (64 << 20) + 16 * M + 4096 + 2 * 256 * K * (M % 256 != 0), (dt, M, K, N)
