@@ -1469,7 +1469,11 @@ int b1_fused_groups(int dt, int64_t M, int64_t N) {
 }
 
 // Rows per group of the two-kernel path: about 1024 workgroups, but at least 16 rows each (partial column sums as above;
-// bf16 4096 x 16384 with the column reduction: 16 rows 157 us, 32 146, 64 155; 1273 x 14080: 8 rows 44.9, 16 42.0, 32 48.2)
+// bf16 4096 x 16384 with the column reduction: 16 rows 157 us, 32 146, 64 155; 1273 x 14080: 8 rows 44.9, 16 42.0, 32 48.2).
+// For bf16 a group's sums are fp32 chains of that many rows, which meet in fp64: 65536 x 16384 has chains of 512, and dgamma, db
+// and dbeta are 4.3e-8, 4.0e-8 and 2.7e-8 from 64 bits there (relative 2-norm; rounding the result alone is 2.7e-8; chains of 64
+// with a polynomial for the CDF were at 5.4e-7, 9.1e-8 and 2.7e-8).  Chains of 16 folded into fp64 reach 2.8e-8, 2.7e-8 and 2.7e-8
+// and cost the whole step 1 - 2 %.
 int b1b_rows_per_group(int dt, int64_t M, int64_t N) {
   const int64_t width = 256 * (dt == kF32 ? 4 : 8), strips = (N + width - 1) / width;
   int64_t rpg = M * strips / 1024;
