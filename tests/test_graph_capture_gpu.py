@@ -36,7 +36,11 @@ def _step(cfg, b, stream):
 @pytest.mark.parametrize("dtype,shape", [("bf16", (2048, 1024, 2048)),    # paired dX + dW launch, finishing launch, blocked dZ
                                          ("bf16", (1000, 256, 768)),      # ragged batch: padded tail copy, generic dW tail
                                          ("bf16", (300, 200, 264)),       # padded mode: weight copies, zeroed dZ columns
-                                         ("f32", (130, 70, 200))])        # generic kernels, partial statistics
+                                         ("f32", (130, 70, 200)),         # fp64 kernels
+                                         # the forward product tiled, with a padded tail copy; on padded copies; its reduction
+                                         # split; fp32 with split tiles; rows dealt out in segments; narrow rows
+                                         ("bf16", (4700, 256, 768)), ("bf16", (4097, 771, 1100)), ("bf16", (512, 4096, 2048)),
+                                         ("f32", (256, 256, 256)), ("f32", (33, 64, 20000)), ("bf16", (3000, 64, 33))])
 def test_one_step_replays_from_a_graph(dtype, shape):
     M, K, N = shape
     cfg = I.custom(dtype, M, K, N, seed=900 + M)

@@ -15,6 +15,12 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(129, 1451, 1451), (700, 100, 4096), (3001, 771, 120), (1000, 515, 2049), (640, 1000, 4101), (2500, 1000, 300),
           (385, 1285, 770), (257, 4099, 264), (20000, 130, 126)]
+# The forward product of many of these is the few-row or the generic kernel's (only their gradients run padded); these are shapes
+# whose forward product is tiled, too: on padded copies, X as it is and copied; the reduction split, padded and on whole tiles
+# (ragged rows among them); not padded, a partial last row tile
+TILED = [(4097, 771, 1100), (4500, 384, 1100), (4300, 515, 2049), (4224, 1000, 1096), (500, 4096, 2000), (640, 2560, 4104),
+         (1030, 4099, 520), (512, 4096, 2048), (700, 2560, 4096), (4700, 256, 768)]
+SHAPES += TILED
 
 
 def nan_workspace(nbytes):
@@ -25,6 +31,21 @@ def nan_workspace(nbytes):
 
 def f64(t):
     return {k: v.numpy().astype(np.float64) for k, v in t.items()}
+
+
+def test_the_forward_products_meant_are_tiled():
+    # seen in the workspace of the forward pass: the other kernels need none of this
+    tile = lambda n: (n + 255) // 256 * 256
+    splits = 0
+    for M, K, N in TILED:
+        have = api.fdl_forward_inference_workspace_bytes("bf16", M, K, N)
+        copies = 0 if N % 256 == 0 and K % 256 == 0 else 2 * tile(N) * tile(K) + 2 * (tile(M) * tile(K) if K % 128 else 257 * K)
+        tail = 512 * K if not copies and M % 256 else 0
+        assert have >= copies + tail and copies + tail + M * N > 0, (M, K, N)
+        split = have - copies - tail > 8 * M * N
+        splits += split
+        assert copies or tail or split, (M, K, N)
+    assert splits == 5
 
 
 @pytest.mark.parametrize("M,K,N", SHAPES)
@@ -96,7 +117,31 @@ def test_feed_forward_block(M, D, Hd):
     H.check("bf16", "Y", H.to_f64(Y.view), S.llama_ffn_forward(n["X"], n["Wg"], n["Wu"], n["Wd"])["Y"])
 
 
-@pytest.mark.parametrize("M,K,N", [(300, 200, 264), (640, 1000, 1000), (400, 771, 1100), (256, 384, 520)])
+@pytest.mark.parametrize("M,K,N", TILED)
+def test_unrounded_fp32_biases(M, K, N):
+    # b is fp32 by contract also with bf16 matrices and enters the tiled products as three bf16 pieces: the stored
+    # pre-activation is the correctly rounded one, within half a bf16 unit in the last place and the fp32 accumulation's error
+    # (at most K terms: measured against 8 x 2^-24 of the sum of magnitudes, sixteen partial sums of matrix instructions)
+    cfg = I.custom("bf16", M, K, N, seed=9600 + M + K + N)
+    t = I.generate(cfg, with_dY=False)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(4141)
+    t["b"] = torch.randn(N, generator=g) * 0.1414 + 0.001
+    got = H.run_fdl(cfg, t, backward=False)
+    n = f64(t)
+    Z = n["X"] @ n["W"].T + n["b"]
+    ulp = 2.0 ** (np.floor(np.log2(np.maximum(np.abs(Z), 1e-30))) - 7)
+    mag = np.abs(n["X"]) @ np.abs(n["W"]).T + np.abs(n["b"])
+    tol = 0.5 * ulp * (1 + 1e-6) + 8 * 2.0 ** -24 * mag
+    assert np.all(np.abs(H.to_f64(got["Z"]) - Z) <= tol)
+    # the bound has teeth: a bias cut to its first piece leaves it
+    low = (n["X"] @ n["W"].T + t["b"].to(torch.bfloat16).float().numpy().astype(np.float64))
+    low = torch.from_numpy(low).float().to(torch.bfloat16).float().numpy().astype(np.float64)
+    assert (np.abs(low - Z) > tol).any()
+
+
+@pytest.mark.parametrize("M,K,N", [(300, 200, 264), (640, 1000, 1000), (400, 771, 1100), (256, 384, 520),
+                                   (4097, 771, 1100), (4224, 1000, 1096), (4300, 515, 2049), (640, 2560, 4104)])
 def test_an_infinity_stays_in_its_row(M, K, N):
     # rows of a product are independent: an infinite and a NaN element of X change their own rows of the outputs only
     cfg = I.custom("bf16", M, K, N, seed=9800 + M + K + N)

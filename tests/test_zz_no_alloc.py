@@ -81,3 +81,32 @@ def test_forward_static_rejects_what_the_array_cannot_hold():
     st = api.fdl_forward_static_raw("f32", M, K, N, z, z, z, z, z, 1e-5, z, z, z, z, None)
     assert st == api.FDL_ERR_WORKSPACE
     assert api.fdl_workspace_bytes("f32", M, K, N) > api.FDL_STATIC_SCRATCH_BYTES
+
+
+# Problems whose plan wants more than the array holds: the call runs without the optional part - the reduction not split; X read
+# as it is instead of through a copy; the generic kernel instead of one on padded copies; fp64 tiles unsplit.  Other kernels or
+# another order of the sums than fdl_forward's: compared to the parity bar of the storage type.
+@pytest.mark.parametrize("dtype,M,K,N", [("bf16", 1024, 4096, 4096), ("bf16", 20000, 1000, 512), ("bf16", 4097, 3001, 3001),
+                                         ("bf16", 1030, 4099, 520), ("f32", 1300, 2000, 1030)])
+def test_forward_static_without_the_optional_scratch(dtype, M, K, N):
+    c = I.custom(dtype, M, K, N, seed=57)
+    assert api.fdl_forward_inference_workspace_bytes(dtype, M, K, N) > api.FDL_STATIC_SCRATCH_BYTES + 16 * M
+    print(f"[no-alloc] static {c.name}", flush=True)
+    t = I.generate(c, with_dY=False)
+    got, ref = run_forward(c, t, static=True), run_forward(c, t, static=False)
+    for k in FWD_OUT:
+        g, r = got[k].double(), ref[k].double()
+        assert torch.isfinite(g).all(), k
+        tol = 2e-2 * r.abs().max() if dtype == "bf16" else 1e-5 + 1e-4 * r.abs()
+        assert torch.all((g - r).abs() <= tol), k
+
+
+# scratch that is not optional: the segments' sums of long rows
+@pytest.mark.parametrize("dtype,M,K,N", [("f32", 100, 64, 20000), ("bf16", 200, 64, 40000), ("bf16", 4700, 256, 768),
+                                         ("bf16", 4500, 384, 1100)])
+def test_forward_static_matches_forward_in_its_own_scratch(dtype, M, K, N):
+    c = I.custom(dtype, M, K, N, seed=58)
+    t = I.generate(c, with_dY=False)
+    got, ref = run_forward(c, t, static=True), run_forward(c, t, static=False)
+    for k in FWD_OUT:
+        assert torch.equal(got[k].view(torch.uint8), ref[k].view(torch.uint8)), k
