@@ -542,13 +542,13 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
     PhaseTimer t(FDL_PHASE_B2, s);
     if (!tail) launch_b2(N, p.b1_groups, colpart, dbeta, dgamma, db, s);
   }
-  if (p.g.pad) {
-    StageJobs j = {};
-    stage_grad(p.g, &j, X, W, ws);
-    launch_stage(j, s);
-  }
   {
     PhaseTimer t(FDL_PHASE_B3, s);
+    if (p.g.pad) {
+      StageJobs j = {};
+      stage_grad(p.g, &j, X, W, ws);
+      launch_stage(j, s);
+    }
     launch_grad_dx(p.g, dZ, W, X, dX, dW, ws, &tj, s);
   }
   {
@@ -566,8 +566,7 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
 
 // ---- forward for inference: nothing is saved for a backward pass ---------------------------------------------------
 // The pre-activation is written into Y and normalised there (the normalisation reads an element before it writes it),
-// so no M x N scratch is needed: the workspace holds the row statistics, the partial statistics where the GEMM
-// epilogue emits them, and the padded copy of X's last rows.
+// so no M x N scratch is needed: the workspace holds the row statistics and what the forward pass needs.
 namespace {
 struct InferencePlan { Plan p; size_t off_mean, off_rstd, bytes; };
 bool make_inference_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, InferencePlan* q) {

@@ -1,5 +1,5 @@
-// Streaming (HBM-bound) phases of the fused dense-layer block: row statistics and normalisation (forward), the LayerNorm/GELU gradient row pass with its column partial sums
-// (backward), and the column reduction that finishes dbeta, dgamma, db.
+// Streaming (HBM-bound) phases of the fused dense-layer block: row statistics and normalisation (forward), the LayerNorm/GELU
+// gradient row pass with its column partial sums (backward), and the column reduction that finishes dbeta, dgamma, db.
 //
 // Row reductions follow the idiom of the paper's row-normalisation kernels (appendix "Highlighted CUDA
 // Kernels", LayerNorm forward and Llama RMSNorm forward: vector loads, wavefront shuffles, a small LDS
@@ -29,7 +29,8 @@ __device__ __forceinline__ double read_lane(double v, int l) {
 // ------------------------------------------------------------------------------------------------
 // F2 with its own statistics, narrow rows (bf16 storage, N <= 512 CH): a wavefront owns a row and keeps it in
 // registers over three sweeps (GELU and sum; deviations and their squares; scale, shift, store), so Zsave is read
-// once, no partial statistics pass through memory and no barrier separates the sweeps.  Lane l holds the 8-element
+// once, no partial statistics pass through memory and, where a wavefront has its row to itself, no barrier separates the
+// sweeps.  Lane l holds the 8-element
 // vectors c*64 + l, c < CH, of its row (every load and store of a wavefront covers 1 KB of one row); the next
 // row's vectors are fetched while the current row is processed.  gamma and beta sit in LDS, permuted so that a
 // lane's four 16-byte reads per vector are lane-contiguous.  Workgroups of NT/64 wavefronts walk the rows with
@@ -878,9 +879,9 @@ __global__ __launch_bounds__(256) void f2_narrow_kernel(int64_t M, int64_t N, fl
 // chip: a workgroup takes rows_per_wg rows of one segment (gamma and beta stay in its registers), as many as leave about 2048
 // workgroups.
 // Bound: HBM for bf16, the fp64 erfc for fp32 storage.  One workgroup per row that streams it three times took, whole
-// inference calls, us, that / now: fp32 17 x 42
-// x 24886 141 / 19, 256 x 34 x 44889 343 / 122; bf16 32 x 256 x 78860 236 / 34, 4096 x 256 x 65536 686 / 606; with the sums taken
-// in the contraction's epilogue as well as an earlier form did, which read each row once, 43, 153, 86 and 612.
+// inference calls, us, that / now: fp32 17 x 42 x 24886 141 / 19, 256 x 34 x 44889 343 / 122; bf16 32 x 256 x 78860 236 / 34,
+// 4096 x 256 x 65536 686 / 606; an earlier form with the sums in the contraction's epilogue, which read each row once, 43, 153, 86
+// and 612.
 constexpr int kLongVectors = 2;
 template <class T> constexpr int64_t long_segment() { return 256 * (16 / (int)sizeof(T)) * kLongVectors; }
 

@@ -102,9 +102,9 @@ def test_forward_static_rejects_bad_arguments_and_oversized_problems_before_any_
     assert _fwd_static(eps=float("nan")) == api.FDL_ERR_EPS
     assert _fwd_static(X=P + 4) == api.FDL_ERR_ALIGN
     assert _fwd_static(M=0) == api.FDL_OK
-    # partial row statistics of 8 bytes per (row, 64-column tile): 65536 rows x 128 tiles = 64 MiB > the 16 MiB array
+    # 8 bytes count per (row, 32-column tile): 65536 rows x 256 tiles = 128 MiB > the 16 MiB array
     assert _fwd_static(dt="f32", M=65536, K=64, N=8192) == api.FDL_ERR_WORKSPACE
-    # the headline shape normalises without partials and needs no scratch at all: accepted up to the launch, which
+    # the headline shape counts for nothing: accepted up to the launch, which
     # this host-only test must not reach, so only its size is checked here
     assert api.FDL_STATIC_SCRATCH_BYTES == 16 * 1024 * 1024
 

@@ -1,4 +1,4 @@
-"""The bf16 kernel for few rows at the edges of its tiles (16 rows, 16 or 32 columns, steps of 32): one row to a few row
+"""The bf16 kernel for few rows, and what is picked beside it, at the edges of its tiles (16 rows, 16 or 32 columns, steps of 32): one row to a few row
 blocks, reductions shorter than a step and ending inside one, widths that end inside a group of four columns; every
 epilogue.  Bars as in the other parity tests, against the fp64 oracles; guard bytes around every output."""
 import numpy as np

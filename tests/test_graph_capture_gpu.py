@@ -34,8 +34,8 @@ def _step(cfg, b, stream):
 
 
 @pytest.mark.parametrize("dtype,shape", [("bf16", (2048, 1024, 2048)),    # paired dX + dW launch, finishing launch, blocked dZ
-                                         ("bf16", (1000, 256, 768)),      # ragged batch: padded tail copy, generic dW tail
-                                         ("bf16", (300, 200, 264)),       # padded mode: weight copies, zeroed dZ columns
+                                         ("bf16", (1000, 256, 768)),      # few rows forward, generic dW tail
+                                         ("bf16", (300, 200, 264)),       # few rows; gradients padded: zeroed dZ columns
                                          ("f32", (130, 70, 200)),         # fp64 kernels
                                          # the forward product tiled, with a padded tail copy; on padded copies; its reduction
                                          # split; fp32 with split tiles; rows dealt out in segments; narrow rows

@@ -101,27 +101,28 @@ def test_small_and_ragged_shapes(dtype, shape):
     ("f32", (384, 128, 1024)), ("f32", (100, 64, 4100)),      # f32 rows longer than the fused row kernel holds
     ("bf16", (24, 16, 8200)), ("bf16", (16, 8, 2051)),        # bf16 rows beyond the fused kernel (aligned / unaligned)
     ("f32", (8, 8, 2051)),
-    # bf16 fast path, row lengths on both sides of what the wavefront-per-row normalisation holds (8192) and of its
-    # vector counts (exact fits 2048 / 8192; masked tails 4352 / 7936; 8448 takes the in-GEMM statistics instead)
+    # bf16, row lengths on both sides of what one wavefront of the normalisation holds (8192) and of its vector counts
+    # (exact fits 2048 / 8192; masked tails 4352 / 7936; 8448: four wavefronts).  The kernel that forms the product is the
+    # cheapest by estimate: at these sizes the tiled one from about 4096 rows or with long rows (the shapes that reach it in
+    # every mode are tests/test_padded_shapes_gpu.py's TILED), else mostly the one for few rows
     ("bf16", (256, 128, 2048)), ("bf16", (512, 128, 8192)), ("bf16", (256, 128, 4352)), ("bf16", (256, 128, 7936)),
     ("bf16", (256, 128, 8448)),
-    # ragged batch dimension on the bf16 fast path: partial last row tile in F1 and dX, dW = fast kernel over the first
-    # rows + generic kernel over the rest (1000 = 896 + 104; 130 = 128 + 2; 300 = 256 + 44), statistics in the GEMM
-    # epilogue for the long rows
+    # ragged batch dimension on whole tiles of columns: partial last row tile in dX, dW = fast kernel over the first
+    # rows + generic kernel over the rest (1000 = 896 + 104; 130 = 128 + 2; 300 = 256 + 44)
     ("bf16", (300, 256, 512)), ("bf16", (1000, 256, 768)), ("bf16", (130, 256, 256)), ("bf16", (385, 512, 1024)),
     ("bf16", (129, 256, 8448)), ("bf16", (2500, 256, 2048)),
-    # K below 128 or not a multiple of 8: the generic GEMM
+    # K below 128 or not a multiple of 8: the generic GEMM for the gradients
     ("bf16", (256, 64, 512)), ("bf16", (320, 100, 256)),
     # padded mode of the tuned kernels: N and K multiples of 8 but not both of 256 - surplus output columns and rows
-    # unstored, weights copied zero-padded, dZ with a padded pitch; with a ragged M on top; with rows longer than the
-    # row-resident normalisation (statistics from the GEMM epilogue, masked at the ragged edge: 8200, 8456); with so
+    # unstored, weights copied zero-padded, dZ with a padded pitch (the gradients; the forward product where that is the
+    # cheapest); with a ragged M on top; with rows shared by four wavefronts that end inside them (8200, 8456); with so
     # few rows that dW falls to the generic kernel on the padded dZ (128, 200); N far below one tile (8, 64)
     ("bf16", (320, 192, 256)), ("bf16", (512, 136, 520)), ("bf16", (2500, 1000, 3000)), ("bf16", (300, 200, 264)),
     ("bf16", (129, 136, 256)), ("bf16", (128, 128, 264)), ("bf16", (200, 248, 2056)), ("bf16", (256, 384, 8200)),
     ("bf16", (385, 256, 8456)), ("bf16", (1024, 1000, 8)), ("bf16", (2048, 1024, 64)), ("bf16", (640, 128, 1000)),
     ("bf16", (4096, 520, 768)), ("bf16", (1500, 768, 776)),
     # batches from 16384 rows on the tuned kernel: the forward contraction reads the weights from a transposed copy
-    # (whole row tiles; a partial last one; rows longer than 8192: statistics in that kernel's epilogue)
+    # (whole row tiles; a partial last one; rows longer than 8192)
     ("bf16", (16384, 128, 256)), ("bf16", (32805, 256, 512)), ("bf16", (16384, 128, 8448)),
     # dZ in 32 x 32 blocks (fused row kernel + tuned dX and dW over all rows; with rows of 1024 threads only from
     # K = 1024): whole and partial wavefronts at the end of a row, split dW, paired dX + dW launch
@@ -135,7 +136,7 @@ def test_aligned_and_long_row_shapes(dtype, shape):
 def test_bf16_with_unrounded_fp32_vectors():
     """b, gamma, beta are fp32 by contract also with bf16 matrices.  The seeded configurations round them to bf16
     values; here they keep all 24 bits, so the lower pieces of the bias (which enters the forward contraction as
-    three bf16 pieces through the matrix pipe) matter.  The stored pre-activation must be the correctly rounded one:
+    three bf16 pieces through the matrix pipe where the product is tiled: test_padded_shapes_gpu.py) matter.  The stored pre-activation must be the correctly rounded one:
     within half a bf16 unit in the last place of the exact value, plus the fp32 accumulation error of the sum."""
     cfg = I.custom("bf16", 512, 256, 768, seed=41)
     t = I.generate(cfg)
@@ -175,7 +176,7 @@ def test_constant_rows_and_zero_weight(dtype):
 
 
 def test_constant_rows_fast_path():
-    """Same degenerate case at a shape the bf16 MFMA fast path and the wavefront-per-row normalisation take."""
+    """Same degenerate case at whole tiles, with the wavefront-per-row normalisation and the tuned gradient kernels."""
     cfg = I.custom("bf16", 256, 128, 1024, seed=9)
     t = I.generate(cfg)
     t["W"].zero_()

@@ -3,10 +3,10 @@ against fdl_forward on the same inputs: same kernels on a different scratch addr
 for bit (stricter than the parity bars, which the fdl_forward side is held to against the oracle elsewhere) - except
 where the array is too small for the transposed weights that fdl_forward uses for large batches (own test below).
 
-Two calls in a row on one GPU, the second with a smaller input, through shapes whose forward pass really uses the
-scratch: partial row statistics from the GEMM epilogue (rows longer than the row-resident normalisation holds, and the
-generic kernel), and the padded copy of X's last rows (ragged M on the bf16 fast path).  This file is collected
-last, so that a failure here cannot hide the other tests."""
+Two calls in a row on one GPU, the second with a smaller input, through shapes whose forward pass uses the scratch: the
+padded copy of X's last rows (ragged M on the tiled kernel), transposed weights; further down padded copies, segments of long
+rows, and what runs where the array has no room for the optional part.  This file is collected last, so that a failure here
+cannot hide the other tests."""
 import sys
 
 import pytest
@@ -39,10 +39,10 @@ def run_forward(cfg, t, static: bool):
 
 def test_forward_static_matches_forward_on_two_calls_in_a_row():
     # first the larger problem, then smaller ones that reuse (part of) the same scratch bytes
-    cases = [I.custom("bf16", 385, 512, 8448, seed=51),     # fast path, ragged M (padded X tail) + epilogue partials
-             I.custom("f32", 130, 70, 200, seed=52),        # generic kernel partials, smaller
-             I.custom("bf16", 300, 256, 512, seed=53),      # fast path, ragged M, row-resident normalisation
-             I.custom("bf16", 200, 136, 264, seed=54),      # padded mode: zero-padded weight copy + X tail in the scratch
+    cases = [I.custom("bf16", 385, 512, 8448, seed=51),     # tiled, ragged M (padded X tail)
+             I.custom("f32", 130, 70, 200, seed=52),        # fp64 kernel, smaller
+             I.custom("bf16", 300, 256, 512, seed=53),      # few rows: no scratch
+             I.custom("bf16", 200, 136, 264, seed=54),      # few rows, widths off the tile
              I.custom("bf16", 16384, 128, 256, seed=55)]    # large batch: transposed weights in the scratch
     inputs = [I.generate(c, with_dY=False) for c in cases]
     got = []
@@ -75,7 +75,7 @@ def test_forward_static_with_weights_too_large_to_transpose_in_the_array():
 
 def test_forward_static_rejects_what_the_array_cannot_hold():
     dev = "cuda"
-    # 8 bytes per (row, 64-column tile): 32768 x 128 tiles = 32 MiB of partial statistics > 16 MiB
+    # 8 bytes count per (row, 32-column tile) whatever the kernels need today: 32768 x 256 = 64 MiB > 16 MiB
     M, K, N = 32768, 8, 8192
     z = torch.zeros(16, device=dev)
     st = api.fdl_forward_static_raw("f32", M, K, N, z, z, z, z, z, 1e-5, z, z, z, z, None)
