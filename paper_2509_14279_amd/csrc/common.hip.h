@@ -34,7 +34,7 @@ template <> __device__ __forceinline__ bf16_t to_storage<bf16_t, double>(double 
 // ---------------------------------------------------------------------------------------------
 // The normal distribution's CDF Phi and density phi are the two pieces of GELU_erf and its derivative:
 //   GELU(z) = z Phi(z),   GELU'(z) = Phi(z) + z phi(z).
-// fp32 storage evaluates them with the library's fp64 erfc and exp, bf16 storage reads them from the table below; every
+// fp32 storage evaluates them in fp64 (NormalTable), bf16 storage reads them from the table below; every
 // row kernel does it through ActTable, so that the forward statistics, the values normalised and the backward pass agree
 // exactly (for a constant row, rstd = eps^-1/2 multiplies any difference between them into Ahat).
 
@@ -131,15 +131,93 @@ template <bool kPair> struct GaussTable {
   }
 };
 
-// What the row kernels ask: T = float evaluates in fp64, T = bf16 holds the table in the workgroup's LDS (kPair: with
-// z phi(z), for the backward pass).  NT: threads of the workgroup.
+// ---------------------------------------------------------------------------------------------
+// Phi and phi in fp64 (fp32 storage), from a table in LDS and two short series.  Node k holds Phi(-c) and phi(c) at c = k / 64;
+// a = |z| lies h = a - c, |h| <= 1/128, from the nearest one.  With m = c + h/2 the middle and E = phi(m) / phi(c):
+//   E = exp(-h (c + h/4) / 2), six terms behind the first;   phi(z) = phi(c) E^2 exp(-h^2 / 4);
+//   Phi(-a) = Phi(-c) - integral of phi from c to a = Phi(-c) - phi(m) h (1 + (m^2 - 1) h^2 / 24 + (m^4 - 6 m^2 + 3) h^4 / 1920),
+// the Taylor expansion about the middle (phi's even derivatives are Hermite polynomials times phi).  Relative error, |z| up to
+// 3 / 6 / 9 / 13.2: 2e-16 / 7e-16 / 2e-14 / 4e-13 for Phi, 9e-16 / 2e-15 / 3e-14 / 4e-13 for phi; from 13.25 on the tail, below the
+// smallest normal fp32 number, is zero.  (0.5 erfc(-z / sqrt 2), which rounds its argument: 3e-14 at 12.)
+// The row kernels of fp32 storage are bound by this arithmetic: some 30 fp64 instructions and no branch, where the library's
+// erfc and exp go through several ranges per wavefront.  3001 x 1537, us: normalisation 26 -> 19, backward row pass 42 -> 25
+// (with one polynomial of degree 20 for the whole axis and exp's, no table: 20 and 36); steps of 20000 x 128 x 1024 and
+// 8192 x 256 x 4096 454 -> 388 and 1055 -> 974.
+constexpr int kNormalNodes = 848;               // up to 13.25
+struct NormalNode { double tail, density; };
+struct NormalTableData { alignas(16) NormalNode node[kNormalNodes + 1]; };
+constexpr NormalTableData make_normal_table() {
+  NormalTableData t = {};
+  // Phi(-13.25) from the continued fraction, then the same integral from node to node, downwards: all terms are positive
+  double x = 13.25 * 0.70710678118654752440, f = x;
+  for (int n = 60; n >= 1; n--) f = x + 0.5 * (double)n / f;
+  double sum = 0.5 * ctmath::exp_neg(0.5 * 13.25 * 13.25) * ctmath::kInvSqrtPi / f, carry = 0.0;
+  for (int k = kNormalNodes - 1; k >= 0; k--) {
+    const double c = (double)k / 64.0, h = 1.0 / 64.0, m = c + 0.5 * h, m2 = m * m, h2 = h * h;
+    const double series = 1.0 + h2 * ((m2 - 1.0) / 24.0 + h2 * ((m2 * (m2 - 6.0) + 3.0) / 1920.0 +
+                                                                h2 * (((m2 - 15.0) * m2 + 45.0) * m2 - 15.0) / 322560.0));
+    const double add = ctmath::exp_neg(0.5 * m2) * 0.39894228040143267794 * h * series + carry;   // (compensated)
+    const double next = sum + add;
+    carry = (sum - next) + add;
+    sum = next;
+    t.node[k].tail = sum;
+    t.node[k].density = ctmath::exp_neg(0.5 * c * c) * 0.39894228040143267794;
+  }
+  return t;
+}
+__device__ const NormalTableData g_normal_table = make_normal_table();
+
+struct NormalTable {
+  typedef __attribute__((address_space(3))) const double lds_double;
+  uint32_t base;
+  template <int NT> __device__ __forceinline__ void build() {
+    __shared__ __attribute__((aligned(16))) double tbl[2 * (kNormalNodes + 1)];
+    const f32x4* src = reinterpret_cast<const f32x4*>(g_normal_table.node);
+#pragma unroll 4
+    for (int i = threadIdx.x; i <= kNormalNodes; i += NT) reinterpret_cast<f32x4*>(tbl)[i] = src[i];
+    base = (uint32_t)(uintptr_t)(lds_double*)tbl;
+    __syncthreads();
+  }
+  template <bool DENSITY> __device__ __forceinline__ void eval(double z, double& Phi, double& phi) const {
+    const double a = __builtin_fmin(__builtin_fabs(z), 13.25);
+    // (the sum's last bits are the nearest node's number)
+    const double magic = 0x1.8p52, t = __builtin_fma(a, 64.0, magic), k = t - magic;
+    const uint32_t at = base + ((uint32_t)__builtin_bit_cast(uint64_t, t) << 4);
+    typedef __attribute__((ext_vector_type(2))) double f64x2;
+    const f64x2 node = *(const __attribute__((address_space(3))) f64x2*)(uintptr_t)at;
+    const double c = k * (1.0 / 64.0), h = a - c;
+    const double v = h * __builtin_fma(h, 0.25, c), m = __builtin_fma(h, -0.5, a), m2 = m * m, h2 = h * h;
+    double E = 1.0 / 46080.0;
+    E = __builtin_fma(E, v, -1.0 / 3840.0);
+    E = __builtin_fma(E, v, 1.0 / 384.0);
+    E = __builtin_fma(E, v, -1.0 / 48.0);
+    E = __builtin_fma(E, v, 0.125);
+    E = __builtin_fma(E, v, -0.5);
+    E = __builtin_fma(E, v, 1.0);
+    double s = __builtin_fma(m2, m2 - 6.0, 3.0) * (h2 * (1.0 / 1920.0));
+    s = __builtin_fma(h2, __builtin_fma(m2, 1.0 / 24.0, s - 1.0 / 24.0), 1.0);
+    const double middle = node[1] * E;
+    const double q = __builtin_fma(-(middle * h), s, node[0]);
+    Phi = z > 0.0 ? 1.0 - q : q;               // (NaN: q = 0; z Phi and z phi are NaN)
+    if (DENSITY) phi = middle * E * __builtin_fma(h2, __builtin_fma(h2, 1.0 / 32.0, -0.25), 1.0);
+  }
+};
+
+// What the row kernels ask; both tables live in the workgroup's LDS (kPair: with z phi(z), for the backward pass).  NT: threads of the workgroup.
 template <class T, bool kPair, int NT> struct ActTable;
 template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
-  __device__ __forceinline__ void build() {}
-  static __device__ __forceinline__ double gelu(double z) { return z * (0.5 * erfc(-z * 0.70710678118654752440)); }
-  static __device__ __forceinline__ void eval(double z, double& Phi, double& zphi) {
-    Phi = 0.5 * erfc(-z * 0.70710678118654752440);
-    zphi = z * (exp(-0.5 * z * z) * 0.39894228040143267794);
+  NormalTable tab;
+  // every thread of the workgroup calls this; ends with a barrier
+  __device__ __forceinline__ void build() { tab.build<NT>(); }
+  __device__ __forceinline__ double gelu(double z) const {
+    double Phi, phi;
+    tab.eval<false>(z, Phi, phi);
+    return z * Phi;
+  }
+  __device__ __forceinline__ void eval(double z, double& Phi, double& zphi) const {
+    double phi;
+    tab.eval<true>(z, Phi, phi);
+    zphi = z * phi;
   }
 };
 template <bool kPair, int NT> struct ActTable<bf16_t, kPair, NT> {

@@ -337,6 +337,8 @@ template <> struct RawVec<bf16_t, false> { typedef bf16x8 type; };
 template <> struct RawVec<float, true> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
 template <> struct RawVec<bf16_t, true> { typedef __bf16 type __attribute__((ext_vector_type(8), aligned(2))); };
 template <class T> struct RawVec<T, true, 1> { typedef T type __attribute__((ext_vector_type(1))); };
+template <> struct RawVec<float, false, 8> { typedef float type __attribute__((ext_vector_type(8), aligned(16))); };
+template <> struct RawVec<float, true, 8> { typedef float type __attribute__((ext_vector_type(8), aligned(4))); };
 
 template <class T, bool ANY, int V = 16 / (int)sizeof(T)>
 __device__ __forceinline__ typename RawVec<T, ANY, V>::type raw_load(const T* p, int nv) {
@@ -532,16 +534,17 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
   const int64_t col = (int64_t)threadIdx.x * V;
   const int nv = col >= N ? 0 : (N - col > V ? V : (int)(N - col));
   const int64_t left = ldz - col;              // columns of dZ this thread and those behind it write
-  C gm[V], accb[V], accg[V], accz[V];
+  C accb[V], accg[V], accz[V];
+  float gm[V];
 #pragma unroll
-  for (int v = 0; v < V; v++) { gm[v] = 0; accb[v] = 0; accg[v] = 0; accz[v] = 0; }
+  for (int v = 0; v < V; v++) { gm[v] = 0.0f; accb[v] = 0; accg[v] = 0; accz[v] = 0; }
   if (nv == V) {
 #pragma unroll
-    for (int v = 0; v < V; v++) gm[v] = (C)gamma[col + v];
+    for (int v = 0; v < V; v++) gm[v] = gamma[col + v];
   } else {
 #pragma unroll
     for (int v = 0; v < V; v++)
-      if (v < nv) gm[v] = (C)gamma[col + v];
+      if (v < nv) gm[v] = gamma[col + v];
   }
   // D rows are kept in flight, one per buffer; as soon as a buffer has been unpacked its refill with the row D G further
   // on is issued (G = gridDim.x), ahead of that row's barrier and second phase.  mean and rstd travel with the row, as
@@ -587,11 +590,14 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
       tab.eval(z, Phi, zphi);
       ah[v] = (z * Phi) * rs + nmr;                        // (A - mean) rstd, one fused multiply-add
       gp[v] = (Phi + zphi) * rs;
-      g[v] = dy * gm[v];                                   // (columns past the end: dY and gamma are zero)
+      float gv = gm[v];
+      if (sizeof(T) == 4) asm volatile("" : "+v"(gv));     // (converted here: kept as doubles they cost registers)
+      g[v] = dy * (C)gv;                                   // (columns past the end: dY and gamma are zero)
       s1 += g[v];
       s2 += g[v] * ah[v];
       accb[v] += dy;
       accg[v] += dy * ah[v];
+      if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
     }
     fetch(buf, row + D * G);
     wg_sum2<C, NT / 64>(s1, s2, red[buf & 1]);
@@ -603,6 +609,7 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
       if (ANY) dz = v < nv ? dz : (C)0;
       accz[v] += dz;
       o[v] = to_storage<T, C>(dz);
+      if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (BLK) {
       // (every lane takes part in the stores, also one whose own columns lie past the end of the row: the pieces it
@@ -693,7 +700,7 @@ __global__ __launch_bounds__(1024) void finish_kernel(TailSums j) {
 // over the three sweeps (activation and sum; deviations and their squares; scale, shift, store), S vectors of four per
 // thread, so that a row is read once.  ACT as above; Z and Y may be the same buffer (a thread reads its part of a row
 // before it writes it).
-// Bound: HBM (with GELU: the fp64 erfc).  What keeps loads in flight: the next row's vectors are fetched as soon as this
+// Bound: HBM (with GELU: fp64 arithmetic).  What keeps loads in flight: the next row's vectors are fetched as soon as this
 // one's are unpacked, ahead of its two reductions, and several workgroups share a compute unit.  The row streams past the
 // caches: LayerNorm of 8192 x 4096 took 74 us with three trips through memory and caches per row, 64 us in this form with
 // plain loads and stores, 52 us (5.2 TB/s) with the non-temporal hint on both.
@@ -765,6 +772,8 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
   };
   const double inv_n = 1.0 / (double)N;
   fetch(blockIdx.x);
+  Act act;
+  if (ACT == ACT_GELU) act.build();
   for (int64_t row = blockIdx.x; row < M; row += gridDim.x) {
     double a[S][V], sum = 0;
 #pragma unroll
@@ -775,7 +784,7 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
 #pragma unroll
       for (int v = 0; v < V; v++) {
         const double z = (double)raw[s][v];
-        a[s][v] = ACT == ACT_GELU ? Act::gelu(z) : z;  // zeros past the end of the row: GELU(0) = 0
+        a[s][v] = ACT == ACT_GELU ? act.gelu(z) : z;  // zeros past the end of the row: GELU(0) = 0
         sum += ACT == ACT_RMS ? z * z : a[s][v];
       }
     }
@@ -878,7 +887,7 @@ __global__ __launch_bounds__(256) void f2_narrow_kernel(int64_t M, int64_t N, fl
 // and normalises its segment.  So GELU is evaluated twice per element and the row read twice, and a few long rows fill the
 // chip: a workgroup takes rows_per_wg rows of one segment (gamma and beta stay in its registers), as many as leave about 2048
 // workgroups.
-// Bound: HBM for bf16, the fp64 erfc for fp32 storage.  One workgroup per row that streams it three times took, whole
+// Bound: HBM for bf16, fp64 arithmetic for fp32 storage.  One workgroup per row that streams it three times took, whole
 // inference calls, us, that / now: fp32 17 x 42 x 24886 141 / 19, 256 x 34 x 44889 343 / 122; bf16 32 x 256 x 78860 236 / 34,
 // 4096 x 256 x 65536 686 / 606; an earlier form with the sums in the contraction's epilogue, which read each row once, 43, 153, 86
 // and 612.
@@ -1212,9 +1221,22 @@ template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int gro
   const bool any = N % V != 0 || ldz != N;
   const dim3 grid((unsigned)groups);
 #define FDL_B1_ARGS s, M, N, ldz, (const T*)dY, (const T*)Z, gamma, mean, rstd, (T*)dZ, (C*)colpart
+  if constexpr (sizeof(T) == 4) {
+    // (1024 threads have 128 registers each, too few for the fp64 state of four columns: 8192 x 4096 221 us, half as many threads
+    // of eight 123; at up to 2048 columns 256 threads of eight lose to 512 of four, 34 to 25 for 3001 x 1537)
+    if (nt == 1024) {
+      if (N % 8 != 0 || ldz != N) hipLaunchKernelGGL((b1_fused_kernel<T, 512, true, false, 8>), grid, dim3(512), 0, FDL_B1_ARGS);
+      else hipLaunchKernelGGL((b1_fused_kernel<T, 512, false, false, 8>), grid, dim3(512), 0, FDL_B1_ARGS);
+      return;
+    }
+  }
 #define FDL_B1F(NT, ANY, BLK) hipLaunchKernelGGL((b1_fused_kernel<T, NT, ANY, BLK>), grid, dim3(NT), 0, FDL_B1_ARGS)
 #define FDL_B1F_NT(ANY, BLK)                                                                                              \
-  do { if (nt == 256) FDL_B1F(256, ANY, BLK); else if (nt == 512) FDL_B1F(512, ANY, BLK); else FDL_B1F(1024, ANY, BLK); } while (0)
+  do {                                                                                                                    \
+    if (nt == 256) FDL_B1F(256, ANY, BLK);                                                                                \
+    else if (nt == 512) FDL_B1F(512, ANY, BLK);                                                                           \
+    else if constexpr (sizeof(T) == 2) FDL_B1F(1024, ANY, BLK);                                                           \
+  } while (0)
   if constexpr (sizeof(T) == 2) {
     if (blocked) { FDL_B1F_NT(false, true); return; }
   }
