@@ -34,6 +34,34 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 // fp32 storage: all tiles as they are, where there is no scratch for the sums of split ones
 F64Split f64_unsplit(int64_t I, int64_t J) { return F64Split{((I + 63) / 64) * ((J + 63) / 64), 0, 1}; }
 
+// room for the sums of split reductions in 128 x 128 tiles; kept: what the other kernels' plan holds in their place
+constexpr size_t kMidMostSums = (size_t)64 << 20;
+size_t mid_room(Room room, size_t kept) { return room == Room::kAll ? (kept > kMidMostSums ? kept : kMidMostSums) : (room == Room::kTight ? kept : 0); }
+
+// Estimated time, us, of dX and dW on the kernels of q, with their copies and sums of split reductions: prices fitted together with
+// mid_grads_cost's to whole backward passes of 1300 shapes.  With the rule in make_grad_plan the kernels picked take 1.01 times the
+// faster ones' time on average; ten of the shapes became slower by more than 2 %, at most by 13 % (8448 x 1036 x 6582, 416 us).
+double grads_cost(const GradPlan& q) {
+  const int64_t Np = q.pad ? fast_pad_dim(q.N) : q.N, Kp = q.pad ? fast_pad_dim(q.K) : q.K, Mp = q.M > 0 ? q.M : 1;
+  const double mk = (double)Mp * (double)q.K / 1e6, nk = (double)q.N * (double)q.K / 1e6;
+  auto rounds = [](int64_t tiles) { return (double)((tiles + 255) / 256); };
+  auto tiles = [](int64_t I, int64_t J) { return ((I + 255) / 256) * ((J + 255) / 256); };
+  double cost = 0.0;
+  if (q.pad) cost += 5.4 + ((double)(Np * Kp) + (q.stage_x ? (double)(Mp * Kp) : 0.0)) * 2.0 / 1e6 * 0.27;
+  if (q.pair) {
+    const int64_t a = Np / q.split_a, b = q.b4_fast_rows / q.split_b;
+    cost += 11.7 + (double)(a > b ? a : b) * 0.0137;
+    if (q.split_a > 1) cost += q.split_a * mk * 1.05;
+  } else {
+    cost += q.b3_fast ? 11.7 + rounds(tiles(Kp, Mp)) * ((double)Np * 0.0145 + 1.3) : 1.2 * generic_xwt_cost(Mp, q.N, q.K);
+    cost += q.b4_fast ? 11.7 + rounds(tiles(Kp, q.N) * q.split_b) * ((double)q.b4_fast_rows / q.split_b * 0.0137 + 1.3)
+                      : 1.2 * generic_xwt_cost(q.N, Mp, q.K);
+  }
+  if (q.extra) cost += 1.2 * generic_xwt_cost(q.N, Mp - q.b4_fast_rows, q.K);
+  if (q.parts_b > 1) cost += q.parts_b * nk * 1.05;
+  return cost;
+}
+
 thread_local bool t_failure_noted = false;
 
 }  // namespace
@@ -80,11 +108,13 @@ bool ensure_dynamic_lds(const void* kernel, int bytes, OnceFlags* flags) {
   return true;
 }
 
+static void tight_pitch(GradPlan* q);
+
 bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
   if (dt != kF32 && dt != kBF16) return false;
   if (!shape_ok(M, K, N)) return false;
   const size_t cs = dt == kF32 ? 8 : 4;   // arithmetic element
-  const bool split = room == Room::kAll;
+  const bool split = room == Room::kAll || room == Room::kTight;
   Plan q = {};
   q.dt = dt; q.M = M; q.K = K; q.N = N;
 
@@ -97,7 +127,8 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
   const int64_t Mp = M > 0 ? M : 1;
 
   // ---- forward
-  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N, room != Room::kNoCopies) : Xwt::kGeneric;
+  double f1_cost = 0.0;
+  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N, room != Room::kNoCopies, true, false, &f1_cost) : Xwt::kGeneric;
   const bool tiled = f1 == Xwt::kTiled || f1 == Xwt::kPadded;
   q.f1_skinny = f1 == Xwt::kSkinny;
   q.pad = f1 == Xwt::kPadded;
@@ -118,6 +149,15 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
   q.f1_wt = tiled && !q.pad && M >= kTransposeFromRows && q.f1_split == 1;
   q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
   q.fwd_bytes = off;
+  // (128 x 128 tiles need no copies: the sums of their split reduction lie where those would)
+  if (dt == kBF16 && mid_supported(Mp, K, N)) {
+    int parts = 1;
+    if (mid_margin(Mp) * mid_xwt_cost(Mp, K, N, mid_room(room, off - q.off_xtail), &parts) < f1_cost) {
+      q.f1_mid = 1; q.f1_split = parts; q.off_part = q.off_xtail;
+      const size_t need = q.off_part + align256(fast_xwt_part_bytes(Mp, N, parts));
+      if (need > q.fwd_bytes) q.fwd_bytes = need;
+    }
+  }
   // The static entry point's limit is part of its contract (see the header) and does not move with the plan: the tiled
   // kernels' copies for whole 16-byte rows, and 8 bytes per (row, column tile) unless rows of whole vectors up to 8192 meet
   // the tiled kernel.
@@ -147,7 +187,8 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
   off = 0;
   q.off_c12 = off; off += align256(q.b1_fused ? 0 : (size_t)2 * Mp * cs);
   q.off_colpart = off; off += align256((size_t)q.b1_groups * 3 * N * cs);
-  make_grad_plan(dt, M, K, N, split, may_block, &off, &q.g);
+  make_grad_plan(dt, M, K, N, room, may_block, &off, &q.g);
+  tight_pitch(&q.g);
   q.bwd_bytes = off;
   // (one buffer for both passes and for fdl_forward_inference, which keeps mean and rstd in it)
   const size_t fwd_all = q.fwd_bytes + 2 * align256((size_t)Mp * 4) + 256;
@@ -158,7 +199,8 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
 
 // The two contractions that end a backward pass, dX [M,K] = dZ W and dW [N,K] = dZ^T X, with the workspace regions they
 // need behind *off.  may_block: the kernel that writes dZ can write it in 32 x 32 blocks.
-void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool split, bool may_block, size_t* off, GradPlan* p) {
+void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may_block, size_t* off, GradPlan* p) {
+  const bool split = room == Room::kAll || room == Room::kTight;
   GradPlan q = {};
   const size_t ts = dt == kF32 ? 4 : 2;
   const int64_t Mp = M > 0 ? M : 1;
@@ -190,6 +232,7 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool split, bool ma
   q.parts_b = q.split_b + q.extra;
   q.off_dxpart = *off; *off += align256(q.split_a > 1 ? (size_t)q.split_a * partial_stride(M * K) * 4 : 0);
   q.off_dwpart = *off; *off += align256(q.parts_b > 1 ? (size_t)q.parts_b * partial_stride(N * K) * 4 : 0);
+  const size_t sums = *off - q.off_dxpart;
   q.off_wpad = *off; *off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_xpad = *off; *off += align256(q.stage_x ? fast_padded_x_bytes(M, K, true) : 0);
   if (dt == kF32) {
@@ -198,7 +241,23 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool split, bool ma
     q.off_part64_a = *off; *off += align256(f64_part_bytes(q.s64_a));
     q.off_part64_b = *off; *off += align256(f64_part_bytes(q.s64_b));
   }
+  if (dt == kBF16 && mid_supported(Mp, K, N)) {
+    int sa = 1, sb = 1;
+    // (7 %: the estimates' spread.  All backward passes of those shapes: 1.65 times as fast as before, 2.3 times around 2^27 products)
+    if (1.07 * mid_grads_cost(Mp, K, N, mid_room(room, sums), &sa, &sb) < grads_cost(q)) {
+      q.mid = 1; q.blocked = 0; q.split_a = sa; q.split_b = q.parts_b = sb;
+      const size_t na = align256(sa > 1 ? (size_t)sa * partial_stride(M * K) * 4 : 0), nb = align256(sb > 1 ? (size_t)sb * partial_stride(N * K) * 4 : 0);
+      if (na + nb > sums) { q.off_dxpart = *off; *off += na + nb; }      // (the copies of padded mode stay where they are)
+      q.off_dwpart = q.off_dxpart + na;
+    }
+  }
   *p = q;
+}
+
+// 128 x 128 tiles: the smallest pitch of dZ whose rows are aligned vectors, where the buffer holds it
+static void tight_pitch(GradPlan* q) {
+  const int64_t want = (q->N + 7) / 8 * 8, Mp = q->M > 0 ? q->M : 1;
+  if (q->mid && Mp * want <= fast_padded_rows(Mp) * q->ldz) q->ldz = want;
 }
 
 }  // namespace fdl
@@ -232,7 +291,7 @@ extern "C" size_t fdl_workspace_bytes(fdl_dtype dt, int64_t M, int64_t K, int64_
 template <class P, class Make> static fdl_status fit_plan(const void* workspace, size_t have, P* plan, Make make) {
   if (!make(Room::kAll, plan)) return FDL_ERR_SHAPE;
   if (workspace == nullptr) return FDL_ERR_WORKSPACE;
-  for (Room room : {Room::kNoSplit, Room::kNoCopies})
+  for (Room room : {Room::kTight, Room::kNoSplit, Room::kNoCopies})
     if (have < plan->bytes) (void)make(room, plan);
   if (have < plan->bytes) return FDL_ERR_WORKSPACE;
   if (!aligned(workspace, 256)) return FDL_ERR_ALIGN;
@@ -307,7 +366,9 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
   const int64_t M = p.M, K = p.K, N = p.N;
   {
     PhaseTimer t(FDL_PHASE_F1, s);
-    if (p.f1_skinny) {
+    if (p.f1_mid) {
+      launch_mid_xwt(0, M, K, N, X, W, b, nullptr, Zsave, N, p.f1_split, ws + p.off_part, s);
+    } else if (p.f1_skinny) {
       launch_skinny_xwt(0, M, K, N, X, W, b, nullptr, Zsave, N, s);
     } else if (p.pad) {
       void* Wp = ws + p.off_wpad_f;
@@ -382,6 +443,10 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   const fdl_status st = check_forward_args(dt, M, K, N, X, W, b, gamma, beta, eps, Y, Zsave, mean, rstd, &p);
   if (st != FDL_OK) return st;
   if (p.static_need > (size_t)FDL_STATIC_SCRATCH_BYTES) return FDL_ERR_WORKSPACE;   // more than the array is stated to hold
+  if (p.f1_mid) {     // (needs no copies; no room for the sums of a split reduction: unsplit)
+    if (p.off_part + fast_xwt_part_bytes(M, N, p.f1_split) > (size_t)FDL_STATIC_SCRATCH_BYTES) p.f1_split = 1;
+    p.fwd_bytes = p.off_part;
+  }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
     p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the transposed weights: the kernel reads W as it is
   }
@@ -434,12 +499,20 @@ static F64Grads grad_f64(const GradPlan& p, const void* dZ, const void* W, const
   return a;
 }
 
-// bf16 storage: dX = dZ W; where both contractions share a launch (p.pair), dW too
+// bf16 storage: dX = dZ W; where both contractions share a launch (p.mid, p.pair), dW too
 static void launch_grad_dx(const GradPlan& p, const void* dZ, const void* W, const void* X, void* dX, void* dW, char* ws,
                            TailSums* tj, hipStream_t s) {
   const int64_t M = p.M, K = p.K, N = p.N;
   const int64_t Kp = p.pad ? fast_pad_dim(K) : K;
-  if (p.pair) {
+  if (p.mid) {
+    MidGrads a = {};
+    a.M = M; a.K = K; a.N = N; a.sa = p.split_a; a.sb = p.split_b;
+    a.dZ = dZ; a.ldz = p.ldz; a.W = W; a.X = X;
+    a.dX = dX; a.dxpart = ws + p.off_dxpart; a.dW = dW; a.dwpart = ws + p.off_dwpart;
+    launch_mid_grads(a, s);
+    if (p.split_a > 1) sum_later(tj, 0, a.dxpart, p.split_a, M * K, dX);
+    if (p.split_b > 1) sum_later(tj, 1, a.dwpart, p.split_b, N * K, dW);
+  } else if (p.pair) {
     PairArgs a = {};
     a.M = M; a.K = K; a.N = N; a.rows = p.b4_fast_rows; a.sa = p.split_a; a.sb = p.split_b; a.extra = p.extra;
     a.dZ = dZ; a.ldz = p.ldz; a.dz_blocked = p.blocked != 0;
@@ -463,6 +536,7 @@ static void launch_grad_dx(const GradPlan& p, const void* dZ, const void* W, con
 static void launch_grad_dw(const GradPlan& p, const void* dZ, const void* X, void* dW, char* ws, TailSums* tj, hipStream_t s) {
   const int64_t K = p.K, N = p.N, Mf = p.b4_fast_rows;
   float* dwpart = reinterpret_cast<float*>(ws + p.off_dwpart);
+  if (p.mid) return;       // (with dX)
   if (!p.b4_fast) {
     GemmDesc g = {dZ, X, N, K, p.M, p.ldz, K, false, false, p.b4_wb};
     launch_generic_store(g, dW, s);
@@ -522,7 +596,7 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
     } else {
       launch_b1a((int)dt, M, N, dY, Zsave, gamma, mean, rstd, c12, s);
       launch_b1b((int)dt, M, N, p.g.ldz, p.b1_rows_per_group, p.b1_groups, dY, Zsave, gamma, mean, rstd, c12, dZ, colpart, s);
-      if (p.g.pad) launch_zero_cols_bf16(dZ, M, N, p.g.ldz, s);   // the surplus columns enter the contractions
+      if (p.g.pad && !p.g.mid) launch_zero_cols_bf16(dZ, M, N, p.g.ldz, s);   // the surplus columns enter the contractions
     }
   }
   // Where the contractions below leave split reductions behind (bf16 tuned path), their sums and the column sums
@@ -544,7 +618,7 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
   }
   {
     PhaseTimer t(FDL_PHASE_B3, s);
-    if (p.g.pad) {
+    if (p.g.pad && !p.g.mid) {
       StageJobs j = {};
       stage_grad(p.g, &j, X, W, ws);
       launch_stage(j, s);
@@ -611,6 +685,7 @@ namespace {
 // forward product needs (padded weights and bias, X or its last rows, or transposed weights), and what the two gradient
 // contractions need, the masked upstream gradient G among it (the dZ of GradPlan).
 struct ReluPlan {
+  int f1_mid;              // the forward product (and its recomputation) in 128 x 128 tiles, f1_split parts
   int f1_skinny;           // few rows: the forward product (and its recomputation) on the kernel made for them
   int f1_fast, f1_wb;      // the tuned kernel, on the operands as they are
   int pad;                 // or in padded mode (then the gradient contractions run in it too)
@@ -621,33 +696,42 @@ struct ReluPlan {
   size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, off_part, bytes;
 };
 bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan* q) {
-  const bool split = room == Room::kAll;
+  const bool split = room == Room::kAll || room == Room::kTight;
   if (dt != kF32 && dt != kBF16) return false;
   if (!shape_ok(M, K, N)) return false;
   const size_t cs = dt == kF32 ? 8 : 4;
   const int64_t Mp = M > 0 ? M : 1;
-  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N) : Xwt::kGeneric;
+  double f1_cost = 0.0;
+  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N, true, true, false, &f1_cost) : Xwt::kGeneric;
   const bool tiled = f1 == Xwt::kTiled || f1 == Xwt::kPadded;
-  q->pad = f1 == Xwt::kPadded;
+  q->f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
+  const size_t kept = dt == kBF16 ? fast_xwt_part_bytes(M, N, q->f1_split) : 0;
+  int parts = 1;
+  q->f1_mid = dt == kBF16 && mid_supported(Mp, K, N) &&
+              mid_margin(Mp) * mid_xwt_cost(Mp, K, N, mid_room(room, kept), &parts) < f1_cost;
+  q->pad = f1 == Xwt::kPadded && !q->f1_mid;
   q->f1_skinny = f1 == Xwt::kSkinny;
-  q->f1_fast = f1 == Xwt::kTiled;
+  q->f1_fast = f1 == Xwt::kTiled && !q->f1_mid;
   q->f1_wb = generic_wb(Mp, N);
   size_t off = 0;
   q->off_colpart = off; off += align256((size_t)colsum_groups(Mp) * N * cs);
   // (the masking epilogue of the tuned forward product can write blocks)
-  q->f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
-  make_grad_plan(dt, M, K, N, split, /*may_block=*/q->f1_fast && q->f1_split == 1, &off, &q->g);
+  make_grad_plan(dt, M, K, N, room, /*may_block=*/q->f1_fast && q->f1_split == 1, &off, &q->g);
+  if (!q->pad) tight_pitch(&q->g);       // (the padded product's masking epilogue writes whole tiles of columns)
   // the padded copies of W and (where all of it is copied) X serve the forward product and the gradient contractions
   q->off_wpad = q->g.off_wpad;
   q->off_xtail = q->g.off_xpad;
+  // (the room of copies is kept where 128 x 128 tiles do without them: sizes do not depend on which of the kernels is picked)
   if (tiled && !q->g.stage_x) {
-    q->off_xtail = off; off += align256(q->pad ? fast_padded_tail_bytes(K) : (q->f1_fast ? fast_f1_tail_bytes(M, K) : 0));
+    q->off_xtail = off; off += align256(f1 == Xwt::kPadded ? fast_padded_tail_bytes(K) : fast_f1_tail_bytes(M, K));
   }
-  q->off_bpad = off; off += align256(q->pad ? (size_t)fast_pad_dim(N) * 4 : 0);
-  q->f1_wt = q->f1_fast && M >= kTransposeFromRows && q->f1_split == 1;
+  q->off_bpad = off; off += align256(f1 == Xwt::kPadded ? (size_t)fast_pad_dim(N) * 4 : 0);
+  q->f1_wt = f1 == Xwt::kTiled && M >= kTransposeFromRows && q->f1_split == 1;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
   if (dt == kF32) q->f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
-  q->off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q->f1_s64) : fast_xwt_part_bytes(M, N, q->f1_split));
+  if (q->f1_mid) q->f1_split = parts;
+  const size_t sums = dt == kF32 ? f64_part_bytes(q->f1_s64) : fast_xwt_part_bytes(M, N, q->f1_split);
+  q->off_part = off; off += align256(sums > kept ? sums : kept);
   q->bytes = off;
   return true;
 }
@@ -656,7 +740,9 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan
 // mode the operands' copies must have been staged (off_xtail, off_wpad, off_bpad).
 void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int64_t N, const void* X, const void* W,
                   const float* b, const void* aux, void* out, char* ws, hipStream_t s) {
-  if (q.f1_skinny) {
+  if (q.f1_mid) {
+    launch_mid_xwt(kind, M, K, N, X, W, b, aux, out, kind == 2 ? q.g.ldz : N, q.f1_split, ws + q.off_part, s);
+  } else if (q.f1_skinny) {
     launch_skinny_xwt(kind, M, K, N, X, W, b, aux, out, kind == 2 ? q.g.ldz : N, s);
   } else if (q.pad) {
     launch_fast_xwt_padded(kind, M, K, N, q.g.stage_x != 0, X, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<const float*>(ws + q.off_bpad),
@@ -727,8 +813,8 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
   char* ws = static_cast<char*>(workspace);
   void* G = ws + q.g.off_dz;
   void* colpart = ws + q.off_colpart;
-  if (q.g.pad) {
-    // the copies serve the recomputation, where that is tiled, and both gradient contractions
+  if (q.pad || (q.g.pad && !q.g.mid)) {
+    // the copies serve the recomputation, where that is padded, and both gradient contractions, where those are
     StageJobs j = {};
     if (!q.pad) {
       stage_padded(&j, M, K, N, true, q.g.stage_x ? X : nullptr, W, nullptr, ws + q.g.off_xpad, ws + q.g.off_wpad, nullptr);
@@ -736,7 +822,7 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
       stage_matrix(&j, nullptr, 0, 0, 0, G, q.g.b4_fast_rows > M ? q.g.b4_fast_rows : M, q.g.ldz);
     } else {
       stage_padded(&j, M, K, N, q.g.stage_x != 0, X, W, b, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<float*>(ws + q.off_bpad));
-      if (q.g.b4_fast_rows > M)
+      if (q.g.b4_fast_rows > M && !q.g.mid)
         stage_matrix(&j, nullptr, 0, 0, 0, static_cast<char*>(G) + (size_t)M * q.g.ldz * 2, q.g.b4_fast_rows - M, q.g.ldz);
     }
     launch_stage(j, s);
@@ -813,7 +899,7 @@ struct FfnPlan {
   size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, off_part, bytes;
 };
 bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* q) {
-  const bool split = room == Room::kAll;
+  const bool split = room == Room::kAll || room == Room::kTight;
   if (dt != kF32 && dt != kBF16) return false;
   if (M < 0 || D < 1 || H < 1 || M > kMaxDim || D > kMaxDim || H > kMaxDim) return false;
   if (M * H > kMaxElems || M * D > kMaxElems || H * D > kMaxElems) return false;

@@ -1057,7 +1057,8 @@ __global__ __launch_bounds__(256) void xwt_reduce_kernel(const float* __restrict
     float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     const float* src = part + m * N + n;
     if (left == 4) {
-      for (int k = 0; k < split; k++) {
+#pragma unroll 4
+      for (int k = 0; k < split; k++) {            // (four loads in flight)
         const f32x4_u t = *reinterpret_cast<const f32x4_u*>(src + (int64_t)k * stride);
 #pragma unroll
         for (int e = 0; e < 4; e++) z[e] += t[e];
@@ -1087,6 +1088,15 @@ __global__ __launch_bounds__(256) void xwt_reduce_kernel(const float* __restrict
 }
 }  // namespace
 
+void launch_xwt_reduce(int kind, int split, const void* part, int64_t stride, int64_t M, int64_t N, const float* bias, const void* aux,
+                       void* out, int64_t ldo, hipStream_t s) {
+  const int64_t vectors = M * ((ldo + 3) / 4);
+  const unsigned blocks = (unsigned)((vectors + 255) / 256 < 4096 ? (vectors + 255) / 256 : 4096);
+  auto kern = kind == 1 ? xwt_reduce_kernel<1> : (kind == 2 ? xwt_reduce_kernel<2> : xwt_reduce_kernel<0>);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, (const float*)part, split, stride, M, N, bias, (const bf16_t*)aux,
+                     (bf16_t*)out, ldo);
+}
+
 // split > 1: part holds fast_xwt_part_bytes; p: the product's operands, tiles and sizes (a forward product of the functions
 // above, before its epilogue is chosen); crag: any N
 static void launch_xwt_split(FastParams p, bool rag, bool crag, int kind, int split, void* part, int64_t M, int64_t N,
@@ -1097,11 +1107,7 @@ static void launch_xwt_split(FastParams p, bool rag, bool crag, int kind, int sp
   if (crag) launch<false, false, EPI_PARTIAL, kF1BK, NS, true, true>(p, s);
   else if (rag) launch<false, false, EPI_PARTIAL, kF1BK, NS, true>(p, s);
   else launch<false, false, EPI_PARTIAL, kF1BK, NS>(p, s);
-  const int64_t vectors = M * ((ldo + 3) / 4);
-  const unsigned blocks = (unsigned)((vectors + 255) / 256 < 4096 ? (vectors + 255) / 256 : 4096);
-  auto kern = kind == 1 ? xwt_reduce_kernel<1> : (kind == 2 ? xwt_reduce_kernel<2> : xwt_reduce_kernel<0>);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, (const float*)part, split, p.pstride, M, N, bias, (const bf16_t*)aux,
-                     (bf16_t*)out, ldo);
+  launch_xwt_reduce(kind, split, part, p.pstride, M, N, bias, aux, out, ldo, s);
 }
 
 // Gated pair of products for the feed-forward block: Hout[m][h] = SiLU(sum_d X[m][d] Wg[h][d]) * (sum_d X[m][d] Wu[h][d]).

@@ -226,12 +226,12 @@ static int64_t skinny_rows(int64_t K) { return K % 8 == 0 ? 4096 : 2048; }
 static double skinny_cost(int64_t M, int64_t K, int64_t N) {
   // start, per 256 workgroups, the same and 1000 elements of K, 1000 elements of K
   static const double price[4][2][4] = {
-      {{2.6, 0.55, 1.2, 0.9}, {2.7, 0.70, 5.2, 2.0}},      // 1 x 1 blocks: rows of whole 16 bytes, any rows
+      {{2.6, 0.55, 1.2, 0.9}, {2.7, 0.70, 5.2, 2.0}},      // 1 x 1 blocks: K even, odd
       {{2.8, 0.43, 1.9, 1.6}, {3.0, 0.49, 8.4, 1.5}},      // 2 x 1
       {{3.5, 0.63, 1.0, 3.0}, {3.5, 0.43, 2.8, 9.7}},      // 2 x 2
       {{2.7, 1.8, 4.6, 1.2}, {3.1, 1.9, 14.0, 1.5}}};      // 4 x 2
   const SkinnyTile t = skinny_tile(M, N);
-  const double* p = price[t.mb == 1 ? 0 : (t.nb == 1 ? 1 : (t.mb == 2 ? 2 : 3))][K % 8 == 0 ? 0 : 1];
+  const double* p = price[t.mb == 1 ? 0 : (t.nb == 1 ? 1 : (t.mb == 2 ? 2 : 3))][K % 2 == 0 ? 0 : 1];   // (4-byte addresses cost as much as 16-byte ones)
   const double wgs = (double)((N + 16 * t.nb - 1) / (16 * t.nb)) * (double)((M + 16 * t.mb - 1) / (16 * t.mb)) / 256.0;
   const double k = (double)K / 1000.0;
   return p[0] + (double)M / 2000.0 + wgs * (p[1] + p[2] * k) + p[3] * k;
@@ -240,7 +240,8 @@ Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy, bool may_pad, bool 
   Xwt best = Xwt::kGeneric;
   double cost = generic_xwt_cost(M, K, N);
   auto offer = [&](Xwt kernel, double c) { if (c < cost) { best = kernel; cost = c; } };
-  if (M <= skinny_rows(K)) offer(Xwt::kSkinny, skinny_cost(M, K, N) * (K % 8 == 0 ? 1.1 : 1.25));
+  const double skinny = M <= skinny_rows(K) ? skinny_cost(M, K, N) : 0.0;
+  if (M <= skinny_rows(K)) offer(Xwt::kSkinny, skinny * (K % 8 == 0 ? 1.1 : 1.25));
   if (fast_f1_supported(M, K, N) && (may_copy || M % 256 == 0)) {
     // (a partial last row tile takes a copy of X's last rows, unless X has readable rows behind them)
     offer(Xwt::kTiled, 1.05 * (fast_xwt_cost(M, K, N, nullptr) + (M % 256 != 0 && !x_padded ? 4.0 : 1.0)));
@@ -249,7 +250,7 @@ Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy, bool may_pad, bool 
     const double copies = (double)(Np * Kp) * 2.0 + (fast_padded_stages_x(K) ? (double)(M * Kp) * 2.0 : 0.0);
     offer(Xwt::kPadded, 1.05 * (10.0 + fast_xwt_cost(M, K, N, nullptr) + copies / 3e6));
   }
-  if (cost_out != nullptr) *cost_out = cost;
+  if (cost_out != nullptr) *cost_out = best == Xwt::kSkinny ? skinny : cost;
   return best;
 }
 

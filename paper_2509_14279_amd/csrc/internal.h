@@ -39,6 +39,8 @@ struct GradPlan {
   size_t off_dxpart;      // float [split_a][M][K]   (split_a > 1)
   size_t off_dwpart;      // float [parts_b][N][K]   (parts_b > 1)
   size_t off_wpad, off_xpad;   // zero-padded copies of W and (stage_x) X
+  int mid;                // 1: both contractions in 128 x 128 tiles, in one launch (gemm_mid.hip); the fields above say what would
+                          //    run otherwise, pitch and parts are this path's
   F64Split s64_a, s64_b;  // fp32 storage: dX, dW
   size_t off_part64_a, off_part64_b;   // their split tiles' sums
 };
@@ -47,6 +49,7 @@ struct Plan {
   int dt;
   int64_t M, K, N;
   // forward
+  int f1_mid;             // 1: 128 x 128 tiles (before those below); f1_split parts, their sums at off_part
   int f1_skinny;          // 1: bf16 kernel for few rows (before the two below)
   int f1_fast;            // 1: bf16 fast MFMA kernel, 0: generic kernel
   int f1_wb;              // generic kernel: 16x16 blocks per wave tile side (wave tile = 16*wb)
@@ -74,11 +77,11 @@ struct Plan {
   size_t bytes;           // max(fwd, bwd)
 };
 
-// split = false: no reduction split, that is without the partial sums that are the optional part of the workspace.
-void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, bool split, bool may_block, size_t* off, GradPlan* p);
-// What a plan may use the workspace for: everything; no partial sums of split reductions; nor, in the block's forward pass,
-// copies of the operands (the kernels that need none then form its product).
-enum class Room { kAll, kNoSplit, kNoCopies };
+// What a plan may use the workspace for: everything; for the sums of split reductions in 128 x 128 tiles only what the other
+// kernels would use; no partial sums of split reductions; nor, in the block's forward pass, copies of the operands (the kernels that
+// need none then form its product).
+enum class Room { kAll, kTight, kNoSplit, kNoCopies };
+void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may_block, size_t* off, GradPlan* p);
 // Returns false when the shape or dtype is not supported.
 bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p);
 
@@ -269,5 +272,27 @@ struct PairArgs {
   void* dX; void* dxpart; void* dW; void* dwpart;
 };
 void launch_fast_pair(const PairArgs& a, hipStream_t s);
+// out = f(the parts' sums + bias), kinds as launch_fast_xwt; parts [M][N] fp32, stride elements apart
+void launch_xwt_reduce(int kind, int split, const void* part, int64_t stride, int64_t M, int64_t N, const float* bias, const void* aux,
+                       void* out, int64_t ldo, hipStream_t s);
+
+// ---- bf16 products in 128 x 128 tiles (gemm_mid.hip): any alignment, no copies; K, N >= 8 ---------
+bool mid_supported(int64_t M, int64_t K, int64_t N);
+// estimated times, us, and the parts of the reductions that give them; room: bytes for the parts' fp32 sums
+double mid_xwt_cost(int64_t M, int64_t K, int64_t N, size_t room, int* split);
+double mid_margin(int64_t M);
+double mid_grads_cost(int64_t M, int64_t K, int64_t N, size_t room, int* sa, int* sb);
+// as launch_fast_xwt (kind 2 leaves columns of out behind N as they are); part: fast_xwt_part_bytes(M, N, split)
+void launch_mid_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias, const void* aux,
+                    void* out, int64_t ldo, int split, void* part, hipStream_t s);
+// dX and dW in one launch; split reductions leave fp32 sums as launch_fast_pair
+struct MidGrads {
+  int64_t M, K, N;
+  int sa, sb;
+  const void* dZ; int64_t ldz;
+  const void* W; const void* X;
+  void* dX; void* dxpart; void* dW; void* dwpart;
+};
+void launch_mid_grads(const MidGrads& a, hipStream_t s);
 
 }  // namespace fdl

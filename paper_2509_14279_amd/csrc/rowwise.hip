@@ -672,7 +672,15 @@ __global__ __launch_bounds__(1024) void finish_kernel(TailSums j) {
       if (i >= j.n[k]) return;
       const float* part = j.part[k];
       f32x4 acc = *reinterpret_cast<const f32x4*>(part + i);
-      for (int q = 1; q < j.parts[k]; q++) {
+      int q = 1;
+      for (; q + 4 <= j.parts[k]; q += 4) {        // (four loads in flight)
+        f32x4 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) t[u] = *reinterpret_cast<const f32x4*>(part + (int64_t)(q + u) * j.stride[k] + i);
+#pragma unroll
+        for (int u = 0; u < 4; u++) { acc[0] += t[u][0]; acc[1] += t[u][1]; acc[2] += t[u][2]; acc[3] += t[u][3]; }
+      }
+      for (; q < j.parts[k]; q++) {
         const f32x4 t = *reinterpret_cast<const f32x4*>(part + (int64_t)q * j.stride[k] + i);
         acc[0] += t[0]; acc[1] += t[1]; acc[2] += t[2]; acc[3] += t[3];
       }
