@@ -886,6 +886,7 @@ namespace {
 // down projection's fast kernel may read a partial last row tile; U only where the two products are separate kernels),
 // then the padded copy of X's last rows.
 struct FfnPlan {
+  int gate_mid, down_mid;  // 128 x 128 tiles (before those below; down_split parts)
   int gate_skinny, down_skinny;   // few rows: the kernel made for them
   int gate_fused;          // 1: one kernel forms both products and the gated activation (no M x H round trip)
   int gate_pad, down_pad;  // the same kernels on zero-padded copies of the weights (widths off their tiles)
@@ -908,7 +909,7 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* 
   // off the tiles: padded copies, where the padding is not most of the work nor the launches most of the time
   const int64_t Hp = fast_gate_pad_h(H), Dq = fast_gate_pad_d(D), Dp = fast_pad_dim(D);
   const bool can_pad = dt == kBF16 && M >= 128 && M * D * H >= kStageFromWork && Hp * Dp <= 6 * H * D && (Hp / 128) * ((M + 255) / 256) <= (1 << 30);
-  const GatePlan g = dt == kBF16 ? pick_gate(Mp, D, H, can_pad) : GatePlan{Gate::kSeparate, Xwt::kGeneric};
+  const GatePlan g = dt == kBF16 ? pick_gate(Mp, D, H, can_pad) : GatePlan{Gate::kSeparate, Xwt::kGeneric, 0.0, 0.0};
   q->gate_skinny = g.gate == Gate::kSkinny;
   q->gate_fused = g.gate == Gate::kTiled;
   q->gate_pad = g.gate == Gate::kPadded;
@@ -940,6 +941,20 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* 
   const size_t up64 = dt == kF32 ? f64_part_bytes(q->up_s64) : 0;
   const size_t down = dt == kF32 ? f64_part_bytes(q->down_s64) : fast_xwt_part_bytes(M, D, q->down_split);
   q->off_part = off; off += align256(up64 > down ? up64 : down);
+  q->gate_mid = q->down_mid = 0;
+  if (dt == kBF16 && mid_supported(Mp, D, H)) {
+    // either product, or both, where that is estimated to be faster (a padded gate product and its down product go together)
+    int parts = 1;
+    const double md = mid_margin(Mp) * mid_xwt_cost(Mp, H, D, mid_room(room, down), &parts), mg = mid_margin(Mp) * mid_gate_cost(Mp, D, H);
+    const bool both = q->gate_pad || q->down_pad;
+    q->gate_mid = both ? mg + md < g.gate_cost + g.down_cost : mg < g.gate_cost;
+    q->down_mid = both ? q->gate_mid : md < g.down_cost;
+    if (q->gate_mid) { q->ldg = H; q->gate_pad = 0; }
+    if (q->down_mid) { q->down_split = parts; q->down_pad = 0; }
+    if (q->gate_mid || q->down_mid) q->g_blocked = 0;
+    const size_t sums = q->down_mid ? fast_xwt_part_bytes(M, D, parts) : down;
+    if (q->off_part + align256(sums) > off) off = q->off_part + align256(sums);
+  }
   q->bytes = off;
   return true;
 }
@@ -978,7 +993,9 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     if (q.down_pad) stage_matrix(&j, Wd, D, H, H, ws + q.off_wdp, fast_pad_dim(D), Hp);
     launch_stage(j, s);
   }
-  if (q.gate_skinny) {
+  if (q.gate_mid) {
+    launch_mid_gate(M, D, H, X, Wg, Wu, G, s);
+  } else if (q.gate_skinny) {
     launch_skinny_gate(M, D, H, X, Wg, Wu, G, s);
   } else if (q.gate_pad) {
     launch_fast_gate_padded(M, D, H, X, ws + q.off_xtail, ws + q.off_wgp, ws + q.off_wup, G, s);
@@ -994,8 +1011,10 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, U, ws + q.off_part, s);
     else launch_generic_xwt(0, g, nullptr, nullptr, U, H, s);
   }
-  if (!q.gate_fused && !q.gate_skinny && !q.gate_pad) launch_silu_mul((int)dt, M * H, G, U, G, s);
-  if (q.down_pad) {
+  if (!q.gate_mid && !q.gate_fused && !q.gate_skinny && !q.gate_pad) launch_silu_mul((int)dt, M * H, G, U, G, s);
+  if (q.down_mid) {
+    launch_mid_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, q.down_split, ws + q.off_part, s);
+  } else if (q.down_pad) {
     launch_fast_down_padded(M, D, q.ldg, G, ws + q.off_wdp, Y, q.down_split, ws + q.off_part, s);
   } else if (q.down_skinny) {
     launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, s);

@@ -5,6 +5,8 @@
 //   forward  Z[m][n]  = sum_k X[m][k] W[n][k] + b[n]   P = W, Q = X, both r-contiguous
 //   dX[m][k] = sum_n dZ[m][n] W[n][k]                  P = W (r-major), Q = dZ (r-contiguous)
 //   dW[n][k] = sum_m dZ[m][n] X[m][k]                  P = X, Q = dZ, both r-major
+//   H[m][h]  = SiLU(sum_d X[m][d] Wg[h][d]) * sum_d X[m][d] Wu[h][d]: the 128 rows of a P slice are 32 gate rows, the same 32 up
+//   rows, the next 32 of each (a wave's blocks a = 0, 1 then hold both products of the same columns); 64 output columns per tile
 //
 // Bound: with one 128 x 128 tile per half of a compute unit, the operands' way from the L2 (a slice of 64 is 32 KB per tile for
 // 2 MFLOP) and the latency of each slice's trip; the matrix cores are half idle.  What it has over the 256 x 256 tiles is four
@@ -26,7 +28,7 @@
 namespace fdl {
 namespace {
 
-enum { MID_STORE = 0, MID_RELU = 1, MID_MASK = 2, MID_PARTIAL = 3 };
+enum { MID_STORE = 0, MID_RELU = 1, MID_MASK = 2, MID_PARTIAL = 3, MID_GATE = 4 };
 
 constexpr int kMidTile = 128, kMidSlice = 64;
 constexpr int kMidOperand = kMidTile * kMidSlice * 2;      // bytes of an operand's slice
@@ -34,6 +36,7 @@ constexpr int kMidLds = 2 * 2 * kMidOperand;
 
 struct MidParams {
   const bf16_t* P; const bf16_t* Q;
+  const bf16_t* P2;        // MID_GATE: the second P operand (same shape and pitch)
   int64_t ldp, ldq;
   bf16_t* C;               // [J][ldc]
   int64_t ldc;
@@ -63,16 +66,20 @@ __device__ __forceinline__ u32x4 drop_front(u32x4 v, int skip) {
   return __builtin_bit_cast(u32x4, x);
 }
 
-// One operand's 128 x 64 slice; a thread moves four 16-byte chunks of it.  RM: r-major in memory.
-template <bool RM> struct MidSide {
+// One operand's 128 x 64 slice; a thread moves four 16-byte chunks of it.  RM: r-major in memory.  TWO (r-contiguous): rows of two
+// matrices in turn, 32 of each.
+template <bool RM, bool TWO = false> struct MidSide {
   global_char* at;         // the slice fetched next (wave-uniform)
+  global_char* at2;        // TWO: of the second matrix
   int64_t step;            // bytes from slice to slice
   uint32_t off[4];         // this thread's chunks
   uint32_t put;            // their place in LDS (4 KB apart)
   uint32_t get[4];         // the lane's fragments: RM by block of 32, else by sub-slice of 16
 
+  // row of a slice that chunk q of this thread belongs to, in its matrix
+  static __device__ __forceinline__ int row_of(int q, int tid) { return (tid >> 3) + 32 * (TWO ? q >> 1 : q); }
   // I rows of the operand (RM: columns) from i0 on; w: the wave's half
-  __device__ __forceinline__ void init(const bf16_t* base, int64_t ld, int i0, int I, int64_t r0, int tid, int w) {
+  __device__ __forceinline__ void init(const bf16_t* base, const bf16_t* base2, int64_t ld, int i0, int I, int64_t r0, int tid, int w) {
     const int lane = tid & 63;
     if (RM) {
       int c = (tid & 15) * 8;
@@ -92,11 +99,12 @@ template <bool RM> struct MidSide {
     } else {
 #pragma unroll
       for (int q = 0; q < 4; q++) {
-        int row = (tid >> 3) + 32 * q;
+        int row = row_of(q, tid);
         row = row < I - i0 ? row : I - i0 - 1;
         off[q] = (uint32_t)(((int64_t)row * ld + (tid & 7) * 8) * 2);
       }
       at = (global_char*)(base + (int64_t)i0 * ld + r0);
+      if (TWO) at2 = (global_char*)(base2 + (int64_t)i0 * ld + r0);
       step = kMidSlice * 2;
       put = (uint32_t)((tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) << 4));
       const int row = w * 64 + (lane & 31), t0 = (lane >> 5) ^ ((lane >> 1) & 7);
@@ -107,11 +115,11 @@ template <bool RM> struct MidSide {
   __device__ __forceinline__ u32x4 fetch(int q) const {
     uint32_t o = off[q];
     asm volatile("" : "+v"(o));      // (kept as 64-bit numbers the offsets take twice the registers)
-    return *(global_u32x4_u*)(at + o);
+    return *(global_u32x4_u*)((TWO && (q & 1) ? at2 : at) + o);
   }
   // The slice at r0, the last one, where it reaches past the reduction's end R or, RM, the end of the matrix: chunks that pass an
   // end are the last eight elements before it (I >= 8, R >= 8), which trim() moves to their place.
-  __device__ __forceinline__ void aim_end(const bf16_t* base, int64_t ld, int i0, int I, int64_t r0, int64_t R, int tid) {
+  __device__ __forceinline__ void aim_end(const bf16_t* base, const bf16_t* base2, int64_t ld, int i0, int I, int64_t r0, int64_t R, int tid) {
     if (RM) {
       const int c = i0 + (tid & 15) * 8, cc = c < I - 8 ? c : I - 8;
       const int rows = (int)(R - r0);
@@ -125,11 +133,12 @@ template <bool RM> struct MidSide {
       const int64_t r = r0 + (tid & 7) * 8, rc = r < R - 8 ? r : R - 8;
 #pragma unroll
       for (int q = 0; q < 4; q++) {
-        int row = (tid >> 3) + 32 * q;
+        int row = row_of(q, tid);
         row = row < I - i0 ? row : I - i0 - 1;
         off[q] = (uint32_t)(((int64_t)row * ld + rc) * 2);
       }
       at = (global_char*)(base + (int64_t)i0 * ld);
+      if (TWO) at2 = (global_char*)(base2 + (int64_t)i0 * ld);
     }
   }
   // chunk q of that slice: zeros past the ends
@@ -170,7 +179,8 @@ __device__ __forceinline__ void mid_unit(const MidParams& p, const int id, char*
   if (tile >= ntiles) return;
   const int band = tile / (8 * p.tiles_i), rem = tile - band * 8 * p.tiles_i;
   const int band_h = p.tiles_j - band * 8 < 8 ? p.tiles_j - band * 8 : 8;
-  const int i0 = rem / band_h * kMidTile, j0 = (band * 8 + rem % band_h) * kMidTile;
+  constexpr bool kGate = EPI == MID_GATE;
+  const int i0 = rem / band_h * (kGate ? kMidTile / 2 : kMidTile), j0 = (band * 8 + rem % band_h) * kMidTile;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave & 1, wj = wave >> 1;
   const int64_t r_begin = (int64_t)pt * p.rlen, r_end = r_begin + p.rlen < p.R ? r_begin + p.rlen : p.R;
@@ -187,9 +197,11 @@ __device__ __forceinline__ void mid_unit(const MidParams& p, const int id, char*
     for (int b = 0; b < 2; b++)
 #pragma unroll
       for (int r = 0; r < 16; r++) acc[a][b][r] = 0.0f;
-  MidSide<P_RM> sp; MidSide<Q_RM> sq;
-  sp.init(p.P, p.ldp, i0, p.I, r_begin, tid, wi);
-  sq.init(p.Q, p.ldq, j0, p.J, r_begin, tid, wj);
+  typedef MidSide<P_RM, kGate> SP;
+  typedef MidSide<Q_RM> SQ;
+  SP sp; SQ sq;
+  sp.init(p.P, p.P2, p.ldp, i0, p.I, r_begin, tid, wi);
+  sq.init(p.Q, nullptr, p.ldq, j0, p.J, r_begin, tid, wj);
   const int total = (int)((r_end - r_begin + kMidSlice - 1) / kMidSlice);      // full, or one more: the end slice
   const int64_t r_last = r_begin + (int64_t)full * kMidSlice;
   if (total > 0) {
@@ -206,11 +218,15 @@ __device__ __forceinline__ void mid_unit(const MidParams& p, const int id, char*
       sp.at += more ? sp.step : 0;
       sq.at += more ? sq.step : 0;
       asm volatile("" : "+s"(sp.at), "+s"(sq.at));
+      if constexpr (kGate) {
+        sp.at2 += more ? sp.step : 0;
+        asm volatile("" : "+s"(sp.at2));
+      }
       if (ahead == full && full < total) {
         int t = tid;
         asm volatile("" : "+v"(t));    // (not to be worked out ahead of the loop)
-        sp.aim_end(p.P, p.ldp, i0, p.I, r_last, p.R, t);
-        sq.aim_end(p.Q, p.ldq, j0, p.J, r_last, p.R, t);
+        sp.aim_end(p.P, p.P2, p.ldp, i0, p.I, r_last, p.R, t);
+        sq.aim_end(p.Q, nullptr, p.ldq, j0, p.J, r_last, p.R, t);
       }
     };
     auto load = [&](int q) __attribute__((always_inline)) { return q < 4 ? sp.fetch(q) : sq.fetch(q - 4); };
@@ -221,7 +237,7 @@ __device__ __forceinline__ void mid_unit(const MidParams& p, const int id, char*
     auto trim = [&](int q, u32x4 x) __attribute__((always_inline)) {
       int t = tid;
       asm volatile("" : "+v"(t));
-      return q < 4 ? MidSide<P_RM>::trim(q, x, i0, p.I, r_last, p.R, t) : MidSide<Q_RM>::trim(q - 4, x, j0, p.J, r_last, p.R, t);
+      return q < 4 ? SP::trim(q, x, i0, p.I, r_last, p.R, t) : SQ::trim(q - 4, x, j0, p.J, r_last, p.R, t);
     };
     // fragment n of a sub-slice, in the order of their use: P0 Q0 Q1 P1
     auto read = [&](int buf, int kk, int n) __attribute__((always_inline)) {
@@ -231,8 +247,8 @@ __device__ __forceinline__ void mid_unit(const MidParams& p, const int id, char*
       else fq[kk & 1][n - 1] = sq.frag(lp + kMidOperand, n - 1, kk);
     };
     if (full == 0) {
-      sp.aim_end(p.P, p.ldp, i0, p.I, r_last, p.R, tid);
-      sq.aim_end(p.Q, p.ldq, j0, p.J, r_last, p.R, tid);
+      sp.aim_end(p.P, p.P2, p.ldp, i0, p.I, r_last, p.R, tid);
+      sq.aim_end(p.Q, nullptr, p.ldq, j0, p.J, r_last, p.R, tid);
     }
 #pragma unroll
     for (int q = 0; q < 8; q++) v[0][q] = load(q);
@@ -319,6 +335,40 @@ __device__ __forceinline__ void mid_unit(const MidParams& p, const int id, char*
   // The tile leaves through LDS as rows of 256 bytes (unit u of 8 bytes of row w in slot u ^ ((w & 15) << 1)).
   __syncthreads();
   typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+  if constexpr (kGate) {
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+      const int il = wi * 32 + g * 8 + half * 4;
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        const int row = wj * 64 + b * 32 + l32;
+        bf16x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const float z = acc[0][b][g * 4 + e], u = acc[1][b][g * 4 + e];
+          v[e] = (bf16_t)(z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * z)) * u);
+        }
+        *(lds_bf16x4*)(lds + row * 256 + (((il >> 2) ^ ((row & 15) << 1)) << 3)) = v;
+      }
+    }
+    __syncthreads();
+    const int c8 = tid & 7, left = p.I - (i0 + c8 * 8);
+#pragma unroll
+    for (int it = 0; it < 4; it++) {
+      const int row = it * 32 + (tid >> 3), j = j0 + row;
+      if (j >= p.J || left <= 0) continue;
+      const u32x4 v = *(const lds_u32x4*)(lds + row * 256 + ((c8 ^ (row & 15)) << 4));
+      bf16_t* dst = p.C + (int64_t)j * p.ldc + i0 + c8 * 8;
+      if (left >= 8) {
+        *reinterpret_cast<u32x4_u*>(dst) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+          if (e < left) reinterpret_cast<unsigned short*>(dst)[e] = (unsigned short)(v[e >> 1] >> ((e & 1) * 16));
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int a = 0; a < 2; a++)
 #pragma unroll
@@ -422,24 +472,24 @@ bool mid_supported(int64_t M, int64_t K, int64_t N) {
 }
 
 // Estimated times, us.  256 compute units take the units of a launch in turn; two on one compute unit share it (a slice of both
-// 0.93, of one alone 0.36 - 0.40, so that a second unit costs less than a third round).  Rows that start at odd elements (K odd)
-// cost half as much again per slice, 4-byte addresses nothing.  The sums of a split reduction: a launch (forward; the gradients'
-// are added by the launch that ends the pass anyway), their traffic, and a little per part.  Fitted to 1300 shapes of 64 - 65536
-// rows, K to 4096, N to 16384 and up to 2^36 products, every split up to 8 (forward), 8 x 32 (gradients): within 0.81 - 1.14
-// (forward), 0.80 - 1.19 (backward) of the measured time for 95 % of them.
+// 0.87, of one alone 0.35 - 0.40, so that a second unit costs less than a third round).  Rows whose slices straddle cache lines cost
+// more, those that start at odd elements more still; 4-byte addresses cost what 16-byte ones do.  The sums of a split reduction: a
+// launch (forward; the gradients' are added by the launch that ends the pass anyway), their traffic, and a little per part.
+// Fitted to 1300 shapes of 64 - 65536 rows, K to 4096, N to 16384 and up to 2^36 products, every split up to 8 (forward), 8 x 32
+// (gradients): within 0.83 - 1.13 (forward), 0.80 - 1.19 (whole backward passes) of the measured time for 95 % of them.
 double mid_xwt_cost(int64_t M, int64_t K, int64_t N, size_t room, int* split_out) {
   const int64_t tiles = mid_tiles(N, M), slices = (K + kMidSlice - 1) / kMidSlice;
-  const double odd = K % 2 ? 1.48 : 1.0, mn = (double)M * (double)N / 1e6;
+  const double odd = K % 2 ? 1.27 : 1.0, lines = K % 64 ? 1.28 : 1.0, alone = K % 64 ? 1.16 : 1.0, mn = (double)M * (double)N / 1e6;
   const double load = (double)K * (double)(M + N) * 2.0 / 5e6;       // the operands, once, at 5 TB/s
   double best = 0.0;
   for (int split = 1; split <= 8; split++) {
     if (split > 1 && (slices < 2 * split || tiles * split > 1536 || fast_xwt_part_bytes(M, N, split) > room)) break;
     const int64_t held = (tiles * split + 255) / 256;
     const double len = (double)((slices + split - 1) / split) * odd;
-    double cost = (double)(held / 2) * (len * 0.93 - 0.5) + (double)(held % 2) * (len * 0.364 + 0.1);
+    double cost = (double)(held / 2) * (len * lines * 0.865 - 0.9) + (double)(held % 2) * (len * alone * 0.35 + 0.2);
     if (cost < load) cost = load;
-    cost += 6.2 + 0.5 * mn;
-    if (split > 1) cost += 3.2 + 0.1 * split + 1.33 * split * mn;
+    cost += 6.0 + (K % 2 ? 0.7 : 0.0) + 0.53 * mn;
+    if (split > 1) cost += 3.3 + 0.1 * split + 1.36 * split * mn;
     if (split == 1 || cost < best) { best = cost; *split_out = split; }
   }
   return best;
@@ -492,6 +542,18 @@ void launch_mid_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, co
   p.bias = bias; p.aux = (const bf16_t*)aux;
   auto kern = kind == 1 ? gemm_mid_kernel<MID_RELU> : (kind == 2 ? gemm_mid_kernel<MID_MASK> : gemm_mid_kernel<MID_STORE>);
   hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
+}
+
+// out[m][h] = SiLU(sum_d X[m][d] Wg[h][d]) * (sum_d X[m][d] Wu[h][d]), out with pitch H
+double mid_gate_cost(int64_t M, int64_t D, int64_t H) {
+  int split;
+  return mid_xwt_cost(M, D, 2 * H, 0, &split);
+}
+void launch_mid_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s) {
+  MidParams p = mid_params(Wg, D, X, D, H, M, D, out, H, 1, nullptr);
+  p.P2 = (const bf16_t*)Wu;
+  p.tiles_i = (int)((H + kMidTile / 2 - 1) / (kMidTile / 2));
+  hipLaunchKernelGGL(gemm_mid_kernel<MID_GATE>, dim3((unsigned)mid_units(p)), dim3(256), 0, s, p);
 }
 
 void launch_mid_grads(const MidGrads& a, hipStream_t s) {

@@ -261,7 +261,7 @@ Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy, bool may_pad, bool 
 // Measured, us, whole blocks: gate on this kernel / as two generic products: 16 x 4096 x 11008 74 / 478, 16 x 4097 x 11008 147 /
 // 280, 66 x 4097 x 65536 2963 / 2120.
 GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad) {
-  GatePlan best = {Gate::kSeparate, Xwt::kGeneric};
+  GatePlan best = {Gate::kSeparate, Xwt::kGeneric, 0.0, 0.0};
   double down = 0.0;
   best.down = pick_xwt(M, H, D, true, can_pad && H % 128 == 0, /*x_padded=*/true, &down);
   const double mh = (double)M * (double)H;
@@ -280,8 +280,10 @@ GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad) {
     const double copies = (double)(Hp * Dq) * 4.0 + (double)(Hp * fast_pad_dim(D)) * 2.0 +
                           (fast_padded_stages_x(D) ? (double)(M * Dq) * 2.0 : 0.0);
     const double padded = 1.1 * (10.0 + copies / 3e6 + tiled + fast_xwt_cost(M, Hp, D, nullptr));
-    if (padded < cost) { best.gate = Gate::kPadded; best.down = Xwt::kPadded; }
+    if (padded < cost) { best.gate = Gate::kPadded; best.down = Xwt::kPadded; down = fast_xwt_cost(M, Hp, D, nullptr); cost = padded; }
   }
+  best.gate_cost = cost - down;
+  best.down_cost = down;
   return best;
 }
 

@@ -187,7 +187,7 @@ enum class Xwt { kGeneric, kSkinny, kTiled, kPadded };
 Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy = true, bool may_pad = true, bool x_padded = false, double* cost = nullptr);
 // and the gate and up products of the feed-forward block, [M,D] x [H,D]^T twice, then its down product
 enum class Gate { kSeparate, kSkinny, kTiled, kPadded };
-struct GatePlan { Gate gate; Xwt down; };
+struct GatePlan { Gate gate; Xwt down; double gate_cost, down_cost; };
 GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad);
 void launch_skinny_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias,
                        const void* aux, void* out, int64_t ldo, hipStream_t s);
@@ -285,6 +285,9 @@ double mid_grads_cost(int64_t M, int64_t K, int64_t N, size_t room, int* sa, int
 // as launch_fast_xwt (kind 2 leaves columns of out behind N as they are); part: fast_xwt_part_bytes(M, N, split)
 void launch_mid_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, const void* W, const float* bias, const void* aux,
                     void* out, int64_t ldo, int split, void* part, hipStream_t s);
+// gate and up products of the feed-forward block with the gated activation
+double mid_gate_cost(int64_t M, int64_t D, int64_t H);
+void launch_mid_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s);
 // dX and dW in one launch; split reductions leave fp32 sums as launch_fast_pair
 struct MidGrads {
   int64_t M, K, N;

@@ -1,7 +1,7 @@
 """The bf16 products in 128 x 128 tiles (gemm_mid.hip): reductions and widths around the slice of 64, the tile and the last eight
 elements, rows that start at any element, the last row read with and without a pitch behind it, reductions split for either
 gradient, both or neither and for the forward product, long rows (two-kernel row pass), the activation's mask, a padded forward
-product before unpadded gradients, few rows.  Workspaces start as NaNs and have guard bytes, as have the outputs; the same calls in
+product before unpadded gradients, few rows; the gated pair of products of the feed-forward block, widths around its 64 columns.  Workspaces start as NaNs and have guard bytes, as have the outputs; the same calls in
 the smallest workspaces run unsplit.  Bars as in the other parity tests, against the fp64 oracles."""
 import numpy as np
 import pytest
@@ -95,3 +95,17 @@ def test_linear_relu(M, K, N):
     for k in ("dX", "dW", "db"):
         got = H.to_f64(out[k].view)
         assert np.all(np.abs(got - ref[k]) <= 2e-2 * np.abs(ref[k]).max() + add[k]), k
+
+
+@pytest.mark.parametrize("M,D,Hd", [(40, 1026, 1500), (129, 136, 1001), (300, 1042, 1027), (512, 515, 1090), (103, 3197, 581), (1000, 640, 1000)])
+def test_feed_forward_block(M, D, Hd):
+    print(f"[mid] ffn {M}x{D}x{Hd}", flush=True)
+    t = I.generate_ffn("bf16", M, D, Hd, seed=7300 + M + D + Hd)
+    d = {k: v.to("cuda", torch.bfloat16) for k, v in t.items()}
+    Y = H.Guarded((M, D), torch.bfloat16)
+    ws = nans(api.fdl_llama_ffn_workspace_bytes("bf16", M, D, Hd))
+    api.fdl_llama_ffn_forward("bf16", d["X"], d["Wg"], d["Wu"], d["Wd"], Y.view, ws.view)
+    torch.cuda.synchronize()
+    assert Y.intact() and ws.intact()
+    n = {k: v.numpy().astype(np.float64) for k, v in t.items()}
+    H.check("bf16", "Y", H.to_f64(Y.view), S.llama_ffn_forward(n["X"], n["Wg"], n["Wu"], n["Wd"])["Y"])
