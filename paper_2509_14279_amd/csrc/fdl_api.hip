@@ -189,6 +189,10 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
   q.off_colpart = off; off += align256((size_t)q.b1_groups * 3 * N * cs);
   make_grad_plan(dt, M, K, N, room, may_block, &off, &q.g);
   tight_pitch(&q.g);
+  if (q.b1_fused) {      // (the partials' room is that of a row per group)
+    const int64_t slots = b1_fused_slots(dt, N, q.g.ldz), most = (Mp + slots - 1) / slots;
+    if (q.b1_groups > most) q.b1_groups = (int)most;
+  }
   q.bwd_bytes = off;
   // (one buffer for both passes and for fdl_forward_inference, which keeps mean and rstd in it)
   const size_t fwd_all = q.fwd_bytes + 2 * align256((size_t)Mp * 4) + 256;

@@ -141,6 +141,7 @@ void launch_b1b(int dt, int64_t M, int64_t N, int64_t ldz, int rows_per_group, i
 // is too long for it
 bool b1_fused_supported(int dt, int64_t N, int64_t ldz);
 int b1_fused_groups(int dt, int64_t M, int64_t N);   // number of row groups it should be launched with (before capping at M)
+int b1_fused_slots(int dt, int64_t N, int64_t ldz);   // rows that a group has in hand at once
 int b1b_rows_per_group(int dt, int64_t M, int64_t N);
 void launch_zero_cols_bf16(void* dZ, int64_t M, int64_t N, int64_t ldz, hipStream_t s);
 // blocked: dZ is written as [M / 32][N / 32] blocks of 32 x 32 elements (bf16, M and N multiples of 32, ldz = N)

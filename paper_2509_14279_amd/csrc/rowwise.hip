@@ -309,6 +309,21 @@ template <class C, int NW> __device__ __forceinline__ void wg_sum2(C& a, C& b, C
   }
 }
 
+// the same over WPR neighbouring wavefronts, from wavefront `w0` of the workgroup on (WPR = 1: no barrier)
+template <class C, int WPR> __device__ __forceinline__ void row_sum2(C& a, C& b, C (*red)[2], int w0) {
+  a = wave_sum(a);
+  b = wave_sum(b);
+  if constexpr (WPR > 1) {
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) { red[wave][0] = a; red[wave][1] = b; }
+    __syncthreads();
+    a = red[w0][0];
+    b = red[w0][1];
+#pragma unroll
+    for (int w = 1; w < WPR; w++) { a += red[w0 + w][0]; b += red[w0 + w][1]; }
+  }
+}
+
 // nv of V consecutive column sums of a thread to memory, 16 bytes at a time from an element-aligned address (one 4-byte
 // store per column and wavefront touches sixteen lines for 256 bytes: a workgroup's 3 N sums took longer than a row)
 template <class C, int V> __device__ __forceinline__ void store_columns(C* p, const C (&a)[V], int nv) {
@@ -337,6 +352,8 @@ template <> struct RawVec<bf16_t, false> { typedef bf16x8 type; };
 template <> struct RawVec<float, true> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
 template <> struct RawVec<bf16_t, true> { typedef __bf16 type __attribute__((ext_vector_type(8), aligned(2))); };
 template <class T> struct RawVec<T, true, 1> { typedef T type __attribute__((ext_vector_type(1))); };
+template <> struct RawVec<bf16_t, false, 4> { typedef __bf16 type __attribute__((ext_vector_type(4))); };
+template <> struct RawVec<bf16_t, true, 4> { typedef __bf16 type __attribute__((ext_vector_type(4), aligned(2))); };
 template <> struct RawVec<float, false, 8> { typedef float type __attribute__((ext_vector_type(8), aligned(16))); };
 template <> struct RawVec<float, true, 8> { typedef float type __attribute__((ext_vector_type(8), aligned(4))); };
 
@@ -516,8 +533,12 @@ __global__ __launch_bounds__(256) void b1b_kernel(int64_t M, int64_t N, int64_t 
 // parks both rows' vectors in a per-wave LDS area and stores whole lines (lanes 8j .. 8j+3 the even row's piece j,
 // lanes 8j+4 .. 8j+7 the odd row's).  Half-line stores straight from the registers cost the phase a third of its
 // bandwidth (0.55 -> 0.73 ms on 65536 x 8192), halves merged in the L2 still a tenth.
-// V: elements per thread; 1 for narrow rows that start at any element (see b1_fused_impl).
-template <class T, int NT, bool ANY, bool BLK = false, int V = 16 / (int)sizeof(T)>
+// V: elements per thread; fewer than a vector for narrow rows (see b1_fused_impl).
+// WPR: wavefronts per row.  Rows of up to 64 V or 128 V elements leave most of a workgroup's threads without one, so neighbouring
+// wavefronts take rows of their own (S of them at a time) and the group's column sums meet in LDS at the end.  Whole backward
+// passes with K = 8, us, one row per workgroup / so: bf16 58578 x 510 162 / 84, 65536 x 64 119 / 44, 33402 x 448 77 / 49, 20000 x 1000
+// 69 / 65; fp32 65536 x 100 345 / 243, 33402 x 448 199 / 167, 30000 x 900 209 / 209.
+template <class T, int NT, bool ANY, bool BLK = false, int V = 16 / (int)sizeof(T), int WPR = NT / 64>
 __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int64_t ldz, const T* __restrict__ dY,
                                                        const T* __restrict__ Z, const float* __restrict__ gamma,
                                                        const float* __restrict__ mean, const float* __restrict__ rstd,
@@ -525,13 +546,15 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
                                                        typename ComputeOf<T>::type* __restrict__ colpart) {
   typedef typename ComputeOf<T>::type C;
   typedef typename RawVec<T, ANY, V>::type raw_t;
-  constexpr int D = 2;
+  constexpr int D = 2, S = NT / 64 / WPR;
   static_assert(!BLK || (sizeof(T) == 2 && !ANY), "blocked output: bf16, whole vectors");
   __shared__ C red[2][NT / 64][2];
   __shared__ __attribute__((aligned(16))) raw_t park[BLK ? NT / 64 : 1][2][BLK ? 64 : 1];   // [wave][row of the pair][lane]
   ActTable<T, true, NT> tab;
   tab.build();
-  const int64_t col = (int64_t)threadIdx.x * V;
+  const int slot = S == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * WPR));     // which row of the S
+  const int thr = (int)threadIdx.x - slot * 64 * WPR;                                             // place in it
+  const int64_t col = (int64_t)thr * V;
   const int nv = col >= N ? 0 : (N - col > V ? V : (int)(N - col));
   const int64_t left = ldz - col;              // columns of dZ this thread and those behind it write
   C accb[V], accg[V], accz[V];
@@ -547,14 +570,14 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
       if (v < nv) gm[v] = gamma[col + v];
   }
   // D rows are kept in flight, one per buffer; as soon as a buffer has been unpacked its refill with the row D G further
-  // on is issued (G = gridDim.x), ahead of that row's barrier and second phase.  mean and rstd travel with the row, as
+  // on is issued (G = S gridDim.x), ahead of that row's barrier and second phase.  mean and rstd travel with the row, as
   // vector loads (zero is a register the compiler cannot see through): a scalar load at the head of the row's work would
   // be waited for there.
   raw_t bdy[D], bz[D];
   float bmu[D], brs[D];
   int zero = 0;
   asm volatile("" : "+v"(zero));
-  const int64_t G = gridDim.x;
+  const int64_t G = (int64_t)gridDim.x * S;
   auto fetch = [&](int buf, int64_t r) {
     if (r < M) {
       bmu[buf] = mean[r + zero];
@@ -572,13 +595,19 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
   // Row-major dZ: the group walks rows b, b + G, b + 2G, ... .  Blocked dZ: rows 2b, 2b + 1, then 2G further on - the
   // two rows in flight are neighbours, so the two 64-byte halves of every line of dZ leave the same compute unit
   // within one row time and merge in its L2 (M is even where dZ is blocked).
-  const int64_t first = BLK ? 2 * (int64_t)blockIdx.x : (int64_t)blockIdx.x;
+  const int64_t lead = (int64_t)blockIdx.x * S * (BLK ? 2 : 1), first = lead + slot * (BLK ? 2 : 1);    // (lead: of slot 0)
   auto ahead = [&](int buf) -> int64_t { return BLK ? (buf >> 1) * 2 * G + (buf & 1) : buf * G; };
 #pragma unroll
   for (int buf = 0; buf < D; buf++) fetch(buf, first + ahead(buf));
 
   const C inv_n = (C)1 / (C)N;
   auto process = [&](int buf, int64_t row) {
+    const bool live = S == 1 || WPR == 1 || row < M;     // (rows that meet at barriers: past the last row all is zero, unstored)
+    if (S > 1 && WPR > 1 && !live) {
+      bmu[buf] = brs[buf] = 0.0f;
+#pragma unroll
+      for (int v = 0; v < V; v++) { bdy[buf][v] = (T)0.0f; bz[buf][v] = (T)0.0f; }
+    }
     const C rs = (C)brs[buf], nmr = -(C)bmu[buf] * rs;
     C ah[V], gp[V], g[V];
     C s1 = 0, s2 = 0;
@@ -600,7 +629,8 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
       if (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
     }
     fetch(buf, row + D * G);
-    wg_sum2<C, NT / 64>(s1, s2, red[buf & 1]);
+    if constexpr (S == 1) wg_sum2<C, NT / 64>(s1, s2, red[buf & 1]);
+    else row_sum2<C, WPR>(s1, s2, red[buf & 1], slot * WPR);
     const C c1 = s1 * inv_n, c2 = s2 * inv_n;
     raw_t o;
 #pragma unroll
@@ -615,6 +645,7 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
       // (every lane takes part in the stores, also one whose own columns lie past the end of the row: the pieces it
       //  stores belong to other lanes' columns)
       const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+      if (!live) return;
       if (nv > 0) park[wv][buf & 1][ln] = o;
       if (buf & 1) {
         // this wave's 16 pieces per row (piece = 4 lanes = 32 columns = one block): two stores of 8 whole lines
@@ -622,7 +653,7 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
 #pragma unroll
         for (int half = 0; half < 2; half++) {
           const int j = half * 8 + (ln >> 3), i = ln & 7;
-          const int64_t nb = (int64_t)wv * 16 + j;                       // block column of piece j
+          const int64_t nb = (int64_t)(wv - slot * WPR) * 16 + j;                       // block column of piece j
           if (nb * 32 < N) {                                             // N is a multiple of 32: a piece is whole or absent
             const raw_t v = park[wv][i >> 2][4 * j + (i & 3)];
             const int64_t at = (((even >> 5) * (N >> 5) + nb) << 10) + ((even & 31) << 5) + i * 8;
@@ -630,14 +661,35 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
           }
         }
       }
-    } else if (ANY ? left > 0 : nv > 0) {
+    } else if (live && (ANY ? left > 0 : nv > 0)) {
       raw_store<T, ANY, V>(dZ + row * ldz + col, o, nv, left);
     }
   };
-  for (int64_t row = first; row < M; row += D * G) {
+  // (what ends the walk is uniform over the wavefronts that meet at a barrier)
+  const int64_t back = WPR == 1 ? 0 : first - lead;
+  for (int64_t row = first; row - back < M; row += D * G) {
 #pragma unroll
     for (int buf = 0; buf < D; buf++)
-      if (row + ahead(buf) < M) process(buf, row + ahead(buf));     // uniform over the workgroup
+      if (row - back + ahead(buf) < M) process(buf, row + ahead(buf));
+  }
+  if constexpr (S > 1) {
+    // the slots' sums meet in slot 0
+    __shared__ C comb[3 * V][(S - 1) * 64 * WPR];
+    if (slot > 0) {
+      const int at = (int)threadIdx.x - 64 * WPR;
+#pragma unroll
+      for (int v = 0; v < V; v++) { comb[v][at] = accb[v]; comb[V + v][at] = accg[v]; comb[2 * V + v][at] = accz[v]; }
+    }
+    __syncthreads();
+    if (slot > 0) return;
+#pragma unroll
+    for (int w = 0; w < S - 1; w++)
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        accb[v] += comb[v][w * 64 * WPR + thr];
+        accg[v] += comb[V + v][w * 64 * WPR + thr];
+        accz[v] += comb[2 * V + v][w * 64 * WPR + thr];
+      }
   }
   if (nv > 0) {
     store_columns<C, V>(colpart + ((int64_t)blockIdx.x * 3 + 0) * N + col, accb, nv);
@@ -1219,6 +1271,13 @@ inline int fused_threads(int dt, int64_t N, int64_t ldz) {
   return per_row <= 1024 ? 1024 : 0;
 }
 
+// Rows that a workgroup of the fused kernel has in hand at once: narrow rows are a wavefront's (64 vectors) or two's.
+inline int b1_slots(int dt, int64_t N, int64_t ldz) {
+  const int V = dt == kF32 ? 4 : 8;
+  const int64_t per_row = ((ldz > N ? ldz : N) + V - 1) / V;
+  return per_row <= 64 ? 4 : (per_row <= 128 ? 2 : 1);
+}
+
 template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int groups, bool blocked, const void* dY, const void* Z,
                                       const float* gamma, const float* mean, const float* rstd, void* dZ,
                                       void* colpart, hipStream_t s) {
@@ -1245,15 +1304,28 @@ template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int gro
     else if (nt == 512) FDL_B1F(512, ANY, BLK);                                                                           \
     else if constexpr (sizeof(T) == 2) FDL_B1F(1024, ANY, BLK);                                                           \
   } while (0)
+  // narrow rows: a wavefront or two per row, an element, four or a vector per thread (b1_slots says how many rows a group takes)
+#define FDL_B1N(ANY, BLK, VV, WPR) hipLaunchKernelGGL((b1_fused_kernel<T, 256, ANY, BLK, VV, WPR>), grid, dim3(256), 0, FDL_B1_ARGS)
+  const int slots = b1_slots(sizeof(T) == 4 ? kF32 : kBF16, N, ldz);
   if constexpr (sizeof(T) == 2) {
-    if (blocked) { FDL_B1F_NT(false, true); return; }
+    if (blocked) {
+      if (slots == 4) FDL_B1N(false, true, V, 1); else if (slots == 2) FDL_B1N(false, true, V, 2); else FDL_B1F_NT(false, true);
+      return;
+    }
+    if (slots == 4 && ldz <= 256 && ldz > 64) {
+      if (N % 4 != 0 || ldz != N) FDL_B1N(true, false, 4, 1); else FDL_B1N(false, false, 4, 1);
+      return;
+    }
   }
-  if (any && ldz <= 256) {
-    // narrow: an element per thread.  (A thread with eight holds the whole of a row of seven, one load after the other:
-    // 13288 x 7 bf16 42 us, so 17)
-    hipLaunchKernelGGL((b1_fused_kernel<T, 256, true, false, 1>), grid, dim3(256), 0, FDL_B1_ARGS);
+  if (slots == 4) {
+    if (ldz <= 64) FDL_B1N(true, false, 1, 1); else if (any) FDL_B1N(true, false, V, 1); else FDL_B1N(false, false, V, 1);
     return;
   }
+  if (slots == 2) {
+    if (any) FDL_B1N(true, false, V, 2); else FDL_B1N(false, false, V, 2);
+    return;
+  }
+#undef FDL_B1N
   if (any) FDL_B1F_NT(true, false);
   else FDL_B1F_NT(false, false);
 #undef FDL_B1F_NT
@@ -1492,6 +1564,7 @@ bool b1_fused_supported(int dt, int64_t N, int64_t ldz) { return fused_threads(d
 // 256 / 512 / 1024 groups: bf16 3001 x 1537: 26.2 / 23.3 / 28.1; 32768 x 1024: 103 / 72.8 / 65.4; 16384 x 4096: 85.3 / 82.0
 // / 88.9; 65536 x 8192: 578 / 569 / 578; 1000 x 5000: 22.3 / 28.5; fp32, whose fp64 arithmetic fills the vector units
 // with one workgroup of 512 threads per compute unit: 3001 x 1537 46.5 / 50.6, 8192 x 4096 191 / 200.
+int b1_fused_slots(int dt, int64_t N, int64_t ldz) { return b1_slots(dt, N, ldz); }
 int b1_fused_groups(int dt, int64_t M, int64_t N) {
   const int nt = fused_threads(dt, N, N);
   if (dt == kF32 && nt > 256) return 256;

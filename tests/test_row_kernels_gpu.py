@@ -50,6 +50,11 @@ def test_stand_alone_norms(dtype, N, M):
                                        # the backward pass (to 256, where they are ragged or padded)
                                        ("bf16", 2600, 15), ("bf16", 33000, 17), ("bf16", 1037, 33), ("bf16", 37, 127),
                                        ("bf16", 300, 128), ("bf16", 70, 129), ("bf16", 515, 255), ("f32", 2600, 17),
+                                       # several rows per workgroup in the backward pass: a wavefront each, two each, at
+                                       # their edges; row counts that leave wavefronts without a row
+                                       ("bf16", 1, 64), ("bf16", 3, 65), ("bf16", 5, 256), ("bf16", 1037, 257), ("bf16", 1039, 512),
+                                       ("bf16", 5, 513), ("bf16", 1037, 1016), ("bf16", 3, 1024), ("f32", 3, 256),
+                                       ("f32", 1037, 257), ("f32", 1039, 512), ("f32", 5, 511), ("f32", 1, 63),
                                        ("f32", 33000, 7), ("f32", 500, 64), ("f32", 70, 65), ("f32", 41, 255),
                                        ("f32", 1, 18433), ("f32", 600, 16385), ("f32", 1300, 18432), ("f32", 37, 20001)])
 def test_forward_and_backward_of_the_block(dtype, M, N):
@@ -101,3 +106,15 @@ def test_statistics_of_nearly_constant_rows(M, K, N):
     mean, rstd = A.mean(axis=1), (A.var(axis=1) + cfg.eps) ** -0.5
     assert np.abs(H.to_f64(got["mean"]) / mean - 1).max() <= 2.0 ** -24 * 1.001
     assert np.abs(H.to_f64(got["rstd"]) / rstd - 1).max() <= 5 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("M,K,N", [(2560, 2560, 512), (5120, 1024, 1024)])
+def test_blocked_gradients_of_narrow_rows(M, K, N):
+    # dZ in 32 x 32 blocks, written by a wavefront or two per row
+    cfg = I.custom("bf16", M, K, N, seed=8200 + N)
+    t = I.generate(cfg)
+    got = H.run_fdl(cfg, t)
+    n = {k: v.numpy().astype(np.float64) for k, v in t.items()}
+    ref = O.forward_backward(n["X"], n["W"], n["b"], n["gamma"], n["beta"], n["dY"], cfg.eps)
+    for k in H.OUTPUTS + ("Z", "mean"):
+        H.check("bf16", k, H.to_f64(got[k]), ref[k])
