@@ -1354,7 +1354,9 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // Rows of 8192 and 16384 take 16 vectors per lane.  The others, whose masks cost registers (one wavefront per SIMD with
   // 16 vectors), take at most 8 and more wavefronts per row: 10000 x 5000 70.7 -> 50.1 us, 8192 x 10496 101.6 -> 71.6,
   // 3001 x 12345 64.9 -> 48.6.
-  int ch = 2, wpr = 1;
+  // Rows of up to 512 columns are one vector per lane (as half of two, us: LayerNorm 65536 x 100 28.8 -> 21.0, 25535 x 337 16.4 -> 12.5,
+  // 58578 x 510 31.7 -> 25.0; forward pass of 65536 x 64 x 256 44 -> 36.5), 512 itself with the plain loads of shorter rows.
+  int ch = 1, wpr = 1;
   while (ch < 8 && ch * 512 < N) ch *= 2;
   while (ch * wpr * 512 < N) wpr *= 2;
   if (N == 8192 || N == 16384) { ch = 16; wpr /= 2; }
@@ -1365,18 +1367,19 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // 2048 x 4097 and beyond are faster the other way.
   const int spread = ch * wpr / 2;
   if (N % 8 != 0 && spread >= 2 && spread <= 8 && M * spread <= (int64_t)di.cus * 32) { ch = 2; wpr = spread; }
-  const int fit = N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
+  const int fit = ch > 1 && N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
   const int nt = 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
   const int64_t per_wg = nt / 64 / wpr;
   int64_t wgs = (M + per_wg - 1) / per_wg;
-  const int64_t cap = (int64_t)di.cus * (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (16 / ch > wpr ? 16 / ch / wpr : 1));
+  const int64_t cap = (int64_t)di.cus * (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (ch == 1 ? 8 : (16 / ch > wpr ? 16 / ch / wpr : 1)));
   if (wgs > cap) wgs = cap;
 #define FDL_F2R(CHH, FIT, WPR)                                                                                        \
   launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
 #define FDL_F2R_FIT(FIT)                                                                                              \
   do {                                                                                                                \
-    if (ch == 2) FDL_F2R(2, FIT, 1); else if (ch == 4) FDL_F2R(4, FIT, 1); else if (wpr == 1) FDL_F2R(8, FIT, 1);     \
+    if (ch == 1) FDL_F2R(1, FIT, 1); else if (ch == 2) FDL_F2R(2, FIT, 1); else if (ch == 4) FDL_F2R(4, FIT, 1);        \
+    else if (wpr == 1) FDL_F2R(8, FIT, 1);                                                                             \
     else if (wpr == 2) FDL_F2R(8, FIT, 2); else if (wpr == 4) FDL_F2R(8, FIT, 4); else FDL_F2R(8, FIT, 8);            \
   } while (0)
   if (fit == FIT_FULL) {

@@ -12,7 +12,7 @@ import harness as H
 
 pytestmark = pytest.mark.gpu
 
-BF16_WIDTHS = [7, 511, 1025, 1727, 2049, 4095, 4097, 8191, 8193, 8208, 16383, 16384, 16391, 32760, 32768, 32771]
+BF16_WIDTHS = [7, 129, 136, 504, 511, 512, 513, 1025, 1727, 2049, 4095, 4097, 8191, 8193, 8208, 16383, 16384, 16391, 32760, 32768, 32771]
 F32_WIDTHS = [3, 257, 1023, 1026, 4097, 8192, 16383, 16388]
 WIDTHS = [("bf16", n) for n in BF16_WIDTHS] + [("f32", n) for n in F32_WIDTHS]
 
@@ -49,7 +49,7 @@ def test_stand_alone_norms(dtype, N, M):
                                        # narrow rows: sixteen lanes each (to 128 and 64 columns), an element per thread in
                                        # the backward pass (to 256, where they are ragged or padded)
                                        ("bf16", 2600, 15), ("bf16", 33000, 17), ("bf16", 1037, 33), ("bf16", 37, 127),
-                                       ("bf16", 300, 128), ("bf16", 70, 129), ("bf16", 515, 255), ("f32", 2600, 17),
+                                       ("bf16", 300, 128), ("bf16", 70, 129), ("bf16", 70, 505), ("bf16", 33000, 504), ("bf16", 37, 511), ("bf16", 515, 255), ("f32", 2600, 17),
                                        # several rows per workgroup in the backward pass: a wavefront each, two each, at
                                        # their edges; row counts that leave wavefronts without a row
                                        ("bf16", 1, 64), ("bf16", 3, 65), ("bf16", 5, 256), ("bf16", 1037, 257), ("bf16", 1039, 512),
