@@ -349,13 +349,13 @@ __device__ __forceinline__ float inv_sqrt(double v) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Column sums from per-group partial sums, colpart [groups][nwhich][N]: 64 consecutive columns per workgroup of 1024
-// threads (coalesced), the groups dealt over the 16 wavefronts, eight loads in flight per thread (the phase is pure
-// latency: a few tens of MB), fp64 sums in a fixed order.
-template <class C>
+// Column sums from per-group partial sums, colpart [groups][nwhich][N]: 64 consecutive columns per workgroup (coalesced), the
+// groups dealt over its SL wavefronts, loads in flight per thread by the eight (the phase is pure latency: a few tens of MB), fp64
+// sums in a fixed order.
+template <class C, int SL = 16>
 __device__ __forceinline__ void b2_columns(int64_t N, int groups, int nwhich, const C* __restrict__ colpart, int cblock,
                                            int which, float* __restrict__ out, double (*red)[64]) {
-  constexpr int kSlices = 16;
+  constexpr int kLoads = SL >= 16 ? 8 : 16;
   const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
   const int64_t col = (int64_t)cblock * 64 + lane;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
@@ -363,21 +363,22 @@ __device__ __forceinline__ void b2_columns(int64_t N, int groups, int nwhich, co
     const C* src = colpart + (int64_t)which * N + col;
     const int64_t gstride = (int64_t)nwhich * N;
     int g = slice;
-    for (; g + 7 * kSlices < groups; g += 8 * kSlices) {
-      C v[8];
+    for (; g + (kLoads - 1) * SL < groups; g += kLoads * SL) {
+      C v[kLoads];
 #pragma unroll
-      for (int e = 0; e < 8; e++) v[e] = src[(int64_t)(g + e * kSlices) * gstride];
+      for (int e = 0; e < kLoads; e++) v[e] = src[(int64_t)(g + e * SL) * gstride];
 #pragma unroll
-      for (int e = 0; e < 8; e++) a[e & 3] += (double)v[e];
+      for (int e = 0; e < kLoads; e++) a[e & 3] += (double)v[e];
     }
-    for (; g < groups; g += kSlices) a[0] += (double)src[(int64_t)g * gstride];
+#pragma unroll 4
+    for (; g < groups; g += SL) a[0] += (double)src[(int64_t)g * gstride];
   }
   red[slice][lane] = (a[0] + a[1]) + (a[2] + a[3]);
   __syncthreads();
   if (slice == 0 && col < N) {
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < kSlices; w++) t += red[w][lane];
+    for (int w = 0; w < SL; w++) t += red[w][lane];
     out[col] = (float)t;
   }
 }

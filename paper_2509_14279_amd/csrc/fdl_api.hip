@@ -513,6 +513,7 @@ static void launch_grad_dx(const GradPlan& p, const void* dZ, const void* W, con
     a.M = M; a.K = K; a.N = N; a.sa = p.split_a; a.sb = p.split_b;
     a.dZ = dZ; a.ldz = p.ldz; a.W = W; a.X = X;
     a.dX = dX; a.dxpart = ws + p.off_dxpart; a.dW = dW; a.dwpart = ws + p.off_dwpart;
+    a.cols = *tj;
     launch_mid_grads(a, s);
     if (p.split_a > 1) sum_later(tj, 0, a.dxpart, p.split_a, M * K, dX);
     if (p.split_b > 1) sum_later(tj, 1, a.dwpart, p.split_b, N * K, dW);
@@ -604,7 +605,7 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
     }
   }
   // Where the contractions below leave split reductions behind (bf16 tuned path), their sums and the column sums
-  // share one launch at the end of the pass; otherwise the column sums are finished here.
+  // share one launch at the end of the pass; otherwise the column sums are finished here, or with both gradients in 128 x 128 tiles.
   const bool tail = grad_leaves_sums(p.g);
   TailSums tj = {};
   tj.colpart = static_cast<const float*>(colpart); tj.groups = p.b1_groups; tj.N = N; tj.kinds = 3;
@@ -618,7 +619,7 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
   }
   {
     PhaseTimer t(FDL_PHASE_B2, s);
-    if (!tail) launch_b2(N, p.b1_groups, colpart, dbeta, dgamma, db, s);
+    if (!tail && !p.g.mid) launch_b2(N, p.b1_groups, colpart, dbeta, dgamma, db, s);
   }
   {
     PhaseTimer t(FDL_PHASE_B3, s);
@@ -844,7 +845,7 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
     launch_f64_grads_finish(a, tj, s);
     return launch_status();
   }
-  if (!tail) launch_colsum_finish(M, N, colpart, db, s);
+  if (!tail && !q.g.mid) launch_colsum_finish(M, N, colpart, db, s);
   launch_grad_dx(q.g, G, W, X, dX, dW, ws, &tj, s);
   launch_grad_dw(q.g, G, X, dW, ws, &tj, s);
   if (tail) launch_finish(tj, s);

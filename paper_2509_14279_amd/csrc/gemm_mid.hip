@@ -434,12 +434,20 @@ void gemm_mid_kernel(MidParams p) {
   mid_unit<false, false, EPI>(p, (int)blockIdx.x, smem);
 }
 
-// dX and dW side by side; the product with the longer units, whose last ones nothing follows to fill the chip, comes first
+// dX and dW side by side; the product with the longer units, whose last ones nothing follows to fill the chip, comes first.  Behind
+// them, where no sums of split reductions need a launch of their own after this one, the column sums of the row pass
+// (j.kinds ceil(N / 64) workgroups, as b2_kernel: a launch of 4 us for whatever it does).
 template <int EPIA, int EPIB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void gemm_mid_pair_kernel(MidParams dx, MidParams dw, int first_units, int dw_first) {
+void gemm_mid_pair_kernel(MidParams dx, MidParams dw, int first_units, int units, int dw_first, TailSums j) {
   __shared__ __attribute__((aligned(1024))) char smem[kMidLds];
   const int id = (int)blockIdx.x;
+  if (EPIA == MID_STORE && EPIB == MID_STORE && id >= units) {
+    const int cblocks = (int)((j.N + 63) / 64), which = (id - units) / cblocks;
+    b2_columns<float, 4>(j.N, j.groups, j.kinds, j.colpart, (id - units) % cblocks, which,
+                         which == 0 ? j.col_out[0] : (which == 1 ? j.col_out[1] : j.col_out[2]), reinterpret_cast<double (*)[64]>(smem));
+    return;
+  }
   const bool first = id < first_units;
   const int unit = first ? id : id - first_units;
   if (first == (dw_first != 0)) mid_unit<true, true, EPIB>(dw, unit, smem);
@@ -521,7 +529,7 @@ double mid_grads_cost(int64_t M, int64_t K, int64_t N, size_t room, int* sa_out,
         work += (A < B ? A : B) * rate * 1.1 * (units > 512.0 ? 1.0 : (units - 256.0) / 256.0);     // the last ones
         one *= 1.14;
       }
-      double cost = 7.5 + (work > one ? work : one);
+      double cost = (sa > 1 || sb > 1 ? 7.5 : 4.0) + (work > one ? work : one);     // (unsplit: no launch for sums follows)
       if (sa > 1) cost += sa * (mk + 0.11);
       if (sb > 1) cost += sb * (nk + 0.11);
       if ((sa == 1 && sb == 1) || cost < best) { best = cost; *sa_out = sa; *sb_out = sb; }
@@ -563,7 +571,8 @@ void launch_mid_grads(const MidGrads& a, hipStream_t s) {
   auto kern = a.sa > 1 ? (a.sb > 1 ? gemm_mid_pair_kernel<MID_PARTIAL, MID_PARTIAL> : gemm_mid_pair_kernel<MID_PARTIAL, MID_STORE>)
                        : (a.sb > 1 ? gemm_mid_pair_kernel<MID_STORE, MID_PARTIAL> : gemm_mid_pair_kernel<MID_STORE, MID_STORE>);
   const bool dw_first = dw.rlen >= dx.rlen;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(nw + nx)), dim3(256), 0, s, dx, dw, dw_first ? nw : nx, dw_first ? 1 : 0);
+  const int cols = a.sa == 1 && a.sb == 1 ? a.cols.kinds * (int)((a.cols.N + 63) / 64) : 0;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(nw + nx + cols)), dim3(256), 0, s, dx, dw, dw_first ? nw : nx, nw + nx, dw_first ? 1 : 0, a.cols);
 }
 
 }  // namespace fdl

@@ -289,13 +289,14 @@ void launch_mid_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, co
 // gate and up products of the feed-forward block with the gated activation
 double mid_gate_cost(int64_t M, int64_t D, int64_t H);
 void launch_mid_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* out, hipStream_t s);
-// dX and dW in one launch; split reductions leave fp32 sums as launch_fast_pair
+// dX and dW in one launch; split reductions leave fp32 sums as launch_fast_pair, unsplit ones finish the column sums `cols` too
 struct MidGrads {
   int64_t M, K, N;
   int sa, sb;
   const void* dZ; int64_t ldz;
   const void* W; const void* X;
   void* dX; void* dxpart; void* dW; void* dwpart;
+  TailSums cols;
 };
 void launch_mid_grads(const MidGrads& a, hipStream_t s);
 
