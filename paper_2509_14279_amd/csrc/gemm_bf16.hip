@@ -541,8 +541,36 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     for (int c = 0; c < 4; c++) roff[c] = (uint32_t)((c * 4 + e_rq) * 256 + ((e_m ^ (c * 4 + e_rq)) << 4));
     const uint32_t svoff = (uint32_t)(e_rq * (int)p.ldc + e_m * 8) * 2u;   // byte offset of the lane inside 4 output rows
     typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
+    // EPI_MASK: the upstream gradient of a block row, fetched while the one before it leaves.  (Fetched where it is used, a tile
+    // made many trips to memory in a row.  Linear+ReLU backward, us, that / so: 10000 x 1000 x 3000 248 / 217, 20000 x 512 x 2048
+    // 224 / 184, 16384 x 1000 x 3001 385 / 324, 65536 x 2048 x 8192 5388 / 5020.)  Rows past the end are the last
+    // one again; a lane whose eight columns pass the end takes the last eight, moved to their place, with zeros behind.
+    u32x4 aux[2][8];
+    auto fetch_aux = [&](int b) {
+      if (EPI != EPI_MASK) return;
+      const int left = CRAG ? p.I - (i0 + wi * 128 + e_m * 8) : 8, early = left >= 8 ? 0 : 8 - left;
+#pragma unroll
+      for (int it = 0; it < 8; it++) {
+        int row = j0 + wj * 128 + b * 32 + it * 4 + e_rq;
+        if (RAG) row = row < p.J ? row : p.J - 1;
+        const bf16_t* ap = p.aux + (int64_t)row * p.I + (i0 + wi * 128 + e_m * 8 - early);
+        if (CRAG) aux[b & 1][it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(ap));
+        else aux[b & 1][it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ap));
+      }
+    };
+    auto place_aux = [&](int b) {
+      if (EPI != EPI_MASK || !CRAG) return;
+      const int left = p.I - (i0 + wi * 128 + e_m * 8);
+      if (left >= 8) return;
+#pragma unroll
+      for (int it = 0; it < 8; it++) {
+        const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, aux[b & 1][it]);
+        aux[b & 1][it] = __builtin_bit_cast(u32x4, left <= 0 ? (unsigned __int128)0 : x >> (16 * (8 - left)));
+      }
+    };
     // Block row b of the wave tile (32 output rows) leaves as soon as it is complete.
     auto flush_rows = [&](int b) {
+      place_aux(b);
       // wave-uniform base of row it*4 of the block row; the lane adds (lane/16) rows and 16 (lane%16) bytes
       char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 32) * p.ldc + i0 + wi * 128);
 #pragma unroll
@@ -572,17 +600,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         if (EPI == EPI_MASK) {
           // v: 8 pre-activations as bf16.  The upstream gradient passes where the pre-activation is positive (bits
           // 0x0001 .. 0x7f80: sign clear, magnitude non-zero, up to infinity) and is zero elsewhere, NaN included.
-          const bf16_t* ap = p.aux + (int64_t)(j0 + wj * 128 + b * 32 + it * 4 + e_rq) * p.I + i0 + wi * 128 + e_m * 8;
-          u32x4 d = {0u, 0u, 0u, 0u};
-          if (!CRAG) {
-            d = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ap));
-          } else if (cleft >= 8) {
-            d = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(ap));
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; e++)
-              if (e < cleft) d[e >> 1] |= (uint32_t)reinterpret_cast<const unsigned short*>(ap)[e] << ((e & 1) * 16);
-          }
+          const u32x4 d = aux[b & 1][it];
           u32x4 g;
 #pragma unroll
           for (int e = 0; e < 4; e++) {
@@ -675,8 +693,12 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     } else {
       // rounded to bf16 and stored (forward: the bias is in the accumulators since their start; the row statistics
       // are taken by the normalisation kernel)
+      fetch_aux(0);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 4; b++) {
+        if (b < 3) fetch_aux(b + 1);
+        if (EPI == EPI_MASK) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int a = 0; a < 4; a++)
 #pragma unroll
