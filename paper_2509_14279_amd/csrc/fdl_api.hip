@@ -368,6 +368,9 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
                                    const float* beta, float eps, void* Y, void* Zsave, float* mean, float* rstd,
                                    char* ws, hipStream_t s) {
   const int64_t M = p.M, K = p.K, N = p.N;
+  // fp32, few tiles, all split: the row kernel adds the parts up
+  const bool sums = p.dt == kF32 && p.f1_s64.split > 1 && p.f1_s64.whole == 0 && f2_takes_sums(N);
+  F64Sums parts = {};
   {
     PhaseTimer t(FDL_PHASE_F1, s);
     if (p.f1_mid) {
@@ -388,7 +391,8 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
                       ws + p.off_part);
     } else {
       GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
-      if (p.dt == kF32) launch_f64(0, g, p.f1_s64, b, nullptr, Zsave, ws + p.off_part, s);
+      if (sums) parts = launch_f64_parts(g, p.f1_s64, b, Zsave, ws + p.off_part, s);
+      else if (p.dt == kF32) launch_f64(0, g, p.f1_s64, b, nullptr, Zsave, ws + p.off_part, s);
       else launch_generic_xwt(0, g, b, nullptr, Zsave, N, s);
     }
   }
@@ -397,7 +401,8 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
   }
   {
     PhaseTimer t(FDL_PHASE_F2, s);
-    launch_f2(p.dt, M, N, eps, Zsave, gamma, beta, Y, mean, rstd, ws + p.off_rows, s);
+    if (sums) launch_f2_sums(M, N, eps, parts, gamma, beta, Y, mean, rstd, s);
+    else launch_f2(p.dt, M, N, eps, Zsave, gamma, beta, Y, mean, rstd, ws + p.off_rows, s);
   }
   return launch_status();
 }

@@ -349,6 +349,12 @@ void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bia
   else dispatch_f64<F64_STORE>(g, p, q.split, s);
 }
 
+F64Sums launch_f64_parts(const GemmDesc& g, const F64Split& q, const float* bias, void* Z, void* part, hipStream_t s) {
+  const F64Params p = f64_params(g, q, bias, nullptr, Z, part);
+  dispatch_f64_main<F64_STORE>(g, p, q.split, s);
+  return F64Sums{(const double*)part, bias, (float*)Z, (int64_t)p.parted * 4096, q.split, p.tiles_j};
+}
+
 // dX (rows of dZ times W) and dW (columns of dZ times X); launch_f64_grads_finish ends both, and the column sums
 void launch_f64_grads(const F64Grads& a, hipStream_t s) {
   const F64Params dx = f64_params(a.dx, a.qx, nullptr, nullptr, a.dX, a.partx), dw = f64_params(a.dw, a.qw, nullptr, nullptr, a.dW, a.partw);

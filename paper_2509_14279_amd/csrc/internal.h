@@ -126,11 +126,18 @@ size_t f64_part_bytes(const F64Split& q);
 void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
                 hipStream_t s);
 
+// the parts of a product whose tiles are all split (q.whole = 0), left for launch_f2_sums: Z [I][J] = their sums + bias
+struct F64Sums { const double* part; const float* bias; float* Z; int64_t stride; int split, tiles_j; };
+F64Sums launch_f64_parts(const GemmDesc& g, const F64Split& q, const float* bias, void* Z, void* part, hipStream_t s);
+
 // ---- row-wise / column-wise phases ------------------------------------------------------------
 // row statistics of GELU(Zsave) and the normalised output (Zsave and Y may be the same buffer); part: f2_part_bytes of scratch
 size_t f2_part_bytes(int dt, int64_t M, int64_t N);
 void launch_f2(int dt, int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
                float* mean, float* rstd, void* part, hipStream_t s);
+bool f2_takes_sums(int64_t N);
+void launch_f2_sums(int64_t M, int64_t N, float eps, const F64Sums& q, const float* gamma, const float* beta, void* Y, float* mean,
+                    float* rstd, hipStream_t s);
 void launch_b1a(int dt, int64_t M, int64_t N, const void* dY, const void* Zsave, const float* gamma,
                 const float* mean, const float* rstd, void* c12, hipStream_t s);
 // ldz: pitch of dZ in elements (N, or N rounded up to the tile in the padded mode of the fast contractions)

@@ -768,10 +768,13 @@ __global__ __launch_bounds__(1024) void finish_kernel(TailSums j) {
 // addresses (the hardware splits what straddles a line), the last, partial one of a row element by element.
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int NT, int S, int ACT>
+// PARTS: Z is not there yet - its tiles' parts (gemm_f64.hip, all of them split) are added here in order, with the bias, rounded
+// and written, to the same bits as by the launch that would do it in between (whole forward passes, us, with that / so: 256^3 14.6 /
+// 12.0, 33 x 1000 x 70 16.5 / 12.2, 128 x 4096 x 1024 34.0 / 30.4, 512^3 19.9 / 17.7, 1000 x 700 x 1000 39.2 / 38.9).
+template <int NT, int S, int ACT, bool PARTS = false>
 __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float eps, const float* Z,
                                                     const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                    float* Y, float* __restrict__ mean, float* __restrict__ rstd) {
+                                                    float* Y, float* __restrict__ mean, float* __restrict__ rstd, F64Sums q) {
   typedef ActTable<float, false, NT> Act;
   constexpr int V = 4, NW = NT / 64;
   constexpr bool kKeep = NT < 1024;      // gamma and beta stay in registers (1024 threads have 128 each: read per row)
@@ -802,6 +805,30 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
   }
   f32x4_u raw[S];
   auto fetch = [&](int64_t row) {
+    if constexpr (PARTS) {
+      if (row >= M) return;
+#pragma unroll
+      for (int s = 0; s < S; s++) {
+        // (four columns from a multiple of four on lie in one tile)
+        const double* p = q.part + ((row >> 6) * q.tiles_j + (col[s] >> 6)) * 4096 + (row & 63) * 64 + (col[s] & 63);
+        f64x4 z = {0.0, 0.0, 0.0, 0.0};
+        if (nv[s] > 0) {
+          z = *reinterpret_cast<const f64x4*>(p);
+#pragma unroll 4
+          for (int k = 1; k < q.split; k++) {
+            const f64x4 x = *reinterpret_cast<const f64x4*>(p + (int64_t)k * q.stride);
+#pragma unroll
+            for (int v = 0; v < V; v++) z[v] += x[v];
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+          raw[s][v] = v < nv[s] ? (float)(z[v] + (double)q.bias[col[s] + v]) : 0.0f;
+          if (v < nv[s]) q.Z[row * N + col[s] + v] = raw[s][v];
+        }
+      }
+      return;
+    }
     const float* z = Z + (row < M ? row : M - 1) * N;  // past the last row: a harmless re-read of it
 #pragma unroll
     for (int s = 0; s < S; s++) {
@@ -1430,7 +1457,7 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
   do {                                                                                                              \
     const int64_t cap = (int64_t)256 * (2048 / NT);   /* a full part's wavefronts; any number is correct */         \
     hipLaunchKernelGGL((row_wg_kernel<NT, S, ACT>), dim3((unsigned)(M < cap ? M : cap)), dim3(NT), 0, s, M, N, eps, \
-                       (const T*)A, gamma, beta, (T*)Y, mean, rstd);                                                \
+                       (const T*)A, gamma, beta, (T*)Y, mean, rstd, F64Sums{});                                     \
     return;                                                                                                         \
   } while (0)
     // (stand-alone norms: three small trips through the caches beat workgroups that do not all fit, where there are more rows
@@ -1469,6 +1496,22 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
   else hipLaunchKernelGGL((row_stream_kernel<T, 1, ACT>), dim3(blocks), dim3(256), 0, s, M, N, eps, (const T*)A, gamma, beta, (T*)Y, mean, rstd);
 }
 
+// fp32 storage, rows of 65 to 2048 columns: the same from the parts of Z's tiles
+bool f2_takes_sums(int64_t N) { return N > 64 && N <= 2048; }
+void launch_f2_sums(int64_t M, int64_t N, float eps, const F64Sums& q, const float* gamma, const float* beta, void* Y, float* mean,
+                    float* rstd, hipStream_t s) {
+#define FDL_SUMS(NT, S)                                                                                                       \
+  do {                                                                                                                        \
+    const int64_t cap = (int64_t)256 * (2048 / NT);                                                                           \
+    hipLaunchKernelGGL((row_wg_kernel<NT, S, ACT_GELU, true>), dim3((unsigned)(M < cap ? M : cap)), dim3(NT), 0, s, M, N,     \
+                       eps, (const float*)q.Z, gamma, beta, (float*)Y, mean, rstd, q);                                        \
+    return;                                                                                                                   \
+  } while (0)
+  if (N <= 256) FDL_SUMS(64, 1);
+  if (N <= 1024) FDL_SUMS(256, 1);
+  FDL_SUMS(256, 2);
+#undef FDL_SUMS
+}
 void launch_f2(int dt, int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
                float* mean, float* rstd, void* part, hipStream_t s) {
   if (dt == kF32) launch_row_norm<float, ACT_GELU>(M, N, eps, Zsave, gamma, beta, Y, mean, rstd, part, s);

@@ -57,3 +57,33 @@ def test_feed_forward_block(M, D, Hd):
     assert Y.intact() and ws.intact()
     n = {k: v.numpy().astype(np.float64) for k, v in t.items()}
     H.check("f32", "Y", H.to_f64(Y.view), S.llama_ffn_forward(n["X"], n["Wg"], n["Wu"], n["Wd"])["Y"])
+
+
+# all tiles of the forward product split, their parts added by the row kernel: one, two vectors per lane, a wavefront or a
+# workgroup per row, rows that end inside a vector or a tile, one row, a partial last row tile
+@pytest.mark.parametrize("M,K,N", [(1, 300, 65), (64, 256, 256), (129, 700, 257), (65, 515, 1023), (300, 300, 1027), (33, 2050, 2047),
+                                   (500, 300, 130)])
+def test_forward_passes(M, K, N):
+    from oracle import fdl_oracle as O
+    cfg = I.custom("f32", M, K, N, seed=9800 + M + K + N)
+    t = I.generate(cfg, with_dY=False)
+    d = {k: t[k].to("cuda") for k in ("X", "W", "b", "gamma", "beta")}
+    f = torch.float32
+    out = {"Y": H.Guarded((M, N), f), "Z": H.Guarded((M, N), f), "I": H.Guarded((M, N), f), "mean": H.Guarded((M,), f), "rstd": H.Guarded((M,), f)}
+    v = {k: g.view for k, g in out.items()}
+    ws = H.Guarded((max(256, api.fdl_workspace_bytes("f32", M, K, N)),), torch.uint8)
+    ws.view.fill_(0xff)
+    api.fdl_forward("f32", d["X"], d["W"], d["b"], d["gamma"], d["beta"], cfg.eps, v["Y"], v["Z"], v["mean"], v["rstd"], ws.view)
+    ws.view.fill_(0xff)
+    api.fdl_forward_inference("f32", d["X"], d["W"], d["b"], d["gamma"], d["beta"], cfg.eps, v["I"], ws.view)
+    torch.cuda.synchronize()
+    for k, g in list(out.items()) + [("workspace", ws)]:
+        assert g.intact(), f"kernel wrote outside the {k} buffer"
+    assert torch.equal(v["I"], v["Y"])
+    n = {k: x.numpy().astype(np.float64) for k, x in t.items()}
+    Z = n["X"] @ n["W"].T + n["b"]
+    # fp64 sums, rounded once
+    assert np.all(np.abs(H.to_f64(v["Z"]) - Z) <= 2.0 ** -24 * np.abs(Z) + 1e-12 * (np.abs(n["X"]) @ np.abs(n["W"]).T + np.abs(n["b"])))
+    ref = O.forward(n["X"], n["W"], n["b"], n["gamma"], n["beta"], cfg.eps)
+    for k in ("Y", "mean"):
+        H.check("f32", k, H.to_f64(v[k]), ref[k])
