@@ -72,12 +72,12 @@ FDL_API const char* fdl_status_string(fdl_status s);
  * problem (the larger of the two, so one buffer serves both).  Returns 0 for
  * an invalid dtype or shape.  Host-only: touches no device.
  * Part of it may be room for the partial sums of split reductions (at most
- * 64 MB for the forward product and for each fp32 gradient), which some shapes
- * want and larger batches do not: the size can fall as M grows.  A buffer that
- * lacks only this part, say one sized for a larger batch, is accepted, and the
- * call runs without splitting (slower, results equal to within the order of
- * the sums); the forward passes of the block also run without the copies of
- * operands that some shapes want.  A smaller one is rejected with
+ * 64 MB for the forward product, for each fp32 gradient and for both bf16
+ * ones), which some shapes want and larger batches do not: the size can fall
+ * as M grows.  A buffer that lacks only this part, say one sized for a larger
+ * batch, is accepted, and the call runs without splitting (slower, results
+ * equal to within the order of the sums); forward products also run without
+ * the copies of operands that some shapes want.  A smaller one is rejected with
  * FDL_ERR_WORKSPACE.  The same holds for the sizes of the other entry points.
  */
 FDL_API size_t fdl_workspace_bytes(fdl_dtype dt, int64_t M, int64_t K, int64_t N);

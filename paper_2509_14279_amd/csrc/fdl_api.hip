@@ -288,8 +288,8 @@ extern "C" size_t fdl_workspace_bytes(fdl_dtype dt, int64_t M, int64_t K, int64_
   return p.bytes;
 }
 
-// A workspace that lacks only the room for split reductions serves the call all the same, without them, and the block's forward
-// pass does without the operands' copies: needs fall with M where few rows make a reduction split or a larger batch runs on a
+// A workspace that lacks only the room for split reductions serves the call all the same, without them, and the forward
+// products do without the operands' copies: needs fall with M where few rows make a reduction split or a larger batch runs on a
 // kernel without copies, and a caller that allocated for its largest batch must not fail on a smaller one.
 // make(room, plan) fills a plan (false: unsupported shape) with its need in plan->bytes.
 template <class P, class Make> static fdl_status fit_plan(const void* workspace, size_t have, P* plan, Make make) {
@@ -712,7 +712,7 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan
   const size_t cs = dt == kF32 ? 8 : 4;
   const int64_t Mp = M > 0 ? M : 1;
   double f1_cost = 0.0;
-  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N, true, true, false, &f1_cost) : Xwt::kGeneric;
+  const Xwt f1 = dt == kBF16 ? pick_xwt(Mp, K, N, room != Room::kNoCopies, true, false, &f1_cost) : Xwt::kGeneric;
   const bool tiled = f1 == Xwt::kTiled || f1 == Xwt::kPadded;
   q->f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
   const size_t kept = dt == kBF16 ? fast_xwt_part_bytes(M, N, q->f1_split) : 0;
@@ -916,6 +916,13 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* 
   if (M * H > kMaxElems || M * D > kMaxElems || H * D > kMaxElems) return false;
   const size_t ts = dt == kF32 ? 4 : 2;
   const int64_t Mp = M > 0 ? M : 1;
+  if (room == Room::kNoCopies && dt == kBF16 && mid_supported(Mp, D, H)) {
+    // room for the activation alone: both products in 128 x 128 tiles, which need no copies
+    *q = FfnPlan{};
+    q->gate_mid = q->down_mid = 1; q->ldg = H; q->down_split = 1;
+    q->off_part = q->bytes = align256((size_t)((Mp + 255) / 256 * 256) * H * ts);
+    return true;
+  }
   // off the tiles: padded copies, where the padding is not most of the work nor the launches most of the time
   const int64_t Hp = fast_gate_pad_h(H), Dq = fast_gate_pad_d(D), Dp = fast_pad_dim(D);
   const bool can_pad = dt == kBF16 && M >= 128 && M * D * H >= kStageFromWork && Hp * Dp <= 6 * H * D && (Hp / 128) * ((M + 255) / 256) <= (1 << 30);

@@ -78,8 +78,8 @@ struct Plan {
 };
 
 // What a plan may use the workspace for: everything; for the sums of split reductions in 128 x 128 tiles only what the other
-// kernels would use; no partial sums of split reductions; nor, in the block's forward pass, copies of the operands (the kernels that
-// need none then form its product).
+// kernels would use; no partial sums of split reductions; nor, in the forward products, copies of the operands (the kernels that
+// need none then form them).
 enum class Room { kAll, kTight, kNoSplit, kNoCopies };
 void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may_block, size_t* off, GradPlan* p);
 // Returns false when the shape or dtype is not supported.

@@ -170,3 +170,12 @@ def test_an_infinity_stays_in_its_row(M, K, N):
     good = [r for r in range(M) if r not in bad]
     for a, c in zip(run(X), clean):
         assert torch.equal(a[good].view(torch.int16), c[good].view(torch.int16))
+
+
+# Shapes of this size and up stay with the large tiles (smaller ones run in 128 x 128 tiles by now): forward products padded with X
+# copied and as it is, tiled with whole and with partial row tiles; gradients padded and on whole tiles, in one launch and in two
+@pytest.mark.parametrize("M,K,N", [(6737, 77, 4352), (4529, 157, 6144), (8760, 128, 5167), (4100, 1024, 3644), (11008, 128, 512),
+                                   (2988, 128, 2816), (8425, 768, 1536), (6087, 2363, 1412)])
+def test_shapes_that_keep_the_large_tiles(M, K, N):
+    test_block(M, K, N)
+    test_linear_relu(M, K, N)
