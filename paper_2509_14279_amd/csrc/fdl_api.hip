@@ -40,7 +40,7 @@ size_t mid_room(Room room, size_t kept) { return room == Room::kAll ? (kept > kM
 
 // Estimated time, us, of dX and dW on the kernels of q, with their copies and sums of split reductions: prices fitted together with
 // mid_grads_cost's to whole backward passes of 1300 shapes.  With the rule in make_grad_plan the kernels picked take 1.01 times the
-// faster ones' time on average; ten of the shapes became slower by more than 2 %, at most by 13 % (8448 x 1036 x 6582, 416 us).
+// faster ones' time on average.
 double grads_cost(const GradPlan& q) {
   const int64_t Np = q.pad ? fast_pad_dim(q.N) : q.N, Kp = q.pad ? fast_pad_dim(q.K) : q.K, Mp = q.M > 0 ? q.M : 1;
   const double mk = (double)Mp * (double)q.K / 1e6, nk = (double)q.N * (double)q.K / 1e6;
@@ -247,8 +247,11 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may
   }
   if (dt == kBF16 && mid_supported(Mp, K, N)) {
     int sa = 1, sb = 1;
-    // (7 %: the estimates' spread.  All backward passes of those shapes: 1.65 times as fast as before, 2.3 times around 2^27 products)
-    if (1.07 * mid_grads_cost(Mp, K, N, mid_room(room, sums), &sa, &sb) < grads_cost(q)) {
+    // 7 % for the estimates' spread, 20 % for large products, where power and the dies' caches decide (12 of the 1300 shapes were
+    // slower than before by more than 2 % with 7 % throughout, now 4).  All backward passes of those shapes: 1.65 times as fast as
+    // before, 2.3 times around 2^27 products.
+    const double margin = (double)Mp * (double)K * (double)N >= 0x1p33 ? 1.2 : 1.07;
+    if (margin * mid_grads_cost(Mp, K, N, mid_room(room, sums), &sa, &sb) < grads_cost(q)) {
       q.mid = 1; q.blocked = 0; q.split_a = sa; q.split_b = q.parts_b = sb;
       const size_t na = align256(sa > 1 ? (size_t)sa * partial_stride(M * K) * 4 : 0), nb = align256(sb > 1 ? (size_t)sb * partial_stride(N * K) * 4 : 0);
       if (na + nb > sums) { q.off_dxpart = *off; *off += na + nb; }      // (the copies of padded mode stay where they are)
