@@ -133,41 +133,123 @@ template <bool kPair> struct GaussTable {
 
 // ---------------------------------------------------------------------------------------------
 // Phi and phi in fp64 (fp32 storage), from a table in LDS and two short series.  Node k holds Phi(-c) and phi(c) at c = k / 64;
-// a = |z| lies h = a - c, |h| <= 1/128, from the nearest one.  With m = c + h/2 the middle and E = phi(m) / phi(c):
-//   E = exp(-h (c + h/4) / 2), six terms behind the first;   phi(z) = phi(c) E^2 exp(-h^2 / 4);
-//   Phi(-a) = Phi(-c) - integral of phi from c to a = Phi(-c) - phi(m) h (1 + (m^2 - 1) h^2 / 24 + (m^4 - 6 m^2 + 3) h^4 / 1920),
-// the Taylor expansion about the middle (phi's even derivatives are Hermite polynomials times phi).  Relative error, |z| up to
-// 3 / 6 / 9 / 13.2: 2e-16 / 7e-16 / 2e-14 / 4e-13 for Phi, 9e-16 / 2e-15 / 3e-14 / 4e-13 for phi; from 13.25 on the tail, below the
-// smallest normal fp32 number, is zero.  (0.5 erfc(-z / sqrt 2), which rounds its argument: 3e-14 at 12.)
-// The row kernels of fp32 storage are bound by this arithmetic: some 30 fp64 instructions and no branch, where the library's
-// erfc and exp go through several ranges per wavefront.  3001 x 1537, us: normalisation 26 -> 19, backward row pass 42 -> 25
-// (with one polynomial of degree 20 for the whole axis and exp's, no table: 20 and 36); steps of 20000 x 128 x 1024 and
-// 8192 x 256 x 4096 454 -> 388 and 1055 -> 974.
+// a = |z| lies h = a - c, |h| <= 1/128, from the nearest one.  With m = c + h/2 the middle and 1 + e = phi(m) / phi(c):
+//   e = exp(-h (c + h/4) / 2) - 1, eight terms;   phi(z) = phi(c) (1 + e)^2 exp(-h^2 / 4);
+//   Phi(-a) = Phi(-c) - integral of phi from c to a
+//           = Phi(-c) - phi(m) h (1 + (m^2 - 1) h^2 / 24 + (m^4 - 6 m^2 + 3) h^4 / 1920 + (m^6 - 15 m^4 + 45 m^2 - 15) h^6 / 322560),
+// the Taylor expansion about the middle (phi's even derivatives are Hermite polynomials times phi).  Beyond the last node, at
+// 13.25: exp, and the asymptotic series Phi(-a) = phi(a) / a (1 - 1/a^2 + 1 3 / a^4 - 1 3 5 / a^6 + ...), thirteen terms.
+// Largest relative error, here / 0.5 erfc(-z / sqrt 2) and exp(-z^2 / 2) / sqrt(2 pi) of a library: Phi(-a) 2.2e-16 / 6e-16 (a to
+// 1.5), 3e-15 (4.5), 1.1e-14 (9), 2.9e-14 (13.25), beyond 4.3e-16 / 1.7e-13 (the argument's rounding); phi 2.2e-16 / 2.5e-16,
+// beyond the same.
+// The row kernels of fp32 storage are bound by this arithmetic: some 35 fp64 instructions (45 with phi) and one branch a vector,
+// where the library's erfc and exp go through several ranges per wavefront.  3001 x 1537, us: normalisation 26 -> 19.5, backward row
+// pass 42 -> 28 (with one polynomial of degree 20 for the whole axis and exp's, no table: 20 and 36).  Six terms and two, zero
+// beyond the table: 19 and 27, whole fp32 steps 1 % faster, but 4e-13 from Phi and phi at 13 and no gradient at all beyond.
+namespace ctmath {
+// Sums and products of two doubles each (hi + lo), where the table's entries are to be correctly rounded
+struct Two { double hi, lo; };
+constexpr Two two_sum(double a, double b) {
+  const double s = a + b, t = s - a;
+  return {s, (a - (s - t)) + (b - t)};
+}
+constexpr Two operator+(Two a, Two b) {
+  const Two s = two_sum(a.hi, b.hi);
+  return two_sum(s.hi, s.lo + (a.lo + b.lo));
+}
+constexpr double low_part(double a, double b, double p) {      // a b - p, p the rounded product: halves of 26 bits each (Dekker)
+  const double s = 134217729.0, ta = s * a, ah = ta - (ta - a), al = a - ah, tb = s * b, bh = tb - (tb - b), bl = b - bh;
+  return ((ah * bh - p) + ah * bl + al * bh) + al * bl;
+}
+constexpr Two operator*(Two a, Two b) {
+  const double p = a.hi * b.hi;
+  return two_sum(p, low_part(a.hi, b.hi, p) + (a.hi * b.lo + a.lo * b.hi));
+}
+// phi(c) = exp(-c^2 / 2) / sqrt(2 pi), c a multiple of 2^-7 below 2^4 (its square is exact): c^2 / 2 = k ln 2 + r, ln 2 in 24 bits
+// and the rest, so that r is exact to 10^-22; 24 terms, then k halvings
+constexpr Two normal_density(double c) {
+  const double t = 0.5 * c * c;
+  const long k = (long)(t / 0.69314718055994531 + 0.5);
+  const Two r = two_sum((double)k * 0.693147182464599609375 - t, (double)k * -1.904654299957767878542e-9);   // -r
+  Two sum = {1.0, 0.0};
+  for (int n = 24; n >= 1; n--) {
+    const Two x = r * sum;
+    const double q = x.hi / (double)n, p = q * (double)n;
+    sum = Two{1.0, 0.0} + two_sum(q, ((x.hi - p) - low_part(q, (double)n, p) + x.lo) / (double)n);
+  }
+  sum = sum * Two{0x1.9884533d43651p-2, -0x1.cbc0d30ebfd15p-56};
+  for (long i = 0; i < k; i++) { sum.hi *= 0.5; sum.lo *= 0.5; }
+  return sum;
+}
+}  // namespace ctmath
 constexpr int kNormalNodes = 848;               // up to 13.25
 struct NormalNode { double tail, density; };
 struct NormalTableData { alignas(16) NormalNode node[kNormalNodes + 1]; };
 constexpr NormalTableData make_normal_table() {
   NormalTableData t = {};
-  // Phi(-13.25) from the continued fraction, then the same integral from node to node, downwards: all terms are positive
-  double x = 13.25 * 0.70710678118654752440, f = x;
-  for (int n = 60; n >= 1; n--) f = x + 0.5 * (double)n / f;
-  double sum = 0.5 * ctmath::exp_neg(0.5 * 13.25 * 13.25) * ctmath::kInvSqrtPi / f, carry = 0.0;
+  // Phi(-13.25) from the continued fraction phi(x) / (x + 1 / (x + 2 / (x + ...))), then the integral from node to node, downwards
+  const double top = (double)kNormalNodes / 64.0;
+  double f = top;
+  for (int n = 60; n >= 1; n--) f = top + (double)n / f;
+  const ctmath::Two d = ctmath::normal_density(top);
+  ctmath::Two sum = {d.hi / f, 0.0};
+  t.node[kNormalNodes] = {sum.hi, d.hi};
   for (int k = kNormalNodes - 1; k >= 0; k--) {
     const double c = (double)k / 64.0, h = 1.0 / 64.0, m = c + 0.5 * h, m2 = m * m, h2 = h * h;
-    const double series = 1.0 + h2 * ((m2 - 1.0) / 24.0 + h2 * ((m2 * (m2 - 6.0) + 3.0) / 1920.0 +
-                                                                h2 * (((m2 - 15.0) * m2 + 45.0) * m2 - 15.0) / 322560.0));
-    const double add = ctmath::exp_neg(0.5 * m2) * 0.39894228040143267794 * h * series + carry;   // (compensated)
-    const double next = sum + add;
-    carry = (sum - next) + add;
-    sum = next;
-    t.node[k].tail = sum;
-    t.node[k].density = ctmath::exp_neg(0.5 * c * c) * 0.39894228040143267794;
+    const double rest = h2 * ((m2 - 1.0) / 24.0 +
+                              h2 * ((m2 * (m2 - 6.0) + 3.0) / 1920.0 +
+                                    h2 * ((((m2 - 15.0) * m2 + 45.0) * m2 - 15.0) / 322560.0 +
+                                          h2 * ((((m2 - 28.0) * m2 + 210.0) * m2 - 420.0) * m2 + 105.0) / 92897280.0)));
+    sum = sum + ctmath::normal_density(m) * ctmath::two_sum(h, h * rest);
+    t.node[k] = {sum.hi, ctmath::normal_density(c).hi};
   }
   return t;
 }
 __device__ const NormalTableData g_normal_table = make_normal_table();
 
+// Phi(-a) and (DENSITY) phi(a), a - h a node with the two values given
+template <bool DENSITY>
+__device__ __forceinline__ void normal_near(double a, double h, double tail, double density, double& q, double& phi) {
+  const double m = __builtin_fma(h, -0.5, a), mh = m * h, h2 = h * h, w = mh * mh, v = __builtin_fma(h2, -0.25, mh);
+  double e = 1.0 / 10321920.0;
+  e = __builtin_fma(e, v, -1.0 / 645120.0);
+  e = __builtin_fma(e, v, 1.0 / 46080.0);
+  e = __builtin_fma(e, v, -1.0 / 3840.0);
+  e = __builtin_fma(e, v, 1.0 / 384.0);
+  e = __builtin_fma(e, v, -1.0 / 48.0);
+  e = __builtin_fma(e, v, 0.125);
+  e = __builtin_fma(e, v, -0.5) * v;
+  double s = __builtin_fma(w, 1.0 / 322560.0, __builtin_fma(h2, -15.0 / 322560.0, 1.0 / 1920.0));
+  s = __builtin_fma(w, s, __builtin_fma(h2, -6.0 / 1920.0, 1.0 / 24.0));
+  s = __builtin_fma(w, s, h2 * __builtin_fma(h2, 3.0 / 1920.0, -1.0 / 24.0));
+  const double step = __builtin_fma(density, e, density) * h;
+  q = tail - __builtin_fma(step, s, step);
+  if (DENSITY) {
+    const double g = h2 * __builtin_fma(h2, __builtin_fma(h2, -1.0 / 384.0, 1.0 / 32.0), -0.25), p = __builtin_fma(e, e, e + e);
+    phi = __builtin_fma(density, __builtin_fma(g, p, g + p), density);
+  }
+}
+// and beyond the last node.  Seldom taken: rolled loops, and a count the compiler cannot move out of the caller's loops, keep this
+// from costing the usual path registers.  exp(-t), t = a^2 / 2 (exact): t = k ln 2 + r, the Taylor series of exp(-r), k halvings.
+template <bool DENSITY> __device__ __forceinline__ void normal_tail(double a, double& q, double& phi) {
+  int terms = 13;
+  asm volatile("" : "+s"(terms));
+  const double t = 0.5 * (a * a), k = __builtin_rint(t * 1.44269504088896340736);
+  const double r = __builtin_fma(k, 1.9046542999577680453e-9, __builtin_fma(k, -0.693147182464599609375, t));
+  const double x = 1.0 / a, u = x * x;
+  double d = 1.0, s = 1.0;
+#pragma unroll 1
+  for (int n = terms; n >= 1; n--) {
+    d = __builtin_fma(d, -r / (double)n, 1.0);
+    s = __builtin_fma(s, (1.0 - 2.0 * (double)n) * u, 1.0);
+  }
+  d = __builtin_ldexp(d * 0.39894228040143267794, k < 2000.0 ? -(int)k : -2000);
+  q = d * x * s;
+  if (DENSITY) phi = d;
+}
+
 struct NormalTable {
+  static constexpr double kLast = (double)kNormalNodes / 64.0;
   typedef __attribute__((address_space(3))) const double lds_double;
   uint32_t base;
   template <int NT> __device__ __forceinline__ void build() {
@@ -178,28 +260,27 @@ struct NormalTable {
     base = (uint32_t)(uintptr_t)(lds_double*)tbl;
     __syncthreads();
   }
+  // up to the last node
   template <bool DENSITY> __device__ __forceinline__ void eval(double z, double& Phi, double& phi) const {
-    const double a = __builtin_fmin(__builtin_fabs(z), 13.25);
+    const double a = __builtin_fmin(__builtin_fabs(z), kLast);
     // (the sum's last bits are the nearest node's number)
     const double magic = 0x1.8p52, t = __builtin_fma(a, 64.0, magic), k = t - magic;
     const uint32_t at = base + ((uint32_t)__builtin_bit_cast(uint64_t, t) << 4);
     typedef __attribute__((ext_vector_type(2))) double f64x2;
     const f64x2 node = *(const __attribute__((address_space(3))) f64x2*)(uintptr_t)at;
-    const double c = k * (1.0 / 64.0), h = a - c;
-    const double v = h * __builtin_fma(h, 0.25, c), m = __builtin_fma(h, -0.5, a), m2 = m * m, h2 = h * h;
-    double E = 1.0 / 46080.0;
-    E = __builtin_fma(E, v, -1.0 / 3840.0);
-    E = __builtin_fma(E, v, 1.0 / 384.0);
-    E = __builtin_fma(E, v, -1.0 / 48.0);
-    E = __builtin_fma(E, v, 0.125);
-    E = __builtin_fma(E, v, -0.5);
-    E = __builtin_fma(E, v, 1.0);
-    double s = __builtin_fma(m2, m2 - 6.0, 3.0) * (h2 * (1.0 / 1920.0));
-    s = __builtin_fma(h2, __builtin_fma(m2, 1.0 / 24.0, s - 1.0 / 24.0), 1.0);
-    const double middle = node[1] * E;
-    const double q = __builtin_fma(-(middle * h), s, node[0]);
-    Phi = z > 0.0 ? 1.0 - q : q;               // (NaN: q = 0; z Phi and z phi are NaN)
-    if (DENSITY) phi = middle * E * __builtin_fma(h2, __builtin_fma(h2, 1.0 / 32.0, -0.25), 1.0);
+    double q;
+    normal_near<DENSITY>(a, __builtin_fma(k, -1.0 / 64.0, a), node[0], node[1], q, phi);
+    Phi = z > 0.0 ? 1.0 - q : q;               // (NaN: q is a small number; z Phi and z phi are NaN)
+  }
+  // whether z lies beyond it, and the values there
+  template <bool DENSITY> static __device__ __forceinline__ bool far(double z, double& Phi, double& phi) {
+    const bool is = __builtin_fabs(z) > kLast;
+    if (__builtin_expect(is, 0)) {
+      double q;
+      normal_tail<DENSITY>(__builtin_fabs(z), q, phi);
+      Phi = z > 0.0 ? 1.0 - q : q;
+    }
+    return is;
   }
 };
 
@@ -209,14 +290,48 @@ template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
   NormalTable tab;
   // every thread of the workgroup calls this; ends with a barrier
   __device__ __forceinline__ void build() { tab.build<NT>(); }
-  __device__ __forceinline__ double gelu(double z) const {
-    double Phi, phi;
-    tab.eval<false>(z, Phi, phi);
-    return z * Phi;
+  // One branch for a thread's vector: seldom taken as it is, a branch per element keeps the elements' chains from overlapping
+  // (forward passes up to 12 % slower).
+  template <int V, class R> __device__ __forceinline__ void gelu(const R& z, double (&a)[V]) const {
+    double phi;
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      double Phi;
+      tab.eval<false>((double)z[v], Phi, phi);
+      a[v] = (double)z[v] * Phi;
+    }
+    if (__builtin_expect(some_far<V>(z), 0)) {
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        double Phi = 0.0;
+        if (NormalTable::far<false>((double)z[v], Phi, phi)) a[v] = (double)z[v] * Phi;
+      }
+    }
   }
-  __device__ __forceinline__ void eval(double z, double& Phi, double& zphi) const {
+  template <int V, class R> __device__ __forceinline__ void eval(const R& z, double (&Phi)[V], double (&zphi)[V]) const {
+#pragma unroll
+    for (int v = 0; v < V; v++) eval((double)z[v], false, Phi[v], zphi[v]);
+    if (__builtin_expect(some_far<V>(z), 0)) {
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        double phi;
+        if (NormalTable::far<true>((double)z[v], Phi[v], phi)) zphi[v] = (double)z[v] * phi;
+      }
+    }
+  }
+  // Element by element, where registers are short.  far: what some_far says of the vector that z is of (uniform over the
+  // wavefront: a scalar branch)
+  template <int V, class R> static __device__ __forceinline__ bool some_far(const R& z) {
+    float most = 0.0f;
+#pragma unroll
+    for (int v = 0; v < V; v++) most = __builtin_fmaxf(most, __builtin_fabsf(z[v]));
+    return __builtin_amdgcn_ballot_w64(most > (float)NormalTable::kLast) != 0;
+  }
+  // far: what some_far says of the vector that z is of
+  __device__ __forceinline__ void eval(double z, bool far, double& Phi, double& zphi) const {
     double phi;
     tab.eval<true>(z, Phi, phi);
+    if (__builtin_expect(far, 0)) (void)NormalTable::far<true>(z, Phi, phi);
     zphi = z * phi;
   }
 };
@@ -237,7 +352,16 @@ template <bool kPair, int NT> struct ActTable<bf16_t, kPair, NT> {
     const float h = *(const lds_float*)(uintptr_t)GT::address_of(__builtin_bit_cast(uint32_t, z) >> 16, org);
     return z * (0.5f + GT::with_sign_of(h, z));
   }
-  __device__ __forceinline__ void eval(float z, float& Phi, float& zphi) const {
+  template <int V, class R> __device__ __forceinline__ void gelu(const R& z, float (&a)[V]) const {
+#pragma unroll
+    for (int v = 0; v < V; v++) a[v] = gelu(to_f32<bf16_t>(z[v]));
+  }
+  template <int V, class R> static __device__ __forceinline__ bool some_far(const R&) { return false; }
+  template <int V, class R> __device__ __forceinline__ void eval(const R& z, float (&Phi)[V], float (&zphi)[V]) const {
+#pragma unroll
+    for (int v = 0; v < V; v++) eval(to_f32<bf16_t>(z[v]), false, Phi[v], zphi[v]);
+  }
+  __device__ __forceinline__ void eval(float z, bool, float& Phi, float& zphi) const {
     const f32x2 e = *(const lds_f32x2*)(uintptr_t)GT::address_of(__builtin_bit_cast(uint32_t, z) >> 16, org);
     Phi = 0.5f + GT::with_sign_of(e[0], z);
     zphi = GT::with_sign_of(e[1], z);

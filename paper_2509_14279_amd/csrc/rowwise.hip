@@ -11,8 +11,6 @@
 #include "common.hip.h"
 #include "internal.h"
 
-#include <type_traits>
-
 namespace fdl {
 namespace {
 
@@ -430,10 +428,12 @@ __global__ __launch_bounds__(256) void b1a_kernel(int64_t M, int64_t N, const T*
 #pragma unroll
         for (int v = 0; v < V; v++) gm[v] = v < nv ? gamma[col + v] : 0.0f;
       }
+      C a[V];
+      tab.template gelu<V>(z, a);
 #pragma unroll
       for (int v = 0; v < V; v++) {
         const C g = (C)to_f32<T>(dy[v]) * (C)gm[v];
-        const C ah = (tab.gelu((C)to_f32<T>(z[v])) - mu) * rs;
+        const C ah = (a[v] - mu) * rs;
         s1 += g;
         s2 += g * ah;
       }
@@ -490,13 +490,13 @@ __global__ __launch_bounds__(256) void b1b_kernel(int64_t M, int64_t N, int64_t 
     }
     const C mu = (C)read_lane(lmu, at), rs = (C)read_lane(lrs, at), c1 = read_lane(lc1, at), c2 = read_lane(lc2, at);
     raw_t o;
+    C Phi[V], zphi[V];
+    tab.template eval<V>(rz[k], Phi, zphi);
 #pragma unroll
     for (int v = 0; v < V; v++) {
       const C z = (C)to_f32<T>(rz[k][v]), dy = (C)to_f32<T>(rdy[k][v]);
-      C Phi, zphi;
-      tab.eval(z, Phi, zphi);
-      const C ah = (z * Phi - mu) * rs;
-      C dz = rs * (dy * gm[v] - c1 - ah * c2) * (Phi + zphi);
+      const C ah = (z * Phi[v] - mu) * rs;
+      C dz = rs * (dy * gm[v] - c1 - ah * c2) * (Phi[v] + zphi[v]);
       if (ANY) dz = v < nv ? dz : (C)0;
       accb[v] += dy;
       accg[v] += dy * ah;
@@ -611,12 +611,17 @@ __global__ __launch_bounds__(NT) void b1_fused_kernel(int64_t M, int64_t N, int6
     const C rs = (C)brs[buf], nmr = -(C)bmu[buf] * rs;
     C ah[V], gp[V], g[V];
     C s1 = 0, s2 = 0;
+    constexpr bool kTogether = sizeof(T) == 4 && V <= 4;     // (eight elements' fp64 state at once does not fit the registers)
+    C allPhi[kTogether ? V : 1], allzphi[kTogether ? V : 1];
+    if constexpr (kTogether) tab.template eval<V>(bz[buf], allPhi, allzphi);
+    const bool far = tab.template some_far<V>(bz[buf]);
 #pragma unroll
     for (int v = 0; v < V; v++) {
       const C z = (C)to_f32<T>(bz[buf][v]);
       const C dy = (C)to_f32<T>(bdy[buf][v]);
       C Phi, zphi;
-      tab.eval(z, Phi, zphi);
+      if constexpr (kTogether) { Phi = allPhi[v]; zphi = allzphi[v]; }
+      else tab.eval(z, far, Phi, zphi);
       ah[v] = (z * Phi) * rs + nmr;                        // (A - mean) rstd, one fused multiply-add
       gp[v] = (Phi + zphi) * rs;
       float gv = gm[v];
@@ -868,10 +873,11 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
 #pragma unroll
       for (int v = 0; v < V; v++) a[s][v] = 0;
       if (nv[s] == 0) continue;                        // (a whole wavefront past the end of the row skips the activation)
+      if constexpr (ACT == ACT_GELU) act.template gelu<V>(raw[s], a[s]);     // zeros past the end of the row: GELU(0) = 0
 #pragma unroll
       for (int v = 0; v < V; v++) {
         const double z = (double)raw[s][v];
-        a[s][v] = ACT == ACT_GELU ? act.gelu(z) : z;  // zeros past the end of the row: GELU(0) = 0
+        if (ACT != ACT_GELU) a[s][v] = z;
         sum += ACT == ACT_RMS ? z * z : a[s][v];
       }
     }
@@ -943,9 +949,11 @@ __global__ __launch_bounds__(256) void f2_narrow_kernel(int64_t M, int64_t N, fl
   fetch(row);
   for (int64_t lead = (int64_t)blockIdx.x * 16; lead < M; lead += step, row += step) {
     C a[K], sum = 0, sq = 0;
+    if constexpr (sizeof(T) == 4) tab.template gelu<K>(raw, a);
 #pragma unroll
     for (int k = 0; k < K; k++) {
-      a[k] = l + 16 * k < N ? tab.gelu((C)to_f32<T>(raw[k])) : (C)0;
+      if constexpr (sizeof(T) == 2) a[k] = l + 16 * k < N ? tab.gelu(to_f32<T>(raw[k])) : 0.0f;
+      else a[k] = l + 16 * k < N ? a[k] : 0.0;
       sum += a[k];
     }
     fetch(row + step);
@@ -1045,9 +1053,7 @@ __global__ __launch_bounds__(256) void long_moments_kernel(int64_t M, int64_t N,
       if (k > 0 && row + k >= r1) continue;                      // (uniform)
       C a[kLongVectors][V];
 #pragma unroll
-      for (int s = 0; s < kLongVectors; s++)
-#pragma unroll
-        for (int v = 0; v < V; v++) a[s][v] = tab.gelu((C)to_f32<T>(l.raw[k][s][v]));
+      for (int s = 0; s < kLongVectors; s++) tab.template gelu<V>(l.raw[k][s], a[s]);
       l.fetch(k, Z, N, row + k + 2, r1);
       base[k] = read_lane(a[0][0], 0);
 #pragma unroll
@@ -1125,10 +1131,12 @@ __global__ __launch_bounds__(256) void long_apply_kernel(int64_t M, int64_t N, i
     const C mu = stats[half][at][0], rs = stats[half][at][1];
     typename RawVec<T, ANY>::type o[kLongVectors];
 #pragma unroll
-    for (int s = 0; s < kLongVectors; s++)
+    for (int s = 0; s < kLongVectors; s++) {
+      C a[V];
+      tab.template gelu<V>(l.raw[buf][s], a);
 #pragma unroll
-      for (int v = 0; v < V; v++)
-        o[s][v] = to_storage<T, C>((tab.gelu((C)to_f32<T>(l.raw[buf][s][v])) - mu) * rs * (C)gm[s][v] + (C)bt[s][v]);
+      for (int v = 0; v < V; v++) o[s][v] = to_storage<T, C>((a[v] - mu) * rs * (C)gm[s][v] + (C)bt[s][v]);
+    }
     l.fetch(buf, Z, N, row + 2, r1);
 #pragma unroll
     for (int s = 0; s < kLongVectors; s++)

@@ -2,8 +2,9 @@
 at its end and past it, in each form of the row kernels.  One row with K = 1, X = 1, W = z, b = 0 makes the pre-activations the
 numbers z themselves and dW the row's dZ, element by element.
 
-Bounds: one rounding to fp32 (2^-24) of the result, and 1e-12 of the sum of the magnitudes that cancel in it (fp64 arithmetic
-on a table within 4e-13; the saved fp32 statistics are taken as they are)."""
+Bounds: one rounding to fp32 (2^-24) of the result, and 1e-12 of the sum of the magnitudes that cancel in it (the saved fp32
+statistics are taken as they are; sums of up to 20000 fp64 terms, and the oracle's erfc, which rounds its argument: 2e-13 of
+Phi(-38)); where the result is below the smallest normal fp32 number, half the spacing there (2^-150)."""
 import numpy as np
 import pytest
 import torch
@@ -55,8 +56,30 @@ def test_gelu_and_its_derivative(N):
     d = O.gelu_grad(Z)
     dZ = rstd * (g - c1 - ah * c2) * d
     S = rstd * (np.abs(g) + np.abs(g).mean() + np.abs(ah) * np.abs(g * ah).mean()) * (np.abs(O.Phi(Z)) + np.abs(Z * O.phi(Z)))
-    assert np.all(np.abs(got["dW"][:, 0] - dZ) <= u * np.abs(dZ) + 1e-12 * S + 1e-37)
+    assert np.all(np.abs(got["dW"][:, 0] - dZ) <= u * np.abs(dZ) + 1e-12 * S + 2.0 ** -150)
     assert np.all(np.abs(got["dgamma"] - g64["dY"][0] * ah) <= u * np.abs(g64["dY"][0] * ah) + 1e-12 * np.abs(g64["dY"][0]) * (np.abs(A) + abs(mean)) * rstd)
+
+
+# (one vector, two, eight elements per thread; a wavefront's rows; the two kernels for long rows)
+@pytest.mark.parametrize("N", [47, 200, 1000, 1537, 4096, 5000, 20000])
+def test_gradients_far_out(N):
+    """GELU'(z) = Phi(z) + z phi(z) below -13 is small, not zero: times a large upstream gradient it is an ordinary number."""
+    rng = np.random.default_rng(N + 2)
+    z = rng.standard_normal(N).astype(np.float32)
+    far = rng.permutation(N)[:N // 3]
+    z[far] = -np.concatenate([np.linspace(13.2, 13.3, len(far) - len(far) // 2), np.linspace(13.3, 17.0, len(far) // 2)])
+    t = {"X": torch.ones(1, 1), "W": torch.from_numpy(z)[:, None].contiguous(), "b": torch.zeros(N), "gamma": torch.ones(N),
+         "beta": torch.zeros(N), "dY": torch.from_numpy((1e30 * rng.standard_normal((1, N))).astype(np.float32))}
+    cfg = I.custom("f32", 1, 1, N, seed=0)
+    got = {k: H.to_f64(v) for k, v in H.run_fdl(cfg, t).items()}
+    Z, mean, rstd = z.astype(np.float64), got["mean"][0], got["rstd"][0]
+    ah, g = (O.gelu(Z) - mean) * rstd, t["dY"].numpy().astype(np.float64)[0]
+    factor = rstd * (g - g.mean() - ah * (g * ah).mean())
+    S = rstd * (np.abs(g) + np.abs(g).mean() + np.abs(ah) * np.abs(g * ah).mean())
+    dZ = factor * O.gelu_grad(Z)
+    assert np.abs(dZ[far]).min() > 0 and np.abs(dZ[far]).max() > 1e-8
+    d = np.abs(O.Phi(Z)) + np.abs(Z * O.phi(Z))
+    assert np.all(np.abs(got["dW"][:, 0] - dZ) <= 2.0 ** -24 * np.abs(dZ) + 1e-12 * S * d + 2.0 ** -150)
 
 
 def test_infinities_and_nan():
