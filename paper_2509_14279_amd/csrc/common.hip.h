@@ -292,7 +292,7 @@ template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
   __device__ __forceinline__ void build() { tab.build<NT>(); }
   // One branch for a thread's vector: seldom taken as it is, a branch per element keeps the elements' chains from overlapping
   // (forward passes up to 12 % slower).
-  template <int V, class R> __device__ __forceinline__ void gelu(const R& z, double (&a)[V]) const {
+  template <int V, class R> __device__ __forceinline__ void gelu(R z, double (&a)[V]) const {
     double phi;
 #pragma unroll
     for (int v = 0; v < V; v++) {
@@ -308,7 +308,7 @@ template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
       }
     }
   }
-  template <int V, class R> __device__ __forceinline__ void eval(const R& z, double (&Phi)[V], double (&zphi)[V]) const {
+  template <int V, class R> __device__ __forceinline__ void eval(R z, double (&Phi)[V], double (&zphi)[V]) const {
 #pragma unroll
     for (int v = 0; v < V; v++) eval((double)z[v], false, Phi[v], zphi[v]);
     if (__builtin_expect(some_far<V>(z), 0)) {
@@ -321,7 +321,7 @@ template <bool kPair, int NT> struct ActTable<float, kPair, NT> {
   }
   // Element by element, where registers are short.  far: what some_far says of the vector that z is of (uniform over the
   // wavefront: a scalar branch)
-  template <int V, class R> static __device__ __forceinline__ bool some_far(const R& z) {
+  template <int V, class R> static __device__ __forceinline__ bool some_far(R z) {
     float most = 0.0f;
 #pragma unroll
     for (int v = 0; v < V; v++) most = __builtin_fmaxf(most, __builtin_fabsf(z[v]));
@@ -352,12 +352,12 @@ template <bool kPair, int NT> struct ActTable<bf16_t, kPair, NT> {
     const float h = *(const lds_float*)(uintptr_t)GT::address_of(__builtin_bit_cast(uint32_t, z) >> 16, org);
     return z * (0.5f + GT::with_sign_of(h, z));
   }
-  template <int V, class R> __device__ __forceinline__ void gelu(const R& z, float (&a)[V]) const {
+  template <int V, class R> __device__ __forceinline__ void gelu(R z, float (&a)[V]) const {
 #pragma unroll
     for (int v = 0; v < V; v++) a[v] = gelu(to_f32<bf16_t>(z[v]));
   }
-  template <int V, class R> static __device__ __forceinline__ bool some_far(const R&) { return false; }
-  template <int V, class R> __device__ __forceinline__ void eval(const R& z, float (&Phi)[V], float (&zphi)[V]) const {
+  template <int V, class R> static __device__ __forceinline__ bool some_far(R) { return false; }
+  template <int V, class R> __device__ __forceinline__ void eval(R z, float (&Phi)[V], float (&zphi)[V]) const {
 #pragma unroll
     for (int v = 0; v < V; v++) eval(to_f32<bf16_t>(z[v]), false, Phi[v], zphi[v]);
   }
