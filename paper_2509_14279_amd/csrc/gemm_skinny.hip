@@ -257,7 +257,9 @@ Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy, bool may_pad, bool 
 // How the feed-forward block's gate and up products run, with what follows from it for the down product: the lowest estimated
 // time of both.  The tiled gate kernel has a tile of 128 columns and no split; in padded mode it hands the activation on with a
 // padded pitch, which the down product then takes in padded mode too.  This kernel's gate variant: about 10.5 us per 10^9
-// products (row blocks of 64; the narrower ones count as 26 - 50 rows), three times that for rows that start at any element.
+// products (row blocks of 64; the narrower ones count as 26 - 50 rows), a tenth more for rows at 4-byte addresses, three times that
+// for rows that start at any element.  (Priced like the last, 330 shapes with even D that is no multiple of 8, 1 - 300 rows, lost 2 %
+// to the faster of this kernel and the 128 x 128 tiles, up to 35 %: 21 x 3924 x 3698 26.7 us here, 42.6 there; now 0.1 %, below 5 %.)
 // Measured, us, whole blocks: gate on this kernel / as two generic products: 16 x 4096 x 11008 74 / 478, 16 x 4097 x 11008 147 /
 // 280, 66 x 4097 x 65536 2963 / 2120.
 GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad) {
@@ -267,10 +269,10 @@ GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad) {
   const double mh = (double)M * (double)H;
   double cost = 2.0 * generic_xwt_cost(M, D, H) + 5.0 + mh * 6.0 / 4e6 + down;
   auto offer = [&](Gate gate, double c) { if (c < cost) { best.gate = gate; cost = c; } };
-  const bool whole = D % 8 == 0;
+  const bool whole = D % 8 == 0, even = D % 2 == 0;
   const double rows = M <= 16 ? (whole ? 40.0 : 26.0) : (M <= 32 ? (whole ? 50.0 : 46.0) : (double)((M + 63) / 64 * 64));
   if (M <= skinny_rows(D))
-    offer(Gate::kSkinny, 1.1 * (4.0 + (whole ? 10.5e-9 : 34e-9) * rows * (double)D * 2.0 * (double)H) + down);
+    offer(Gate::kSkinny, 1.1 * (even && !whole ? 5.0 : 4.0) + 1.1 * (whole ? 10.5e-9 : (even ? 11.5e-9 : 34e-9)) * rows * (double)D * 2.0 * (double)H + down);
   const int64_t tiles = ((H + 127) / 128) * ((M + 255) / 256);
   const double tiled = (double)((tiles + 255) / 256) * ((double)D / 64 * 1.1 + 8.0);
   if (fast_gate_supported(M, D, H)) {

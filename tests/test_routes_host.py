@@ -16,3 +16,10 @@ def test_pitch_of_the_gradient(op, M, K, N, pitch):
     assert gradients.startswith("mid"), gradients
     if not (op == "relu" and forward.startswith("padded")):      # (the padded product's masking epilogue writes whole tiles)
         assert int(ldz) == pitch
+
+
+# few rows whose width is even but no multiple of 8: the few-row kernel takes 27, 30, 35, 19 and 17 us, 128 x 128 tiles 43, 40, 45, 23
+# and 20
+@pytest.mark.parametrize("M,D,H", [(21, 3924, 3698), (36, 3114, 3032), (17, 3754, 3369), (117, 1634, 1428), (1, 718, 8352)])
+def test_gate_products_of_few_even_rows(M, D, H):
+    assert route("ffn", "bf16", M, D, H)[0] == "few rows"
