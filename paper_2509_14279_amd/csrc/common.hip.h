@@ -231,9 +231,11 @@ __device__ __forceinline__ void normal_near(double a, double h, double tail, dou
 }
 // and beyond the last node.  Seldom taken: rolled loops, and a count the compiler cannot move out of the caller's loops, keep this
 // from costing the usual path registers.  exp(-t), t = a^2 / 2 (exact): t = k ln 2 + r, the Taylor series of exp(-r), k halvings.
+// From 39 on both are zero: larger arguments, infinity among them, count as 52 (beyond 10^8 nothing would be left of r).
 template <bool DENSITY> __device__ __forceinline__ void normal_tail(double a, double& q, double& phi) {
   int terms = 13;
   asm volatile("" : "+s"(terms));
+  a = __builtin_fmin(a, 52.0);
   const double t = 0.5 * (a * a), k = __builtin_rint(t * 1.44269504088896340736);
   const double r = __builtin_fma(k, 1.9046542999577680453e-9, __builtin_fma(k, -0.693147182464599609375, t));
   const double x = 1.0 / a, u = x * x;
@@ -243,7 +245,7 @@ template <bool DENSITY> __device__ __forceinline__ void normal_tail(double a, do
     d = __builtin_fma(d, -r / (double)n, 1.0);
     s = __builtin_fma(s, (1.0 - 2.0 * (double)n) * u, 1.0);
   }
-  d = __builtin_ldexp(d * 0.39894228040143267794, k < 2000.0 ? -(int)k : -2000);
+  d = __builtin_ldexp(d * 0.39894228040143267794, -(int)k);
   q = d * x * s;
   if (DENSITY) phi = d;
 }

@@ -82,6 +82,33 @@ def test_gradients_far_out(N):
     assert np.all(np.abs(got["dW"][:, 0] - dZ) <= 2.0 ** -24 * np.abs(dZ) + 1e-12 * S * d + 2.0 ** -150)
 
 
+# (the forms of the row kernels as above)
+@pytest.mark.parametrize("N", [47, 200, 1000, 1537, 4096, 5000, 20000])
+def test_very_large_arguments(N):
+    """Phi is 0 or 1 for any finite argument that is large, also where its square leaves no digit of it: GELU(z) is 0 or z, and the
+    normalised row is that of the few elements of the largest magnitude."""
+    rng = np.random.default_rng(N + 3)
+    z = rng.standard_normal(N).astype(np.float32)
+    at = rng.permutation(N)[:9]
+    z[at] = [1e25, -1e25, 1e30, -1e30, 3e9, -3e9, -3.4e38, 2e30, -1e15]
+    t = {"X": torch.ones(1, 1), "W": torch.from_numpy(z)[:, None].contiguous(), "b": torch.zeros(N), "gamma": torch.ones(N),
+         "beta": torch.zeros(N), "dY": torch.from_numpy(rng.standard_normal((1, N)).astype(np.float32))}
+    cfg = I.custom("f32", 1, 1, N, seed=0)
+    got = {k: H.to_f64(v) for k, v in H.run_fdl(cfg, t).items()}
+    Z, mean, rstd = z.astype(np.float64), got["mean"][0], got["rstd"][0]
+    A, u = O.gelu(Z), 2.0 ** -24
+    assert A[at[0]] == Z[at[0]] and A[at[6]] == 0
+    exact_mean, exact_rstd = A.mean(), 1.0 / np.sqrt(A.var() + cfg.eps)
+    assert abs(mean - exact_mean) <= (u + 1e-12) * exact_mean and abs(rstd - exact_rstd) <= (u + 1e-12) * exact_rstd
+    Y = (A - exact_mean) * exact_rstd
+    assert np.all(np.abs(got["Y"][0] - Y) <= u * np.abs(Y) + 1e-12 * (np.abs(A) + exact_mean) * exact_rstd)
+    ah, g = (A - mean) * rstd, t["dY"].numpy().astype(np.float64)[0]
+    dZ = rstd * (g - g.mean() - ah * (g * ah).mean()) * O.gelu_grad(Z)
+    S = rstd * (np.abs(g) + np.abs(g).mean() + np.abs(ah) * np.abs(g * ah).mean()) * (np.abs(O.Phi(Z)) + np.abs(Z * O.phi(Z)))
+    assert np.isfinite(dZ).all()
+    assert np.all(np.abs(got["dW"][:, 0] - dZ) <= u * np.abs(dZ) + 1e-12 * S + 2.0 ** -150)
+
+
 def test_infinities_and_nan():
     # as the library's erfc and exp: GELU(-inf) and whatever a row with a NaN or an infinity gives are NaN, rows beside it are not
     for bad in (np.inf, -np.inf, np.nan):
@@ -91,3 +118,9 @@ def test_infinities_and_nan():
         got = {k: H.to_f64(v) for k, v in H.run_fdl(cfg, t).items()}
         assert np.isnan(got["Y"][1]).all() and np.isnan(got["dX"][1]).all()
         assert np.isfinite(got["Y"][[0, 2]]).all() and np.isfinite(got["dX"][[0, 2]]).all()
+    # GELU(inf) is infinite, and so is the mean of a row that has it and no NaN
+    cfg = I.custom("f32", 1, 1, 130, seed=3)
+    t = I.generate(cfg)
+    t["X"][0, 0] = 1.0
+    t["W"][7, 0] = np.inf
+    assert H.to_f64(H.run_fdl(cfg, t)["mean"])[0] == np.inf

@@ -21,7 +21,7 @@ def values(tmp_path_factory):
     text = open(HEADER).read()
     code = text[text.index("namespace ctmath {\n// Sums and products"):text.index("struct NormalTable {")]
     code = code.replace("__device__ const NormalTableData", "static const NormalTableData").replace('"+s"', '"+r"')
-    prog = ("#include <cmath>\n#include <cstdio>\n#define __device__\n#define __forceinline__ inline\nusing std::exp;\n" + code +
+    prog = ("#include <cmath>\n#include <cstdio>\n#include <initializer_list>\n#define __device__\n#define __forceinline__ inline\nusing std::exp;\n" + code +
             """int main() {
   for (int i = 0; i < 20000; i++) {
     // fp32 numbers: spread evenly, and around the nodes and the places half way between them
@@ -37,6 +37,11 @@ def values(tmp_path_factory):
       }
       std::printf("%a %a %a\\n", z, q, phi);
     }
+  }
+  for (double z : {40.0, 51.9, 52.1, 1e3, 1e8, 1e10, 1e15, 1e20, 1e25, 1e30, 1e38, (double)__FLT_MAX__, (double)INFINITY}) {
+    double q, phi;
+    normal_tail<true>(z, q, phi);
+    std::printf("%a %a %a\\n", z, q, phi);
   }
 }
 """)
@@ -54,9 +59,19 @@ def test_tail_and_density(values):
     mp = pytest.importorskip("mpmath")
     mp.mp.dps = 40
     for z, q, phi in values[::5]:
+        if z >= 40:
+            continue
         x = mp.mpf(z)
         exact, density = mp.erfc(x / mp.sqrt(2)) / 2, mp.exp(-x * x / 2) / mp.sqrt(2 * mp.pi)
         if density < mp.mpf(2) ** -1000:
             continue
         assert abs(q / exact - 1) <= (5 * U if z > 13.25 else 4 * U + 6e-16), z
         assert abs(phi / density - 1) <= (5 * U if z > 13.25 else 3 * U), z
+
+
+def test_beyond_the_smallest_double(values):
+    # both are zero there, at the largest fp32 number and at infinity as well: Phi is exactly 0 or 1
+    beyond = [v for v in values if v[0] >= 40]
+    assert beyond[-1][0] == float("inf") and len(beyond) == 13
+    for z, q, phi in beyond:
+        assert q == 0 and phi == 0, (z, q, phi)
