@@ -2,6 +2,11 @@
 kernel have to reach it, and the rules that were measured have to hold where they were measured."""
 import pytest
 
+import test_mid_tiles_gpu
+import test_padded_shapes_gpu
+import test_row_kernels_gpu
+import test_small_workspaces_gpu
+import test_special_values_gpu
 from routes import route
 
 
@@ -23,3 +28,42 @@ def test_pitch_of_the_gradient(op, M, K, N, pitch):
 @pytest.mark.parametrize("M,D,H", [(21, 3924, 3698), (36, 3114, 3032), (17, 3754, 3369), (117, 1634, 1428), (1, 718, 8352)])
 def test_gate_products_of_few_even_rows(M, D, H):
     assert route("ffn", "bf16", M, D, H)[0] == "few rows"
+
+
+def forward(op, shapes):
+    return [route(op, "bf16", *s)[0] for s in shapes]
+
+
+# the tests of infinite and very large biases, of infinities in X, of the smallest workspaces and of parity on the large tiles: each
+# form of the forward product is among the shapes of each
+@pytest.mark.parametrize("op", ["block", "relu"])
+def test_forward_products_of_the_large_tiles(op):
+    large = forward(op, test_padded_shapes_gpu.LARGE)
+    assert set(large) == {"tiled", "padded", "tiled split", "padded split"}
+    assert {m % 256 == 0 for (m, _, _), f in zip(test_padded_shapes_gpu.LARGE, large) if f == "tiled split"} == {True, False}
+    assert {k % 128 == 0 for (_, k, _), f in zip(test_padded_shapes_gpu.LARGE, large) if f == "padded"} == {True, False}
+    special = forward(op, test_special_values_gpu.SHAPES)
+    assert set(special) >= set(large) | {"tiled transposed", "mid", "mid split", "few rows", "generic"}
+    assert set(forward(op, [s[1:] for s in test_small_workspaces_gpu.SHAPES if s[0] == "bf16"])) >= set(large)
+    assert set(forward(op, test_mid_tiles_gpu.SHAPES)) >= {"mid", "mid split"}
+
+
+@pytest.mark.parametrize("op", ["block", "relu"])
+def test_gradients(op):
+    large = {route(op, "bf16", *s)[1] for s in test_padded_shapes_gpu.LARGE}
+    assert large >= {"pair padded-x", "pair padded extra", "pair extra", "tiled and tiled padded-x"}
+    mid = {route(op, "bf16", *s)[1] for s in test_mid_tiles_gpu.SHAPES}
+    assert mid == {"mid", "mid dx-split", "mid dw-split", "mid dx-split dw-split"}
+
+
+def test_blocked_gradients():
+    narrow = [s for s in test_row_kernels_gpu.BLOCKED if "blocked" in route("block", "bf16", *s)[1]]
+    assert narrow == test_row_kernels_gpu.BLOCKED[1:]
+    assert min(n for _, _, n in narrow) <= 512 < max(n for _, _, n in narrow) <= 1024
+
+
+def test_feed_forward_products():
+    expected = {"padded | padded", "padded | padded split", "tiled | tiled", "tiled | tiled split", "tiled | mid"}
+    for shapes in (test_padded_shapes_gpu.LARGE_FFN, test_special_values_gpu.FFN):
+        assert {" | ".join(route("ffn", "bf16", *s)) for s in shapes} >= expected
+    assert "mid | tiled split" in {" | ".join(route("ffn", "bf16", *s)) for s in test_padded_shapes_gpu.LARGE_FFN}

@@ -108,9 +108,13 @@ def test_statistics_of_nearly_constant_rows(M, K, N):
     assert np.abs(H.to_f64(got["rstd"]) / rstd - 1).max() <= 5 * 2.0 ** -24
 
 
-@pytest.mark.parametrize("M,K,N", [(2560, 2560, 512), (5120, 1024, 1024)])
+# (a wavefront per row, two; 6656 and 11520 rows leave wavefronts without a pair of rows on the last round)
+BLOCKED = [(2560, 2560, 512), (5120, 1024, 1024), (8192, 3584, 512), (6656, 1024, 512), (11520, 512, 768)]
+
+
+@pytest.mark.parametrize("M,K,N", BLOCKED)
 def test_blocked_gradients_of_narrow_rows(M, K, N):
-    # dZ in 32 x 32 blocks, written by a wavefront or two per row
+    # dZ in 32 x 32 blocks, written by a wavefront or two per row (test_routes_host.py: all but the first)
     cfg = I.custom("bf16", M, K, N, seed=8200 + N)
     t = I.generate(cfg)
     got = H.run_fdl(cfg, t)

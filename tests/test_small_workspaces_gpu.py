@@ -35,10 +35,11 @@ def workspace(nbytes):
     return ws
 
 
-# fp32: all tiles split, the last round split; bf16: split tiles whole / ragged rows / padded, odd K (copy of X), dW with rows left
-# over, dX and dW in one launch, aligned rows with a partial tile
+# fp32: all tiles split, the last round split; bf16: 128 x 128 tiles, split and whole; 256 x 256 tiles with copies for padding, of X's
+# last rows, and split, whole and padded (a test of the routes asks for these), gradients in one launch and with rows left over
 SHAPES = [("f32", 256, 256, 256), ("f32", 300, 1025, 771), ("bf16", 512, 4096, 2048), ("bf16", 500, 2560, 4104),
-          ("bf16", 700, 4099, 520), ("bf16", 1000, 256, 768), ("bf16", 2048, 1024, 2048), ("bf16", 4300, 256, 768)]
+          ("bf16", 700, 4099, 520), ("bf16", 1000, 256, 768), ("bf16", 2048, 1024, 2048), ("bf16", 4300, 256, 768),
+          ("bf16", 4529, 157, 6144), ("bf16", 8425, 768, 1536), ("bf16", 1337, 3072, 3328), ("bf16", 2062, 2651, 2073)]
 
 
 @pytest.mark.parametrize("dtype,M,K,N", SHAPES)
@@ -93,7 +94,8 @@ def test_block_and_siblings(dtype, M, K, N):
 
 
 @pytest.mark.parametrize("dtype,M,D,Hd", [("f32", 130, 300, 515), ("bf16", 1000, 640, 1000), ("bf16", 512, 1024, 2816),
-                                          ("bf16", 600, 700, 1280), ("bf16", 1024, 1024, 2816)])
+                                          ("bf16", 600, 700, 1280), ("bf16", 1024, 1024, 2816), ("bf16", 4526, 1077, 1120),
+                                          ("bf16", 2037, 1039, 3834), ("bf16", 1540, 2560, 3840)])
 def test_feed_forward_block(dtype, M, D, Hd):
     t = I.generate_ffn(dtype, M, D, Hd, seed=9991 + M)
     d = {k: x.to("cuda", I.storage_torch_dtype(dtype)) for k, x in t.items()}

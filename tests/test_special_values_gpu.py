@@ -1,5 +1,6 @@
 """Infinities, NaN and the largest finite numbers in the products' epilogues, on every kernel that forms a forward product: the
-tiled one on operands as they are, on padded copies and with a split reduction, the few-row and the generic one.  A bias of
+256 x 256 tiles on operands as they are, on padded copies and with a split reduction, the 128 x 128 ones whole and split, the
+few-row and the generic one.  A bias of
 -infinity closes a unit and one of +infinity opens it, whatever the rest; the gradient of a unit whose pre-activation is NaN
 is zero; a row of the feed-forward block overflows to infinity where its exact value does."""
 import numpy as np
@@ -11,9 +12,12 @@ from paper_2509_14279_amd import api, inputs as I
 pytestmark = pytest.mark.gpu
 
 BIG = 3.4e38          # above the largest bf16 number: it rounds to infinity there, in fp32 it is finite
-# tiled; tiled, ragged rows; from transposed weights; padded, X as it is / as a copy; split; few rows; generic
+# 128 x 128 tiles; from transposed weights; 128 x 128, two of them split; few rows
 SHAPES = [(4608, 256, 768), (4700, 256, 768), (16384, 128, 256), (4500, 384, 1100), (4097, 771, 1100), (512, 4096, 2048),
           (500, 4096, 2000), (32, 128, 256), (200, 136, 264), (127, 33, 1030)]
+# 256 x 256 tiles: as they are; ragged rows; padded, X as it is / as a copy; split, ragged rows, padded; and the generic kernel
+SHAPES += [(11008, 128, 512), (8425, 768, 1536), (8760, 128, 5167), (4529, 157, 6144), (1280, 3072, 3584), (1337, 3072, 3328),
+           (2062, 2651, 2073), (4864, 151, 70)]
 
 
 def data(M, K, N):
@@ -74,8 +78,13 @@ def test_a_nan_pre_activation_passes_no_gradient(M, K, N):
     assert torch.isfinite(dX.float()).all() and torch.isfinite(db).all()
 
 
-# gate and up products on padded copies (H % 128 != 0; D as it is, D through a copy of X), fused, on few rows, separate
-@pytest.mark.parametrize("M,D,H", [(4500, 384, 1100), (4097, 771, 1003), (4608, 256, 640), (16, 256, 264), (150, 100, 130)])
+# gate, up and down products in 128 x 128 tiles; on few rows; on padded copies (D as it is, D through a copy of X, down product
+# split); on 256 x 256 tiles, the down product whole, split and in 128 x 128 tiles
+FFN = [(4500, 384, 1100), (4097, 771, 1003), (4608, 256, 640), (16, 256, 264), (150, 100, 130),
+       (5827, 672, 1144), (4526, 1077, 1120), (2037, 1039, 3834), (5832, 1536, 1024), (1540, 2560, 3840), (3383, 512, 1280)]
+
+
+@pytest.mark.parametrize("M,D,H", FFN)
 def test_an_infinite_row_of_the_feed_forward_block(M, D, H):
     print(f"[special] ffn {M}x{D}x{H}", flush=True)
     t = I.generate_ffn("bf16", M, D, H, seed=9950 + M)
