@@ -72,9 +72,10 @@ FDL_API const char* fdl_status_string(fdl_status s);
  * problem (the larger of the two, so one buffer serves both).  Returns 0 for
  * an invalid dtype or shape.  Host-only: touches no device.
  * Part of it may be room for the partial sums of split reductions (at most
- * 64 MB for the forward product, for each fp32 gradient and for both bf16
- * ones), which some shapes want and larger batches do not: the size can fall
- * as M grows.  A buffer that lacks only this part, say one sized for a larger
+ * 64 MB for the forward product and for each fp32 gradient; for the bf16
+ * gradients 4 bytes per element of dX or dW and part, which is several times
+ * dW where a long reduction is split or has rows left over), which some shapes
+ * want and larger batches do not: the size can fall as M grows.  A buffer that lacks only this part, say one sized for a larger
  * batch, is accepted, and the call runs without splitting (slower, results
  * equal to within the order of the sums); forward products also run without
  * the copies of operands that some shapes want.  A smaller one is rejected with
@@ -227,7 +228,9 @@ FDL_API fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, int
  * each phase of a call with HIP events on the call's own stream).
  *
  * Phases: forward = F1 (GEMM + fused epilogue), FS (nothing: the statistics are F2's), F2 (statistics + normalise);
- *         backward = B1 (row pass), B2 (column reduce), B3 (dX GEMM), B4 (dW GEMM).
+ *         backward = B1 (row pass), B2 (column reduce), B3 (dX GEMM), B4 (dW GEMM).  What shares a launch is counted
+ *         where that launch is: dW to B3 where one launch forms both gradients, the column sums to it too where they ride
+ *         behind them, or to B4 where the launch that adds up split reductions ends them; B2 and B4 are then empty.
  * `events` is a HOST array of 2*FDL_PHASE_COUNT hipEvent_t handles created by the caller (or NULL to switch
  * the instrumentation off, the default).  While set, fdl_forward / fdl_backward record events[2*p] just
  * before and events[2*p+1] just after the launches of phase p on the call's stream.  The array is copied;

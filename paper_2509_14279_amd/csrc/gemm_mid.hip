@@ -9,9 +9,9 @@
 //   rows, the next 32 of each (a wave's blocks a = 0, 1 then hold both products of the same columns); 64 output columns per tile
 //
 // Bound: with one 128 x 128 tile per half of a compute unit, the operands' way from the L2 (a slice of 64 is 32 KB per tile for
-// 2 MFLOP) and the latency of each slice's trip; the matrix cores are half idle.  What it has over the 256 x 256 tiles is four
-// times as many of them - 3001 x 1537 has 72 of those on 256 compute units, 312 of these on 512 places - and no copies: rows are
-// read as they lie.
+// 2 MFLOP) and the latency of each slice's trip; the matrix cores are half idle.  What it has over the 256 x 256 tiles is up to
+// four times as many of them - 3001 x 1537 has 84 of those on 256 compute units, 312 of these on 512 places - and no copies: rows
+// are read as they lie.
 // Measured, us, whole calls, before / with this kernel: forward product 2048 x 2048 x 2048 43 / 21 (800 TFLOP/s), 512 x 4096 x 4096
 // 41 / 23, 3001 x 771 x 1537 39 / 23; both gradients of 1000 x 300 x 700 49 / 11, 16384 x 256 x 1024 56 / 28, 3001 x 771 x 1537
 // 60 / 34; large ones stay with the other tiles: 8192 x 1024 x 4096 forward 63 to 76 here, gradients 120 to 140.
