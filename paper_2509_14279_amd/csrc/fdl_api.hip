@@ -247,11 +247,10 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may
   }
   if (dt == kBF16 && mid_supported(Mp, K, N)) {
     int sa = 1, sb = 1;
-    // 7 % for the estimates' spread, 20 % for large products, where power and the dies' caches decide (12 of the 1300 shapes were
-    // slower than before by more than 2 % with 7 % throughout, now 4).  All backward passes of those shapes: 1.65 times as fast as
-    // before, 2.3 times around 2^27 products.
-    const double margin = (double)Mp * (double)K * (double)N >= 0x1p33 ? 1.2 : 1.07;
-    if (margin * mid_grads_cost(Mp, K, N, mid_room(room, sums), &sa, &sb) < grads_cost(q)) {
+    // 7 % for the estimates' spread.  2600 shapes where either could be the faster, whole backward passes: 4 are more than 2 % slower
+    // than in 256 x 256 tiles (6 % at most; 29 without the term for dZ, with 20 % from 2^33 products on: 11 %), the kernels picked take
+    // 1.01 times the faster ones' time on average.
+    if (1.07 * mid_grads_cost(Mp, K, N, mid_room(room, sums), &sa, &sb) < grads_cost(q)) {
       q.mid = 1; q.blocked = 0; q.split_a = sa; q.split_b = q.parts_b = sb;
       const size_t na = align256(sa > 1 ? (size_t)sa * partial_stride(M * K) * 4 : 0), nb = align256(sb > 1 ? (size_t)sb * partial_stride(N * K) * 4 : 0);
       if (na + nb > sums) { q.off_dxpart = *off; *off += na + nb; }      // (the copies of padded mode stay where they are)

@@ -535,6 +535,12 @@ double mid_grads_cost(int64_t M, int64_t K, int64_t N, size_t room, int* sa_out,
       if ((sa == 1 && sb == 1) || cost < best) { best = cost; *sa_out = sa; *sb_out = sb; }
     }
   }
+  // One to four columns of tiles (256 x 256 ones: one or two) read all of dZ each, and little else is read: of 2600 shapes those took 6 -
+  // 10 us more than the above, by dZ's size up to 3 x 10^7 elements and no more beyond.
+  if (K <= 512) {
+    const double dz = 0.45 * (double)M * (double)N / 1e6;
+    best += dz < 14.0 ? dz : 14.0;
+  }
   return best;
 }
 

@@ -1612,13 +1612,16 @@ void launch_zero_cols_bf16(void* dZ, int64_t M, int64_t N, int64_t ldz, hipStrea
 
 bool b1_fused_supported(int dt, int64_t N, int64_t ldz) { return fused_threads(dt, N, ldz) != 0; }
 
+int b1_fused_slots(int dt, int64_t N, int64_t ldz) { return b1_slots(dt, N, ldz); }
+
 // Row groups (= workgroups) of the fused kernel.  Each group leaves 3 N partial column sums behind and pays for its start
 // (the table, the first rows), so fewer groups mean less traffic for the phase and for the column reduction after it;
 // more of them hide the chain of each row's reductions behind one another.  Measured with the column reduction, us, for
 // 256 / 512 / 1024 groups: bf16 3001 x 1537: 26.2 / 23.3 / 28.1; 32768 x 1024: 103 / 72.8 / 65.4; 16384 x 4096: 85.3 / 82.0
-// / 88.9; 65536 x 8192: 578 / 569 / 578; 1000 x 5000: 22.3 / 28.5; fp32, whose fp64 arithmetic fills the vector units
-// with one workgroup of 512 threads per compute unit: 3001 x 1537 46.5 / 50.6, 8192 x 4096 191 / 200.
-int b1_fused_slots(int dt, int64_t N, int64_t ldz) { return b1_slots(dt, N, ldz); }
+// / 88.9; 65536 x 8192: 578 / 569 / 578; 1000 x 5000: 22.3 / 28.5.  fp32 rows of more than 1024 columns, whose fp64 arithmetic
+// fills the vector units with one workgroup of 512 threads (four columns each, eight above 2048) per compute unit: whole
+// backward passes with K = 8, 256 / 512 groups, 3001 x 1537 62.3 / 66.4, 8192 x 4096 243 / 255, 500 x 2292 40.2 / 46.6; 256 are
+// faster on all of 65 shapes, by 1 % (30000 rows) to 17 % (a thousand and fewer).
 int b1_fused_groups(int dt, int64_t M, int64_t N) {
   const int nt = fused_threads(dt, N, N);
   if (dt == kF32 && nt > 256) return 256;

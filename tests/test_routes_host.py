@@ -13,7 +13,7 @@ from routes import route
 # N, and the pitch of dZ where both gradients run in 128 x 128 tiles: whole lines of 64 elements where those add at most an eighth
 # (57: not padded, no room for more)
 @pytest.mark.parametrize("op", ["block", "relu"])
-@pytest.mark.parametrize("M,K,N,pitch", [(3001, 771, 1537, 1600), (20067, 473, 824, 832), (1024, 777, 513, 576), (1025, 776, 520, 576),
+@pytest.mark.parametrize("M,K,N,pitch", [(3001, 771, 1537, 1600), (20067, 773, 824, 832), (1024, 777, 513, 576), (1025, 776, 520, 576),
                                          (2500, 1000, 300, 320), (9000, 100, 264, 264), (3000, 200, 71, 72), (2000, 500, 57, 57),
                                          (4097, 130, 8, 8), (1024, 512, 640, 640)])
 def test_pitch_of_the_gradient(op, M, K, N, pitch):
@@ -53,7 +53,14 @@ def test_gradients(op):
     large = {route(op, "bf16", *s)[1] for s in test_padded_shapes_gpu.LARGE}
     assert large >= {"pair padded-x", "pair padded extra", "pair extra", "tiled and tiled padded-x"}
     mid = {route(op, "bf16", *s)[1] for s in test_mid_tiles_gpu.SHAPES}
-    assert mid == {"mid", "mid dx-split", "mid dw-split", "mid dx-split dw-split"}
+    assert mid >= {"mid", "mid dx-split", "mid dw-split", "mid dx-split dw-split"}
+
+
+# dZ read by one to four columns of tiles: 128 x 128 ones were up to 11 % slower here (whole backward passes, 104 to 115, 105 to 116,
+# 139 to 152, 134 to 147 us)
+@pytest.mark.parametrize("M,K,N", [(8857, 216, 3592), (7336, 152, 4488), (6656, 381, 5808), (35638, 248, 1128)])
+def test_gradients_of_few_columns_and_a_large_dz(M, K, N):
+    assert not route("block", "bf16", M, K, N)[1].startswith("mid")
 
 
 def test_blocked_gradients():

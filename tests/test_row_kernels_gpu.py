@@ -109,7 +109,7 @@ def test_statistics_of_nearly_constant_rows(M, K, N):
 
 
 # (a wavefront per row, two; 6656 and 11520 rows leave wavefronts without a pair of rows on the last round)
-BLOCKED = [(2560, 2560, 512), (5120, 1024, 1024), (8192, 3584, 512), (6656, 1024, 512), (11520, 512, 768)]
+BLOCKED = [(2560, 2560, 512), (5120, 1024, 1024), (12288, 3584, 512), (6656, 1024, 512), (11520, 512, 768)]
 
 
 @pytest.mark.parametrize("M,K,N", BLOCKED)
