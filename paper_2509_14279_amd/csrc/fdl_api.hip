@@ -110,7 +110,7 @@ bool ensure_dynamic_lds(const void* kernel, int bytes, OnceFlags* flags) {
 
 static void tight_pitch(GradPlan* q);
 
-bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
+bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p, bool forward_only) {
   if (dt != kF32 && dt != kBF16) return false;
   if (!shape_ok(M, K, N)) return false;
   const size_t cs = dt == kF32 ? 8 : 4;   // arithmetic element
@@ -167,6 +167,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p) {
   q.static_need = (limit_fast && N % 8 == 0 && N <= 8192 ? 0 : align256((size_t)((N + limit_tile - 1) / limit_tile) * Mp * 8)) +
                   align256(copies ? fast_padded_tail_bytes(K) : (limit_fast ? fast_f1_tail_bytes(M, K) : 0)) +
                   align256(copies ? (size_t)Np * Kp * 2 : 0) + align256(copies ? (size_t)Np * 4 : 0);
+  if (forward_only) { *p = q; return true; }
 
   // ---- backward
   // dZ in 32 x 32 blocks where only the fused row kernel writes it and only the tuned kernels read it; the vector path of
@@ -662,7 +663,7 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
 namespace {
 struct InferencePlan { Plan p; size_t off_mean, off_rstd, bytes; };
 bool make_inference_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, InferencePlan* q) {
-  if (!make_plan(dt, M, K, N, room, &q->p)) return false;
+  if (!make_plan(dt, M, K, N, room, &q->p, /*forward_only=*/true)) return false;
   const int64_t Mp = M > 0 ? M : 1;
   size_t off = q->p.fwd_bytes;
   q->off_mean = off; off += align256((size_t)Mp * 4);

@@ -82,8 +82,8 @@ struct Plan {
 // need none then form them).
 enum class Room { kAll, kTight, kNoSplit, kNoCopies };
 void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may_block, size_t* off, GradPlan* p);
-// Returns false when the shape or dtype is not supported.
-bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p);
+// Returns false when the shape or dtype is not supported.  forward_only: the backward pass is not planned (bytes stays 0).
+bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p, bool forward_only = false);
 
 // ---- per-device facts and per-call failure notes --------------------------------------------------
 // Compute units and accelerator dies (each die has its own L2) of the calling thread's current device, queried from

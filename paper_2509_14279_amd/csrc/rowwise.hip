@@ -829,7 +829,7 @@ __global__ __launch_bounds__(NT) void row_wg_kernel(int64_t M, int64_t N, float 
 #pragma unroll
         for (int v = 0; v < V; v++) {
           raw[s][v] = v < nv[s] ? (float)(z[v] + (double)q.bias[col[s] + v]) : 0.0f;
-          if (v < nv[s]) q.Z[row * N + col[s] + v] = raw[s][v];
+          if (v < nv[s] && q.Z != Y) q.Z[row * N + col[s] + v] = raw[s][v];     // (inference keeps no Z: it would lie in Y)
         }
       }
       return;
