@@ -1461,9 +1461,12 @@ void launch_row_norm(int64_t M, int64_t N, float eps, const void* A, const float
   }
   if constexpr (sizeof(T) == 4) {
     const int64_t vectors = (N + V - 1) / V;
+    // (GELU with up to two vectors a thread: 94 registers, most of them constants, five workgroups of 256 on a compute unit; with eight
+    // of them in the grid forward passes of 80 shapes with 257 - 1024 columns were 2 - 4 % slower, 3630 x 64 x 913 31.1 to 30.3 us)
 #define FDL_ROW(NT, S)                                                                                              \
   do {                                                                                                              \
-    const int64_t cap = (int64_t)256 * (2048 / NT);   /* a full part's wavefronts; any number is correct */         \
+    /* a full part's wavefronts, or what fits beside one another; any number is correct */                          \
+    const int64_t cap = (int64_t)256 * (NT == 256 && S <= 2 && ACT == ACT_GELU ? 5 : 2048 / NT);                     \
     hipLaunchKernelGGL((row_wg_kernel<NT, S, ACT>), dim3((unsigned)(M < cap ? M : cap)), dim3(NT), 0, s, M, N, eps, \
                        (const T*)A, gamma, beta, (T*)Y, mean, rstd, F64Sums{});                                     \
     return;                                                                                                         \
