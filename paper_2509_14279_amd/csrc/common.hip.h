@@ -139,13 +139,14 @@ template <bool kPair> struct GaussTable {
 //           = Phi(-c) - phi(m) h (1 + (m^2 - 1) h^2 / 24 + (m^4 - 6 m^2 + 3) h^4 / 1920 + (m^6 - 15 m^4 + 45 m^2 - 15) h^6 / 322560),
 // the Taylor expansion about the middle (phi's even derivatives are Hermite polynomials times phi).  Beyond the last node, at
 // 13.25: exp, and the asymptotic series Phi(-a) = phi(a) / a (1 - 1/a^2 + 1 3 / a^4 - 1 3 5 / a^6 + ...), thirteen terms.
-// Largest relative error, here / 0.5 erfc(-z / sqrt 2) and exp(-z^2 / 2) / sqrt(2 pi) of a library: Phi(-a) 2.2e-16 / 6e-16 (a to
-// 1.5), 3e-15 (4.5), 1.1e-14 (9), 2.9e-14 (13.25), beyond 4.3e-16 / 1.7e-13 (the argument's rounding); phi 2.2e-16 / 2.5e-16,
-// beyond the same.
+// Largest relative error, here / 0.5 erfc(-z / sqrt 2) and exp(-z^2 / 2) / sqrt(2 pi) of a library: Phi(-a), a to 1.5 2.2e-16 /
+// 6e-16, to 4.5 2.0e-16 / 3e-15, to 9 2.7e-16 / 1.1e-14, to 13.25 8e-16 / 2.9e-14, beyond 4.4e-16 / 1.7e-13 (the argument's rounding);
+// phi 2.1e-16 / 2.5e-16, beyond 2.8e-16 / 2.5e-16.
 // The row kernels of fp32 storage are bound by this arithmetic: some 35 fp64 instructions (45 with phi) and one branch a vector,
-// where the library's erfc and exp go through several ranges per wavefront.  3001 x 1537, us: normalisation 26 -> 19.5, backward row
+// where the library's erfc and exp go through several ranges per wavefront.  3001 x 1537, us: normalisation 26 -> 18, backward row
 // pass 42 -> 28 (with one polynomial of degree 20 for the whole axis and exp's, no table: 20 and 36).  Six terms and two, zero
-// beyond the table: 19 and 27, whole fp32 steps 1 % faster, but 4e-13 from Phi and phi at 13 and no gradient at all beyond.
+// beyond the table: 4e-13 from Phi and phi at 13 and no gradient at all beyond, for whole fp32 steps 1 % faster and forward passes of
+// short reductions 2 - 3 % (257 - 1024 columns, where 64 instead of 94 registers let eight workgroups share a compute unit, 2 - 8 %).
 namespace ctmath {
 // Sums and products of two doubles each (hi + lo), where the table's entries are to be correctly rounded
 struct Two { double hi, lo; };
