@@ -15,8 +15,13 @@
 //       (dZ is the library's own buffer and may be stored in 32 x 32 blocks, which suits both of its readers: Loader)
 // (the linear layer's forward, grad-input and grad-weight products of the paper's linear tasks.)
 //
-// Workgroup: 256 threads = 4 waves (2 x 2), one per SIMD; block tile 256 x 256, wave tile 128 x 128 as 4 x 4
-// v_mfma_f32_32x32x16_bf16 blocks (256 fp32 accumulators per lane, held in AGPRs).  The reduction runs in slices of
+// Workgroup: 256 threads = 4 waves (2 x 2), one per SIMD; block tile 256 x 256, wave tile 128 x 128 as 8 x 8
+// v_mfma_f32_16x16x32_bf16 blocks (256 fp32 accumulators per lane, held in AGPRs).  Under matrix load the part's power limit
+// sets its clock, and these MFMAs take less energy per product than v_mfma_f32_32x32x16_bf16, whose accumulators pass through
+// the pipe once per 16 products instead of 32: a loop of nothing but MFMAs on normal random numbers 2010 against 1750 TFLOP/s on one
+// machine, 2137 against 1866 on another (on zeros 2440 both).  Whole calls, us, 32 x 32 / 16 x 16 blocks: step 65536 x 2048 x 8192
+// 5629 / 5440, 4096 x 4096 x 16384 1431 / 1365, 8192 x 1024 x 4096 266 / 258, Linear+ReLU 10000 x 1000 x 3000 291 / 276,
+// feed-forward 16384 x 4096 x 11008 3319 / 3168.  The reduction runs in slices of
 // BK through NS LDS stages (BK x NS = 64 x 2 or 32 x 4, 128 KB either way) filled by direct global->LDS loads
 // (16 bytes per lane, no staging registers); the loads of slice kt+NS are issued as soon as slice kt's stage is
 // released and stay in flight for NS-1 slice times while the MFMAs of the other stages run.  Workgroups are
@@ -31,12 +36,12 @@
 // conflict probe - and an 8-byte read in two groups of 32 consecutive lanes; a group completes in one cycle when
 // its lanes touch 64 distinct banks.
 //   r-contiguous operand: [256 rows][BK/8 chunks of 16 B]; BK = 64 (rows of 128 B, two rows per bank round): chunk c
-//       of row w in slot c ^ ((w >> 1) & 7); BK = 32 (rows of 64 B, four rows per bank round): slot c ^ ((w >> 2) & 3);
-//       fragments are read with ds_read_b128 (8 consecutive r of the lane's row): the 16 rows of a lane group then
-//       cover all 64 banks.
-//   r-major operand:      [BK r-rows][32 chunks of 16 B]; chunk c of r-row w sits in slot c ^ ((w & 3) << 2);
+//       of row w in slot c ^ ((w >> 1) & 7); BK = 32 (rows of 64 B, four rows per bank round): slot c ^ g((w >> 2) & 3) with
+//       g = 0, 2, 3, 1; fragments are read with ds_read_b128 (lane l: 8 consecutive r, chunk l/16 of row l%16): a lane group has
+//       rows 0-3 and 12-15 of one chunk and rows 4-11 of its neighbour, or the reverse, which then cover all 64 banks.
+//   r-major operand:      [BK r-rows][32 chunks of 16 B]; chunk c of r-row w sits in slot c ^ ((w & 3) << 2) ^ ((w >> 2) & 2);
 //       fragments are read with the transposing ds_read_b64_tr_b16 (4 consecutive r for the lane's column): the 32
-//       lanes of a group read 64 bytes from each of 4 r-rows, which the swizzle spreads over the 256-byte bank round.
+//       lanes of a group read 32 bytes from each of 8 r-rows, which the swizzle spreads over the 256-byte bank round.
 #include "common.hip.h"
 #include "internal.h"
 
@@ -54,7 +59,7 @@ constexpr int kLdsBytes = kLdsStages + 4 * 8192; // + 8 KB per wave for the outp
 
 // Geometry of one pipeline configuration: reduction slices of BK, NS stages.
 template <int BK> struct Geo {
-  static constexpr int kSub = BK / 16;                    // MFMA sub-slices per slice
+  static constexpr int kSub = BK / 32;                    // MFMA sub-slices per slice
   static constexpr int kOperandBytes = kTile * BK * 2;    // one operand tile of one slice
   static constexpr int kStageBytes = 2 * kOperandBytes;   // P tile then Q tile
   static constexpr int kDpw = BK / 8;                     // direct-load instructions per operand, wave and slice
@@ -112,6 +117,10 @@ __device__ __forceinline__ void dma4(uint32_t voff, const void* sbase, uint32_t 
 // wait until at most N vector-memory operations of this wave are outstanding (loads complete in order)
 template <int N> __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
+// where chunks of 16 bytes sit in the LDS rows: chunk c in slot c ^ swizzle(row) (see the top of the file)
+__device__ __forceinline__ int rm_swizzle(int w) { return ((w & 3) << 2) | ((w >> 2) & 2); }
+__device__ __forceinline__ int rc32_swizzle(int w) { return (((w >> 2) ^ (w >> 3)) & 1) << 1 | ((w >> 3) & 1); }
+
 template <bool RM, int BK> struct Loader {
   // voff[q]: per-lane byte offset of instruction q (constant over the reduction loop).  kDpw instructions per wave
   // fill this wave's quarter of the operand tile; the only per-slice scalar work is one base pointer.
@@ -124,23 +133,23 @@ template <bool RM, int BK> struct Loader {
   static constexpr int kDpw = Geo<BK>::kDpw;
   uint32_t voff[kDpw];
   int blocked;
-  __device__ __forceinline__ void init(int lane, int64_t ld, int blocked_operand = 0) {
+  __device__ __forceinline__ void init(int lane, int wave, int64_t ld, int blocked_operand = 0) {
     blocked = (BK == 32) ? blocked_operand : 0;
 #pragma unroll
     for (int q = 0; q < kDpw; q++) {
       if (BK == 32 && blocked && RM) {
         // r-row 2q + h of this wave's 8 (all in one block row), chunk c: block c / 4, 16-byte piece c % 4 of its row
         const int h = lane >> 5, slot = lane & 31;
-        const int c = slot ^ (((2 * q + h) & 3) << 2);
+        const int c = slot ^ rm_swizzle(wave * (BK / 4) + 2 * q + h);
         voff[q] = (uint32_t)((c >> 2) * 2048 + (2 * q + h) * 64 + (c & 3) * 16);
       } else if (BK == 32 && blocked) {
         // row 16q + w of this wave's 64 (two block rows), piece slot ^ swizzle of its 64 bytes in the block
         const int w = lane >> 2, slot = lane & 3, rr = 16 * q + w;
-        voff[q] = (uint32_t)((int64_t)(rr >> 5) * (ld >> 5) * 2048 + (rr & 31) * 64 + ((slot ^ ((w >> 2) & 3)) * 16));
+        voff[q] = (uint32_t)((int64_t)(rr >> 5) * (ld >> 5) * 2048 + (rr & 31) * 64 + ((slot ^ rc32_swizzle(w)) * 16));
       } else if (RM) {
         // instruction q covers r-rows 2q, 2q+1 of this wave's BK/4; lane: r-row 2q + h, h = lane/32, slot lane%32
         const int h = lane >> 5, slot = lane & 31;
-        const int c = slot ^ (((2 * q + h) & 3) << 2);
+        const int c = slot ^ rm_swizzle(wave * (BK / 4) + 2 * q + h);
         voff[q] = (uint32_t)((int64_t)(2 * q + h) * ld * 2 + c * 16);
       } else if (BK == 64) {
         // instruction q covers rows 8q..8q+7 of this wave's 64; lane: row 8q + w, w = lane/8, slot lane%8
@@ -149,7 +158,7 @@ template <bool RM, int BK> struct Loader {
       } else {
         // BK = 32: instruction q covers rows 16q..16q+15 of this wave's 64; lane: row 16q + w, w = lane/4, slot lane%4
         const int w = lane >> 2, slot = lane & 3;
-        voff[q] = (uint32_t)((int64_t)(16 * q + w) * ld * 2 + ((slot ^ ((w >> 2) & 3)) * 16));
+        voff[q] = (uint32_t)((int64_t)(16 * q + w) * ld * 2 + ((slot ^ rc32_swizzle(w)) * 16));
       }
     }
   }
@@ -183,35 +192,31 @@ template <bool RM, int BK> struct Loader {
 
 template <bool RM, int BK> struct Frags {
   // LDS byte offsets of this lane's fragment reads inside an operand tile.
-  //  r-contiguous: off[kk] for the sub-slices; block a adds a * 32 rows.
-  //  r-major:      off[a] for the 4 blocks; sub-slice kk and half t add (kk*16 + 4t)*512.
-  uint32_t off[4];
+  //  r-contiguous: off[kk] for the sub-slices; block a adds a * 16 rows.
+  //  r-major:      off[a] for the 8 blocks; sub-slice kk and half t add (kk*32 + 4t)*512.
+  uint32_t off[8];
   __device__ __forceinline__ void init(int lane, int w /* wave coordinate along this operand */) {
     if (RM) {
       const int G = lane >> 4, p = lane & 15;
-      const int r = 8 * (G >> 1) + (p >> 2);
+      const int r = 8 * G + (p >> 2);
 #pragma unroll
-      for (int a = 0; a < 4; a++) {
-        const int c = w * 16 + a * 4 + 2 * (G & 1) + ((p & 3) >> 1);
-        off[a] = (uint32_t)(r * 512 + ((c ^ ((p >> 2) << 2)) * 16) + (p & 1) * 8);
+      for (int a = 0; a < 8; a++) {
+        const int c = w * 16 + a * 2 + ((p & 3) >> 1);
+        off[a] = (uint32_t)(r * 512 + ((c ^ rm_swizzle(r)) * 16) + (p & 1) * 8);
       }
-    } else if (BK == 64) {
-      // rows of 128 B, chunk c of row r in slot c ^ ((r >> 1) & 7)
-      const int row = w * 128 + (lane & 31);
-      const int t0 = (lane >> 5) ^ ((lane >> 1) & 7);
-#pragma unroll
-      for (int kk = 0; kk < 4; kk++) off[kk] = (uint32_t)(row * 128 + (((kk << 1) ^ t0) << 4));
     } else {
-      // rows of 64 B, chunk c of row r in slot c ^ ((r >> 2) & 3)
-      const int row = w * 128 + (lane & 31);
-      const int sw = (lane >> 2) & 3;
+      const int row = w * 128 + (lane & 15), c = lane >> 4;
+      if (BK == 64) {
 #pragma unroll
-      for (int kk = 0; kk < 4; kk++) off[kk] = (uint32_t)(row * 64 + (((((kk & 1) << 1) | (lane >> 5)) ^ sw) << 4));
+        for (int kk = 0; kk < 2; kk++) off[kk] = (uint32_t)(row * 128 + (((kk * 4 + c) ^ ((row >> 1) & 7)) << 4));
+      } else {
+        off[0] = (uint32_t)(row * 64 + ((c ^ rc32_swizzle(row)) << 4));
+      }
     }
   }
   __device__ __forceinline__ bf16x8 load(const lds_char* tile, int a, int kk) const {
     if (RM) {
-      const lds_char* p0 = tile + off[a] + (kk * 16) * 512;
+      const lds_char* p0 = tile + off[a] + (kk * 32) * 512;
       const short4_ lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)p0);
       const short4_ hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(p0 + 4 * 512));
       typedef __attribute__((ext_vector_type(8))) short short8_;
@@ -220,7 +225,7 @@ template <bool RM, int BK> struct Frags {
       return __builtin_bit_cast(bf16x8, v);
     } else {
       typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
-      return *(const lds_bf16x8*)(tile + off[kk] + a * (32 * BK * 2));
+      return *(const lds_bf16x8*)(tile + off[kk] + a * (16 * BK * 2));
     }
   }
 };
@@ -256,7 +261,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   static_assert(!CRAG || RAG, "ragged columns come with the ragged-row checks");
   typedef Geo<BK> G;
   static_assert(NS * G::kStageBytes == kLdsStages, "stages must fill 128 KB");
-  static_assert((NS == 2 || NS == 4) && (G::kSub & 1) == 0, "2 or 4 stages, even number of sub-slices");
+  static_assert((NS == 2 || NS == 4) && ((NS * G::kSub) & 1) == 0, "2 or 4 stages, an even number of sub-slices in a round");
   lds_char* lds = (lds_char*)smem;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   const int lane = threadIdx.x & 63;
@@ -291,7 +296,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   auto init_offsets = [&]() {
     int lt = lane;
     asm volatile("" : "+v"(lt));
-    lp.init(lt, p.ldp); lq.init(lt, p.ldq, p.qblocked);
+    lp.init(lt, wave, p.ldp); lq.init(lt, wave, p.ldq, p.qblocked);
     fp.init(lt, wi); fq.init(lt, wj);
   };
   init_offsets();   // for the initial fill below; every tile recomputes them
@@ -332,35 +337,40 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   const bf16_t* pfetch = pcur + (NS - 1) * pstep;
   const bf16_t* qfetch = qcur + (NS - 1) * qstep;
   int fidx = NS - 1;
+  constexpr bool kBias = EPI == EPI_BIAS || EPI == EPI_RELU || EPI == EPI_MASK;
+  // The wave's 128 bias values go to the second half of its staging area by two direct loads, a tile ahead: no register and no
+  // compiler-inserted wait is involved.
+  const uint32_t wbias = (uint32_t)(kLdsStages + wave * 8192 + 4096);
+  auto fetch_bias = [&](int i0) {
+    int lb = lane;
+    asm volatile("" : "+v"(lb));
+    const float* bsrc = p.bias + i0 + wi * 128;
+    dma4<0>((uint32_t)lb * 4u, bsrc, lds0 + wbias);
+    dma4<256>((uint32_t)lb * 4u, bsrc + 64, lds0 + wbias);
+  };
+  if (kBias) fetch_bias(tc.i0);
   wait_dma<0>();
   __syncthreads();
 
-  // Fragments are double-buffered in registers: while the 16 MFMAs of a sub-slice run, the 8 fragment reads of the
-  // next sub-slice are issued between them.  The last sub-slice's MFMAs are issued after the barrier that
+  // Fragments are double-buffered in registers: while the 64 MFMAs of a sub-slice run, the 16 fragment reads of the
+  // next sub-slice (of 32) are issued between them.  The last sub-slice's MFMAs are issued after the barrier that
   // publishes the next stage, behind the first fragment reads of that stage, so the matrix pipe has work while
   // those reads are in flight.
-  bf16x8 pf[2][4], qf[2][4];
-
-  const int half = lane >> 5, l32 = lane & 31;
+  bf16x8 pf[2][8], qf[2][8];
   typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-
-  // Forward: the bias enters through the matrix pipe as one extra reduction step after the last slice,
-  // acc += Pb Qb^T with Pb[i][0..2] = the three bf16 pieces of bias[i] (hi + mid + lo = the fp32 value exactly:
-  // 3 x 8 significant bits) and Qb[j][0..2] = 1: sixteen MFMAs per tile and no vector arithmetic in the epilogue.
-  // A lane needs the bias of one column per block a (only lanes 0..31 carry k = 0..7).  The wave's 128 bias
-  // values are fetched at the top of the tile by two direct loads into its output staging area, which is idle
-  // until the epilogue: like every direct load they are older than the slice loads issued after them, so the main
-  // loop's own waits cover them, and no register or compiler-inserted wait is involved.
-  constexpr bool kBias = EPI == EPI_BIAS || EPI == EPI_RELU || EPI == EPI_MASK;
+  typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
   for (;;) {
     // slice 0 of this tile has landed in stage 0 (initial fill, or prefetched during the previous tile and
     // published by its last barrier): first fragments
     init_offsets();
 #pragma unroll
-    for (int a = 0; a < 4; a++) pf[0][a] = fp.load(lds, a, 0);
+    for (int n = 0; n < 8; n++) {
+      if (n == 0) pf[0][0] = fp.load(lds, 0, 0);
+      qf[0][n] = fq.load(lds + G::kOperandBytes, n, 0);
+    }
 #pragma unroll
-    for (int b = 0; b < 4; b++) qf[0][b] = fq.load(lds + G::kOperandBytes, b, 0);
+    for (int a = 1; a < 8; a++) pf[0][a] = fp.load(lds, a, 0);
 
     // the tile after this one (its first NS slices are fetched during this tile's last NS slices); a workgroup
     // without a next tile fetches its own last slice again instead (never read)
@@ -372,22 +382,21 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     const bf16_t* qwrap = has_next ? q_origin(tn.j0) : q_origin(tc.j0) + (int64_t)(nkt - 1) * qstep;
     const int fwrap = has_next ? 0 : nkt - 1;
 
-    if (kBias) {
-      int lb = lane;
-      asm volatile("" : "+v"(lb));
-      const float* bsrc = p.bias + tc.i0 + wi * 128;
-      const uint32_t wst = lds0 + (uint32_t)kLdsStages + (uint32_t)wave * 8192u;
-      dma4<0>((uint32_t)lb * 4u, bsrc, wst);
-      dma4<256>((uint32_t)lb * 4u, bsrc + 64, wst);
-    }
-
-    // The accumulators are never cleared: the first sub-slice of a tile's slice 0 runs its MFMAs with a zero
-    // addend (slice 0 has its own copy of the slice code for that; the other slices, at least NS-1 of them -
-    // checked on the host - run in the loop).
-    f32x16 acc[4][4];
-    f32x16 zero16;
+    // The accumulators are never cleared: the first sub-slice of a tile's slice 0 (which has its own copy of the slice code for
+    // that; the other slices, at least NS-1 of them - checked on the host - run in the loop) adds its products to the bias, of
+    // which a lane needs the same four values for all blocks of a column, or to zero.
+    f32x4 acc[8][8], start[8];
 #pragma unroll
-    for (int r = 0; r < 16; r++) zero16[r] = 0.0f;
+    for (int a = 0; a < 8; a++) {
+      if (kBias) {
+        int lb = lane;
+        asm volatile("" : "+v"(lb));
+        start[a] = *(const lds_f32x4*)(lds + wbias + (lb >> 4) * 16 + a * 64);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++) start[a][r] = 0.0f;
+      }
+    }
 
     // One slice; the LDS stage it lives in is a compile-time constant (the number of slices per tile is a multiple
     // of NS - checked on the host - so a tile's slice 0 is always in stage 0 and the slice loop is unrolled NS
@@ -411,7 +420,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
       // neither the LDS reads nor the global loads keep the matrix pipe waiting for long.
 #pragma unroll
       for (int kk = 0; kk < G::kSub; kk++) {
-        const int use = kk & 1, fill = use ^ 1;
+        const int use = (cur * G::kSub + kk) & 1, fill = use ^ 1;
         const bool lastsub = kk == G::kSub - 1;
         if (lastsub) {
           // slice kt+1 must have landed; the direct loads of the NS-2 slices after it may stay in flight
@@ -423,12 +432,12 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         const lds_char* rq = lastsub ? nq_ : tq;
         const int rk = lastsub ? 0 : kk + 1;
 #pragma unroll
-        for (int t = 0; t < 16; t++) {
-          const int a = t >> 2, b = t & 3;
+        for (int t = 0; t < 64; t++) {
+          const int a = t >> 3, b = t & 7;
           if (kFirst && kk == 0)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[use][a], qf[use][b], zero16, 0, 0, 0);
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf[use][a], qf[use][b], start[a], 0, 0, 0);
           else
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[use][a], qf[use][b], acc[a][b], 0, 0, 0);
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf[use][a], qf[use][b], acc[a][b], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
           // next slice of the fetch stream: the following one of this tile, else (pwrap, qwrap, fwrap) = slice 0
           // of the next tile or, without a next tile, this tile's last slice again, which is never read; spread
@@ -445,25 +454,25 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
             fidx = fidx + 1 == nkt ? fwrap : fidx + 1;
             __builtin_amdgcn_sched_barrier(0);
           }
+          // (this tile's bias is in registers since the first sub-slice; the waits of the round's NS - 1 other slices cover this)
+          if (kBias && kFirst && lastsub && t == 63) fetch_bias(tn.i0);
           const bf16_t* const pn = pfetch;
           const bf16_t* const qn = qfetch;
-          if ((t & 1) == 0) {
-            // read order: P0, Q0, Q1, Q2, Q3, P1, P2, P3 (the order in which the next sub-slice consumes them)
-            const int slot = t >> 1;
+          if (t % 3 == 0 && t < 48) {
+            // read order: P0, Q0 .. Q7, P1 .. P7 (the order in which the next sub-slice consumes them)
+            const int slot = t / 3;
             if (slot == 0) pf[fill][0] = fp.load(rp, 0, rk);
-            else if (slot <= 4) qf[fill][slot - 1] = fq.load(rq, slot - 1, rk);
-            else pf[fill][slot - 4] = fp.load(rp, slot - 4, rk);
+            else if (slot <= 8) qf[fill][slot - 1] = fq.load(rq, slot - 1, rk);
+            else pf[fill][slot - 8] = fp.load(rp, slot - 8, rk);
             __builtin_amdgcn_sched_barrier(0);
           }
           if (lastsub) {
-            if (G::kDpw == 8) {            // 16 direct loads: one behind every MFMA
-              if (t < 8) lp.issue_q(t, pn, own);
-              else lq.issue_q(t - 8, qn, own + G::kOperandBytes);
-              __builtin_amdgcn_sched_barrier(0);
-            } else if (t & 1) {            // 8 direct loads: one behind every other MFMA
-              const int d = t >> 1;
-              if (d < 4) lp.issue_q(d, pn, own);
-              else lq.issue_q(d - 4, qn, own + G::kOperandBytes);
+            // the direct loads, in the first half: one behind every second (BK = 64: 16 of them) or fourth MFMA (8)
+            constexpr int kEvery = G::kDpw == 8 ? 2 : 4;
+            if (t < 32 && t % kEvery == 1) {
+              const int d = t / kEvery;
+              if (d < G::kDpw) lp.issue_q(d, pn, own);
+              else lq.issue_q(d - G::kDpw, qn, own + G::kOperandBytes);
               __builtin_amdgcn_sched_barrier(0);
             }
           }
@@ -483,79 +492,50 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     // here: the next tile's slice 0 has landed in stage 0, its following slices are in flight
 
     // ---------------------------------------------------------------- epilogue of tile (tc.i0, tc.j0)
-    // Accumulator register r of block (a, b): i = a*32 + (r/4)*8 + (lane/32)*4 + r%4, j = b*32 + lane%32.  A lane's
-    // four adjacent values are only 8 bytes of an output row, so bf16 tiles leave through LDS: each wave owns 8 KB
-    // beyond the pipeline stages, writes one block row (32 output rows x 256 B) as [32 rows][32 units of 8 B] with
-    // unit u of row w in slot u ^ ((w & 15) << 1) (conflict-free both ways), reads it back 16 bytes per lane and
+    // Accumulator register r of block (a, b): i = a*16 + (lane/16)*4 + r, j = b*16 + lane%16.  A lane's
+    // four adjacent values are only 8 bytes of an output row, so bf16 tiles leave through LDS: each wave owns 4 KB
+    // beyond the pipeline stages, writes one block row (16 output rows x 256 B) as [16 rows][32 units of 8 B] with
+    // unit u of row w in slot u ^ (w << 1) (conflict-free both ways), reads it back 16 bytes per lane and
     // stores 256 contiguous bytes per row.
     // Every per-lane constant of the epilogue is derived here from a copy of the lane id the compiler cannot see
     // through: hoisted out of the tile loop they would be spilled around the main loop, and each reload in the
     // epilogue would wait for the output stores issued before it (vector memory operations retire in order).
-    if (kBias) {
-      bf16x8 ones, bfrag[4];
+    // (The accumulators get a fresh start with the register allocator too: without it, it parks a few of them in scratch
+    // memory across the epilogue.)
 #pragma unroll
-      for (int e = 0; e < 8; e++) ones[e] = (bf16_t)(e < 3 ? 1.0f : 0.0f);
+    for (int a = 0; a < 8; a++)
 #pragma unroll
-      for (int a = 0; a < 4; a++) {
-        typedef __attribute__((address_space(3))) float lds_float;
-        const float xb = *(const lds_float*)(lds + kLdsStages + wave * 8192 + (a * 32 + l32) * 4);
-        const float x = half == 0 ? xb : 0.0f;
-        // (an infinity has one piece; the largest finite numbers, which bf16 would round to one, take their leading bits)
-        const bool huge = __builtin_fabsf(x) >= 0x1.fep127f && __builtin_fabsf(x) < __builtin_inff();
-        const bf16_t hi = huge ? (bf16_t)__builtin_copysignf(0x1.fep127f, x) : (bf16_t)x;
-        const float r1 = __builtin_isinf(x) ? 0.0f : x - (float)hi;
-        const bf16_t mid = (bf16_t)r1;
-        const bf16_t lo = (bf16_t)(r1 - (float)mid);
-#pragma unroll
-        for (int e = 0; e < 8; e++) bfrag[a][e] = (bf16_t)0.0f;
-        bfrag[a][0] = hi; bfrag[a][1] = mid; bfrag[a][2] = lo;
-      }
-#pragma unroll
-      for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int b = 0; b < 4; b++) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag[a], ones, acc[a][b], 0, 0, 0);
-    }
-    if (!kBias) {
-      // give the register allocator a fresh start for the accumulators here, as the bias MFMAs do in the forward
-      // kernels (without it, it parks a few of them in scratch memory across the epilogue)
-#pragma unroll
-      for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int b = 0; b < 4; b++) asm volatile("" : "+a"(acc[a][b]));
-    }
+      for (int b = 0; b < 8; b++) asm volatile("" : "+a"(acc[a][b]));
     int le = lane;
     asm volatile("" : "+v"(le));
-    const int e_half = le >> 5, e_l32 = le & 31;
     const int i0 = tc.i0, j0 = tc.j0;
     lds_char* wtile = lds + kLdsStages + wave * 8192;
-    uint32_t woff[4][4];                         // LDS byte offset of the lane's 8-byte unit (a, g) in row lane%32
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-      for (int g = 0; g < 4; g++)
-        woff[a][g] = (uint32_t)(e_l32 * 256 + (((a * 8 + g * 2) ^ ((e_l32 & 15) << 1)) + e_half) * 8);
-    // read side: rows it*4 + lane/16 of the block row, 16-byte chunk lane%16 (slot chunk ^ (row & 15))
+    // e_m, e_rq: column group and row of four (accumulators: row and column group)
     const int e_m = le & 15, e_rq = le >> 4;
+    uint32_t woff[8];                            // LDS byte offset of the lane's 8-byte unit a in row lane%16
+#pragma unroll
+    for (int a = 0; a < 8; a++) woff[a] = (uint32_t)(e_m * 256 + (((a * 4 + e_rq) ^ (e_m << 1)) << 3));
+    // read side: rows it*4 + lane/16 of the block row, 16-byte chunk lane%16 (slot chunk ^ row)
     uint32_t roff[4];
 #pragma unroll
-    for (int c = 0; c < 4; c++) roff[c] = (uint32_t)((c * 4 + e_rq) * 256 + ((e_m ^ (c * 4 + e_rq)) << 4));
+    for (int it = 0; it < 4; it++) roff[it] = (uint32_t)((it * 4 + e_rq) * 256 + ((e_m ^ (it * 4 + e_rq)) << 4));
     const uint32_t svoff = (uint32_t)(e_rq * (int)p.ldc + e_m * 8) * 2u;   // byte offset of the lane inside 4 output rows
     typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
-    // EPI_MASK: the upstream gradient of a block row, fetched while the one before it leaves.  (Fetched where it is used, a tile
+    // EPI_MASK: the upstream gradient of a block row, fetched while the two before it leave.  (Fetched where it is used, a tile
     // made many trips to memory in a row.  Linear+ReLU backward, us, that / so: 10000 x 1000 x 3000 248 / 217, 20000 x 512 x 2048
     // 224 / 184, 16384 x 1000 x 3001 385 / 324, 65536 x 2048 x 8192 5388 / 5020.)  Rows past the end are the last
     // one again; a lane whose eight columns pass the end takes the last eight, moved to their place, with zeros behind.
-    u32x4 aux[2][8];
+    u32x4 aux[3][4];
     auto fetch_aux = [&](int b) {
       if (EPI != EPI_MASK) return;
       const int left = CRAG ? p.I - (i0 + wi * 128 + e_m * 8) : 8, early = left >= 8 ? 0 : 8 - left;
 #pragma unroll
-      for (int it = 0; it < 8; it++) {
-        int row = j0 + wj * 128 + b * 32 + it * 4 + e_rq;
+      for (int it = 0; it < 4; it++) {
+        int row = j0 + wj * 128 + b * 16 + it * 4 + e_rq;
         if (RAG) row = row < p.J ? row : p.J - 1;
         const bf16_t* ap = p.aux + (int64_t)row * p.I + (i0 + wi * 128 + e_m * 8 - early);
-        if (CRAG) aux[b & 1][it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(ap));
-        else aux[b & 1][it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ap));
+        if (CRAG) aux[b % 3][it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(ap));
+        else aux[b % 3][it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ap));
       }
     };
     auto place_aux = [&](int b) {
@@ -563,28 +543,28 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
       const int left = p.I - (i0 + wi * 128 + e_m * 8);
       if (left >= 8) return;
 #pragma unroll
-      for (int it = 0; it < 8; it++) {
-        const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, aux[b & 1][it]);
-        aux[b & 1][it] = __builtin_bit_cast(u32x4, left <= 0 ? (unsigned __int128)0 : x >> (16 * (8 - left)));
+      for (int it = 0; it < 4; it++) {
+        const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, aux[b % 3][it]);
+        aux[b % 3][it] = __builtin_bit_cast(u32x4, left <= 0 ? (unsigned __int128)0 : x >> (16 * (8 - left)));
       }
     };
-    // Block row b of the wave tile (32 output rows) leaves as soon as it is complete.
+    // Block row b of the wave tile (16 output rows) leaves as soon as it is complete.
     auto flush_rows = [&](int b) {
       place_aux(b);
       // wave-uniform base of row it*4 of the block row; the lane adds (lane/16) rows and 16 (lane%16) bytes
-      char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 32) * p.ldc + i0 + wi * 128);
+      char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 16) * p.ldc + i0 + wi * 128);
 #pragma unroll
-      for (int it = 0; it < 8; it++) {
-        const u32x4 v = *(const lds_u32x4*)(wtile + roff[it & 3] + (it >> 2) * 4096);
+      for (int it = 0; it < 4; it++) {
+        const u32x4 v = *(const lds_u32x4*)(wtile + roff[it]);
         u32x4* dst = reinterpret_cast<u32x4*>(cbase + (int64_t)(it * 4) * p.ldc * 2 + svoff);
         if (EPI == EPI_MASK && p.cblocked) {
           // row R0 + lane/16 (R0 a multiple of 4, so the four rows share a block row), columns col .. col + 7:
           // four rows x 64 bytes of each of the four blocks = 256 contiguous bytes per block
-          const int64_t R0 = j0 + wj * 128 + b * 32 + it * 4;
+          const int64_t R0 = j0 + wj * 128 + b * 16 + it * 4;
           const int col = i0 + wi * 128 + e_m * 8;
           dst = reinterpret_cast<u32x4*>(p.C + (((R0 >> 5) * (p.I >> 5) + (col >> 5)) << 10) + (((R0 & 31) + e_rq) << 5) + (col & 31));
         }
-        if (RAG && j0 + wj * 128 + b * 32 + it * 4 + e_rq >= p.J) continue;   // a row past the end
+        if (RAG && j0 + wj * 128 + b * 16 + it * 4 + e_rq >= p.J) continue;   // a row past the end
         const int cleft = CRAG ? p.I - (i0 + wi * 128 + e_m * 8) : 8;          // columns from this lane's first to the end
         if (CRAG && EPI != EPI_MASK) {
           if (cleft >= 8) {
@@ -600,7 +580,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         if (EPI == EPI_MASK) {
           // v: 8 pre-activations as bf16.  The upstream gradient passes where the pre-activation is positive (bits
           // 0x0001 .. 0x7f80: sign clear, magnitude non-zero, up to infinity) and is zero elsewhere, NaN included.
-          const u32x4 d = aux[b & 1][it];
+          const u32x4 d = aux[b % 3][it];
           u32x4 g;
 #pragma unroll
           for (int e = 0; e < 4; e++) {
@@ -618,31 +598,29 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
       }
     };
     if (EPI == EPI_GATE) {
-      // H = SiLU(gate) * up for this wave's 64 columns x 128 rows, one block row of 32 rows at a time through the
+      // H = SiLU(gate) * up for this wave's 64 columns x 128 rows, one block row of 16 rows at a time through the
       // staging area (units 0..15 of each 256-byte staging row), stored as 128-byte row segments
       const int h0 = (i0 >> 1) + wi * 64;
       const int g_m = le & 7, g_rq = le >> 3;      // read side: 16-byte chunk lane%8 of row it*8 + lane/8
 #pragma unroll
-      for (int b = 0; b < 4; b++) {
+      for (int b = 0; b < 8; b++) {
 #pragma unroll
-        for (int a = 0; a < 2; a++)
+        for (int a = 0; a < 4; a++) {
+          bf16x4 v;
 #pragma unroll
-          for (int g = 0; g < 4; g++) {
-            bf16x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              const float z = acc[a][b][g * 4 + e], u = acc[a + 2][b][g * 4 + e];
-              const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * z));
-              v[e] = (bf16_t)(z * sg * u);
-            }
-            *(lds_bf16x4*)(wtile + woff[a][g]) = v;
+          for (int e = 0; e < 4; e++) {
+            const float z = acc[a][b][e], u = acc[a + 4][b][e];
+            const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * z));
+            v[e] = (bf16_t)(z * sg * u);
           }
-        char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 32) * p.ldc + h0);
+          *(lds_bf16x4*)(wtile + woff[a]) = v;
+        }
+        char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 16) * p.ldc + h0);
 #pragma unroll
-        for (int it = 0; it < 4; it++) {
+        for (int it = 0; it < 2; it++) {
           const int row = it * 8 + g_rq;
-          u32x4 v = *(const lds_u32x4*)(wtile + row * 256 + ((g_m ^ (row & 15)) << 4));
-          if (RAG && j0 + wj * 128 + b * 32 + row >= p.J) continue;   // a row past the end
+          u32x4 v = *(const lds_u32x4*)(wtile + row * 256 + ((g_m ^ row) << 4));
+          if (RAG && j0 + wj * 128 + b * 16 + row >= p.J) continue;   // a row past the end
           if (CRAG && h0 + g_m * 8 + 8 > p.I) {
             // the surplus columns of a padded width are zeros (their sums are too, but not where X holds an infinity)
 #pragma unroll
@@ -651,7 +629,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
           }
           if (p.cblocked) {
             // blocked output (the down projection reads it best that way): row R of the matrix, columns col .. col + 7
-            const int64_t R = j0 + wj * 128 + b * 32 + row;
+            const int64_t R = j0 + wj * 128 + b * 16 + row;
             const int col = h0 + g_m * 8;
             *reinterpret_cast<u32x4*>(p.C + (((R >> 5) * (p.I >> 5) + (col >> 5)) << 10) + ((R & 31) << 5) + (col & 31)) = v;
             continue;
@@ -664,51 +642,44 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
       // fp32 partial sums of this reduction part, straight from the registers (wave-uniform base + lane offset)
       float* out = p.Cpart + (int64_t)part * p.pstride;
       typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
-      const uint32_t pvoff = (uint32_t)(e_l32 * p.I + e_half * 4) * 4u;
+      const uint32_t pvoff = (uint32_t)(e_m * p.I + e_rq * 4) * 4u;
 #pragma unroll
-      for (int b = 0; b < 4; b++) {
-        char* obase = reinterpret_cast<char*>(out + (int64_t)(j0 + wj * 128 + b * 32) * p.I + i0 + wi * 128);
+      for (int b = 0; b < 8; b++) {
+        char* obase = reinterpret_cast<char*>(out + (int64_t)(j0 + wj * 128 + b * 16) * p.I + i0 + wi * 128);
 #pragma unroll
-        for (int a = 0; a < 4; a++)
+        for (int a = 0; a < 8; a++) {
+          if (RAG && j0 + wj * 128 + b * 16 + e_m >= p.J) continue;                     // a row past the end
+          float* dst = reinterpret_cast<float*>(obase + a * 64 + pvoff);
+          const int cleft = CRAG ? p.I - (i0 + wi * 128 + a * 16 + e_rq * 4) : 4;       // columns to the end
+          if (CRAG && cleft < 4) {
 #pragma unroll
-          for (int g = 0; g < 4; g++) {
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; e++) v[e] = acc[a][b][g * 4 + e];
-            if (RAG && j0 + wj * 128 + b * 32 + e_l32 >= p.J) continue;                          // a row past the end
-            float* dst = reinterpret_cast<float*>(obase + (a * 32 + g * 8) * 4 + pvoff);
-            const int cleft = CRAG ? p.I - (i0 + wi * 128 + a * 32 + g * 8 + e_half * 4) : 4;    // columns to the end
-            if (CRAG && cleft < 4) {
-#pragma unroll
-              for (int e = 0; e < 4; e++)
-                if (e < cleft) dst[e] = v[e];
-            } else if (CRAG) {
-              *reinterpret_cast<f32x4_u*>(dst) = v;
-            } else {
-              *reinterpret_cast<f32x4*>(dst) = v;
-            }
+            for (int e = 0; e < 4; e++)
+              if (e < cleft) dst[e] = acc[a][b][e];
+          } else if (CRAG) {
+            *reinterpret_cast<f32x4_u*>(dst) = acc[a][b];
+          } else {
+            *reinterpret_cast<f32x4*>(dst) = acc[a][b];
           }
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
       // rounded to bf16 and stored (forward: the bias is in the accumulators since their start; the row statistics
       // are taken by the normalisation kernel)
       fetch_aux(0);
+      fetch_aux(1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int b = 0; b < 4; b++) {
-        if (b < 3) fetch_aux(b + 1);
+      for (int b = 0; b < 8; b++) {
+        if (b < 6) fetch_aux(b + 2);
         if (EPI == EPI_MASK) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int a = 0; a < 4; a++)
+        for (int a = 0; a < 8; a++) {
+          bf16x4 v;
 #pragma unroll
-          for (int g = 0; g < 4; g++) {
-            bf16x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; e++)
-              v[e] = (bf16_t)(EPI == EPI_RELU ? __builtin_fmaxf(acc[a][b][g * 4 + e], 0.0f) : acc[a][b][g * 4 + e]);
-            *(lds_bf16x4*)(wtile + woff[a][g]) = v;
-          }
+          for (int e = 0; e < 4; e++) v[e] = (bf16_t)(EPI == EPI_RELU ? __builtin_fmaxf(acc[a][b][e], 0.0f) : acc[a][b][e]);
+          *(lds_bf16x4*)(wtile + woff[a]) = v;
+        }
         flush_rows(b);
         __builtin_amdgcn_sched_barrier(0);   // one block row at a time: keeps the accumulator copies in few registers
       }
