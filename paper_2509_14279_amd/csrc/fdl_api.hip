@@ -140,7 +140,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p, bool
   q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K, q.stage_x != 0) : fast_f1_tail_bytes(M, K)));
   q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
-  // Large batches on the tuned kernel (tile-aligned N and K): the weights are transposed first, 4 N K bytes of traffic
+  // Large batches on the tuned kernel (tile-aligned N and K): the weights are blocked first, 4 N K bytes of traffic
   // against about 6 % of the contraction's time; that pays from roughly 10^4 rows, with a margin for the extra launch.
   if (dt == kF32) q.f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
   q.f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
@@ -395,7 +395,7 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
       launch_fast_xwt_padded(0, M, K, N, p.stage_x != 0, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, p.f1_split, ws + p.off_part, s);
     } else if (p.f1_fast) {
       void* Wt = p.f1_wt ? ws + p.off_wt : nullptr;
-      if (p.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
+      if (p.f1_wt) launch_fast_block(N, K, W, Wt, s);
       launch_fast_xwt(0, M, K, N, X, false, W, Wt, b, nullptr, Zsave, false, ws + p.off_xtail, s, false, p.f1_split,
                       ws + p.off_part);
     } else {
@@ -466,7 +466,7 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
     p.fwd_bytes = p.off_part;
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
-    p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the transposed weights: the kernel reads W as it is
+    p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the blocked weights: the kernel reads W as it is
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_split > 1) {
     p.f1_split = 1; p.fwd_bytes = p.off_part;         // (the sums of a split reduction are the last region here)
@@ -487,7 +487,7 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   clear_stale_error();
   char* ws = static_scratch_address();
   if (ws == nullptr) return launch_status();
-  // every scratch location a forward pass reads has been written earlier in the same pass (padded or transposed
+  // every scratch location a forward pass reads has been written earlier in the same pass (padded or blocked
   // weights, the padded copy of X's last rows), so nothing has to be cleared between calls
   return forward_launches(p, X, W, b, gamma, beta, eps, Y, Zsave, mean, rstd, ws, static_cast<hipStream_t>(hip_stream));
 }
@@ -701,14 +701,14 @@ extern "C" fdl_status fdl_forward_inference(fdl_dtype dt, int64_t M, int64_t K, 
 // ---- Linear + ReLU -------------------------------------------------------------------------------------------------
 namespace {
 // Workspace of the Linear+ReLU pair (one layout for both passes): the first-stage column partials of db, the copies the
-// forward product needs (padded weights and bias, X or its last rows, or transposed weights), and what the two gradient
+// forward product needs (padded weights and bias, X or its last rows, or blocked weights), and what the two gradient
 // contractions need, the masked upstream gradient G among it (the dZ of GradPlan).
 struct ReluPlan {
   int f1_mid;              // the forward product (and its recomputation) in 128 x 128 tiles, f1_split parts
   int f1_skinny;           // few rows: the forward product (and its recomputation) on the kernel made for them
   int f1_fast, f1_wb;      // the tuned kernel, on the operands as they are
   int pad;                 // or in padded mode (then the gradient contractions run in it too)
-  int f1_wt;               // the forward product (and its recomputation) reads the weights from a transposed copy
+  int f1_wt;               // the forward product (and its recomputation) reads the weights from a blocked copy
   GradPlan g;
   F64Split f1_s64;         // fp32 storage
   int f1_split;            // bf16, tiled: parts of the forward product's reduction
@@ -768,7 +768,7 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
                            aux, out, q.f1_split, ws + q.off_part, s);
   } else if (q.f1_fast) {
     void* Wt = q.f1_wt ? ws + q.off_wt : nullptr;
-    if (q.f1_wt) launch_fast_transpose(N, K, W, Wt, s);
+    if (q.f1_wt) launch_fast_block(N, K, W, Wt, s);
     launch_fast_xwt(kind, M, K, N, X, false, W, Wt, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s, false,
                     q.f1_split, ws + q.off_part);
   } else {
@@ -911,8 +911,8 @@ struct FfnPlan {
   int gate_pad, down_pad;  // the same kernels on zero-padded copies of the weights (widths off their tiles)
   int down_fast, up_wb, down_wb;
   int64_t ldg;             // pitch of G
-  int down_wt;             // the down projection reads its weights from a transposed copy
-  int gate_wt;             // the fused gate/up kernel reads both weight matrices from one interleaved transposed copy
+  int down_wt;             // the down projection reads its weights from a blocked copy
+  int gate_wt;             // the fused gate/up kernel reads both weight matrices from one interleaved blocked copy
   int g_blocked;           // the gated activation passes from the fused kernel to the down projection in 32 x 32 blocks
   F64Split up_s64, down_s64;   // fp32 storage
   int down_split;              // bf16, tiled: parts of the down projection's reduction
@@ -1027,7 +1027,7 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     launch_fast_gate_padded(M, D, H, X, ws + q.off_xtail, ws + q.off_wgp, ws + q.off_wup, G, s);
   } else if (q.gate_fused) {
     void* Wcat = q.gate_wt ? ws + q.off_wcat : nullptr;
-    if (q.gate_wt) launch_fast_transpose_gate(H, D, Wg, Wu, Wcat, s);
+    if (q.gate_wt) launch_fast_block_gate(H, D, Wg, Wu, Wcat, s);
     launch_fast_gate(M, D, H, X, Wg, Wu, Wcat, G, q.g_blocked != 0, ws + q.off_xtail, s);
   } else {
     GemmDesc g = {X, Wg, M, H, D, D, D, true, true, q.up_wb};
@@ -1046,7 +1046,7 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, s);
   } else if (q.down_fast) {
     void* Wt = q.down_wt ? ws + q.off_wt : nullptr;
-    if (q.down_wt) launch_fast_transpose(D, H, Wd, Wt, s);
+    if (q.down_wt) launch_fast_block(D, H, Wd, Wt, s);
     launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wt, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0,
                     q.down_split, ws + q.off_part);
   } else {

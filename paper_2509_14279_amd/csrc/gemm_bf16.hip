@@ -6,7 +6,6 @@
 // output row j in adjacent accumulator registers.
 //
 //   F1  Z[m][n]  = sum_k X[m][k] W[n][k] + b[n]   P = W (i = n, r-contiguous)   Q = X  (j = m, r-contiguous)
-//       or, for large batches,                    P = W^T (a transposed copy: r = k major)
 //       (also the forward product of the sibling operators: Linear+ReLU, its backward pass's recomputation of the
 //        pre-activation with the activation mask applied to the upstream gradient, and the three products of the
 //        gated feed-forward block)
@@ -89,7 +88,8 @@ struct FastParams {
   int nkt;               // reduction slices per workgroup
   int split;
   int xcds;              // accelerator dies the workgroup ids are dealt over (1: no die-aware tile order)
-  int qblocked;          // 1: Q (the library's own dZ buffer, ldq columns) is stored in blocks of 32 x 32, see Loader
+  int pblocked;          // 1: P (r-contiguous, BK = 32: the weights' copy, ldp columns) is stored in blocks of 32 x 32, see Loader
+  int qblocked;          // 1: so is Q (the library's own dZ buffer, ldq columns)
   int cblocked;          // 1: the output C [J][I] is written in that blocked layout (EPI_MASK: the masked gradient;
                          //    EPI_GATE: the gated activation)
 };
@@ -256,6 +256,20 @@ __device__ __forceinline__ TileCoord tile_coord(int L, int tiles_i, int tiles_j)
 // length up and makes one operand zero over the surplus (the other only has to be readable and finite there).
 // The body of the kernel: the persistent tile loop of workgroup `bid` of `nblk` on reduction part `part`.  It is a
 // function of its own so that one launch can carry two contractions side by side (see gemm_bf16_pair_kernel).
+// The MFMA with its accumulator in place, in AGPRs: left to choose, the register allocator moves accumulators about in straight
+// code and parks some in scratch memory.  (Written as asm they are no MFMAs to the compiler, which would otherwise put wait states
+// between one and a vector instruction that reads or has written its accumulator: the kernel does.  Its operands come from LDS, whose
+// waits the compiler inserts for asm too.)
+__device__ __forceinline__ void mfma_add(f32x4& acc, bf16x8 p, bf16x8 q) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
+}
+// acc = p q + start, or p q
+template <bool START> __device__ __forceinline__ void mfma_start(f32x4& acc, bf16x8 p, bf16x8 q, f32x4& start) {
+  if (!START) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
+  else if (&acc == &start) mfma_add(acc, p, q);
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)), "a"(start));
+}
+
 template <bool P_RM, bool Q_RM, int EPI, int BK, int NS, bool RAG, bool CRAG = false>
 __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, const int bid, const int nblk, const int part) {
   static_assert(!CRAG || RAG, "ragged columns come with the ragged-row checks");
@@ -296,12 +310,13 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   auto init_offsets = [&]() {
     int lt = lane;
     asm volatile("" : "+v"(lt));
-    lp.init(lt, wave, p.ldp); lq.init(lt, wave, p.ldq, p.qblocked);
+    lp.init(lt, wave, p.ldp, p.pblocked); lq.init(lt, wave, p.ldq, p.qblocked);
     fp.init(lt, wi); fq.init(lt, wj);
   };
   init_offsets();   // for the initial fill below; every tile recomputes them
 
-  const int64_t pstep = P_RM ? (int64_t)BK * p.ldp : BK;
+  const bool pblk = BK == 32 && !P_RM && p.pblocked != 0;
+  const int64_t pstep = P_RM ? (int64_t)BK * p.ldp : (pblk ? 1024 : BK);
   const bool qblk = BK == 32 && p.qblocked != 0;
   // (a slice step of an r-major operand is 32 rows = one block row either way: 32 ldq elements)
   const int64_t qstep = Q_RM ? (int64_t)BK * p.ldq : (qblk ? 1024 : BK);
@@ -311,7 +326,9 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   // product and a = 2, 3 the up product of the same 64 output columns, register for register, and the gated
   // activation needs no exchange between lanes.  The tile is 128 output columns wide.
   auto p_origin = [&](int i0) {
-    if (EPI == EPI_GATE && !P_RM)   // (an r-major P for this epilogue is one matrix with that row order built in)
+    if (pblk)    // block (i0 / 32, r_begin / 32) (for EPI_GATE one matrix with the row order below built in)
+      return lp.wave_base(p.P + ((int64_t)(i0 >> 5) * (p.ldp >> 5) + (r_begin >> 5)) * 1024, p.ldp, wave);
+    if (EPI == EPI_GATE)
       return ((wave & 1) ? p.P2 : p.P) + (int64_t)((i0 >> 1) + (wave >> 1) * 64) * p.ldp + r_begin;
     return lp.wave_base(P_RM ? p.P + r_begin * p.ldp + i0 : p.P + (int64_t)i0 * p.ldp + r_begin, p.ldp, wave);
   };
@@ -382,21 +399,19 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     const bf16_t* qwrap = has_next ? q_origin(tn.j0) : q_origin(tc.j0) + (int64_t)(nkt - 1) * qstep;
     const int fwrap = has_next ? 0 : nkt - 1;
 
-    // The accumulators are never cleared: the first sub-slice of a tile's slice 0 (which has its own copy of the slice code for
-    // that; the other slices, at least NS-1 of them - checked on the host - run in the loop) adds its products to the bias, of
-    // which a lane needs the same four values for all blocks of a column, or to zero.
-    f32x4 acc[8][8], start[8];
+    // The accumulators are never cleared: the first MFMAs of a tile add to zero or to the bias, of which a lane needs the same four
+    // values for all blocks of a column; they wait in the column's last accumulator, whose first MFMA is the last to read them.
+    f32x4 acc[8][8];
+    if (kBias) {
+      int lb = lane;
+      asm volatile("" : "+v"(lb));
 #pragma unroll
-    for (int a = 0; a < 8; a++) {
-      if (kBias) {
-        int lb = lane;
-        asm volatile("" : "+v"(lb));
-        start[a] = *(const lds_f32x4*)(lds + wbias + (lb >> 4) * 16 + a * 64);
-      } else {
+      for (int a = 0; a < 8; a++) acc[a][7] = *(const lds_f32x4*)(lds + wbias + (lb >> 4) * 16 + a * 64);
 #pragma unroll
-        for (int r = 0; r < 4; r++) start[a][r] = 0.0f;
-      }
+      for (int a = 0; a < 8; a++) asm volatile("" : "+a"(acc[a][7]));
+      asm volatile("s_nop 7");
     }
+    if (kBias) fetch_bias(tn.i0);      // (covered by the waits of this tile's slices, of which there are at least NS)
 
     // One slice; the LDS stage it lives in is a compile-time constant (the number of slices per tile is a multiple
     // of NS - checked on the host - so a tile's slice 0 is always in stage 0 and the slice loop is unrolled NS
@@ -423,8 +438,12 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         const int use = (cur * G::kSub + kk) & 1, fill = use ^ 1;
         const bool lastsub = kk == G::kSub - 1;
         if (lastsub) {
-          // slice kt+1 must have landed; the direct loads of the NS-2 slices after it may stay in flight
-          wait_dma<(NS - 2) * 2 * G::kDpw>();
+          // Slice kt+1 must have landed; the direct loads of the NS-2 slices after it may stay in flight.  So may, in a tile's first
+          // slices, whose successors were all fetched before them, the previous tile's stores (no fewer than counted: a lane's 16
+          // bytes are an instruction each) and the bias: these all retire in order, and the stores' way to memory is long.
+          constexpr int kStores = RAG ? 0 : (EPI == EPI_PARTIAL ? 64 : (EPI == EPI_GATE ? 16 : 32));
+          constexpr int kBehind = kFirst && cur < NS - 1 ? kStores + (kBias ? 2 : 0) : 0, kFlying = (NS - 2) * 2 * G::kDpw + kBehind;
+          wait_dma<kFlying < 63 ? kFlying : 63>();
           __syncthreads();
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -434,10 +453,8 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
 #pragma unroll
         for (int t = 0; t < 64; t++) {
           const int a = t >> 3, b = t & 7;
-          if (kFirst && kk == 0)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf[use][a], qf[use][b], start[a], 0, 0, 0);
-          else
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf[use][a], qf[use][b], acc[a][b], 0, 0, 0);
+          if (kFirst && cur == 0 && kk == 0) mfma_start<kBias>(acc[a][b], pf[use][a], qf[use][b], acc[a][7]);
+          else mfma_add(acc[a][b], pf[use][a], qf[use][b]);
           __builtin_amdgcn_sched_barrier(0);
           // next slice of the fetch stream: the following one of this tile, else (pwrap, qwrap, fwrap) = slice 0
           // of the next tile or, without a next tile, this tile's last slice again, which is never read; spread
@@ -454,8 +471,6 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
             fidx = fidx + 1 == nkt ? fwrap : fidx + 1;
             __builtin_amdgcn_sched_barrier(0);
           }
-          // (this tile's bias is in registers since the first sub-slice; the waits of the round's NS - 1 other slices cover this)
-          if (kBias && kFirst && lastsub && t == 63) fetch_bias(tn.i0);
           const bf16_t* const pn = pfetch;
           const bf16_t* const qn = qfetch;
           if (t % 3 == 0 && t < 48) {
@@ -467,9 +482,11 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
             __builtin_amdgcn_sched_barrier(0);
           }
           if (lastsub) {
-            // the direct loads, in the first half: one behind every second (BK = 64: 16 of them) or fourth MFMA (8)
-            constexpr int kEvery = G::kDpw == 8 ? 2 : 4;
-            if (t < 32 && t % kEvery == 1) {
+            // The direct loads, as far apart as the sub-slice allows: bunched they fill the memory pipe's queue, and a wave that
+            // waits to issue one issues no MFMA either (forward product 4096 x 4096 x 16384, 16 loads behind every second /
+            // fourth MFMA 466 / 420 us).
+            constexpr int kEvery = G::kDpw == 8 ? 4 : 6;
+            if (t < 2 * G::kDpw * kEvery && t % kEvery == 2) {
               const int d = t / kEvery;
               if (d < G::kDpw) lp.issue_q(d, pn, own);
               else lq.issue_q(d - G::kDpw, qn, own + G::kOperandBytes);
@@ -481,10 +498,10 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     };
     auto group = [&](auto first_tag) {
       slice(std::integral_constant<int, 0>(), first_tag);
-      slice(std::integral_constant<int, 1>(), std::false_type());
+      slice(std::integral_constant<int, 1>(), first_tag);
       if constexpr (NS == 4) {
-        slice(std::integral_constant<int, 2>(), std::false_type());
-        slice(std::integral_constant<int, 3>(), std::false_type());
+        slice(std::integral_constant<int, 2>(), first_tag);
+        slice(std::integral_constant<int, 3>(), first_tag);
       }
     };
     group(std::true_type());
@@ -500,8 +517,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     // Every per-lane constant of the epilogue is derived here from a copy of the lane id the compiler cannot see
     // through: hoisted out of the tile loop they would be spilled around the main loop, and each reload in the
     // epilogue would wait for the output stores issued before it (vector memory operations retire in order).
-    // (The accumulators get a fresh start with the register allocator too: without it, it parks a few of them in scratch
-    // memory across the epilogue.)
+    asm volatile("s_nop 15\n\ts_nop 15");      // (the last MFMAs' results)
 #pragma unroll
     for (int a = 0; a < 8; a++)
 #pragma unroll
@@ -509,16 +525,34 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     int le = lane;
     asm volatile("" : "+v"(le));
     const int i0 = tc.i0, j0 = tc.j0;
-    lds_char* wtile = lds + kLdsStages + wave * 8192;
+    const uint32_t wtile = lds0 + (uint32_t)(kLdsStages + wave * 8192);
     // e_m, e_rq: column group and row of four (accumulators: row and column group)
     const int e_m = le & 15, e_rq = le >> 4;
-    uint32_t woff[8];                            // LDS byte offset of the lane's 8-byte unit a in row lane%16
+    uint32_t woff[8];                            // LDS address of the lane's 8-byte unit a in row lane%16
 #pragma unroll
-    for (int a = 0; a < 8; a++) woff[a] = (uint32_t)(e_m * 256 + (((a * 4 + e_rq) ^ (e_m << 1)) << 3));
+    for (int a = 0; a < 8; a++) {
+      woff[a] = wtile + (uint32_t)(e_m * 256 + (((a * 4 + e_rq) ^ (e_m << 1)) << 3));
+      asm volatile("" : "+v"(woff[a]));
+    }
     // read side: rows it*4 + lane/16 of the block row, 16-byte chunk lane%16 (slot chunk ^ row)
     uint32_t roff[4];
 #pragma unroll
-    for (int it = 0; it < 4; it++) roff[it] = (uint32_t)((it * 4 + e_rq) * 256 + ((e_m ^ (it * 4 + e_rq)) << 4));
+    for (int it = 0; it < 4; it++) {
+      // (EPI_GATE: 16-byte chunk lane%8 of rows it*8 + lane/8)
+      if (EPI == EPI_GATE) roff[it] = wtile + (uint32_t)((it * 8 + (le >> 3)) * 256 + (((le & 7) ^ (it * 8 + (le >> 3))) << 4));
+      else roff[it] = wtile + (uint32_t)((it * 4 + e_rq) * 256 + ((e_m ^ (it * 4 + e_rq)) << 4));
+      asm volatile("" : "+v"(roff[it]));
+    }
+    // Block row b: stage() rounds it into the staging area, collect() reads it back as rows, store_rows() sends those out.  One
+    // row's stores are issued behind the conversions of the next, which cover the trip through LDS (a wave's LDS operations stay in
+    // order, so one area serves them all): the tile end of the
+    // forward product 65536 x 2048 x 8192 was 10 % of its 1630 us, 26 of which this and the accumulators kept in place give back.
+    constexpr int kCollect = EPI == EPI_GATE ? 2 : 4;
+    u32x4 rows[2][4];
+    auto collect = [&](int b) {
+#pragma unroll
+      for (int it = 0; it < kCollect; it++) rows[b & 1][it] = *(const lds_u32x4*)(uintptr_t)roff[it];
+    };
     const uint32_t svoff = (uint32_t)(e_rq * (int)p.ldc + e_m * 8) * 2u;   // byte offset of the lane inside 4 output rows
     typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
     // EPI_MASK: the upstream gradient of a block row, fetched while the two before it leave.  (Fetched where it is used, a tile
@@ -548,14 +582,13 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         aux[b % 3][it] = __builtin_bit_cast(u32x4, left <= 0 ? (unsigned __int128)0 : x >> (16 * (8 - left)));
       }
     };
-    // Block row b of the wave tile (16 output rows) leaves as soon as it is complete.
-    auto flush_rows = [&](int b) {
+    auto store_rows = [&](int b) {
       place_aux(b);
       // wave-uniform base of row it*4 of the block row; the lane adds (lane/16) rows and 16 (lane%16) bytes
       char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 16) * p.ldc + i0 + wi * 128);
 #pragma unroll
       for (int it = 0; it < 4; it++) {
-        const u32x4 v = *(const lds_u32x4*)(wtile + roff[it]);
+        const u32x4 v = rows[b & 1][it];
         u32x4* dst = reinterpret_cast<u32x4*>(cbase + (int64_t)(it * 4) * p.ldc * 2 + svoff);
         if (EPI == EPI_MASK && p.cblocked) {
           // row R0 + lane/16 (R0 a multiple of 4, so the four rows share a block row), columns col .. col + 7:
@@ -601,9 +634,8 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
       // H = SiLU(gate) * up for this wave's 64 columns x 128 rows, one block row of 16 rows at a time through the
       // staging area (units 0..15 of each 256-byte staging row), stored as 128-byte row segments
       const int h0 = (i0 >> 1) + wi * 64;
-      const int g_m = le & 7, g_rq = le >> 3;      // read side: 16-byte chunk lane%8 of row it*8 + lane/8
-#pragma unroll
-      for (int b = 0; b < 8; b++) {
+      const int g_m = le & 7, g_rq = le >> 3;
+      auto stage = [&](int b) {
 #pragma unroll
         for (int a = 0; a < 4; a++) {
           bf16x4 v;
@@ -613,13 +645,21 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
             const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * z));
             v[e] = (bf16_t)(z * sg * u);
           }
-          *(lds_bf16x4*)(wtile + woff[a]) = v;
+          *(lds_bf16x4*)(uintptr_t)woff[a] = v;
         }
+      };
+      stage(0);
+      collect(0);
+#pragma unroll
+      for (int b = 0; b < 8; b++) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (b < 7) stage(b + 1);
+        __builtin_amdgcn_sched_barrier(0);
         char* cbase = reinterpret_cast<char*>(p.C + (int64_t)(j0 + wj * 128 + b * 16) * p.ldc + h0);
 #pragma unroll
         for (int it = 0; it < 2; it++) {
           const int row = it * 8 + g_rq;
-          u32x4 v = *(const lds_u32x4*)(wtile + row * 256 + ((g_m ^ row) << 4));
+          u32x4 v = rows[b & 1][it];
           if (RAG && j0 + wj * 128 + b * 16 + row >= p.J) continue;   // a row past the end
           if (CRAG && h0 + g_m * 8 + 8 > p.I) {
             // the surplus columns of a padded width are zeros (their sums are too, but not where X holds an infinity)
@@ -637,6 +677,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
           *reinterpret_cast<u32x4*>(cbase + ((int64_t)row * p.ldc + g_m * 8) * 2) = v;
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (b < 7) collect(b + 1);
       }
     } else if (EPI == EPI_PARTIAL) {
       // fp32 partial sums of this reduction part, straight from the registers (wave-uniform base + lane offset)
@@ -666,22 +707,28 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     } else {
       // rounded to bf16 and stored (forward: the bias is in the accumulators since their start; the row statistics
       // are taken by the normalisation kernel)
-      fetch_aux(0);
-      fetch_aux(1);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int b = 0; b < 8; b++) {
-        if (b < 6) fetch_aux(b + 2);
-        if (EPI == EPI_MASK) __builtin_amdgcn_sched_barrier(0);
+      auto stage = [&](int b) {
 #pragma unroll
         for (int a = 0; a < 8; a++) {
           bf16x4 v;
 #pragma unroll
           for (int e = 0; e < 4; e++) v[e] = (bf16_t)(EPI == EPI_RELU ? __builtin_fmaxf(acc[a][b][e], 0.0f) : acc[a][b][e]);
-          *(lds_bf16x4*)(wtile + woff[a]) = v;
+          *(lds_bf16x4*)(uintptr_t)woff[a] = v;
         }
-        flush_rows(b);
+      };
+      fetch_aux(0);
+      fetch_aux(1);
+      stage(0);
+      collect(0);
+#pragma unroll
+      for (int b = 0; b < 8; b++) {
         __builtin_amdgcn_sched_barrier(0);   // one block row at a time: keeps the accumulator copies in few registers
+        if (b < 6) fetch_aux(b + 2);
+        if (b < 7) stage(b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        store_rows(b);
+        __builtin_amdgcn_sched_barrier(0);
+        if (b < 7) collect(b + 1);
       }
     }
 
@@ -715,33 +762,15 @@ void gemm_bf16_pair_kernel(FastParams pa, FastParams pb, int na, int nb) {
   }
 }
 
-// dst [cols][rows] = src [rows][cols]^T in 64 x 64 tiles through LDS (rows, cols multiples of 64): both sides move
-// 128-byte row segments.
-// The tile of source rows r0 .. r0 + 63 lands in destination columns (r0 / 64) * tile_stride + col_off .. + 63 of a
-// destination with pitch dst_ld (plain transposition: dst_ld = rows, tile_stride = 64, col_off = 0).
-__global__ __launch_bounds__(256) void transpose64_kernel(const bf16_t* __restrict__ src, int64_t rows, int64_t cols,
-                                                          bf16_t* __restrict__ dst, int64_t dst_ld, int tile_stride,
-                                                          int col_off) {
-  __shared__ unsigned short tile[64][66];
-  const int64_t c0 = (int64_t)blockIdx.x * 64, r0 = (int64_t)blockIdx.y * 64;
-  const int t = threadIdx.x, r = t >> 2, q = (t & 3) * 16;
-  const unsigned short* sp = reinterpret_cast<const unsigned short*>(src) + (r0 + r) * cols + c0 + q;
-  const u32x4 a = *reinterpret_cast<const u32x4*>(sp), b = *reinterpret_cast<const u32x4*>(sp + 8);
-#pragma unroll
-  for (int e = 0; e < 4; e++) {
-    tile[r][q + 2 * e] = (unsigned short)(a[e] & 0xffffu); tile[r][q + 2 * e + 1] = (unsigned short)(a[e] >> 16);
-    tile[r][q + 8 + 2 * e] = (unsigned short)(b[e] & 0xffffu); tile[r][q + 8 + 2 * e + 1] = (unsigned short)(b[e] >> 16);
-  }
-  __syncthreads();
-  u32x4 o0, o1;
-#pragma unroll
-  for (int e = 0; e < 4; e++) {
-    o0[e] = (uint32_t)tile[q + 2 * e][r] | ((uint32_t)tile[q + 2 * e + 1][r] << 16);
-    o1[e] = (uint32_t)tile[q + 8 + 2 * e][r] | ((uint32_t)tile[q + 8 + 2 * e + 1][r] << 16);
-  }
-  unsigned short* dp = reinterpret_cast<unsigned short*>(dst) + (c0 + r) * dst_ld + (r0 / 64) * tile_stride + col_off + q;
-  *reinterpret_cast<u32x4*>(dp) = o0;
-  *reinterpret_cast<u32x4*>(dp + 8) = o1;
+// src [rows][cols] in blocks of 32 x 32 (see Loader; rows multiples of 32, cols of 64): a workgroup moves two neighbouring blocks,
+// 128 bytes of each of 32 rows.  Block row b of src becomes block row (b / 2) * pair_stride + b % 2 + row_off of dst (plain: 2, 0).
+__global__ __launch_bounds__(256) void block32_kernel(const bf16_t* __restrict__ src, int64_t cols, bf16_t* __restrict__ dst,
+                                                      int pair_stride, int row_off) {
+  const int row = threadIdx.x >> 3, chunk = threadIdx.x & 7;
+  const int64_t b = blockIdx.y, c0 = (int64_t)blockIdx.x * 64;
+  const u32x4 v = *reinterpret_cast<const u32x4*>(src + (b * 32 + row) * cols + c0 + chunk * 8);
+  const int64_t to = ((b >> 1) * pair_stride + (b & 1) + row_off) * (cols >> 5) + (c0 >> 5) + (chunk >> 2);
+  *reinterpret_cast<u32x4*>(dst + to * 1024 + row * 32 + (chunk & 3) * 8) = v;
 }
 
 // Zero-padded copies, several in one launch (they are small dependent launches otherwise, a few microseconds each):
@@ -911,19 +940,17 @@ void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, bool staged, co
   if (biasp != nullptr) stage_vector(j, bias, N, biasp, Np);
 }
 
-// Wt [K][N] = W^T (N, K multiples of 64).
-void launch_fast_transpose(int64_t N, int64_t K, const void* W, void* Wt, hipStream_t s) {
-  const dim3 grid((unsigned)(K / 64), (unsigned)(N / 64));
-  hipLaunchKernelGGL(transpose64_kernel, grid, dim3(256), 0, s, (const bf16_t*)W, N, K, (bf16_t*)Wt, N, 64, 0);
+// Wb = W [N][K] in blocks of 32 x 32 (N, K multiples of 64).
+void launch_fast_block(int64_t N, int64_t K, const void* W, void* Wb, hipStream_t s) {
+  hipLaunchKernelGGL(block32_kernel, dim3((unsigned)(K / 64), (unsigned)(N / 32)), dim3(256), 0, s, (const bf16_t*)W, K, (bf16_t*)Wb, 2, 0);
 }
 
-// Wcat [D][2H]: the transposed gate and up weights side by side in groups of 64 columns - 64 of Wg^T, the same 64 of
-// Wu^T, the next 64 of Wg^T, ... - which is the order in which the gated kernel wants the 256 rows of its P tile
-// (H, D multiples of 64).
-void launch_fast_transpose_gate(int64_t H, int64_t D, const void* Wg, const void* Wu, void* Wcat, hipStream_t s) {
-  const dim3 grid((unsigned)(D / 64), (unsigned)(H / 64));
-  hipLaunchKernelGGL(transpose64_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wg, H, D, (bf16_t*)Wcat, 2 * H, 128, 0);
-  hipLaunchKernelGGL(transpose64_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wu, H, D, (bf16_t*)Wcat, 2 * H, 128, 64);
+// Wcat [2H][D]: the gate and up weights' rows side by side in groups of 64 - 64 of Wg, the same 64 of Wu, the next 64 of Wg, ... -
+// which is the order in which the gated kernel wants the 256 rows of its P tile, in blocks of 32 x 32 (H, D multiples of 64).
+void launch_fast_block_gate(int64_t H, int64_t D, const void* Wg, const void* Wu, void* Wcat, hipStream_t s) {
+  const dim3 grid((unsigned)(D / 64), (unsigned)(H / 32));
+  hipLaunchKernelGGL(block32_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wg, D, (bf16_t*)Wcat, 4, 0);
+  hipLaunchKernelGGL(block32_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wu, D, (bf16_t*)Wcat, 4, 2);
 }
 
 static void launch_xwt_split(FastParams p, bool rag, bool crag, int kind, int split, void* part, int64_t M, int64_t N,
@@ -955,18 +982,14 @@ void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, bool stag
 //   kind 2: aux[m][n] where the sum is positive, else 0
 // xtail: fast_f1_tail_bytes(M, K) bytes of scratch when M is not a multiple of 256, unless X itself has readable rows
 // up to the next multiple of 256 (x_padded).
-// Wt: null, or W^T [K][N] (launch_fast_transpose): the weights then enter as the r-major operand.  A tile slice of an
-// r-major operand is 32 runs of 512 contiguous bytes, of an r-contiguous one 256 runs of 128 or 64 bytes, and the
-// contraction runs faster for every operand it can read the first way (measured on 65536 x 2048 x 8192: 1.77 -> 1.65
-// ms; with the reduction long enough to hide the tile boundaries the three combinations reach 1.16 - 1.27, 1.31 - 1.35
-// and 1.43 - 1.44 PFLOP/s), which pays for transposing the weights once the batch is large (the caller decides).
+// Wb: null, or W in blocks of 32 x 32 (launch_fast_block), whose slices of 32 are long runs in memory.
 // out_blocked (kind 2 only; M, N multiples of 32): out is written in 32 x 32 blocks, as the dX and dW kernels read it best.
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
-                     const void* Wt, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
+                     const void* Wb, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
                      hipStream_t s, bool x_blocked, int split, void* part) {
   FastParams p = {};
   p.cblocked = (out_blocked && kind == 2) ? 1 : 0;
-  p.qblocked = (x_blocked && Wt != nullptr) ? 1 : 0;   // only the transposed-weight kernels read a blocked X
+  p.qblocked = (x_blocked && Wb != nullptr) ? 1 : 0;   // (with the weights' copy only: slices of 32)
   p.P = (const bf16_t*)W; p.Q = (const bf16_t*)X; p.ldp = K; p.ldq = K;
   p.C = (bf16_t*)out; p.bias = bias; p.aux = (const bf16_t*)aux;
   p.I = (int)N; p.J = (int)M; p.tiles_i = (int)(N / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
@@ -978,19 +1001,19 @@ void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, b
     stage_x_tail(&j, X, M, K, xtail, 0);
     launch_stage(j, s);
   }
-  if (Wt != nullptr) {   // the weights as the r-major operand
-    p.P = (const bf16_t*)Wt; p.ldp = N; p.nkt = (int)(K / kB3BK);
+  if (Wb != nullptr) {
+    p.P = (const bf16_t*)Wb; p.pblocked = 1; p.nkt = (int)(K / kB3BK);
     constexpr int NST = stages_of(kB3BK);
-#define FDL_XWT_T(EPI)                                                            \
+#define FDL_XWT_B(EPI)                                                            \
   do {                                                                            \
-    if (rag) launch<true, false, EPI, kB3BK, NST, true>(p, s);                    \
-    else launch<true, false, EPI, kB3BK, NST, false>(p, s);                       \
+    if (rag) launch<false, false, EPI, kB3BK, NST, true>(p, s);                   \
+    else launch<false, false, EPI, kB3BK, NST, false>(p, s);                       \
   } while (0)
-    if (kind == 1) FDL_XWT_T(EPI_RELU);
-    else if (kind == 2) FDL_XWT_T(EPI_MASK);
-    else if (bias != nullptr) FDL_XWT_T(EPI_BIAS);
-    else FDL_XWT_T(EPI_STORE);
-#undef FDL_XWT_T
+    if (kind == 1) FDL_XWT_B(EPI_RELU);
+    else if (kind == 2) FDL_XWT_B(EPI_MASK);
+    else if (bias != nullptr) FDL_XWT_B(EPI_BIAS);
+    else FDL_XWT_B(EPI_STORE);
+#undef FDL_XWT_B
     return;
   }
   if (split > 1) { launch_xwt_split(p, rag, false, kind, split, part, M, N, bias, aux, out, N, s); return; }
@@ -1125,11 +1148,11 @@ void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void
     stage_x_tail(&j, X, M, D, xtail, 0);
     launch_stage(j, s);
   }
-  if (Wcat != nullptr) {   // Wcat from launch_fast_transpose_gate: the weights as one r-major operand (see launch_fast_xwt)
-    p.P = (const bf16_t*)Wcat; p.P2 = nullptr; p.ldp = 2 * H; p.nkt = (int)(D / kB3BK);
+  if (Wcat != nullptr) {   // Wcat from launch_fast_block_gate (see launch_fast_xwt)
+    p.P = (const bf16_t*)Wcat; p.P2 = nullptr; p.pblocked = 1; p.nkt = (int)(D / kB3BK);
     constexpr int NST = stages_of(kB3BK);
-    if (rag) launch<true, false, EPI_GATE, kB3BK, NST, true>(p, s);
-    else launch<true, false, EPI_GATE, kB3BK, NST, false>(p, s);
+    if (rag) launch<false, false, EPI_GATE, kB3BK, NST, true>(p, s);
+    else launch<false, false, EPI_GATE, kB3BK, NST, false>(p, s);
     return;
   }
   constexpr int NS = stages_of(kF1BK);
