@@ -140,13 +140,11 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p, bool
   q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K, q.stage_x != 0) : fast_f1_tail_bytes(M, K)));
   q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
-  // Large batches on the tuned kernel (tile-aligned N and K): the weights are blocked first, 4 N K bytes of traffic
-  // against about 6 % of the contraction's time; that pays from roughly 10^4 rows, with a margin for the extra launch.
   if (dt == kF32) q.f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
   q.f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
   q.off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q.f1_s64) : fast_xwt_part_bytes(M, N, q.f1_split));
   q.fwd_bytes_plain = off;
-  q.f1_wt = tiled && !q.pad && M >= kTransposeFromRows && q.f1_split == 1;
+  q.f1_wt = tiled && !q.pad && copies_weights(M, K) && q.f1_split == 1;
   q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
   q.fwd_bytes = off;
   // (128 x 128 tiles need no copies: the sums of their split reduction lie where those would)
@@ -394,9 +392,9 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
       launch_stage(j, s);
       launch_fast_xwt_padded(0, M, K, N, p.stage_x != 0, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, p.f1_split, ws + p.off_part, s);
     } else if (p.f1_fast) {
-      void* Wt = p.f1_wt ? ws + p.off_wt : nullptr;
-      if (p.f1_wt) launch_fast_block(N, K, W, Wt, s);
-      launch_fast_xwt(0, M, K, N, X, false, W, Wt, b, nullptr, Zsave, false, ws + p.off_xtail, s, false, p.f1_split,
+      void* Wb = p.f1_wt ? ws + p.off_wt : nullptr;
+      if (p.f1_wt) launch_fast_block(N, K, W, Wb, s);
+      launch_fast_xwt(0, M, K, N, X, false, W, Wb, b, nullptr, Zsave, false, ws + p.off_xtail, s, false, p.f1_split,
                       ws + p.off_part);
     } else {
       GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
@@ -466,7 +464,7 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
     p.fwd_bytes = p.off_part;
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
-    p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the blocked weights: the kernel reads W as it is
+    p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the weights' copy: the kernel reads W as it is
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_split > 1) {
     p.f1_split = 1; p.fwd_bytes = p.off_part;         // (the sums of a split reduction are the last region here)
@@ -701,14 +699,14 @@ extern "C" fdl_status fdl_forward_inference(fdl_dtype dt, int64_t M, int64_t K, 
 // ---- Linear + ReLU -------------------------------------------------------------------------------------------------
 namespace {
 // Workspace of the Linear+ReLU pair (one layout for both passes): the first-stage column partials of db, the copies the
-// forward product needs (padded weights and bias, X or its last rows, or blocked weights), and what the two gradient
+// forward product needs (padded weights and bias, X or its last rows, or the weights in blocks), and what the two gradient
 // contractions need, the masked upstream gradient G among it (the dZ of GradPlan).
 struct ReluPlan {
   int f1_mid;              // the forward product (and its recomputation) in 128 x 128 tiles, f1_split parts
   int f1_skinny;           // few rows: the forward product (and its recomputation) on the kernel made for them
   int f1_fast, f1_wb;      // the tuned kernel, on the operands as they are
   int pad;                 // or in padded mode (then the gradient contractions run in it too)
-  int f1_wt;               // the forward product (and its recomputation) reads the weights from a blocked copy
+  int f1_wt;               // the forward product (and its recomputation) reads the weights from a copy in blocks
   GradPlan g;
   F64Split f1_s64;         // fp32 storage
   int f1_split;            // bf16, tiled: parts of the forward product's reduction
@@ -745,7 +743,7 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan
     q->off_xtail = off; off += align256(f1 == Xwt::kPadded ? fast_padded_tail_bytes(K) : fast_f1_tail_bytes(M, K));
   }
   q->off_bpad = off; off += align256(f1 == Xwt::kPadded ? (size_t)fast_pad_dim(N) * 4 : 0);
-  q->f1_wt = f1 == Xwt::kTiled && M >= kTransposeFromRows && q->f1_split == 1;
+  q->f1_wt = f1 == Xwt::kTiled && copies_weights(M, K) && q->f1_split == 1;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
   if (dt == kF32) q->f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
   if (q->f1_mid) q->f1_split = parts;
@@ -767,9 +765,9 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
     launch_fast_xwt_padded(kind, M, K, N, q.g.stage_x != 0, X, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<const float*>(ws + q.off_bpad),
                            aux, out, q.f1_split, ws + q.off_part, s);
   } else if (q.f1_fast) {
-    void* Wt = q.f1_wt ? ws + q.off_wt : nullptr;
-    if (q.f1_wt) launch_fast_block(N, K, W, Wt, s);
-    launch_fast_xwt(kind, M, K, N, X, false, W, Wt, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s, false,
+    void* Wb = q.f1_wt ? ws + q.off_wt : nullptr;
+    if (q.f1_wt) launch_fast_block(N, K, W, Wb, s);
+    launch_fast_xwt(kind, M, K, N, X, false, W, Wb, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s, false,
                     q.f1_split, ws + q.off_part);
   } else {
     GemmDesc g = {X, W, M, N, K, K, K, true, true, q.f1_wb};
@@ -911,12 +909,12 @@ struct FfnPlan {
   int gate_pad, down_pad;  // the same kernels on zero-padded copies of the weights (widths off their tiles)
   int down_fast, up_wb, down_wb;
   int64_t ldg;             // pitch of G
-  int down_wt;             // the down projection reads its weights from a blocked copy
-  int gate_wt;             // the fused gate/up kernel reads both weight matrices from one interleaved blocked copy
+  int down_wt;             // the down projection reads its weights from a copy in blocks
+  int gate_wt;             // the fused gate/up kernel reads its weights from a copy (it never does)
   int g_blocked;           // the gated activation passes from the fused kernel to the down projection in 32 x 32 blocks
   F64Split up_s64, down_s64;   // fp32 storage
   int down_split;              // bf16, tiled: parts of the down projection's reduction
-  size_t off_g, off_u, off_xtail, off_wt, off_wcat, off_wgp, off_wup, off_wdp, off_part, bytes;
+  size_t off_g, off_u, off_xtail, off_wt, off_wgp, off_wup, off_wdp, off_part, bytes;
 };
 bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* q) {
   const bool split = room == Room::kAll || room == Room::kTight;
@@ -955,10 +953,9 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* 
   q->off_wup = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wdp = off; off += align256(q->down_pad ? (size_t)Dp * Hp * 2 : 0);
   q->down_split = split && (q->down_pad || q->down_fast) ? fast_xwt_split(M, q->down_pad ? Hp : H, D) : 1;
-  q->down_wt = q->down_fast && M >= kTransposeFromRows && q->down_split == 1;
+  q->down_wt = q->down_fast && M >= kCopyFromRows && q->down_split == 1;
   q->off_wt = off; off += align256(q->down_wt ? (size_t)D * H * 2 : 0);
-  q->gate_wt = q->gate_fused && M >= kTransposeFromRows && H % 64 == 0 && D % 64 == 0;
-  q->off_wcat = off; off += align256(q->gate_wt ? (size_t)2 * D * H * 2 : 0);
+  q->gate_wt = 0;
   q->g_blocked = q->gate_fused && q->down_wt && H % 32 == 0;
   if (dt == kF32) {
     q->up_s64 = split ? f64_plan(Mp, H, D) : f64_unsplit(Mp, H);
@@ -1026,9 +1023,7 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
   } else if (q.gate_pad) {
     launch_fast_gate_padded(M, D, H, X, ws + q.off_xtail, ws + q.off_wgp, ws + q.off_wup, G, s);
   } else if (q.gate_fused) {
-    void* Wcat = q.gate_wt ? ws + q.off_wcat : nullptr;
-    if (q.gate_wt) launch_fast_block_gate(H, D, Wg, Wu, Wcat, s);
-    launch_fast_gate(M, D, H, X, Wg, Wu, Wcat, G, q.g_blocked != 0, ws + q.off_xtail, s);
+    launch_fast_gate(M, D, H, X, Wg, Wu, G, q.g_blocked != 0, ws + q.off_xtail, s);
   } else {
     GemmDesc g = {X, Wg, M, H, D, D, D, true, true, q.up_wb};
     if (dt == FDL_F32) launch_f64(0, g, q.up_s64, nullptr, nullptr, G, ws + q.off_part, s);
@@ -1045,9 +1040,9 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
   } else if (q.down_skinny) {
     launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, s);
   } else if (q.down_fast) {
-    void* Wt = q.down_wt ? ws + q.off_wt : nullptr;
-    if (q.down_wt) launch_fast_block(D, H, Wd, Wt, s);
-    launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wt, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0,
+    void* Wb = q.down_wt ? ws + q.off_wt : nullptr;
+    if (q.down_wt) launch_fast_block(D, H, Wd, Wb, s);
+    launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wb, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0,
                     q.down_split, ws + q.off_part);
   } else {
     GemmDesc g = {G, Wd, M, D, H, H, H, true, true, q.down_wb};

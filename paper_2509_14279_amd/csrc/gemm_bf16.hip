@@ -326,7 +326,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   // product and a = 2, 3 the up product of the same 64 output columns, register for register, and the gated
   // activation needs no exchange between lanes.  The tile is 128 output columns wide.
   auto p_origin = [&](int i0) {
-    if (pblk)    // block (i0 / 32, r_begin / 32) (for EPI_GATE one matrix with the row order below built in)
+    if (pblk)    // block (i0 / 32, r_begin / 32)
       return lp.wave_base(p.P + ((int64_t)(i0 >> 5) * (p.ldp >> 5) + (r_begin >> 5)) * 1024, p.ldp, wave);
     if (EPI == EPI_GATE)
       return ((wave & 1) ? p.P2 : p.P) + (int64_t)((i0 >> 1) + (wave >> 1) * 64) * p.ldp + r_begin;
@@ -763,13 +763,12 @@ void gemm_bf16_pair_kernel(FastParams pa, FastParams pb, int na, int nb) {
 }
 
 // src [rows][cols] in blocks of 32 x 32 (see Loader; rows multiples of 32, cols of 64): a workgroup moves two neighbouring blocks,
-// 128 bytes of each of 32 rows.  Block row b of src becomes block row (b / 2) * pair_stride + b % 2 + row_off of dst (plain: 2, 0).
-__global__ __launch_bounds__(256) void block32_kernel(const bf16_t* __restrict__ src, int64_t cols, bf16_t* __restrict__ dst,
-                                                      int pair_stride, int row_off) {
+// 128 bytes of each of 32 rows.
+__global__ __launch_bounds__(256) void block32_kernel(const bf16_t* __restrict__ src, int64_t cols, bf16_t* __restrict__ dst) {
   const int row = threadIdx.x >> 3, chunk = threadIdx.x & 7;
   const int64_t b = blockIdx.y, c0 = (int64_t)blockIdx.x * 64;
   const u32x4 v = *reinterpret_cast<const u32x4*>(src + (b * 32 + row) * cols + c0 + chunk * 8);
-  const int64_t to = ((b >> 1) * pair_stride + (b & 1) + row_off) * (cols >> 5) + (c0 >> 5) + (chunk >> 2);
+  const int64_t to = b * (cols >> 5) + (c0 >> 5) + (chunk >> 2);
   *reinterpret_cast<u32x4*>(dst + to * 1024 + row * 32 + (chunk & 3) * 8) = v;
 }
 
@@ -942,15 +941,7 @@ void stage_padded(StageJobs* j, int64_t M, int64_t K, int64_t N, bool staged, co
 
 // Wb = W [N][K] in blocks of 32 x 32 (N, K multiples of 64).
 void launch_fast_block(int64_t N, int64_t K, const void* W, void* Wb, hipStream_t s) {
-  hipLaunchKernelGGL(block32_kernel, dim3((unsigned)(K / 64), (unsigned)(N / 32)), dim3(256), 0, s, (const bf16_t*)W, K, (bf16_t*)Wb, 2, 0);
-}
-
-// Wcat [2H][D]: the gate and up weights' rows side by side in groups of 64 - 64 of Wg, the same 64 of Wu, the next 64 of Wg, ... -
-// which is the order in which the gated kernel wants the 256 rows of its P tile, in blocks of 32 x 32 (H, D multiples of 64).
-void launch_fast_block_gate(int64_t H, int64_t D, const void* Wg, const void* Wu, void* Wcat, hipStream_t s) {
-  const dim3 grid((unsigned)(D / 64), (unsigned)(H / 32));
-  hipLaunchKernelGGL(block32_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wg, D, (bf16_t*)Wcat, 4, 0);
-  hipLaunchKernelGGL(block32_kernel, grid, dim3(256), 0, s, (const bf16_t*)Wu, D, (bf16_t*)Wcat, 4, 2);
+  hipLaunchKernelGGL(block32_kernel, dim3((unsigned)(K / 64), (unsigned)(N / 32)), dim3(256), 0, s, (const bf16_t*)W, K, (bf16_t*)Wb);
 }
 
 static void launch_xwt_split(FastParams p, bool rag, bool crag, int kind, int split, void* part, int64_t M, int64_t N,
@@ -982,7 +973,11 @@ void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, bool stag
 //   kind 2: aux[m][n] where the sum is positive, else 0
 // xtail: fast_f1_tail_bytes(M, K) bytes of scratch when M is not a multiple of 256, unless X itself has readable rows
 // up to the next multiple of 256 (x_padded).
-// Wb: null, or W in blocks of 32 x 32 (launch_fast_block), whose slices of 32 are long runs in memory.
+// Wb: null, or W in blocks of 32 x 32 (launch_fast_block).  With X in blocks too (x_blocked: the library's own buffer, rows padded to
+// whole tiles) every slice of either operand is long runs, for which slices of 32 in four stages serve better than slices of 64 in
+// two: the feed-forward block's down product 16384 x 11008 x 4096 1115 us from rows 22 KB apart, 935 so, 14 of it the copy.
+// An X that comes as rows gains nothing from blocked weights (inference, us, with / without: 16384 x 4096 x 4096 428 / 408,
+// 32768 x 2048 x 8192 956 / 930, 16384 x 11008 x 4096 1187 / 1188).
 // out_blocked (kind 2 only; M, N multiples of 32): out is written in 32 x 32 blocks, as the dX and dW kernels read it best.
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
                      const void* Wb, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
@@ -1133,8 +1128,8 @@ bool fast_gate_supported(int64_t M, int64_t D, int64_t H) {
   return M >= kMinRaggedRows && H > 0 && H % 128 == 0 && D > 0 && D % (stages_of(kF1BK) * kF1BK) == 0 && H <= (1 << 24) &&
          M <= (1 << 24) && (H / 128) * tj <= (1 << 30);
 }
-void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, const void* Wcat,
-                      void* Hout, bool out_blocked, void* xtail, hipStream_t s) {
+void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* Hout, bool out_blocked,
+                      void* xtail, hipStream_t s) {
   FastParams p = {};
   p.cblocked = out_blocked ? 1 : 0;    // H a multiple of 32; rows past M are not stored
   p.P = (const bf16_t*)Wg; p.P2 = (const bf16_t*)Wu; p.Q = (const bf16_t*)X; p.ldp = D; p.ldq = D;
@@ -1147,13 +1142,6 @@ void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void
     StageJobs j = {};
     stage_x_tail(&j, X, M, D, xtail, 0);
     launch_stage(j, s);
-  }
-  if (Wcat != nullptr) {   // Wcat from launch_fast_block_gate (see launch_fast_xwt)
-    p.P = (const bf16_t*)Wcat; p.P2 = nullptr; p.pblocked = 1; p.nkt = (int)(D / kB3BK);
-    constexpr int NST = stages_of(kB3BK);
-    if (rag) launch<false, false, EPI_GATE, kB3BK, NST, true>(p, s);
-    else launch<false, false, EPI_GATE, kB3BK, NST, false>(p, s);
-    return;
   }
   constexpr int NS = stages_of(kF1BK);
   if (rag) launch<false, false, EPI_GATE, kF1BK, NS, true>(p, s);

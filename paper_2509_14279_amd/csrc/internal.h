@@ -53,13 +53,13 @@ struct Plan {
   int f1_skinny;          // 1: bf16 kernel for few rows (before the two below)
   int f1_fast;            // 1: bf16 fast MFMA kernel, 0: generic kernel
   int f1_wb;              // generic kernel: 16x16 blocks per wave tile side (wave tile = 16*wb)
-  int f1_wt;              // 1: the fast kernel reads the weights from a blocked copy (large batches)
-  size_t off_wt;          // bf16 [K][N], the last region of the forward workspace
+  int f1_wt;              // 1: the fast kernel reads the weights from a copy in blocks (copies_weights)
+  size_t off_wt;          // bf16 [N][K], the last region of the forward workspace
   size_t off_rows;        // F2's scratch for rows beyond its registers, the first
   F64Split f1_s64;        // fp32 storage
   int f1_split;           // bf16, tiled: parts of the reduction where there are few tiles
   size_t off_part;        // their sums
-  size_t fwd_bytes;       // (without the blocked weights: fwd_bytes - align256(N K 2), see fwd_bytes_plain)
+  size_t fwd_bytes;       // (without the weights' copy: fwd_bytes - align256(N K 2), see fwd_bytes_plain)
   size_t fwd_bytes_plain; // forward workspace of the same plan with f1_wt = 0
   size_t static_need;     // what fdl_forward_static compares with its array (the header's rule)
   // backward
@@ -209,8 +209,8 @@ bool fast_b3_supported(int64_t M, int64_t K, int64_t N);
 bool fast_b4_supported(int64_t M, int64_t K, int64_t N);
 int64_t fast_b4_rows(int64_t M);
 size_t fast_f1_tail_bytes(int64_t M, int64_t K);
-// Wt: null, or the weights in blocks [N][K] from launch_fast_block (N, K multiples of 64)
-void launch_fast_block(int64_t N, int64_t K, const void* W, void* Wt, hipStream_t s);
+// Wb [N][K]: W in blocks of 32 x 32 (N, K multiples of 64)
+void launch_fast_block(int64_t N, int64_t K, const void* W, void* Wb, hipStream_t s);
 // zero-padded copies of up to four matrices and one vector in one launch (see stage_kernel)
 struct StageJob { const void* src; void* dst; int64_t rows, cols, ld, rows_out, cols_out; int blocks; };
 struct StageJobs { StageJob job[4]; int count; const float* vsrc; float* vdst; int64_t vn, vn_out; };
@@ -250,18 +250,19 @@ void launch_fast_b3_padded(int64_t M, int64_t K, int64_t N, const void* dZ, cons
 void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, int extra, const void* dZ, const void* X, int64_t ldx,
                            void* dW, void* dwpart, hipStream_t s);
 // the forward product, also of the sibling operators (see gemm_bf16.hip); shapes as fast_f1_supported;
-// Wt: null, or the blocked weights from launch_fast_block
-constexpr int64_t kTransposeFromRows = 16384;   // batch size from which transposing the weights first pays
+// Wb: null, or the weights' copy from launch_fast_block
+constexpr int64_t kCopyFromRows = 16384;   // batch size from which copying the weights first pays
+// Whether a product of X as rows reads its weights from that copy: at one round of the pipeline only, where four stages of 32 instead of
+// two of 64 make up for it from a few thousand columns on (inference 16384 x 128 x 8448 200 us either way, x 256 23.5 against 20.3).
+inline bool copies_weights(int64_t M, int64_t K) { return M >= kCopyFromRows && K <= 128; }
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
-                     const void* Wt, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
-                     hipStream_t s, bool x_blocked = false,    // x_blocked: X in 32 x 32 blocks (needs Wt, x_padded)
-                     int split = 1, void* part = nullptr);     // see fast_xwt_split (without Wt)
+                     const void* Wb, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
+                     hipStream_t s, bool x_blocked = false,    // x_blocked: X in 32 x 32 blocks (needs Wb, x_padded)
+                     int split = 1, void* part = nullptr);     // see fast_xwt_split (without Wb)
 // gate and up products of the feed-forward block with the gated activation in the epilogue (see gemm_bf16.hip)
 bool fast_gate_supported(int64_t M, int64_t D, int64_t H);
-// Wcat: null, or the interleaved weights in blocks [2H][D] from launch_fast_block_gate
-void launch_fast_block_gate(int64_t H, int64_t D, const void* Wg, const void* Wu, void* Wcat, hipStream_t s);
-void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, const void* Wcat,
-                      void* Hout, bool out_blocked, void* xtail, hipStream_t s);
+void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* Hout, bool out_blocked,
+                      void* xtail, hipStream_t s);
 // dZ must have readable rows up to the next multiple of 256
 // dz_blocked: dZ is stored in 32 x 32 blocks (launch_b1_fused with blocked = true; M, N multiples of 32)
 void launch_fast_b3(int64_t M, int64_t K, int64_t N, const void* dZ, bool dz_blocked, const void* W, void* dX,
