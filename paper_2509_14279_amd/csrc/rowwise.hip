@@ -1374,7 +1374,7 @@ template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int gro
 template <int CH, int FIT, int NT, int ACT, int WPR = 1>
 void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float eps, const bf16_t* Z, const float* gamma,
                         const float* beta, bf16_t* Y, float* mean, float* rstd) {
-  constexpr size_t kLds = (affine_in_lds(CH * WPR) ? (size_t)CH * WPR * 4096 : 0) + GaussTable<false>::kBytes;
+  constexpr size_t kLds = (affine_in_lds(CH * WPR) ? (size_t)CH * WPR * 4096 : 0) + (ACT == ACT_GELU ? GaussTable<false>::kBytes : 0);
   auto kern = f2_rows_kernel<CH, FIT, NT, ACT, WPR>;
   if constexpr (kLds > 64 * 1024) {
     static OnceFlags configured;
@@ -1383,10 +1383,11 @@ void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float 
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(NT), kLds, s, M, N, eps, Z, gamma, beta, Y, mean, rstd);
 }
 
+constexpr int64_t kMemorySideCache = (int64_t)256 << 20;      // bytes
 template <int ACT>
 void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const float* gamma, const float* beta, void* Y,
                      float* mean, float* rstd, hipStream_t s) {
-  // Rows of 8192 and 16384 take 16 vectors per lane.  The others, whose masks cost registers (one wavefront per SIMD with
+  // Rows of 16384 take 16 vectors per lane.  The others, whose masks cost registers (one wavefront per SIMD with
   // 16 vectors), take at most 8 and more wavefronts per row: 10000 x 5000 70.7 -> 50.1 us, 8192 x 10496 101.6 -> 71.6,
   // 3001 x 12345 64.9 -> 48.6.
   // Rows of up to 512 columns are one vector per lane (as half of two, us: LayerNorm 65536 x 100 28.8 -> 21.0, 25535 x 337 16.4 -> 12.5,
@@ -1394,45 +1395,59 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   int ch = 1, wpr = 1;
   while (ch < 8 && ch * 512 < N) ch *= 2;
   while (ch * wpr * 512 < N) wpr *= 2;
-  if (N == 8192 || N == 16384) { ch = 16; wpr /= 2; }
+  if (N == 16384) { ch = 16; wpr /= 2; }
   DeviceInfo di;
   if (!device_info(&di)) return;
   // A row that starts at any element, one of few: a wavefront's own work on it is the call's time, so it takes two vectors per
   // lane where the wavefronts are there for it.  LayerNorm, us: 16 x 2071 8.8 -> 4.6, 512 x 3001 9.0 -> 4.7, 16 x 5003 8.8 -> 4.5;
   // 2048 x 4097 and beyond are faster the other way.
   const int spread = ch * wpr / 2;
-  if (N % 8 != 0 && spread >= 2 && spread <= 8 && M * spread <= (int64_t)di.cus * 32) { ch = 2; wpr = spread; }
+  const bool few = N % 8 != 0 && spread >= 2 && spread <= 8 && M * spread <= (int64_t)di.cus * 32;
+  // Rows of exactly 4096 and 8192 always do, the next of a workgroup's rows in flight beside it in three or two workgroups per compute
+  // unit; a lane with 8 or 16 vectors left a fraction of the wavefronts.  us, before / so: RMSNorm 16384 x 4096 49.6 / 41.2, LayerNorm 64 x
+  // 4096 4.6 / 3.3, 16384 x 4096 50.5 / 43.3, 65536 x 4096 191 / 182, 4096 x 8192 30.3 / 23.2, 65536 x 8192 390 / 369; inference with
+  // K = 128, 8192 x 4096 54.9 / 47.6, 65536 x 8192 630 / 599.  (Between 1024 and 4096 rows of 4096 the normalisation of GELU has too few
+  // rows for what a workgroup sets up: 2048 22.3 / 23.6.  2048 columns are 10 % slower so, other widths 5 to 15 %.)
+  const bool whole = N == 8192 || (N == 4096 && (ACT != ACT_GELU || M <= 1024 || M >= 4096));
+  if (few || whole) { ch = 2; wpr = spread; }
   const int fit = ch > 1 && N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
+  // (a stand-alone norm of more than the memory-side cache holds is faster past the caches: 65536 x 8192 404 us, so 369; one of less the
+  // other way: RMSNorm 16384 x 4096 45.1, so 41.2)
+  const bool past_caches = whole && ACT != ACT_GELU && M * N * 2 > kMemorySideCache;
   const int nt = 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
   const int64_t per_wg = nt / 64 / wpr;
   int64_t wgs = (M + per_wg - 1) / per_wg;
-  const int64_t cap = (int64_t)di.cus * (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (ch == 1 ? 8 : (16 / ch > wpr ? 16 / ch / wpr : 1)));
+  const int64_t per_cu = whole && !past_caches ? (ACT == ACT_GELU && N == 4096 ? 3 : 4)
+                                              : (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (ch == 1 ? 8 : (16 / ch > wpr ? 16 / ch / wpr : 1)));
+  const int64_t cap = (int64_t)di.cus * per_cu;
   if (wgs > cap) wgs = cap;
 #define FDL_F2R(CHH, FIT, WPR)                                                                                        \
   launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
+#define FDL_F2R_FEW(WPR)                                                                                              \
+  do {                                                                                                                \
+    if (fit == FIT_ANY) FDL_F2R(2, FIT_ANY, WPR); else if (past_caches) FDL_F2R(2, FIT_FULL, WPR);                     \
+    else FDL_F2R(2, FIT_VECTORS, WPR);                                                                                 \
+  } while (0)
 #define FDL_F2R_FIT(FIT)                                                                                              \
   do {                                                                                                                \
     if (ch == 1) FDL_F2R(1, FIT, 1); else if (ch == 2) FDL_F2R(2, FIT, 1); else if (ch == 4) FDL_F2R(4, FIT, 1);        \
     else if (wpr == 1) FDL_F2R(8, FIT, 1);                                                                             \
     else if (wpr == 2) FDL_F2R(8, FIT, 2); else if (wpr == 4) FDL_F2R(8, FIT, 4); else FDL_F2R(8, FIT, 8);            \
   } while (0)
-  if (fit == FIT_FULL) {
+  if (ch == 2 && wpr > 1) {
+    if (wpr == 2) FDL_F2R_FEW(2); else if (wpr == 4) FDL_F2R_FEW(4); else FDL_F2R_FEW(8);
+  } else if (fit == FIT_FULL) {
     if (ch == 2) FDL_F2R(2, FIT_FULL, 1); else if (ch == 4) FDL_F2R(4, FIT_FULL, 1);
     else if (ch == 8 && wpr == 1) FDL_F2R(8, FIT_FULL, 1); else if (ch == 8) FDL_F2R(8, FIT_FULL, 8);
-    else if (wpr == 1) FDL_F2R(16, FIT_FULL, 1); else FDL_F2R(16, FIT_FULL, 2);
+    else FDL_F2R(16, FIT_FULL, 2);
   } else if (fit == FIT_VECTORS) {
     FDL_F2R_FIT(FIT_VECTORS);
-  } else if (ch == 2 && wpr == 2) {
-    FDL_F2R(2, FIT_ANY, 2);
-  } else if (ch == 2 && wpr == 4) {
-    FDL_F2R(2, FIT_ANY, 4);
-  } else if (ch == 2 && wpr == 8) {
-    FDL_F2R(2, FIT_ANY, 8);
   } else {
     FDL_F2R_FIT(FIT_ANY);
   }
 #undef FDL_F2R_FIT
+#undef FDL_F2R_FEW
 #undef FDL_F2R
 }
 
