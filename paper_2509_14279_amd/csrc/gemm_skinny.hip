@@ -13,8 +13,14 @@
 // 16 x 11008 x 4096 24 (3.8 TB/s); gated 16 x 4096 x 11008 46 (3.9 TB/s).  The 64 x 64 tiles of the generic kernel took 93 us
 // for 32 x 4096 x 4096 (64 workgroups, each alone with 256 slices) and 158 for each product of the 16-row block.  Loads of W
 // past the caches cost 10 - 20 %; 16 steps in flight gain nothing over 8.
+// A compute unit's vector cache has room for 256 lines, which is what limits the loads in flight, X's among them: 1024 lines of either
+// matrix take a compute unit 4 us (32 x 4096 x 4096: 7 us without the loads of X, 15 with).  A fragment's 64-byte pieces of 16 rows
+// hold a line for half of its bytes; from kLinesFrom on a load therefore takes 128 bytes of 8 rows, and lanes exchange what is
+// not theirs (as_fragments).
 #include "common.hip.h"
 #include "internal.h"
+
+#include <type_traits>
 
 namespace fdl {
 namespace {
@@ -40,9 +46,44 @@ template <bool AL> __device__ __forceinline__ bf16x8 load8(const bf16_t* p) {
     return *reinterpret_cast<const bf16x8_u*>(p);
   }
 }
+typedef __attribute__((address_space(1))) const char global_char;
+// 16 bytes at a wave-uniform base and a lane's byte offset (one address register)
+template <bool AL> __device__ __forceinline__ bf16x8 load8(const bf16_t* base, uint32_t off) {
+  asm("" : "+s"(base), "+v"(off));     // (not to be added up ahead of the loop, in twice the registers)
+  if constexpr (AL) {
+    return *(__attribute__((address_space(1))) const bf16x8*)((global_char*)base + off);
+  } else {
+    typedef __bf16 bf16x8_u __attribute__((ext_vector_type(8), aligned(2)));
+    return *(__attribute__((address_space(1))) const bf16x8_u*)((global_char*)base + off);
+  }
+}
+// v without its first `skip` elements (8 and more: without any), zeros in their place
+__device__ __forceinline__ bf16x8 clear_front(bf16x8 v, int skip) {
+  if (skip <= 0) return v;
+  unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
+  x = skip >= 8 ? 0 : x >> (16 * skip) << (16 * skip);
+  return __builtin_bit_cast(bf16x8, x);
+}
+
+// Two loads of 64 reduction indices of 16 rows: lane l has chunk l / 8 (of 16 bytes) of row l % 8 in lo and of row 8 + l % 8 in hi,
+// so that each row's piece is 128 contiguous bytes.  As fragments - lane l: row l % 16, its eight reduction indices the chunk
+// 2 (l / 16) in the first, the next one in the second - lanes 8 apart exchange one of their vectors.
+__device__ __forceinline__ void as_fragments(bf16x8& lo, bf16x8& hi, bool upper) {
+  typedef __attribute__((ext_vector_type(4))) int i32x4;
+  i32x4 a = __builtin_bit_cast(i32x4, lo), b = __builtin_bit_cast(i32x4, hi);
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    const int give = upper ? a[e] : b[e];
+    const int get = __builtin_amdgcn_update_dpp(0, give, 0x128 /* row_ror:8 */, 0xf, 0xf, true);
+    if (upper) a[e] = get; else b[e] = get;
+  }
+  lo = __builtin_bit_cast(bf16x8, a);
+  hi = __builtin_bit_cast(bf16x8, b);
+}
 
 // AL: K is a multiple of 8 (every row starts on 16 bytes); otherwise the same loads from element-aligned addresses.
-template <int MB, int NB, int EPI, int WAVES, int U, bool AL>
+// LINES (K >= kLinesFrom): loads of whole lines, U steps of 64 in flight; otherwise of 64 bytes of 16 rows, U steps of 32.
+template <int MB, int NB, int EPI, int WAVES, int U, bool AL, bool LINES>
 __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p) {
   constexpr int NMAT = EPI == SK_GATE ? 2 : 1;
   constexpr int NF = NMAT * NB;                      // W fragments per step
@@ -59,20 +100,6 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
   if (n0 >= p.N) return;                             // (the grid is rounded up to whole groups of 8)
 
   // rows past the end of either matrix read the last row; what they contribute is not stored
-  const bf16_t* wp[NF];
-  const bf16_t* xp[MB];
-#pragma unroll
-  for (int f = 0; f < NF; f++) {
-    int n = n0 + (f % NB) * 16 + l16;
-    n = n < p.N ? n : p.N - 1;
-    wp[f] = (f < NB ? p.W : p.W2) + (int64_t)n * p.K + g * 8;
-  }
-#pragma unroll
-  for (int b = 0; b < MB; b++) {
-    int m = m0 + b * 16 + l16;
-    m = m < p.M ? m : p.M - 1;
-    xp[b] = p.X + (int64_t)m * p.K + g * 8;
-  }
   f32x4 acc[NF][MB];
 #pragma unroll
   for (int f = 0; f < NF; f++)
@@ -81,42 +108,134 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
 #pragma unroll
       for (int r = 0; r < 4; r++) acc[f][b][r] = 0.0f;
 
-  const int full = (int)(p.K >> 5);                  // whole steps of 32
-  // groups of U steps are dealt over the wavefronts in turn: together they walk 64 U WAVES contiguous bytes of each row
-  for (int s = wave * U; s < full; s += WAVES * U) {
-    bf16x8 w[U][NF], x[U][MB];
+  if constexpr (LINES) {
+    const bool upper = (lane & 8) != 0;
+    const bf16_t* wb[NF];                            // first row of each block of 16
+    const bf16_t* xb[MB];
+    uint32_t wo[NF][2], xo[MB][2];                   // the lane's bytes from there (K is at most 2^24)
+    auto offset = [&](int h, int last) __attribute__((always_inline)) {
+      const int r = h * 8 + (lane & 7);
+      return (uint32_t)(r < last ? r : last) * (uint32_t)p.K * 2u + (uint32_t)(lane >> 3) * 16u;
+    };
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int64_t k = (int64_t)(s + u < full ? s + u : full - 1) * 32;   // past the end: the last step again, unused
+    for (int f = 0; f < NF; f++) {
+      const int n = n0 + (f % NB) * 16, at = n < p.N ? n : p.N - 1;
+      wb[f] = (f < NB ? p.W : p.W2) + (int64_t)at * p.K;
 #pragma unroll
-      for (int f = 0; f < NF; f++) w[u][f] = load8<AL>(wp[f] + k);
-#pragma unroll
-      for (int b = 0; b < MB; b++) x[u][b] = load8<AL>(xp[b] + k);
+      for (int h = 0; h < 2; h++) wo[f][h] = offset(h, p.N - 1 - at);
     }
 #pragma unroll
-    for (int u = 0; u < U; u++)
-      if (s + u < full) {                            // wave-uniform
+    for (int b = 0; b < MB; b++) {
+      const int m = m0 + b * 16, at = m < p.M ? m : p.M - 1;
+      xb[b] = p.X + (int64_t)at * p.K;
 #pragma unroll
-        for (int f = 0; f < NF; f++)
-#pragma unroll
-          for (int b = 0; b < MB; b++) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][f], x[u][b], acc[f][b], 0, 0, 0);
+      for (int h = 0; h < 2; h++) xo[b][h] = offset(h, p.M - 1 - at);
+    }
+    const int full = (int)(p.K >> 6);                  // whole steps of 64
+    // C steps from reduction index k0 on; LAST: the first `skip` indices have been counted
+    auto steps = [&](auto count, auto last, int64_t k0, int skip) __attribute__((always_inline)) {
+      constexpr int C = decltype(count)::value;
+      constexpr bool LAST = decltype(last)::value;
+      bf16x8 w[C][NF][2], x[C][MB][2];
+  #pragma unroll
+      for (int u = 0; u < C; u++) {
+        const int64_t k = k0 + u * 64;
+  #pragma unroll
+        for (int h = 0; h < 2; h++) {
+  #pragma unroll
+          for (int f = 0; f < NF; f++) w[u][f][h] = load8<AL>(wb[f] + k, wo[f][h]);
+  #pragma unroll
+          for (int b = 0; b < MB; b++) x[u][b][h] = load8<AL>(xb[b] + k, xo[b][h]);
+        }
       }
-  }
-  if ((p.K & 31) != 0 && wave == WAVES - 1) {        // the last, partial step: element by element, zeros past the end
-    const int64_t k = (int64_t)full * 32;
-    bf16x8 w[NF], x[MB];
+      if (LAST) {
+        const int clear = skip - (lane >> 3) * 8;
+  #pragma unroll
+        for (int h = 0; h < 2; h++) {
+  #pragma unroll
+          for (int f = 0; f < NF; f++) w[0][f][h] = clear_front(w[0][f][h], clear);
+  #pragma unroll
+          for (int b = 0; b < MB; b++) x[0][b][h] = clear_front(x[0][b][h], clear);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);               // (all loads first: the scheduler would have few in flight to save registers)
+  #pragma unroll
+      for (int u = 0; u < C; u++) {
+  #pragma unroll
+        for (int f = 0; f < NF; f++) as_fragments(w[u][f][0], w[u][f][1], upper);
+  #pragma unroll
+        for (int b = 0; b < MB; b++) as_fragments(x[u][b][0], x[u][b][1], upper);
+  #pragma unroll
+        for (int h = 0; h < 2; h++)
+  #pragma unroll
+          for (int f = 0; f < NF; f++)
+  #pragma unroll
+            for (int b = 0; b < MB; b++)
+              acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][f][h], x[u][b][h], acc[f][b], 0, 0, 0);
+      }
+    };
+    // Groups of U steps are dealt over the wavefronts in turn - together they walk 128 U WAVES contiguous bytes of each row - then
+    // single ones.  (No condition inside a group: under one, a step's loads sink to where it uses them.)
+    typedef std::integral_constant<int, U> group;
+    typedef std::integral_constant<int, 1> single;
+    int s = wave * U;
+    for (; s + U <= full; s += WAVES * U) steps(group(), std::false_type(), (int64_t)s * 64, 0);
+    for (s = full / U * U + WAVES - 1 - wave; s < full; s += WAVES) steps(single(), std::false_type(), (int64_t)s * 64, 0);
+    if ((p.K & 63) != 0 && wave == WAVES / 2 - 1)
+      // what is left: the last 64 indices, without those of them that whole steps have counted
+      steps(single(), std::true_type(), p.K - 64, 64 - (int)(p.K & 63));
+  } else {
+    const bf16_t* wp[NF];
+    const bf16_t* xp[MB];
 #pragma unroll
-    for (int e = 0; e < 8; e++) {
-      const bool in = k + g * 8 + e < p.K;
-#pragma unroll
-      for (int f = 0; f < NF; f++) w[f][e] = in ? wp[f][k + e] : (bf16_t)0.0f;
-#pragma unroll
-      for (int b = 0; b < MB; b++) x[b][e] = in ? xp[b][k + e] : (bf16_t)0.0f;
+    for (int f = 0; f < NF; f++) {
+      int n = n0 + (f % NB) * 16 + l16;
+      n = n < p.N ? n : p.N - 1;
+      wp[f] = (f < NB ? p.W : p.W2) + (int64_t)n * p.K + g * 8;
     }
 #pragma unroll
-    for (int f = 0; f < NF; f++)
+    for (int b = 0; b < MB; b++) {
+      int m = m0 + b * 16 + l16;
+      m = m < p.M ? m : p.M - 1;
+      xp[b] = p.X + (int64_t)m * p.K + g * 8;
+    }
+    const int full = (int)(p.K >> 5);                // whole steps of 32
+    // groups of U steps are dealt over the wavefronts in turn: together they walk 64 U WAVES contiguous bytes of each row
+    for (int s = wave * U; s < full; s += WAVES * U) {
+      bf16x8 w[U][NF], x[U][MB];
 #pragma unroll
-      for (int b = 0; b < MB; b++) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[f], x[b], acc[f][b], 0, 0, 0);
+      for (int u = 0; u < U; u++) {
+        const int64_t k = (int64_t)(s + u < full ? s + u : full - 1) * 32;   // past the end: the last step again, unused
+#pragma unroll
+        for (int f = 0; f < NF; f++) w[u][f] = load8<AL>(wp[f] + k);
+#pragma unroll
+        for (int b = 0; b < MB; b++) x[u][b] = load8<AL>(xp[b] + k);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (s + u < full) {                          // wave-uniform
+#pragma unroll
+          for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int b = 0; b < MB; b++) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][f], x[u][b], acc[f][b], 0, 0, 0);
+        }
+    }
+    if ((p.K & 31) != 0 && wave == WAVES - 1) {      // the last, partial step: element by element, zeros past the end
+      const int64_t k = (int64_t)full * 32;
+      bf16x8 w[NF], x[MB];
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        const bool in = k + g * 8 + e < p.K;
+#pragma unroll
+        for (int f = 0; f < NF; f++) w[f][e] = in ? wp[f][k + e] : (bf16_t)0.0f;
+#pragma unroll
+        for (int b = 0; b < MB; b++) x[b][e] = in ? xp[b][k + e] : (bf16_t)0.0f;
+      }
+#pragma unroll
+      for (int f = 0; f < NF; f++)
+#pragma unroll
+        for (int b = 0; b < MB; b++) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[f], x[b], acc[f][b], 0, 0, 0);
+    }
   }
 
   // pairwise over the wavefronts: the upper half hands its sums to the lower half until one is left
@@ -182,12 +301,17 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
   }
 }
 
+// Reduction length from which whole lines are loaded (feed-forward block, us, 64-byte pieces / lines: 16 x 4096 x 11008 62.0 / 57.1,
+// 1 x 4096 x 11008 52.8 / 48.5; at K = 1024 to 2000 equal within 2 %, below 1024 3 to 6 % slower: two steps of a wavefront or fewer).
+constexpr int64_t kLinesFrom = 2048;
 template <int MB, int NB, int EPI, int WAVES, int U> void launch_skinny(SkinnyParams p, hipStream_t s) {
   p.mblocks = (p.M + 16 * MB - 1) / (16 * MB);
   const int strips = (p.N + 16 * NB - 1) / (16 * NB);
   const unsigned grid = (unsigned)((strips + 7) / 8 * 8) * (unsigned)p.mblocks;
-  if (p.K % 8 == 0) hipLaunchKernelGGL((gemm_skinny_kernel<MB, NB, EPI, WAVES, U, true>), dim3(grid), dim3(64 * WAVES), 0, s, p);
-  else hipLaunchKernelGGL((gemm_skinny_kernel<MB, NB, EPI, WAVES, U, false>), dim3(grid), dim3(64 * WAVES), 0, s, p);
+  const bool lines = p.K >= kLinesFrom;
+  auto kern = p.K % 8 == 0 ? (lines ? gemm_skinny_kernel<MB, NB, EPI, WAVES, 2, true, true> : gemm_skinny_kernel<MB, NB, EPI, WAVES, U, true, false>)
+                           : (lines ? gemm_skinny_kernel<MB, NB, EPI, WAVES, 2, false, true> : gemm_skinny_kernel<MB, NB, EPI, WAVES, U, false, false>);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WAVES), 0, s, p);
 }
 
 // Tile and depth by the number of rows: the fewer there are, the more loads of W a wavefront can hold; from 33 rows on
