@@ -32,7 +32,7 @@ bool shape_ok(int64_t M, int64_t K, int64_t N) {
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // fp32 storage: all tiles as they are, where there is no scratch for the sums of split ones
-F64Split f64_unsplit(int64_t I, int64_t J) { return F64Split{((I + 63) / 64) * ((J + 63) / 64), 0, 1}; }
+F64Split f64_unsplit(int64_t I, int64_t J, int64_t R) { return F64Split{((I + 63) / 64) * ((J + 63) / 64), 0, 1, f64_plan(I, J, R).small}; }
 
 // room for the sums of split reductions in 128 x 128 tiles; kept: what the other kernels' plan holds in their place
 constexpr size_t kMidMostSums = (size_t)64 << 20;
@@ -140,7 +140,7 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p, bool
   q.off_xtail = off; off += align256(!tiled ? 0 : (q.pad ? fast_padded_x_bytes(M, K, q.stage_x != 0) : fast_f1_tail_bytes(M, K)));
   q.off_wpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_bpad_f = off; off += align256(tiled && q.pad ? (size_t)Np * 4 : 0);
-  if (dt == kF32) q.f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
+  if (dt == kF32) q.f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N, K);
   q.f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
   q.off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q.f1_s64) : fast_xwt_part_bytes(M, N, q.f1_split));
   q.fwd_bytes_plain = off;
@@ -239,8 +239,9 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may
   q.off_wpad = *off; *off += align256(q.pad ? (size_t)Np * Kp * 2 : 0);
   q.off_xpad = *off; *off += align256(q.stage_x ? fast_padded_x_bytes(M, K, true) : 0);
   if (dt == kF32) {
-    q.s64_a = split ? f64_plan(Mp, K, N) : f64_unsplit(Mp, K);
-    q.s64_b = split ? f64_plan(N, K, Mp) : f64_unsplit(N, K);
+    q.s64_a = split ? f64_plan(Mp, K, N) : f64_unsplit(Mp, K, N);
+    q.s64_b = split ? f64_plan(N, K, Mp) : f64_unsplit(N, K, Mp);
+    q.s64_a.small = q.s64_b.small = f64_small_grads(Mp, K, N);
     q.off_part64_a = *off; *off += align256(f64_part_bytes(q.s64_a));
     q.off_part64_b = *off; *off += align256(f64_part_bytes(q.s64_b));
   }
@@ -376,7 +377,7 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
                                    char* ws, hipStream_t s) {
   const int64_t M = p.M, K = p.K, N = p.N;
   // fp32, few tiles, all split: the row kernel adds the parts up
-  const bool sums = p.dt == kF32 && p.f1_s64.split > 1 && p.f1_s64.whole == 0 && f2_takes_sums(N);
+  const bool sums = p.dt == kF32 && !p.f1_s64.small && p.f1_s64.split > 1 && p.f1_s64.whole == 0 && f2_takes_sums(N);
   F64Sums parts = {};
   {
     PhaseTimer t(FDL_PHASE_F1, s);
@@ -478,7 +479,7 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES) {
     p.pad = 0; p.f1_fast = 0; p.fwd_bytes = p.off_xtail;   // no room for the padded copies either: the generic kernel needs none,
-    p.f1_s64 = f64_unsplit(M, N);                     // nor the fp64 kernel, with all tiles whole
+    p.f1_s64 = f64_unsplit(M, N, K);                   // nor the fp64 kernel, with all tiles whole
   }
   if (!forward_args_aligned(X, W, b, gamma, beta, Y, Zsave, mean, rstd)) return FDL_ERR_ALIGN;
   if (M == 0) return FDL_OK;
@@ -625,7 +626,7 @@ extern "C" fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N
   if (dt == FDL_F32) {
     const F64Grads a = grad_f64(p.g, dZ, W, X, dX, dW, ws);
     { PhaseTimer t(FDL_PHASE_B2, s); }      // (the column sums are finished with the contractions')
-    { PhaseTimer t(FDL_PHASE_B3, s); launch_f64_grads(a, s); }
+    { PhaseTimer t(FDL_PHASE_B3, s); launch_f64_grads(a, tj, s); }
     { PhaseTimer t(FDL_PHASE_B4, s); launch_f64_grads_finish(a, tj, s); }
     return launch_status();
   }
@@ -745,7 +746,7 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan
   q->off_bpad = off; off += align256(f1 == Xwt::kPadded ? (size_t)fast_pad_dim(N) * 4 : 0);
   q->f1_wt = f1 == Xwt::kTiled && copies_weights(M, K) && q->f1_split == 1;
   q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
-  if (dt == kF32) q->f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N);
+  if (dt == kF32) q->f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N, K);
   if (q->f1_mid) q->f1_split = parts;
   const size_t sums = dt == kF32 ? f64_part_bytes(q->f1_s64) : fast_xwt_part_bytes(M, N, q->f1_split);
   q->off_part = off; off += align256(sums > kept ? sums : kept);
@@ -853,7 +854,7 @@ extern "C" fdl_status fdl_linear_relu_backward(fdl_dtype dt, int64_t M, int64_t 
   tj.colpart = static_cast<const float*>(colpart); tj.groups = colsum_groups(M); tj.N = N; tj.kinds = 1; tj.col_out[0] = db;
   if (dt == FDL_F32) {
     const F64Grads a = grad_f64(q.g, G, W, X, dX, dW, ws);
-    launch_f64_grads(a, s);
+    launch_f64_grads(a, tj, s);
     launch_f64_grads_finish(a, tj, s);
     return launch_status();
   }
@@ -958,8 +959,8 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* 
   q->gate_wt = 0;
   q->g_blocked = q->gate_fused && q->down_wt && H % 32 == 0;
   if (dt == kF32) {
-    q->up_s64 = split ? f64_plan(Mp, H, D) : f64_unsplit(Mp, H);
-    q->down_s64 = split ? f64_plan(Mp, D, H) : f64_unsplit(Mp, D);
+    q->up_s64 = split ? f64_plan(Mp, H, D) : f64_unsplit(Mp, H, D);
+    q->down_s64 = split ? f64_plan(Mp, D, H) : f64_unsplit(Mp, D, H);
   }
   const size_t up64 = dt == kF32 ? f64_part_bytes(q->up_s64) : 0;
   const size_t down = dt == kF32 ? f64_part_bytes(q->down_s64) : fast_xwt_part_bytes(M, D, q->down_split);

@@ -16,7 +16,7 @@
 //
 // A compute unit's time is the number of tiles it is dealt.  Whole rounds of 256 tiles are done as they are; the tiles of an
 // incomplete last round (or all tiles, where that is estimated to be faster) are split over the reduction in the same launch, leave fp64 sums, and
-// a second kernel adds them in order (f64_plan).
+// a second kernel adds them in order (f64_plan).  Small products are dealt out otherwise (f64_small_unit).
 // Measured, us (floor at 77 TFLOP/s): 8192 x 1024 x 1024 251 - 260 (223) for each orientation; 64-wide tiles whose operands
 // were widened at every read, with bounds in the loop, took 314 - 325 for 4096 x 1024 x 2048 (now 256 - 281).
 #include "common.hip.h"
@@ -248,6 +248,139 @@ __global__ __launch_bounds__(256) void gemm_f64_pair_kernel(F64Params dx, F64Par
   else f64_unit<true, false, F64_STORE>(dx, id - dw_units, lds);
 }
 
+// ---- small products: 32 x 32 tiles, the reduction dealt over a workgroup's four wavefronts ------------------------------------
+// Layers of a few hundred rows and columns have fewer 64 x 64 tiles than compute units, and a split of those leaves sums that another
+// launch, of 4 us whatever it does, has to add.  Here a wavefront has the whole tile (2 x 2 blocks) for every fourth step of 16 indices, takes
+// its fragments straight from memory, widened in registers, and the four sums meet in LDS, in order: no operand passes through LDS
+// and no barrier stands before the end.  Bound: latency - the launch, the first loads, 1024 cycles of MFMA per step.
+// 256^3, us, split 64 x 64 tiles / so: step 25.5 / 20.5, Linear+ReLU forward and backward 32.8 / 21.0.
+template <bool RC> struct Strip {
+  const float* at;         // RC: the lane's row at its first index; else column
+  int64_t ld;
+  __device__ __forceinline__ void init(const float* base, int64_t ld_, int64_t i, int64_t I, int g) {
+    i = i < I ? i : I - 1;                           // (past the end: the last row again, whose results are not stored)
+    ld = ld_;
+    at = RC ? base + i * ld + g * 4 : base + (int64_t)(g * 4) * ld + i;
+  }
+  __device__ __forceinline__ f32x4_e fetch(int64_t k) const {
+    if (RC) return *reinterpret_cast<const f32x4_e*>(at + k);
+    f32x4_e v;
+#pragma unroll
+    for (int e = 0; e < 4; e++) v[e] = at[(k + e) * ld];
+    return v;
+  }
+  // left: indices from the lane's first one to the end
+  __device__ __forceinline__ f32x4_e fetch_guarded(int64_t k, int64_t left) const {
+    f32x4_e v;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      // (unconditional, from the last index inside)
+      const int64_t kk = k + (e < left ? e : left - 1);
+      v[e] = at[RC ? kk : kk * ld];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; e++) v[e] = e < left ? v[e] : 0.0f;
+    return v;
+  }
+};
+
+constexpr int kSmallTile = 32, kSmallDepth = 4;      // steps a wavefront has in flight
+constexpr int kSmallLds = 4 * kSmallTile * (kSmallTile + 1);      // doubles
+inline int64_t small_tiles(int64_t I, int64_t J) { return ((I + kSmallTile - 1) / kSmallTile) * ((J + kSmallTile - 1) / kSmallTile); }
+
+template <bool A_RC, bool B_RC, int EPI>
+__device__ __forceinline__ void f64_small_unit(const F64Params& p, const int tile, double* smem) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = (int64_t)(tile / p.tiles_j) * kSmallTile, j0 = (int64_t)(tile % p.tiles_j) * kSmallTile;
+  Strip<A_RC> sa[2]; Strip<B_RC> sb[2];
+#pragma unroll
+  for (int a = 0; a < 2; a++) {
+    sa[a].init(p.A, p.lda, i0 + a * 16 + l16, p.I, g);
+    sb[a].init(p.B, p.ldb, j0 + a * 16 + l16, p.J, g);
+  }
+  f64x4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; a++)
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[a][b][r] = 0.0;
+  auto multiply = [&](const f32x4_e (&va)[2], const f32x4_e (&vb)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)va[a][s], (double)vb[b][s], acc[a][b], 0, 0, 0);
+  };
+  const int64_t full = p.R / 16, rounds = full / (4 * kSmallDepth);
+  for (int64_t t = 0; t < rounds; t++) {
+    f32x4_e va[kSmallDepth][2], vb[kSmallDepth][2];
+#pragma unroll
+    for (int u = 0; u < kSmallDepth; u++) {
+      const int64_t k = ((t * kSmallDepth + u) * 4 + wave) * 16;
+#pragma unroll
+      for (int a = 0; a < 2; a++) { va[u][a] = sa[a].fetch(k); vb[u][a] = sb[a].fetch(k); }
+    }
+    __builtin_amdgcn_sched_barrier(0);               // (all loads first)
+#pragma unroll
+    for (int u = 0; u < kSmallDepth; u++) multiply(va[u], vb[u]);
+  }
+  for (int64_t s = rounds * 4 * kSmallDepth + wave; s * 16 < p.R; s += 4) {
+    const int64_t k = s * 16, left = p.R - k - g * 4;
+    f32x4_e va[2], vb[2];
+#pragma unroll
+    for (int a = 0; a < 2; a++) {
+      if (left >= 4) {
+        va[a] = sa[a].fetch(k); vb[a] = sb[a].fetch(k);
+      } else {
+        va[a] = sa[a].fetch_guarded(k, left); vb[a] = sb[a].fetch_guarded(k, left);
+      }
+    }
+    multiply(va, vb);
+  }
+  constexpr int kRow = kSmallTile + 1;
+  double* mine = smem + wave * kSmallTile * kRow;
+#pragma unroll
+  for (int a = 0; a < 2; a++)
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) mine[(a * 16 + r * 4 + g) * kRow + b * 16 + l16] = acc[a][b][r];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    const int at = e * 256 + (int)threadIdx.x, row = at >> 5, col = at & 31;
+    double z = smem[row * kRow + col];
+#pragma unroll
+    for (int w = 1; w < 4; w++) z += smem[(w * kSmallTile + row) * kRow + col];
+    const int64_t i = i0 + row, j = j0 + col;
+    if (i < p.I && j < p.J) finish_element<EPI>(p, i, j, z + (p.bias != nullptr ? (double)p.bias[j] : 0.0));
+  }
+}
+
+template <bool A_RC, bool B_RC, int EPI>
+__global__ __launch_bounds__(256) void gemm_f64_small_kernel(F64Params p) {
+  __shared__ double smem[kSmallLds];
+  f64_small_unit<A_RC, B_RC, EPI>(p, (int)blockIdx.x, smem);
+}
+// dW, dX and, behind them, the column sums (as f64_finish_kernel's)
+__global__ __launch_bounds__(256) void gemm_f64_small_pair_kernel(F64Params dx, F64Params dw, int dw_units, int units, TailSums j) {
+  __shared__ double smem[kSmallLds];
+  const int id = (int)blockIdx.x;
+  if (id >= units) {
+    const int cblocks = (int)((j.N + 63) / 64), which = (id - units) / cblocks;
+    b2_columns<double, 4>(j.N, j.groups, j.kinds, reinterpret_cast<const double*>(j.colpart), (id - units) % cblocks, which,
+                          which == 0 ? j.col_out[0] : (which == 1 ? j.col_out[1] : j.col_out[2]), reinterpret_cast<double (*)[64]>(smem));
+  } else if (id < dw_units) {
+    f64_small_unit<false, false, F64_STORE>(dw, id, smem);
+  } else {
+    f64_small_unit<true, false, F64_STORE>(dx, id - dw_units, smem);
+  }
+}
+
 // the split tiles' outputs: the parts' sums in order, then as above; 1024 elements of a tile from `at`, four per thread
 template <int EPI> __device__ __forceinline__ void f64_reduce_tile(const F64Params& p, int split, int t, int at) {
   const int tile = p.whole + t;
@@ -289,15 +422,21 @@ __global__ __launch_bounds__(1024) void f64_finish_kernel(F64Params dx, int spli
 // are the better schedule (758 x 2048 x 2304: step 398 us with two launches, 427 with one).
 constexpr int kF64Resident = 1024;
 
-template <int EPI> void dispatch_f64_main(const GemmDesc& g, const F64Params& p, int split, hipStream_t s) {
-  const dim3 grid((unsigned)f64_units(p, split));
+template <int EPI> void dispatch_f64_main(const GemmDesc& g, const F64Params& p, const F64Split& q, hipStream_t s) {
+  if (q.small) {
+    auto kern = g.a_rc ? (g.b_rc ? gemm_f64_small_kernel<true, true, EPI> : gemm_f64_small_kernel<true, false, EPI>)
+                       : (g.b_rc ? gemm_f64_small_kernel<false, true, EPI> : gemm_f64_small_kernel<false, false, EPI>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)small_tiles(p.I, p.J)), dim3(256), 0, s, p);
+    return;
+  }
+  const dim3 grid((unsigned)f64_units(p, q.split));
   auto kern = g.a_rc ? (g.b_rc ? gemm_f64_kernel<true, true, EPI> : gemm_f64_kernel<true, false, EPI>)
                      : (g.b_rc ? gemm_f64_kernel<false, true, EPI> : gemm_f64_kernel<false, false, EPI>);
   hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
 }
-template <int EPI> void dispatch_f64(const GemmDesc& g, const F64Params& p, int split, hipStream_t s) {
-  dispatch_f64_main<EPI>(g, p, split, s);
-  if (p.parted > 0) hipLaunchKernelGGL(f64_reduce_kernel<EPI>, dim3((unsigned)p.parted * 4), dim3(256), 0, s, p, split);
+template <int EPI> void dispatch_f64(const GemmDesc& g, const F64Params& p, const F64Split& q, hipStream_t s) {
+  dispatch_f64_main<EPI>(g, p, q, s);
+  if (p.parted > 0) hipLaunchKernelGGL(f64_reduce_kernel<EPI>, dim3((unsigned)p.parted * 4), dim3(256), 0, s, p, q.split);
 }
 
 }  // namespace
@@ -308,11 +447,12 @@ template <int EPI> void dispatch_f64(const GemmDesc& g, const F64Params& p, int 
 // or all of them.  Measured, us, without / with the split: 3001 x 771 x 1537 by reduction over 771 (1175 tiles) 143 / 133,
 // over 1537 (611) 166 / 140, over 3001 (325, all in 3 parts) 199 / 148; 256^3 (16 tiles, 8 parts) 14.5 / 11; 512^3 24.5 / 16;
 // 128 x 4096 x 1024 (32 tiles) 159 / 30.  The plan must not depend on the device: 256 compute units.
+constexpr int64_t kF64MaxSmall = 1024;      // 32 x 32 tiles
 constexpr int64_t kF64MaxUnits = 2048;      // parts of 32 KB each: at most 64 MB
 F64Split f64_plan(int64_t I, int64_t J, int64_t R) {
   const int64_t tiles = ((I + 63) / 64) * ((J + 63) / 64), slices = (R + 15) / 16;
   const int64_t full = tiles / 256, rest = tiles % 256;
-  F64Split best = {tiles, 0, 1};
+  F64Split best = {tiles, 0, 1, 0};
   double best_cost = (double)slices * ((full == 1 && rest == 0 ? 0.68 : full * 0.52) + (rest == 0 ? 0.0 : (full >= 4 ? 0.75 : (full == 0 ? 0.68 : 0.55))));
   for (int split = 2; split <= 16 && split <= slices; split++)
     for (int all = 0; all < 2; all++) {
@@ -324,7 +464,21 @@ F64Split f64_plan(int64_t I, int64_t J, int64_t R) {
       cost += 4.0 + units * 0.006 + split * 0.15;
       if (cost < (best.split == 1 ? 0.97 : 1.0) * best_cost) { best.whole = rounds * 256; best.parted = parted; best.split = split; best_cost = cost; }
     }
+  // 32 x 32 tiles, all of them whole: a step of 64 indices 0.67 us, two tiles on a compute unit twice that.  Inference, us, before / so: 256 x 256
+  // x 256 11.2 / 10.7, 512 x 512 x 512 17.3 / 14.6, 500 x 1024 x 512 25.2 / 19.7, 1000 x 200 x 300 18.0 / 14.4; not taken 256 x 1024 x 256 14.1 / 19.2,
+  // 1024 x 1024 x 1024 46.2 / 48.8; feed-forward 256 x 512 x 1024 48.4 / 37.2, 100 x 1024 x 2000 63.4 / 52.2.
+  const int64_t small = small_tiles(I, J);
+  if (small <= kF64MaxSmall && 3.0 + (double)((small + 255) / 256) * (double)((slices + 3) / 4) * 0.67 < 0.92 * best_cost) best.small = 1;
   return best;
+}
+// Both gradients in 32 x 32 tiles, in one launch with the column sums, which takes the finishing launch away.  Two steps of 16 rows of an
+// operand whose rows are reduction indices are 32 loads, so the work of a compute unit (steps of 64) and the longest reduction are
+// bounded.  Steps, us, before / so (less what the forward pass gained): 256 x 256 x 256 25.5 / 20.5 (0.6), 300 x 300 x 700 44.3 / 36.6
+// (2.7), 1000 x 200 x 300 43.3 / 36.5 (3.6), 256 x 512 x 1024 49.6 / 44.6 (2.3); beyond: 256 x 2048 x 256 41.9 / 44.4 (0), 333 x 777 x 555 53.4 / 52.4 (3.6), 2000 x 128 x 256
+// 40.6 / 48.1 (2.3), 1024 x 1024 x 1024 139 / 168.
+bool f64_small_grads(int64_t M, int64_t K, int64_t N) {
+  const int64_t tx = small_tiles(M, K), tw = small_tiles(N, K), sx = (N + 63) / 64, sw = (M + 63) / 64;
+  return tx <= kF64MaxSmall && tw <= kF64MaxSmall && sx <= 16 && sw <= 16 && tx + tw <= 768 && tx * sx + tw * sw <= 16 * 256;
 }
 size_t f64_part_bytes(const F64Split& q) { return q.split > 1 ? (size_t)q.parted * q.split * 4096 * 8 : 0; }
 
@@ -338,35 +492,44 @@ static F64Params f64_params(const GemmDesc& g, const F64Split& q, const float* b
   p.tiles_j = (int)((g.J + 63) / 64);
   p.whole = (int)q.whole; p.parted = (int)q.parted;
   const int64_t slices = (g.R + 15) / 16;
+  if (q.small) { p.whole = p.parted = 0; p.tiles_j = (int)((g.J + kSmallTile - 1) / kSmallTile); return p; }
   p.rlen = (slices + q.split - 1) / q.split * 16;
   return p;
 }
 void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
                 hipStream_t s) {
   const F64Params p = f64_params(g, q, bias, aux, C, part);
-  if (kind == 1) dispatch_f64<F64_RELU>(g, p, q.split, s);
-  else if (kind == 2) dispatch_f64<F64_MASK>(g, p, q.split, s);
-  else dispatch_f64<F64_STORE>(g, p, q.split, s);
+  if (kind == 1) dispatch_f64<F64_RELU>(g, p, q, s);
+  else if (kind == 2) dispatch_f64<F64_MASK>(g, p, q, s);
+  else dispatch_f64<F64_STORE>(g, p, q, s);
 }
 
 F64Sums launch_f64_parts(const GemmDesc& g, const F64Split& q, const float* bias, void* Z, void* part, hipStream_t s) {
   const F64Params p = f64_params(g, q, bias, nullptr, Z, part);
-  dispatch_f64_main<F64_STORE>(g, p, q.split, s);
+  dispatch_f64_main<F64_STORE>(g, p, q, s);
   return F64Sums{(const double*)part, bias, (float*)Z, (int64_t)p.parted * 4096, q.split, p.tiles_j};
 }
 
-// dX (rows of dZ times W) and dW (columns of dZ times X); launch_f64_grads_finish ends both, and the column sums
-void launch_f64_grads(const F64Grads& a, hipStream_t s) {
+// dX (rows of dZ times W) and dW (columns of dZ times X); launch_f64_grads_finish ends both, and the column sums j, unless both are
+// small: then this launch does all
+void launch_f64_grads(const F64Grads& a, const TailSums& j, hipStream_t s) {
   const F64Params dx = f64_params(a.dx, a.qx, nullptr, nullptr, a.dX, a.partx), dw = f64_params(a.dw, a.qw, nullptr, nullptr, a.dW, a.partw);
+  if (a.qx.small && a.qw.small) {
+    const int nw = (int)small_tiles(dw.I, dw.J), nx = (int)small_tiles(dx.I, dx.J);
+    const unsigned blocks = (unsigned)(nw + nx) + (unsigned)j.kinds * (unsigned)((j.N + 63) / 64);
+    hipLaunchKernelGGL(gemm_f64_small_pair_kernel, dim3(blocks), dim3(256), 0, s, dx, dw, nw, nw + nx, j);
+    return;
+  }
   const int nw = f64_units(dw, a.qw.split), nx = f64_units(dx, a.qx.split);
   if (nw + nx > kF64Resident) {
-    dispatch_f64_main<F64_STORE>(a.dx, dx, a.qx.split, s);
-    dispatch_f64_main<F64_STORE>(a.dw, dw, a.qw.split, s);
+    dispatch_f64_main<F64_STORE>(a.dx, dx, a.qx, s);
+    dispatch_f64_main<F64_STORE>(a.dw, dw, a.qw, s);
     return;
   }
   hipLaunchKernelGGL(gemm_f64_pair_kernel, dim3((unsigned)(nw + nx)), dim3(256), 0, s, dx, dw, nw);
 }
 void launch_f64_grads_finish(const F64Grads& a, const TailSums& j, hipStream_t s) {
+  if (a.qx.small && a.qw.small) return;
   const F64Params dx = f64_params(a.dx, a.qx, nullptr, nullptr, a.dX, a.partx), dw = f64_params(a.dw, a.qw, nullptr, nullptr, a.dW, a.partw);
   const unsigned blocks = (unsigned)(dx.parted + dw.parted) + (unsigned)j.kinds * (unsigned)((j.N + 63) / 64);
   hipLaunchKernelGGL(f64_finish_kernel, dim3(blocks), dim3(1024), 0, s, dx, a.qx.split, dw, a.qw.split, j);

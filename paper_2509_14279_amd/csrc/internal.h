@@ -18,7 +18,8 @@ namespace fdl {
 enum DType { kF32 = 0, kBF16 = 1 };
 
 // How a product in fp64 is dealt out (gemm_f64.hip): tiles done as a whole, tiles split into `split` parts
-struct F64Split { int64_t whole, parted; int split; };
+// (small: in 32 x 32 tiles, none split; the rest, and the room, are what would be otherwise)
+struct F64Split { int64_t whole, parted; int split, small; };
 
 // The two contractions that end a backward pass: dX [M,K] = dZ W, dW [N,K] = dZ^T X.
 struct GradPlan {
@@ -122,6 +123,7 @@ void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s);
 
 // ---- fp32-storage contractions in fp64 (gemm_f64.hip): GemmDesc as above, any shape ---------------
 F64Split f64_plan(int64_t I, int64_t J, int64_t R);
+bool f64_small_grads(int64_t M, int64_t K, int64_t N);
 size_t f64_part_bytes(const F64Split& q);
 void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
                 hipStream_t s);
@@ -175,7 +177,7 @@ void launch_finish(TailSums j, hipStream_t s);
 // fp32 storage: both gradient contractions in one launch; then their split tiles' sums and the column sums (j.colpart holds
 // doubles, j's split products unused) in another
 struct F64Grads { GemmDesc dx, dw; F64Split qx, qw; void *dX, *partx, *dW, *partw; };
-void launch_f64_grads(const F64Grads& a, hipStream_t s);
+void launch_f64_grads(const F64Grads& a, const TailSums& j, hipStream_t s);
 void launch_f64_grads_finish(const F64Grads& a, const TailSums& j, hipStream_t s);
 
 // ---- sibling operators' row-wise / element-wise kernels ------------------------------------------

@@ -1404,16 +1404,16 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   const int spread = ch * wpr / 2;
   const bool few = N % 8 != 0 && spread >= 2 && spread <= 8 && M * spread <= (int64_t)di.cus * 32;
   // Rows of exactly 4096 and 8192 always do, the next of a workgroup's rows in flight beside it in three or two workgroups per compute
-  // unit; a lane with 8 or 16 vectors left a fraction of the wavefronts.  us, before / so: RMSNorm 16384 x 4096 49.6 / 41.2, LayerNorm 64 x
+  // unit; a lane with 8 or 16 vectors left a fraction of the wavefronts.  us, before / so: RMSNorm 16384 x 4096 50.0 / 44.7, LayerNorm 64 x
   // 4096 4.6 / 3.3, 16384 x 4096 50.5 / 43.3, 65536 x 4096 191 / 182, 4096 x 8192 30.3 / 23.2, 65536 x 8192 390 / 369; inference with
   // K = 128, 8192 x 4096 54.9 / 47.6, 65536 x 8192 630 / 599.  (Between 1024 and 4096 rows of 4096 the normalisation of GELU has too few
   // rows for what a workgroup sets up: 2048 22.3 / 23.6.  2048 columns are 10 % slower so, other widths 5 to 15 %.)
   const bool whole = N == 8192 || (N == 4096 && (ACT != ACT_GELU || M <= 1024 || M >= 4096));
   if (few || whole) { ch = 2; wpr = spread; }
   const int fit = ch > 1 && N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
-  // (a stand-alone norm of more than the memory-side cache holds is faster past the caches: 65536 x 8192 404 us, so 369; one of less the
-  // other way: RMSNorm 16384 x 4096 45.1, so 41.2)
-  const bool past_caches = whole && ACT != ACT_GELU && M * N * 2 > kMemorySideCache;
+  // (A stand-alone norm whose input and output together fill the memory-side cache is faster past the caches: LayerNorm
+  // 65536 x 8192 404 us, so 369, RMSNorm 16384 x 4096 48.0, so 44.7.)
+  const bool past_caches = whole && ACT != ACT_GELU && M * N * 4 >= kMemorySideCache;
   const int nt = 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
   const int64_t per_wg = nt / 64 / wpr;
