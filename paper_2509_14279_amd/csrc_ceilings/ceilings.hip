@@ -2,7 +2,7 @@
 // the LDS deliver to the simplest possible kernels.  Benchmark support only: built into its own shared object
 // (libfdl_ceilings.so), never linked into libfdl.so.  C ABI; every call enqueues kernels on the given stream.
 //
-//   fdlc_mfma_bf16      register-resident v_mfma_f32_32x32x16_bf16 loop, one or two waves per SIMD on every CU
+//   fdlc_mfma_bf16      register-resident v_mfma_f32_16x16x32_bf16 loop, one or two waves per SIMD on every CU
 //   fdlc_mfma_f64       the same for v_mfma_f64_16x16x4_f64 (the fp32-storage path's instruction)
 //   fdlc_stream_*       read-only / write-only / copy / two-reads-one-write over large buffers, 16 bytes per lane,
 //                       non-temporal
@@ -18,7 +18,7 @@ namespace {
 
 typedef __bf16 bf16_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
@@ -34,32 +34,35 @@ __device__ __forceinline__ bf16_t pseudo(uint32_t i) {
 }
 
 // ---------------------------------------------------------------------------------------------- MFMA
-// 4 x NB independent accumulator blocks, 4 + NB operand fragments, all in registers.  NB = 4 with one wave per SIMD
-// is the GEMM kernel's own shape (256 accumulator registers per lane); NB = 2 with two waves per SIMD halves both.
+// 8 x NB independent accumulator blocks, 8 + NB operand fragments, all in registers.  NB = 8 with one wave per SIMD
+// is the GEMM kernel's own shape (256 accumulator registers per lane); NB = 4 with two waves per SIMD halves both.
 template <int NB, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4)))
 void mfma_bf16_kernel(int iters, float* out) {
-  bf16x8 a[4], b[NB];
-  for (int i = 0; i < 4; i++)
-    for (int e = 0; e < 8; e++) a[i][e] = pseudo((threadIdx.x * 4 + i) * 8 + e);
+  bf16x8 a[8], b[NB];
+  for (int i = 0; i < 8; i++)
+    for (int e = 0; e < 8; e++) a[i][e] = pseudo((threadIdx.x * 8 + i) * 8 + e);
   for (int j = 0; j < NB; j++)
-    for (int e = 0; e < 8; e++) b[j][e] = pseudo(0x10000u + (threadIdx.x * 4 + j) * 8 + e);
-  f32x16 acc[4][NB];
-  for (int i = 0; i < 4; i++)
+    for (int e = 0; e < 8; e++) b[j][e] = pseudo(0x10000u + (threadIdx.x * 8 + j) * 8 + e);
+  f32x4 acc[8][NB];
+  for (int i = 0; i < 8; i++)
     for (int j = 0; j < NB; j++)
-      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.0f;
+      for (int r = 0; r < 4; r++) acc[i][j][r] = 0.0f;
   for (int it = 0; it < iters; it++) {
 #pragma unroll
-    for (int i = 0; i < 4; i++)
+    for (int i = 0; i < 8; i++)
 #pragma unroll
-      for (int j = 0; j < NB; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < NB; j++) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
-    for (int i = 0; i < 4; i++) asm volatile("" : "+v"(a[i]));   // the operands stay opaque: nothing is hoisted or folded
+    for (int i = 0; i < 8; i++) asm volatile("" : "+v"(a[i]));   // the operands stay opaque: nothing is hoisted or folded
   }
   float s = 0.0f;
-  for (int i = 0; i < 4; i++)
+  for (int i = 0; i < 8; i++)
     for (int j = 0; j < NB; j++)
-      for (int r = 0; r < 16; r++) s += acc[i][j][r];
+      for (int r = 0; r < 4; r++) s += acc[i][j][r];
   if (s == 123.456f) out[0] = s;   // keeps the loop alive; practically never true
 }
 
@@ -302,15 +305,15 @@ __global__ __launch_bounds__(256) void lds_probe_table_kernel(const uint32_t* __
 
 }  // namespace
 
-// iters rounds of 16 MFMAs per wave; grid workgroups of `waves` wavefronts (4 = one per SIMD, 8 = two per SIMD)
+// iters rounds of 64 (two waves per SIMD: 32) MFMAs per wave; grid workgroups of `waves` wavefronts (4 = one per SIMD, 8 = two per SIMD)
 FDLC_API int fdlc_mfma_bf16(int grid, int waves, int iters, float* out, void* stream) {
   if (grid < 1 || iters < 1 || (waves != 4 && waves != 8) || out == nullptr) return 1;
-  if (waves == 4) hipLaunchKernelGGL((mfma_bf16_kernel<4, 4>), dim3(grid), dim3(256), 0, (hipStream_t)stream, iters, out);
-  else hipLaunchKernelGGL((mfma_bf16_kernel<2, 8>), dim3(grid), dim3(512), 0, (hipStream_t)stream, iters, out);
+  if (waves == 4) hipLaunchKernelGGL((mfma_bf16_kernel<8, 4>), dim3(grid), dim3(256), 0, (hipStream_t)stream, iters, out);
+  else hipLaunchKernelGGL((mfma_bf16_kernel<4, 8>), dim3(grid), dim3(512), 0, (hipStream_t)stream, iters, out);
   return hipGetLastError() == hipSuccess ? 0 : 2;
 }
 FDLC_API double fdlc_mfma_bf16_flop(int grid, int waves, int iters) {
-  return (double)grid * waves * iters * (waves == 4 ? 16.0 : 8.0) * (2.0 * 32 * 32 * 16);
+  return (double)grid * waves * iters * (waves == 4 ? 64.0 : 32.0) * (2.0 * 16 * 16 * 32);
 }
 // iters rounds of 16 v_mfma_f64_16x16x4_f64 per wave, grid workgroups of four wavefronts
 FDLC_API int fdlc_mfma_f64(int grid, int iters, float* out, void* stream) {
