@@ -910,9 +910,8 @@ struct FfnPlan {
   int gate_pad, down_pad;  // the same kernels on zero-padded copies of the weights (widths off their tiles)
   int down_fast, up_wb, down_wb;
   int64_t ldg;             // pitch of G
-  int down_wt;             // the down projection reads its weights from a copy in blocks
-  int gate_wt;             // the fused gate/up kernel reads its weights from a copy (it never does)
-  int g_blocked;           // the gated activation passes from the fused kernel to the down projection in 32 x 32 blocks
+  int g_blocked;           // the gated activation passes from the fused kernel to the down projection in 32 x 32 blocks, and the
+                           // down projection reads its weights from a copy in such blocks
   F64Split up_s64, down_s64;   // fp32 storage
   int down_split;              // bf16, tiled: parts of the down projection's reduction
   size_t off_g, off_u, off_xtail, off_wt, off_wgp, off_wup, off_wdp, off_part, bytes;
@@ -954,10 +953,6 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* 
   q->off_wup = off; off += align256(q->gate_pad ? (size_t)Hp * Dq * 2 : 0);
   q->off_wdp = off; off += align256(q->down_pad ? (size_t)Dp * Hp * 2 : 0);
   q->down_split = split && (q->down_pad || q->down_fast) ? fast_xwt_split(M, q->down_pad ? Hp : H, D) : 1;
-  q->down_wt = q->down_fast && M >= kCopyFromRows && q->down_split == 1;
-  q->off_wt = off; off += align256(q->down_wt ? (size_t)D * H * 2 : 0);
-  q->gate_wt = 0;
-  q->g_blocked = q->gate_fused && q->down_wt && H % 32 == 0;
   if (dt == kF32) {
     q->up_s64 = split ? f64_plan(Mp, H, D) : f64_unsplit(Mp, H, D);
     q->down_s64 = split ? f64_plan(Mp, D, H) : f64_unsplit(Mp, D, H);
@@ -975,10 +970,11 @@ bool make_ffn_plan(int dt, int64_t M, int64_t D, int64_t H, Room room, FfnPlan* 
     q->down_mid = both ? q->gate_mid : md < g.down_cost;
     if (q->gate_mid) { q->ldg = H; q->gate_pad = 0; }
     if (q->down_mid) { q->down_split = parts; q->down_pad = 0; }
-    if (q->gate_mid || q->down_mid) q->g_blocked = 0;
     const size_t sums = q->down_mid ? fast_xwt_part_bytes(M, D, parts) : down;
     if (q->off_part + align256(sums) > off) off = q->off_part + align256(sums);
   }
+  q->g_blocked = q->gate_fused && !q->gate_mid && q->down_fast && !q->down_mid && M >= kCopyFromRows && q->down_split == 1;
+  q->off_wt = off; off += align256(q->g_blocked ? (size_t)D * H * 2 : 0);
   q->bytes = off;
   return true;
 }
@@ -1041,8 +1037,8 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
   } else if (q.down_skinny) {
     launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, s);
   } else if (q.down_fast) {
-    void* Wb = q.down_wt ? ws + q.off_wt : nullptr;
-    if (q.down_wt) launch_fast_block(D, H, Wd, Wb, s);
+    void* Wb = q.g_blocked ? ws + q.off_wt : nullptr;
+    if (q.g_blocked) launch_fast_block(D, H, Wd, Wb, s);
     launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wb, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0,
                     q.down_split, ws + q.off_part);
   } else {

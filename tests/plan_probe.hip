@@ -5,11 +5,11 @@
 #include <string>
 
 namespace {
-std::string product(int mid, int skinny, int pad, int tiled, int split, int transposed) {
+std::string product(int mid, int skinny, int pad, int tiled, int split, int copied) {
   if (mid) return split > 1 ? "mid split" : "mid";
   if (skinny) return "few rows";
   if (!pad && !tiled) return "generic";
-  return std::string(pad ? "padded" : "tiled") + (split > 1 ? " split" : "") + (transposed && !pad ? " transposed" : "");
+  return std::string(pad ? "padded" : "tiled") + (split > 1 ? " split" : "") + (copied && !pad ? " from blocks" : "");
 }
 std::string gradients(const GradPlan& g) {
   if (g.mid) return std::string("mid") + (g.split_a > 1 ? " dx-split" : "") + (g.split_b > 1 ? " dw-split" : "");
@@ -36,8 +36,8 @@ extern "C" __attribute__((visibility("default"))) const char* plan_probe(int op,
   } else {
     FfnPlan p = {};
     if (!make_ffn_plan(dt, M, K, N, Room::kAll, &p)) return "";
-    text = product(p.gate_mid, p.gate_skinny, p.gate_pad, p.gate_fused, 1, p.gate_wt) + " | " +
-           product(p.down_mid, p.down_skinny, p.down_pad, p.down_fast, p.down_split, p.down_wt);
+    text = product(p.gate_mid, p.gate_skinny, p.gate_pad, p.gate_fused, 1, 0) + " | " +
+           product(p.down_mid, p.down_skinny, p.down_pad, p.down_fast, p.down_split, p.g_blocked);
   }
   return text.c_str();
 }

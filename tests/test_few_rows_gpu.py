@@ -65,3 +65,56 @@ def test_feed_forward_block(M, D, Hd):
     assert Y.intact() and ws.intact()
     n = f64(t)
     H.check("bf16", "Y", H.to_f64(Y.view), S.llama_ffn_forward(n["X"], n["Wg"], n["Wu"], n["Wd"])["Y"])
+
+
+# Reductions from 2048 on, whose loads take whole lines of 8 rows: whole steps of 64 alone, with 8 indices left, with one, with four; every
+# tile (1 and 2 blocks of 16 rows; 2 and 4 of them with two of columns; the gated one with 1, 2 and 4); widths that end inside a
+# block of 16 columns and inside a group of four.  test_routes_host.py: all run on this kernel.
+LINES = [(M, K, 1003) for M in (1, 16, 17, 33, 64) for K in (2048, 2056, 2049, 4100) if M <= 32 or K % 8 == 0] + [(40, 2056, 8203), (1, 8191, 40)]
+LINES_FFN = [(M, D, H) for M in (1, 16, 17, 33, 64) for D, H in ((2048, 2056), (2056, 2048), (2049, 2056))] + [(16, 2112, 2059), (9, 4100, 2049)]
+
+
+@pytest.mark.parametrize("M,K,N", LINES)
+def test_linear_relu_of_long_reductions(M, K, N):
+    print(f"[few rows] lines {M}x{K}x{N}", flush=True)
+    t = I.generate(I.custom("bf16", M, K, N, seed=9200 + M + K + N))
+    X, W, dY = (t[k].to("cuda", torch.bfloat16) for k in ("X", "W", "dY"))
+    b = t["b"].to("cuda")
+    Y = H.Guarded((M, N), torch.bfloat16)
+    dX, dW, db = (torch.empty(s, device="cuda", dtype=d) for s, d in (((M, K), X.dtype), ((N, K), X.dtype), ((N,), torch.float32)))
+    ws = torch.empty(max(256, api.fdl_linear_relu_workspace_bytes("bf16", M, K, N)), dtype=torch.uint8, device="cuda")
+    api.fdl_linear_relu_forward("bf16", X, W, b, Y.view, ws)
+    api.fdl_linear_relu_backward("bf16", dY, X, W, b, dX, dW, db, ws)
+    torch.cuda.synchronize()
+    assert Y.intact()
+    z = X.double() @ W.double().t() + b.double()
+    # fp32 sums of K + 1 terms, rounded to bf16 once (half a unit: 2^-8 at most)
+    near = (K + 1) * 2.0 ** -24 * (X.double().abs() @ W.double().abs().t() + b.double().abs())
+    assert torch.all((Y.view.double() - z.clamp(min=0)).abs() <= 2.0 ** -8 * z.clamp(min=0) + near)
+    # db: sums of dY over the rows whose mask the recomputation leaves open (M terms in fp32 or more)
+    mask, d = (z > 0).double(), dY.double()
+    unsure = (z.abs() <= near).double()
+    assert torch.all((db.double() - (d * mask).sum(0)).abs() <= (d.abs() * unsure).sum(0) + M * 2.0 ** -24 * d.abs().sum(0))
+
+
+@pytest.mark.parametrize("M,D,Hd", LINES_FFN)
+def test_feed_forward_block_of_long_reductions(M, D, Hd):
+    print(f"[few rows] lines ffn {M}x{D}x{Hd}", flush=True)
+    t = I.generate_ffn("bf16", M, D, Hd, seed=9300 + M + D + Hd)
+    d = {k: v.to("cuda", torch.bfloat16) for k, v in t.items()}
+    Y = H.Guarded((M, D), torch.bfloat16)
+    ws = H.Guarded((max(256, api.fdl_llama_ffn_workspace_bytes("bf16", M, D, Hd)),), torch.uint8)
+    api.fdl_llama_ffn_forward("bf16", d["X"], d["Wg"], d["Wu"], d["Wd"], Y.view, ws.view)
+    torch.cuda.synchronize()
+    assert Y.intact() and ws.intact()
+    x, wg, wu, wd = (d[k].double() for k in ("X", "Wg", "Wu", "Wd"))
+    g, u = x @ wg.t(), x @ wu.t()
+    act = torch.nn.functional.silu(g) * u
+    ref = act @ wd.t()
+    # gate and up sums in fp32 (|SiLU'| <= 1.1; its exp2 and reciprocal 2^-20), the activation rounded to bf16, the down sums in fp32,
+    # the output rounded to bf16
+    s = 2.0 ** -24 * D
+    err = 1.1 * s * (x.abs() @ wg.abs().t()) * u.abs() + s * (x.abs() @ wu.abs().t()) * torch.nn.functional.silu(g).abs() + 2.0 ** -20 * act.abs()
+    err = err + 2.0 ** -8 * (act.abs() + err)
+    bound = err @ wd.abs().t() + 2.0 ** -24 * Hd * (act.abs() @ wd.abs().t())
+    assert torch.all((Y.view.double() - ref).abs() <= bound + 2.0 ** -8 * (ref.abs() + bound))

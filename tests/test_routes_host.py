@@ -2,11 +2,13 @@
 kernel have to reach it, and the rules that were measured have to hold where they were measured."""
 import pytest
 
+import test_few_rows_gpu
 import test_mid_tiles_gpu
 import test_padded_shapes_gpu
 import test_row_kernels_gpu
 import test_small_workspaces_gpu
 import test_special_values_gpu
+from paper_2509_14279_amd import api
 from routes import route
 
 
@@ -43,7 +45,7 @@ def test_forward_products_of_the_large_tiles(op):
     assert {m % 256 == 0 for (m, _, _), f in zip(test_padded_shapes_gpu.LARGE, large) if f == "tiled split"} == {True, False}
     assert {k % 128 == 0 for (_, k, _), f in zip(test_padded_shapes_gpu.LARGE, large) if f == "padded"} == {True, False}
     special = forward(op, test_special_values_gpu.SHAPES)
-    assert set(special) >= set(large) | {"tiled transposed", "mid", "mid split", "few rows", "generic"}
+    assert set(special) >= set(large) | {"tiled from blocks", "mid", "mid split", "few rows", "generic"}
     assert set(forward(op, [s[1:] for s in test_small_workspaces_gpu.SHAPES if s[0] == "bf16"])) >= set(large)
     assert set(forward(op, test_mid_tiles_gpu.SHAPES)) >= {"mid", "mid split"}
 
@@ -74,3 +76,20 @@ def test_feed_forward_products():
     for shapes in (test_padded_shapes_gpu.LARGE_FFN, test_special_values_gpu.FFN):
         assert {" | ".join(route("ffn", "bf16", *s)) for s in shapes} >= expected
     assert "mid | tiled split" in {" | ".join(route("ffn", "bf16", *s)) for s in test_padded_shapes_gpu.LARGE_FFN}
+
+
+# from 16384 rows on the activation passes to the down product in blocks, whose weights are then copied into such blocks; an activation
+# that comes as rows gains nothing from the copy, and the workspace has no room for it
+@pytest.mark.parametrize("M,D,H,gate,down", [(16384, 4096, 11008, "tiled", "tiled from blocks"), (16384, 1024, 4096, "tiled", "tiled from blocks"),
+                                             (16385, 512, 1024, "mid", "tiled"), (32805, 256, 512, "mid", "tiled")])
+def test_the_down_products_copy_goes_with_the_blocked_activation(M, D, H, gate, down):
+    assert route("ffn", "bf16", M, D, H) == [gate, down]
+    rows = (M + 255) // 256 * 256
+    tails = 2 * (256 * D * 2 + 256)
+    assert api.fdl_llama_ffn_workspace_bytes("bf16", M, D, H) <= rows * H * 2 + (D * H * 2 if "blocks" in down else 0) + tails
+
+
+def test_long_reductions_of_few_rows():
+    assert {route("relu", "bf16", *s)[0] for s in test_few_rows_gpu.LINES} == {"few rows"}
+    assert {tuple(route("ffn", "bf16", *s)) for s in test_few_rows_gpu.LINES_FFN} <= {("few rows", "few rows"), ("few rows", "mid split")}
+    assert sum(route("ffn", "bf16", *s)[1] == "few rows" for s in test_few_rows_gpu.LINES_FFN) >= 12
