@@ -143,9 +143,6 @@ bool make_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, Plan* p, bool
   if (dt == kF32) q.f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N, K);
   q.f1_split = tiled && split ? fast_xwt_split(M, K, N) : 1;
   q.off_part = off; off += align256(dt == kF32 ? f64_part_bytes(q.f1_s64) : fast_xwt_part_bytes(M, N, q.f1_split));
-  q.fwd_bytes_plain = off;
-  q.f1_wt = tiled && !q.pad && copies_weights(M, K) && q.f1_split == 1;
-  q.off_wt = off; off += align256(q.f1_wt ? (size_t)N * K * 2 : 0);
   q.fwd_bytes = off;
   // (128 x 128 tiles need no copies: the sums of their split reduction lie where those would)
   if (dt == kBF16 && mid_supported(Mp, K, N)) {
@@ -393,10 +390,7 @@ static fdl_status forward_launches(const Plan& p, const void* X, const void* W, 
       launch_stage(j, s);
       launch_fast_xwt_padded(0, M, K, N, p.stage_x != 0, X, ws + p.off_xtail, Wp, bp, nullptr, Zsave, p.f1_split, ws + p.off_part, s);
     } else if (p.f1_fast) {
-      void* Wb = p.f1_wt ? ws + p.off_wt : nullptr;
-      if (p.f1_wt) launch_fast_block(N, K, W, Wb, s);
-      launch_fast_xwt(0, M, K, N, X, false, W, Wb, b, nullptr, Zsave, false, ws + p.off_xtail, s, false, p.f1_split,
-                      ws + p.off_part);
+      launch_fast_xwt(0, M, K, N, X, false, W, b, nullptr, Zsave, false, ws + p.off_xtail, s, p.f1_split, ws + p.off_part);
     } else {
       GemmDesc g = {X, W, M, N, K, K, K, true, true, p.f1_wb};
       if (sums) parts = launch_f64_parts(g, p.f1_s64, b, Zsave, ws + p.off_part, s);
@@ -464,9 +458,6 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
     if (p.off_part + fast_xwt_part_bytes(M, N, p.f1_split) > (size_t)FDL_STATIC_SCRATCH_BYTES) p.f1_split = 1;
     p.fwd_bytes = p.off_part;
   }
-  if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_wt) {
-    p.f1_wt = 0; p.fwd_bytes = p.fwd_bytes_plain;   // no room for the weights' copy: the kernel reads W as it is
-  }
   if (p.fwd_bytes > (size_t)FDL_STATIC_SCRATCH_BYTES && p.f1_split > 1) {
     p.f1_split = 1; p.fwd_bytes = p.off_part;         // (the sums of a split reduction are the last region here)
   }
@@ -486,7 +477,7 @@ extern "C" fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int
   clear_stale_error();
   char* ws = static_scratch_address();
   if (ws == nullptr) return launch_status();
-  // every scratch location a forward pass reads has been written earlier in the same pass (padded or blocked
+  // every scratch location a forward pass reads has been written earlier in the same pass (padded
   // weights, the padded copy of X's last rows), so nothing has to be cleared between calls
   return forward_launches(p, X, W, b, gamma, beta, eps, Y, Zsave, mean, rstd, ws, static_cast<hipStream_t>(hip_stream));
 }
@@ -700,18 +691,17 @@ extern "C" fdl_status fdl_forward_inference(fdl_dtype dt, int64_t M, int64_t K, 
 // ---- Linear + ReLU -------------------------------------------------------------------------------------------------
 namespace {
 // Workspace of the Linear+ReLU pair (one layout for both passes): the first-stage column partials of db, the copies the
-// forward product needs (padded weights and bias, X or its last rows, or the weights in blocks), and what the two gradient
+// forward product needs (padded weights and bias, X or its last rows), and what the two gradient
 // contractions need, the masked upstream gradient G among it (the dZ of GradPlan).
 struct ReluPlan {
   int f1_mid;              // the forward product (and its recomputation) in 128 x 128 tiles, f1_split parts
   int f1_skinny;           // few rows: the forward product (and its recomputation) on the kernel made for them
   int f1_fast, f1_wb;      // the tuned kernel, on the operands as they are
   int pad;                 // or in padded mode (then the gradient contractions run in it too)
-  int f1_wt;               // the forward product (and its recomputation) reads the weights from a copy in blocks
   GradPlan g;
   F64Split f1_s64;         // fp32 storage
   int f1_split;            // bf16, tiled: parts of the forward product's reduction
-  size_t off_colpart, off_xtail, off_wt, off_wpad, off_bpad, off_part, bytes;
+  size_t off_colpart, off_xtail, off_wpad, off_bpad, off_part, bytes;
 };
 bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan* q) {
   const bool split = room == Room::kAll || room == Room::kTight;
@@ -744,8 +734,6 @@ bool make_relu_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, ReluPlan
     q->off_xtail = off; off += align256(f1 == Xwt::kPadded ? fast_padded_tail_bytes(K) : fast_f1_tail_bytes(M, K));
   }
   q->off_bpad = off; off += align256(f1 == Xwt::kPadded ? (size_t)fast_pad_dim(N) * 4 : 0);
-  q->f1_wt = f1 == Xwt::kTiled && copies_weights(M, K) && q->f1_split == 1;
-  q->off_wt = off; off += align256(q->f1_wt ? (size_t)N * K * 2 : 0);
   if (dt == kF32) q->f1_s64 = split ? f64_plan(Mp, N, K) : f64_unsplit(Mp, N, K);
   if (q->f1_mid) q->f1_split = parts;
   const size_t sums = dt == kF32 ? f64_part_bytes(q->f1_s64) : fast_xwt_part_bytes(M, N, q->f1_split);
@@ -766,10 +754,8 @@ void relu_product(const ReluPlan& q, int kind, int dt, int64_t M, int64_t K, int
     launch_fast_xwt_padded(kind, M, K, N, q.g.stage_x != 0, X, ws + q.off_xtail, ws + q.off_wpad, reinterpret_cast<const float*>(ws + q.off_bpad),
                            aux, out, q.f1_split, ws + q.off_part, s);
   } else if (q.f1_fast) {
-    void* Wb = q.f1_wt ? ws + q.off_wt : nullptr;
-    if (q.f1_wt) launch_fast_block(N, K, W, Wb, s);
-    launch_fast_xwt(kind, M, K, N, X, false, W, Wb, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s, false,
-                    q.f1_split, ws + q.off_part);
+    launch_fast_xwt(kind, M, K, N, X, false, W, b, aux, out, kind == 2 && q.g.blocked != 0, ws + q.off_xtail, s, q.f1_split,
+                    ws + q.off_part);
   } else {
     GemmDesc g = {X, W, M, N, K, K, K, true, true, q.f1_wb};
     if (dt == kF32) launch_f64(kind, g, q.f1_s64, b, aux, out, ws + q.off_part, s);
@@ -1036,11 +1022,11 @@ extern "C" fdl_status fdl_llama_ffn_forward(fdl_dtype dt, int64_t M, int64_t D, 
     launch_fast_down_padded(M, D, q.ldg, G, ws + q.off_wdp, Y, q.down_split, ws + q.off_part, s);
   } else if (q.down_skinny) {
     launch_skinny_xwt(0, M, H, D, G, Wd, nullptr, nullptr, Y, D, s);
+  } else if (q.g_blocked) {
+    launch_fast_block(D, H, Wd, ws + q.off_wt, s);
+    launch_fast_xwt_blocked(M, H, D, G, ws + q.off_wt, Y, s);
   } else if (q.down_fast) {
-    void* Wb = q.g_blocked ? ws + q.off_wt : nullptr;
-    if (q.g_blocked) launch_fast_block(D, H, Wd, Wb, s);
-    launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, Wb, nullptr, nullptr, Y, false, nullptr, s, q.g_blocked != 0,
-                    q.down_split, ws + q.off_part);
+    launch_fast_xwt(0, M, H, D, G, /*x_padded=*/true, Wd, nullptr, nullptr, Y, false, nullptr, s, q.down_split, ws + q.off_part);
   } else {
     GemmDesc g = {G, Wd, M, D, H, H, H, true, true, q.down_wb};
     if (dt == FDL_F32) launch_f64(0, g, q.down_s64, nullptr, nullptr, Y, ws + q.off_part, s);

@@ -973,18 +973,12 @@ void launch_fast_xwt_padded(int kind, int64_t M, int64_t K, int64_t N, bool stag
 //   kind 2: aux[m][n] where the sum is positive, else 0
 // xtail: fast_f1_tail_bytes(M, K) bytes of scratch when M is not a multiple of 256, unless X itself has readable rows
 // up to the next multiple of 256 (x_padded).
-// Wb: null, or W in blocks of 32 x 32 (launch_fast_block).  With X in blocks too (x_blocked: the library's own buffer, rows padded to
-// whole tiles) every slice of either operand is long runs, for which slices of 32 in four stages serve better than slices of 64 in
-// two: the feed-forward block's down product 16384 x 11008 x 4096 1115 us from rows 22 KB apart, 935 so, 14 of it the copy.
-// An X that comes as rows gains nothing from blocked weights (inference, us, with / without: 16384 x 4096 x 4096 428 / 408,
-// 32768 x 2048 x 8192 956 / 930, 16384 x 11008 x 4096 1187 / 1188).
 // out_blocked (kind 2 only; M, N multiples of 32): out is written in 32 x 32 blocks, as the dX and dW kernels read it best.
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
-                     const void* Wb, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
-                     hipStream_t s, bool x_blocked, int split, void* part) {
+                     const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
+                     hipStream_t s, int split, void* part) {
   FastParams p = {};
   p.cblocked = (out_blocked && kind == 2) ? 1 : 0;
-  p.qblocked = (x_blocked && Wb != nullptr) ? 1 : 0;   // (with the weights' copy only: slices of 32)
   p.P = (const bf16_t*)W; p.Q = (const bf16_t*)X; p.ldp = K; p.ldq = K;
   p.C = (bf16_t*)out; p.bias = bias; p.aux = (const bf16_t*)aux;
   p.I = (int)N; p.J = (int)M; p.tiles_i = (int)(N / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
@@ -995,21 +989,6 @@ void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, b
     StageJobs j = {};
     stage_x_tail(&j, X, M, K, xtail, 0);
     launch_stage(j, s);
-  }
-  if (Wb != nullptr) {
-    p.P = (const bf16_t*)Wb; p.pblocked = 1; p.nkt = (int)(K / kB3BK);
-    constexpr int NST = stages_of(kB3BK);
-#define FDL_XWT_B(EPI)                                                            \
-  do {                                                                            \
-    if (rag) launch<false, false, EPI, kB3BK, NST, true>(p, s);                   \
-    else launch<false, false, EPI, kB3BK, NST, false>(p, s);                       \
-  } while (0)
-    if (kind == 1) FDL_XWT_B(EPI_RELU);
-    else if (kind == 2) FDL_XWT_B(EPI_MASK);
-    else if (bias != nullptr) FDL_XWT_B(EPI_BIAS);
-    else FDL_XWT_B(EPI_STORE);
-#undef FDL_XWT_B
-    return;
   }
   if (split > 1) { launch_xwt_split(p, rag, false, kind, split, part, M, N, bias, aux, out, N, s); return; }
   constexpr int NS = stages_of(kF1BK);
@@ -1023,6 +1002,24 @@ void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, b
   else if (bias != nullptr) FDL_XWT(EPI_BIAS);
   else FDL_XWT(EPI_STORE);
 #undef FDL_XWT
+}
+
+// out = X W^T with both operands in blocks of 32 x 32, X (the library's own buffer) with its rows padded to whole tiles.  Every slice
+// of either is long runs, for which slices of 32 in four stages serve better than slices of 64 in two: the feed-forward block's down
+// product 16384 x 11008 x 4096 1115 us from rows 22 KB apart, 935 so, 14 of it the weights' copy.  An X that comes as rows gains nothing
+// from blocked weights (inference, us, with / without: 16384 x 4096 x 4096 428 / 408, 32768 x 2048 x 8192 956 / 930,
+// 16384 x 11008 x 4096 1187 / 1188; at the shortest
+// reduction, K = 128, whole calls of 16384 to 100000 rows, without / with, on average: 256 columns 0.92, 2048 0.97, 4096 and more 0.98 - 1.0).
+void launch_fast_xwt_blocked(int64_t M, int64_t K, int64_t N, const void* X, const void* Wb, void* out, hipStream_t s) {
+  FastParams p = {};
+  p.pblocked = p.qblocked = 1;
+  p.P = (const bf16_t*)Wb; p.Q = (const bf16_t*)X; p.ldp = K; p.ldq = K;
+  p.C = (bf16_t*)out;
+  p.I = (int)N; p.J = (int)M; p.tiles_i = (int)(N / kTile); p.tiles_j = (int)((M + kTile - 1) / kTile);
+  p.nkt = (int)(K / kB3BK); p.split = 1;
+  constexpr int NS = stages_of(kB3BK);
+  if (M % kTile != 0) launch<false, false, EPI_STORE, kB3BK, NS, true>(p, s);
+  else launch<false, false, EPI_STORE, kB3BK, NS, false>(p, s);
 }
 
 // ---- the forward product with a split reduction ------------------------------------------------------------------

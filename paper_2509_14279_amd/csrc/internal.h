@@ -54,14 +54,11 @@ struct Plan {
   int f1_skinny;          // 1: bf16 kernel for few rows (before the two below)
   int f1_fast;            // 1: bf16 fast MFMA kernel, 0: generic kernel
   int f1_wb;              // generic kernel: 16x16 blocks per wave tile side (wave tile = 16*wb)
-  int f1_wt;              // 1: the fast kernel reads the weights from a copy in blocks (copies_weights)
-  size_t off_wt;          // bf16 [N][K], the last region of the forward workspace
   size_t off_rows;        // F2's scratch for rows beyond its registers, the first
   F64Split f1_s64;        // fp32 storage
   int f1_split;           // bf16, tiled: parts of the reduction where there are few tiles
   size_t off_part;        // their sums
-  size_t fwd_bytes;       // (without the weights' copy: fwd_bytes - align256(N K 2), see fwd_bytes_plain)
-  size_t fwd_bytes_plain; // forward workspace of the same plan with f1_wt = 0
+  size_t fwd_bytes;
   size_t static_need;     // what fdl_forward_static compares with its array (the header's rule)
   // backward
   int b1_fused;           // 1: one pass with the row held in registers; 0: B1a + B1b
@@ -251,16 +248,13 @@ inline int64_t partial_stride(int64_t n) { return (n + 3) & ~(int64_t)3; }
 void launch_fast_b3_padded(int64_t M, int64_t K, int64_t N, const void* dZ, const void* Wp, void* dX, hipStream_t s);
 void launch_fast_b4_padded(int64_t M, int64_t K, int64_t N, int split, int extra, const void* dZ, const void* X, int64_t ldx,
                            void* dW, void* dwpart, hipStream_t s);
-// the forward product, also of the sibling operators (see gemm_bf16.hip); shapes as fast_f1_supported;
-// Wb: null, or the weights' copy from launch_fast_block
-constexpr int64_t kCopyFromRows = 16384;   // batch size from which copying the weights first pays
-// Whether a product of X as rows reads its weights from that copy: at one round of the pipeline only, where four stages of 32 instead of
-// two of 64 make up for it from a few thousand columns on (inference 16384 x 128 x 8448 200 us either way, x 256 23.5 against 20.3).
-inline bool copies_weights(int64_t M, int64_t K) { return M >= kCopyFromRows && K <= 128; }
+// the forward product, also of the sibling operators (see gemm_bf16.hip); shapes as fast_f1_supported
 void launch_fast_xwt(int kind, int64_t M, int64_t K, int64_t N, const void* X, bool x_padded, const void* W,
-                     const void* Wb, const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
-                     hipStream_t s, bool x_blocked = false,    // x_blocked: X in 32 x 32 blocks (needs Wb, x_padded)
-                     int split = 1, void* part = nullptr);     // see fast_xwt_split (without Wb)
+                     const float* bias, const void* aux, void* out, bool out_blocked, void* xtail,
+                     hipStream_t s, int split = 1, void* part = nullptr);     // see fast_xwt_split
+// the plain product of an X in 32 x 32 blocks (rows padded to whole tiles) and weights from launch_fast_block
+constexpr int64_t kCopyFromRows = 16384;   // batch size from which the feed-forward block's down product runs so
+void launch_fast_xwt_blocked(int64_t M, int64_t K, int64_t N, const void* X, const void* Wb, void* out, hipStream_t s);
 // gate and up products of the feed-forward block with the gated activation in the epilogue (see gemm_bf16.hip)
 bool fast_gate_supported(int64_t M, int64_t D, int64_t H);
 void launch_fast_gate(int64_t M, int64_t D, int64_t H, const void* X, const void* Wg, const void* Wu, void* Hout, bool out_blocked,

@@ -28,11 +28,11 @@ extern "C" __attribute__((visibility("default"))) const char* plan_probe(int op,
   if (op == 0) {
     Plan p;
     if (!make_plan(dt, M, K, N, Room::kAll, &p)) return "";
-    text = product(p.f1_mid, p.f1_skinny, p.pad, p.f1_fast, p.f1_split, p.f1_wt) + " | " + gradients(p.g) + " | " + std::to_string(p.g.ldz);
+    text = product(p.f1_mid, p.f1_skinny, p.pad, p.f1_fast, p.f1_split, 0) + " | " + gradients(p.g) + " | " + std::to_string(p.g.ldz);
   } else if (op == 1) {
     ReluPlan p = {};
     if (!make_relu_plan(dt, M, K, N, Room::kAll, &p)) return "";
-    text = product(p.f1_mid, p.f1_skinny, p.pad, p.f1_fast, p.f1_split, p.f1_wt) + " | " + gradients(p.g) + " | " + std::to_string(p.g.ldz);
+    text = product(p.f1_mid, p.f1_skinny, p.pad, p.f1_fast, p.f1_split, 0) + " | " + gradients(p.g) + " | " + std::to_string(p.g.ldz);
   } else {
     FfnPlan p = {};
     if (!make_ffn_plan(dt, M, K, N, Room::kAll, &p)) return "";

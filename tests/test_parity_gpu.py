@@ -121,8 +121,8 @@ def test_small_and_ragged_shapes(dtype, shape):
     ("bf16", (129, 136, 256)), ("bf16", (128, 128, 264)), ("bf16", (200, 248, 2056)), ("bf16", (256, 384, 8200)),
     ("bf16", (385, 256, 8456)), ("bf16", (1024, 1000, 8)), ("bf16", (2048, 1024, 64)), ("bf16", (640, 128, 1000)),
     ("bf16", (4096, 520, 768)), ("bf16", (1500, 768, 776)),
-    # batches from 16384 rows on the tuned kernel: the forward contraction reads the weights from a transposed copy
-    # (whole row tiles; a partial last one; rows longer than 8192)
+    # batches from 16384 rows on: one round of the pipeline on the tuned kernel, a partial last row tile in 128 x 128 tiles, rows
+    # longer than 8192
     ("bf16", (16384, 128, 256)), ("bf16", (32805, 256, 512)), ("bf16", (16384, 128, 8448)),
     # dZ in 32 x 32 blocks (fused row kernel + tuned dX and dW over all rows; with rows of 1024 threads only from
     # K = 1024): whole and partial wavefronts at the end of a row, split dW, paired dX + dW launch

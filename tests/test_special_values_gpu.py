@@ -12,7 +12,7 @@ from paper_2509_14279_amd import api, inputs as I
 pytestmark = pytest.mark.gpu
 
 BIG = 3.4e38          # above the largest bf16 number: it rounds to infinity there, in fp32 it is finite
-# 128 x 128 tiles; from transposed weights; 128 x 128, two of them split; few rows
+# 128 x 128 tiles; 256 x 256, one round of the pipeline; 128 x 128, two of them split; few rows
 SHAPES = [(4608, 256, 768), (4700, 256, 768), (16384, 128, 256), (4500, 384, 1100), (4097, 771, 1100), (512, 4096, 2048),
           (500, 4096, 2000), (32, 128, 256), (200, 136, 264), (127, 33, 1030)]
 # 256 x 256 tiles: as they are; ragged rows; padded, X as it is / as a copy; split, ragged rows, padded; and the generic kernel

@@ -8,7 +8,7 @@ from paper_2509_14279_amd import api, inputs as I
 pytestmark = pytest.mark.gpu
 
 
-# slices of 64, slices of 32 (from 16384 rows on), ragged rows, padded columns
+# whole tiles, more of them, ragged rows, padded columns, two rounds
 @pytest.mark.parametrize("M,K,N", [(12032, 128, 6144), (16384, 128, 8448), (12100, 128, 6144), (8760, 128, 5167), (12032, 256, 6144)])
 def test_bias_of_every_tile(M, K, N):
     print(f"[bias] {M}x{K}x{N}", flush=True)

@@ -1,10 +1,10 @@
 """fdl_forward_static (the forward pass on the library's own fixed scratch array, for callers that cannot allocate)
 against fdl_forward on the same inputs: same kernels on a different scratch address, so every output must agree bit
 for bit (stricter than the parity bars, which the fdl_forward side is held to against the oracle elsewhere) - except
-where the array is too small for the transposed weights that fdl_forward uses for large batches (own test below).
+where the array has no room for an optional part (own test below).
 
 Two calls in a row on one GPU, the second with a smaller input, through shapes whose forward pass uses the scratch: the
-padded copy of X's last rows (ragged M on the tiled kernel), transposed weights; further down padded copies, segments of long
+padded copy of X's last rows (ragged M on the tiled kernel); further down padded copies, segments of long
 rows, and what runs where the array has no room for the optional part.  This file is collected last, so that a failure here
 cannot hide the other tests."""
 import sys
@@ -43,7 +43,7 @@ def test_forward_static_matches_forward_on_two_calls_in_a_row():
              I.custom("f32", 130, 70, 200, seed=52),        # fp64 kernel, smaller
              I.custom("bf16", 300, 256, 512, seed=53),      # few rows: no scratch
              I.custom("bf16", 200, 136, 264, seed=54),      # few rows, widths off the tile
-             I.custom("bf16", 16384, 128, 256, seed=55)]    # large batch: transposed weights in the scratch
+             I.custom("bf16", 16384, 128, 256, seed=55)]    # large batch: none
     inputs = [I.generate(c, with_dY=False) for c in cases]
     got = []
     for c, t in zip(cases, inputs):                          # the static calls back to back, nothing in between
@@ -59,9 +59,7 @@ def test_forward_static_matches_forward_on_two_calls_in_a_row():
 
 
 def test_forward_static_with_weights_too_large_to_transpose_in_the_array():
-    # a large batch: fdl_forward transposes W into its workspace (2 N K = 17.8 MB here); the array has no room for that,
-    # so the static entry point runs the same contraction on W as it is.  Different kernels: compared to the parity
-    # bar of bf16 storage rather than bit for bit.
+    # a large batch whose weights are more than the array holds (2 N K = 17.8 MB): they are read as they are
     c = I.custom("bf16", 32768, 2048, 4352, seed=56)
     assert 2 * c.N * c.K > api.FDL_STATIC_SCRATCH_BYTES
     t = I.generate(c, with_dY=False)
