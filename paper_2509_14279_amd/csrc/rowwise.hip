@@ -1418,7 +1418,12 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
   const int64_t per_wg = nt / 64 / wpr;
   int64_t wgs = (M + per_wg - 1) / per_wg;
-  const int64_t per_cu = whole && !past_caches ? (ACT == ACT_GELU && N == 4096 ? 3 : 4)
+  // (Stand-alone norms of 8192 columns: as many workgroups as gamma and beta leave room for in LDS.  With twice as many each sets those
+  // up for half the rows, before the others end.  LayerNorm / RMSNorm, us, a wavefront per row / four / two per compute unit: 1536 rows
+  // 10.6 11.7 10.5 / 9.5 10.1 9.0, 1792 11.3 12.6 11.3 / 10.2 11.5 10.3, 2304 18.5 15.8 13.7 / 15.9 13.6 12.5, 4096 21.8 22.8 22.0 / 21.3 20.9
+  // 20.9, 6144 35.3 31.7 31.8 / 35.6 30.1 30.4.)
+  const bool pair = past_caches || (N == 8192 && ACT != ACT_GELU);
+  const int64_t per_cu = whole && !pair ? (ACT == ACT_GELU && N == 4096 ? 3 : 4)
                                               : (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (ch == 1 ? 8 : (16 / ch > wpr ? 16 / ch / wpr : 1)));
   const int64_t cap = (int64_t)di.cus * per_cu;
   if (wgs > cap) wgs = cap;
