@@ -82,7 +82,7 @@ __device__ __forceinline__ void as_fragments(bf16x8& lo, bf16x8& hi, bool upper)
 }
 
 // AL: K is a multiple of 8 (every row starts on 16 bytes); otherwise the same loads from element-aligned addresses.
-// LINES (K >= kLinesFrom): loads of whole lines, U steps of 64 in flight; otherwise of 64 bytes of 16 rows, U steps of 32.
+// LINES: loads of whole lines, U steps of 64 in flight; otherwise of 64 bytes of 16 rows, U steps of 32.
 template <int MB, int NB, int EPI, int WAVES, int U, bool AL, bool LINES>
 __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p) {
   constexpr int NMAT = EPI == SK_GATE ? 2 : 1;
@@ -303,14 +303,19 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
 
 // Reduction length from which whole lines are loaded (feed-forward block, us, 64-byte pieces / lines: 16 x 4096 x 11008 62.0 / 57.1,
 // 1 x 4096 x 11008 52.8 / 48.5; at K = 1024 to 2000 equal within 2 %, below 1024 3 to 6 % slower: two steps of a wavefront or fewer).
-constexpr int64_t kLinesFrom = 2048;
+// Four row blocks load X more than W.  Lines over pieces, whole calls, mean (and extremes) of 140 to 300 shapes each: gated, D 1024 to
+// 4096 1.00 (0.88 - 1.07), beyond 0.97 (0.85 - 1.04); beside two column blocks, K 1024 to 2048 1.05 (up to 1.23: inference 50 x 2048 x 8960
+// 76 / 86 us), 2048 to 2900 1.02 (up to 1.15), and beyond another kernel is picked.
+constexpr int64_t kLinesFrom = 2048, kLinesFromGate4 = 4096;
 template <int MB, int NB, int EPI, int WAVES, int U> void launch_skinny(SkinnyParams p, hipStream_t s) {
   p.mblocks = (p.M + 16 * MB - 1) / (16 * MB);
   const int strips = (p.N + 16 * NB - 1) / (16 * NB);
   const unsigned grid = (unsigned)((strips + 7) / 8 * 8) * (unsigned)p.mblocks;
-  const bool lines = p.K >= kLinesFrom;
-  auto kern = p.K % 8 == 0 ? (lines ? gemm_skinny_kernel<MB, NB, EPI, WAVES, 2, true, true> : gemm_skinny_kernel<MB, NB, EPI, WAVES, U, true, false>)
-                           : (lines ? gemm_skinny_kernel<MB, NB, EPI, WAVES, 2, false, true> : gemm_skinny_kernel<MB, NB, EPI, WAVES, U, false, false>);
+  auto kern = p.K % 8 == 0 ? gemm_skinny_kernel<MB, NB, EPI, WAVES, U, true, false> : gemm_skinny_kernel<MB, NB, EPI, WAVES, U, false, false>;
+  if constexpr (MB < 4 || NB == 1) {
+    if (p.K >= (MB < 4 ? kLinesFrom : kLinesFromGate4))
+      kern = p.K % 8 == 0 ? gemm_skinny_kernel<MB, NB, EPI, WAVES, 2, true, true> : gemm_skinny_kernel<MB, NB, EPI, WAVES, 2, false, true>;
+  }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WAVES), 0, s, p);
 }
 

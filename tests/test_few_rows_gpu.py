@@ -68,10 +68,11 @@ def test_feed_forward_block(M, D, Hd):
 
 
 # Reductions from 2048 on, whose loads take whole lines of 8 rows: whole steps of 64 alone, with 8 indices left, with one, with four; every
-# tile (1 and 2 blocks of 16 rows; 2 and 4 of them with two of columns; the gated one with 1, 2 and 4); widths that end inside a
-# block of 16 columns and inside a group of four.  test_routes_host.py: all run on this kernel.
+# tile (1 and 2 blocks of 16 rows; 2 of them with two of columns, and 4, which keep the shorter loads; the gated one with 1, 2 and, from
+# 4096 on, 4); widths that end inside a block of 16 columns and inside a group of four.  test_routes_host.py: all run on this kernel.
 LINES = [(M, K, 1003) for M in (1, 16, 17, 33, 64) for K in (2048, 2056, 2049, 4100) if M <= 32 or K % 8 == 0] + [(40, 2056, 8203), (1, 8191, 40)]
-LINES_FFN = [(M, D, H) for M in (1, 16, 17, 33, 64) for D, H in ((2048, 2056), (2056, 2048), (2049, 2056))] + [(16, 2112, 2059), (9, 4100, 2049)]
+LINES_FFN = [(M, D, H) for M in (1, 16, 17, 33, 64) for D, H in ((2048, 2056), (2056, 2048), (2049, 2056))]
+LINES_FFN += [(16, 2112, 2059), (9, 4100, 2049), (40, 4104, 1096), (64, 4097, 1003)]
 
 
 @pytest.mark.parametrize("M,K,N", LINES)
