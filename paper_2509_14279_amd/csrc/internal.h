@@ -120,7 +120,7 @@ void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s);
 
 // ---- fp32-storage contractions in fp64 (gemm_f64.hip): GemmDesc as above, any shape ---------------
 F64Split f64_plan(int64_t I, int64_t J, int64_t R);
-bool f64_small_grads(int64_t M, int64_t K, int64_t N);
+bool f64_small_grads(int64_t M, int64_t K, int64_t N, bool split);   // split: there is room for the other kernel's sums
 size_t f64_part_bytes(const F64Split& q);
 void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
                 hipStream_t s);

@@ -12,6 +12,7 @@ std::string product(int mid, int skinny, int pad, int tiled, int split, int copi
   return std::string(pad ? "padded" : "tiled") + (split > 1 ? " split" : "") + (copied && !pad ? " from blocks" : "");
 }
 std::string gradients(const GradPlan& g) {
+  if (g.dt == kF32) return g.s64_a.small && g.s64_b.small ? "32 x 32" : "64 x 64";
   if (g.mid) return std::string("mid") + (g.split_a > 1 ? " dx-split" : "") + (g.split_b > 1 ? " dw-split" : "");
   std::string s = g.pair ? "pair" : (std::string(g.b3_fast ? "tiled" : "generic") + " and " + (g.b4_fast ? "tiled" : "generic"));
   if (g.pad) s += g.stage_x ? " padded-x" : " padded";

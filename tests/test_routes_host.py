@@ -93,3 +93,12 @@ def test_long_reductions_of_few_rows():
     assert {route("relu", "bf16", *s)[0] for s in test_few_rows_gpu.LINES} == {"few rows"}
     assert {tuple(route("ffn", "bf16", *s)) for s in test_few_rows_gpu.LINES_FFN} <= {("few rows", "few rows"), ("few rows", "mid split")}
     assert sum(route("ffn", "bf16", *s)[1] == "few rows" for s in test_few_rows_gpu.LINES_FFN) >= 12
+
+
+# fp32 gradients in 32 x 32 tiles, unless a long reduction of few of them is one wavefront's chain (whole calls, us, so / in split 64 x 64
+# tiles: 42.8 / 35.5, 35.5 / 29.8, 31.5 / 28.1, 30.6 / 27.2; and where they are faster 20.5 / 25.5, 36.6 / 44.3, 36.5 / 43.3, 44.6 / 49.6)
+@pytest.mark.parametrize("op", ["block", "relu"])
+@pytest.mark.parametrize("M,K,N,tiles", [(24, 512, 1024, 64), (26, 512, 1024, 64), (1016, 88, 48, 64), (27, 256, 1024, 64),
+                                         (256, 256, 256, 32), (300, 300, 700, 32), (1000, 200, 300, 32), (256, 512, 1024, 32)])
+def test_small_fp32_gradients(op, M, K, N, tiles):
+    assert route(op, "f32", M, K, N)[1] == f"{tiles} x {tiles}"
