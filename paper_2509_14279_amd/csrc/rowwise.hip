@@ -36,7 +36,7 @@ __device__ __forceinline__ double read_lane(double v, int l) {
 // threads per row the same normalisation of 4096 x 16384 took 66 - 89 us: its two reductions stop every wavefront of the
 // compute unit).  WPR = 8, rows above 16384: gamma and beta do not fit in LDS and are read from the caches at each row
 // (LayerNorm of 4096 x 32768: 105 us, 176 with the row reread from the caches for each sweep; x 30003: 163, 293).
-// FIT_FULL: N == 512 CH, every lane holds every vector.  FIT_VECTORS (N % 8 == 0): the vectors past the end of the row
+// FIT_FULL: N == 512 CH WPR, every lane holds every vector, and loads and stores go past the caches (non-temporal).  FIT_VECTORS (N % 8 == 0): the vectors past the end of the row
 // are fetched from a clamped address, masked to zero (GELU(0) = 0 adds nothing to the sum), left out of the squared
 // deviations and never stored; the code stays free of divergent branches either way.  FIT_ANY: rows start at any element
 // and end inside a vector - the same 16-byte loads and stores from element-aligned addresses (the hardware splits what
@@ -1429,30 +1429,31 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   if (wgs > cap) wgs = cap;
 #define FDL_F2R(CHH, FIT, WPR)                                                                                        \
   launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
-#define FDL_F2R_FEW(WPR)                                                                                              \
-  do {                                                                                                                \
-    if (fit == FIT_ANY) FDL_F2R(2, FIT_ANY, WPR); else if (past_caches) FDL_F2R(2, FIT_FULL, WPR);                     \
-    else FDL_F2R(2, FIT_VECTORS, WPR);                                                                                 \
-  } while (0)
 #define FDL_F2R_FIT(FIT)                                                                                              \
   do {                                                                                                                \
     if (ch == 1) FDL_F2R(1, FIT, 1); else if (ch == 2) FDL_F2R(2, FIT, 1); else if (ch == 4) FDL_F2R(4, FIT, 1);        \
     else if (wpr == 1) FDL_F2R(8, FIT, 1);                                                                             \
     else if (wpr == 2) FDL_F2R(8, FIT, 2); else if (wpr == 4) FDL_F2R(8, FIT, 4); else FDL_F2R(8, FIT, 8);            \
   } while (0)
-  if (ch == 2 && wpr > 1) {
-    if (wpr == 2) FDL_F2R_FEW(2); else if (wpr == 4) FDL_F2R_FEW(4); else FDL_F2R_FEW(8);
+  if (few) {
+    if (wpr == 2) FDL_F2R(2, FIT_ANY, 2); else if (wpr == 4) FDL_F2R(2, FIT_ANY, 4); else FDL_F2R(2, FIT_ANY, 8);
+  } else if (past_caches) {
+    if constexpr (ACT != ACT_GELU) { if (wpr == 4) FDL_F2R(2, FIT_FULL, 4); else FDL_F2R(2, FIT_FULL, 8); }
+  } else if (whole) {
+    if (wpr == 4) FDL_F2R(2, FIT_VECTORS, 4); else FDL_F2R(2, FIT_VECTORS, 8);
   } else if (fit == FIT_FULL) {
-    if (ch == 2) FDL_F2R(2, FIT_FULL, 1); else if (ch == 4) FDL_F2R(4, FIT_FULL, 1);
-    else if (ch == 8 && wpr == 1) FDL_F2R(8, FIT_FULL, 1); else if (ch == 8) FDL_F2R(8, FIT_FULL, 8);
-    else FDL_F2R(16, FIT_FULL, 2);
+    // (1024, 2048, 16384 and 32768 columns; 4096 where `whole` leaves it)
+    if (ch == 2) FDL_F2R(2, FIT_FULL, 1);
+    else if (ch == 4) FDL_F2R(4, FIT_FULL, 1);
+    else if (ch == 16) FDL_F2R(16, FIT_FULL, 2);
+    else if (wpr == 8) FDL_F2R(8, FIT_FULL, 8);
+    else if constexpr (ACT == ACT_GELU) FDL_F2R(8, FIT_FULL, 1);
   } else if (fit == FIT_VECTORS) {
     FDL_F2R_FIT(FIT_VECTORS);
   } else {
     FDL_F2R_FIT(FIT_ANY);
   }
 #undef FDL_F2R_FIT
-#undef FDL_F2R_FEW
 #undef FDL_F2R
 }
 
