@@ -263,11 +263,8 @@ __device__ __forceinline__ TileCoord tile_coord(int L, int tiles_i, int tiles_j)
 __device__ __forceinline__ void mfma_add(f32x4& acc, bf16x8 p, bf16x8 q) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
 }
-// acc = p q + start, or p q
-template <bool START> __device__ __forceinline__ void mfma_start(f32x4& acc, bf16x8 p, bf16x8 q, f32x4& start) {
-  if (!START) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
-  else if (&acc == &start) mfma_add(acc, p, q);
-  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)), "a"(start));
+__device__ __forceinline__ void mfma_start(f32x4& acc, bf16x8 p, bf16x8 q) {      // acc = p q
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
 }
 
 template <bool P_RM, bool Q_RM, int EPI, int BK, int NS, bool RAG, bool CRAG = false>
@@ -355,7 +352,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   const bf16_t* qfetch = qcur + (NS - 1) * qstep;
   int fidx = NS - 1;
   constexpr bool kBias = EPI == EPI_BIAS || EPI == EPI_RELU || EPI == EPI_MASK;
-  // The wave's 128 bias values go to the second half of its staging area by two direct loads, a tile ahead: no register and no
+  // The wave's 128 bias values go to the second half of its staging area by two direct loads at the top of the tile: no register and no
   // compiler-inserted wait is involved.
   const uint32_t wbias = (uint32_t)(kLdsStages + wave * 8192 + 4096);
   auto fetch_bias = [&](int i0) {
@@ -365,7 +362,6 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     dma4<0>((uint32_t)lb * 4u, bsrc, lds0 + wbias);
     dma4<256>((uint32_t)lb * 4u, bsrc + 64, lds0 + wbias);
   };
-  if (kBias) fetch_bias(tc.i0);
   wait_dma<0>();
   __syncthreads();
 
@@ -399,19 +395,8 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     const bf16_t* qwrap = has_next ? q_origin(tn.j0) : q_origin(tc.j0) + (int64_t)(nkt - 1) * qstep;
     const int fwrap = has_next ? 0 : nkt - 1;
 
-    // The accumulators are never cleared: the first MFMAs of a tile add to zero or to the bias, of which a lane needs the same four
-    // values for all blocks of a column; they wait in the column's last accumulator, whose first MFMA is the last to read them.
-    f32x4 acc[8][8];
-    if (kBias) {
-      int lb = lane;
-      asm volatile("" : "+v"(lb));
-#pragma unroll
-      for (int a = 0; a < 8; a++) acc[a][7] = *(const lds_f32x4*)(lds + wbias + (lb >> 4) * 16 + a * 64);
-#pragma unroll
-      for (int a = 0; a < 8; a++) asm volatile("" : "+a"(acc[a][7]));
-      asm volatile("s_nop 7");
-    }
-    if (kBias) fetch_bias(tn.i0);      // (covered by the waits of this tile's slices, of which there are at least NS)
+    f32x4 acc[8][8];                   // never cleared: the first MFMAs of a tile add to zero
+    if (kBias) fetch_bias(tc.i0);      // (covered by the waits of this tile's slices, of which there are at least NS)
 
     // One slice; the LDS stage it lives in is a compile-time constant (the number of slices per tile is a multiple
     // of NS - checked on the host - so a tile's slice 0 is always in stage 0 and the slice loop is unrolled NS
@@ -453,7 +438,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
 #pragma unroll
         for (int t = 0; t < 64; t++) {
           const int a = t >> 3, b = t & 7;
-          if (kFirst && cur == 0 && kk == 0) mfma_start<kBias>(acc[a][b], pf[use][a], qf[use][b], acc[a][7]);
+          if (kFirst && cur == 0 && kk == 0) mfma_start(acc[a][b], pf[use][a], qf[use][b]);
           else mfma_add(acc[a][b], pf[use][a], qf[use][b]);
           __builtin_amdgcn_sched_barrier(0);
           // next slice of the fetch stream: the following one of this tile, else (pwrap, qwrap, fwrap) = slice 0
@@ -705,14 +690,22 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
-      // rounded to bf16 and stored (forward: the bias is in the accumulators since their start; the row statistics
-      // are taken by the normalisation kernel)
+      // rounded to bf16 and stored (the row statistics are taken by the normalisation kernel).  The bias is added to the finished sum: one
+      // rounding, where a sum that starts from it has one at the bias's size for every 32 products (values of Z that are not the nearest
+      // bf16 to the exact one, 4096 x 8192 x 4096, |b| 1000 times the products: 1.1e-4, so 4e-6).  It takes 256 additions per lane and tile.
+      f32x4 bias[8];                   // of columns a * 16 + e_rq * 4 + e
+      if (kBias)
+#pragma unroll
+        for (int a = 0; a < 8; a++) bias[a] = *(const lds_f32x4*)(lds + wbias + e_rq * 16 + a * 64);
       auto stage = [&](int b) {
 #pragma unroll
         for (int a = 0; a < 8; a++) {
           bf16x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; e++) v[e] = (bf16_t)(EPI == EPI_RELU ? __builtin_fmaxf(acc[a][b][e], 0.0f) : acc[a][b][e]);
+          for (int e = 0; e < 4; e++) {
+            const float z = kBias ? acc[a][b][e] + bias[a][e] : acc[a][b][e];
+            v[e] = (bf16_t)(EPI == EPI_RELU ? __builtin_fmaxf(z, 0.0f) : z);
+          }
           *(lds_bf16x4*)(uintptr_t)woff[a] = v;
         }
       };

@@ -8,6 +8,7 @@ import test_padded_shapes_gpu
 import test_row_kernels_gpu
 import test_small_workspaces_gpu
 import test_special_values_gpu
+import test_tile_bias_gpu
 from paper_2509_14279_amd import api
 from routes import route
 
@@ -48,6 +49,7 @@ def test_forward_products_of_the_large_tiles(op):
     assert set(special) >= set(large) | {"mid", "mid split", "few rows", "generic"}
     assert set(forward(op, [s[1:] for s in test_small_workspaces_gpu.SHAPES if s[0] == "bf16"])) >= set(large)
     assert set(forward(op, test_mid_tiles_gpu.SHAPES)) >= {"mid", "mid split"}
+    assert set(forward(op, test_tile_bias_gpu.EVERY)) == set(large) | {"mid", "mid split", "few rows", "generic"}
 
 
 @pytest.mark.parametrize("op", ["block", "relu"])
