@@ -1,5 +1,6 @@
 """Normalisation of rows of exactly 4096 and 8192 columns, which four or eight wavefronts share: one row, a workgroup's remainder, more
-rows than are in flight at once, and (stand-alone norms) more bytes than the memory-side cache holds."""
+rows than are in flight at once, and (stand-alone norms) input and output of as many bytes as the memory-side cache, a row less and twice
+as many."""
 import pytest
 import torch
 
@@ -54,9 +55,9 @@ def test_normalised_gelu(M, N):
     assert torch.all((Y.double() - (x + b)).abs() <= 2.0 ** -8 * (x + b).abs() + 2.0 ** -18 * (x.abs() + b.abs() + 1))
 
 
-@pytest.mark.parametrize("N", [4096, 8192])
-def test_rows_past_the_caches_have_the_same_bits(N):
-    M = (1 << 28) // (2 * N) + 5                 # just above 256 MB
+# input and output together: 256 MB less a row; 256 MB, from which on loads and stores go past the caches; 512 MB and a little
+@pytest.mark.parametrize("N,M", [(n, m) for n in (4096, 8192) for m in ((1 << 28) // (4 * n) - 1, (1 << 28) // (4 * n), (1 << 28) // (2 * n) + 5)])
+def test_rows_past_the_caches_have_the_same_bits(N, M):
     t = {k: v.to("cuda") for k, v in I.generate_norm("bf16", 300, N, seed=N).items()}
     A, gamma, beta = t["A"].bfloat16(), t["gamma"], t["beta"]
     print(f"[even rows] {M}x{N}", flush=True)
@@ -73,3 +74,27 @@ def test_rows_past_the_caches_have_the_same_bits(N):
             assert torch.equal(whole[i:i + 300].view(torch.uint8), part[:len(whole[i:i + 300])].view(torch.uint8))
         tail = M % 300
         assert torch.equal(whole[M - tail:].view(torch.uint8), part[:tail].view(torch.uint8))
+
+
+# rows of the block at 4096 columns run in one of two forms by their number; small integers, whose products' sums are exact, give every
+# batch the same pre-activations, and sums in fp64 leave the statistics' fp32 roundings the same
+@pytest.mark.parametrize("N,batches", [(4096, (1, 1000, 1024, 1025, 4095, 4096, 5000)), (8192, (1, 700, 2000, 5000))])
+def test_rows_of_the_block_do_not_depend_on_the_rows_beside_them(N, batches):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    X = torch.randint(-3, 4, (max(batches), 8), device="cuda", generator=g).to(torch.bfloat16)
+    W = (torch.randint(-3, 4, (N, 8), device="cuda", generator=g) / 8).to(torch.bfloat16)
+    b, gamma, beta = (torch.randn(N, device="cuda", generator=g) * 0.1 + c for c in (0.0, 1.0, 0.0))
+
+    def run(M):
+        ws = torch.empty(api.fdl_workspace_bytes("bf16", M, 8, N), dtype=torch.uint8, device="cuda")
+        Y, Z = (torch.empty(M, N, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        mean, rstd = torch.empty(M, device="cuda"), torch.empty(M, device="cuda")
+        api.fdl_forward("bf16", X[:M].contiguous(), W, b, gamma, beta, EPS, Y, Z, mean, rstd, ws)
+        return Y, Z, mean, rstd
+
+    most = run(max(batches))
+    for M in batches:
+        print(f"[even rows] block {M} of {N}", flush=True)
+        for got, ref in zip(run(M), most):
+            assert torch.equal(got.view(torch.uint8), ref[:M].contiguous().view(torch.uint8))
