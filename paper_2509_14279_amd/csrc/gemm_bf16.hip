@@ -54,7 +54,7 @@ constexpr int kTile = 256;
 // of the dW reduction is planned for the part's 256 compute units; the launch itself asks the device.
 constexpr int kPlanCUs = 256;
 constexpr int kLdsStages = 128 * 1024;           // all pipeline stages together (2 x 64 KB or 4 x 32 KB)
-constexpr int kLdsBytes = kLdsStages + 4 * 8192; // + 8 KB per wave for the output block rows = 160 KB
+constexpr int kLdsBytes = kLdsStages + 4 * 8192; // + 8 KB per wave, 4 for the output block rows and 0.5 for the bias = 160 KB
 
 // Geometry of one pipeline configuration: reduction slices of BK, NS stages.
 template <int BK> struct Geo {
@@ -88,7 +88,7 @@ struct FastParams {
   int nkt;               // reduction slices per workgroup
   int split;
   int xcds;              // accelerator dies the workgroup ids are dealt over (1: no die-aware tile order)
-  int pblocked;          // 1: P (r-contiguous, BK = 32: the weights' copy, ldp columns) is stored in blocks of 32 x 32, see Loader
+  int pblocked;          // 1: P (r-contiguous, BK = 32: a copy of the weights, ldp columns) is stored in blocks of 32 x 32, see Loader
   int qblocked;          // 1: so is Q (the library's own dZ buffer, ldq columns)
   int cblocked;          // 1: the output C [J][I] is written in that blocked layout (EPI_MASK: the masked gradient;
                          //    EPI_GATE: the gated activation)
@@ -244,6 +244,17 @@ __device__ __forceinline__ TileCoord tile_coord(int L, int tiles_i, int tiles_j)
   return c;
 }
 
+// The MFMA with its accumulator in place, in AGPRs: left to choose, the register allocator moves accumulators about in straight
+// code and parks some in scratch memory.  (Written as asm they are no MFMAs to the compiler, which would otherwise put wait states
+// between one and a vector instruction that reads or has written its accumulator: the kernel does, and a host test looks at the built code.
+// Its operands come from LDS, whose waits the compiler inserts for asm too.)
+__device__ __forceinline__ void mfma_add(f32x4& acc, bf16x8 p, bf16x8 q) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
+}
+__device__ __forceinline__ void mfma_start(f32x4& acc, bf16x8 p, bf16x8 q) {      // acc = p q
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
+}
+
 // RAG: the number of output rows J is not a multiple of the tile (ragged batch dimension of F1 and B3, ragged N of
 // B4).  The last row tile then reads its Q rows from a padded copy (or from a Q buffer that is itself padded), computes
 // the surplus rows on whatever that padding holds - rows of a product are independent - and does not store them.
@@ -256,17 +267,6 @@ __device__ __forceinline__ TileCoord tile_coord(int L, int tiles_i, int tiles_j)
 // length up and makes one operand zero over the surplus (the other only has to be readable and finite there).
 // The body of the kernel: the persistent tile loop of workgroup `bid` of `nblk` on reduction part `part`.  It is a
 // function of its own so that one launch can carry two contractions side by side (see gemm_bf16_pair_kernel).
-// The MFMA with its accumulator in place, in AGPRs: left to choose, the register allocator moves accumulators about in straight
-// code and parks some in scratch memory.  (Written as asm they are no MFMAs to the compiler, which would otherwise put wait states
-// between one and a vector instruction that reads or has written its accumulator: the kernel does.  Its operands come from LDS, whose
-// waits the compiler inserts for asm too.)
-__device__ __forceinline__ void mfma_add(f32x4& acc, bf16x8 p, bf16x8 q) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
-}
-__device__ __forceinline__ void mfma_start(f32x4& acc, bf16x8 p, bf16x8 q) {      // acc = p q
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(__builtin_bit_cast(u32x4, p)), "v"(__builtin_bit_cast(u32x4, q)));
-}
-
 template <bool P_RM, bool Q_RM, int EPI, int BK, int NS, bool RAG, bool CRAG = false>
 __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, const int bid, const int nblk, const int part) {
   static_assert(!CRAG || RAG, "ragged columns come with the ragged-row checks");
@@ -319,8 +319,8 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
   const int64_t qstep = Q_RM ? (int64_t)BK * p.ldq : (qblk ? 1024 : BK);
   // first element this wave fetches of slice 0 of the tile at (i0, j0)
   // EPI_GATE: the 256 rows of a P tile are 64 gate rows, the same 64 up rows, the next 64 gate rows and their up rows
-  // (rows of P and P2 from i0/2 on), one quarter per wave: a wave's accumulator blocks a = 0, 1 then hold the gate
-  // product and a = 2, 3 the up product of the same 64 output columns, register for register, and the gated
+  // (rows of P and P2 from i0/2 on), one quarter per wave: a wave's accumulator blocks a = 0 .. 3 then hold the gate
+  // product and a = 4 .. 7 the up product of the same 64 output columns, register for register, and the gated
   // activation needs no exchange between lanes.  The tile is 128 output columns wide.
   auto p_origin = [&](int i0) {
     if (pblk)    // block (i0 / 32, r_begin / 32)
@@ -415,8 +415,8 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
       const lds_char* tq = tp + G::kOperandBytes;
       const lds_char* np_ = lds + nxt * G::kStageBytes;
       const lds_char* nq_ = np_ + G::kOperandBytes;
-      // Issue order is pinned by hand (a scheduling barrier after every step): MFMA t of a sub-slice is followed
-      // by a fragment read of the next sub-slice (even t) and, in the last sub-slice, by a direct load, so
+      // Issue order is pinned by hand (a scheduling barrier after every step): every third of the first 48 MFMAs of a sub-slice
+      // is followed by a fragment read of the next sub-slice and, in the last sub-slice, every fourth or sixth by a direct load, so
       // neither the LDS reads nor the global loads keep the matrix pipe waiting for long.
 #pragma unroll
       for (int kk = 0; kk < G::kSub; kk++) {

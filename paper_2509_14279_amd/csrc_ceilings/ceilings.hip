@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kStreamThreads) void stream_mix21_kernel(u32x4* __r
 // ---------------------------------------------------------------------------------------------- LDS probes
 // Lane -> byte offset inside a 64 KB LDS tile for each pattern (the formulas of the GEMM kernel's fragment reads
 // are restated here on purpose: this file shares no code with the library).
-// (7-9: the swizzles the GEMM kernel used before, laid out for 32 banks - kept as the reference for what a two-way
+// (7-9: fragments of 32 rows in swizzles laid out for 32 banks - kept as the reference for what a two-way
 // conflict costs and for what the bank-conflict counter reads on it.)
 enum { LDS_B128_LINEAR = 0, LDS_B128_GEMM_BK64 = 1, LDS_B128_GEMM_BK32 = 2, LDS_TR16_GEMM = 3, LDS_B128_SAME_BANK = 4,
        LDS_B64_LINEAR = 5, LDS_B32_LINEAR = 6, LDS_B128_OLD_BK64 = 7, LDS_B128_OLD_BK32 = 8, LDS_TR16_OLD = 9,
@@ -176,24 +176,38 @@ enum { LDS_B128_LINEAR = 0, LDS_B128_GEMM_BK64 = 1, LDS_B128_GEMM_BK32 = 2, LDS_
 
 template <int PAT> __device__ __forceinline__ uint32_t lds_offset(int lane, int step) {
   if (PAT == LDS_B128_LINEAR) return (uint32_t)(lane * 16 + step * 1024);
-  if (PAT == LDS_B128_GEMM_BK64 || PAT == LDS_B128_OLD_BK64) {
-    // rows of 128 B; 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7) (before: c ^ (r & 7)); sub-slice kk = step & 3
+  // fragments of 16 rows: lane l has chunk l / 16 of row l % 16
+  if (PAT == LDS_B128_GEMM_BK64) {
+    // rows of 128 B; 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7); sub-slice kk = step & 1
+    const int row = (lane & 15) + 16 * (step >> 1), c = (step & 1) * 4 + (lane >> 4);
+    return (uint32_t)(row * 128 + ((c ^ ((row >> 1) & 7)) << 4));
+  }
+  if (PAT == LDS_B128_GEMM_BK32) {
+    // rows of 64 B; chunk c of row r in slot c ^ g((r >> 2) & 3), g = 0, 2, 3, 1
+    const int row = (lane & 15) + 16 * step, q = (row >> 2) & 3, sw = ((q ^ (q >> 1)) & 1) << 1 | (q >> 1);
+    return (uint32_t)(row * 64 + (((lane >> 4) ^ sw) << 4));
+  }
+  if (PAT == LDS_TR16_GEMM) {
+    // r-major tile [r][32 chunks of 16 B], chunk c of r-row w in slot c ^ ((w & 3) << 2) ^ ((w >> 2) & 2); block a = step & 3,
+    // the half of the fragment step >> 2
+    const int p = lane & 15, r = 8 * (lane >> 4) + 4 * (step >> 2) + (p >> 2), c = (step & 3) * 2 + ((p & 3) >> 1);
+    return (uint32_t)(r * 512 + ((c ^ ((r & 3) << 2) ^ ((r >> 2) & 2)) * 16) + (p & 1) * 8);
+  }
+  if (PAT == LDS_B128_OLD_BK64) {
+    // rows of 128 B, chunk c of row r in slot c ^ (r & 7); sub-slice kk = step & 3
     const int row = (lane & 31) + 32 * (step >> 2), kk = step & 3, c = (kk << 1) | (lane >> 5);
-    const int sw = PAT == LDS_B128_GEMM_BK64 ? (row >> 1) & 7 : row & 7;
-    return (uint32_t)(row * 128 + (((c ^ sw) & 7) << 4));
+    return (uint32_t)(row * 128 + (((c ^ row) & 7) << 4));
   }
-  if (PAT == LDS_B128_GEMM_BK32 || PAT == LDS_B128_OLD_BK32) {
-    // rows of 64 B; chunk c of row r in slot c ^ ((r >> 2) & 3) (before: c ^ ((r >> 1) & 3))
+  if (PAT == LDS_B128_OLD_BK32) {
+    // rows of 64 B, chunk c of row r in slot c ^ ((r >> 1) & 3)
     const int row = (lane & 31) + 32 * (step >> 1), kk = step & 1, c = (kk << 1) | (lane >> 5);
-    const int sw = PAT == LDS_B128_GEMM_BK32 ? (row >> 2) & 3 : (row >> 1) & 3;
-    return (uint32_t)(row * 64 + (((c ^ sw) & 3) << 4));
+    return (uint32_t)(row * 64 + (((c ^ (row >> 1)) & 3) << 4));
   }
-  if (PAT == LDS_TR16_GEMM || PAT == LDS_TR16_OLD) {
-    // r-major tile [r][32 chunks of 16 B], chunk c of r-row w in slot c ^ ((w & 3) << 2) (before: << 1)
+  if (PAT == LDS_TR16_OLD) {
+    // r-major tile [r][32 chunks of 16 B], chunk c of r-row w in slot c ^ ((w & 3) << 1)
     const int G = lane >> 4, p = lane & 15, r = 8 * (G >> 1) + (p >> 2);
     const int c = (step & 3) * 4 + 2 * (G & 1) + ((p & 3) >> 1);
-    const int sw = (p >> 2) << (PAT == LDS_TR16_GEMM ? 2 : 1);
-    return (uint32_t)((r + 16 * (step >> 2)) * 512 + ((c ^ sw) * 16) + (p & 1) * 8);
+    return (uint32_t)((r + 16 * (step >> 2)) * 512 + ((c ^ ((p >> 2) << 1)) * 16) + (p & 1) * 8);
   }
   if (PAT == LDS_B128_SAME_BANK) return (uint32_t)(lane * 512 + step * 16);   // every lane on the same banks
   if (PAT == LDS_B64_LINEAR) return (uint32_t)(lane * 8 + step * 512);
