@@ -114,8 +114,7 @@ FDL_API fdl_status fdl_forward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * holds.  What counts, independent of the kernels a problem takes today: 8 bytes per (row, column tile of 32 to 128) -
  * nothing for them on the bf16 path with K % 128 == 0, N % 256 == 0, N <= 8192, M >= 128 - plus, where bf16 N and K are
  * multiples of 8 off the tile, the zero-padded weights and last rows of X.  Scratch beyond that is optional: where the
- * array has no room for it the call runs without (a reduction not split, X not copied, the
- * kernel that needs none).  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
+ * array has no room for it the call runs without (a reduction not split, X not copied, the kernel that needs none).  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
  * one GPU (different streams, different host threads) race: order them on one stream or with events.
  */
 #define FDL_STATIC_SCRATCH_BYTES (16 * 1024 * 1024)
@@ -156,9 +155,8 @@ FDL_API fdl_status fdl_backward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * Forward pass for inference (the paper's experiments are mostly forward kernels: section "Optimizing individual
  * operations", task table of the robust kernel benchmark): Y as fdl_forward computes it, and nothing saved for a
  * backward pass.  The pre-activation passes through Y itself and is normalised in place.  The workspace holds row
- * statistics and what the contraction needs: on the tuned bf16 kernels
- * zero-padded copies of W and X where N or K is off the tile, and partial sums (at most 64 MB) where
- * few output tiles make it split its reduction; for fp32 storage the partial sums of split tiles (at most 64 MB);
+ * statistics and what the contraction needs: on the tuned bf16 kernels zero-padded copies of W and X where N or K is off
+ * the tile, and partial sums (at most 64 MB) where few output tiles make it split its reduction; for fp32 storage the partial sums of split tiles (at most 64 MB);
  * for rows above 32768 (bf16) or 16384 (fp32) elements 16 bytes per row and 4096 or 2048 columns:
  * fdl_forward_inference_workspace_bytes bytes (0 for an invalid dtype or shape), 256-byte aligned.
  * in : X [M,K], W [N,K] (dt);  b, gamma, beta [N] fp32;  eps >= 0.     out: Y [M,N] (dt).

@@ -39,8 +39,7 @@ constexpr size_t kMidMostSums = (size_t)64 << 20;
 size_t mid_room(Room room, size_t kept) { return room == Room::kAll ? (kept > kMidMostSums ? kept : kMidMostSums) : (room == Room::kTight ? kept : 0); }
 
 // Estimated time, us, of dX and dW on the kernels of q, with their copies and sums of split reductions: prices fitted together with
-// mid_grads_cost's to whole backward passes of 1300 shapes.  With the rule in make_grad_plan the kernels picked take 1.01 times the
-// faster ones' time on average.
+// mid_grads_cost's to whole backward passes of 1300 shapes (see make_grad_plan for what the rule loses).
 double grads_cost(const GradPlan& q) {
   const int64_t Np = q.pad ? fast_pad_dim(q.N) : q.N, Kp = q.pad ? fast_pad_dim(q.K) : q.K, Mp = q.M > 0 ? q.M : 1;
   const double mk = (double)Mp * (double)q.K / 1e6, nk = (double)q.N * (double)q.K / 1e6;
@@ -244,9 +243,9 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may
   }
   if (dt == kBF16 && mid_supported(Mp, K, N)) {
     int sa = 1, sb = 1;
-    // 7 % for the estimates' spread.  2600 shapes where either could be the faster, whole backward passes: 4 are more than 2 % slower
-    // than in 256 x 256 tiles (6 % at most; 29 without the term for dZ, with 20 % from 2^33 products on: 11 %), the kernels picked take
-    // 1.01 times the faster ones' time on average.
+    // 7 % for the estimates' spread.  4149 shapes (256 to 40000 rows), whole backward passes, both forced: the kernels picked take 1.008
+    // times the faster ones' time on average, 1.045 at the 95th percentile, 1.25 at most, nearly always 256 x 256 tiles; 74 are more than
+    // 2 % slower than in those (7.5 % at most).  (The prices were fitted before the 256 x 256 tiles took 16 x 16 x 32 MFMAs.)
     if (1.07 * mid_grads_cost(Mp, K, N, mid_room(room, sums), &sa, &sb) < grads_cost(q)) {
       q.mid = 1; q.blocked = 0; q.split_a = sa; q.split_b = q.parts_b = sb;
       const size_t na = align256(sa > 1 ? (size_t)sa * partial_stride(M * K) * 4 : 0), nb = align256(sb > 1 ? (size_t)sb * partial_stride(N * K) * 4 : 0);

@@ -692,7 +692,7 @@ __device__ __forceinline__ void gemm_tile_loop(const FastParams& p, char* smem, 
     } else {
       // rounded to bf16 and stored (the row statistics are taken by the normalisation kernel).  The bias is added to the finished sum: one
       // rounding, where a sum that starts from it has one at the bias's size for every 32 products (values of Z that are not the nearest
-      // bf16 to the exact one, 4096 x 8192 x 4096, |b| 1000 times the products: 1.1e-4, so 4e-6).  It takes 256 additions per lane and tile.
+      // bf16 to the exact one, 4096 x 8192 x 4096, |b| 1000 times the products: 1.1e-4, so 3e-7).  It takes 256 additions per lane and tile.
       f32x4 bias[8];                   // of columns a * 16 + e_rq * 4 + e
       if (kBias)
 #pragma unroll

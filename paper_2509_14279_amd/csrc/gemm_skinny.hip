@@ -9,13 +9,13 @@
 //     a row of X or W, so both operands go straight from global memory into the registers the matrix pipe reads: no LDS
 //     tile, no barrier, and U steps of loads in flight per wavefront;
 //   * the wavefronts' sums meet in LDS once, at the end, in a fixed order (pairwise), in fp32.
-// Measured (weights not in the L2), M x K x N, us: 16 x 4096 x 4096 10 (3.4 TB/s), 32 rows 14, 64 rows 20, 128 rows 27;
-// 16 x 11008 x 4096 24 (3.8 TB/s); gated 16 x 4096 x 11008 46 (3.9 TB/s).  The 64 x 64 tiles of the generic kernel took 93 us
+// Measured, M x K x N, us: 16 x 4096 x 4096 11 (3.1 TB/s), 32 rows 15; 16 x 11008 x 4096 23 (3.9 TB/s); gated 16 x 4096 x 11008 37
+// (4.9 TB/s; 46 by 64-byte loads).  The 64 x 64 tiles of the generic kernel took 93 us
 // for 32 x 4096 x 4096 (64 workgroups, each alone with 256 slices) and 158 for each product of the 16-row block.  Loads of W
 // past the caches cost 10 - 20 %; 16 steps in flight gain nothing over 8.
 // A compute unit's vector cache has room for 256 lines, which is what limits the loads in flight, X's among them: 1024 lines of either
-// matrix take a compute unit 4 us (32 x 4096 x 4096: 7 us without the loads of X, 15 with).  A fragment's 64-byte pieces of 16 rows
-// hold a line for half of its bytes; from kLinesFrom on a load therefore takes 128 bytes of 8 rows, and lanes exchange what is
+// matrix take a compute unit 4 us (32 x 4096 x 4096: 7.5 us without the loads of X, 15.2 with).  A fragment's 64-byte pieces of 16 rows
+// hold a line for half of its bytes; from kLinesFrom on (which see) a load therefore takes 128 bytes of 8 rows, and lanes exchange what is
 // not theirs (as_fragments).
 #include "common.hip.h"
 #include "internal.h"
@@ -347,8 +347,11 @@ template <int EPI> void dispatch_skinny(const SkinnyParams& p, hipStream_t s) {
 // every 16 or 32 columns, so its time grows with its workgroups: per 256 of them a start and a price per element of K, which
 // depends on the tile and on where rows start; above 4096 rows (2048 that start at any element) X no longer stays in the
 // caches and the estimate no longer holds.  The tiled kernel's time is its own estimate, and the padded copies' where they are
-// needed.  On 2247 shapes (1 - 5000 rows, K to 8192, N to 262144) the kernel picked takes 1.01 times the fastest one's time on
-// average, 1.06 at the 95th percentile.  Measured, us, this kernel / generic: 4096 x 4096: 16 rows 10 / 87, 64 rows 20 / 88;
+// needed.  The prices are those of 64-byte loads and of the 32 x 32 x 16 tiles, which the present kernels beat by up to 15 and 8 %.  Inference,
+// each kernel forced, the 128 x 128 tiles (offered after this) among them: on 3096 shapes (1 - 5000 rows, K to 8192, N to 16384) the kernel
+// picked takes 1.015 times the fastest one's time on average, 1.07 at the 95th percentile, 1.6 at most; on 1476 of up to 300 rows and K from
+// 2048 on 1.03, 1.18 and 2.1, nearly always this kernel where 128 x 128 tiles with a split reduction are faster, rows at any element above
+// all (26 x 5323 x 664 40 / 19).  Measured with 64-byte loads, us, this kernel / generic: 4096 x 4096: 16 rows 10 / 87, 64 rows 20 / 88;
 // 64 x 65536, 127 rows 36 / 16; 4097 x 65536: 31 rows 567 / 261, 127 rows 1169 / 293; this kernel / tiled: 4096 x 4096: 128 rows
 // 29 / 31, 256 rows 48 / 35; 4096 x 1024: 384 rows 33 / 34, 1536 rows 72 / 41.
 static int64_t skinny_rows(int64_t K) { return K % 8 == 0 ? 4096 : 2048; }
@@ -389,7 +392,7 @@ Xwt pick_xwt(int64_t M, int64_t K, int64_t N, bool may_copy, bool may_pad, bool 
 // products (row blocks of 64; the narrower ones count as 26 - 50 rows), a tenth more for rows at 4-byte addresses, three times that
 // for rows that start at any element.  (Priced like the last, 330 shapes with even D that is no multiple of 8, 1 - 300 rows, lost 2 %
 // to the faster of this kernel and the 128 x 128 tiles, up to 35 %: 21 x 3924 x 3698 26.7 us here, 42.6 there; now 0.1 %, below 5 %.)
-// Measured, us, whole blocks: gate on this kernel / as two generic products: 16 x 4096 x 11008 74 / 478, 16 x 4097 x 11008 147 /
+// Measured, us, whole blocks: gate on this kernel / as two generic products: 16 x 4096 x 11008 64 / 478, 16 x 4097 x 11008 147 /
 // 280, 66 x 4097 x 65536 2963 / 2120.
 GatePlan pick_gate(int64_t M, int64_t D, int64_t H, bool can_pad) {
   GatePlan best = {Gate::kSeparate, Xwt::kGeneric, 0.0, 0.0};

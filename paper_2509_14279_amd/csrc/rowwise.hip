@@ -1403,16 +1403,20 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // 2048 x 4097 and beyond are faster the other way.
   const int spread = ch * wpr / 2;
   const bool few = N % 8 != 0 && spread >= 2 && spread <= 8 && M * spread <= (int64_t)di.cus * 32;
-  // Rows of exactly 4096 and 8192 always do, the next of a workgroup's rows in flight beside it in three or two workgroups per compute
-  // unit; a lane with 8 or 16 vectors left a fraction of the wavefronts.  us, before / so: RMSNorm 16384 x 4096 50.0 / 44.7, LayerNorm 64 x
-  // 4096 4.6 / 3.3, 16384 x 4096 50.5 / 43.3, 65536 x 4096 191 / 182, 4096 x 8192 30.3 / 23.2, 65536 x 8192 390 / 369; inference with
-  // K = 128, 8192 x 4096 54.9 / 47.6, 65536 x 8192 630 / 599.  (Between 1024 and 4096 rows of 4096 the normalisation of GELU has too few
-  // rows for what a workgroup sets up: 2048 22.3 / 23.6.  2048 columns are 10 % slower so, other widths 5 to 15 %.)
+  // Rows of exactly 4096 and 8192 always do, the next of a workgroup's rows in flight beside it; a lane with 8 or 16 vectors left a fraction
+  // of the wavefronts.  us, before / so: RMSNorm 12288 x 4096 36.0 / 30.4, LayerNorm 12288 x 4096 39.7 / 31.3, 5120 x 8192 32.2 / 26.8,
+  // 16384 x 8192 97 / 88; inference with K = 128, 8192 x 4096 54.9 / 47.6, 65536 x 8192 630 / 599.  (Between 1024 and 4096 rows of 4096 the
+  // normalisation of GELU has too few rows for what a workgroup sets up: 2048 22.3 / 23.6.)  Other multiples of 8 keep a wavefront or two
+  // per row.  So over that, 64 to 16384 rows: LayerNorm 2560 to 4088 columns 0.84 - 1.03 (mean 0.98), 5120 to 8184 0.93 - 1.03 (0.99),
+  // RMSNorm 0.90 - 1.02 and 0.89 - 1.01, inference with K = 128 0.89 - 1.03 (0.95) and 0.91 - 1.12 (1.04).
   const bool whole = N == 8192 || (N == 4096 && (ACT != ACT_GELU || M <= 1024 || M >= 4096));
   if (few || whole) { ch = 2; wpr = spread; }
   const int fit = ch > 1 && N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
-  // (A stand-alone norm whose input and output together fill the memory-side cache is faster past the caches: LayerNorm
-  // 65536 x 8192 404 us, so 369, RMSNorm 16384 x 4096 48.0, so 44.7.)
+  // A stand-alone norm whose input and output together fill the memory-side cache runs past the caches.  4096 columns, us, through / past
+  // them, buffers new to every pass: LayerNorm 8192 rows 25.0 / 24.8, 12288 38.6 / 35.1, 16384 49.0 / 45.5, 20480 61.9 / 56.4 (RMSNorm
+  // 24.4 / 24.4, 38.1 / 34.7, 48.4 / 45.3, 61.3 / 56.4); the same buffers in every pass, which is how a layer finds what the one before it
+  // wrote: 21.6 / 23.7, 31.3 / 34.7, 44.5 / 44.8, 61.5 / 55.9 (20.8 / 23.1, 30.3 / 33.6, 40.9 / 44.4, 60.6 / 55.7).  The line stands where the
+  // two weigh the same.
   const bool past_caches = whole && ACT != ACT_GELU && M * N * 4 >= kMemorySideCache;
   const int nt = 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them

@@ -113,7 +113,7 @@ def test_feed_forward_block(M, D, Hd):
 
 @pytest.mark.parametrize("M,K,N", TILED + LARGE)
 def test_unrounded_fp32_biases(M, K, N):
-    # b is fp32 by contract also with bf16 matrices and enters the 256 x 256 tiles as three bf16 pieces: the stored
+    # b is fp32 by contract also with bf16 matrices and is added in fp32: the stored
     # pre-activation is the correctly rounded one, within half a bf16 unit in the last place and the fp32 accumulation's error
     # (at most K terms: measured against 8 x 2^-24 of the sum of magnitudes, sixteen partial sums of matrix instructions)
     cfg = I.custom("bf16", M, K, N, seed=9600 + M + K + N)

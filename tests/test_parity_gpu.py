@@ -135,8 +135,8 @@ def test_aligned_and_long_row_shapes(dtype, shape):
 
 def test_bf16_with_unrounded_fp32_vectors():
     """b, gamma, beta are fp32 by contract also with bf16 matrices.  The seeded configurations round them to bf16
-    values; here they keep all 24 bits, so the lower pieces of the bias (which enters the forward contraction as
-    three bf16 pieces through the matrix pipe where the product is tiled: test_padded_shapes_gpu.py) matter.  The stored pre-activation must be the correctly rounded one:
+    values; here they keep all 24 bits, so the lower bits of the bias (added in fp32; where the product is
+    tiled: test_padded_shapes_gpu.py) matter.  The stored pre-activation must be the correctly rounded one:
     within half a bf16 unit in the last place of the exact value, plus the fp32 accumulation error of the sum."""
     cfg = I.custom("bf16", 512, 256, 768, seed=41)
     t = I.generate(cfg)
