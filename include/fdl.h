@@ -114,8 +114,9 @@ FDL_API fdl_status fdl_forward(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
  * holds.  What counts, independent of the kernels a problem takes today: 8 bytes per (row, column tile of 32 to 128) -
  * nothing for them on the bf16 path with K % 128 == 0, N % 256 == 0, N <= 8192, M >= 128 - plus, where bf16 N and K are
  * multiples of 8 off the tile, the zero-padded weights and last rows of X.  Scratch beyond that is optional: where the
- * array has no room for it the call runs without (a reduction not split, X not copied, the kernel that needs none).  Every call on one GPU shares that GPU's array, so two calls that overlap in time on
- * one GPU (different streams, different host threads) race: order them on one stream or with events.
+ * array has no room for it the call runs without (a reduction not split, X not copied, the kernel that needs none).
+ * Every call on one GPU shares that GPU's array, so two calls that overlap in time on one GPU (different streams,
+ * different host threads) race: order them on one stream or with events.
  */
 #define FDL_STATIC_SCRATCH_BYTES (16 * 1024 * 1024)
 FDL_API fdl_status fdl_forward_static(fdl_dtype dt, int64_t M, int64_t K, int64_t N,
