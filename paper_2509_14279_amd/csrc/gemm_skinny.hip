@@ -304,8 +304,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(SkinnyParams p)
 // Reduction length from which whole lines are loaded (feed-forward block, us, 64-byte pieces / lines: 16 x 4096 x 11008 62.0 / 57.1,
 // 1 x 4096 x 11008 52.8 / 48.5; at K = 1024 to 2000 equal within 2 %, below 1024 3 to 6 % slower: two steps of a wavefront or fewer).
 // Four row blocks load X more than W.  Lines over pieces, whole calls, mean (and extremes) of 140 to 300 shapes each: gated, D 1024 to
-// 4096 1.00 (0.88 - 1.07), beyond 0.97 (0.85 - 1.04); beside two column blocks, K 1024 to 2048 1.05 (up to 1.23: inference 50 x 2048 x 8960
-// 76 / 86 us), 2048 to 2900 1.02 (up to 1.15), and beyond another kernel is picked.
+// 4096 1.00 (0.88 - 1.07), beyond 0.97 (0.85 - 1.04); beside two column blocks, K 1024 to 2048 1.05 (up to 1.23), 2048 to 2900
+// 1.02 (up to 1.15: inference 34 x 2176 x 9152 29.4 / 32.7 us), and beyond another kernel is picked.
 constexpr int64_t kLinesFrom = 2048, kLinesFromGate4 = 4096;
 template <int MB, int NB, int EPI, int WAVES, int U> void launch_skinny(SkinnyParams p, hipStream_t s) {
   p.mblocks = (p.M + 16 * MB - 1) / (16 * MB);

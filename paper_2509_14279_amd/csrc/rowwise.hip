@@ -36,7 +36,8 @@ __device__ __forceinline__ double read_lane(double v, int l) {
 // threads per row the same normalisation of 4096 x 16384 took 66 - 89 us: its two reductions stop every wavefront of the
 // compute unit).  WPR = 8, rows above 16384: gamma and beta do not fit in LDS and are read from the caches at each row
 // (LayerNorm of 4096 x 32768: 105 us, 176 with the row reread from the caches for each sweep; x 30003: 163, 293).
-// FIT_FULL: N == 512 CH WPR, every lane holds every vector, and loads and stores go past the caches (non-temporal).  FIT_VECTORS (N % 8 == 0): the vectors past the end of the row
+// FIT_FULL: N == 512 CH WPR, every lane holds every vector, and loads and stores go past the caches (non-temporal).
+// FIT_VECTORS (N % 8 == 0): the vectors past the end of the row
 // are fetched from a clamped address, masked to zero (GELU(0) = 0 adds nothing to the sum), left out of the squared
 // deviations and never stored; the code stays free of divergent branches either way.  FIT_ANY: rows start at any element
 // and end inside a vector - the same 16-byte loads and stores from element-aligned addresses (the hardware splits what
@@ -1408,7 +1409,9 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // 16384 x 8192 97 / 88; inference with K = 128, 8192 x 4096 54.9 / 47.6, 65536 x 8192 630 / 599.  (Between 1024 and 4096 rows of 4096 the
   // normalisation of GELU has too few rows for what a workgroup sets up: 2048 22.3 / 23.6.)  Other multiples of 8 keep a wavefront or two
   // per row.  So over that, 64 to 16384 rows: LayerNorm 2560 to 4088 columns 0.84 - 1.03 (mean 0.98), 5120 to 8184 0.93 - 1.03 (0.99),
-  // RMSNorm 0.90 - 1.02 and 0.89 - 1.01, inference with K = 128 0.89 - 1.03 (0.95) and 0.91 - 1.12 (1.04).
+  // RMSNorm 0.90 - 1.02 and 0.89 - 1.01, inference with K = 128 0.89 - 1.03 (0.95) and 0.91 - 1.12 (1.04).  From some 256 MB per buffer on
+  // a stand-alone norm's time hangs on the distance between input and output, where a wavefront per row did not care: LayerNorm 65536 x
+  // 4096, 191 us that way, 177 - 181 so at 15 of 22 distances from 0 to 256 MB, 192 - 212 at the others; 16384 x 4096 45 at any.
   const bool whole = N == 8192 || (N == 4096 && (ACT != ACT_GELU || M <= 1024 || M >= 4096));
   if (few || whole) { ch = 2; wpr = spread; }
   const int fit = ch > 1 && N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
