@@ -54,11 +54,12 @@ template <int CH, int FIT, int NT, int ACT, int WPR>
 __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float eps, const bf16_t* Z,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
                                                       bf16_t* Y, float* __restrict__ mean,
-                                                      float* __restrict__ rstd) {
+                                                      float* __restrict__ rstd, int stretches) {
   // products are formed once and reused (fusing GELU's final multiplication into each later use would keep
   // both of its factors alive for every element of the row); the fused operations wanted are written out
 #pragma clang fp contract(off)
   constexpr bool FULL = FIT == FIT_FULL, ANY = FIT == FIT_ANY;
+  constexpr bool kStretches = FULL && WPR > 1 && ACT != ACT_GELU;
   // The block's statistics (ACT_GELU; saved, and multiplied into everything the backward pass forms): fp32 inside a vector -
   // up to 1024 columns, where a row has little other work, inside a row of 16 lanes - and fp64 from there on, as is rstd.
   // (fp32 throughout, inference 65536 x 128 x 512: 61.1 us, so 61.9, fp64 from the vector on 64.2; 4096 x 128 x 16384: 108.8,
@@ -101,7 +102,17 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
     }
   }
   __syncthreads();
-  const int64_t nw = (int64_t)gridDim.x * (NT / 64 / WPR);
+  // A workgroup's rows: every gridDim.x-th group of kRows, or (stretches > 1, of which the grid is a multiple) the same within its own
+  // stretch of them.
+  constexpr int kRows = NT / 64 / WPR;
+  int64_t first = (int64_t)blockIdx.x * kRows, nw = (int64_t)gridDim.x * kRows, end = M;
+  if (kStretches && stretches > 1) {
+    const int64_t len = (M + (int64_t)stretches * kRows - 1) / ((int64_t)stretches * kRows) * kRows;
+    const int64_t at = (int64_t)(blockIdx.x % (unsigned)stretches) * len;
+    first = at + (int64_t)(blockIdx.x / (unsigned)stretches) * kRows;
+    nw = (int64_t)(gridDim.x / (unsigned)stretches) * kRows;
+    end = at + len < M ? at + len : M;
+  }
   const stat_t inv_n = (stat_t)1 / (stat_t)N;
   const int sub = WPR == 1 ? 0 : wave % WPR;   // which part of every vector group this wavefront of the row holds
   // sum k of this trip's row over the wavefronts that share it (row_sum_slot: why one barrier each is enough)
@@ -160,7 +171,7 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
       raw[c] = *reinterpret_cast<const u32x4*>(zr + voff[c]);
     }
   };
-  int64_t row = (int64_t)blockIdx.x * (NT / 64 / WPR) + wave / WPR;
+  int64_t row = first + wave / WPR;
   {
     const bf16_t* zr = Z + (row < M ? row : M - 1) * N;
 #pragma unroll
@@ -168,8 +179,8 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   }
   // Where wavefronts share rows, those of a workgroup stay together (barriers): the last trip may find some of them past
   // the last row, which they then redo without storing.
-  for (int64_t lead = (int64_t)blockIdx.x * (NT / 64 / WPR); WPR == 1 ? row < M : lead < M; row += nw, lead += nw, trip++) {
-    const bool live = WPR == 1 || row < M;
+  for (int64_t lead = first; WPR == 1 ? row < end : lead < end; row += nw, lead += nw, trip++) {
+    const bool live = WPR == 1 || row < end;
     float a[CH][8];
     sum_t sum = 0;
     const bf16_t* znext = Z + (row + nw < M ? row + nw : M - 1) * N;
@@ -1373,7 +1384,7 @@ template <class T> void b1_fused_impl(int64_t M, int64_t N, int64_t ldz, int gro
 
 // one instantiation: gamma/beta (4 KB per 512 columns) plus the Phi table can exceed the default 64 KB of dynamic LDS
 template <int CH, int FIT, int NT, int ACT, int WPR = 1>
-void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float eps, const bf16_t* Z, const float* gamma,
+void launch_f2_rows_one(int64_t wgs, int stretches, hipStream_t s, int64_t M, int64_t N, float eps, const bf16_t* Z, const float* gamma,
                         const float* beta, bf16_t* Y, float* mean, float* rstd) {
   constexpr size_t kLds = (affine_in_lds(CH * WPR) ? (size_t)CH * WPR * 4096 : 0) + (ACT == ACT_GELU ? GaussTable<false>::kBytes : 0);
   auto kern = f2_rows_kernel<CH, FIT, NT, ACT, WPR>;
@@ -1381,7 +1392,7 @@ void launch_f2_rows_one(int64_t wgs, hipStream_t s, int64_t M, int64_t N, float 
     static OnceFlags configured;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLds, &configured)) return;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(NT), kLds, s, M, N, eps, Z, gamma, beta, Y, mean, rstd);
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(NT), kLds, s, M, N, eps, Z, gamma, beta, Y, mean, rstd, stretches);
 }
 
 constexpr int64_t kMemorySideCache = (int64_t)256 << 20;      // bytes
@@ -1409,9 +1420,7 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // 16384 x 8192 97 / 88; inference with K = 128, 8192 x 4096 54.9 / 47.6, 65536 x 8192 630 / 599.  (Between 1024 and 4096 rows of 4096 the
   // normalisation of GELU has too few rows for what a workgroup sets up: 2048 22.3 / 23.6.)  Other multiples of 8 keep a wavefront or two
   // per row.  So over that, 64 to 16384 rows: LayerNorm 2560 to 4088 columns 0.84 - 1.03 (mean 0.98), 5120 to 8184 0.93 - 1.03 (0.99),
-  // RMSNorm 0.90 - 1.02 and 0.89 - 1.01, inference with K = 128 0.89 - 1.03 (0.95) and 0.91 - 1.12 (1.04).  From some 256 MB per buffer on
-  // a stand-alone norm's time hangs on the distance between input and output, where a wavefront per row did not care: LayerNorm 65536 x
-  // 4096, 191 us that way, 177 - 181 so at 15 of 22 distances from 0 to 256 MB, 192 - 212 at the others; 16384 x 4096 45 at any.
+  // RMSNorm 0.90 - 1.02 and 0.89 - 1.01, inference with K = 128 0.89 - 1.03 (0.95) and 0.91 - 1.12 (1.04).
   const bool whole = N == 8192 || (N == 4096 && (ACT != ACT_GELU || M <= 1024 || M >= 4096));
   if (few || whole) { ch = 2; wpr = spread; }
   const int fit = ch > 1 && N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
@@ -1429,13 +1438,20 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // up for half the rows, before the others end.  LayerNorm / RMSNorm, us, a wavefront per row / four / two per compute unit: 1536 rows
   // 10.6 11.7 10.5 / 9.5 10.1 9.0, 1792 11.3 12.6 11.3 / 10.2 11.5 10.3, 2304 18.5 15.8 13.7 / 15.9 13.6 12.5, 4096 21.8 22.8 22.0 / 21.3 20.9
   // 20.9, 6144 35.3 31.7 31.8 / 35.6 30.1 30.4.)
+  // From half as much again on, one workgroup per compute unit, each die in a stretch of the rows of its own: where all walk the
+  // rows side by side, what they read and, rows behind, write keep one distance, and at some distances the two get in each other's way.
+  // LayerNorm 65536 x 4096, us, at 13 distances between input and output from 0 to 128 MB: a wavefront per row 189 - 193, two workgroups side by
+  // side 177 - 213, so 171 - 174 (one side by side 173 - 213, two so 187 - 196); 65536 x 8192 382 - 391, 359 - 429, 349 - 365.  Side by
+  // side / so at a good distance: 16384 x 4096 45 / 48, 20000 54.8 / 55.0, 24000 64.9 / 64.4, 10000 x 8192 55.6 / 55.3, 16384 88.5 / 86.4.
+  const bool apart = past_caches && M * N * 4 >= kMemorySideCache / 2 * 3;
   const bool pair = past_caches || (N == 8192 && ACT != ACT_GELU);
   const int64_t per_cu = whole && !pair ? (ACT == ACT_GELU && N == 4096 ? 3 : 4)
                                               : (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (ch == 1 ? 8 : (16 / ch > wpr ? 16 / ch / wpr : 1)));
-  const int64_t cap = (int64_t)di.cus * per_cu;
+  const int64_t cap = (int64_t)di.cus * (apart ? 1 : per_cu);
   if (wgs > cap) wgs = cap;
+  const int stretches = apart && wgs % di.xcds == 0 ? di.xcds : 1;
 #define FDL_F2R(CHH, FIT, WPR)                                                                                        \
-  launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
+  launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, stretches, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
 #define FDL_F2R_FIT(FIT)                                                                                              \
   do {                                                                                                                \
     if (ch == 1) FDL_F2R(1, FIT, 1); else if (ch == 2) FDL_F2R(2, FIT, 1); else if (ch == 4) FDL_F2R(4, FIT, 1);        \

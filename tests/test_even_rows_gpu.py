@@ -1,6 +1,6 @@
 """Normalisation of rows of exactly 4096 and 8192 columns, which four or eight wavefronts share: one row, a workgroup's remainder, more
-rows than are in flight at once, and (stand-alone norms) input and output of as many bytes as the memory-side cache, a row less and twice
-as many."""
+rows than are in flight at once, and (stand-alone norms) input and output of as many bytes as the memory-side cache, half as many more,
+twice as many."""
 import pytest
 import torch
 
@@ -55,8 +55,10 @@ def test_normalised_gelu(M, N):
     assert torch.all((Y.double() - (x + b)).abs() <= 2.0 ** -8 * (x + b).abs() + 2.0 ** -18 * (x.abs() + b.abs() + 1))
 
 
-# input and output together: 256 MB less a row; 256 MB, from which on loads and stores go past the caches; 512 MB and a little
-@pytest.mark.parametrize("N,M", [(n, m) for n in (4096, 8192) for m in ((1 << 28) // (4 * n) - 1, (1 << 28) // (4 * n), (1 << 28) // (2 * n) + 5)])
+# input and output together: 256 MB less a row; 256 MB, from which on loads and stores go past the caches; 384 MB less a row; 384 MB, from
+# which on each die has a stretch of the rows; a row more; 512 MB and a little
+@pytest.mark.parametrize("N,M", [(n, m) for n in (4096, 8192) for m in ((1 << 28) // (4 * n) - 1, (1 << 28) // (4 * n), (3 << 27) // (4 * n) - 1,
+                                                                       (3 << 27) // (4 * n), (3 << 27) // (4 * n) + 1, (1 << 28) // (2 * n) + 5)])
 def test_rows_past_the_caches_have_the_same_bits(N, M):
     t = {k: v.to("cuda") for k, v in I.generate_norm("bf16", 300, N, seed=N).items()}
     A, gamma, beta = t["A"].bfloat16(), t["gamma"], t["beta"]
