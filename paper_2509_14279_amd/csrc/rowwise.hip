@@ -59,7 +59,7 @@ __global__ __launch_bounds__(NT) void f2_rows_kernel(int64_t M, int64_t N, float
   // both of its factors alive for every element of the row); the fused operations wanted are written out
 #pragma clang fp contract(off)
   constexpr bool FULL = FIT == FIT_FULL, ANY = FIT == FIT_ANY;
-  constexpr bool kStretches = FULL && WPR > 1 && ACT != ACT_GELU;
+  constexpr bool kStretches = FULL && WPR > 1;
   // The block's statistics (ACT_GELU; saved, and multiplied into everything the backward pass forms): fp32 inside a vector -
   // up to 1024 columns, where a row has little other work, inside a row of 16 lanes - and fp64 from there on, as is rstd.
   // (fp32 throughout, inference 65536 x 128 x 512: 61.1 us, so 61.9, fp64 from the vector on 64.2; 4096 x 128 x 16384: 108.8,
@@ -1424,12 +1424,23 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   const bool whole = N == 8192 || (N == 4096 && (ACT != ACT_GELU || M <= 1024 || M >= 4096));
   if (few || whole) { ch = 2; wpr = spread; }
   const int fit = ch > 1 && N == (int64_t)ch * wpr * 512 ? FIT_FULL : (N % 8 == 0 ? FIT_VECTORS : FIT_ANY);
+  // Where all workgroups walk the rows side by side, what they read and, rows behind, write keep one distance, and at some distances the
+  // two get in each other's way.  From half as much again as the memory-side cache on, they walk stretches of the rows instead.
+  // Stand-alone norms, one workgroup per compute unit, a stretch for each die: LayerNorm 65536 x 4096, us, at 13 distances between input and
+  // output from 0 to 128 MB: a wavefront per row 189 - 193, two workgroups side by side 177 - 213, so 171 - 174 (one side by side 173 - 213, two so
+  // 187 - 196); 65536 x 8192 382 - 391, 359 - 429, 349 - 365.  Side by side / so at a good distance: 16384 x 4096 45 / 48, 20000 54.8 / 55.0,
+  // 24000 64.9 / 64.4, 10000 x 8192 55.6 / 55.3, 16384 88.5 / 86.4.
+  // The block, two workgroups past the caches, three stretches (eight 186 - 198, one workgroup 210 - 219), unless it normalises in place: at
+  // four distances, a wavefront per row / through the caches side by side / so: 24576 x 4096 78 - 82 77 - 78 73 - 74, 65536 x 4096 193 - 200 204 - 209
+  // 187 - 191, 32768 x 8192 199 - 203 197 - 208 192 - 194, 65536 x 8192 399 - 404 407 - 424 378 - 392; 22000 x 4096 70 64 67, 11000 x 8192 77 67
+  // 69; in place 65536 x 4096 196 167 197.
+  const bool apart = whole && M * N * 4 >= kMemorySideCache / 2 * 3 && (ACT != ACT_GELU || Zsave != Y);
   // A stand-alone norm whose input and output together fill the memory-side cache runs past the caches.  4096 columns, us, through / past
   // them, buffers new to every pass: LayerNorm 8192 rows 25.0 / 24.8, 12288 38.6 / 35.1, 16384 49.0 / 45.5, 20480 61.9 / 56.4 (RMSNorm
   // 24.4 / 24.4, 38.1 / 34.7, 48.4 / 45.3, 61.3 / 56.4); the same buffers in every pass, which is how a layer finds what the one before it
   // wrote: 21.6 / 23.7, 31.3 / 34.7, 44.5 / 44.8, 61.5 / 55.9 (20.8 / 23.1, 30.3 / 33.6, 40.9 / 44.4, 60.6 / 55.7).  The line stands where the
   // two weigh the same.
-  const bool past_caches = whole && ACT != ACT_GELU && M * N * 4 >= kMemorySideCache;
+  const bool past_caches = apart || (whole && ACT != ACT_GELU && M * N * 4 >= kMemorySideCache);
   const int nt = 512;
   // a workgroup of the widest variant fills a CU's register file; narrower rows leave room for more of them
   const int64_t per_wg = nt / 64 / wpr;
@@ -1438,18 +1449,13 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   // up for half the rows, before the others end.  LayerNorm / RMSNorm, us, a wavefront per row / four / two per compute unit: 1536 rows
   // 10.6 11.7 10.5 / 9.5 10.1 9.0, 1792 11.3 12.6 11.3 / 10.2 11.5 10.3, 2304 18.5 15.8 13.7 / 15.9 13.6 12.5, 4096 21.8 22.8 22.0 / 21.3 20.9
   // 20.9, 6144 35.3 31.7 31.8 / 35.6 30.1 30.4.)
-  // From half as much again on, one workgroup per compute unit, each die in a stretch of the rows of its own: where all walk the
-  // rows side by side, what they read and, rows behind, write keep one distance, and at some distances the two get in each other's way.
-  // LayerNorm 65536 x 4096, us, at 13 distances between input and output from 0 to 128 MB: a wavefront per row 189 - 193, two workgroups side by
-  // side 177 - 213, so 171 - 174 (one side by side 173 - 213, two so 187 - 196); 65536 x 8192 382 - 391, 359 - 429, 349 - 365.  Side by
-  // side / so at a good distance: 16384 x 4096 45 / 48, 20000 54.8 / 55.0, 24000 64.9 / 64.4, 10000 x 8192 55.6 / 55.3, 16384 88.5 / 86.4.
-  const bool apart = past_caches && M * N * 4 >= kMemorySideCache / 2 * 3;
   const bool pair = past_caches || (N == 8192 && ACT != ACT_GELU);
   const int64_t per_cu = whole && !pair ? (ACT == ACT_GELU && N == 4096 ? 3 : 4)
                                               : (wpr == 8 || (ch == 2 && wpr > 1) ? 2 : (ch == 1 ? 8 : (16 / ch > wpr ? 16 / ch / wpr : 1)));
-  const int64_t cap = (int64_t)di.cus * (apart ? 1 : per_cu);
+  const int64_t cap = (int64_t)di.cus * (apart && ACT != ACT_GELU ? 1 : per_cu);
   if (wgs > cap) wgs = cap;
-  const int stretches = apart && wgs % di.xcds == 0 ? di.xcds : 1;
+  const int stretches = apart ? (ACT == ACT_GELU ? 3 : di.xcds) : 1;
+  wgs -= wgs % stretches;            // (of many)
 #define FDL_F2R(CHH, FIT, WPR)                                                                                        \
   launch_f2_rows_one<CHH, FIT, 512, ACT, WPR>(wgs, stretches, s, M, N, eps, (const bf16_t*)Zsave, gamma, beta, (bf16_t*)Y, mean, rstd)
 #define FDL_F2R_FIT(FIT)                                                                                              \
@@ -1461,7 +1467,7 @@ void launch_rows_act(int64_t M, int64_t N, float eps, const void* Zsave, const f
   if (few) {
     if (wpr == 2) FDL_F2R(2, FIT_ANY, 2); else if (wpr == 4) FDL_F2R(2, FIT_ANY, 4); else FDL_F2R(2, FIT_ANY, 8);
   } else if (past_caches) {
-    if constexpr (ACT != ACT_GELU) { if (wpr == 4) FDL_F2R(2, FIT_FULL, 4); else FDL_F2R(2, FIT_FULL, 8); }
+    if (wpr == 4) FDL_F2R(2, FIT_FULL, 4); else FDL_F2R(2, FIT_FULL, 8);
   } else if (whole) {
     if (wpr == 4) FDL_F2R(2, FIT_VECTORS, 4); else FDL_F2R(2, FIT_VECTORS, 8);
   } else if (fit == FIT_FULL) {

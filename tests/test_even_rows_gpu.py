@@ -78,9 +78,10 @@ def test_rows_past_the_caches_have_the_same_bits(N, M):
         assert torch.equal(whole[M - tail:].view(torch.uint8), part[:tail].view(torch.uint8))
 
 
-# rows of the block at 4096 columns run in one of two forms by their number; small integers, whose products' sums are exact, give every
-# batch the same pre-activations, and sums in fp64 leave the statistics' fp32 roundings the same
-@pytest.mark.parametrize("N,batches", [(4096, (1, 1000, 1024, 1025, 4095, 4096, 5000)), (8192, (1, 700, 2000, 5000))])
+# rows of the block run in one of three forms by their number (the last, from 384 MB of input and output on, not where it normalises in
+# place); small integers, whose products' sums are exact, give every batch the same pre-activations, and sums in fp64 leave the statistics'
+# fp32 roundings the same
+@pytest.mark.parametrize("N,batches", [(4096, (1, 1000, 1024, 1025, 4095, 4096, 5000, 24575, 24576, 24583)), (8192, (1, 700, 2000, 12287, 12288, 12290))])
 def test_rows_of_the_block_do_not_depend_on_the_rows_beside_them(N, batches):
     g = torch.Generator(device="cuda")
     g.manual_seed(N)
@@ -100,3 +101,8 @@ def test_rows_of_the_block_do_not_depend_on_the_rows_beside_them(N, batches):
         print(f"[even rows] block {M} of {N}", flush=True)
         for got, ref in zip(run(M), most):
             assert torch.equal(got.view(torch.uint8), ref[:M].contiguous().view(torch.uint8))
+    M = max(batches)
+    Y = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
+    ws = torch.empty(max(256, api.fdl_forward_inference_workspace_bytes("bf16", M, 8, N)), dtype=torch.uint8, device="cuda")
+    api.fdl_forward_inference("bf16", X, W, b, gamma, beta, EPS, Y, ws)
+    assert torch.equal(Y.view(torch.uint8), most[0].view(torch.uint8))
