@@ -237,7 +237,7 @@ void make_grad_plan(int dt, int64_t M, int64_t K, int64_t N, Room room, bool may
   if (dt == kF32) {
     q.s64_a = split ? f64_plan(Mp, K, N) : f64_unsplit(Mp, K, N);
     q.s64_b = split ? f64_plan(N, K, Mp) : f64_unsplit(N, K, Mp);
-    q.s64_a.small = q.s64_b.small = f64_small_grads(Mp, K, N, split);
+    q.s64_a.small = q.s64_b.small = f64_small_grads(Mp, K, N, split ? &q.s64_a : nullptr, &q.s64_b);
     q.off_part64_a = *off; *off += align256(f64_part_bytes(q.s64_a));
     q.off_part64_b = *off; *off += align256(f64_part_bytes(q.s64_b));
   }

@@ -478,19 +478,19 @@ F64Split f64_plan(int64_t I, int64_t J, int64_t R) {
 // 40.6 / 48.1 (2.3), 1024 x 1024 x 1024 139 / 168.
 // Within those bounds a long reduction of few tiles is one wavefront's chain, which a split deals out (Linear+ReLU 24 x 512 x 1024, dX 16 tiles of
 // 16 steps: 35.5 split, 42.8 so).  Estimated, us: here 0.5 for each step of the longest unit or 0.74 for each of a compute unit's, 0.24 more
-// for these; split 0.7 for each slice of its longest part, 2.7 for 256 parts, 3.7 for the launch that ends it.  (Fitted to 2727 shapes of 6
-// to 16 steps, rms 1.5 us; on them, whole calls: 0.907 of the split's time on average always so, 0.906 by this rule, 204 and 90 of them more than 2 %
-// slower than split, 1.21 and 1.12 times at most.)
-bool f64_small_grads(int64_t M, int64_t K, int64_t N, bool split) {
+// for these; split 0.7 for each slice of its longest part, 2.7 for 256 parts, 4 for the launch that ends it.  (Fitted to 2727 shapes of 6
+// to 16 steps, rms 1.5 us.  On them, whole calls: 0.907 of the split's time on average always so, 0.905 by this rule; 167 and 93 more than 3 % slower
+// than split, 1.21 and 1.18 times at most, and by this rule 20 more than 3 % slower than so, 1.10 at most.)
+bool f64_small_grads(int64_t M, int64_t K, int64_t N, const F64Split* dx, const F64Split* dw) {
   const int64_t tx = small_tiles(M, K), tw = small_tiles(N, K), sx = (N + 63) / 64, sw = (M + 63) / 64;
   if (!(tx <= kF64MaxSmall && tw <= kF64MaxSmall && sx <= 16 && sw <= 16 && tx + tw <= 768 && tx * sx + tw * sw <= 16 * 256)) return false;
-  if (!split) return true;                           // (no room for a split's sums)
-  const F64Split x = f64_plan(M, K, N), w = f64_plan(N, K, M);
+  if (dx == nullptr) return true;
+  const F64Split &x = *dx, &w = *dw;
   auto part = [](const F64Split& q, int64_t R) { return (double)((R + 15) / 16) / q.split; };       // slices
   const double longest = (double)(sx > sw ? sx : sw), all = (double)(tx * sx + tw * sw) / 256.0;
   const double px = part(x, N), pw = part(w, M), parts = (x.split > 1 ? (double)x.parted * x.split : 0.0) + (w.split > 1 ? (double)w.parted * w.split : 0.0);
   const double here = (0.5 * longest > 0.74 * all ? 0.5 * longest : 0.74 * all) + 0.24 * all;
-  return here < 0.7 * (px > pw ? px : pw) + 2.7 * parts / 256.0 + 3.7 - 0.6;
+  return here < 0.7 * (px > pw ? px : pw) + 2.7 * parts / 256.0 + 4.0;
 }
 size_t f64_part_bytes(const F64Split& q) { return q.split > 1 ? (size_t)q.parted * q.split * 4096 * 8 : 0; }
 

@@ -120,7 +120,8 @@ void launch_generic_store_f32(const GemmDesc& g, float* C, hipStream_t s);
 
 // ---- fp32-storage contractions in fp64 (gemm_f64.hip): GemmDesc as above, any shape ---------------
 F64Split f64_plan(int64_t I, int64_t J, int64_t R);
-bool f64_small_grads(int64_t M, int64_t K, int64_t N, bool split);   // split: there is room for the other kernel's sums
+// dx, dw: what would run otherwise, or null: no room for its sums
+bool f64_small_grads(int64_t M, int64_t K, int64_t N, const F64Split* dx, const F64Split* dw);
 size_t f64_part_bytes(const F64Split& q);
 void launch_f64(int kind, const GemmDesc& g, const F64Split& q, const float* bias, const void* aux, void* C, void* part,
                 hipStream_t s);
